@@ -107,7 +107,7 @@ def main():
     ap.add_argument("--dual-rounds", type=int, default=1,
                     help="separation + message-passing blocks per round on the same graph (default 1: the paper's loop)")
     ap.add_argument("--cycle-search", type=int, default=0, choices=[0, 1, 2, 3],
-                    help="cycles of length 4-5: 0 = default choice, 1 = plain per-thread walk, 2 = cooperative search, 3 = walk whose last level closes from the far endpoint")
+                    help="cycles of length 4-5: 0 = default choice, 1 = plain per-thread walk, 2 = hashed search, 3 = walk whose last level closes from the far endpoint")
     ap.add_argument("--kernels", type=int, default=16, help="how many kernels the per-kernel table lists")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="first run a plain 1 GiB device copy three times (reference reading for rocprofv3 --pmc "

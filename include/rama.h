@@ -165,9 +165,10 @@ rama_status rama_set_sort_split(rama_ctx *ctx, int64_t n_min, int32_t min_passes
  *   3  the same walk, but its last level closes from vL's side as in the appendix algorithm "Parallel Conf.
  *      5-Cycles" (pairs (v1,v3) of N+(v0) x N+(vL) meeting in a common neighbour): the rows of N+(vL)'s
  *      entries are fetched once per repulsive edge and held in registers (rows of up to 8 entries);
- *   2  the cooperative search for lengths 4 and 5: sixteen lanes per repulsive edge, N+(v0), N+(vL) and
- *      the rows of N+(vL)'s entries staged in LDS (rows of up to 16 entries; edges with longer rows are
- *      walked as in 3), hits placed by ballots and prefix sums over the sixteen lanes.
+ *   2  the hashed search for lengths 4 and 5: sixteen lanes (on graphs with more than 12 attractive neighbours
+ *      per node on average: 64) per repulsive edge enter the rows of N+(vL)'s entries into a hash table in LDS
+ *      and look the second nodes of the paths from v0 up in it; what does not fit the tables is walked by a
+ *      wave per edge.
  * Searches for triangles only (max_cycle_len 3) are row intersections: by one thread per repulsive edge
  * (modes 1 and 3), or by sixteen lanes per edge that bisect the longer row for sixteen entries of the shorter
  * one at a time (mode 2).

@@ -245,8 +245,8 @@ class Rama:
         self._check(self.lib.rama_set_sort_split(self.ctx, int(n_min), int(min_passes_replaced)), "rama_set_sort_split")
 
     def set_cycle_search(self, mode):
-        """0: cooperative search for cycles of length 4-5 on graphs with short rows (default), 1: always the
-        per-thread walk, 2: always cooperative.  The lists are the same either way."""
+        """0: chosen from the sizes of the graph (default), 1: always the per-thread walk, 2: always the hashed
+        search for cycles of length 4-5, 3: the walk that closes from the far endpoint.  The lists are the same."""
         self._check(self.lib.rama_set_cycle_search(self.ctx, int(mode)), "rama_set_cycle_search")
 
     def profile_get(self):

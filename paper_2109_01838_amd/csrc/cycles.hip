@@ -320,6 +320,7 @@ __device__ __forceinline__ void walk_from_first(const Adj &g, const EndRow &end,
 constexpr size_t kListHitsFrom = size_t(1) << 17;
 constexpr int kHeavyRow = 128;
 constexpr unsigned kHeavyGroups = 512;
+constexpr unsigned kSpillGroups = 768;     // three workgroups per CU: what their LDS allows
 __device__ __forceinline__ bool heavy_edge(const Adj &g, int32_t v0, int max_len)
 {
     return max_len >= 4 && g.ptr[v0 + 1] - g.ptr[v0] > kHeavyRow;
@@ -410,22 +411,6 @@ __global__ __launch_bounds__(kBlock) void k_count_cycles(size_t nr, const int32_
 {
     const size_t r = (size_t)blockIdx.x * kBlock + threadIdx.x;
     count_edge<MAXL, MEET>(r < nr, r, ri, rj, g, max_len, flags, cnt, heavy, n_heavy, saturated);
-}
-
-// the same for the repulsive edges on a list whose length is only known on the device (fixed grid,
-// every workgroup strides over the list)
-template <int MAXL, bool MEET>
-__global__ __launch_bounds__(kBlock) void k_count_cycles_listed(const uint32_t *list, const uint32_t *n_list,
-                                                                const int32_t *ri, const int32_t *rj, Adj g, int max_len,
-                                                                int flags, ListPtrs<uint32_t, MAXL - 2> cnt,
-                                                                uint32_t *heavy, uint32_t *n_heavy, uint32_t *saturated)
-{
-    const size_t n = *n_list;
-    for (size_t base = (size_t)blockIdx.x * kBlock; base < n; base += (size_t)gridDim.x * kBlock) {
-        const size_t q = base + threadIdx.x;
-        const bool valid = q < n;
-        count_edge<MAXL, MEET>(valid, valid ? list[q] : 0, ri, rj, g, max_len, flags, cnt, heavy, n_heavy, saturated);
-    }
 }
 
 // counts of the listed heavy edges: a wave per edge, lane l takes the first hops l, l+64, ...
@@ -537,271 +522,303 @@ __global__ __launch_bounds__(kBlock) void k_fill_cycles(size_t nh, const uint32_
     fill_edge<MAXL, MEET>(hit ? hit[h] : (uint32_t)h, ri, rj, g, live, max_len, cnt, off, out);
 }
 
-template <int MAXL, bool MEET>
-__global__ __launch_bounds__(kBlock) void k_fill_cycles_listed(const uint32_t *list, const uint32_t *n_list,
-                                                               const int32_t *ri, const int32_t *rj, Adj g, int live,
-                                                               int max_len, ListPtrs<uint32_t, MAXL - 2> cnt,
-                                                               ListPtrs<uint64_t, MAXL - 2> off,
-                                                               ListPtrs<int32_t, MAXL - 2> out)
-{
-    const size_t n = *n_list;
-    for (size_t q = (size_t)blockIdx.x * kBlock + threadIdx.x; q < n; q += (size_t)gridDim.x * kBlock)
-        fill_edge<MAXL, MEET>(list[q], ri, rj, g, live, max_len, cnt, off, out);
-}
-
-// ---- cooperative search for cycles of length up to 5 ---------------------------------------------
-// The appendix algorithm "Parallel Conf. 5-Cycles" meets in the middle: for a repulsive edge (v0,vL)
-// it pairs v1 in N+(v0) with v3 in N+(vL) and intersects N+(v1) with N+(v3).  Only the rows of the two
-// endpoints and of their neighbours are touched -- 2d+2 rows instead of the d^2+d+2 rows a walk from v0
-// over three hops fetches -- and all of them can be requested at once.  Sixteen lanes share one edge:
-// they stage N+(v0), N+(vL) and the rows of N+(vL)'s entries in LDS (every lane fetches one row), then
-// take the pairs (v1, v2), v2 in N+(v1), sixteen at a time in list order; a lane tests its v2 against
-// N+(vL) (a 4-cycle) and against the staged row of every v3 (5-cycles) out of LDS.  The count kernel
-// adds the lanes' hits up; the fill kernel places them with prefix sums over the sixteen lanes, so the
-// lists come out in the same order as from the walk: (v0, vL, v1, v2, v3).
-// Edges with a row beyond the staged sizes go to a list that the walking kernels work off.
-constexpr int kCoopLanes = 16;                     // lanes per repulsive edge (one DPP row)
-constexpr int kCoopEdges = kBlock / kCoopLanes;    // edges per workgroup
-constexpr int kCoopCap = 16;                       // longest N+(v0), N+(vL) and N+(v3) that are staged
-constexpr int kCoopCapA = 64;                      // longest N+(v1) (read from memory, bounds the pairs per edge)
-struct alignas(16) CoopStage {
-    int32_t rowA[kCoopCap];                   // N+(v0)
-    int32_t rowB[kCoopCap];                   // N+(vL), -1 behind its end
-    int32_t startA[kCoopCap];                 // where the row of rowA[k] starts in the adjacency array
-    int32_t offA[kCoopCap];                   // pairs before the row of rowA[k]; the largest int behind the last row
-    int32_t rowsB[kCoopCap][kCoopCap];        // the rows of rowB[k], -1 behind their ends
+// ---- hashed search for cycles of length up to 5 --------------------------------------------------
+// The same meeting in the middle on rows that are too long for registers and for the staged rows above.  G lanes
+// share a repulsive edge.  They enter every node of the rows of N+(vL)'s entries v3 into a hash table in LDS, with
+// one bit per v3 whose row holds the node (and one more bit for the nodes of N+(vL) itself); a pair (v1, v2),
+// v2 in N+(v1), then needs one look into the table: its bits say which v3 close (v0,v1,v2,v3,vL) and whether
+// (v0,v1,v2,vL) is a cycle.  That is d^2 entries and d^2 looks per edge, where the walk makes d^3 steps that each
+// wait for a row.  What bounds the kernels: LDS latency (a look is a chain of a row search, a probe and the bits) at the
+// ten to sixteen waves per CU that the tables leave room for.
+// Edges whose rows or entries do not fit the table go to a list that a second launch works off with a table of 4096
+// places; what does not fit there either (more than 64 attractive neighbours at v0, more than 63 at vL) is heavy.
+constexpr uint32_t kNoKey = 0xffffffffu;
+constexpr uint32_t kHashPairs = 1u << 24;      // beyond that a 32-bit count could overflow
+template <int G, int SLOTS>
+struct alignas(16) HashStage {
+    static constexpr int W = G > 32 ? 2 : 1;   // words of a bit mask over N+(vL); the last bit is "in N+(vL)"
+    uint32_t key[SLOTS];
+    uint32_t mask[W][SLOTS];
+    // N+(v0); per entry the number of pairs before its row (the largest int behind the last one) and where item 0
+    // would sit in the adjacency array if the row's items were numbered from that on
+    int32_t rowA[G], offA[G], fromA[G];
+    int32_t rowB[G], offB[G], fromB[G];        // the same of N+(vL)
 };
-// what every lane of a group keeps in registers once the rows are staged: one wait for eight 16-byte
-// LDS reads instead of a wait per entry inside the loops over the pairs
-struct CoopRegs {
-    int32_t rowB[kCoopCap];
-    int32_t offA[kCoopCap];
-    __device__ __forceinline__ void load(const CoopStage &S)
-    {
-        __builtin_memcpy(rowB, S.rowB, sizeof(rowB));
-        __builtin_memcpy(offA, S.offA, sizeof(offA));
-    }
-};
-
-__device__ __forceinline__ uint32_t group_ballot(bool p)
+// LDS that one wave shares: orders what its lanes wrote before against what they read behind
+__device__ __forceinline__ void wave_lds_fence()
 {
-    return (uint32_t)(__ballot(p) >> (lane_id() & 48)) & 0xffffu;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
-__device__ __forceinline__ uint32_t group_sum(uint32_t v)
+template <int G>
+__device__ __forceinline__ uint32_t lanes_exclusive_scan(uint32_t v, uint32_t *total)
 {
+    uint32_t inc;
+    if constexpr (G == 64) {
+        inc = wave_inclusive_scan(v);
+        *total = wave_last(inc);
+    } else {
+        const int gl = (int)(threadIdx.x & (G - 1));
+        inc = v;
 #pragma unroll
-    for (int off = 8; off > 0; off >>= 1) v += (uint32_t)__shfl_xor((int)v, off, kCoopLanes);
-    return v;
-}
-// exclusive prefix over the sixteen lanes of a group; *total = the group's sum
-__device__ __forceinline__ uint32_t group_exclusive_scan(uint32_t v, uint32_t *total)
-{
-    uint32_t inc = v;
-    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xf, 0xf, false);   // row_shr:1
-    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xf, 0xf, false);   // row_shr:2
-    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xf, 0xf, false);   // row_shr:4
-    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xf, 0xf, false);   // row_shr:8
-    *total = (uint32_t)__shfl((int)inc, kCoopLanes - 1, kCoopLanes);
+        for (int off = 1; off < G; off <<= 1) {
+            const uint32_t t = (uint32_t)__shfl_up((int)inc, off, G);
+            if (gl >= off) inc += t;
+        }
+        *total = (uint32_t)__shfl((int)inc, G - 1, G);
+    }
     return inc - v;
 }
+template <int G>
+__device__ __forceinline__ uint64_t lanes_ballot(bool p)
+{
+    const uint64_t b = __ballot(p);
+    if constexpr (G == 64) return b;
+    else return (b >> (lane_id() & (64 - G))) & ((1ull << G) - 1ull);
+}
+template <int G>
+__device__ __forceinline__ uint32_t lanes_sum(uint32_t v)
+{
+#pragma unroll
+    for (int off = G / 2; off > 0; off >>= 1) v += (uint32_t)__shfl_xor((int)v, off, G);
+    return v;
+}
+template <int SLOTS>
+__device__ __forceinline__ uint32_t hash_slot(uint32_t v)
+{
+    static_assert((SLOTS & (SLOTS - 1)) == 0, "power of two");
+    return (v * 0x9E3779B1u) >> (32 - __builtin_ctz(SLOTS));
+}
+// the table is never full (hash_stage sees to that): both loops end
+template <int G, int SLOTS>
+__device__ __forceinline__ uint32_t hash_enter(HashStage<G, SLOTS> &S, uint32_t v)
+{
+    uint32_t h = hash_slot<SLOTS>(v);
+    for (;;) {
+        const uint32_t old = atomicCAS(&S.key[h], kNoKey, v);
+        if (old == kNoKey || old == v) return h;
+        h = (h + 1) & (SLOTS - 1);
+    }
+}
+template <int G, int SLOTS>
+__device__ __forceinline__ uint64_t hash_look(const HashStage<G, SLOTS> &S, uint32_t v)
+{
+    uint32_t h = hash_slot<SLOTS>(v);
+    for (;;) {
+        const uint32_t k = S.key[h];
+        if (k == v) break;
+        if (k == kNoKey) return 0ull;
+        h = (h + 1) & (SLOTS - 1);
+    }
+    uint64_t m = S.mask[0][h];
+    if constexpr (HashStage<G, SLOTS>::W == 2) m |= (uint64_t)S.mask[1][h] << 32;
+    return m;
+}
+// the last k with off[k] <= w (off ascends, entries behind the last row hold the largest int)
+template <int G>
+__device__ __forceinline__ int row_of(const int32_t *off, int32_t w)
+{
+    int k = 0;
+#pragma unroll
+    for (int step = G / 2; step > 0; step >>= 1)
+        if (off[k + step] <= w) k += step;
+    return k;
+}
 
-// what a group knows about its edge after staging
-struct CoopEdge {
+struct HashEdge {
     int32_t v0, vl;
     int dA, dB;
     uint32_t pairs;     // number of (v1, v2) pairs
     int32_t my_v1;      // lane k < dA: rowA[k]
     bool live;          // the edge is searched here (valid, both rows non-empty, everything fits)
-    bool spilled;       // a row is too long: the walking kernels take this edge
+    bool spilled;       // it does not fit
 };
 
-// stages the rows of edge (v0, vl) for the calling group; the caller synchronises the workgroup afterwards
-__device__ __forceinline__ CoopEdge coop_stage(CoopStage &S, bool valid, int32_t v0, int32_t vl, const Adj &g, int max_len)
+template <int G, int SLOTS>
+__device__ __forceinline__ HashEdge hash_stage(HashStage<G, SLOTS> &S, bool valid, int32_t v0, int32_t vl, const Adj &g, int max_len)
 {
-    const int gl = (int)(threadIdx.x & (kCoopLanes - 1));
-    CoopEdge E;
+    constexpr int W = HashStage<G, SLOTS>::W;
+    constexpr int kFlag = G > 32 ? 31 : G - 1;   // bit of the last mask word: in N+(vL)
+    const int gl = (int)(threadIdx.x & (G - 1));
+    HashEdge E;
     E.v0 = v0; E.vl = vl; E.my_v1 = -1; E.pairs = 0;
     int32_t pa0 = 0, pa1 = 0, pb0 = 0, pb1 = 0;
     if (valid) { pa0 = g.ptr[v0]; pa1 = g.ptr[v0 + 1]; pb0 = g.ptr[vl]; pb1 = g.ptr[vl + 1]; }
     E.dA = pa1 - pa0; E.dB = pb1 - pb0;
-    const bool fits = E.dA <= kCoopCap && E.dB <= kCoopCap;
     const bool search = valid && E.dA > 0 && E.dB > 0;
-    bool too_long = false;
-    uint32_t lenA = 0;
+    const bool fits = E.dA <= G && E.dB <= G - 1;
+    int32_t startA = 0, startB = 0, v3 = -1;
+    uint32_t lenA = 0, lenB = 0;
     if (search && fits) {
         if (gl < E.dA) {
-            const int32_t v1 = g.nb[pa0 + gl];
-            const int32_t q0 = g.ptr[v1];
-            lenA = (uint32_t)(g.ptr[v1 + 1] - q0);
-            S.rowA[gl] = v1; S.startA[gl] = q0;
-            E.my_v1 = v1;
-            too_long |= lenA > (uint32_t)kCoopCapA;
+            E.my_v1 = g.nb[pa0 + gl];
+            startA = g.ptr[E.my_v1];
+            lenA = (uint32_t)(g.ptr[E.my_v1 + 1] - startA);
         }
-        S.rowB[gl] = -1;
         if (gl < E.dB) {
-            const int32_t v3 = g.nb[pb0 + gl];
-            S.rowB[gl] = v3;
+            v3 = g.nb[pb0 + gl];
             if (max_len >= 5) {
-                const int32_t s0 = g.ptr[v3];
-                const int32_t lb = g.ptr[v3 + 1] - s0;
-                if (lb > kCoopCap) {
-                    too_long = true;
-                } else {
-                    // the whole row with four 16-byte loads (the array is padded; what lies behind the row's end becomes -1)
-                    int32_t row[kCoopCap];
-                    __builtin_memcpy(row, g.nb + s0, sizeof(row));
-#pragma unroll
-                    for (int q = 0; q < kCoopCap; ++q) row[q] = q < lb ? row[q] : -1;
-                    __builtin_memcpy(S.rowsB[gl], row, sizeof(row));
-                }
+                startB = g.ptr[v3];
+                lenB = (uint32_t)(g.ptr[v3 + 1] - startB);
             }
         }
     }
-    E.spilled = search && (!fits || group_ballot(too_long) != 0);
+    // a heavy row among N+(v0)'s entries is no trouble here (its pairs are only looked up), one among N+(vL)'s does not fit
+    uint32_t entries;
+    const uint32_t beforeA = lanes_exclusive_scan<G>(lenA, &E.pairs), beforeB = lanes_exclusive_scan<G>(lenB, &entries);
+    E.spilled = search && (!fits || entries + (uint32_t)E.dB > (uint32_t)(SLOTS / 8 * 7) || E.pairs > kHashPairs);
     E.live = search && !E.spilled;
-    const uint32_t excl = group_exclusive_scan(E.live ? lenA : 0u, &E.pairs);
-    S.offA[gl] = gl < E.dA ? (int32_t)excl : 0x7fffffff;
+    if (!E.live) return E;
+    wave_lds_fence();      // the stage may still be in use for the edge before this one
+    S.rowA[gl] = E.my_v1; S.fromA[gl] = startA - (int32_t)beforeA; S.offA[gl] = gl < E.dA ? (int32_t)beforeA : 0x7fffffff;
+    S.rowB[gl] = v3; S.fromB[gl] = startB - (int32_t)beforeB; S.offB[gl] = gl < E.dB ? (int32_t)beforeB : 0x7fffffff;
+    for (int k = gl * 4; k < SLOTS; k += G * 4) {
+        *reinterpret_cast<uint4 *>(&S.key[k]) = make_uint4(kNoKey, kNoKey, kNoKey, kNoKey);
+#pragma unroll
+        for (int q = 0; q < W; ++q) *reinterpret_cast<uint4 *>(&S.mask[q][k]) = make_uint4(0, 0, 0, 0);
+    }
+    wave_lds_fence();
+    if (v3 >= 0) atomicOr(&S.mask[W - 1][hash_enter(S, (uint32_t)v3)], 1u << kFlag);
+    for (uint32_t w = (uint32_t)gl; w < entries; w += G) {
+        const int b = row_of<G>(S.offB, (int32_t)w);
+        const int32_t v2 = g.nb[S.fromB[b] + (int32_t)w];
+        if (v2 == v0 || v2 == vl) continue;
+        atomicOr(&S.mask[W == 2 ? b >> 5 : 0][hash_enter(S, (uint32_t)v2)], 1u << (b & 31));
+    }
+    wave_lds_fence();
     return E;
 }
 
-// pair number w of the staged edge: v1, v2, whether (v0,v1,v2,vl) is a cycle, and -- as a bit mask over
-// N+(vL) -- which v3 close the 5-cycle (v0,v1,v2,v3,vl)
-__device__ __forceinline__ void coop_pair(const CoopStage &S, const CoopRegs &R, const CoopEdge &E, const Adj &g, uint32_t w,
-                                          int max_len, int32_t &v1, int32_t &v2, bool &four, uint32_t &fives)
+// what the table says about pair number w: v1, v2, whether (v0,v1,v2,vl) is a cycle, which v3 close a 5-cycle
+template <int G, int SLOTS>
+__device__ __forceinline__ void hash_pair(const HashStage<G, SLOTS> &S, const HashEdge &E, const Adj &g, uint32_t w, int32_t &v1,
+                                          int32_t &v2, bool &four, uint64_t &fives)
 {
-    int a = 0;
-#pragma unroll
-    for (int k = 1; k < kCoopCap; ++k) a += (R.offA[k] <= (int32_t)w);   // the last row that starts at or before w
+    constexpr uint64_t kFlagBit = 1ull << (G - 1);
+    const int a = row_of<G>(S.offA, (int32_t)w);
     v1 = S.rowA[a];
-    v2 = g.nb[S.startA[a] + ((int32_t)w - S.offA[a])];
-    four = false;
-#pragma unroll
-    for (int b = 0; b < kCoopCap; ++b) four |= (R.rowB[b] == v2);
-    fives = 0;
-    if (max_len >= 5 && v2 != E.v0 && v2 != E.vl) {
-#pragma unroll
-        for (int b = 0; b < kCoopCap; ++b) {
-            if (b < E.dB && R.rowB[b] != v1) {
-                int32_t row[kCoopCap];
-                __builtin_memcpy(row, S.rowsB[b], sizeof(row));
-                bool hit = false;
-#pragma unroll
-                for (int q = 0; q < kCoopCap; ++q) hit |= (row[q] == v2);
-                fives |= hit ? (1u << b) : 0u;
+    v2 = g.nb[S.fromA[a] + (int32_t)w];
+    const uint64_t m = hash_look(S, (uint32_t)v2);     // v0 and vl are not in the table
+    four = (m & kFlagBit) != 0;
+    fives = m & ~kFlagBit;
+    if (fives) {            // v3 == v1 is no cycle; it can only be among the bits when v1 is in N+(vL)
+        const uint64_t m1 = hash_look(S, (uint32_t)v1);
+        if (m1 & kFlagBit) {
+            int lo = 0, hi = E.dB;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (S.rowB[mid] < v1) lo = mid + 1; else hi = mid;
             }
+            fives &= ~(1ull << lo);
         }
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_count_cycles_coop(size_t nr, const int32_t *ri, const int32_t *rj, Adj g,
-                                                              int max_len, int shortest_only, ListPtrs<uint32_t, 3> cnt,
-                                                              uint32_t *spill, uint32_t *n_spill)
+template <int G>
+struct HashBlock {      // edges per workgroup of the kernels below: one wave, or 256 threads of narrower groups
+    static constexpr int threads = G == 64 ? 64 : kBlock;
+    static constexpr int edges = threads / G;
+};
+
+// `list` (optional): the edges to search, *n_list of them; else the edges 0..nr-1.  Edges that do not fit go to `spill`.
+template <int G, int SLOTS>
+__global__ __launch_bounds__(HashBlock<G>::threads) void k_count_cycles_hash(size_t nr, const uint32_t *list, const uint32_t *n_list,
+                                                                           const int32_t *ri, const int32_t *rj, Adj g, int max_len,
+                                                                           int shortest_only, ListPtrs<uint32_t, 3> cnt,
+                                                                           uint32_t *spill, uint32_t *n_spill)
 {
-    __shared__ CoopStage stage[kCoopEdges];
-    const int gl = (int)(threadIdx.x & (kCoopLanes - 1)), grp = (int)(threadIdx.x / kCoopLanes);
-    CoopStage &S = stage[grp];
-    const size_t r = (size_t)blockIdx.x * kCoopEdges + grp;
-    const bool valid = r < nr;
-    const CoopEdge E = coop_stage(S, valid, valid ? ri[r] : 0, valid ? rj[r] : 0, g, max_len);
-    __syncthreads();
-    uint32_t n3 = 0, n4 = 0, n5 = 0;
-    if (E.live) {
-        CoopRegs R;
-        R.load(S);
-        if (gl < E.dA) {
-            bool hit = false;
-#pragma unroll
-            for (int b = 0; b < kCoopCap; ++b) hit |= (R.rowB[b] == E.my_v1);
-            n3 = hit ? 1u : 0u;
+    constexpr int kEdges = HashBlock<G>::edges;
+    __shared__ HashStage<G, SLOTS> stage[kEdges];
+    const int gl = (int)(threadIdx.x & (G - 1)), grp = (int)(threadIdx.x / G);
+    HashStage<G, SLOTS> &S = stage[grp];
+    const size_t n = list ? (size_t)*n_list : nr;
+    for (size_t h = (size_t)blockIdx.x * kEdges + grp; h < n; h += (size_t)gridDim.x * kEdges) {
+        const size_t r = list ? (size_t)list[h] : h;
+        const HashEdge E = hash_stage(S, true, ri[r], rj[r], g, max_len);
+        uint32_t n3 = 0, n4 = 0, n5 = 0;
+        if (E.live) {
+            if (E.my_v1 >= 0) n3 = (uint32_t)(hash_look(S, (uint32_t)E.my_v1) >> (G - 1)) & 1u;
+            for (uint32_t w = (uint32_t)gl; w < E.pairs; w += G) {
+                int32_t v1, v2;
+                bool four;
+                uint64_t fives;
+                hash_pair(S, E, g, w, v1, v2, four, fives);
+                n4 += four ? 1u : 0u;
+                n5 += (uint32_t)__popcll(fives);
+            }
         }
-        for (uint32_t w = (uint32_t)gl; w < E.pairs; w += kCoopLanes) {
-            int32_t v1, v2;
-            bool four;
-            uint32_t fives;
-            coop_pair(S, R, E, g, w, max_len, v1, v2, four, fives);
-            n4 += four ? 1u : 0u;
-            n5 += (uint32_t)__popc(fives);
+        n3 = lanes_sum<G>(n3); n4 = lanes_sum<G>(n4); n5 = lanes_sum<G>(n5);
+        if (shortest_only) {   // only the shortest length that closes a cycle is kept
+            if (n3) { n4 = 0; n5 = 0; }
+            else if (n4) n5 = 0;
         }
-    }
-    n3 = group_sum(n3); n4 = group_sum(n4); n5 = group_sum(n5);
-    if (shortest_only) {   // only the shortest length that closes a cycle is kept
-        if (n3) { n4 = 0; n5 = 0; }
-        else if (n4) n5 = 0;
-    }
-    if (valid && gl == 0) {
-        cnt.p[0][r] = n3;
-        if (max_len >= 4) cnt.p[1][r] = n4;
-        if (max_len >= 5) cnt.p[2][r] = n5;
-        if (E.spilled) spill[atomicAdd(n_spill, 1u)] = (uint32_t)r;   // counted again by the walking kernel
+        if (gl == 0) {
+            cnt.p[0][r] = n3;
+            if (max_len >= 4) cnt.p[1][r] = n4;
+            if (max_len >= 5) cnt.p[2][r] = n5;
+            if (E.spilled) spill[atomicAdd(n_spill, 1u)] = (uint32_t)r;   // counted again by the kernel behind this one
+        }
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_fill_cycles_coop(size_t nh, const uint32_t *hit, const int32_t *ri,
-                                                             const int32_t *rj, Adj g, int max_len, int live,
-                                                             ListPtrs<uint32_t, 3> cnt, ListPtrs<uint64_t, 3> off,
-                                                             ListPtrs<int32_t, 3> out)
+// writes the cycles of the edges that fit at the places the scans of the counts gave them
+template <int G, int SLOTS>
+__global__ __launch_bounds__(HashBlock<G>::threads) void k_fill_cycles_hash(size_t nh, const uint32_t *list, const uint32_t *n_list,
+                                                                          const int32_t *ri, const int32_t *rj, Adj g, int max_len,
+                                                                          int live, ListPtrs<uint32_t, 3> cnt,
+                                                                          ListPtrs<uint64_t, 3> off, ListPtrs<int32_t, 3> out)
 {
-    __shared__ CoopStage stage[kCoopEdges];
-    const int gl = (int)(threadIdx.x & (kCoopLanes - 1)), grp = (int)(threadIdx.x / kCoopLanes);
-    CoopStage &S = stage[grp];
-    const size_t h = (size_t)blockIdx.x * kCoopEdges + grp;
-    bool valid = h < nh;
-    const uint32_t r = valid ? (hit ? hit[h] : (uint32_t)h) : 0u;
-    if (valid && !hit) {   // no list of the edges with cycles was made: look at the counts first
-        uint32_t any = 0;   // `live`: bit k set iff list k holds any cycle at all
-        if (live & 1) any |= cnt.p[0][r];
-        if (live & 2) any |= cnt.p[1][r];
-        if (live & 4) any |= cnt.p[2][r];
-        valid = any != 0;
-    }
-    const CoopEdge E = coop_stage(S, valid, valid ? ri[r] : 0, valid ? rj[r] : 0, g, max_len);
-    __syncthreads();
-    if (!E.live) return;   // nothing to search, or written by the walking kernels; the whole group leaves
-    // a list is written iff the count pass kept cycles of that length (with shortest_only: one length only)
-    const bool want3 = (live & 1) && cnt.p[0][r] != 0;
-    const bool want4 = (live & 2) && cnt.p[1][r] != 0;
-    const bool want5 = (live & 4) && cnt.p[2][r] != 0;
-    CoopRegs R;
-    R.load(S);
-    if (want3) {
-        bool c3 = false;
-        if (gl < E.dA) {
-#pragma unroll
-            for (int b = 0; b < kCoopCap; ++b) c3 |= (R.rowB[b] == E.my_v1);
-        }
-        const uint32_t vote = group_ballot(c3);
-        if (c3) {
-            int32_t *o = out.p[0] + 3 * (off.p[0][r] + (uint64_t)__popc(vote & ((1u << gl) - 1u)));
-            o[0] = E.v0; o[1] = E.my_v1; o[2] = E.vl;
-        }
-    }
-    if (!want4 && !want5) return;
-    uint64_t at4 = want4 ? off.p[1][r] : 0, at5 = want5 ? off.p[2][r] : 0;
-    for (uint32_t base = 0; base < E.pairs; base += kCoopLanes) {   // the same number of turns for every lane of the group
-        const uint32_t w = base + (uint32_t)gl;
-        int32_t v1 = 0, v2 = 0;
-        bool four = false;
-        uint32_t fives = 0;
-        if (w < E.pairs) coop_pair(S, R, E, g, w, max_len, v1, v2, four, fives);
-        if (want4) {
-            const uint32_t vote = group_ballot(four);
-            if (four) {
-                int32_t *o = out.p[1] + 4 * (at4 + (uint64_t)__popc(vote & ((1u << gl) - 1u)));
-                o[0] = E.v0; o[1] = v1; o[2] = v2; o[3] = E.vl;
+    constexpr int kEdges = HashBlock<G>::edges;
+    __shared__ HashStage<G, SLOTS> stage[kEdges];
+    const int gl = (int)(threadIdx.x & (G - 1)), grp = (int)(threadIdx.x / G);
+    HashStage<G, SLOTS> &S = stage[grp];
+    const uint64_t below = (1ull << gl) - 1ull;
+    const size_t n = n_list ? (size_t)*n_list : nh;
+    for (size_t h = (size_t)blockIdx.x * kEdges + grp; h < n; h += (size_t)gridDim.x * kEdges) {
+        const uint32_t r = list ? list[h] : (uint32_t)h;
+        // a list is written iff the count pass kept cycles of that length (with shortest_only: one length only);
+        // `live`: bit k set iff list k holds any cycle at all
+        const bool want3 = (live & 1) && cnt.p[0][r] != 0;
+        const bool want4 = (live & 2) && cnt.p[1][r] != 0;
+        const bool want5 = (live & 4) && cnt.p[2][r] != 0;
+        const HashEdge E = hash_stage(S, want3 || want4 || want5, ri[r], rj[r], g, want5 ? max_len : 4);
+        if (!E.live) continue;     // nothing to write, or written by the kernels behind this one; the whole group goes on
+        if (want3) {
+            const bool c3 = E.my_v1 >= 0 && ((hash_look(S, (uint32_t)E.my_v1) >> (G - 1)) & 1ull);
+            const uint64_t vote = lanes_ballot<G>(c3);
+            if (c3) {
+                int32_t *o = out.p[0] + 3 * (off.p[0][r] + (uint64_t)__popcll(vote & below));
+                o[0] = E.v0; o[1] = E.my_v1; o[2] = E.vl;
             }
-            at4 += (uint64_t)__popc(vote);
         }
-        if (want5) {
-            uint32_t total;
-            const uint32_t before = group_exclusive_scan((uint32_t)__popc(fives), &total);
-            int32_t *o = out.p[2] + 5 * (at5 + before);
-            while (fives) {
-                const int b = __ffs((int)fives) - 1;
-                fives &= fives - 1;
-                o[0] = E.v0; o[1] = v1; o[2] = v2; o[3] = S.rowB[b]; o[4] = E.vl;
-                o += 5;
+        if (!want4 && !want5) continue;
+        uint64_t at4 = want4 ? off.p[1][r] : 0, at5 = want5 ? off.p[2][r] : 0;
+        for (uint32_t base = 0; base < E.pairs; base += G) {   // the same number of turns for every lane of the group
+            const uint32_t w = base + (uint32_t)gl;
+            int32_t v1 = 0, v2 = 0;
+            bool four = false;
+            uint64_t fives = 0;
+            if (w < E.pairs) hash_pair(S, E, g, w, v1, v2, four, fives);
+            if (want4) {
+                const uint64_t vote = lanes_ballot<G>(four);
+                if (four) {
+                    int32_t *o = out.p[1] + 4 * (at4 + (uint64_t)__popcll(vote & below));
+                    o[0] = E.v0; o[1] = v1; o[2] = v2; o[3] = E.vl;
+                }
+                at4 += (uint64_t)__popcll(vote);
             }
-            at5 += total;
+            if (want5) {
+                uint32_t total;
+                const uint32_t before = lanes_exclusive_scan<G>((uint32_t)__popcll(fives), &total);
+                int32_t *o = out.p[2] + 5 * (at5 + before);
+                while (fives) {
+                    const int b = __ffsll((long long)fives) - 1;
+                    fives &= fives - 1;
+                    o[0] = E.v0; o[1] = v1; o[2] = v2; o[3] = S.rowB[b]; o[4] = E.vl;
+                    o += 5;
+                }
+                at5 += total;
+            }
         }
     }
 }
@@ -812,13 +829,15 @@ __global__ __launch_bounds__(kBlock) void k_fill_cycles_coop(size_t nh, const ui
 // entry.  Here sixteen lanes share the edge: they take the shorter row sixteen entries at a time, every lane
 // bisects the longer row for its entry, and a ballot counts -- or, in the fill pass, places -- the common
 // neighbours.  The shorter row is ascending, so the triangles (v0, v1, vL) come out in list order.
+constexpr int kTriLanes = 16;                    // lanes per repulsive edge (one DPP row)
+constexpr int kTriEdges = kBlock / kTriLanes;    // edges per workgroup
 template <bool FILL>
 __global__ __launch_bounds__(kBlock) void k_triangles_group(size_t nr, const uint32_t *hit, const int32_t *ri,
                                                             const int32_t *rj, Adj g, uint32_t *cnt0, const uint64_t *off0,
                                                             int32_t *out0)
 {
-    const int gl = (int)(threadIdx.x & (kCoopLanes - 1));
-    const size_t h = (size_t)blockIdx.x * kCoopEdges + threadIdx.x / kCoopLanes;
+    const int gl = (int)(threadIdx.x & (kTriLanes - 1));
+    const size_t h = (size_t)blockIdx.x * kTriEdges + threadIdx.x / kTriLanes;
     if (h >= nr) return;                                   // the whole group
     const uint32_t r = hit ? hit[h] : (uint32_t)h;
     if (FILL && cnt0[r] == 0) return;
@@ -828,7 +847,7 @@ __global__ __launch_bounds__(kBlock) void k_triangles_group(size_t nr, const uin
     uint32_t found = 0;
     uint64_t at = FILL ? off0[r] : 0;
     if (b0 < b1)
-        for (int32_t base = a0; base < a1; base += kCoopLanes) {   // the same number of turns for every lane of the group
+        for (int32_t base = a0; base < a1; base += kTriLanes) {   // the same number of turns for every lane of the group
             const int32_t p = base + gl;
             bool common = false;
             int32_t x = 0;
@@ -841,7 +860,7 @@ __global__ __launch_bounds__(kBlock) void k_triangles_group(size_t nr, const uin
                 }
                 common = lo < b1 && g.nb[lo] == x;
             }
-            const uint32_t vote = group_ballot(common);
+            const uint32_t vote = (uint32_t)lanes_ballot<kTriLanes>(common);
             if (FILL) {
                 if (common) {
                     int32_t *o = out0 + 3 * (at + (uint64_t)__popc(vote & ((1u << gl) - 1u)));
@@ -924,25 +943,24 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
         RAMA_TRY(off[k].alloc(ctx, mr + 1));
         cp.p[k] = cnt[k].get(); op.p[k] = off[k].get();
     }
-    // heavy edges (only possible for max_len >= 4): listed by the first kernel, counted by the second,
-    // which ends at once when the list is empty
+    // heavy edges (only possible for max_len >= 4): listed by the kernels in front, counted by a wave each in a kernel
+    // that ends at once when the list is empty
     const bool may_be_heavy = max_len >= 4;
-    // Lengths 4 and 5.  If every attractive row has at most kRowRegs entries (3-D grids), the walk holds the
-    // rows it needs in registers and is the fastest; if rows are longer but still short on average (2-D
-    // grids with long-range edges, neighbour graphs), the cooperative search stages them in LDS, and what
-    // does not fit its staged sizes is listed and walked; with long rows on average (contracted graphs)
-    // everything is walked.  Measured on the 320^3 grid (rows <= 6): walk 4.4 ms, cooperative 12.0 ms; on
-    // the 512^2 grid with long-range edges (rows <= 12): 4.0 against 1.0 ms; on the 6-nearest-neighbour
-    // graph of 10^6 points (rows of 3..15): 1.5 against 0.55 ms.
-    bool coop = false;
-    if constexpr (MAXL == 5) {
-        const bool short_on_average = 2 * mp <= (size_t)12 * (size_t)n;
-        const bool fit_registers = longest_row <= (uint32_t)kRowRegs;
-        coop = max_len >= 4 && (ctx.cycle_search == 2 || (ctx.cycle_search == 0 && short_on_average && !fit_registers));
-    }
-    Buf<uint32_t> heavy, spill, n_heavy;   // n_heavy[0]: length of the heavy list, [1]: a count saturated, [2]: length of the spill list
+    // Lengths 4 and 5.  If every attractive row has at most kRowRegs entries (3-D grids), the walk holds the rows it
+    // needs in registers and is the fastest: 4.4 ms against 4.8 for the hashed search (eight lanes per edge) on the
+    // 320^3 grid (rows <= 6, 3.1e7 repulsive edges).  Otherwise the hashed search: sixteen lanes per edge while rows hold
+    // up to twelve entries on average, a wave per edge beyond.  Measured (count pass, ms): 512^2 grid with long-range
+    // edges (rows <= 12) 0.30 with sixteen lanes, 0.38 with 32, 0.75 with 64, 3.9 for the walk; 6-nearest-neighbour graph
+    // of 10^6 points (rows of 3..15) 0.40, 0.56, 1.16, walk 1.27; a 180x181 long-range grid after one dual round
+    // (rows of 16 on average, up to 43; 8e4 repulsive edges) 0.23 with 64 lanes, walk 21.
+    bool hashed = false;
+    const bool wide = 2 * mp > (size_t)12 * (size_t)n;
+    if constexpr (MAXL == 5)
+        hashed = max_len >= 4 && (ctx.cycle_search == 2 || (ctx.cycle_search == 0 && longest_row > (uint32_t)kRowRegs));
+    Buf<uint32_t> heavy, spill, n_heavy;   // n_heavy[0]: length of the heavy list, [1]: a count saturated, [2]: length of the
+                                           // list of edges that take the large hash table
     RAMA_TRY(heavy.alloc(ctx, may_be_heavy ? mr : 1));
-    RAMA_TRY(spill.alloc(ctx, coop ? mr : 1));
+    RAMA_TRY(spill.alloc(ctx, hashed ? mr : 1));
     RAMA_TRY(zeroed<uint32_t>(ctx, 3, n_heavy));
     // mode 1 is the walk that fetches a row per path at its last level, kept for comparison; walks of at
     // most three nodes have no such level
@@ -950,17 +968,19 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     const int walk_flags = shortest_only ? 1 : 0;
     const double search_bytes = (double)(mr * (8 + 4 * (size_t)lists) + ((size_t)n + 1) * 4 + mp * 8);
     if constexpr (MAXL == 5) {
-        if (coop) {
-            {
-                ProfScope ps_(ctx, "k_count_cycles_coop", search_bytes);
-                k_count_cycles_coop<<<grid_for(mr, kCoopEdges), kBlock, 0, ctx.stream>>>(mr, ri, rj, adj, max_len, shortest_only ? 1 : 0,
-                                                                                      cp, spill.get(), n_heavy.get() + 2);
-            }
-            LAUNCH_TRY(ctx, "count_cycles_coop");
-            ProfScope ps_(ctx, "k_count_cycles_listed", 0.0);
-            k_count_cycles_listed<MAXL, true><<<kHeavyGroups, kBlock, 0, ctx.stream>>>(spill.get(), n_heavy.get() + 2, ri, rj, adj, max_len,
-                                                                                     walk_flags, cp, heavy.get(), n_heavy.get(),
-                                                                                     n_heavy.get() + 1);
+        if (hashed) {
+            auto count = [&](auto lanes, auto slots, size_t edges, const uint32_t *list, const uint32_t *n_list, uint32_t *spill_to, uint32_t *n_spill) {
+                constexpr int G = decltype(lanes)::value, S = decltype(slots)::value;
+                ProfScope ps_(ctx, "k_count_cycles_hash", list ? 0.0 : search_bytes);
+                k_count_cycles_hash<G, S><<<grid_for(edges, HashBlock<G>::edges), HashBlock<G>::threads, 0, ctx.stream>>>(
+                    mr, list, n_list, ri, rj, adj, max_len, shortest_only ? 1 : 0, cp, spill_to, n_spill);
+            };
+            using std::integral_constant;
+            if (wide) count(integral_constant<int, 64>{}, integral_constant<int, 1024>{}, mr, nullptr, nullptr, spill.get(), n_heavy.get() + 2);
+            else count(integral_constant<int, 16>{}, integral_constant<int, 256>{}, mr, nullptr, nullptr, spill.get(), n_heavy.get() + 2);
+            LAUNCH_TRY(ctx, "count_cycles_hash");
+            count(integral_constant<int, 64>{}, integral_constant<int, 4096>{}, kSpillGroups, spill.get(), n_heavy.get() + 2, heavy.get(), n_heavy.get());
+            LAUNCH_TRY(ctx, "count_cycles_hash");
         }
     }
     // triangles only, rows of more than 12 attractive neighbours on average: sixteen lanes per repulsive edge
@@ -969,9 +989,9 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
         wide3 = ctx.cycle_search == 2 || (ctx.cycle_search == 0 && 2 * mp > (size_t)12 * (size_t)n);
     if (wide3) {
         ProfScope ps_(ctx, "k_count_triangles_group", search_bytes);
-        k_triangles_group<false><<<grid_for(mr, kCoopEdges), kBlock, 0, ctx.stream>>>(mr, (const uint32_t *)nullptr, ri, rj, adj, cp.p[0],
+        k_triangles_group<false><<<grid_for(mr, kTriEdges), kBlock, 0, ctx.stream>>>(mr, (const uint32_t *)nullptr, ri, rj, adj, cp.p[0],
                                                                                    (const uint64_t *)nullptr, (int32_t *)nullptr);
-    } else if (!coop) {
+    } else if (!hashed) {
         ProfScope ps_(ctx, MAXL == 3 ? "k_count_cycles<3>" : MAXL == 5 ? "k_count_cycles<5>" : "k_count_cycles<7>", search_bytes);
         if (meet)
             k_count_cycles<MAXL, (MAXL >= 5)><<<grid_for(mr), kBlock, 0, ctx.stream>>>(mr, ri, rj, adj, max_len, walk_flags, cp,
@@ -1031,28 +1051,30 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
         RAMA_TRY((scan_emit<uint32_t>(ctx, has, CollectHitsEmit{hit.get()}, hits, (double)((size_t)nh * 4))));
     }
     const double fill_bytes = (double)((size_t)nh * (12 + 12 * (size_t)lists) + ((size_t)n + 1) * 4 + mp * 8) + list_bytes;
-    // without 5-cycles (bipartite inputs) the fill only has to go two hops deep: the walk does that with
-    // one row per first hop and needs nothing staged
     bool long_cycles = false;   // is there any cycle of length 5 or more to write?
     for (int k = 2; k < lists; ++k) long_cycles |= tot[k] != 0;
-    if (!long_cycles) coop = false;
     if constexpr (MAXL == 5) {
-        if (coop) {
-            {
-                ProfScope ps_(ctx, "k_fill_cycles_coop", fill_bytes);
-                k_fill_cycles_coop<<<grid_for(nh, kCoopEdges), kBlock, 0, ctx.stream>>>(nh, list_hits ? hit.get() : nullptr, ri, rj, adj, max_len, live, cp, op, vp);
-            }
-            LAUNCH_TRY(ctx, "fill_cycles_coop");
-            ProfScope ps_(ctx, "k_fill_cycles_listed", 0.0);
-            k_fill_cycles_listed<MAXL, true><<<kHeavyGroups, kBlock, 0, ctx.stream>>>(spill.get(), n_heavy.get() + 2, ri, rj, adj, live,
-                                                                                    max_len, cp, op, vp);
+        if (hashed) {
+            auto write = [&](auto lanes, auto slots, size_t edges, const uint32_t *list, const uint32_t *n_list) {
+                constexpr int G = decltype(lanes)::value, S = decltype(slots)::value;
+                ProfScope ps_(ctx, "k_fill_cycles_hash", n_list ? 0.0 : fill_bytes);
+                k_fill_cycles_hash<G, S><<<grid_for(edges, HashBlock<G>::edges), HashBlock<G>::threads, 0, ctx.stream>>>(
+                    nh, list, n_list, ri, rj, adj, max_len, live, cp, op, vp);
+            };
+            using std::integral_constant;
+            const uint32_t *hits = list_hits ? hit.get() : nullptr;
+            if (wide) write(integral_constant<int, 64>{}, integral_constant<int, 1024>{}, nh, hits, nullptr);
+            else write(integral_constant<int, 16>{}, integral_constant<int, 256>{}, nh, hits, nullptr);
+            LAUNCH_TRY(ctx, "fill_cycles_hash");
+            write(integral_constant<int, 64>{}, integral_constant<int, 4096>{}, kSpillGroups, spill.get(), n_heavy.get() + 2);
+            LAUNCH_TRY(ctx, "fill_cycles_hash");
         }
     }
     if (wide3) {
         ProfScope ps_(ctx, "k_fill_triangles_group", fill_bytes);
-        k_triangles_group<true><<<grid_for(nh, kCoopEdges), kBlock, 0, ctx.stream>>>(nh, list_hits ? hit.get() : nullptr, ri, rj, adj, cp.p[0],
+        k_triangles_group<true><<<grid_for(nh, kTriEdges), kBlock, 0, ctx.stream>>>(nh, list_hits ? hit.get() : nullptr, ri, rj, adj, cp.p[0],
                                                                                   op.p[0], vp.p[0]);
-    } else if (!coop) {
+    } else if (!hashed) {
         ProfScope ps_(ctx, MAXL == 3 ? "k_fill_cycles<3>" : MAXL == 5 ? "k_fill_cycles<5>" : "k_fill_cycles<7>", fill_bytes);
         if (meet && long_cycles)
             k_fill_cycles<MAXL, (MAXL >= 5)><<<grid_for(nh), kBlock, 0, ctx.stream>>>(nh, list_hits ? hit.get() : nullptr, ri, rj, adj, live, max_len, cp, op, vp);

@@ -86,6 +86,45 @@ def test_cycles_bit_exact(rama, oracle32, name, lmax, search_mode):
         assert np.array_equal(np_(got[L]), want[L]), (name, lmax, L + 3, got[L].shape, want[L].shape)
 
 
+def fan_graph(d_a, d_b, row, isolated, seed=0):
+    """One repulsive edge (0, last) between a node with d_a and a node with d_b attractive neighbours, three of them
+    shared; every neighbour has `row` more attractive neighbours among 300 middle nodes, some of which are the other
+    side's neighbours.  `isolated` further nodes bring the average row down."""
+    rng = np.random.default_rng(seed)
+    side_a = np.arange(1, 1 + d_a)
+    side_b = np.concatenate([side_a[:3], np.arange(1 + d_a, 1 + d_a + d_b)])[:d_b]
+    last = 1 + d_a + d_b + 300 + isolated
+    middle = np.arange(1 + d_a + d_b, 301 + d_a + d_b)
+    edges = [(0, x) for x in side_a] + [(x, last) for x in side_b]
+    for x in np.unique(np.concatenate([side_a, side_b])):
+        edges += [(x, y) for y in rng.choice(middle, row, replace=False)]
+    edges += [(x, y) for x in side_a[:5] for y in side_b[-5:] if x != y]
+    key = np.unique([min(e) * (last + 1) + max(e) for e in edges])
+    i = np.concatenate([key // (last + 1), [0]]).astype(np.int32)
+    j = np.concatenate([key % (last + 1), [last]]).astype(np.int32)
+    c = np.concatenate([1.0 + rng.random(key.size), [-1.0]]).astype(np.float32)
+    return int(last + 1), i, j, c
+
+
+# the limits of the hashed search: 16 lanes take rows of 16 and 15 entries and a table of 224, 64 lanes rows of 64 and
+# 63 and tables of 896 and 3584 entries (entries: the rows of the far endpoint's neighbours); the next size up goes to
+# the larger table or to the wave-per-edge walk
+@pytest.mark.parametrize("isolated", [0, 4000], ids=["wide", "narrow"])
+@pytest.mark.parametrize("d_a,d_b,row", [(1, 1, 1), (16, 15, 13), (16, 15, 14), (17, 15, 5), (16, 16, 5), (64, 63, 11), (64, 63, 14),
+                                         (64, 63, 55), (64, 63, 60), (65, 63, 9), (64, 64, 9), (130, 70, 9)])
+@pytest.mark.parametrize("lmax,shortest", [(4, False), (5, False), (5, True)])
+def test_hashed_search_at_its_limits(rama, oracle32, isolated, d_a, d_b, row, lmax, shortest):
+    n, i, j, c = fan_graph(d_a, d_b, row, isolated)
+    want = oracle32.find_conflicted_cycles(n, i, j, c, lmax, shortest_only=shortest)
+    rama.set_cycle_search(2)
+    try:
+        got = rama.find_conflicted_cycles(n, i, j, c, lmax, shortest_only=shortest)
+    finally:
+        rama.set_cycle_search(0)
+    for L in range(lmax - 2):
+        assert np.array_equal(np_(got[L]), want[L]), (L + 3, got[L].shape, want[L].shape)
+
+
 # cycles of length 6 and 7 (named as future work in Sec. 5) and the shortest-only separation; the
 # cases are the ones whose plain enumeration the oracle finishes in seconds
 LONG_CASES = [("cfg1", 7), ("grid3d_24", 7), ("random_sparse", 7), ("knn_20000", 7), ("knn_20000", 6),

@@ -324,6 +324,10 @@ __global__ __launch_bounds__(kBlock) void k_inner(size_t m, const int32_t *i, co
     uint32_t p = pos[e];
     key[p] = (uint32_t)a;
     val[p] = __float_as_uint(c[e]);
+// diag[k] = sum of the values of run k of the sorted keys, in order of appearance (an ordered sum is a chain of adds, so
+// what can be saved is the wait for its operands).  A wave takes 64 places; the runs that start there are added up from
+// registers, all of them in step, and the one that goes on behind the 64 places is carried on by the whole wave: it
+// fetches 64 values at a time, the next ones while these are added, and adds them lane by lane.
 }
 
 struct HeadFlag {
@@ -335,13 +339,51 @@ struct HeadFlag {
 
 __global__ __launch_bounds__(kBlock) void k_diag_runs(size_t m, const uint32_t *key, const uint32_t *val, float *diag)
 {
-    size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e >= m) return;
-    uint32_t k = key[e];
-    if (e > 0 && key[e - 1] == k) return;
-    float acc = __uint_as_float(val[e]);
-    for (size_t f = e + 1; f < m && key[f] == k; ++f) acc = acc + __uint_as_float(val[f]);
-    diag[k] = acc;
+    const size_t base = (size_t)blockIdx.x * kBlock + (threadIdx.x & ~63u), e = base + lane_id();
+    if (base >= m) return;      // the whole wave
+    const int lane = lane_id();
+    const uint32_t k = e < m ? key[e] : 0xffffffffu;      // no key: a node id is below 2^31
+    const float v = e < m ? __uint_as_float(val[e]) : 0.0f;
+    uint32_t left = (uint32_t)__shfl_up((int)k, 1, 64);
+    if (lane == 0) left = base > 0 ? key[base - 1] : 0xffffffffu;
+    const bool head = e < m && (k != left || e == 0);
+    const uint64_t heads = __ballot(head);
+    if (heads == 0ull) return;
+    // places of the lane's run within the wave: up to the next head or the end
+    const uint64_t later = lane == 63 ? 0ull : heads >> (lane + 1);
+    const int in_wave = m - base < 64 ? (int)(m - base) : 64;
+    const int len = !head ? 0 : later ? __ffsll((long long)later) : in_wave - lane;
+    float acc = v;
+    for (int d = 1; __ballot(d < len); ++d) {
+        const float x = __shfl_down(v, d, 64);
+        if (d < len) acc = acc + x;
+    }
+    const int last = 63 - __clzll((long long)heads);      // the run that may go on
+    if (in_wave == 64 && base + 64 < m) {
+        const uint32_t run = (uint32_t)__builtin_amdgcn_readlane((int)k, last);
+        float sum = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(acc), last));
+        size_t p = base + 64;
+        uint32_t nk = p + lane < m ? key[p + lane] : 0xffffffffu;
+        float nv = p + lane < m ? __uint_as_float(val[p + lane]) : 0.0f;
+        for (;;) {
+            const uint64_t same = __ballot(nk == run);      // the keys ascend: the run's places come first
+            const int cnt = same == ~0ull ? 64 : __ffsll((long long)~same) - 1;
+            if (cnt == 0) break;
+            const uint32_t x = __float_as_uint(nv);
+            p += 64;
+            if (cnt == 64) {
+                nk = p + lane < m ? key[p + lane] : 0xffffffffu;
+                nv = p + lane < m ? __uint_as_float(val[p + lane]) : 0.0f;
+#pragma unroll
+                for (int q = 0; q < 64; ++q) sum = sum + __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)x, q));
+            } else {
+                for (int q = 0; q < cnt; ++q) sum = sum + __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)x, q));
+                break;
+            }
+        }
+        if (lane == last) acc = sum;
+    }
+    if (head) diag[k] = acc;
 }
 
 

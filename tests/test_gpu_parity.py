@@ -387,6 +387,24 @@ def test_forest_deep_tree(rama, oracle32, n):
     assert np.array_equal(np_(got["c"]), want["c"])
 
 
+# runs of diagonal entries that end on either side of the 64 places a wave holds, and one much longer; ordered sums, so
+# the result is the oracle's bit for bit
+@pytest.mark.parametrize("sizes", [(1,), (2, 1, 2), (64,), (65,), (66, 2, 64), (33, 33), (32, 34, 3, 129, 2), (5000, 2, 700)])
+def test_diagonal_of_long_runs(rama, oracle32, sizes):
+    rng = np.random.default_rng(len(sizes))
+    i, j, start = [], [], 0
+    for k in sizes:                     # a path of k nodes, doubled by chords: contracted into one node
+        i += list(range(start, start + k - 1)) + list(range(start, start + k - 2))
+        j += list(range(start + 1, start + k)) + list(range(start + 2, start + k))
+        start += k
+    i, j = np.array(i, np.int32), np.array(j, np.int32)
+    c = (rng.random(i.size) + 0.01).astype(np.float32)
+    want = oracle32.contract(start, i, j, c, repeat=0)
+    got = rama.contract(start, i, j, c, repeat=0)
+    assert got["n_nodes"] == want["n_nodes"] == len(sizes)
+    assert np.array_equal(np_(got["diag"]), want["diag"][: len(sizes)])
+
+
 def test_contract_fig2_graph(rama, oracle32):
     # the graph of the paper's Fig. 2; with the matching rule S={st} (cost 4 is the best edge at s and t;
     # rs=3 loses at s), so only the mechanics are compared with the oracle here

@@ -210,6 +210,26 @@ rama_status rama_find_conflicted_cycles(rama_ctx *ctx, int32_t n_nodes, int64_t 
                                         int32_t *const *cycles, int64_t *n_cycles_out);
 
 /*
+ * Room for results whose size is known only when they are about to be written: `room` returns device memory of the
+ * caller's of at least `bytes` bytes (> 0), or NULL when it has none (the call then ends with RAMA_ERR_OOM).  It is
+ * called from the thread that calls into the library, at most once per result and call; the library writes the result on
+ * the ctx's stream and keeps no reference to the memory after the call.
+ */
+typedef struct {
+    void *(*room)(void *user, int32_t which, int64_t bytes);
+    void *user;
+} rama_room;
+
+/*
+ * rama_find_conflicted_cycles without the size query: the search runs once and asks for the memory of every list that
+ * is not empty when it knows its length (`which` = cycle length).  Everything else as above.
+ */
+rama_status rama_find_conflicted_cycles_room(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges,
+                                             const int32_t *i, const int32_t *j, const float *c,
+                                             int32_t max_cycle_len, int32_t shortest_only, const rama_room *room,
+                                             int64_t *n_cycles_out);
+
+/*
  * Dual update of one round (Sec. 3.2.1 Lagrange decomposition, eq. 5 and 6; Sec. 3.2.3,
  * algorithm "Parallel-Message-Passing"; inner loop of "Primal-Dual Multicut"):
  * triangulate the given cycles, run k_iters iterations of edge->triangle and
@@ -260,6 +280,13 @@ rama_status rama_dual_rounds(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges,
                              const int32_t *i, const int32_t *j, const float *c, const rama_params *params,
                              int64_t edge_cap, int32_t *i_out, int32_t *j_out, float *c_out, int64_t *n_edges_out,
                              double *lower_bound, double *lb_trace, int64_t *n_triangles_out);
+
+/* rama_dual_rounds that asks for the memory of its edge list (`which` = 0: i_out, 1: j_out, 2: c_out) when it knows the
+ * number of edges, instead of failing when a guess was too small.  Nothing is asked for an empty list. */
+rama_status rama_dual_rounds_room(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges,
+                                  const int32_t *i, const int32_t *j, const float *c, const rama_params *params,
+                                  const rama_room *room, int64_t *n_edges_out,
+                                  double *lower_bound, double *lb_trace, int64_t *n_triangles_out);
 
 /*
  * Primal update (Sec. 3.1: Lemma 1, Lemma 3, algorithm "Parallel-Edge-Contraction", "Finding

@@ -20,7 +20,7 @@ EXPORTS = [
     "rama_round_count", "rama_round_get",
     "rama_profile_enable", "rama_profile_count", "rama_profile_get", "rama_set_sort_split", "rama_set_cycle_search",
     "rama_find_conflicted_cycles", "rama_message_passing", "rama_dual_rounds", "rama_contract", "rama_solve",
-    "rama_solve_static",
+    "rama_solve_static", "rama_find_conflicted_cycles_room", "rama_dual_rounds_room",
 ]
 STATIC_MAX_NODES, STATIC_MAX_EDGES = 1 << 17, 1 << 18   # RAMA_STATIC_MAX_* of include/rama.h
 
@@ -65,6 +65,13 @@ class RamaAlloc(C.Structure):
     _fields_ = [("alloc", ALLOC_FN), ("free", FREE_FN), ("user", C.c_void_p)]
 
 
+ROOM_FN = C.CFUNCTYPE(C.c_void_p, C.c_void_p, C.c_int32, C.c_int64)
+
+
+class RamaRoom(C.Structure):
+    _fields_ = [("room", ROOM_FN), ("user", C.c_void_p)]
+
+
 class RamaError(RuntimeError):
     def __init__(self, status, where, msg):
         super().__init__(f"{where} failed with status {status}: {msg}")
@@ -105,6 +112,9 @@ def load_library():
                                          vp, vp, vp, C.POINTER(i64), C.POINTER(C.c_double), C.POINTER(C.c_double)]
     lib.rama_dual_rounds.argtypes = [vp, i32, i64, vp, vp, vp, C.POINTER(RamaParams), i64, vp, vp, vp, C.POINTER(i64),
                                      C.POINTER(C.c_double), C.POINTER(C.c_double), C.POINTER(i64)]
+    lib.rama_find_conflicted_cycles_room.argtypes = [vp, i32, i64, vp, vp, vp, i32, i32, C.POINTER(RamaRoom), C.POINTER(i64)]
+    lib.rama_dual_rounds_room.argtypes = [vp, i32, i64, vp, vp, vp, C.POINTER(RamaParams), C.POINTER(RamaRoom), C.POINTER(i64),
+                                          C.POINTER(C.c_double), C.POINTER(C.c_double), C.POINTER(i64)]
     lib.rama_contract.argtypes = [vp, i32, i64, vp, vp, vp, C.POINTER(RamaParams), i32, vp, vp, vp, vp, vp,
                                   C.POINTER(i32), C.POINTER(i64)]
     lib.rama_solve.argtypes = [vp, i32, i64, vp, vp, vp, C.POINTER(RamaParams), vp, C.POINTER(C.c_double),
@@ -219,6 +229,21 @@ class Rama:
     def _empty(self, n, dtype):
         return self.torch.empty(max(int(n), 1), dtype=dtype, device=self.device)
 
+    def _room(self, dtypes):
+        """A rama_room that makes tensors when the library asks for them (dtypes: which -> dtype), the dict it puts
+        them into, and the list of what went wrong in it: no exception may cross the C boundary."""
+        made, wrong = {}, []
+
+        def room(_user, which, nbytes):
+            try:
+                made[which] = self._empty(nbytes // 4, dtypes[which])
+                return made[which].data_ptr()
+            except Exception as e:
+                wrong.append(e)
+                return None
+
+        return RamaRoom(ROOM_FN(room), None), made, wrong
+
     def workspace_bytes(self):
         return int(self.lib.rama_workspace_bytes(self.ctx))
 
@@ -269,18 +294,13 @@ class Rama:
         if nl < 1 or max_cycle_len > MAX_CYCLE_LEN:
             raise ValueError("max_cycle_len out of range")
         cnt = (C.c_int64 * nl)()
-        st = self.lib.rama_find_conflicted_cycles(self.ctx, n_nodes, i.numel(), i.data_ptr(), j.data_ptr(),
-                                                  c.data_ptr(), max_cycle_len, int(shortest_only), None, None, cnt)
-        if st not in (RAMA_OK, RAMA_ERR_CAPACITY):
-            self._check(st, "rama_find_conflicted_cycles")
-        want = [cnt[k] for k in range(nl)]
-        outs = [self._empty(want[k] * (k + 3), t.int32) for k in range(nl)]
-        cap = (C.c_int64 * nl)(*want)
-        ptrs = (C.c_void_p * nl)(*[o.data_ptr() for o in outs])
-        st = self.lib.rama_find_conflicted_cycles(self.ctx, n_nodes, i.numel(), i.data_ptr(), j.data_ptr(),
-                                                  c.data_ptr(), max_cycle_len, int(shortest_only), cap, ptrs, cnt)
+        room, made, wrong = self._room({q + 3: t.int32 for q in range(nl)})
+        st = self.lib.rama_find_conflicted_cycles_room(self.ctx, n_nodes, i.numel(), i.data_ptr(), j.data_ptr(), c.data_ptr(),
+                                                       max_cycle_len, int(shortest_only), C.byref(room), cnt)
+        if wrong:
+            raise wrong[0]
         self._check(st, "rama_find_conflicted_cycles")
-        return [outs[k][: want[k] * (k + 3)].view(-1, k + 3) for k in range(nl)]
+        return [made[q + 3].view(-1, q + 3) if cnt[q] else self._empty(0, t.int32)[:0].view(-1, q + 3) for q in range(nl)]
 
     def message_passing(self, n_nodes, i, j, c, cycles, k_iters, trace=False):
         """cycles: list whose entry q holds the (q+3)-cycles, as returned by find_conflicted_cycles."""
@@ -311,17 +331,13 @@ class Rama:
         params = params or default_params()
         mo, nt, lb = C.c_int64(0), C.c_int64(0), C.c_double(0.0)
         tr = (C.c_double * (params.dual_rounds + 1))()
-        cap = i.numel()
-        while True:     # the number of chords is only known afterwards: grow and repeat on a capacity miss
-            io, jo, co = self._empty(cap, t.int32), self._empty(cap, t.int32), self._empty(cap, t.float32)
-            st = self.lib.rama_dual_rounds(self.ctx, n_nodes, i.numel(), i.data_ptr(), j.data_ptr(), c.data_ptr(),
-                                           C.byref(params), cap, io.data_ptr(), jo.data_ptr(), co.data_ptr(),
-                                           C.byref(mo), C.byref(lb), tr, C.byref(nt))
-            if st == RAMA_ERR_CAPACITY and mo.value > cap:
-                cap = mo.value
-                continue
-            self._check(st, "rama_dual_rounds")
-            break
+        room, made, wrong = self._room({0: t.int32, 1: t.int32, 2: t.float32})
+        st = self.lib.rama_dual_rounds_room(self.ctx, n_nodes, i.numel(), i.data_ptr(), j.data_ptr(), c.data_ptr(),
+                                            C.byref(params), C.byref(room), C.byref(mo), C.byref(lb), tr, C.byref(nt))
+        if wrong:
+            raise wrong[0]
+        self._check(st, "rama_dual_rounds")
+        io, jo, co = (made.get(q, self._empty(0, dt)) for q, dt in ((0, t.int32), (1, t.int32), (2, t.float32)))
         k = mo.value
         return dict(i=io[:k], j=jo[:k], c=co[:k], lower_bound=lb.value, lb_trace=list(tr), n_triangles=nt.value)
 

@@ -88,6 +88,29 @@ bool bad_graph_args(int32_t n, int64_t m, const void *i, const void *j, const vo
     return n < 0 || m < 0 || (m > 0 && (!i || !j || !c));
 }
 
+// memory of the caller's for a result of `bytes` bytes
+rama_status ask_room(Ctx &ctx, const rama_room *room, int32_t which, size_t bytes, void **p)
+{
+    *p = room->room(room->user, which, (int64_t)bytes);
+    if (!*p) return fail(ctx, RAMA_ERR_OOM, "the caller gave no room for a result of " + std::to_string(bytes) + " bytes");
+    return RAMA_OK;
+}
+
+// separation on the caller's edge list, straight into the memory the sink names; the counts are written first
+rama_status cycles_into(Ctx &ctx, int32_t n_nodes, int64_t n_edges, const int32_t *i, const int32_t *j, const float *c,
+                        int32_t max_cycle_len, int32_t shortest_only, int64_t *n_cycles_out, const CycleSink &sink)
+{
+    const int lists = max_cycle_len - 2;
+    Graph g;
+    RAMA_TRY(canonicalise(ctx, n_nodes, n_edges, i, j, c, g));
+    for (int q = 0; q < lists; ++q) n_cycles_out[q] = 0;
+    CycleLists cyc;
+    return find_cycles(ctx, g, max_cycle_len, shortest_only != 0, cyc, [&](const int64_t *n, int32_t **to) -> rama_status {
+        for (int q = 0; q < lists; ++q) n_cycles_out[q] = n[q];
+        return sink(n, to);
+    });
+}
+
 // Dual part of a round on graph g (replaced by the augmented graph with reparametrised costs):
 // `rounds` times { separate, add triangles to the kept set, k iterations }.  lb: after the last round
 // that ran (untouched if none ran: *ran stays false).  trace: optional [rounds+1].
@@ -105,7 +128,7 @@ rama_status dual_block(Ctx &ctx, Graph &g, int lmax, bool shortest_only, int k, 
     int done = 0;
     for (int d = 1; d <= rounds && lmax >= 3; ++d) {
         CycleLists cyc;
-        RAMA_TRY(find_cycles(ctx, g, lmax, shortest_only, false, cyc));
+        RAMA_TRY(find_cycles(ctx, g, lmax, shortest_only, cyc));
         int64_t n_cyc = 0;
         const int32_t *lists[kCycleLists];
         for (int q = 0; q < kCycleLists; ++q) { n_cyc += cyc.n[q]; lists[q] = cyc.v[q].get(); }
@@ -191,7 +214,7 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
         if (lmax >= 3 && k > 0) {
             if (P.dual_rounds == 1) {
                 CycleLists cyc;
-                RAMA_TRY(find_cycles(ctx, g, lmax, P.shortest_cycles_only != 0, false, cyc));
+                RAMA_TRY(find_cycles(ctx, g, lmax, P.shortest_cycles_only != 0, cyc));
                 clock.mark(round, 1);
                 dual_marked = true;
                 R.n_attractive = cyc.n_attractive; R.n_repulsive = cyc.n_repulsive;
@@ -447,28 +470,30 @@ rama_status rama_find_conflicted_cycles(rama_ctx *ctx, int32_t n_nodes, int64_t 
         if (cq < 0 || (cq > 0 && (!cycles || !cycles[q])))
             return fail(*ctx, RAMA_ERR_INVALID_ARG, "rama_find_conflicted_cycles: bad capacities or null list");
     }
-    auto body = [&]() -> rama_status {
-        Graph g;
-        RAMA_TRY(canonicalise(*ctx, n_nodes, n_edges, i, j, c, g));
-        CycleLists cnt;
-        RAMA_TRY(find_cycles(*ctx, g, max_cycle_len, shortest_only != 0, true, cnt));
-        bool fits = true;
-        int64_t total = 0;
-        for (int q = 0; q < lists; ++q) {
-            n_cycles_out[q] = cnt.n[q];
-            total += cnt.n[q];
-            if (cnt.n[q] > (cap ? cap[q] : 0)) fits = false;
-        }
-        if (!fits)
-            return fail(*ctx, RAMA_ERR_CAPACITY, "cycle output lists are too small; needed sizes written to n_cycles_out");
-        if (total == 0) return RAMA_OK;
-        CycleLists cyc;
-        RAMA_TRY(find_cycles(*ctx, g, max_cycle_len, shortest_only != 0, false, cyc));
+    return finish(*ctx, cycles_into(*ctx, n_nodes, n_edges, i, j, c, max_cycle_len, shortest_only, n_cycles_out,
+                                    [&](const int64_t *n, int32_t **to) -> rama_status {
         for (int q = 0; q < lists; ++q)
-            if (cyc.n[q] > 0) RAMA_TRY(copy_out(*ctx, cycles[q], cyc.v[q].get(), (size_t)cyc.n[q] * (q + 3) * 4));
-        return finish(*ctx, RAMA_OK);
-    };
-    return finish(*ctx, body());
+            if (n[q] > (cap ? cap[q] : 0))
+                return fail(*ctx, RAMA_ERR_CAPACITY, "cycle output lists are too small; needed sizes written to n_cycles_out");
+        for (int q = 0; q < lists; ++q) to[q] = n[q] > 0 ? cycles[q] : nullptr;
+        return RAMA_OK;
+    }));
+}
+
+rama_status rama_find_conflicted_cycles_room(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const int32_t *i,
+                                             const int32_t *j, const float *c, int32_t max_cycle_len, int32_t shortest_only,
+                                             const rama_room *room, int64_t *n_cycles_out)
+{
+    if (!ctx) return RAMA_ERR_INVALID_ARG;
+    if (bad_graph_args(n_nodes, n_edges, i, j, c) || !n_cycles_out || max_cycle_len < 3 || max_cycle_len > kMaxCycleLen || !room || !room->room)
+        return fail(*ctx, RAMA_ERR_INVALID_ARG, "rama_find_conflicted_cycles_room: bad arguments");
+    const int lists = max_cycle_len - 2;
+    return finish(*ctx, cycles_into(*ctx, n_nodes, n_edges, i, j, c, max_cycle_len, shortest_only, n_cycles_out,
+                                    [&](const int64_t *n, int32_t **to) -> rama_status {
+        for (int q = 0; q < lists; ++q)
+            if (n[q] > 0) RAMA_TRY(ask_room(*ctx, room, q + 3, (size_t)n[q] * (size_t)(q + 3) * 4, (void **)&to[q]));
+        return RAMA_OK;
+    }));
 }
 
 rama_status rama_message_passing(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const int32_t *i, const int32_t *j,
@@ -551,16 +576,14 @@ rama_status rama_contract(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const
     return finish(*ctx, body());
 }
 
-rama_status rama_dual_rounds(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const int32_t *i, const int32_t *j,
-                             const float *c, const rama_params *params, int64_t edge_cap, int32_t *i_out,
-                             int32_t *j_out, float *c_out, int64_t *n_edges_out, double *lower_bound, double *lb_trace,
-                             int64_t *n_triangles_out)
+// rama_dual_rounds and rama_dual_rounds_room: `place` names the memory for the m edges of the result
+static rama_status dual_rounds_impl(rama_ctx *ctx, const char *what, int32_t n_nodes, int64_t n_edges, const int32_t *i, const int32_t *j,
+                                    const float *c, const rama_params *params, const std::function<rama_status(int64_t, void **)> &place,
+                                    int64_t *n_edges_out, double *lower_bound, double *lb_trace, int64_t *n_triangles_out)
 {
-    if (!ctx) return RAMA_ERR_INVALID_ARG;
-    if (bad_graph_args(n_nodes, n_edges, i, j, c) || !params || !n_edges_out || edge_cap < 0 ||
-        (edge_cap > 0 && (!i_out || !j_out || !c_out)) || params->dual_rounds < 0 || params->mp_iters_first < 0 ||
-        params->max_cycle_len_first > RAMA_MAX_CYCLE_LEN)
-        return fail(*ctx, RAMA_ERR_INVALID_ARG, "rama_dual_rounds: bad arguments");
+    if (bad_graph_args(n_nodes, n_edges, i, j, c) || !params || !n_edges_out || params->dual_rounds < 0 ||
+        params->mp_iters_first < 0 || params->max_cycle_len_first > RAMA_MAX_CYCLE_LEN)
+        return fail(*ctx, RAMA_ERR_INVALID_ARG, std::string(what) + ": bad arguments");
     auto body = [&]() -> rama_status {
         Graph g;
         RAMA_TRY(canonicalise(*ctx, n_nodes, n_edges, i, j, c, g));
@@ -574,14 +597,42 @@ rama_status rama_dual_rounds(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, co
         if (lb_trace) for (size_t d = 0; d < trace.size(); ++d) lb_trace[d] = trace[d];
         if (n_triangles_out) *n_triangles_out = ntri;
         *n_edges_out = g.m;
-        if (g.m > edge_cap)
-            return fail(*ctx, RAMA_ERR_CAPACITY, "edge output buffers are too small; needed size written to n_edges_out");
-        RAMA_TRY(copy_out(*ctx, i_out, g.i.get(), (size_t)g.m * 4));
-        RAMA_TRY(copy_out(*ctx, j_out, g.j.get(), (size_t)g.m * 4));
-        RAMA_TRY(copy_out(*ctx, c_out, g.c.get(), (size_t)g.m * 4));
-        return finish(*ctx, RAMA_OK);
+        void *to[3] = {nullptr, nullptr, nullptr};
+        RAMA_TRY(place(g.m, to));
+        RAMA_TRY(copy_out(*ctx, to[0], g.i.get(), (size_t)g.m * 4));
+        RAMA_TRY(copy_out(*ctx, to[1], g.j.get(), (size_t)g.m * 4));
+        RAMA_TRY(copy_out(*ctx, to[2], g.c.get(), (size_t)g.m * 4));
+        return RAMA_OK;
     };
     return finish(*ctx, body());
+}
+
+rama_status rama_dual_rounds(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const int32_t *i, const int32_t *j,
+                             const float *c, const rama_params *params, int64_t edge_cap, int32_t *i_out,
+                             int32_t *j_out, float *c_out, int64_t *n_edges_out, double *lower_bound, double *lb_trace,
+                             int64_t *n_triangles_out)
+{
+    if (!ctx) return RAMA_ERR_INVALID_ARG;
+    if (edge_cap < 0 || (edge_cap > 0 && (!i_out || !j_out || !c_out)))
+        return fail(*ctx, RAMA_ERR_INVALID_ARG, "rama_dual_rounds: bad arguments");
+    return dual_rounds_impl(ctx, "rama_dual_rounds", n_nodes, n_edges, i, j, c, params, [&](int64_t m, void **to) -> rama_status {
+        if (m > edge_cap)
+            return fail(*ctx, RAMA_ERR_CAPACITY, "edge output buffers are too small; needed size written to n_edges_out");
+        to[0] = i_out; to[1] = j_out; to[2] = c_out;
+        return RAMA_OK;
+    }, n_edges_out, lower_bound, lb_trace, n_triangles_out);
+}
+
+rama_status rama_dual_rounds_room(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const int32_t *i, const int32_t *j,
+                                  const float *c, const rama_params *params, const rama_room *room, int64_t *n_edges_out,
+                                  double *lower_bound, double *lb_trace, int64_t *n_triangles_out)
+{
+    if (!ctx) return RAMA_ERR_INVALID_ARG;
+    if (!room || !room->room) return fail(*ctx, RAMA_ERR_INVALID_ARG, "rama_dual_rounds_room: bad arguments");
+    return dual_rounds_impl(ctx, "rama_dual_rounds_room", n_nodes, n_edges, i, j, c, params, [&](int64_t m, void **to) -> rama_status {
+        for (int32_t q = 0; q < 3 && m > 0; ++q) RAMA_TRY(ask_room(*ctx, room, q, (size_t)m * 4, &to[q]));
+        return RAMA_OK;
+    }, n_edges_out, lower_bound, lb_trace, n_triangles_out);
 }
 
 rama_status rama_solve(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const int32_t *i, const int32_t *j,

@@ -7,6 +7,7 @@
 #include <chrono>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <utility>
 #include <vector>
@@ -451,8 +452,11 @@ struct CycleLists {
 rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const int32_t *j, const float *c, Graph &out);
 
 // a1: conflicted cycles of lengths 3..max_len; shortest_only keeps, per repulsive edge, only the
-// cycles of its smallest length.  With count_only the lists stay empty.
-rama_status find_cycles(Ctx &ctx, const Graph &g, int max_len, bool shortest_only, bool count_only, CycleLists &out);
+// cycles of its smallest length.  `sink` (optional) is asked for the lists' memory once the counts are known: list q
+// goes to to[q] (null for an empty list) and out.v stays empty; a failure of the sink ends the search before the
+// lists are written.
+using CycleSink = std::function<rama_status(const int64_t *n, int32_t **to)>;
+rama_status find_cycles(Ctx &ctx, const Graph &g, int max_len, bool shortest_only, CycleLists &out, const CycleSink &sink = nullptr);
 
 // a2+a3: triangulate, k iterations of message passing; `out` = augmented graph with reduced costs
 struct DualInfo {

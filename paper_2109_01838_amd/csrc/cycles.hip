@@ -927,7 +927,7 @@ __global__ __launch_bounds__(kBlock) void k_fill_cycles_heavy(const uint32_t *he
 // count, scan, fill for walks of at most MAXL nodes
 template <int MAXL>
 rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t *rj, Adj adj, int32_t n, size_t mp,
-                           int max_len, bool shortest_only, bool count_only, CycleLists &out, uint32_t longest_row = 0xffffffffu)
+                           int max_len, bool shortest_only, CycleLists &out, const CycleSink &sink, uint32_t longest_row = 0xffffffffu)
 {
     constexpr int NL = MAXL - 2;
     const int lists = max_len - 2;
@@ -1022,13 +1022,14 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
         out.n[k] = (int64_t)tot[k];
         all += tot[k];
     }
-    if (count_only) return RAMA_OK;
+    int32_t *to[kCycleLists] = {};
+    if (sink) RAMA_TRY(sink(out.n, to));
     double list_bytes = 0.0;
     for (int k = 0; k < lists; ++k) {
         if ((uint64_t)(k + 3) * tot[k] >= (uint64_t(1) << 31))
             return fail(ctx, RAMA_ERR_CAPACITY, "cycle list reaches 2^31 entries");
-        RAMA_TRY(out.v[k].alloc(ctx, (size_t)(k + 3) * tot[k]));
-        vp.p[k] = out.v[k].get();
+        if (!sink) RAMA_TRY(out.v[k].alloc(ctx, (size_t)(k + 3) * tot[k]));
+        vp.p[k] = sink ? to[k] : out.v[k].get();
         list_bytes += 4.0 * (k + 3) * (double)tot[k];
     }
     if (all == 0) return RAMA_OK;
@@ -1093,7 +1094,7 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
 
 }  // namespace
 
-rama_status find_cycles(Ctx &ctx, const Graph &g, int max_len, bool shortest_only, bool count_only, CycleLists &out)
+rama_status find_cycles(Ctx &ctx, const Graph &g, int max_len, bool shortest_only, CycleLists &out, const CycleSink &sink)
 {
     for (int k = 0; k < kCycleLists; ++k) { out.n[k] = 0; out.v[k].reset(); }
     out.n_attractive = 0; out.n_repulsive = 0;
@@ -1156,12 +1157,11 @@ rama_status find_cycles(Ctx &ctx, const Graph &g, int max_len, bool shortest_onl
     if (want_longest) RAMA_TRY(read_back(ctx, &longest_row, longest.get(), 4));
     // one instantiation per depth class: triangles are row intersections and need no walk state
     if (max_len <= 3)
-        return count_and_fill<3>(ctx, (size_t)mr, ri.get(), rj.get(), adj, n, (size_t)mp, max_len, shortest_only, count_only, out);
+        return count_and_fill<3>(ctx, (size_t)mr, ri.get(), rj.get(), adj, n, (size_t)mp, max_len, shortest_only, out, sink);
     if (max_len <= 5)
-        return count_and_fill<5>(ctx, (size_t)mr, ri.get(), rj.get(), adj, n, (size_t)mp, max_len, shortest_only, count_only, out,
+        return count_and_fill<5>(ctx, (size_t)mr, ri.get(), rj.get(), adj, n, (size_t)mp, max_len, shortest_only, out, sink,
                                  longest_row);
-    return count_and_fill<kMaxCycleLen>(ctx, (size_t)mr, ri.get(), rj.get(), adj, n, (size_t)mp, max_len, shortest_only,
-                                        count_only, out);
+    return count_and_fill<kMaxCycleLen>(ctx, (size_t)mr, ri.get(), rj.get(), adj, n, (size_t)mp, max_len, shortest_only, out, sink);
 }
 
 }  // namespace rama

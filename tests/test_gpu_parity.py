@@ -225,6 +225,43 @@ def test_cycles_capacity_protocol(rama):
     assert rama.lib.rama_find_conflicted_cycles(*args, 5, 0, cap, ptrs, cnt) == binding.RAMA_ERR_INVALID_ARG
 
 
+def test_room_for_results_of_unknown_size(rama):
+    """The entry points that ask the caller for memory give what the sizing protocol gives, ask only for results that
+    are not empty, and end with RAMA_ERR_OOM -- nothing written, the ctx usable -- when there is none."""
+    import ctypes as C
+    import torch
+    from paper_2109_01838_amd import binding, default_params
+    g = CASES["cfg1"]
+    i, j, c = (torch.as_tensor(g[k], device="cuda") for k in ("i", "j", "c"))
+    args = (rama.ctx, g["n_nodes"], i.numel(), i.data_ptr(), j.data_ptr(), c.data_ptr())
+    cnt, got = (C.c_int64 * 3)(), {}
+
+    def give(_user, which, nbytes):
+        got[which] = torch.full((nbytes // 4,), -7, dtype=torch.int32, device="cuda")
+        return got[which].data_ptr()
+
+    room, none = binding.RamaRoom(binding.ROOM_FN(give), None), binding.RamaRoom(binding.ROOM_FN(lambda *_: None), None)
+    assert rama.lib.rama_find_conflicted_cycles_room(*args, 5, 0, C.byref(room), cnt) == binding.RAMA_OK
+    assert list(got) == [4] and cnt[0] == cnt[2] == 0
+    ref = torch.full((4 * cnt[1],), -7, dtype=torch.int32, device="cuda")
+    cap, ptrs = (C.c_int64 * 3)(0, cnt[1], 0), (C.c_void_p * 3)(None, ref.data_ptr(), None)
+    assert rama.lib.rama_find_conflicted_cycles(*args, 5, 0, cap, ptrs, cnt) == binding.RAMA_OK
+    assert torch.equal(got[4], ref)
+    assert rama.lib.rama_find_conflicted_cycles_room(*args, 5, 0, C.byref(none), cnt) == binding.RAMA_ERR_OOM
+    assert rama.lib.rama_find_conflicted_cycles_room(*args, 5, 0, None, cnt) == binding.RAMA_ERR_INVALID_ARG
+    p, m = default_params(dual_rounds=2), C.c_int64(0)
+    got.clear()
+    assert rama.lib.rama_dual_rounds_room(*args, C.byref(p), C.byref(room), C.byref(m), None, None, None) == binding.RAMA_OK
+    assert sorted(got) == [0, 1, 2] and all(x.numel() == m.value for x in got.values())
+    ref = [torch.empty(m.value, dtype=torch.int32, device="cuda") for _ in range(3)]
+    assert rama.lib.rama_dual_rounds(*args, C.byref(p), m.value - 1, *(x.data_ptr() for x in ref), C.byref(m), None, None,
+                                     None) == binding.RAMA_ERR_CAPACITY
+    assert rama.lib.rama_dual_rounds(*args, C.byref(p), m.value, *(x.data_ptr() for x in ref), C.byref(m), None, None,
+                                     None) == binding.RAMA_OK
+    assert all(torch.equal(got[q], ref[q]) for q in range(3))
+    assert rama.lib.rama_dual_rounds_room(*args, C.byref(p), C.byref(none), C.byref(m), None, None, None) == binding.RAMA_ERR_OOM
+
+
 # --------------------------------------------------------------------------------------------
 # a2 + a3 message passing
 # --------------------------------------------------------------------------------------------

@@ -100,7 +100,8 @@ typedef struct {
     int64_t n_edges_aug;        /* edges after adding chords */
     int64_t n_contracted;       /* |S| */
     int64_t workspace_peak;     /* largest number of workspace bytes in use at one time during the round */
-    double ms_cycles, ms_dual, ms_contract; /* stream time between stage marks (HIP events) */
+    double ms_cycles, ms_dual, ms_contract; /* stream time between stage marks (HIP events); for rounds that run inside one
+                                   kernel, its own clock at the same places */
 } rama_round_stats;
 
 /* Optional source of device workspace (for instance a framework's caching allocator).  alloc returns

@@ -199,7 +199,35 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
     double lb = 0.0;
     bool have_lb = false;
     int32_t n_cur = n;
-    for (int round = 1; P.max_rounds <= 0 || round <= P.max_rounds; ++round) {
+    std::vector<size_t> clocked;        // rounds whose times the stage clock has (the others bring theirs along)
+    // Later rounds on graphs that one workgroup can hold run there, many in one launch (tail.hip; ms per solve before and
+    // with it): 32^2 grid 2.25 and 0.75, 128^2 long-range grid 6.0 and 4.5, 512^2 long-range grid 10.4 and 9.6.
+    const bool separates_later = P.max_cycle_len_later >= 3 && P.mp_iters_later > 0;
+    bool tail_ok = !separates_later || (P.max_cycle_len_later == 3 && P.dual_rounds == 1);
+    bool finished = false;
+    for (int round = 1; !finished && (P.max_rounds <= 0 || round <= P.max_rounds); ++round) {
+        if (round > 1 && tail_ok && tail_fits(g)) {
+            Buf<int32_t> ftail;
+            TailResult res;
+            ctx.active->reset_peak();
+            RAMA_TRY(tail_rounds(ctx, g, g, separates_later, P.mp_iters_later, P.contract_threshold, P.matching_rounds_cap,
+                                 P.forest_ratio, P.max_rounds > 0 ? P.max_rounds - round + 1 : 0, ftail, res));
+            for (rama_round_stats &R : res.rounds) {
+                R.workspace_peak = (int64_t)ctx.active->peak_live();
+                ctx.rounds.push_back(R);
+            }
+            maps.push_back(std::move(ftail));
+            map_size.push_back((size_t)n_cur);
+            n_cur = g.n;
+            round += (int)res.rounds.size();
+            S.rounds = round - 1;
+            if (res.status != kTailTooMany) {
+                finished = res.status == kTailDone;
+                --round;
+                continue;
+            }
+            if (P.max_rounds > 0 && round > P.max_rounds) break;
+        }
         const int lmax = round == 1 ? P.max_cycle_len_first : P.max_cycle_len_later;
         const int k = round == 1 ? P.mp_iters_first : P.mp_iters_later;
         rama_round_stats R;
@@ -263,6 +291,7 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
         R.n_contracted = ns;
         R.used_forest = forest ? 1 : 0;
         R.workspace_peak = (int64_t)ctx.active->peak_live();
+        clocked.push_back(ctx.rounds.size());
         ctx.rounds.push_back(R);
         if (ns == 0) break;
     }
@@ -310,11 +339,13 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
     S.n_clusters = n_cur;
     S.n_edges_final = g.m;
     S.ms_total = now_ms() - t_begin;
-    for (size_t r = 0; r < ctx.rounds.size(); ++r) {
+    for (size_t r : clocked) {
         rama_round_stats &R = ctx.rounds[r];
         R.ms_cycles = clock.between((int)r + 1, 0, 1);
         R.ms_dual = clock.between((int)r + 1, 1, 2);
         R.ms_contract = clock.between((int)r + 1, 2, 3);
+    }
+    for (const rama_round_stats &R : ctx.rounds) {
         S.ms_cycles += R.ms_cycles; S.ms_dual += R.ms_dual; S.ms_contract += R.ms_contract;
     }
     S.ms_other = S.ms_total - S.ms_cycles - S.ms_dual - S.ms_contract;
@@ -357,6 +388,11 @@ rama_status rama_create(rama_ctx **out, void *hip_stream, const rama_alloc *allo
         }
     }
     for (int k = 0; k < rama_ctx::kStageEvents && e == hipSuccess; ++k) e = hipEventCreate(&ctx->stage_ev[k]);
+    if (e == hipSuccess) {
+        int khz = 0;
+        e = hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, ctx->device);
+        if (e == hipSuccess && khz > 0) ctx->wall_khz = (double)khz;
+    }
     if (e == hipSuccess && ctx->device >= 0 && ctx->device < kMaxDevices) {
         // every GPU holds its own copy of the static scratch array at its own address
         if (!g_scratch_ptr[ctx->device]) {
@@ -548,6 +584,27 @@ rama_status rama_contract(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const
         const Graph *cur = &g0;
         int32_t n_cur = n_nodes;
         for (;;) {
+            if (tail_fits(*cur)) {
+                Buf<int32_t> ftail;
+                TailResult res;
+                if (cur == &g0) {      // the diagonal still needs the first graph
+                    const size_t room = (size_t)(g0.m > 0 ? g0.m : 1);
+                    RAMA_TRY(g.i.alloc(*ctx, room));
+                    RAMA_TRY(g.j.alloc(*ctx, room));
+                    RAMA_TRY(g.c.alloc(*ctx, room));
+                }
+                RAMA_TRY(tail_rounds(*ctx, *cur, g, false, 0, params->contract_threshold, params->matching_rounds_cap, params->forest_ratio,
+                                     repeat ? 1 : 0, ftail, res));
+                {
+                    ProfScope ps_(*ctx, "k_compose", (double)((size_t)n_nodes * 12));
+                    k_compose<<<grid_for((size_t)n_nodes), kBlock, 0, ctx->stream>>>((size_t)n_nodes, mapping, ftail.get());
+                }
+                LAUNCH_TRY(*ctx, "compose");
+                cur = &g;
+                n_cur = g.n;
+                if (repeat || res.status == kTailDone) break;
+                continue;
+            }
             Buf<int32_t> fprime;
             Graph gn;
             int32_t n_new = n_cur;

@@ -265,7 +265,7 @@ struct rama_ctx {
     // host polls that number for a bounded time instead of going through a stream synchronisation (~9 us
     // instead of ~17 us per round trip measured), and falls back to the synchronisation when the kernels in
     // front of the message take longer.
-    static constexpr size_t kMailWords = 64;          // 8-byte words of one message, word 0 is the number
+    static constexpr size_t kMailWords = 192;         // 8-byte words of one message, word 0 is the number
     uint64_t mail_seq = 0;
     uint32_t *ticket = nullptr;  // device word, zero at rest: "last workgroup to finish" election of the fused scans
     // Flags and counters that must start at zero (a dozen per round, a few words each) are handed out from one
@@ -274,6 +274,7 @@ struct rama_ctx {
     static constexpr size_t kZeroPageWords = size_t(1) << 14;
     uint32_t *zero_page = nullptr;
     size_t zero_used = 0;
+    double wall_khz = 1e5;                     // ticks of the device's wall clock per millisecond
     int cycle_search = 0;                      // see rama_set_cycle_search
     size_t sort_split_min = size_t(1) << 21;   // arrays at least this long may take the split sort ...
     int sort_split_gain = 2;                   // ... when it replaces at least this many passes
@@ -479,6 +480,22 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
 // a4..a6: one primal update.  fmap[n] -> [0,n_new); n_matched = |S|.  If |S|==0 nothing else is produced.
 rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, float forest_ratio, Buf<int32_t> &fmap,
                           int32_t &n_new, Graph &out, int64_t &n_matched, bool *used_forest = nullptr);
+
+// Whole rounds -- separation of triangles (optional) with k_iters iterations of message passing, matching or forest,
+// contraction -- on a graph that one workgroup can hold, by a single launch.  fmap[g.n] -> [0, out.n).  out's arrays
+// (room for g.m edges; they may be g's own) get the graph behind the last round.
+constexpr int kTailEdges = 8192, kTailNodes = 6144;
+constexpr int kTailMaxRounds = 24, kTailRecord = 6;      // rounds per launch, words of a round's record in the message
+constexpr int kTailDone = 0;        // the last round found nothing to contract
+constexpr int kTailMore = 1;        // max_rounds rounds ran, or kTailMaxRounds
+constexpr int kTailTooMany = 2;     // the next round has more triangles than fit: nothing of it was done
+struct TailResult {
+    int status = kTailDone;
+    std::vector<rama_round_stats> rounds;
+};
+inline bool tail_fits(const Graph &g) { return g.n <= kTailNodes && g.m <= kTailEdges; }
+rama_status tail_rounds(Ctx &ctx, const Graph &g, Graph &out, bool separate, int k_iters, float tau, int rounds_cap,
+                        float forest_ratio, int max_rounds, Buf<int32_t> &fmap, TailResult &res);
 
 // diagonal of K^T A K for a mapping F on canonical graph g: diag[a] = sum of edges with F(i)=F(j)=a
 rama_status contraction_diagonal(Ctx &ctx, const Graph &g, const int32_t *fmap, int32_t n_new, float *diag);

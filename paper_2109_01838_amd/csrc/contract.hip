@@ -17,20 +17,11 @@
 //   A'  : endpoints relabelled through f', re-oriented, sorted by (row, col) with the cost as
 //         payload (stable), runs of equal pairs summed in order, loops dropped.
 #include "prim.h"
+#include "steps.h"
 
 namespace rama {
 
 namespace {
-
-__device__ __forceinline__ uint32_t ordered_bits(float x)
-{
-    uint32_t u = __float_as_uint(x + 0.0f);   // -0 and +0 rank alike
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ __forceinline__ unsigned long long edge_rank(float cost, uint32_t e)
-{
-    return ((unsigned long long)ordered_bits(cost) << 32) | (unsigned long long)(0xFFFFFFFFu - e);
-}
 
 struct CandFlag {
     static constexpr int bytes = 4;   // bytes read per item
@@ -324,10 +315,6 @@ __global__ __launch_bounds__(kBlock) void k_inner(size_t m, const int32_t *i, co
     uint32_t p = pos[e];
     key[p] = (uint32_t)a;
     val[p] = __float_as_uint(c[e]);
-// diag[k] = sum of the values of run k of the sorted keys, in order of appearance (an ordered sum is a chain of adds, so
-// what can be saved is the wait for its operands).  A wave takes 64 places; the runs that start there are added up from
-// registers, all of them in step, and the one that goes on behind the 64 places is carried on by the whole wave: it
-// fetches 64 values at a time, the next ones while these are added, and adds them lane by lane.
 }
 
 struct HeadFlag {
@@ -337,6 +324,10 @@ struct HeadFlag {
     __device__ __forceinline__ uint32_t operator()(size_t e) const { return (e == 0 || key[e] != key[e - 1]) ? 1u : 0u; }
 };
 
+// diag[k] = sum of the values of run k of the sorted keys, in order of appearance (an ordered sum is a chain of adds, so
+// what can be saved is the wait for its operands).  A wave takes 64 places; the runs that start there are added up from
+// registers, all of them in step, and the one that goes on behind the 64 places is carried on by the whole wave: it
+// fetches 64 values at a time, the next ones while these are added, and adds them lane by lane.
 __global__ __launch_bounds__(kBlock) void k_diag_runs(size_t m, const uint32_t *key, const uint32_t *val, float *diag)
 {
     const size_t base = (size_t)blockIdx.x * kBlock + (threadIdx.x & ~63u), e = base + lane_id();

@@ -23,6 +23,7 @@
 #include <hip/hip_ext.h>
 
 #include "prim.h"
+#include "steps.h"
 
 namespace rama {
 
@@ -395,28 +396,6 @@ __global__ __launch_bounds__(kBlock) void k_edge_init(size_t na, const uint32_t 
     share[a] = ce[act_edge[a]] / (float)(act_start[a + 1] - act_start[a]);
 }
 
-// costs of the four non-trivial labelings of M_T = {000,110,101,011,111}
-struct TriCosts {
-    float l110, l101, l011, l111;
-};
-__device__ __forceinline__ TriCosts labeling_costs(float a, float b, float c)
-{
-    TriCosts r;
-    r.l110 = a + b;
-    r.l101 = a + c;
-    r.l011 = b + c;
-    r.l111 = (a + b) + c;
-    return r;
-}
-// min-marginal of slot s: min over labelings that cut s minus min over those that do not
-__device__ __forceinline__ float min_marginal(float a, float b, float c, int s)
-{
-    TriCosts l = labeling_costs(a, b, c);
-    if (s == 0) return fminf(fminf(l.l110, l.l101), l.l111) - fminf(0.0f, l.l011);
-    if (s == 1) return fminf(fminf(l.l110, l.l011), l.l111) - fminf(0.0f, l.l101);
-    return fminf(fminf(l.l101, l.l011), l.l111) - fminf(0.0f, l.l110);
-}
-
 // FIRST: the triangles are new and this is their first iteration: their costs are zero and have not been stored
 // (the sum with zero stays, so that the result is the same bit for bit, signs of zeros included).
 template <bool FIRST>
@@ -431,14 +410,8 @@ __global__ __launch_bounds__(kBlock) void k_triangle_update(size_t T, const uint
     float b = (FIRST ? 0.0f : ct[3 * t + 1]) + share[e1];
     float c = (FIRST ? 0.0f : ct[3 * t + 2]) + share[e2];
     // triangles -> edges
-    const float third = 1.0f / 3.0f, half = 1.0f / 2.0f;
-    float oa = 0.0f, ob = 0.0f, oc = 0.0f, d;
-    d = third * min_marginal(a, b, c, 0); a = a - d; oa = oa + d;
-    d = half * min_marginal(a, b, c, 1);  b = b - d; ob = ob + d;
-    d = 1.0f * min_marginal(a, b, c, 2);  c = c - d; oc = oc + d;
-    d = half * min_marginal(a, b, c, 0);  a = a - d; oa = oa + d;
-    d = 1.0f * min_marginal(a, b, c, 1);  b = b - d; ob = ob + d;
-    d = 1.0f * min_marginal(a, b, c, 0);  a = a - d; oa = oa + d;
+    float oa, ob, oc;
+    triangle_to_edges(a, b, c, oa, ob, oc);
     ct[3 * t] = a; ct[3 * t + 1] = b; ct[3 * t + 2] = c;
     msg[3 * t] = oa; msg[3 * t + 1] = ob; msg[3 * t + 2] = oc;
 }

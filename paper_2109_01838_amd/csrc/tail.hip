@@ -1,0 +1,670 @@
+// Whole rounds of the solver on graphs that one workgroup can hold (up to 8192 edges and 6144 nodes).
+//
+// A round of a small graph through the stage kernels is some sixty launches and ten host waits, 250 to 1100 us whatever
+// the size: nothing but latency (2.3 us per dependent launch, 9 us per count the host waits for).  Here one workgroup of
+// 1024 threads keeps the edge list in LDS and runs round after round -- triangles, message passing, matching or
+// spanning forest, contraction -- between barriers, and the host hears of it when it is over.  The arithmetic, its order
+// and every tie are those of the stage kernels, so the results are the same bit for bit.
+//
+// Bounded by barriers and LDS latency (one CU works).  Measured per round: 84 us at 7254 edges (540 through the stage
+// kernels), 48 at 4958 with a forest (1240), 30 at 438 with message passing (390 to 600), 14 at 36 edges.
+#include "prim.h"
+#include "steps.h"
+
+namespace rama {
+
+namespace {
+
+constexpr int kTailThreads = 1024;
+constexpr int kTailWaves = kTailThreads / 64;
+constexpr int kTailItems = kTailEdges / kTailThreads;          // edges per thread
+constexpr int kTailNodeItems = kTailNodes / kTailThreads;      // nodes per thread
+constexpr int kTailTriangles = 2048;                           // more in a round: the stage kernels take it
+constexpr int kTriItems = kTailTriangles / kTailThreads;
+constexpr int kSlotItems = 3 * kTailTriangles / kTailThreads;
+constexpr int kNodeBits = 13;
+constexpr uint32_t kNodeMask = (1u << kNodeBits) - 1u;
+static_assert(kTailNodes <= (1 << kNodeBits) - 1 && kTailEdges <= (1 << 13) && 3 * kTailTriangles <= kTailEdges, "field widths");
+static_assert(kTailEdges % kTailThreads == 0 && kTailNodes % (2 * kTailThreads) == 0, "whole items per thread");
+
+// the work area (in 4-byte words), used by one step after another:
+//   sort        keys [0, 8192), values [8192, 16384), digit counts of the 16 waves [16384, 20480)
+//   separation  row ends [0, 3136) (16 bits each), cursors [3136, 6272), adjacency [6272, 14464) (16-bit edge numbers),
+//               triangles found: keys [14464, 16512), third edges [16512, 18560)
+//   messages    sorted slots as the sort left them, messages [14336, 20480)
+//   matching    rank words [0, 12288), mates [12288, 15360) (16 bits each)
+//   forest      rank words [0, 12288), later depth, parent, edge to it (16 bits each) [0, 9216); components
+//               [12288, 15360), hooks [15360, 18432), forest bits [18432, 18688), removed bits [18688, 18944)
+//   mapping     representatives [0, 6144), new numbers [6144, 9216) (16 bits each)
+constexpr int kWorkWords = 20480;
+constexpr int kSortVal = kTailEdges, kSortHist = 2 * kTailEdges;
+constexpr int kSepCur = 3136, kSepAdj = 6272, kSepKey = 14464, kSepThird = 16512;
+constexpr int kMsg = 14336;
+constexpr int kMate = 12288, kComp = 12288, kHook = 15360, kInForest = 18432, kRemoved = 18688;
+constexpr int kDepth = 0, kUp = 3072, kUpEdge = 6144;
+constexpr int kRep = 0, kNew = 6144;
+static_assert(kSepCur * 2 >= kTailNodes + 1 && kSepAdj + kTailEdges <= kSepKey && kSepThird + kTailTriangles <= kWorkWords, "separation");
+static_assert(kSortVal + 3 * kTailTriangles <= kMsg && kMsg + 3 * kTailTriangles <= kWorkWords, "messages");
+static_assert(2 * kTailNodes <= kMate && kMate + kTailNodes / 2 <= kHook && kHook + kTailNodes / 2 <= kInForest, "matching, forest");
+static_assert(kInForest + kTailEdges / 32 <= kRemoved && kRemoved + kTailEdges / 32 <= kWorkWords, "forest bits");
+static_assert(kSortHist + kTailWaves * kRadix <= kWorkWords, "sort");
+
+struct TailShared {
+    uint32_t key[kTailEdges];      // lo << 13 | hi, ascending
+    float cost[kTailEdges];
+    uint32_t work[kWorkWords];
+    uint32_t wave[kTailWaves];
+    uint32_t digit[4];
+    uint32_t count[4];
+};
+
+struct TailArgs {
+    int32_t n, m;
+    const int32_t *i, *j;          // graph in, graph out (the arrays may be the same)
+    const float *c;
+    int32_t *io, *jo;
+    float *co;
+    int32_t *fmap;                 // [n]: node of the first graph -> node of the last
+    int separate, iters, cap, max_rounds;
+    float tau, forest_ratio;
+    uint64_t *mail;
+    uint64_t seq;
+};
+
+__device__ __forceinline__ int tail_lane() { return (int)(threadIdx.x & 63u); }
+__device__ __forceinline__ int tail_wave() { return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)); }
+
+// exclusive scan over the 1024 threads
+__device__ __forceinline__ uint32_t tail_scan(uint32_t v, uint32_t *total, uint32_t *s_wave)
+{
+    const uint32_t inc = wave_inclusive_scan(v);
+    const int w = tail_wave();
+    if (tail_lane() == 63) s_wave[w] = inc;
+    __syncthreads();
+    uint32_t x = s_wave[tail_lane() & (kTailWaves - 1)];
+    x = wave_inclusive_scan(tail_lane() < kTailWaves ? x : 0u);
+    const uint32_t before = w ? (uint32_t)__builtin_amdgcn_readlane((int)x, w - 1) : 0u;
+    *total = (uint32_t)__builtin_amdgcn_readlane((int)x, kTailWaves - 1);
+    __syncthreads();
+    return before + inc - v;
+}
+
+// Stable sort of cnt (key, value) pairs by the key's low `bits` bits.  Item r of lane l in wave w is number
+// (w*rows + r)*64 + l, rows = ceil(cnt / 1024); the result is in work[0..) and work[kSortVal..).  The passes are those
+// of k_rs_local.
+__device__ __forceinline__ void tail_sort(TailShared &S, uint32_t (&key)[kTailItems], uint32_t (&val)[kTailItems], uint32_t cnt, int bits)
+{
+    uint32_t *skey = S.work, *sval = S.work + kSortVal;
+    uint32_t *whist = S.work + kSortHist;
+    const int tid = (int)threadIdx.x, lane = tail_lane(), w = tail_wave();
+    const int rows = (int)((cnt + kTailThreads - 1) / kTailThreads);
+    const uint32_t base = (uint32_t)(w * rows * 64 + lane);
+    const uint64_t lt = (1ull << lane) - 1ull;
+    uint32_t rank[kTailItems];
+    const int passes = (bits + kRadixBits - 1) / kRadixBits;
+    int shift = 0, remaining = bits;
+    for (int p = 0; p < passes; ++p) {
+        const int b = (remaining + (passes - p) - 1) / (passes - p);
+        const uint32_t mask = (1u << b) - 1u;
+        for (int k = tid; k < kTailWaves * kRadix; k += kTailThreads) whist[k] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kTailItems; ++r)
+            if (r < rows) {
+                const bool valid = base + (uint32_t)r * 64u < cnt;
+                const uint32_t d = (key[r] >> shift) & mask;
+                const uint64_t same = match_digit(d, b, __ballot(valid));
+                uint32_t *h = whist + w * kRadix + d;
+                const uint32_t before = *h;
+                rank[r] = before + (uint32_t)__popcll(same & lt);
+                __builtin_amdgcn_wave_barrier();
+                if (valid && lane == __ffsll((long long)same) - 1) *h = before + (uint32_t)__popcll(same);
+                __builtin_amdgcn_wave_barrier();
+            }
+        __syncthreads();
+        uint32_t c[kTailWaves], tot = 0;
+        if (tid < kRadix) {
+#pragma unroll
+            for (int k = 0; k < kTailWaves; ++k) { c[k] = whist[k * kRadix + tid]; tot += c[k]; }
+        }
+        const uint32_t inc = wave_inclusive_scan(tot);
+        if (tid < kRadix && lane == 63) S.digit[w] = inc;
+        __syncthreads();
+        if (tid < kRadix) {
+            uint32_t run = inc - tot;
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                if (k < w) run += S.digit[k];
+#pragma unroll
+            for (int k = 0; k < kTailWaves; ++k) { whist[k * kRadix + tid] = run; run += c[k]; }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kTailItems; ++r)
+            if (r < rows && base + (uint32_t)r * 64u < cnt) {
+                const uint32_t at = whist[w * kRadix + ((key[r] >> shift) & mask)] + rank[r];
+                skey[at] = key[r];
+                sval[at] = val[r];
+            }
+        __syncthreads();
+        if (p + 1 < passes) {
+#pragma unroll
+            for (int r = 0; r < kTailItems; ++r)
+                if (r < rows && base + (uint32_t)r * 64u < cnt) {
+                    key[r] = skey[base + (uint32_t)r * 64u];
+                    val[r] = sval[base + (uint32_t)r * 64u];
+                }
+        }
+        shift += b;
+        remaining -= b;
+    }
+}
+
+__device__ __forceinline__ int tail_bits(uint32_t n)      // bits for values in [0, n)
+{
+    return n <= 2u ? 1 : 32 - __clz((int)(n - 1u));
+}
+
+// place of an edge in the sorted list, or -1
+__device__ __forceinline__ int tail_find(const TailShared &S, int m, uint32_t key)
+{
+    int lo = 0, hi = m;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (S.key[mid] < key) lo = mid + 1; else hi = mid;
+    }
+    return lo < m && S.key[lo] == key ? lo : -1;
+}
+
+// Triangles with one repulsive edge (a round that separates up to length 3).  Returns their number; up to
+// kTailTriangles of them are in work[kSepKey..) -- (first edge, second edge) -- and work[kSepThird..), in any order.
+__device__ __forceinline__ uint32_t tail_triangles(TailShared &S, int n, int m, uint32_t &n_attractive, uint32_t &n_repulsive)
+{
+    const int tid = (int)threadIdx.x;
+    uint16_t *row_end = (uint16_t *)S.work, *adj = (uint16_t *)(S.work + kSepAdj);
+    for (int k = tid; k < kSepAdj; k += kTailThreads) S.work[k] = 0;      // degrees and cursors
+    if (tid < 3) S.count[tid] = 0;
+    __syncthreads();
+    uint32_t pos = 0, neg = 0;
+#pragma unroll
+    for (int q = 0; q < kTailItems; ++q) {
+        const int e = tid + q * kTailThreads;
+        if (e >= m) continue;
+        const float c = S.cost[e];
+        neg += c < 0.0f ? 1u : 0u;
+        if (c > 0.0f) {
+            ++pos;
+            const uint32_t u = S.key[e] >> kNodeBits, v = S.key[e] & kNodeMask;
+            atomicAdd(&S.work[u >> 1], 1u << (16 * (u & 1)));      // at most 8191 per node: no carry between the halves
+            atomicAdd(&S.work[v >> 1], 1u << (16 * (v & 1)));
+        }
+    }
+    pos = wave_sum(pos); neg = wave_sum(neg);
+    if (tail_lane() == 0) { atomicAdd(&S.count[0], pos); atomicAdd(&S.count[1], neg); }
+    __syncthreads();
+    n_attractive = S.count[0]; n_repulsive = S.count[1];
+    if (n_attractive == 0 || n_repulsive == 0) return 0;
+    uint32_t deg[kTailNodeItems], mine = 0, all;
+#pragma unroll
+    for (int q = 0; q < kTailNodeItems; ++q) { deg[q] = row_end[tid * kTailNodeItems + q]; mine += deg[q]; }
+    uint32_t run = tail_scan(mine, &all, S.wave);
+    uint16_t *cursor = (uint16_t *)(S.work + kSepCur);
+#pragma unroll
+    for (int q = 0; q < kTailNodeItems; ++q) {
+        const int v = tid * kTailNodeItems + q;
+        cursor[v] = (uint16_t)run;
+        run += deg[q];
+        row_end[v] = (uint16_t)run;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kTailItems; ++q) {
+        const int e = tid + q * kTailThreads;
+        if (e < m && S.cost[e] > 0.0f) {
+            const uint32_t u = S.key[e] >> kNodeBits, v = S.key[e] & kNodeMask;
+            const uint32_t au = atomicAdd(&S.work[kSepCur + (u >> 1)], 1u << (16 * (u & 1)));
+            const uint32_t av = atomicAdd(&S.work[kSepCur + (v >> 1)], 1u << (16 * (v & 1)));
+            adj[(au >> (16 * (u & 1))) & 0xffffu] = (uint16_t)e;
+            adj[(av >> (16 * (v & 1))) & 0xffffu] = (uint16_t)e;
+        }
+    }
+    __syncthreads();
+    for (int q = 0; q < kTailItems; ++q) {
+        const int e = tid + q * kTailThreads;
+        if (e >= m || !(S.cost[e] < 0.0f)) continue;
+        uint32_t s = S.key[e] >> kNodeBits, o = S.key[e] & kNodeMask;
+        int s0 = s ? row_end[s - 1] : 0, s1 = row_end[s];
+        const int o0 = o ? row_end[o - 1] : 0, o1 = row_end[o];
+        if (s1 - s0 > o1 - o0) { const uint32_t t = s; s = o; o = t; s0 = o0; s1 = o1; }
+        if (o0 == o1) continue;
+        for (int p = s0; p < s1; ++p) {
+            const int a = adj[p];
+            const uint32_t lo = S.key[a] >> kNodeBits, hi = S.key[a] & kNodeMask, x = lo == s ? hi : lo;
+            const int b = tail_find(S, m, min(x, o) << kNodeBits | max(x, o));
+            if (b < 0 || !(S.cost[b] > 0.0f)) continue;
+            // the edges (u,v), (u,w), (v,w) of a triangle u < v < w stand in this order in the list
+            const int e0 = min(e, min(a, b)), e2 = max(e, max(a, b)), e1 = e + a + b - e0 - e2;
+            const uint32_t at = atomicAdd(&S.count[2], 1u);
+            if (at < (uint32_t)kTailTriangles) {
+                S.work[kSepKey + at] = (uint32_t)e0 << 13 | (uint32_t)e1;
+                S.work[kSepThird + at] = (uint32_t)e2;
+            }
+        }
+    }
+    __syncthreads();
+    return S.count[2];
+}
+
+// `iters` iterations of message passing over the T <= kTailTriangles triangles tail_triangles left behind
+__device__ __forceinline__ void tail_messages(TailShared &S, int m, uint32_t T, int iters)
+{
+    const int tid = (int)threadIdx.x, lane = tail_lane(), w = tail_wave();
+    const int ebits = tail_bits((uint32_t)m);
+    uint32_t *skey = S.work, *sval = S.work + kSortVal;
+    uint32_t key[kTailItems] = {}, val[kTailItems] = {};
+    {
+        const uint32_t rows = (T + kTailThreads - 1) / kTailThreads, base = (uint32_t)w * rows * 64u + (uint32_t)lane;
+#pragma unroll
+        for (int r = 0; r < kTriItems; ++r)
+            if ((uint32_t)r < rows && base + (uint32_t)r * 64u < T) {
+                key[r] = S.work[kSepKey + base + (uint32_t)r * 64u];
+                val[r] = S.work[kSepThird + base + (uint32_t)r * 64u];
+            }
+    }
+    __syncthreads();
+    tail_sort(S, key, val, T, 13 + ebits);
+    uint32_t e0[kTriItems] = {}, e1[kTriItems] = {}, e2[kTriItems] = {};
+#pragma unroll
+    for (int q = 0; q < kTriItems; ++q) {
+        const uint32_t t = (uint32_t)(tid + q * kTailThreads);
+        if (t < T) { e0[q] = skey[t] >> 13; e1[q] = skey[t] & 8191u; e2[q] = sval[t]; }
+    }
+    // slots 3t, 3t+1, 3t+2 of triangle t, sorted by edge (stable: an edge's slots ascend)
+    const uint32_t ns = 3 * T;
+    {
+        const uint32_t rows = (ns + kTailThreads - 1) / kTailThreads, base = (uint32_t)w * rows * 64u + (uint32_t)lane;
+#pragma unroll
+        for (int r = 0; r < kSlotItems; ++r) {
+            const uint32_t s = base + (uint32_t)r * 64u;
+            if ((uint32_t)r < rows && s < ns) {
+                const uint32_t t = s / 3u, k = s - 3u * t;
+                key[r] = k == 0 ? skey[t] >> 13 : k == 1 ? skey[t] & 8191u : sval[t];
+                val[r] = s;
+            }
+        }
+    }
+    __syncthreads();
+    tail_sort(S, key, val, ns, ebits);
+    uint32_t len[kSlotItems], edge[kSlotItems];
+#pragma unroll
+    for (int q = 0; q < kSlotItems; ++q) {      // the run of slots that starts at place p
+        const uint32_t p = (uint32_t)(tid + q * kTailThreads);
+        len[q] = 0; edge[q] = 0;
+        if (p < ns && (p == 0 || skey[p] != skey[p - 1])) {
+            edge[q] = skey[p];
+            uint32_t end = p + 1;
+            while (end < ns && skey[end] == edge[q]) ++end;
+            len[q] = end - p;
+            S.cost[edge[q]] = S.cost[edge[q]] / (float)len[q];      // from here to the last iteration: the share
+        }
+    }
+    __syncthreads();
+    float *msg = reinterpret_cast<float *>(S.work + kMsg);
+    float a[kTriItems] = {}, b[kTriItems] = {}, c[kTriItems] = {};
+    for (int it = 1; it <= iters; ++it) {
+#pragma unroll
+        for (int q = 0; q < kTriItems; ++q) {
+            const uint32_t t = (uint32_t)(tid + q * kTailThreads);
+            if (t < T) {
+                a[q] = a[q] + S.cost[e0[q]]; b[q] = b[q] + S.cost[e1[q]]; c[q] = c[q] + S.cost[e2[q]];
+                float oa, ob, oc;
+                triangle_to_edges(a[q], b[q], c[q], oa, ob, oc);
+                msg[3 * t] = oa; msg[3 * t + 1] = ob; msg[3 * t + 2] = oc;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kSlotItems; ++q)
+            if (len[q]) {
+                const uint32_t p = (uint32_t)(tid + q * kTailThreads);
+                float acc = 0.0f;
+                for (uint32_t s = 0; s < len[q]; ++s) acc = acc + msg[sval[p + s]];
+                S.cost[edge[q]] = it == iters ? acc : acc / (float)len[q];
+            }
+        __syncthreads();
+    }
+}
+
+// handshake matching; mates (0xffff: none) in work[kMate..); returns the number of pairs
+__device__ __forceinline__ uint32_t tail_matching(TailShared &S, int n, int m, float tau, int cap)
+{
+    const int tid = (int)threadIdx.x;
+    unsigned long long *best = reinterpret_cast<unsigned long long *>(S.work);
+    uint16_t *mate = (uint16_t *)(S.work + kMate);
+    for (int k = tid; k < kTailNodes / 2; k += kTailThreads) S.work[kMate + k] = 0xffffffffu;
+    uint32_t alive = 0, made = 0, uv[kTailItems];
+    unsigned long long rank[kTailItems];
+#pragma unroll
+    for (int q = 0; q < kTailItems; ++q) {
+        const int e = tid + q * kTailThreads;
+        uv[q] = 0; rank[q] = 0;
+        if (e < m && S.cost[e] > tau) {
+            alive |= 1u << q;
+            uv[q] = S.key[e];
+            rank[q] = edge_rank(S.cost[e], (uint32_t)e);
+        }
+    }
+    for (int r = 0; r < cap; ++r) {
+        if (!__syncthreads_or(alive != 0u)) break;
+        for (int v = tid; v < n; v += kTailThreads) best[v] = 0ull;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kTailItems; ++q)
+            if (alive & (1u << q)) {
+                atomicMax(&best[uv[q] >> kNodeBits], rank[q]);
+                atomicMax(&best[uv[q] & kNodeMask], rank[q]);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kTailItems; ++q)
+            if (alive & (1u << q)) {
+                const uint32_t u = uv[q] >> kNodeBits, v = uv[q] & kNodeMask;
+                if (best[u] == rank[q] && best[v] == rank[q]) { mate[u] = (uint16_t)v; mate[v] = (uint16_t)u; ++made; }
+            }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kTailItems; ++q)
+            if ((alive & (1u << q)) && (mate[uv[q] >> kNodeBits] != 0xffffu || mate[uv[q] & kNodeMask] != 0xffffu)) alive &= ~(1u << q);
+    }
+    uint32_t all;
+    (void)tail_scan(made, &all, S.wave);
+    return all;
+}
+
+// S by the spanning forest without conflicts; returns |S|, representatives (smallest node of the component of (V,S)) in
+// work[kRep..)
+__device__ __forceinline__ uint32_t tail_forest(TailShared &S, int n, int m, float tau)
+{
+    const int tid = (int)threadIdx.x;
+    unsigned long long *best = reinterpret_cast<unsigned long long *>(S.work);
+    uint16_t *comp = (uint16_t *)(S.work + kComp), *hook = (uint16_t *)(S.work + kHook);
+    for (int v = tid; v < kTailNodes; v += kTailThreads) { comp[v] = (uint16_t)v; hook[v] = (uint16_t)v; best[v] = 0ull; }
+    for (int k = tid; k < kTailEdges / 32; k += kTailThreads) { S.work[kInForest + k] = 0u; S.work[kRemoved + k] = 0u; }
+    uint32_t alive = 0;
+#pragma unroll
+    for (int q = 0; q < kTailItems; ++q) {
+        const int e = tid + q * kTailThreads;
+        if (e < m && S.cost[e] > tau) alive |= 1u << q;
+    }
+    // Boruvka rounds; every one at least halves the number of components that have a candidate left
+    for (int round = 0; round < 64; ++round) {
+        if (!__syncthreads_or(alive != 0u)) break;
+        for (int q = 0; q < kTailItems; ++q) {
+            const int e = tid + q * kTailThreads;
+            if (!(alive & (1u << q))) continue;
+            const uint32_t cu = comp[S.key[e] >> kNodeBits], cv = comp[S.key[e] & kNodeMask];
+            const unsigned long long r = edge_rank(S.cost[e], (uint32_t)e);
+            atomicMax(&best[cu], r);
+            atomicMax(&best[cv], r);
+        }
+        __syncthreads();
+        for (int q = 0; q < kTailItems; ++q) {
+            const int e = tid + q * kTailThreads;
+            if (!(alive & (1u << q))) continue;
+            const uint32_t cu = comp[S.key[e] >> kNodeBits], cv = comp[S.key[e] & kNodeMask];
+            const unsigned long long r = edge_rank(S.cost[e], (uint32_t)e);
+            const bool bu = best[cu] == r, bv = best[cv] == r;
+            if (!(bu || bv)) continue;
+            atomicOr(&S.work[kInForest + (e >> 5)], 1u << (e & 31));
+            if (bu && !(bv && cu < cv)) hook[cu] = (uint16_t)cv;
+            if (bv && !(bu && cv < cu)) hook[cv] = (uint16_t)cu;
+        }
+        __syncthreads();
+        for (int v = tid; v < n; v += kTailThreads) {
+            uint32_t r = comp[v], h = hook[r];
+            while (h != r) { r = h; h = hook[r]; }      // the hook graph is a forest: every chain ends in a root
+            comp[v] = (uint16_t)r;
+        }
+        __syncthreads();
+        for (int v = tid; v < n; v += kTailThreads) { best[v] = 0ull; hook[v] = (uint16_t)v; }   // comp[] holds roots only
+        for (int q = 0; q < kTailItems; ++q) {
+            const int e = tid + q * kTailThreads;
+            if ((alive & (1u << q)) && comp[S.key[e] >> kNodeBits] == comp[S.key[e] & kNodeMask]) alive &= ~(1u << q);
+        }
+    }
+    // rooting at the component representatives, breadth first
+    uint16_t *depth = (uint16_t *)(S.work + kDepth), *up = (uint16_t *)(S.work + kUp), *up_edge = (uint16_t *)(S.work + kUpEdge);
+    for (int v = tid; v < n; v += kTailThreads) { depth[v] = comp[v] == v ? 0 : 0xffffu; up[v] = (uint16_t)v; }
+    uint32_t tree = 0;      // own forest edges
+#pragma unroll
+    for (int q = 0; q < kTailItems; ++q) {
+        const int e = tid + q * kTailThreads;
+        if (e < m && (S.work[kInForest + (e >> 5)] >> (e & 31)) & 1u) tree |= 1u << q;
+    }
+    __syncthreads();
+    for (uint32_t lvl = 0; lvl < (uint32_t)n; ++lvl) {      // the sweep behind the deepest level changes nothing
+        bool changed = false;
+        for (int q = 0; q < kTailItems; ++q) {
+            if (!(tree & (1u << q))) continue;
+            const int e = tid + q * kTailThreads;
+            const uint32_t a = S.key[e] >> kNodeBits, b = S.key[e] & kNodeMask;
+            const uint32_t da = depth[a], db = depth[b];
+            // a tree: nobody else reaches the child on this level
+            if (da == lvl && db == 0xffffu) { depth[b] = (uint16_t)(lvl + 1); up[b] = (uint16_t)a; up_edge[b] = (uint16_t)e; changed = true; }
+            else if (db == lvl && da == 0xffffu) { depth[a] = (uint16_t)(lvl + 1); up[a] = (uint16_t)b; up_edge[a] = (uint16_t)e; changed = true; }
+        }
+        if (!__syncthreads_or(changed)) break;
+    }
+    for (int q = 0; q < kTailItems; ++q) {      // the lowest edge on the tree path of every repulsive edge
+        const int e = tid + q * kTailThreads;
+        if (e >= m || !(S.cost[e] < 0.0f)) continue;
+        uint32_t a = S.key[e] >> kNodeBits, b = S.key[e] & kNodeMask;
+        if (comp[a] != comp[b]) continue;
+        uint32_t da = depth[a], db = depth[b], low_e = 0;
+        unsigned long long low = ~0ull;
+        while (a != b) {
+            uint32_t pe;
+            if (da >= db) { pe = up_edge[a]; a = up[a]; --da; } else { pe = up_edge[b]; b = up[b]; --db; }
+            const unsigned long long r = edge_rank(S.cost[pe], pe);
+            if (r < low) { low = r; low_e = pe; }
+        }
+        if (low != ~0ull) atomicOr(&S.work[kRemoved + (low_e >> 5)], 1u << (low_e & 31));
+    }
+    __syncthreads();
+    uint32_t kept = 0;
+    for (int q = 0; q < kTailItems; ++q) {
+        const int e = tid + q * kTailThreads;
+        if ((tree & (1u << q)) && (S.work[kRemoved + (e >> 5)] >> (e & 31)) & 1u) tree &= ~(1u << q);
+        kept += (tree >> q) & 1u;
+    }
+    uint32_t all;
+    (void)tail_scan(kept, &all, S.wave);
+    // components: hooking of the larger root onto the smaller, pointers only ever decrease
+    uint32_t *rep = S.work + kRep;
+    for (int v = tid; v < n; v += kTailThreads) rep[v] = (uint32_t)v;
+    __syncthreads();
+    for (int sweep = 0; sweep < 64; ++sweep) {
+        bool changed = false;
+        for (int q = 0; q < kTailItems; ++q) {
+            if (!(tree & (1u << q))) continue;
+            const uint32_t k = S.key[tid + q * kTailThreads];
+            uint32_t a = k >> kNodeBits, b = k & kNodeMask;
+            for (uint32_t p = rep[a]; p != a; p = rep[a]) a = p;
+            for (uint32_t p = rep[b]; p != b; p = rep[b]) b = p;
+            if (a != b) { atomicMin(&rep[max(a, b)], min(a, b)); changed = true; }
+        }
+        if (!__syncthreads_or(changed)) break;
+    }
+    for (int v = tid; v < n; v += kTailThreads) {
+        uint32_t r = rep[v];
+        for (uint32_t p = rep[r]; p != r; p = rep[r]) r = p;
+        rep[v] = r;      // a shorter way to the same root: no walk of another thread goes wrong
+    }
+    __syncthreads();
+    return all;
+}
+
+__global__ __launch_bounds__(kTailThreads) void k_tail_rounds(TailArgs A)
+{
+    __shared__ TailShared S;
+    const int tid = (int)threadIdx.x, lane = tail_lane(), w = tail_wave();
+    int n = A.n, m = A.m;
+    for (int e = tid; e < m; e += kTailThreads) {
+        S.key[e] = (uint32_t)A.i[e] << kNodeBits | (uint32_t)A.j[e];
+        S.cost[e] = A.c[e];
+    }
+    for (int v = tid; v < A.n; v += kTailThreads) A.fmap[v] = v;
+    __syncthreads();
+    uint64_t *rec = A.mail + 3;
+    uint32_t status = kTailMore, rounds = 0;
+    while (rounds < (uint32_t)A.max_rounds) {
+        const uint64_t t0 = wall_clock64();
+        uint32_t T = 0, n_attractive = 0, n_repulsive = 0;
+        if (A.separate) T = tail_triangles(S, n, m, n_attractive, n_repulsive);
+        if (T > (uint32_t)kTailTriangles) { status = kTailTooMany; break; }
+        const uint64_t t1 = wall_clock64();
+        if (T) tail_messages(S, m, T, A.iters);
+        const uint64_t t2 = wall_clock64();
+        uint32_t ns = tail_matching(S, n, m, A.tau, A.cap);
+        bool forest = false;
+        uint32_t *rep = S.work + kRep;
+        uint16_t *fnew = (uint16_t *)(S.work + kNew);
+        if (ns && A.forest_ratio > 0.0f && (double)ns < (double)A.forest_ratio * (double)n) {
+            forest = true;
+            ns = tail_forest(S, n, m, A.tau);
+        } else if (ns) {
+            const uint16_t *mate = (const uint16_t *)(S.work + kMate);
+            for (int v = tid; v < n; v += kTailThreads) rep[v] = mate[v] < v ? mate[v] : (uint32_t)v;
+            __syncthreads();
+        }
+        const int n_old = n, m_old = m;
+        if (ns) {
+            // new numbers: ranks of the representatives
+            uint32_t root = 0, n_new;
+#pragma unroll
+            for (int q = 0; q < kTailNodeItems; ++q) {
+                const int v = tid * kTailNodeItems + q;
+                root += v < n && rep[v] == (uint32_t)v ? 1u : 0u;
+            }
+            uint32_t run = tail_scan(root, &n_new, S.wave);
+#pragma unroll
+            for (int q = 0; q < kTailNodeItems; ++q) {
+                const int v = tid * kTailNodeItems + q;
+                if (v < n && rep[v] == (uint32_t)v) fnew[v] = (uint16_t)run++;
+            }
+            __syncthreads();
+            for (int v = tid; v < n; v += kTailThreads)
+                if (rep[v] != (uint32_t)v) fnew[v] = fnew[rep[v]];
+            __syncthreads();
+            for (int v = tid; v < A.n; v += kTailThreads) A.fmap[v] = fnew[A.fmap[v]];   // always the same thread's entries
+            // relabelled edges, loops behind everything else; sorted, runs summed in order
+            const int nb = tail_bits(n_new);
+            const uint32_t fmask = (1u << nb) - 1u, loop_key = 0xffffffffu >> (32 - 2 * nb);
+            const uint32_t rows = ((uint32_t)m + kTailThreads - 1) / kTailThreads, base = (uint32_t)w * rows * 64u + (uint32_t)lane;
+            uint32_t key[kTailItems] = {}, val[kTailItems] = {}, stays = 0, kept;
+#pragma unroll
+            for (int r = 0; r < kTailItems; ++r) {
+                const uint32_t e = base + (uint32_t)r * 64u;
+                if ((uint32_t)r < rows && e < (uint32_t)m) {
+                    const uint32_t a = fnew[S.key[e] >> kNodeBits], b = fnew[S.key[e] & kNodeMask];
+                    key[r] = a == b ? loop_key : min(a, b) << nb | max(a, b);
+                    val[r] = __float_as_uint(S.cost[e]);
+                    stays += a != b ? 1u : 0u;
+                }
+            }
+            (void)tail_scan(stays, &kept, S.wave);
+            tail_sort(S, key, val, (uint32_t)m, 2 * nb);
+            const uint32_t *skey = S.work, *sval = S.work + kSortVal;
+            uint32_t heads = 0, place[kTailItems], carry = 0;
+#pragma unroll
+            for (int r = 0; r < kTailItems; ++r) {
+                const uint32_t p = base + (uint32_t)r * 64u;
+                const bool head = (uint32_t)r < rows && p < kept && (p == 0 || skey[p] != skey[p - 1]);
+                const uint64_t vote = __ballot(head);
+                place[r] = carry + (uint32_t)__popcll(vote & ((1ull << lane) - 1ull));
+                carry += (uint32_t)__popcll(vote);
+                heads |= head ? 1u << r : 0u;
+            }
+            uint32_t m_new;
+            const uint32_t first = tail_scan(lane == 0 ? carry : 0u, &m_new, S.wave);
+            const uint32_t before = (uint32_t)__builtin_amdgcn_readfirstlane((int)first);      // heads of the waves in front
+#pragma unroll
+            for (int r = 0; r < kTailItems; ++r)
+                if (heads & (1u << r)) {
+                    uint32_t p = base + (uint32_t)r * 64u;
+                    const uint32_t k = skey[p];
+                    float acc = __uint_as_float(sval[p]);
+                    for (++p; p < kept && skey[p] == k; ++p) acc = acc + __uint_as_float(sval[p]);
+                    S.key[before + place[r]] = (k >> nb) << kNodeBits | (k & fmask);
+                    S.cost[before + place[r]] = acc;
+                }
+            __syncthreads();
+            n = (int)n_new; m = (int)m_new;
+        }
+        if (tid == 0) {
+            const uint64_t t3 = wall_clock64();
+            rec[0] = (uint64_t)(uint32_t)n_old | (uint64_t)(uint32_t)m_old << 32;
+            rec[1] = (uint64_t)n_attractive | (uint64_t)n_repulsive << 32;
+            rec[2] = (uint64_t)T | (uint64_t)(forest ? 1u : 0u) << 32;
+            rec[3] = (uint64_t)ns;
+            rec[4] = (uint64_t)(uint32_t)(t1 - t0) | (uint64_t)(uint32_t)(t2 - t1) << 32;
+            rec[5] = (uint64_t)(t3 - t2);
+        }
+        rec += kTailRecord;
+        ++rounds;
+        if (ns == 0) { status = kTailDone; break; }
+    }
+    for (int e = tid; e < m; e += kTailThreads) {
+        A.io[e] = (int32_t)(S.key[e] >> kNodeBits);
+        A.jo[e] = (int32_t)(S.key[e] & kNodeMask);
+        A.co[e] = S.cost[e];
+    }
+    if (tid == 0) {
+        A.mail[1] = (uint64_t)status | (uint64_t)rounds << 32;
+        A.mail[2] = (uint64_t)(uint32_t)n | (uint64_t)(uint32_t)m << 32;
+    }
+    mail_send(A.mail, A.seq);
+}
+
+}  // namespace
+
+rama_status tail_rounds(Ctx &ctx, const Graph &g, Graph &out, bool separate, int k_iters, float tau, int rounds_cap,
+                        float forest_ratio, int max_rounds, Buf<int32_t> &fmap, TailResult &res)
+{
+    if (!tail_fits(g)) return fail(ctx, RAMA_ERR_INVALID_ARG, "tail_rounds: graph too large");
+    RAMA_TRY(fmap.alloc(ctx, (size_t)(g.n > 0 ? g.n : 1)));
+    static_assert(3 + kTailMaxRounds * kTailRecord <= (int)Ctx::kMailWords, "a record per round in one message");
+    if (max_rounds <= 0 || max_rounds > kTailMaxRounds) max_rounds = kTailMaxRounds;
+    const uint64_t seq = ++ctx.mail_seq;
+    {
+        ProfScope ps_(ctx, "k_tail_rounds", (double)((size_t)g.m * 24 + (size_t)g.n * 4));
+        k_tail_rounds<<<1, kTailThreads, 0, ctx.stream>>>(TailArgs{g.n, (int32_t)g.m, g.i.get(), g.j.get(), g.c.get(), out.i.get(), out.j.get(),
+                                                                  out.c.get(), fmap.get(), separate ? 1 : 0, k_iters, rounds_cap > 0 ? rounds_cap : 0,
+                                                                  max_rounds, tau, forest_ratio, mailbox(ctx), seq});
+    }
+    LAUNCH_TRY(ctx, "tail_rounds");
+    RAMA_TRY(wait_mail(ctx, seq));
+    const volatile uint64_t *mail = mailbox(ctx);
+    auto lo = [](uint64_t x) { return (int64_t)(uint32_t)x; };
+    auto hi = [](uint64_t x) { return (int64_t)(x >> 32); };
+    res.status = (int)lo(mail[1]);
+    res.rounds.clear();
+    for (int r = 0; r < (int)hi(mail[1]); ++r) {
+        const volatile uint64_t *w = mail + 3 + r * kTailRecord;
+        rama_round_stats R;
+        memset(&R, 0, sizeof R);
+        R.n_nodes = (int32_t)lo(w[0]); R.n_edges = hi(w[0]); R.n_edges_aug = hi(w[0]);
+        R.n_attractive = separate ? lo(w[1]) : -1; R.n_repulsive = separate ? hi(w[1]) : -1;
+        R.n_cycles[0] = lo(w[2]); R.n_triangles = lo(w[2]); R.used_forest = (int32_t)hi(w[2]);
+        R.n_contracted = lo(w[3]);
+        R.ms_cycles = (double)lo(w[4]) / ctx.wall_khz; R.ms_dual = (double)hi(w[4]) / ctx.wall_khz;
+        R.ms_contract = (double)w[5] / ctx.wall_khz;
+        res.rounds.push_back(R);
+    }
+    out.n = (int32_t)lo(mail[2]);
+    out.m = hi(mail[2]);
+    out.sign_sums.reset();
+    return RAMA_OK;
+}
+
+}  // namespace rama

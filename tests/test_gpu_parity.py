@@ -442,6 +442,47 @@ def test_diagonal_of_long_runs(rama, oracle32, sizes):
     assert np.array_equal(np_(got["diag"]), want["diag"][: len(sizes)])
 
 
+# --------------------------------------------------------------------------------------------
+# whole rounds in one workgroup: graphs of up to 8192 edges and 6144 nodes
+# --------------------------------------------------------------------------------------------
+TAIL_SIZES = [(2, 1), (3, 3), (64, 63), (90, 1023), (90, 1024), (91, 1025), (700, 5000), (128, 8128), (3000, 8191), (3000, 8192),
+              (3000, 8193), (6143, 8192), (6144, 8192), (6145, 8192)]
+
+
+@pytest.mark.parametrize("n,m", TAIL_SIZES)
+@pytest.mark.parametrize("repeat,ratio,pos", [(1, 0.1, 0.8), (0, 0.1, 0.6), (0, 1.0, 0.8), (0, 0.0, 0.9)])
+def test_contraction_in_one_workgroup(rama, oracle32, n, m, repeat, ratio, pos):
+    """Both sides of the limits; matching, forest and mixed; ties among the costs (a few values only)."""
+    from paper_2109_01838_amd import default_params
+    g = signed(inputs.random_graph(n, m, n + m), 5, pos)
+    c = g["c"] if m % 2 else (np.round(g["c"] * 2) / 2).astype(np.float32)
+    want = oracle32.contract(n, g["i"], g["j"], c, repeat=repeat, forest_ratio=ratio)
+    got = rama.contract(n, g["i"], g["j"], c, params=default_params(forest_ratio=ratio), repeat=repeat)
+    assert got["n_nodes"] == want["n_nodes"]
+    assert np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+    assert np.array_equal(np_(got["diag"]), want["diag"][: got["n_nodes"]])
+
+
+@pytest.mark.parametrize("n,m,pos", [(64, 300, 0.7), (90, 2000, 0.9), (128, 8128, 0.75), (128, 8128, 0.97), (1000, 8000, 0.8), (4000, 8200, 0.9),
+                                     (400, 6000, 0.9), (8000, 20000, 0.85)])
+@pytest.mark.parametrize("later,iters,max_rounds", [(3, 5, 0), (3, 1, 3), (0, 0, 0), (3, 12, 2)])
+def test_solve_rounds_in_one_workgroup(rama, oracle32, n, m, pos, later, iters, max_rounds):
+    """Rounds behind the first on small graphs, with and without triangles (up to and beyond the 2048 that fit)."""
+    from paper_2109_01838_amd import default_params
+    g = signed(inputs.random_graph(n, m, 3 * n + m), 9, pos)
+    want = oracle32.solve(n, g["i"], g["j"], g["c"], max_cycle_len_first=3, max_cycle_len_later=later, mp_iters_first=2, mp_iters_later=iters,
+                          max_rounds=max_rounds)
+    p = default_params(max_cycle_len_first=3, max_cycle_len_later=later, mp_iters_first=2, mp_iters_later=iters, max_rounds=max_rounds)
+    got = rama.solve(n, g["i"], g["j"], g["c"], p)
+    assert got["rounds"] == want["rounds"] and got["n_clusters"] == want["n_clusters"]
+    assert np.array_equal(np_(got["labels"]), want["labels"])
+    assert rel_close(got["primal"], want["primal"], 1e-9) and rel_close(got["lower_bound"], want["lower_bound"], 1e-6)
+    rounds = rama.round_stats()
+    assert len(rounds) == got["rounds"] and rounds[-1]["n_edges_aug"] >= got["n_edges_final"]
+
+
 def test_contract_fig2_graph(rama, oracle32):
     # the graph of the paper's Fig. 2; with the matching rule S={st} (cost 4 is the best edge at s and t;
     # rs=3 loses at s), so only the mechanics are compared with the oracle here

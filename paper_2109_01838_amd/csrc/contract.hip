@@ -531,10 +531,172 @@ __global__ __launch_bounds__(kBlock) void k_mark_conflicts(size_t m, const int32
     if (low != ~0ull) removed[low_e] = 1;
 }
 
+// ---- the same for a short candidate list: one workgroup ----------------------------------------------------------
+// The rounds that fall back to the forest are late ones: few candidates are left, and the kernels above spend their time
+// on launches (four per Boruvka round, one per level of the trees, one per sweep over the components) and on the counts
+// the host looks at in between, 1.0 to 1.9 ms a forest.  One workgroup of 1024 threads walks through all of it between
+// barriers, each thread with up to 32 candidates; only nodes that have a candidate are touched (comp, hook, rep and best
+// start out as v, v, v and 0 for all nodes).  61x97x131 grid, three forests: 10.55 -> 10.16 ms a solve;
+// 6-NN graph of 10^6 points, one forest: 15.54 -> 15.37.
+constexpr uint32_t kShortForest = 32768;
+constexpr int kForestThreads = 1024;
+static_assert(kShortForest == 32u * kForestThreads, "a bit per candidate of a thread");
+
+// words that atomics of the same launch change are read where the atomics are carried out
+template <typename T>
+__device__ __forceinline__ T load_past_cache(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+__global__ __launch_bounds__(kBlock) void k_forest_init(size_t n, int32_t *comp, int32_t *hook, int32_t *rep, unsigned long long *best)
+{
+    const size_t v = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (v >= n) return;
+    comp[v] = (int32_t)v; hook[v] = (int32_t)v; rep[v] = (int32_t)v;
+    best[v] = 0ull;
+}
+
+// forest and rooting; state[k] = 1 iff candidate k is in the forest, up_cand[v] = candidate that joins v to its parent
+__global__ __launch_bounds__(kForestThreads) void k_forest_short(uint32_t na, Cands a, int32_t *comp, int32_t *hook, unsigned long long *best,
+                                                                 int32_t *depth, int32_t *up, uint32_t *up_cand, uint8_t *state)
+{
+    const uint32_t tid = threadIdx.x;
+    uint32_t own = 0, tree = 0;      // this thread's candidates tid, tid + 1024, ..; those in the forest
+    for (uint32_t q = 0; q < 32 && tid + q * kForestThreads < na; ++q) own |= 1u << q;
+    uint32_t alive = own;
+    for (int round = 0; round < 64; ++round) {      // the number of components with an outgoing candidate at least halves
+        for (uint32_t left = alive; left; left &= left - 1) {
+            const uint32_t k = tid + (uint32_t)(__ffs((int)left) - 1) * kForestThreads;
+            const unsigned long long r = a.r[k];
+            atomicMax(&best[comp[a.u[k]]], r);
+            atomicMax(&best[comp[a.v[k]]], r);
+        }
+        if (!__syncthreads_or(alive != 0u)) break;
+        for (uint32_t left = alive; left; left &= left - 1) {
+            const int q = __ffs((int)left) - 1;
+            const uint32_t k = tid + (uint32_t)q * kForestThreads;
+            const int32_t cu = comp[a.u[k]], cv = comp[a.v[k]];
+            const unsigned long long r = a.r[k];
+            const bool bu = load_past_cache(&best[cu]) == r, bv = load_past_cache(&best[cv]) == r;
+            if (!(bu || bv)) continue;
+            tree |= 1u << q;
+            if (bu && !(bv && cu < cv)) hook[cu] = cv;
+            if (bv && !(bu && cv < cu)) hook[cv] = cu;
+        }
+        __syncthreads();
+        // the hook graph is a forest and a root hooks onto itself: every chain ends
+        uint32_t next = alive;
+        for (uint32_t left = alive; left; left &= left - 1) {
+            const int q = __ffs((int)left) - 1;
+            const uint32_t k = tid + (uint32_t)q * kForestThreads;
+            const int32_t u = a.u[k], v = a.v[k];
+            int32_t ru = comp[u], rv = comp[v];
+            for (int32_t h = hook[ru]; h != ru; h = hook[ru]) ru = h;
+            for (int32_t h = hook[rv]; h != rv; h = hook[rv]) rv = h;
+            comp[u] = ru; comp[v] = rv;      // several threads may write, all of them the same root
+            if (ru == rv) next &= ~(1u << q);
+            best[ru] = 0ull; best[rv] = 0ull;
+        }
+        alive = next;
+        __syncthreads();
+    }
+    for (uint32_t left = own; left; left &= left - 1) {
+        const uint32_t k = tid + (uint32_t)(__ffs((int)left) - 1) * kForestThreads;
+        const int32_t e[2] = {a.u[k], a.v[k]};
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            int32_t r = comp[e[s]];
+            for (int32_t h = hook[r]; h != r; h = hook[r]) r = h;
+            comp[e[s]] = r;
+            depth[e[s]] = r == e[s] ? 0 : -1;
+            up[e[s]] = e[s];
+        }
+        state[k] = (uint8_t)((tree >> ((k - tid) / kForestThreads)) & 1u);
+    }
+    __syncthreads();
+    for (int32_t lvl = 0; lvl <= (int32_t)na; ++lvl) {      // a tree of na edges is at most na levels deep
+        bool changed = false;
+        for (uint32_t left = tree; left; left &= left - 1) {
+            const int q = __ffs((int)left) - 1;
+            const uint32_t k = tid + (uint32_t)q * kForestThreads;
+            const int32_t u = a.u[k], v = a.v[k], du = depth[u], dv = depth[v];
+            // a tree: nobody else reaches the child on this level
+            if (du == lvl && dv < 0) { depth[v] = lvl + 1; up[v] = u; up_cand[v] = k; changed = true; }
+            else if (dv == lvl && du < 0) { depth[u] = lvl + 1; up[u] = v; up_cand[u] = k; changed = true; }
+            if (du >= 0 && dv >= 0) tree &= ~(1u << q);      // both ends rooted: done with this edge
+        }
+        if (!__syncthreads_or(changed)) break;
+    }
+}
+
+// as k_mark_conflicts, on candidate numbers: state 2 = removed
+__global__ __launch_bounds__(kBlock) void k_mark_conflicts_short(size_t m, const int32_t *i, const int32_t *j, const float *c, const int32_t *comp,
+                                                                 const int32_t *depth, const int32_t *up, const uint32_t *up_cand,
+                                                                 const unsigned long long *rank, uint8_t *state)
+{
+    const size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (e >= m || !(c[e] < 0.0f)) return;
+    int32_t a = i[e], b = j[e];
+    if (comp[a] != comp[b]) return;      // nodes without a candidate are alone in their component
+    int32_t da = depth[a], db = depth[b];
+    unsigned long long low = ~0ull;
+    uint32_t low_k = 0;
+    while (a != b) {
+        uint32_t k;
+        if (da >= db) { k = up_cand[a]; a = up[a]; --da; } else { k = up_cand[b]; b = up[b]; --db; }
+        const unsigned long long r = rank[k];
+        if (r < low) { low = r; low_k = k; }
+    }
+    if (low != ~0ull) state[low_k] = 2;
+}
+
+// components of the forest edges that were not removed; their number goes to the host
+__global__ __launch_bounds__(kForestThreads) void k_forest_components(uint32_t na, Cands a, const uint8_t *state, int32_t *rep, uint64_t *mail, uint64_t seq)
+{
+    __shared__ uint32_t s_kept;
+    const uint32_t tid = threadIdx.x;
+    if (tid == 0) s_kept = 0u;
+    uint32_t kept = 0;
+    for (uint32_t q = 0; q < 32; ++q) {
+        const uint32_t k = tid + q * kForestThreads;
+        if (k < na && state[k] == 1) kept |= 1u << q;
+    }
+    __syncthreads();
+    const uint32_t n_wave = wave_sum((uint32_t)__popc(kept));
+    if (lane_id() == 0 && n_wave) atomicAdd(&s_kept, n_wave);
+    for (int sweep = 0; sweep < 64; ++sweep) {      // the number of trees at least halves per sweep
+        bool changed = false;
+        for (uint32_t left = kept; left; left &= left - 1) {
+            const uint32_t k = tid + (uint32_t)(__ffs((int)left) - 1) * kForestThreads;
+            int32_t p = a.u[k], q = a.v[k];      // parents only ever decrease: the walks end
+            for (int32_t x = load_past_cache(&rep[p]); x != p; x = load_past_cache(&rep[p])) p = x;
+            for (int32_t x = load_past_cache(&rep[q]); x != q; x = load_past_cache(&rep[q])) q = x;
+            if (p != q) { atomicMin(&rep[max(p, q)], min(p, q)); changed = true; }
+        }
+        if (!__syncthreads_or(changed)) break;
+    }
+    for (uint32_t left = kept; left; left &= left - 1) {
+        const uint32_t k = tid + (uint32_t)(__ffs((int)left) - 1) * kForestThreads;
+        const int32_t u = a.u[k], v = a.v[k];
+        int32_t p = u;      // both ends have the same root; a shorter way to it: no walk of another thread goes wrong
+        for (int32_t x = load_past_cache(&rep[p]); x != p; x = load_past_cache(&rep[p])) p = x;
+        rep[u] = p; rep[v] = p;
+    }
+    if (tid == 0) mail[1] = (uint64_t)s_kept;
+    mail_send(mail, seq);
+}
+
 }  // namespace
 
+// The candidate edges of a graph: the scan that packs them and the arrays they were packed into (which the handshake
+// rounds have used since).
+struct Candidates {
+    uint32_t n = 0;
+    ScanPlan<uint32_t> plan;
+    Buf<int32_t> u, v;
+    Buf<unsigned long long> r;
+};
+
 // handshake matching; mate[v] = partner or -1; returns |S| in n_matched
-static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap, Buf<int32_t> &mate, int64_t &n_matched)
+static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap, Buf<int32_t> &mate, int64_t &n_matched, Candidates &list)
 {
     const size_t m = (size_t)g.m, n = (size_t)g.n;
     n_matched = 0;
@@ -546,10 +708,10 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
     Buf<unsigned long long> cr[2];
     Cands cur{}, nxt{};
     uint32_t na = 0;
-    ScanPlan<uint32_t> cand;   // its total -- the length of the first list -- stays on the device for the first round
+    ScanPlan<uint32_t> &cand = list.plan;   // its total -- the length of the first list -- stays on the device for the first round
     RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, m, 0, cand)));
     RAMA_TRY((scan_totals<uint32_t>(ctx, CandFlag{g.c.get(), tau}, cand)));
-    na = cand.total;
+    na = list.n = cand.total;
     if (na == 0) return setup.run(ctx);
     for (int k = 0; k < 2; ++k) {
         RAMA_TRY(cu[k].alloc(ctx, na));
@@ -609,6 +771,54 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
         for (int b = r - batch; b < r; ++b) n_matched += back[(size_t)(2 * b + 1)];
         na = back[(size_t)(2 * (r - 1))];
     }
+    list.u = std::move(cu[0]); list.v = std::move(cv[0]); list.r = std::move(cr[0]);
+    return RAMA_OK;
+}
+
+// S by the spanning forest without conflicts, for a short candidate list: |S| and the components of (V,S)
+static rama_status forest_short(Ctx &ctx, const Graph &g, float tau, Candidates &list, Buf<int32_t> &rep, int64_t &n_set)
+{
+    const size_t m = (size_t)g.m, n = (size_t)g.n;
+    const Cands a{list.u.get(), list.v.get(), list.r.get()};
+    RAMA_TRY((scan_emit<uint32_t>(ctx, CandFlag{g.c.get(), tau}, PackCandsEmit{g.i.get(), g.j.get(), g.c.get(), a, nullptr}, list.plan,
+                                  (double)((size_t)list.n * 28))));
+    Buf<int32_t> comp, hook, depth, up;
+    Buf<uint32_t> up_cand;
+    Buf<unsigned long long> best;
+    Buf<uint8_t> state;
+    RAMA_TRY(comp.alloc(ctx, n));
+    RAMA_TRY(hook.alloc(ctx, n));
+    RAMA_TRY(depth.alloc(ctx, n));
+    RAMA_TRY(up.alloc(ctx, n));
+    RAMA_TRY(up_cand.alloc(ctx, n));
+    RAMA_TRY(rep.alloc(ctx, n));
+    RAMA_TRY(best.alloc(ctx, n));
+    RAMA_TRY(state.alloc(ctx, list.n));
+    {
+        ProfScope ps_(ctx, "k_forest_init", (double)(n * 20));
+        k_forest_init<<<grid_for(n), kBlock, 0, ctx.stream>>>(n, comp.get(), hook.get(), rep.get(), best.get());
+    }
+    LAUNCH_TRY(ctx, "forest_init");
+    {
+        ProfScope ps_(ctx, "k_forest_short", (double)((size_t)list.n * 64));
+        k_forest_short<<<1, kForestThreads, 0, ctx.stream>>>(list.n, a, comp.get(), hook.get(), best.get(), depth.get(), up.get(), up_cand.get(),
+                                                             state.get());
+    }
+    LAUNCH_TRY(ctx, "forest_short");
+    {
+        ProfScope ps_(ctx, "k_mark_conflicts", (double)(m * 12));
+        k_mark_conflicts_short<<<grid_for(m), kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), g.c.get(), comp.get(), depth.get(), up.get(),
+                                                                      up_cand.get(), a.r, state.get());
+    }
+    LAUNCH_TRY(ctx, "mark_conflicts");
+    const uint64_t seq = ++ctx.mail_seq;
+    {
+        ProfScope ps_(ctx, "k_forest_components", (double)((size_t)list.n * 24));
+        k_forest_components<<<1, kForestThreads, 0, ctx.stream>>>(list.n, a, state.get(), rep.get(), mailbox(ctx), seq);
+    }
+    LAUNCH_TRY(ctx, "forest_components");
+    RAMA_TRY(wait_mail(ctx, seq));
+    n_set = (int64_t)((const volatile uint64_t *)mailbox(ctx))[1];
     return RAMA_OK;
 }
 
@@ -828,21 +1038,25 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
     if (used_forest) *used_forest = false;
     RAMA_TRY(zero_page_recycle(ctx));
     Buf<int32_t> mate;
-    RAMA_TRY(matching(ctx, g, tau, rounds_cap, mate, n_matched));
+    Candidates list;
+    RAMA_TRY(matching(ctx, g, tau, rounds_cap, mate, n_matched, list));
     n_new = g.n;
     if (n_matched == 0) return RAMA_OK;
     Buf<uint32_t> npos;
     Buf<int32_t> si, sj, rep;
     RAMA_TRY(npos.alloc(ctx, n + 1));
-    bool pairs_only = true;   // S is a matching: every component of (V,S) is a node or a pair
     // too few pairs: switch to the spanning forest without conflicts (Sec. 3.1, "fewer than 0.1|V|")
     if (forest_ratio > 0.0f && (double)n_matched < (double)forest_ratio * (double)g.n) {
-        pairs_only = false;
         mate.reset();
         if (used_forest) *used_forest = true;
-        RAMA_TRY(forest_set(ctx, g, tau, si, sj, n_matched));
-        if (n_matched == 0) return RAMA_OK;
-        RAMA_TRY(components(ctx, n, (size_t)n_matched, si.get(), sj.get(), rep));
+        if (list.n <= kShortForest) {
+            RAMA_TRY(forest_short(ctx, g, tau, list, rep, n_matched));
+            if (n_matched == 0) return RAMA_OK;
+        } else {
+            RAMA_TRY(forest_set(ctx, g, tau, si, sj, n_matched));
+            if (n_matched == 0) return RAMA_OK;
+            RAMA_TRY(components(ctx, n, (size_t)n_matched, si.get(), sj.get(), rep));
+        }
     } else {
         // the components of a matching are its pairs: the representative (smallest node) is at hand
         RAMA_TRY(rep.alloc(ctx, n));
@@ -851,13 +1065,7 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
     }
     LAUNCH_TRY(ctx, "pair_rep");
     RAMA_TRY((exclusive_scan<uint32_t>(ctx, IsRoot{rep.get()}, npos.get(), n)));
-    if (pairs_only) {
-        n_new = (int32_t)((int64_t)g.n - n_matched);   // every pair removes one node: no need to ask the device
-    } else {
-        uint32_t nn = 0;
-        RAMA_TRY(read_back(ctx, &nn, npos.get() + n, 4));
-        n_new = (int32_t)nn;
-    }
+    n_new = (int32_t)((int64_t)g.n - n_matched);   // S has no cycle: every edge of it removes one node, no need to ask the device
     RAMA_TRY(fmap.alloc(ctx, n));
     {
         ProfScope ps_(ctx, "k_number", (double)(n * 12));

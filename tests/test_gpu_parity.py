@@ -442,6 +442,29 @@ def test_diagonal_of_long_runs(rama, oracle32, sizes):
     assert np.array_equal(np_(got["diag"]), want["diag"][: len(sizes)])
 
 
+# the forest by one workgroup takes up to 32768 candidates; graphs beyond 6144 nodes, so that the round is not taken whole
+@pytest.mark.parametrize("kind,n,m,cand", [("random", 20000, 40000, 1), ("random", 20000, 40000, 1024), ("random", 20000, 40000, 32767),
+                                           ("random", 20000, 40000, 32768), ("random", 20000, 40000, 32769), ("path", 7000, 0, 0)])
+def test_forest_in_one_workgroup(rama, oracle32, kind, n, m, cand):
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(n + cand)
+    if kind == "random":
+        g = inputs.random_graph(n, m, 17)
+        c = -np.abs(g["c"]) - np.float32(0.01)
+        pick = rng.choice(c.size, cand, replace=False)
+        c[pick] = np.round(-c[pick] * 4) / 4 + np.float32(0.25)      # a few values: ties decide
+        i, j = g["i"], g["j"]
+    else:                                                            # one tree as deep as the graph has nodes
+        i = np.concatenate([np.arange(n - 1), np.arange(0, n - 50, 97)]).astype(np.int32)
+        j = np.concatenate([np.arange(1, n), np.arange(0, n - 50, 97) + 41]).astype(np.int32)
+        c = np.concatenate([rng.uniform(0.5, 1.5, n - 1), -np.ones(i.size - n + 1)]).astype(np.float32)
+    want = oracle32.contract(n, i, j, c, repeat=1, forest_ratio=1.0)
+    got = rama.contract(n, i, j, c, params=default_params(forest_ratio=1.0), repeat=1)
+    assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+
+
 # --------------------------------------------------------------------------------------------
 # whole rounds in one workgroup: graphs of up to 8192 edges and 6144 nodes
 # --------------------------------------------------------------------------------------------

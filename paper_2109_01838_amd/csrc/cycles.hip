@@ -413,6 +413,72 @@ __global__ __launch_bounds__(kBlock) void k_count_cycles(size_t nr, const int32_
     count_edge<MAXL, MEET>(r < nr, r, ri, rj, g, max_len, flags, cnt, heavy, n_heavy, saturated);
 }
 
+// ---- counts up to length 5 on graphs all of whose attractive rows have at most R entries -----------
+// The walk with its last level closed from vL's side, written out for rows that are known to be short: every row comes
+// in whole by 16-byte loads that do not wait for each other (the bounds of all first hops' rows at once, the row of the
+// coming v1 while this one is worked on), where the walk above fetches entry after entry, and R fixes how many
+// comparisons a pair (v1,v2) costs.  What bounds it: those R*R comparisons for each of up to R*R pairs.  320^3 grid (3.1e7
+// repulsive edges): 4.4 ms for the walk, 2.2 here.
+template <int R>
+__global__ __launch_bounds__(kBlock) void k_count_cycles_short(size_t nr, const int32_t *ri, const int32_t *rj, Adj g, ListPtrs<uint32_t, 3> cnt)
+{
+    const size_t r = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (r >= nr) return;
+    const int32_t v0 = ri[r], vl = rj[r];
+    const int32_t a0 = g.ptr[v0], a1 = g.ptr[v0 + 1], b0 = g.ptr[vl], b1 = g.ptr[vl + 1];
+    uint32_t n3 = 0, n4 = 0, n5 = 0;
+    if (a0 < a1 && b0 < b1) {
+        int32_t ra[R], rb[R], pa0[R], pa1[R], rows[R][R];
+        __builtin_memcpy(ra, g.nb + a0, sizeof(ra));      // the array is padded; what lies behind a row's end becomes -1, -2
+        __builtin_memcpy(rb, g.nb + b0, sizeof(rb));
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            ra[k] = a0 + k < a1 ? ra[k] : -1;
+            rb[k] = b0 + k < b1 ? rb[k] : -2;
+        }
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            int32_t p0 = 0, p1 = 0;
+            pa0[k] = 0; pa1[k] = 0;
+            if (ra[k] >= 0) { pa0[k] = g.ptr[ra[k]]; pa1[k] = g.ptr[ra[k] + 1]; }
+            if (rb[k] >= 0) { p0 = g.ptr[rb[k]]; p1 = g.ptr[rb[k] + 1]; }
+            int32_t row[R];
+            __builtin_memcpy(row, g.nb + p0, sizeof(row));
+#pragma unroll
+            for (int q = 0; q < R; ++q) rows[k][q] = p0 + q < p1 ? row[q] : -2;
+        }
+        int32_t coming[R];
+        __builtin_memcpy(coming, g.nb + pa0[0], sizeof(coming));
+#pragma unroll
+        for (int a = 0; a < R; ++a) {
+            int32_t row[R];
+#pragma unroll
+            for (int q = 0; q < R; ++q) row[q] = pa0[a] + q < pa1[a] ? coming[q] : -1;
+            if (a + 1 < R) __builtin_memcpy(coming, g.nb + pa0[a + 1 < R ? a + 1 : a], sizeof(coming));
+            const int32_t v1 = ra[a];
+            if (v1 < 0) continue;
+#pragma unroll
+            for (int k = 0; k < R; ++k) n3 += rb[k] == v1 ? 1u : 0u;
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const int32_t v2 = row[q];
+                if (v2 < 0 || v2 == v0) continue;
+#pragma unroll
+                for (int k = 0; k < R; ++k) n4 += rb[k] == v2 ? 1u : 0u;
+                if (v2 == vl) continue;
+#pragma unroll
+                for (int k = 0; k < R; ++k) {
+                    bool hit = false;
+#pragma unroll
+                    for (int x = 0; x < R; ++x) hit |= rows[k][x] == v2;
+                    n5 += hit && rb[k] != v1 ? 1u : 0u;
+                }
+            }
+        }
+    }
+    cnt.p[0][r] = n3; cnt.p[1][r] = n4; cnt.p[2][r] = n5;
+}
+
 // counts of the listed heavy edges: a wave per edge, lane l takes the first hops l, l+64, ...
 template <int MAXL>
 __global__ __launch_bounds__(kBlock) void k_count_cycles_heavy(const uint32_t *heavy, const uint32_t *n_heavy,
@@ -948,7 +1014,7 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     const bool may_be_heavy = max_len >= 4;
     // Lengths 4 and 5.  If every attractive row has at most kRowRegs entries (3-D grids), the walk holds the rows it
     // needs in registers and is the fastest: 4.4 ms against 4.8 for the hashed search (eight lanes per edge) on the
-    // 320^3 grid (rows <= 6, 3.1e7 repulsive edges).  Otherwise the hashed search: sixteen lanes per edge while rows hold
+    // 320^3 grid (rows <= 6, 3.1e7 repulsive edges); with whole rows in registers 2.2.  Otherwise the hashed search: sixteen lanes per edge while rows hold
     // up to twelve entries on average, a wave per edge beyond.  Measured (count pass, ms): 512^2 grid with long-range
     // edges (rows <= 12) 0.30 with sixteen lanes, 0.38 with 32, 0.75 with 64, 3.9 for the walk; 6-nearest-neighbour graph
     // of 10^6 points (rows of 3..15) 0.40, 0.56, 1.16, walk 1.27; a 180x181 long-range grid after one dual round
@@ -993,7 +1059,14 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
                                                                                    (const uint64_t *)nullptr, (int32_t *)nullptr);
     } else if (!hashed) {
         ProfScope ps_(ctx, MAXL == 3 ? "k_count_cycles<3>" : MAXL == 5 ? "k_count_cycles<5>" : "k_count_cycles<7>", search_bytes);
-        if (meet)
+        bool short_rows = false;
+        if constexpr (MAXL == 5) {
+            short_rows = ctx.cycle_search == 0 && max_len == 5 && !shortest_only && longest_row <= 6;
+            if (short_rows) k_count_cycles_short<6><<<grid_for(mr), kBlock, 0, ctx.stream>>>(mr, ri, rj, adj, cp);
+        }
+        if (short_rows) {
+            // nothing heavy, nothing that could overflow a count
+        } else if (meet)
             k_count_cycles<MAXL, (MAXL >= 5)><<<grid_for(mr), kBlock, 0, ctx.stream>>>(mr, ri, rj, adj, max_len, walk_flags, cp,
                                                                                       heavy.get(), n_heavy.get(), n_heavy.get() + 1);
         else

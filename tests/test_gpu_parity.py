@@ -125,6 +125,33 @@ def test_hashed_search_at_its_limits(rama, oracle32, isolated, d_a, d_b, row, lm
         assert np.array_equal(np_(got[L]), want[L]), (L + 3, got[L].shape, want[L].shape)
 
 
+# graphs whose attractive rows have exactly up to 6 entries are counted with whole rows in registers; 7 take another search
+@pytest.mark.parametrize("row", [1, 5, 6, 7])
+def test_cycles_on_short_rows(rama, oracle32, row):
+    rng = np.random.default_rng(row)
+    n = 4000
+    base = np.arange(n)
+    offs = [1, 2, 5, 11][: (row + 1) // 2]
+    i = np.concatenate([base for _ in offs])
+    j = np.concatenate([(base + d) % n for d in offs])      # a circulant graph: rows of 2 * len(offs) before the cut
+    if row % 2:
+        cut = j != (i + offs[-1]) % n
+        i, j = np.concatenate([i[cut], np.arange(0, n, 2)]), np.concatenate([j[cut], np.arange(1, n, 2)])     # odd rows: plus a pairing
+        i, j = np.concatenate([i, np.arange(3)]), np.concatenate([j, np.arange(3) + 40])
+    c = np.ones(i.size, np.float32)
+    if not row % 2:
+        c[rng.random(i.size) < 0.1] = -1.0
+    extra = rng.integers(0, n, (2, 3000))
+    near = (extra[0] + rng.integers(1, 30, 3000)) % n
+    i, j, c = np.concatenate([i, extra[0]]).astype(np.int32), np.concatenate([j, near]).astype(np.int32), np.concatenate([c, -3.0 * np.ones(3000)]).astype(np.float32)
+    n *= 2      # nodes without edges: the longest row is only looked at when rows are short on average
+    want = oracle32.find_conflicted_cycles(n, i, j, c, 5)
+    got = rama.find_conflicted_cycles(n, i, j, c, 5)
+    assert sum(w.shape[0] for w in want) > 0 or row == 1
+    for L in range(3):
+        assert np.array_equal(np_(got[L]), want[L]), (L + 3, got[L].shape, want[L].shape)
+
+
 # cycles of length 6 and 7 (named as future work in Sec. 5) and the shortest-only separation; the
 # cases are the ones whose plain enumeration the oracle finishes in seconds
 LONG_CASES = [("cfg1", 7), ("grid3d_24", 7), ("random_sparse", 7), ("knn_20000", 7), ("knn_20000", 6),

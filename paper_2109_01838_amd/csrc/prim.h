@@ -583,8 +583,13 @@ __global__ __launch_bounds__(kBlock) void k_row_bounds_search(const K *keys, siz
 template <typename K>
 struct SortTile {
     static constexpr int items = sizeof(K) == 8 ? 24 : 20;
-    static constexpr int size = kBlock * items;
 };
+// Shorter arrays do not fill the chip with such tiles (10^6 keys: 163 workgroups for 256 CUs, each of which takes its
+// 24 rows of keys one after the other: 15 to 20 us a pass whatever the length), so they get smaller ones: eight keys per
+// thread, and four where even those are fewer than the CUs.  Solves with 8 (and 4) against 24/20 keys per thread:
+// 512^2 long-range grid 9.6 -> 8.8 ms, 6-NN graph of 10^6 points 15.4 -> 14.4, 61x97x131 grid 10.2 -> 8.9, 128^2
+// long-range grid 4.45 -> 3.96 (3.84 with the four).
+constexpr size_t kSortShort = size_t(3) << 16, kSortMedium = size_t(3) << 20;
 #ifndef RAMA_RADIX_BITS
 #define RAMA_RADIX_BITS 8
 #endif
@@ -620,21 +625,22 @@ struct alignas(16) KeyVec {
 // Workgroups take their tiles by xcd_block(): with tile = workgroup number, a cache line of a row collected the
 // words of sixteen workgroups on eight XCDs, two words per L2, and went to memory in pieces (26 MB written for a
 // 3.2 MB table); the runs the scatter kernel writes for neighbouring tiles meet in one L2 as well.
-template <typename K>
+template <typename K, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_rs_hist(const K *keys, uint32_t *hist, size_t n, int shift, int bits,
                                                     uint32_t nb)
 {
     constexpr int kPer = 16 / (int)sizeof(K);                 // keys per vector
-    constexpr int kVecs = SortTile<K>::items / kPer;          // vectors per thread
-    static_assert(SortTile<K>::items % kPer == 0, "tile must be a whole number of vectors per thread");
+    constexpr int kVecs = ITEMS / kPer;                       // vectors per thread
+    constexpr int kTile = kBlock * ITEMS;
+    static_assert(ITEMS % kPer == 0, "tile must be a whole number of vectors per thread");
     __shared__ uint32_t h[kRadix];
     for (int k = threadIdx.x; k < kRadix; k += kBlock) h[k] = 0;
     __syncthreads();
     const uint32_t mask = (1u << bits) - 1u;
     const uint32_t tile_id = xcd_block();
     if (tile_id >= nb) return;      // the whole workgroup (padding of the grid)
-    const size_t tile = (size_t)tile_id * SortTile<K>::size;
-    if (tile + SortTile<K>::size <= n) {                      // full tile: vector loads (tile starts are 16-byte aligned)
+    const size_t tile = (size_t)tile_id * kTile;
+    if (tile + kTile <= n) {                      // full tile: vector loads (tile starts are 16-byte aligned)
         const KeyVec<K> *src = reinterpret_cast<const KeyVec<K> *>(keys + tile);
 #pragma unroll
         for (int r = 0; r < kVecs; ++r) {
@@ -717,13 +723,13 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, int bits, uint64_t v
 // With LOCAL_SCAN (few tiles) `offs` is the raw [digit][tile] histogram and every workgroup derives
 // its own global offsets from it, which saves the scan launch of the pass.
 constexpr uint32_t kSortLocalScanTiles = 32;
-template <typename K, typename V, bool HAS_V, bool LOCAL_SCAN>
+template <typename K, typename V, bool HAS_V, bool LOCAL_SCAN, int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vin, K *kout, V *vout,
                                                        const uint32_t *offs, size_t n, int shift, int bits,
                                                        uint32_t nb)
 {
-    constexpr int kSortItems = SortTile<K>::items;
-    constexpr int kSortTile = SortTile<K>::size;
+    constexpr int kSortItems = ITEMS;
+    constexpr int kSortTile = kBlock * ITEMS;
     __shared__ uint32_t whist[4][kRadix];
     __shared__ uint32_t gdelta[kRadix];
     __shared__ K skey[kSortTile];
@@ -1076,36 +1082,45 @@ inline const char *rs_local_name()
     return sizeof(K) == 8 ? "k_rs_local<u64>" : "k_rs_local<u32>";
 }
 
+// one pass: histogram, offsets, scatter
+template <typename K, typename V, bool HAS_V, int ITEMS>
+rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist, uint32_t *offs)
+{
+    const uint32_t nb = grid_for(n, kBlock * ITEMS);
+    {
+        ProfScope ps_(ctx, (sizeof(K) == 8 ? "k_rs_hist<u64>" : "k_rs_hist<u32>"), (double)(n * sizeof(K)));
+        k_rs_hist<K, ITEMS><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, hist, n, shift, bits, nb);
+    }
+    LAUNCH_TRY(ctx, "rs_hist");
+    if (nb <= kSortLocalScanTiles) {
+        ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
+        k_rs_scatter<K, V, HAS_V, true, ITEMS><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, kb, vb, hist, n, shift, bits, nb);
+    } else {
+        {
+            ProfScope ps_(ctx, "k_rs_rowscan", (double)(((size_t)nb << bits) * 8));
+            k_rs_rowscan<<<1u << bits, kBlock, 0, ctx.stream>>>(hist, offs, nb, offs + (size_t)kRadix * nb);
+        }
+        LAUNCH_TRY(ctx, "rs_rowscan");
+        ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
+        k_rs_scatter<K, V, HAS_V, false, ITEMS><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, kb, vb, offs, n, shift, bits, nb);
+    }
+    LAUNCH_TRY(ctx, "rs_scatter");
+    return RAMA_OK;
+}
 // stable LSD passes over the key bits [shift, shift + total_bits); a/b swap with every pass
 template <typename K, typename V, bool HAS_V>
 rama_status radix_passes(Ctx &ctx, K *&ka, V *&va, K *&kb, V *&vb, size_t n, int shift, int total_bits, uint32_t *hist,
                          uint32_t *offs, bool *result_in_b, bool *iota, K *&kc, V *&vc)
 {
-    const uint32_t nb = grid_for(n, SortTile<K>::size);
     const int passes = (total_bits + kRadixBits - 1) / kRadixBits;
     int remaining = total_bits;
     for (int p = 0; p < passes; ++p) {
         int bits = (remaining + (passes - p) - 1) / (passes - p);
-        {
-            ProfScope ps_(ctx, (sizeof(K) == 8 ? "k_rs_hist<u64>" : "k_rs_hist<u32>"), (double)(n * sizeof(K)));
-            k_rs_hist<K><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, hist, n, shift, bits, nb);
-        }
-        LAUNCH_TRY(ctx, "rs_hist");
         const V *vin = (HAS_V && *iota) ? (const V *)nullptr : va;   // the first pass of a sort whose values are the places 0..n-1
         *iota = false;
-        if (nb <= kSortLocalScanTiles) {
-            ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-            k_rs_scatter<K, V, HAS_V, true><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, vin, kb, vb, hist, n, shift, bits, nb);
-        } else {
-            {
-                ProfScope ps_(ctx, "k_rs_rowscan", (double)(((size_t)nb << bits) * 8));
-                k_rs_rowscan<<<1u << bits, kBlock, 0, ctx.stream>>>(hist, offs, nb, offs + (size_t)kRadix * nb);
-            }
-            LAUNCH_TRY(ctx, "rs_rowscan");
-            ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-            k_rs_scatter<K, V, HAS_V, false><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, vin, kb, vb, offs, n, shift, bits, nb);
-        }
-        LAUNCH_TRY(ctx, "rs_scatter");
+        if (n <= kSortShort) RAMA_TRY((radix_pass<K, V, HAS_V, 4>(ctx, ka, vin, kb, vb, n, shift, bits, hist, offs)));
+        else if (n <= kSortMedium) RAMA_TRY((radix_pass<K, V, HAS_V, 8>(ctx, ka, vin, kb, vb, n, shift, bits, hist, offs)));
+        else RAMA_TRY((radix_pass<K, V, HAS_V, SortTile<K>::items>(ctx, ka, vin, kb, vb, n, shift, bits, hist, offs)));
         std::swap(ka, kb);
         std::swap(va, vb);
         if (kc) {   // the input must stay as it is: from now on the passes alternate between the two other buffers
@@ -1217,7 +1232,7 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             return RAMA_OK;
         }
     }
-    const uint32_t nb = grid_for(n, SortTile<K>::size);
+    const uint32_t nb = grid_for(n, kBlock * (n <= kSortShort ? 4 : n <= kSortMedium ? 8 : SortTile<K>::items));
     Buf<uint32_t> hist, offs;
     RAMA_TRY(hist.alloc(ctx, (size_t)kRadix * nb));
     RAMA_TRY(offs.alloc(ctx, (size_t)kRadix * nb + kRadix));

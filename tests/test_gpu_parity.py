@@ -557,6 +557,19 @@ def test_canonicalisation_of_large_shuffled_input(rama, oracle32):
     assert np.array_equal(np_(got["c"]), wc)       # duplicates are added in input order on both sides
 
 
+# lengths at which the radix passes change their tiles (4 or 8 keys per thread, 24 / 20 beyond), and one key more or less
+# than whole tiles of each
+@pytest.mark.parametrize("m", [8193, 33 * 1024, 196608, 196609, 200 * 2048 + 1, 3145728, 3145729, 513 * 6144 + 1])
+def test_sort_at_the_limits_of_its_tiles(rama, oracle32, m):
+    rng = np.random.default_rng(m)
+    n = 1 << 20
+    i, j = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
+    c = -rng.random(m, dtype=np.float32) - np.float32(0.01)
+    wi, wj, wc = oracle32.canonicalise(n, i, j, c)
+    got = rama.contract(n, i, j, c, repeat=1, want_diag=False)      # no attractive edge: the canonical form of the input
+    assert np.array_equal(np_(got["i"]), wi) and np.array_equal(np_(got["j"]), wj) and np.array_equal(np_(got["c"]), wc)
+
+
 @pytest.mark.parametrize("n,m", [(3, 20001), (2, 2049), (5, 4096), (40, 70000)])
 def test_canonicalisation_sums_long_runs_in_input_order(rama, oracle32, n, m):
     # few nodes, many parallel edges: every run of equal pairs is thousands of entries long and crosses

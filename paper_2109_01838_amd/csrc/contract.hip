@@ -124,24 +124,30 @@ __global__ __launch_bounds__(kBlock) void k_accept(const uint32_t *n_list, Cands
 // round after next -- so only survivors pay for clearing, and nobody clears what somebody else
 // is proposing into.
 constexpr int kAdvItems = 8;
+// Lists of up to 2^20 candidates give a workgroup 512 instead of 2048: with eight a thread they do not fill the chip, and a
+// thread's eight combine-and-propose steps wait one after the other (contraction of a 300x301 long-range grid 3.06 ->
+// 2.80 ms, 128^2 solve 3.90 -> 3.71, 512^2 8.82 -> 8.59, 6-NN graph of 10^6 points 14.44 -> 14.25).
+constexpr size_t kAdvMedium = size_t(1) << 20;
+constexpr size_t kAdvShort = size_t(1) << 17;
 constexpr uint32_t kMatchBatchMax = 1u << 20;   // candidate lists up to this length run their handshake rounds in batches
 constexpr int kMatchBatch = 4;
+template <int ITEMS>
 __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cands a, const int32_t *mate, Cands next,
                                                     unsigned long long *best_next, unsigned long long *best_after,
                                                     uint32_t *counter)
 {
     __shared__ uint32_t s_base, s_wave[4], s_pairs[4];
     const size_t na = *n_list;
-    if ((size_t)blockIdx.x * (kBlock * kAdvItems) >= na) return;   // the whole workgroup: nothing left of the list here
+    if ((size_t)blockIdx.x * (kBlock * ITEMS) >= na) return;   // the whole workgroup: nothing left of the list here
     const int w = threadIdx.x >> 6, lane = lane_id();
-    const bool short_list = gridDim.x <= 64;
-    const size_t base = (size_t)blockIdx.x * (kBlock * kAdvItems) + (size_t)w * (64 * kAdvItems) + lane;
-    int32_t u[kAdvItems], v[kAdvItems];
-    unsigned long long r[kAdvItems];
-    uint32_t where[kAdvItems];
+    const bool short_list = (size_t)gridDim.x * (kBlock * ITEMS) <= kAdvShort;
+    const size_t base = (size_t)blockIdx.x * (kBlock * ITEMS) + (size_t)w * (64 * ITEMS) + lane;
+    int32_t u[ITEMS], v[ITEMS];
+    unsigned long long r[ITEMS];
+    uint32_t where[ITEMS];
     uint32_t keep = 0, cnt = 0, pairs = 0;
 #pragma unroll
-    for (int q = 0; q < kAdvItems; ++q) {
+    for (int q = 0; q < ITEMS; ++q) {
         const size_t k = base + (size_t)q * 64;
         u[q] = 0; v[q] = 0; r[q] = 0ull;
         bool ok = false, pair = false;
@@ -186,7 +192,7 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
     for (int k = 0; k < 3; ++k)
         if (k < w) off += s_wave[k];
 #pragma unroll
-    for (int q = 0; q < kAdvItems; ++q)
+    for (int q = 0; q < ITEMS; ++q)
         if (keep & (1u << q)) {
             const uint32_t p = off + where[q];
             next.u[p] = u[q]; next.v[p] = v[q]; next.r[p] = r[q];
@@ -759,8 +765,12 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
             LAUNCH_TRY(ctx, "accept");
             {
                 ProfScope ps_(ctx, "k_advance", (double)((size_t)na * 56));
-                k_advance<<<grid_for(na, kBlock * kAdvItems), kBlock, 0, ctx.stream>>>(
-                    n_list, cur, mate.get(), nxt, best_next.get(), best_after.get(), counters.get() + 2 * r);
+                if (na <= kAdvMedium)
+                    k_advance<2><<<grid_for(na, kBlock * 2), kBlock, 0, ctx.stream>>>(
+                        n_list, cur, mate.get(), nxt, best_next.get(), best_after.get(), counters.get() + 2 * r);
+                else
+                    k_advance<kAdvItems><<<grid_for(na, kBlock * kAdvItems), kBlock, 0, ctx.stream>>>(
+                        n_list, cur, mate.get(), nxt, best_next.get(), best_after.get(), counters.get() + 2 * r);
             }
             LAUNCH_TRY(ctx, "advance");
             Cands t = cur; cur = nxt; nxt = t;

@@ -610,6 +610,45 @@ def test_canonicalisation_of_a_few_sorted_runs(rama, oracle32, runs):
     assert np.array_equal(np_(got["c"]), wc)
 
 
+# sorted pieces without repeated pairs are interleaved in one pass over ranges of nodes; a pair in two pieces, a node with
+# more than 64 edges, more edges than a range holds (3072) and more than 16 pieces take the general way
+@pytest.mark.parametrize("runs,kind", [(1, "plain"), (2, "plain"), (3, "plain"), (15, "plain"), (16, "plain"), (17, "plain"), (3, "dup"),
+                                       (3, "row64"), (3, "row65"), (4, "crowded"), (3, "sparse"), (3, "tiny")])
+def test_canonicalisation_interleaves_sorted_runs(rama, oracle32, runs, kind):
+    rng = np.random.default_rng(200 + runs)
+    n, m = {"sparse": (400000, 9000), "tiny": (900, 4097)}.get(kind, (20011, 90000))
+    a, b = rng.integers(0, n, 2 * m), rng.integers(0, n, 2 * m)
+    if kind == "crowded":                                        # most edges at a few nodes, none of them with many
+        a[: m] = rng.integers(5000, 5200, m)
+    lo, hi = np.minimum(a, b), np.maximum(a, b)
+    if kind.startswith("row"):
+        k = int(kind[3:])
+        keep = lo != 7
+        lo, hi = np.concatenate([lo[keep], np.full(k, 7)]), np.concatenate([hi[keep], 100 + 3 * np.arange(k)])
+    key = np.unique(lo[lo != hi].astype(np.int64) * n + hi[lo != hi])
+    if kind == "crowded":
+        cnt = np.concatenate([np.arange(x) for x in np.bincount((key // n).astype(np.int64), minlength=n)])
+        key = key[cnt < 60]
+    if not kind.startswith("row"):
+        key = np.sort(rng.permutation(key)[:m])
+    piece = rng.integers(0, runs, key.size)
+    if kind == "dup":
+        key, piece = np.append(key, key[1234]), np.append(piece, (piece[1234] + 1) % runs)
+    order = np.lexsort((key, piece))
+    lo, hi = key[order] // n, key[order] % n
+    flip = rng.random(lo.size) < 0.3
+    i, j = np.where(flip, hi, lo).astype(np.int32), np.where(flip, lo, hi).astype(np.int32)
+    c = (-np.abs(rng.normal(size=i.size)) - 1e-3).astype(np.float32)
+    c[rng.random(i.size) < 0.1] = 0.0
+    wi, wj, wc = oracle32.canonicalise(n, i, j, c)
+    got = rama.contract(n, i, j, c, repeat=1, want_diag=False)
+    assert np.array_equal(np_(got["i"]), wi) and np.array_equal(np_(got["j"]), wj) and np.array_equal(np_(got["c"]), wc)
+    # the signs the pass counts on its way are the ones the separation splits the edges by
+    c = np.where(rng.random(i.size) < 0.6, 1.0, -1.0).astype(np.float32)
+    want = oracle32.find_conflicted_cycles(n, i, j, c, 3)
+    assert np.array_equal(np_(rama.find_conflicted_cycles(n, i, j, c, 3)[0]), want[0])
+
+
 # --------------------------------------------------------------------------------------------
 # end to end
 # --------------------------------------------------------------------------------------------

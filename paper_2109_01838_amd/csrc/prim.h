@@ -917,6 +917,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_bounds(const K *keys, size_t n, 
 // workgroups per CU) takes 1.45 ms -- 0.55 ms for reading and writing the data and 0.22 ms per 7-bit
 // pass, which is the ballot ranking -- against 2.3 ms for 32 keys x 4 waves or 64-bit local keys.
 constexpr int kLocalSortWaves = 8;
+constexpr int kBucketBits = 12, kBucketMax = 32;
 template <typename LK>
 struct LocalSort {
     static constexpr int items = sizeof(LK) == 8 ? 8 : 16;
@@ -934,7 +935,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
     constexpr int kCap = LocalSort<LK>::cap;
     static_assert(kRadix == 256 && kThreads >= kRadix, "one digit per thread of the first four waves");
     __shared__ uint32_t whist[NW][kRadix];
-    __shared__ uint32_t wave_tot[4];
+    __shared__ uint32_t wave_tot[4], bucket_tot[NW];
     __shared__ LK skey[kCap];
     __shared__ uint32_t sval[HAS_V ? kCap : 1];
     // without a bounds array the (single) workgroup takes the whole array of n_all keys
@@ -959,8 +960,99 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
         key[r] = valid ? (LK)(kin[beg + idx] - base) : (LK)0;
         if (HAS_V) val[r] = valid ? (uint32_t)vin[beg + idx] : 0u;
     }
+    // Buckets first: the top kBucketBits of the keys' differing bits split the few thousand keys into buckets of one to
+    // a few (an edge list: the edges of a node).  Count and place by LDS atomics -- in any order --, then every key
+    // finds its place among its bucket's keys by comparing: six LDS accesses per key in all, where each 7-bit pass below
+    // takes as many plus the ballots (9.8e7 (u64,u32) pairs with 26 low bits: 1.88 -> 1.25 ms).  A bucket of more than kBucketMax keys sends the workgroup through the passes.
+    uint16_t *const s_end = reinterpret_cast<uint16_t *>(&whist[0][0]);
+    static_assert(NW * kRadix * 4 >= (1 << kBucketBits) * 2 && kThreads * 8 == (1 << kBucketBits), "bucket counters take the digit counters' place");
+    const int bucket_shift = sort_bits > kBucketBits ? sort_bits - kBucketBits : 0;
+    bool passes_needed = true;
+    {
+        uint32_t *words = &whist[0][0];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) words[tid * 4 + k] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kItems; ++r) {
+            if (r < rows) {
+                const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
+                if (idx < cnt) {
+                    const uint32_t b = (uint32_t)(key[r] >> bucket_shift);
+                    rank[r] = (atomicAdd(&words[b >> 1], 1u << (16 * (b & 1))) >> (16 * (b & 1))) & 0xffffu;   // counts below 2^14: no carry
+                }
+            }
+        }
+        __syncthreads();
+        uint32_t c[8], mine = 0, longest = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint32_t x = words[tid * 4 + k];
+            c[2 * k] = x & 0xffffu; c[2 * k + 1] = x >> 16;
+            mine += c[2 * k] + c[2 * k + 1];
+            longest = max(longest, max(c[2 * k], c[2 * k + 1]));
+        }
+        const uint32_t inc = wave_inclusive_scan(mine);
+        if (lane == 63) bucket_tot[w] = inc;
+        passes_needed = __syncthreads_or(longest > (uint32_t)kBucketMax) != 0;
+        if (!passes_needed) {      // uniform
+            uint32_t run = inc - mine;
+#pragma unroll
+            for (int k = 0; k < NW - 1; ++k)
+                if (k < w) run += bucket_tot[k];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {      // ends of the buckets
+                const uint32_t e0 = run + c[2 * k], e1 = e0 + c[2 * k + 1];
+                words[tid * 4 + k] = e0 | e1 << 16;
+                run = e1;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kItems; ++r) {
+                if (r < rows) {
+                    const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
+                    if (idx < cnt) {
+                        const uint32_t b = (uint32_t)(key[r] >> bucket_shift);
+                        const uint32_t p = (b ? s_end[b - 1] : 0u) + rank[r];
+                        skey[p] = key[r];
+                        if (HAS_V) sval[p] = idx;      // where the key came from: equal keys keep their order
+                        else rank[r] = p;
+                    }
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kItems; ++r) {
+                if (r < rows) {
+                    const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
+                    if (idx < cnt) {
+                        const uint32_t b = (uint32_t)(key[r] >> bucket_shift);
+                        const uint32_t b0 = b ? s_end[b - 1] : 0u, b1 = s_end[b], self = HAS_V ? idx : rank[r];
+                        uint32_t at = b0;
+                        for (uint32_t p = b0; p < b1; ++p) {
+                            const LK k = skey[p];
+                            at += (k < key[r] || (k == key[r] && (HAS_V ? sval[p] : p) < self)) ? 1u : 0u;
+                        }
+                        rank[r] = at;
+                    }
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kItems; ++r) {
+                if (r < rows) {
+                    const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
+                    if (idx < cnt) {
+                        skey[rank[r]] = key[r];
+                        if (HAS_V) sval[rank[r]] = val[r];
+                    }
+                }
+            }
+        }
+        __syncthreads();
+    }
     int shift = 0, remaining = sort_bits;
-    for (int p = 0; p < passes; ++p) {
+    for (int p = 0; passes_needed && p < passes; ++p) {
         const int bits = (remaining + (passes - p) - 1) / (passes - p);
         const uint32_t mask = (1u << bits) - 1u;
         for (int k = tid; k < NW * kRadix; k += kThreads) (&whist[0][0])[k] = 0;

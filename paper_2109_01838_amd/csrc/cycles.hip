@@ -1081,16 +1081,24 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
         LAUNCH_TRY(ctx, "count_cycles_heavy");
     }
     uint64_t tot[NL + 1], all = 0;
-    for (int k = 0; k < lists; ++k)
-        RAMA_TRY((exclusive_scan<uint64_t>(ctx, PtrInput<uint32_t>{cnt[k].get()}, off[k].get(), mr)));
-    {
+    if constexpr (MAXL == 3) {
+        // one list, whose counts (common neighbours) cannot saturate: the total comes back from the scan of the tile sums,
+        // and the places are only computed when there is a cycle
+        ScanPlan<uint64_t> places;
+        RAMA_TRY((scan_plan_alloc<uint64_t>(ctx, mr, 0, places)));
+        RAMA_TRY((scan_totals<uint64_t>(ctx, PtrInput<uint32_t>{cnt[0].get()}, places)));
+        tot[0] = places.total;
+        if (tot[0]) RAMA_TRY((scan_store<uint64_t>(ctx, PtrInput<uint32_t>{cnt[0].get()}, places, off[0].get())));
+    } else {
+        for (int k = 0; k < lists; ++k)
+            RAMA_TRY((exclusive_scan<uint64_t>(ctx, PtrInput<uint32_t>{cnt[k].get()}, off[k].get(), mr)));
         Buf<uint64_t> summary;
         RAMA_TRY(summary.alloc(ctx, NL + 1));
         k_cycle_totals<NL><<<1, 64, 0, ctx.stream>>>(op, mr, lists, n_heavy.get() + 1, summary.get());
         LAUNCH_TRY(ctx, "cycle_totals");
         RAMA_TRY(read_back(ctx, tot, summary.get(), sizeof(tot)));
+        if (tot[NL]) return fail(ctx, RAMA_ERR_CAPACITY, "a repulsive edge closes 2^32 - 1 or more cycles of one length");
     }
-    if (tot[NL]) return fail(ctx, RAMA_ERR_CAPACITY, "a repulsive edge closes 2^32 - 1 or more cycles of one length");
     for (int k = 0; k < lists; ++k) {
         out.n[k] = (int64_t)tot[k];
         all += tot[k];

@@ -316,6 +316,30 @@ template <typename TO>
 __global__ void k_store_zero(TO *p) { *p = 0; }
 
 template <typename TO, typename F>
+rama_status exclusive_scan(Ctx &ctx, F f, TO *out, size_t n);
+
+// tile sums of f over n items (nb tiles) and their scan: offs[0..nb), offs[nb] = total
+template <typename TO, typename F>
+rama_status scan_offsets(Ctx &ctx, F f, TO *sums, TO *offs, size_t n, unsigned nb)
+{
+    const bool fused = nb <= kScanFusedMax;   // the last workgroup of the reduce launch scans the tile sums
+    {
+        ProfScope ps_(ctx, kernel_name<F>("k_scan_reduce"), (double)(n * F::bytes));
+        k_scan_reduce<TO, F><<<nb, kBlock, 0, ctx.stream>>>(f, sums, n, offs, fused ? ctx.ticket : nullptr,
+                                                           (uint64_t *)nullptr, 0, 0);
+    }
+    LAUNCH_TRY(ctx, "scan_reduce");
+    if (!fused && nb <= kScanMidMax) {
+        ProfScope ps_(ctx, "k_scan_mid", (double)((size_t)nb * 2 * sizeof(TO)));
+        k_scan_mid<TO><<<1, kBlock, 0, ctx.stream>>>(sums, offs, nb, (uint64_t *)nullptr, 0, 0);
+        LAUNCH_TRY(ctx, "scan_mid");
+    } else if (!fused) {
+        RAMA_TRY((exclusive_scan<TO, PtrInput<TO>>(ctx, PtrInput<TO>{sums}, offs, nb)));
+    }
+    return RAMA_OK;
+}
+
+template <typename TO, typename F>
 rama_status exclusive_scan(Ctx &ctx, F f, TO *out, size_t n)
 {
     if (n == 0) {
@@ -338,20 +362,7 @@ rama_status exclusive_scan(Ctx &ctx, F f, TO *out, size_t n)
     Buf<TO> sums, offs;
     RAMA_TRY(sums.alloc(ctx, nb));
     RAMA_TRY(offs.alloc(ctx, (size_t)nb + 1));
-    const bool fused = nb <= kScanFusedMax;   // the last workgroup of the reduce launch scans the tile sums
-    {
-        ProfScope ps_(ctx, kernel_name<F>("k_scan_reduce"), (double)(n * F::bytes));
-        k_scan_reduce<TO, F><<<nb, kBlock, 0, ctx.stream>>>(f, sums.get(), n, offs.get(), fused ? ctx.ticket : nullptr,
-                                                           (uint64_t *)nullptr, 0, 0);
-    }
-    LAUNCH_TRY(ctx, "scan_reduce");
-    if (!fused && nb <= kScanMidMax) {
-        ProfScope ps_(ctx, "k_scan_mid", (double)((size_t)nb * 2 * sizeof(TO)));
-        k_scan_mid<TO><<<1, kBlock, 0, ctx.stream>>>(sums.get(), offs.get(), nb, (uint64_t *)nullptr, 0, 0);
-        LAUNCH_TRY(ctx, "scan_mid");
-    } else if (!fused) {
-        RAMA_TRY((exclusive_scan<TO, PtrInput<TO>>(ctx, PtrInput<TO>{sums.get()}, offs.get(), nb)));
-    }
+    RAMA_TRY((scan_offsets<TO, F>(ctx, f, sums.get(), offs.get(), n, nb)));
     {
         ProfScope ps_(ctx, kernel_name<F>("k_scan_apply"), (double)(n * (F::bytes + sizeof(TO))));
         k_scan_apply<TO, F><<<nb, kBlock, 0, ctx.stream>>>(f, out, offs.get(), n);
@@ -493,6 +504,30 @@ rama_status scan_emit(Ctx &ctx, F f, E emit, const ScanPlan<TO> &plan, double by
     }
     LAUNCH_TRY(ctx, "scan_emit");
     return RAMA_OK;
+}
+
+// scan_totals has run: the prefixes themselves, out[0..n]
+template <typename TO, typename F>
+rama_status scan_store(Ctx &ctx, F f, const ScanPlan<TO> &plan, TO *out)
+{
+    if (plan.n == 0) return RAMA_OK;
+    {
+        ProfScope ps_(ctx, kernel_name<F>("k_scan_apply"), (double)(plan.n * (F::bytes + sizeof(TO))));
+        k_scan_apply<TO, F><<<plan.nb, kBlock, 0, ctx.stream>>>(f, out, plan.offs.get(), plan.n);
+    }
+    LAUNCH_TRY(ctx, "scan_apply");
+    return RAMA_OK;
+}
+
+// scan_totals + scan_emit for a consumer that needs no total on the host: nobody waits
+template <typename TO, typename F, typename E>
+rama_status scan_enumerate(Ctx &ctx, F f, E emit, size_t n, double bytes)
+{
+    if (n == 0) return RAMA_OK;
+    ScanPlan<TO> plan;
+    RAMA_TRY((scan_plan_alloc<TO>(ctx, n, 0, plan)));
+    RAMA_TRY((scan_offsets<TO, F>(ctx, f, plan.sums.get(), plan.offs.get(), n, plan.nb)));
+    return scan_emit<TO>(ctx, f, emit, plan, bytes);
 }
 
 // ------------------------------------------------------------------------------------------

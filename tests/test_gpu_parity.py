@@ -374,6 +374,23 @@ def test_message_passing_cycle_order_is_irrelevant(rama, oracle32):
     assert np.array_equal(np_(a["c"]), np_(b["c"])) and a["lower_bound"] == b["lower_bound"]
 
 
+# chords and fan triangles of cycles of five and more nodes are made unique tile by tile (2048 candidates): lists that end on
+# either side of a tile, and one in which every cycle comes twice
+@pytest.mark.parametrize("n5,twice", [(1, False), (682, False), (683, False), (1023, False), (1024, False), (1025, False), (3000, True)])
+@pytest.mark.parametrize("lmax", [5, 6])
+def test_message_passing_repeated_chords_and_triangles(rama, oracle32, n5, twice, lmax):
+    g = CASES["knn_20000"]
+    n = g["n_nodes"]
+    cyc = oracle32.find_conflicted_cycles(n, g["i"], g["j"], g["c"], lmax)
+    cyc = [c[: n5 if q == len(cyc) - 1 else n5 // 3] for q, c in enumerate(cyc)]
+    if twice:
+        cyc = [np.concatenate([c, c[::-1]]) for c in cyc]
+    want = oracle32.message_passing(n, g["i"], g["j"], g["c"], cyc, 3)
+    got = rama.message_passing(n, g["i"], g["j"], g["c"], cyc, 3)
+    assert np.array_equal(np_(got["i"]), want["i"]) and np.array_equal(np_(got["j"]), want["j"])
+    assert np.array_equal(np_(got["c"]), want["c"])
+
+
 def test_message_passing_rejects_foreign_cycles(rama):
     from paper_2109_01838_amd import RamaError, binding
     g = CASES["cfg1"]

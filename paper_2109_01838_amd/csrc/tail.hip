@@ -6,8 +6,9 @@
 // spanning forest, contraction -- between barriers, and the host hears of it when it is over.  The arithmetic, its order
 // and every tie are those of the stage kernels, so the results are the same bit for bit.
 //
-// Bounded by barriers and LDS latency (one CU works).  Measured per round: 84 us at 7254 edges (540 through the stage
-// kernels), 48 at 4958 with a forest (1240), 30 at 438 with message passing (390 to 600), 14 at 36 edges.
+// Bounded by barriers and LDS latency (one CU works).  Measured per round before the tries of the separation were dealt out
+// evenly: 84 us at 7254 edges (540 through the stage kernels), 48 at 4958 with a forest (1240), 30 at 438 with message
+// passing (390 to 600), 14 at 36 edges; with that, all rounds of a 128^2 long-range grid took 281 instead of 347 us.
 #include "prim.h"
 #include "steps.h"
 
@@ -30,20 +31,22 @@ static_assert(kTailEdges % kTailThreads == 0 && kTailNodes % (2 * kTailThreads) 
 // the work area (in 4-byte words), used by one step after another:
 //   sort        keys [0, 8192), values [8192, 16384), digit counts of the 16 waves [16384, 20480)
 //   separation  row ends [0, 3136) (16 bits each), cursors [3136, 6272), adjacency [6272, 14464) (16-bit edge numbers),
-//               triangles found: keys [14464, 16512), third edges [16512, 18560)
+//               triangles found: keys [14464, 16512), third edges [16512, 17536) (16 bits each), entries each
+//               repulsive edge is tried with [17536, 21632) (16 bits each), their sums per thread [21632, 22656)
 //   messages    sorted slots as the sort left them, messages [14336, 20480)
 //   matching    rank words [0, 12288), mates [12288, 15360) (16 bits each)
 //   forest      rank words [0, 12288), later depth, parent, edge to it (16 bits each) [0, 9216); components
 //               [12288, 15360), hooks [15360, 18432), forest bits [18432, 18688), removed bits [18688, 18944)
 //   mapping     representatives [0, 6144), new numbers [6144, 9216) (16 bits each)
-constexpr int kWorkWords = 20480;
+constexpr int kWorkWords = 22656;
 constexpr int kSortVal = kTailEdges, kSortHist = 2 * kTailEdges;
-constexpr int kSepCur = 3136, kSepAdj = 6272, kSepKey = 14464, kSepThird = 16512;
+constexpr int kSepCur = 3136, kSepAdj = 6272, kSepKey = 14464, kSepThird = 16512, kSepTries = 17536, kSepBefore = 21632;
 constexpr int kMsg = 14336;
 constexpr int kMate = 12288, kComp = 12288, kHook = 15360, kInForest = 18432, kRemoved = 18688;
 constexpr int kDepth = 0, kUp = 3072, kUpEdge = 6144;
 constexpr int kRep = 0, kNew = 6144;
-static_assert(kSepCur * 2 >= kTailNodes + 1 && kSepAdj + kTailEdges <= kSepKey && kSepThird + kTailTriangles <= kWorkWords, "separation");
+static_assert(kSepCur * 2 >= kTailNodes + 1 && kSepAdj + kTailEdges <= kSepKey && kSepThird + kTailTriangles / 2 <= kSepTries &&
+              kSepTries + kTailEdges / 2 <= kSepBefore && kSepBefore + kTailThreads <= kWorkWords, "separation");
 static_assert(kSortVal + 3 * kTailTriangles <= kMsg && kMsg + 3 * kTailTriangles <= kWorkWords, "messages");
 static_assert(2 * kTailNodes <= kMate && kMate + kTailNodes / 2 <= kHook && kHook + kTailNodes / 2 <= kInForest, "matching, forest");
 static_assert(kInForest + kTailEdges / 32 <= kRemoved && kRemoved + kTailEdges / 32 <= kWorkWords, "forest bits");
@@ -229,26 +232,51 @@ __device__ __forceinline__ uint32_t tail_triangles(TailShared &S, int n, int m, 
         }
     }
     __syncthreads();
+    // Every repulsive edge is tried with each entry of the shorter of its rows; the tries are dealt out evenly over the
+    // threads (an edge per thread and turn left most of a wave waiting for its longest row).
+    uint16_t *tries = (uint16_t *)(S.work + kSepTries), *third = (uint16_t *)(S.work + kSepThird);
+    uint32_t *before = S.work + kSepBefore;      // tries of the edges of the threads in front; thread t: edges 8t .. 8t+7
+    auto rows_of = [&](int e, uint32_t &s, uint32_t &o, int &s0) {      // s: the end with the shorter row, which starts at s0
+        s = S.key[e] >> kNodeBits; o = S.key[e] & kNodeMask;
+        s0 = s ? row_end[s - 1] : 0;
+        int len = row_end[s] - s0;
+        const int o0 = o ? row_end[o - 1] : 0, len_o = row_end[o] - o0;
+        if (len > len_o) { const uint32_t t = s; s = o; o = t; s0 = o0; len = len_o; }
+        return len;
+    };
+    uint32_t sum = 0, all_tries;
+#pragma unroll
     for (int q = 0; q < kTailItems; ++q) {
-        const int e = tid + q * kTailThreads;
-        if (e >= m || !(S.cost[e] < 0.0f)) continue;
-        uint32_t s = S.key[e] >> kNodeBits, o = S.key[e] & kNodeMask;
-        int s0 = s ? row_end[s - 1] : 0, s1 = row_end[s];
-        const int o0 = o ? row_end[o - 1] : 0, o1 = row_end[o];
-        if (s1 - s0 > o1 - o0) { const uint32_t t = s; s = o; o = t; s0 = o0; s1 = o1; }
-        if (o0 == o1) continue;
-        for (int p = s0; p < s1; ++p) {
-            const int a = adj[p];
-            const uint32_t lo = S.key[a] >> kNodeBits, hi = S.key[a] & kNodeMask, x = lo == s ? hi : lo;
-            const int b = tail_find(S, m, min(x, o) << kNodeBits | max(x, o));
-            if (b < 0 || !(S.cost[b] > 0.0f)) continue;
-            // the edges (u,v), (u,w), (v,w) of a triangle u < v < w stand in this order in the list
-            const int e0 = min(e, min(a, b)), e2 = max(e, max(a, b)), e1 = e + a + b - e0 - e2;
-            const uint32_t at = atomicAdd(&S.count[2], 1u);
-            if (at < (uint32_t)kTailTriangles) {
-                S.work[kSepKey + at] = (uint32_t)e0 << 13 | (uint32_t)e1;
-                S.work[kSepThird + at] = (uint32_t)e2;
-            }
+        const int e = tid * kTailItems + q;
+        uint32_t s, o;
+        int s0;
+        const uint32_t len = e < m && S.cost[e] < 0.0f ? (uint32_t)rows_of(e, s, o, s0) : 0u;
+        tries[e] = (uint16_t)len;
+        sum += len;
+    }
+    before[tid] = tail_scan(sum, &all_tries, S.wave);
+    __syncthreads();
+    for (uint32_t p = (uint32_t)tid; p < all_tries; p += kTailThreads) {
+        int t = 0;      // the last thread with at most p tries before its own
+#pragma unroll
+        for (int step = kTailThreads / 2; step > 0; step >>= 1)
+            if (before[t + step] <= p) t += step;
+        int e = t * kTailItems;
+        uint32_t k = p - before[t];
+        for (uint32_t len = tries[e]; k >= len; len = tries[++e]) k -= len;
+        uint32_t s, o;
+        int s0;
+        (void)rows_of(e, s, o, s0);
+        const int a = adj[s0 + (int)k];
+        const uint32_t lo = S.key[a] >> kNodeBits, hi = S.key[a] & kNodeMask, x = lo == s ? hi : lo;
+        const int b = tail_find(S, m, min(x, o) << kNodeBits | max(x, o));
+        if (b < 0 || !(S.cost[b] > 0.0f)) continue;
+        // the edges (u,v), (u,w), (v,w) of a triangle u < v < w stand in this order in the list
+        const int e0 = min(e, min(a, b)), e2 = max(e, max(a, b)), e1 = e + a + b - e0 - e2;
+        const uint32_t at = atomicAdd(&S.count[2], 1u);
+        if (at < (uint32_t)kTailTriangles) {
+            S.work[kSepKey + at] = (uint32_t)e0 << 13 | (uint32_t)e1;
+            third[at] = (uint16_t)e2;
         }
     }
     __syncthreads();
@@ -268,7 +296,7 @@ __device__ __forceinline__ void tail_messages(TailShared &S, int m, uint32_t T, 
         for (int r = 0; r < kTriItems; ++r)
             if ((uint32_t)r < rows && base + (uint32_t)r * 64u < T) {
                 key[r] = S.work[kSepKey + base + (uint32_t)r * 64u];
-                val[r] = S.work[kSepThird + base + (uint32_t)r * 64u];
+                val[r] = reinterpret_cast<const uint16_t *>(S.work + kSepThird)[base + (uint32_t)r * 64u];
             }
     }
     __syncthreads();

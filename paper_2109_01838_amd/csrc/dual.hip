@@ -379,6 +379,7 @@ struct HeadFlagT {
 template <typename KT>
 struct TrianglesEmit {
     static constexpr const char *tag = sizeof(KT) == 8 ? "Triangles64" : "Triangles";
+    static constexpr bool long_chain = true;   // key -> nodes -> row -> entry: four loads that wait for each other
     const KT *key;
     const int32_t *rowptr, *j;
     int dbits;
@@ -491,22 +492,26 @@ __global__ __launch_bounds__(kBlock) void k_triangle_update(size_t T, const uint
 // per load instruction than one-thread-per-edge loops do -- and then every thread adds up its own
 // runs from LDS, in slot order (ordered sum: bit-reproducible).  Against the per-edge loop this took
 // the kernel from 14.7 to 11.5 ms per solve at the 320^3 grid.
+// Few active edges do not fill the chip with 1024 per workgroup, so up to 2^21 of them come 256 to a workgroup: 8.2 -> 3.7 us
+// a launch in the solve of a 128^2 long-range grid, two dual rounds on a 180x181 one 2.99 -> 2.87 ms.  The line at 2^18, 2^20
+// or 2^22 measures the same there and on the larger graphs; 256 for every length costs the 320^3 grid 94.4 -> 96.2 ms.
 constexpr int kEdgesPerThread = 4;
+constexpr size_t kFewEdges = size_t(1) << 21;
 constexpr int kSlotsPerThread = 8;
 constexpr int kEdgeChunk = kSlotsPerThread * kBlock;
-template <bool STORE_CE>
+template <bool STORE_CE, int PER>
 __global__ __launch_bounds__(kBlock) void k_edge_update(size_t na, const uint32_t *act_edge, const uint32_t *act_start,
                                                                const uint32_t *slot, const float *msg, float *ce, float *share)
 {
     __shared__ float sm[kEdgeChunk];
-    const size_t a0 = (size_t)xcd_block() * (kBlock * kEdgesPerThread);
+    const size_t a0 = (size_t)xcd_block() * (kBlock * PER);
     if (a0 >= na) return;      // the whole workgroup
-    const size_t alast = a0 + kBlock * kEdgesPerThread < na ? a0 + kBlock * kEdgesPerThread : na;
+    const size_t alast = a0 + kBlock * PER < na ? a0 + kBlock * PER : na;
     const uint32_t P0 = act_start[a0], P1 = act_start[alast];
-    uint32_t p0[kEdgesPerThread], p1[kEdgesPerThread];
-    float acc[kEdgesPerThread];
+    uint32_t p0[PER], p1[PER];
+    float acc[PER];
 #pragma unroll
-    for (int j = 0; j < kEdgesPerThread; ++j) {
+    for (int j = 0; j < PER; ++j) {
         const size_t a = a0 + (size_t)j * kBlock + threadIdx.x;
         p0[j] = 0; p1[j] = 0; acc[j] = 0.0f;
         if (a < na) { p0[j] = act_start[a]; p1[j] = act_start[a + 1]; }
@@ -524,14 +529,14 @@ __global__ __launch_bounds__(kBlock) void k_edge_update(size_t na, const uint32_
             if (q[k] != 0xffffffffu) sm[k * kBlock + threadIdx.x] = msg[q[k]];
         __syncthreads();
 #pragma unroll
-        for (int j = 0; j < kEdgesPerThread; ++j) {
+        for (int j = 0; j < PER; ++j) {
             const uint32_t lo = p0[j] > cb ? p0[j] : cb, hi = p1[j] < cend ? p1[j] : cend;
             for (uint32_t p = lo; p < hi; ++p) acc[j] = acc[j] + sm[p - cb];
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int j = 0; j < kEdgesPerThread; ++j) {
+    for (int j = 0; j < PER; ++j) {
         const size_t a = a0 + (size_t)j * kBlock + threadIdx.x;
         if (a < na) {
             if (STORE_CE) ce[act_edge[a]] = acc[j];
@@ -850,12 +855,19 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
         {
             const bool store_ce = it == k_iters || lb_trace != nullptr;
             ProfScope ps_(ctx, store_ce ? "k_edge_update<true>" : "k_edge_update<false>", (double)(na * (store_ce ? 16 : 8) + 3 * T * 8));
-            if (store_ce)
-                k_edge_update<true><<<xcd_grid(grid_for(na, kBlock * kEdgesPerThread)), kBlock, 0, ctx.stream>>>(na, act_edge.get(), act_start.get(), slot.get(),
-                                                                         msg.get(), ce, share.get());
-            else
-                k_edge_update<false><<<xcd_grid(grid_for(na, kBlock * kEdgesPerThread)), kBlock, 0, ctx.stream>>>(na, act_edge.get(), act_start.get(), slot.get(),
-                                                                          msg.get(), ce, share.get());
+            auto update = [&](auto store, auto per) {
+                constexpr int kPer = decltype(per)::value;
+                k_edge_update<decltype(store)::value, kPer><<<xcd_grid(grid_for(na, kBlock * kPer)), kBlock, 0, ctx.stream>>>(
+                    na, act_edge.get(), act_start.get(), slot.get(), msg.get(), ce, share.get());
+            };
+            using std::integral_constant;
+            if (na <= kFewEdges) {
+                if (store_ce) update(std::true_type{}, integral_constant<int, 1>{});
+                else update(std::false_type{}, integral_constant<int, 1>{});
+            } else {
+                if (store_ce) update(std::true_type{}, integral_constant<int, kEdgesPerThread>{});
+                else update(std::false_type{}, integral_constant<int, kEdgesPerThread>{});
+            }
         }
         LAUNCH_TRY(ctx, "edge_update");
         if (lb_trace) {

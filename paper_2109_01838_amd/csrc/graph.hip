@@ -86,6 +86,20 @@ struct PackEdgesEmit {
     }
 };
 
+// the same as a source of the sort
+struct InputEdges {
+    const int32_t *i, *j;
+    const float *c;
+    int dbits;
+    __device__ __forceinline__ uint64_t key(size_t e) const
+    {
+        const int32_t a = i[e], b = j[e];
+        return edge_key((uint32_t)min(a, b), (uint32_t)max(a, b), dbits);
+    }
+    __device__ __forceinline__ bool takes_part(uint64_t k) const { return (k & ((uint64_t(1) << dbits) - 1u)) != 0u; }   // hi > lo
+    __device__ __forceinline__ uint32_t value(size_t e) const { return __float_as_uint(c[e]); }
+};
+
 struct HeadFlag {
     static constexpr int bytes = 8;   // bytes read per item
     static constexpr const char *tag = "HeadFlag";
@@ -101,7 +115,7 @@ struct HeadFlag {
 // in two runs, a range with more edges than fit and a node with more than kRowMax of them raise *flag: the list is then
 // canonicalised the general way.
 // Bounded by LDS latency and the barriers between the steps: 0.79 ms for 9.8e7 edges of the 320^3 grid, where a copy of the
-// 24 bytes per edge takes 0.45 and packing, merging and summing took 2.7; 160^3 grid (1.2e7 edges) 0.37 -> 0.11 ms.
+// 24 bytes per edge takes 0.45 and packing, merging and summing took 2.7; 84 us for the 1.2e7 of a 160^3 one.
 constexpr int kRangeEdges = 3072, kRangeNodes = 1024, kRowMax = 64;
 constexpr int kRangeItems = kRangeEdges / kBlock;
 struct Runs {
@@ -445,34 +459,45 @@ rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const
     Buf<uint32_t> val;
     RAMA_TRY(key.alloc(ctx, kept));
     RAMA_TRY(val.alloc(ctx, kept));
-    RAMA_TRY((scan_emit<uint32_t>(ctx, NotLoop{i, j}, PackEdgesEmit{i, j, c, dbits, key.get(), val.get()}, keep,
-                                  (double)((size_t)m * 4 + (size_t)kept * 12))));
-    keep.offs.reset();
     Buf<uint32_t> head_sums;   // heads per scan tile, if the sort's last kernel could count them
-    bool merged = false;
-    if (hf[3] < kMergeRuns && kept > (uint32_t)LocalSort<uint64_t>::cap) {
-        // few places where the order breaks: the packed list is a handful of sorted runs (dropping self-loops cannot
-        // add any): find their starts and merge them, one pass per doubling, instead of sorting by all key bits
-        Buf<uint32_t> desc;
-        RAMA_TRY(zeroed<uint32_t>(ctx, kMergeRuns, desc));
-        {
-            ProfScope ps_(ctx, "k_find_descents", (double)kept * 8);
-            k_find_descents<<<grid_for(kept), kBlock, 0, ctx.stream>>>(key.get(), kept, desc.get());
+    const bool few_runs = hf[3] < kMergeRuns;
+    if (!few_runs && sort_takes_source(kept, (size_t)m)) {      // the sort's first pass reads the edges itself
+        Buf<uint64_t> key2;
+        Buf<uint32_t> val2;
+        RAMA_TRY(key2.alloc(ctx, kept));
+        RAMA_TRY(val2.alloc(ctx, kept));
+        keep.offs.reset();
+        RAMA_TRY((radix_sort_source<uint64_t, uint32_t>(ctx, InputEdges{i, j, c, dbits}, (size_t)m, key, val, key2, val2, kept, nbits + dbits,
+                                                        &head_sums, (uint64_t)n << dbits)));
+    } else {
+        RAMA_TRY((scan_emit<uint32_t>(ctx, NotLoop{i, j}, PackEdgesEmit{i, j, c, dbits, key.get(), val.get()}, keep,
+                                      (double)((size_t)m * 4 + (size_t)kept * 12))));
+        keep.offs.reset();
+        bool merged = false;
+        if (few_runs && kept > (uint32_t)LocalSort<uint64_t>::cap) {
+            // few places where the order breaks: the packed list is a handful of sorted runs (dropping self-loops cannot
+            // add any): find their starts and merge them, one pass per doubling, instead of sorting by all key bits
+            Buf<uint32_t> desc;
+            RAMA_TRY(zeroed<uint32_t>(ctx, kMergeRuns, desc));
+            {
+                ProfScope ps_(ctx, "k_find_descents", (double)kept * 8);
+                k_find_descents<<<grid_for(kept), kBlock, 0, ctx.stream>>>(key.get(), kept, desc.get());
+            }
+            LAUNCH_TRY(ctx, "find_descents");
+            uint32_t hd[kMergeRuns];
+            RAMA_TRY(read_back(ctx, hd, desc.get(), sizeof hd));
+            if (hd[0] < (uint32_t)kMergeRuns) {
+                std::vector<uint32_t> start(hd + 1, hd + 1 + hd[0]);
+                start.push_back(0u);
+                start.push_back(kept);
+                std::sort(start.begin(), start.end());
+                RAMA_TRY(merge_runs(ctx, key, val, kept, start));
+                merged = true;
+            }
         }
-        LAUNCH_TRY(ctx, "find_descents");
-        uint32_t hd[kMergeRuns];
-        RAMA_TRY(read_back(ctx, hd, desc.get(), sizeof hd));
-        if (hd[0] < (uint32_t)kMergeRuns) {
-            std::vector<uint32_t> start(hd + 1, hd + 1 + hd[0]);
-            start.push_back(0u);
-            start.push_back(kept);
-            std::sort(start.begin(), start.end());
-            RAMA_TRY(merge_runs(ctx, key, val, kept, start));
-            merged = true;
-        }
+        if (!merged)
+            RAMA_TRY((radix_sort_pairs<uint64_t, uint32_t>(ctx, key, val, kept, nbits + dbits, false, &head_sums, (uint64_t)n << dbits)));
     }
-    if (!merged)
-        RAMA_TRY((radix_sort_pairs<uint64_t, uint32_t>(ctx, key, val, kept, nbits + dbits, false, &head_sums, (uint64_t)n << dbits)));
     ScanPlan<uint32_t> runs;
     RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, kept, 0, runs)));
     RAMA_TRY((scan_totals<uint32_t>(ctx, HeadFlag{key.get()}, runs, head_sums.get())));

@@ -667,14 +667,22 @@ struct alignas(16) KeyVec {
     K k[16 / sizeof(K)];
 };
 
+// The first pass of a sort may take its keys and values from a source instead of arrays: a functor that makes the key and
+// the value of a place and tells by the key whether the place takes part (key 0 never does) or is left out.  What a
+// compaction in front of the sort would write and the pass read again then never exists (both sides stand at
+// RelabelledEdges).  All keys of a thread are made before the first is looked at: with a branch per place the loads
+// wait one for the other, and the pass took 4.4 instead of 2.9 ms per solve of the 320^3 grid.
+struct NoSource {};
+
 // The [digit][tile] tables of a pass: a workgroup stores (and later fetches) one word in each of up to 256 rows.
 // Workgroups take their tiles by xcd_block(): with tile = workgroup number, a cache line of a row collected the
 // words of sixteen workgroups on eight XCDs, two words per L2, and went to memory in pieces (26 MB written for a
 // 3.2 MB table); the runs the scatter kernel writes for neighbouring tiles meet in one L2 as well.
-template <typename K, int ITEMS>
-__global__ __launch_bounds__(kBlock) void k_rs_hist(const K *keys, uint32_t *hist, size_t n, int shift, int bits,
+template <typename K, int ITEMS, typename SRC>
+__global__ __launch_bounds__(kBlock) void k_rs_hist(const K *keys, SRC src, uint32_t *hist, size_t n, int shift, int bits,
                                                     uint32_t nb)
 {
+    constexpr bool kFromSource = !std::is_same<SRC, NoSource>::value;
     constexpr int kPer = 16 / (int)sizeof(K);                 // keys per vector
     constexpr int kVecs = ITEMS / kPer;                       // vectors per thread
     constexpr int kTile = kBlock * ITEMS;
@@ -686,33 +694,46 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const K *keys, uint32_t *his
     const uint32_t tile_id = xcd_block();
     if (tile_id >= nb) return;      // the whole workgroup (padding of the grid)
     const size_t tile = (size_t)tile_id * kTile;
-    if (tile + kTile <= n) {                      // full tile: vector loads (tile starts are 16-byte aligned)
-        const KeyVec<K> *src = reinterpret_cast<const KeyVec<K> *>(keys + tile);
+    // The top digits of nearly sorted keys (edge lists keyed by their first endpoint, the edges of
+    // triangles listed triangle by triangle) take one, two or three values across a wave more often
+    // than not, and atomics on one LDS word run one after the other: up to four times the lanes that
+    // share the digit of the first lane left add their count once, as long as they are eight or more
+    // (spread digits pay for one look only: on a neighbour graph's keys four looks per key made this
+    // kernel 68 % slower); what is left then adds lane by lane.
+    auto count = [&](K key, uint64_t left) {      // left: the lanes that hold a key, the same in all of them and not 0
+        const uint32_t d = (uint32_t)(key >> shift) & mask;
+#pragma unroll
+        for (int round = 0; round < 4; ++round) {
+            const int first = __ffsll((long long)left) - 1;
+            const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
+            const uint64_t same = __ballot(d == d0) & left;
+            if (__popcll(same) < 8) break;                                     // uniform: digits are spread, no point
+            if (lane_id() == first) atomicAdd(&h[d0], (uint32_t)__popcll(same));
+            left &= ~same;
+            if (left == 0ull) break;                                           // uniform
+        }
+        if (left & (1ull << lane_id())) atomicAdd(&h[d], 1u);
+    };
+    if constexpr (kFromSource) {
+        K key[ITEMS];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const size_t idx = tile + (size_t)r * kBlock + threadIdx.x;
+            const K k = src.key(idx < n ? idx : n - 1);
+            key[r] = idx < n ? k : (K)0;
+        }
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint64_t lanes = __ballot(src.takes_part(key[r]));
+            if (lanes) count(key[r], lanes);                                   // uniform
+        }
+    } else if (tile + kTile <= n) {               // full tile: vector loads (tile starts are 16-byte aligned)
+        const KeyVec<K> *from = reinterpret_cast<const KeyVec<K> *>(keys + tile);
 #pragma unroll
         for (int r = 0; r < kVecs; ++r) {
-            KeyVec<K> v = src[(size_t)r * kBlock + threadIdx.x];
+            KeyVec<K> v = from[(size_t)r * kBlock + threadIdx.x];
 #pragma unroll
-            for (int q = 0; q < kPer; ++q) {
-                // The top digits of nearly sorted keys (edge lists keyed by their first endpoint, the edges of
-                // triangles listed triangle by triangle) take one, two or three values across a wave more often
-                // than not, and atomics on one LDS word run one after the other: up to four times the lanes that
-                // share the digit of the first lane left add their count once, as long as they are eight or more
-                // (spread digits pay for one look only: on a neighbour graph's keys four looks per key made this
-                // kernel 68 % slower); what is left then adds lane by lane.
-                const uint32_t d = (uint32_t)(v.k[q] >> shift) & mask;
-                uint64_t left = ~0ull;
-#pragma unroll
-                for (int round = 0; round < 4; ++round) {
-                    const int first = __ffsll((long long)left) - 1;
-                    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)d, first);
-                    const uint64_t same = __ballot(d == d0) & left;
-                    if (__popcll(same) < 8) break;                                     // uniform: digits are spread, no point
-                    if (lane_id() == first) atomicAdd(&h[d0], (uint32_t)__popcll(same));
-                    left &= ~same;
-                    if (left == 0ull) break;                                           // uniform
-                }
-                if (left & (1ull << lane_id())) atomicAdd(&h[d], 1u);
-            }
+            for (int q = 0; q < kPer; ++q) count(v.k[q], ~0ull);
         }
     } else {
         for (size_t idx = tile + threadIdx.x; idx < n; idx += kBlock)
@@ -769,11 +790,12 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, int bits, uint64_t v
 // With LOCAL_SCAN (few tiles) `offs` is the raw [digit][tile] histogram and every workgroup derives
 // its own global offsets from it, which saves the scan launch of the pass.
 constexpr uint32_t kSortLocalScanTiles = 32;
-template <typename K, typename V, bool HAS_V, bool LOCAL_SCAN, int ITEMS>
-__global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vin, K *kout, V *vout,
+template <typename K, typename V, bool HAS_V, bool LOCAL_SCAN, int ITEMS, typename SRC>
+__global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vin, SRC src, K *kout, V *vout,
                                                        const uint32_t *offs, size_t n, int shift, int bits,
                                                        uint32_t nb)
 {
+    constexpr bool kFromSource = !std::is_same<SRC, NoSource>::value;
     constexpr int kSortItems = ITEMS;
     constexpr int kSortTile = kBlock * ITEMS;
     __shared__ uint32_t whist[4][kRadix];
@@ -796,13 +818,24 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vi
     for (int r = 0; r < kSortItems; ++r) {
         size_t idx = wave_base + (size_t)r * 64 + lane;
         bool valid = idx < n;
-        key[r] = valid ? kin[idx] : (K)0;
-        if (HAS_V) val[r] = valid ? (vin ? (uint32_t)vin[idx] : (uint32_t)idx) : 0u;   // no array of values: a key's value is its place
+        if constexpr (kFromSource) {
+            const size_t at = valid ? idx : n - 1;
+            const K k = src.key(at);
+            key[r] = valid ? k : (K)0;
+            if (HAS_V) val[r] = src.value(at);
+        } else {
+            key[r] = valid ? kin[idx] : (K)0;
+            if (HAS_V) val[r] = valid ? (vin ? (uint32_t)vin[idx] : (uint32_t)idx) : 0u;   // no array of values: a key's value is its place
+        }
     }
+    auto takes_part = [&](int r) {
+        if constexpr (kFromSource) return src.takes_part(key[r]);
+        else return wave_base + (size_t)r * 64 + lane < n;
+    };
+    uint32_t cnt = (uint32_t)((n - tile_base) < (size_t)kSortTile ? (n - tile_base) : (size_t)kSortTile);
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
-        size_t idx = wave_base + (size_t)r * 64 + lane;
-        bool valid = idx < n;
+        bool valid = takes_part(r);
         uint32_t d = (uint32_t)(key[r] >> shift) & mask;
         uint64_t m = match_digit(d, bits, __ballot(valid));
         uint32_t before = whist[w][d];
@@ -822,6 +855,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vi
                 tot += c[q][k];
             }
         uint32_t run = block_inclusive_scan(tot, &all) - tot;
+        if (kFromSource) cnt = all;
         uint32_t goff[kDigitsPerThread];
         if (LOCAL_SCAN) {
             // keys of smaller digits (all tiles) + keys of the same digit in earlier tiles
@@ -875,8 +909,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vi
     __syncthreads();
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
-        size_t idx = wave_base + (size_t)r * 64 + lane;
-        if (idx < n) {
+        if (takes_part(r)) {
             uint32_t d = (uint32_t)(key[r] >> shift) & mask;
             uint32_t lpos = whist[w][d] + rank[r];
             skey[lpos] = key[r];
@@ -884,7 +917,6 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vi
         }
     }
     __syncthreads();
-    const uint32_t cnt = (uint32_t)((n - tile_base) < (size_t)kSortTile ? (n - tile_base) : (size_t)kSortTile);
 #pragma unroll
     for (int r = 0; r < kSortItems; ++r) {
         uint32_t idx = (uint32_t)r * kBlock + tid;
@@ -1221,18 +1253,18 @@ inline const char *rs_local_name()
 }
 
 // one pass: histogram, offsets, scatter
-template <typename K, typename V, bool HAS_V, int ITEMS>
-rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist, uint32_t *offs)
+template <typename K, typename V, bool HAS_V, int ITEMS, typename SRC>
+rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist, uint32_t *offs)
 {
     const uint32_t nb = grid_for(n, kBlock * ITEMS);
     {
         ProfScope ps_(ctx, (sizeof(K) == 8 ? "k_rs_hist<u64>" : "k_rs_hist<u32>"), (double)(n * sizeof(K)));
-        k_rs_hist<K, ITEMS><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, hist, n, shift, bits, nb);
+        k_rs_hist<K, ITEMS, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, src, hist, n, shift, bits, nb);
     }
     LAUNCH_TRY(ctx, "rs_hist");
     if (nb <= kSortLocalScanTiles) {
         ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-        k_rs_scatter<K, V, HAS_V, true, ITEMS><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, kb, vb, hist, n, shift, bits, nb);
+        k_rs_scatter<K, V, HAS_V, true, ITEMS, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb);
     } else {
         {
             ProfScope ps_(ctx, "k_rs_rowscan", (double)(((size_t)nb << bits) * 8));
@@ -1240,15 +1272,24 @@ rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, K *kb, V *vb, size_t 
         }
         LAUNCH_TRY(ctx, "rs_rowscan");
         ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-        k_rs_scatter<K, V, HAS_V, false, ITEMS><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, kb, vb, offs, n, shift, bits, nb);
+        k_rs_scatter<K, V, HAS_V, false, ITEMS, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, src, kb, vb, offs, n, shift, bits, nb);
     }
     LAUNCH_TRY(ctx, "rs_scatter");
     return RAMA_OK;
 }
+// ITEMS by the number of keys n; a pass over a source goes over its n_src >= n places in tiles of the same size
+template <typename K, typename V, bool HAS_V, typename SRC>
+rama_status radix_pass_sized(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, size_t places, int shift, int bits,
+                             uint32_t *hist, uint32_t *offs)
+{
+    if (n <= kSortShort) return radix_pass<K, V, HAS_V, 4, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, offs);
+    if (n <= kSortMedium) return radix_pass<K, V, HAS_V, 8, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, offs);
+    return radix_pass<K, V, HAS_V, SortTile<K>::items, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, offs);
+}
 // stable LSD passes over the key bits [shift, shift + total_bits); a/b swap with every pass
-template <typename K, typename V, bool HAS_V>
+template <typename K, typename V, bool HAS_V, typename SRC>
 rama_status radix_passes(Ctx &ctx, K *&ka, V *&va, K *&kb, V *&vb, size_t n, int shift, int total_bits, uint32_t *hist,
-                         uint32_t *offs, bool *result_in_b, bool *iota, K *&kc, V *&vc)
+                         uint32_t *offs, bool *result_in_b, bool *iota, K *&kc, V *&vc, const SRC *&src, size_t n_src)
 {
     const int passes = (total_bits + kRadixBits - 1) / kRadixBits;
     int remaining = total_bits;
@@ -1256,9 +1297,12 @@ rama_status radix_passes(Ctx &ctx, K *&ka, V *&va, K *&kb, V *&vb, size_t n, int
         int bits = (remaining + (passes - p) - 1) / (passes - p);
         const V *vin = (HAS_V && *iota) ? (const V *)nullptr : va;   // the first pass of a sort whose values are the places 0..n-1
         *iota = false;
-        if (n <= kSortShort) RAMA_TRY((radix_pass<K, V, HAS_V, 4>(ctx, ka, vin, kb, vb, n, shift, bits, hist, offs)));
-        else if (n <= kSortMedium) RAMA_TRY((radix_pass<K, V, HAS_V, 8>(ctx, ka, vin, kb, vb, n, shift, bits, hist, offs)));
-        else RAMA_TRY((radix_pass<K, V, HAS_V, SortTile<K>::items>(ctx, ka, vin, kb, vb, n, shift, bits, hist, offs)));
+        if (src) {
+            RAMA_TRY((radix_pass_sized<K, V, HAS_V, SRC>(ctx, ka, vin, *src, kb, vb, n, n_src, shift, bits, hist, offs)));
+            src = nullptr;
+        } else {
+            RAMA_TRY((radix_pass_sized<K, V, HAS_V, NoSource>(ctx, ka, vin, NoSource{}, kb, vb, n, n, shift, bits, hist, offs)));
+        }
         std::swap(ka, kb);
         std::swap(va, vb);
         if (kc) {   // the input must stay as it is: from now on the passes alternate between the two other buffers
@@ -1327,11 +1371,13 @@ static __global__ __launch_bounds__(kBlock) void k_iota(size_t n, uint32_t *p)
     size_t k = (size_t)blockIdx.x * kBlock + threadIdx.x;
     if (k < n) p[k] = (uint32_t)k;
 }
-template <typename K, typename V, bool HAS_V>
+template <typename K, typename V, bool HAS_V, typename SRC = NoSource>
 rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int total_bits, bool *result_in_b, bool iota = false,
                             Buf<uint32_t> *head_sums = nullptr, uint64_t key_limit = 0, K *kc = nullptr, V *vc = nullptr,
-                            K **res_k = nullptr, V **res_v = nullptr)
+                            K **res_k = nullptr, V **res_v = nullptr, const SRC *src = nullptr, size_t n_src = 0)
 {
+    // src (optional): the keys and values come from a source of n_src places, n of which take part; there is no input a
+    // then, and n is more than one workgroup sorts alone
     // kc, vc (optional): a third pair of buffers; the input a is then only read, and the sorted data ends up in b or
     // in c: *res_k, *res_v say where
     // key_limit (optional): all keys are below it (and it needs total_bits bits); 0 = nothing known
@@ -1370,7 +1416,7 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             return RAMA_OK;
         }
     }
-    const uint32_t nb = grid_for(n, kBlock * (n <= kSortShort ? 4 : n <= kSortMedium ? 8 : SortTile<K>::items));
+    const uint32_t nb = grid_for(src ? n_src : n, kBlock * (n <= kSortShort ? 4 : n <= kSortMedium ? 8 : SortTile<K>::items));
     Buf<uint32_t> hist, offs;
     RAMA_TRY(hist.alloc(ctx, (size_t)kRadix * nb));
     RAMA_TRY(offs.alloc(ctx, (size_t)kRadix * nb + kRadix));
@@ -1399,7 +1445,7 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
         const bool split = narrow || plan(LocalSort<uint64_t>::cap, &top_bits);
         if (split) {
             const int low_bits = total_bits - top_bits;
-            RAMA_TRY((radix_passes<K, V, HAS_V>(ctx, ka, va, kb, vb, n, low_bits, top_bits, hist.get(), offs.get(), result_in_b, &iota, kc, vc)));
+            RAMA_TRY((radix_passes<K, V, HAS_V, SRC>(ctx, ka, va, kb, vb, n, low_bits, top_bits, hist.get(), offs.get(), result_in_b, &iota, kc, vc, src, n_src)));
             bool done = false;
             if (narrow) RAMA_TRY((split_sort_tail<K, V, HAS_V, uint32_t>(ctx, ka, va, kb, vb, n, low_bits, &done, head_sums)));
             else RAMA_TRY((split_sort_tail<K, V, HAS_V, uint64_t>(ctx, ka, va, kb, vb, n, low_bits, &done, head_sums)));
@@ -1410,7 +1456,7 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             }
         }
     }
-    RAMA_TRY((radix_passes<K, V, HAS_V>(ctx, ka, va, kb, vb, n, 0, total_bits, hist.get(), offs.get(), result_in_b, &iota, kc, vc)));
+    RAMA_TRY((radix_passes<K, V, HAS_V, SRC>(ctx, ka, va, kb, vb, n, 0, total_bits, hist.get(), offs.get(), result_in_b, &iota, kc, vc, src, n_src)));
     if (res_k) { *res_k = ka; *res_v = va; }
     return RAMA_OK;
 }
@@ -1437,6 +1483,29 @@ rama_status radix_sort_pairs(Ctx &ctx, Buf<K> &k, Buf<V> &v, size_t n, int total
     bool in_b = false;
     RAMA_TRY((radix_sort_impl<K, V, true>(ctx, k.get(), v.get(), k2.get(), v2.get(), n, total_bits, &in_b, iota, head_sums, key_limit)));
     if (in_b) { k.swap(k2); v.swap(v2); }
+    return RAMA_OK;
+}
+
+// The same sort for the places of a source (see NoSource), n of whose n_src places take part.  k, v and the second pair
+// k2, v2 come in allocated for n each; k2 may hold what the source reads (the first pass writes k and v only).
+// For what one workgroup sorts alone there is no first pass; and the pass goes twice over the places that take no part and
+// keeps its table for them, so where they are more than half the list is compacted first.
+inline bool sort_takes_source(size_t n, size_t n_src)
+{
+    static_assert(LocalSort<uint64_t>::cap <= LocalSort<uint32_t>::cap, "no longer array is sorted by one workgroup");
+    return n > (size_t)LocalSort<uint32_t>::cap && n >= n_src / 2;
+}
+template <typename K, typename V, typename SRC>
+rama_status radix_sort_source(Ctx &ctx, const SRC &source, size_t n_src, Buf<K> &k, Buf<V> &v, Buf<K> &k2, Buf<V> &v2, size_t n, int total_bits,
+                              Buf<uint32_t> *head_sums, uint64_t key_limit)
+{
+    static_assert(sizeof(V) == 4, "32-bit payload");
+    bool in_b = false;
+    K *rk = nullptr;
+    V *rv = nullptr;
+    RAMA_TRY((radix_sort_impl<K, V, true, SRC>(ctx, (K *)nullptr, (V *)nullptr, k.get(), v.get(), n, total_bits, &in_b, false, head_sums, key_limit,
+                                               k2.get(), v2.get(), &rk, &rv, &source, n_src)));
+    if (rk == k2.get()) { k.swap(k2); v.swap(v2); }
     return RAMA_OK;
 }
 

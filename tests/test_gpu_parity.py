@@ -666,6 +666,46 @@ def test_canonicalisation_interleaves_sorted_runs(rama, oracle32, runs, kind):
     assert np.array_equal(np_(rama.find_conflicted_cycles(n, i, j, c, 3)[0]), want[0])
 
 
+# the first pass of the sort takes the edges themselves, unless one workgroup sorts them alone (8192) or less than half remain
+@pytest.mark.parametrize("kept,loops", [(8192, 5), (8193, 0), (8193, 8192), (8193, 8194), (8193, 8195), (8193, 60000), (40961, 1000),
+                                        (196608, 12345), (196609, 100000), (3145729, 77)])
+def test_sort_leaves_self_loops_out(rama, oracle32, kept, loops):
+    rng = np.random.default_rng(kept + loops)
+    n = 60013
+    a, b = rng.integers(0, n, kept), rng.integers(0, n - 1, kept)
+    b += b >= a                                                  # no loop among these; pairs may repeat
+    v = rng.integers(0, n, loops)
+    order = rng.permutation(kept + loops)
+    i, j = np.concatenate([a, v])[order].astype(np.int32), np.concatenate([b, v])[order].astype(np.int32)
+    c = (-np.abs(rng.normal(size=i.size)) - 1e-3).astype(np.float32)
+    wi, wj, wc = oracle32.canonicalise(n, i, j, c)
+    got = rama.contract(n, i, j, c, repeat=1, want_diag=False)
+    assert np.array_equal(np_(got["i"]), wi) and np.array_equal(np_(got["j"]), wj) and np.array_equal(np_(got["c"]), wc)
+
+
+@pytest.mark.parametrize("between", [8192, 8193, 60000, 65998, 65999, 66000, 66001, 66002, 300000])
+def test_contraction_leaves_inner_edges_out(rama, oracle32, between):
+    """1000 cliques of 12 nodes, all attractive, become 1000 nodes: 66000 edges inside them, `between` repulsive ones across."""
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(between)
+    q = np.arange(1000)[:, None] * 12
+    x, y = np.triu_indices(12, 1)
+    key = np.unique(rng.integers(0, 12000, 4 * between) * 12000 + rng.integers(0, 12000, 4 * between))
+    lo, hi = key // 12000, key % 12000
+    key = rng.permutation(key[(lo < hi) & (lo // 12 != hi // 12)])[:between]
+    i = np.concatenate([(q + x).ravel(), key // 12000]).astype(np.int32)
+    j = np.concatenate([(q + y).ravel(), key % 12000]).astype(np.int32)
+    c = np.concatenate([1.0 + rng.random(66000), -1.0 - rng.random(between)]).astype(np.float32)
+    assert i.size == 66000 + between
+    want = oracle32.contract(12000, i, j, c, repeat=1, forest_ratio=1.0)
+    got = rama.contract(12000, i, j, c, params=default_params(forest_ratio=1.0), repeat=1)
+    assert got["n_nodes"] == want["n_nodes"] == 1000
+    assert np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+    assert np.array_equal(np_(got["diag"]), want["diag"][:1000])
+
+
 # --------------------------------------------------------------------------------------------
 # end to end
 # --------------------------------------------------------------------------------------------

@@ -415,17 +415,21 @@ struct CompactKeysEmit {
     }
 };
 
-__global__ __launch_bounds__(kBlock) void k_inner(size_t m, const int32_t *i, const int32_t *j, const float *c,
-                                                  const int32_t *fmap, const uint32_t *pos, uint32_t *key, uint32_t *val)
-{
-    size_t e = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e >= m) return;
-    int32_t a = fmap[i[e]], b = fmap[j[e]];
-    if (a != b) return;
-    uint32_t p = pos[e];
-    key[p] = (uint32_t)a;
-    val[p] = __float_as_uint(c[e]);
-}
+// consumer of the scan over InnerFlag: edge e inside a new node goes to place p.  (Positions of all edges, and a kernel that
+// looks up both endpoints once more to use them, were two passes, 75 us on a 127x160x161
+// grid, where this is one, 51.)
+struct InnerEmit {
+    static constexpr const char *tag = "Inner";
+    const int32_t *i, *fmap;
+    const float *c;
+    uint32_t *key, *val;
+    __device__ __forceinline__ void operator()(size_t e, uint32_t inner, uint32_t p) const
+    {
+        if (!inner) return;
+        key[p] = (uint32_t)fmap[i[e]];
+        val[p] = __float_as_uint(c[e]);
+    }
+};
 
 struct HeadFlag {
     static constexpr int bytes = 8;   // bytes read per item
@@ -1213,20 +1217,16 @@ rama_status contraction_diagonal(Ctx &ctx, const Graph &g, const int32_t *fmap, 
     const size_t m = (size_t)g.m;
     RAMA_TRY(fill<float>(ctx, diag, 0.0f, (size_t)n_new));
     if (m == 0) return RAMA_OK;
-    Buf<uint32_t> pos;
-    RAMA_TRY(pos.alloc(ctx, m + 1));
-    RAMA_TRY((exclusive_scan<uint32_t>(ctx, InnerFlag{g.i.get(), g.j.get(), fmap}, pos.get(), m)));
-    uint32_t kept = 0;
-    RAMA_TRY(read_back(ctx, &kept, pos.get() + m, 4));
+    const InnerFlag inner{g.i.get(), g.j.get(), fmap};
+    ScanPlan<uint32_t> plan;
+    RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, m, 0, plan)));
+    RAMA_TRY((scan_totals<uint32_t>(ctx, inner, plan)));
+    const uint32_t kept = plan.total;
     if (kept == 0) return RAMA_OK;
     Buf<uint32_t> key, val;
     RAMA_TRY(key.alloc(ctx, kept));
     RAMA_TRY(val.alloc(ctx, kept));
-    {
-        ProfScope ps_(ctx, "k_inner", (double)(m * 28 + (size_t)kept * 8));
-        k_inner<<<grid_for(m), kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), g.c.get(), fmap, pos.get(), key.get(), val.get());
-    }
-    LAUNCH_TRY(ctx, "inner");
+    RAMA_TRY((scan_emit<uint32_t>(ctx, inner, InnerEmit{g.i.get(), fmap, g.c.get(), key.get(), val.get()}, plan, (double)((size_t)kept * 16))));
     RAMA_TRY((radix_sort_pairs<uint32_t, uint32_t>(ctx, key, val, kept, bits_for((uint64_t)n_new), false, nullptr, (uint64_t)n_new)));
     {
         ProfScope ps_(ctx, "k_diag_runs", (double)((size_t)kept * 12));

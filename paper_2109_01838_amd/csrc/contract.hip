@@ -132,7 +132,6 @@ constexpr int kAdvItems = 8;
 // thread's eight combine-and-propose steps wait one after the other (contraction of a 300x301 long-range grid 3.06 ->
 // 2.80 ms, 128^2 solve 3.90 -> 3.71, 512^2 8.82 -> 8.59, 6-NN graph of 10^6 points 14.44 -> 14.25).
 constexpr size_t kAdvMedium = size_t(1) << 20;
-constexpr size_t kAdvShort = size_t(1) << 17;
 constexpr uint32_t kMatchBatchMax = 1u << 20;   // candidate lists up to this length run their handshake rounds in batches
 // The edge a node points at (its rank word names it) is matched iff its other end points at it as well: lists of up to 2^20
 // candidates have each candidate find out for both of its ends by itself (ACCEPTS: four more gathers, no k_accept launch in
@@ -154,42 +153,59 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
     const size_t na = *n_list;
     if ((size_t)blockIdx.x * (kBlock * ITEMS) >= na) return;   // the whole workgroup: nothing left of the list here
     const int w = threadIdx.x >> 6, lane = lane_id();
-    const bool short_list = (size_t)gridDim.x * (kBlock * ITEMS) <= kAdvShort;
     const size_t base = (size_t)blockIdx.x * (kBlock * ITEMS) + (size_t)w * (64 * ITEMS) + lane;
     int32_t u[ITEMS], v[ITEMS];
     unsigned long long r[ITEMS];
     uint32_t where[ITEMS];
-    uint32_t keep = 0, cnt = 0, pairs = 0;
+    uint32_t live = 0, won = 0, cnt = 0, pairs = 0;     // bit q: candidate q
+    // a thread's candidates take every step together (places behind the end read the last one): one after the other, each of
+    // them would wait for its chain of gathers alone
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q) {
-        const size_t k = base + (size_t)q * 64;
-        u[q] = 0; v[q] = 0; r[q] = 0ull;
-        bool ok = false, pair = false;
-        if (k < na) {
-            u[q] = a.u[k]; v[q] = a.v[k];
-            // a short list is all latency: its rank words come in with the endpoints instead of after the test
-            // (on a long list that costs more than it saves: most of its candidates do not survive)
-            unsigned long long rk = 0ull;
-            if (!ACCEPTS && short_list) rk = a.r[k];
-            if constexpr (ACCEPTS) {
-                r[q] = rk = a.r[k];
-                const unsigned long long wu = best[u[q]], wv = best[v[q]];
-                pair = wu == rk && wv == rk;
-                ok = !pair && !node_is_matched(u[q], wu, best, gi, gj) && !node_is_matched(v[q], wv, best, gi, gj);
-                if (pair) { mate[u[q]] = v[q]; mate[v[q]] = u[q]; }
-            } else {
-                const int32_t mu = mate[u[q]], mv = mate[v[q]];
-                ok = mu < 0 && mv < 0;
-                pair = mu == v[q];            // this very edge was matched in the round that just ended
-                if (ok) r[q] = short_list ? rk : a.r[k];
-            }
+        const size_t k = base + (size_t)q * 64, at = k < na ? k : na - 1;
+        u[q] = a.u[at]; v[q] = a.v[at];
+        if (ACCEPTS) r[q] = a.r[at];
+    }
+    if constexpr (ACCEPTS) {
+        unsigned long long wu[ITEMS], wv[ITEMS], pu[ITEMS], pv[ITEMS];
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) { wu[q] = best[u[q]]; wv[q] = best[v[q]]; }
+        int32_t xu[ITEMS], yu[ITEMS], xv[ITEMS], yv[ITEMS];
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) {
+            const uint32_t eu = 0xFFFFFFFFu - (uint32_t)wu[q], ev = 0xFFFFFFFFu - (uint32_t)wv[q];
+            xu[q] = gi[eu]; yu[q] = gj[eu]; xv[q] = gi[ev]; yv[q] = gj[ev];
         }
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) { pu[q] = best[xu[q] == u[q] ? yu[q] : xu[q]]; pv[q] = best[xv[q] == v[q] ? yv[q] : xv[q]]; }
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) {
+            const bool pair = wu[q] == r[q] && wv[q] == r[q], in = base + (size_t)q * 64 < na;
+            if (in && pair) won |= 1u << q;
+            if (in && !pair && pu[q] != wu[q] && pv[q] != wv[q]) live |= 1u << q;
+        }
+    } else {
+        int32_t mu[ITEMS], mv[ITEMS];
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) { mu[q] = mate[u[q]]; mv[q] = mate[v[q]]; }
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) {
+            const bool in = base + (size_t)q * 64 < na;
+            if (in && mu[q] == v[q]) won |= 1u << q;               // this very edge was matched in the round that just ended
+            if (in && mu[q] < 0 && mv[q] < 0) live |= 1u << q;
+        }
+#pragma unroll
+        for (int q = 0; q < ITEMS; ++q) r[q] = a.r[(live & (1u << q)) ? base + (size_t)q * 64 : (size_t)0];   // most do not survive
+    }
+#pragma unroll
+    for (int q = 0; q < ITEMS; ++q) {
+        const bool ok = (live & (1u << q)) != 0u, pair = (won & (1u << q)) != 0u;
+        if (ACCEPTS && pair) { mate[u[q]] = v[q]; mate[v[q]] = u[q]; }
         pairs += (uint32_t)__popcll(__ballot(pair));
         const unsigned long long vote = __ballot(ok);
         where[q] = cnt + (uint32_t)__popcll(vote & ((1ull << lane) - 1ull));
         cnt += (uint32_t)__popcll(vote);
         if (ok) {
-            keep |= 1u << q;
             best_after[u[q]] = 0ull;
             best_after[v[q]] = 0ull;
         }
@@ -215,7 +231,7 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
         if (k < w) off += s_wave[k];
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q)
-        if (keep & (1u << q)) {
+        if (live & (1u << q)) {
             const uint32_t p = off + where[q];
             next.u[p] = u[q]; next.v[p] = v[q]; next.r[p] = r[q];
         }

@@ -79,7 +79,8 @@ struct CutCost {
     const int32_t *labels;
     __device__ __forceinline__ double operator()(size_t e) const
     {
-        return labels[i[e]] != labels[j[e]] ? (double)c[e] : 0.0;
+        const float w = c[e];
+        return labels[i[e]] != labels[j[e]] ? (double)w : 0.0;
     }
 };
 

@@ -80,26 +80,18 @@ struct PackCandsEmit {
     const float *c;
     Cands out;
     unsigned long long *best;
-    __device__ __forceinline__ void operator()(size_t e, uint32_t cand, uint32_t p) const
+    struct Item { int32_t u, v; float c; };
+    __device__ __forceinline__ Item load(size_t e) const { return {i[e], j[e], c[e]}; }
+    __device__ __forceinline__ void operator()(size_t e, uint32_t cand, uint32_t p, const Item &x) const
     {
-        int32_t u = 0, v = 0;
         unsigned long long r = 0ull;
         if (cand) {
-            u = i[e]; v = j[e];
-            r = edge_rank(c[e], (uint32_t)e);
-            out.u[p] = u; out.v[p] = v; out.r[p] = r;
+            r = edge_rank(x.c, (uint32_t)e);
+            out.u[p] = x.u; out.v[p] = x.v; out.r[p] = r;
         }
-        if (best) propose_edge(cand != 0u, u, v, r, best);   // uniform
+        if (best) propose_edge(cand != 0u, x.u, x.v, r, best);   // uniform
     }
 };
-
-// first proposals as a launch of their own (short lists, see matching())
-__global__ __launch_bounds__(kBlock) void k_propose(size_t na, Cands a, unsigned long long *best)
-{
-    size_t k = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    const bool valid = k < na;
-    propose_edge(valid, valid ? a.u[k] : 0, valid ? a.v[k] : 0, valid ? a.r[k] : 0ull, best);
-}
 
 // words that atomics of the same launch change are read where the atomics are carried out
 template <typename T>
@@ -137,12 +129,6 @@ constexpr uint32_t kMatchBatchMax = 1u << 20;   // candidate lists up to this le
 // candidates have each candidate find out for both of its ends by itself (ACCEPTS: four more gathers, no k_accept launch in
 // front, and the pairs are noted here).  Contraction of a 300x301 long-range grid 2.68 ->
 // 2.53 ms, 512^2 solve 8.38 -> 8.07, 6-NN graph of 10^6 points 14.28 -> 13.98; on longer lists the gathers cost more than the launch.
-__device__ __forceinline__ bool node_is_matched(int32_t u, unsigned long long word, const unsigned long long *best, const int32_t *gi, const int32_t *gj)
-{
-    const uint32_t e = 0xFFFFFFFFu - (uint32_t)word;
-    const int32_t x = gi[e], y = gj[e];
-    return best[x == u ? y : x] == word;
-}
 template <int ITEMS, bool ACCEPTS>
 __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cands a, int32_t *mate, Cands next,
                                                     const unsigned long long *best, const int32_t *gi, const int32_t *gj,
@@ -305,11 +291,12 @@ struct NumberPairsEmit {
     static constexpr const char *tag = "NumberPairs";
     const int32_t *mate;
     int32_t *fmap;
-    __device__ __forceinline__ void operator()(size_t v, uint32_t root, uint32_t number) const
+    using Item = int32_t;
+    __device__ __forceinline__ Item load(size_t v) const { return mate[v]; }
+    __device__ __forceinline__ void operator()(size_t v, uint32_t root, uint32_t number, Item w) const
     {
         if (!root) return;
         fmap[v] = (int32_t)number;
-        const int32_t w = mate[v];
         if (w >= 0) fmap[w] = (int32_t)number;
     }
 };
@@ -422,12 +409,13 @@ struct CompactKeysEmit {
     int dbits;
     uint64_t *key;
     uint32_t *val;
-    __device__ __forceinline__ void operator()(size_t e, uint32_t keep, uint32_t p) const
+    struct Item { uint64_t k; float c; };
+    __device__ __forceinline__ Item load(size_t e) const { return {raw[e], c[e]}; }
+    __device__ __forceinline__ void operator()(size_t, uint32_t keep, uint32_t p, const Item &x) const
     {
         if (!keep) return;
-        const uint64_t k = raw[e];
-        key[p] = ((k >> 32) << dbits) | (k & 0xFFFFFFFFull);
-        val[p] = __float_as_uint(c[e]);
+        key[p] = ((x.k >> 32) << dbits) | (x.k & 0xFFFFFFFFull);
+        val[p] = __float_as_uint(x.c);
     }
 };
 
@@ -439,11 +427,13 @@ struct InnerEmit {
     const int32_t *i, *fmap;
     const float *c;
     uint32_t *key, *val;
-    __device__ __forceinline__ void operator()(size_t e, uint32_t inner, uint32_t p) const
+    struct Item { int32_t a; float c; };
+    __device__ __forceinline__ Item load(size_t e) const { return {fmap[i[e]], c[e]}; }
+    __device__ __forceinline__ void operator()(size_t, uint32_t inner, uint32_t p, const Item &x) const
     {
         if (!inner) return;
-        key[p] = (uint32_t)fmap[i[e]];
-        val[p] = __float_as_uint(c[e]);
+        key[p] = (uint32_t)x.a;
+        val[p] = __float_as_uint(x.c);
     }
 };
 
@@ -451,7 +441,7 @@ struct HeadFlag {
     static constexpr int bytes = 8;   // bytes read per item
     static constexpr const char *tag = "HeadFlag";
     const uint64_t *key;
-    __device__ __forceinline__ uint32_t operator()(size_t e) const { return (e == 0 || key[e] != key[e - 1]) ? 1u : 0u; }
+    __device__ __forceinline__ uint32_t operator()(size_t e) const { return ((e == 0) | (key[e] != key[e ? e - 1 : 0])) ? 1u : 0u; }
 };
 
 // diag[k] = sum of the values of run k of the sorted keys, in order of appearance (an ordered sum is a chain of adds, so
@@ -857,18 +847,10 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
     setup.add(best_next.get(), 0u, n);
     setup.add(counters.get(), 0u, (size_t)(2 * cap + 4));
     RAMA_TRY(setup.run(ctx));
-    // The list is packed and, on long edge lists, makes the first round's proposals on the way (the packed list is
-    // not read once more just for that: -0.5 ms per solve on the 320^3 grid); on short ones the proposals are a
-    // launch of their own over the candidates only (the fused kernel shuffles for every edge: +0.1-0.2 ms on the
-    // 512^2 grid).
-    const bool fused = cap > 0 && m >= (size_t(1) << 21);
+    // The list is packed and makes the first round's proposals on the way: it is not read once more just for that.
     RAMA_TRY((scan_emit<uint32_t>(ctx, CandFlag{g.c.get(), tau},
-                                  PackCandsEmit{g.i.get(), g.j.get(), g.c.get(), cur, fused ? best.get() : nullptr}, cand,
-                                  (double)((size_t)na * (fused ? 44 : 28)))));
-    if (cap > 0 && !fused) {
-        ProfScope ps_(ctx, "k_propose", (double)((size_t)na * 32));
-        k_propose<<<grid_for(na), kBlock, 0, ctx.stream>>>(na, cur, best.get());
-    }
+                                  PackCandsEmit{g.i.get(), g.j.get(), g.c.get(), cur, cap > 0 ? best.get() : nullptr}, cand,
+                                  (double)((size_t)na * (cap > 0 ? 44 : 28)))));
     LAUNCH_TRY(ctx, "propose");
     // Long lists: one round per look at the counts, so that every launch has its exact size.  Short lists (the launches
     // are empty anyway): as many rounds as should bring the list to what one workgroup finishes (a round keeps about two

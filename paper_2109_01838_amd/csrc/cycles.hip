@@ -37,16 +37,17 @@ struct SplitSignEmit {
     const int32_t *i, *j;
     int32_t *pi, *pj;
     int32_t *ri, *rj;
-    __device__ __forceinline__ void operator()(size_t e, uint64_t sign, uint64_t prefix) const
+    struct Item { int32_t a, b; };
+    __device__ __forceinline__ Item load(size_t e) const { return {i[e], j[e]}; }
+    __device__ __forceinline__ void operator()(size_t, uint64_t sign, uint64_t prefix, const Item &x) const
     {
         if (sign == 0) return;
-        const int32_t a = i[e], b = j[e];
         if (sign == 1ull) {
             const uint32_t p = (uint32_t)prefix;
-            pi[p] = a; pj[p] = b;
+            pi[p] = x.a; pj[p] = x.b;
         } else {
             const uint32_t p = (uint32_t)(prefix >> 32);
-            ri[p] = a; rj[p] = b;
+            ri[p] = x.a; rj[p] = x.b;
         }
     }
 };

@@ -368,7 +368,7 @@ struct HeadFlagT {
     static constexpr int bytes = (int)sizeof(KT);   // bytes read per item
     static constexpr const char *tag = sizeof(KT) == 8 ? "HeadFlag64" : "HeadFlag32";
     const KT *key;
-    __device__ __forceinline__ uint32_t operator()(size_t e) const { return (e == 0 || key[e] != key[e - 1]) ? 1u : 0u; }
+    __device__ __forceinline__ uint32_t operator()(size_t e) const { return ((e == 0) | (key[e] != key[e ? e - 1 : 0])) ? 1u : 0u; }
 };
 
 // Consumer of the scan over the heads of the sorted triangle keys.  The head of run t is triangle t:
@@ -431,7 +431,7 @@ struct HeadFlag32 {
     static constexpr int bytes = 4;   // bytes read per item
     static constexpr const char *tag = "HeadFlag32";
     const uint32_t *key;
-    __device__ __forceinline__ uint32_t operator()(size_t p) const { return (p == 0 || key[p] != key[p - 1]) ? 1u : 0u; }
+    __device__ __forceinline__ uint32_t operator()(size_t p) const { return ((p == 0) | (key[p] != key[p ? p - 1 : 0])) ? 1u : 0u; }
 };
 
 // consumer of the scan over HeadFlag32: run number a of the sorted slot list starts at p and belongs
@@ -444,13 +444,15 @@ struct ActiveEdgesEmit {
     const uint32_t *skey, *sval;
     uint32_t ns, na;
     uint32_t *act_edge, *act_start, *tri_act;
-    __device__ __forceinline__ void operator()(size_t p, uint32_t head, uint32_t before) const
+    struct Item { uint32_t edge, slot; };
+    __device__ __forceinline__ Item load(size_t p) const { return {skey[p], sval[p]}; }
+    __device__ __forceinline__ void operator()(size_t p, uint32_t head, uint32_t before, const Item &x) const
     {
         if (p == 0) act_start[na] = ns;
         const uint32_t a = before + head - 1u;   // the first slot is a head
-        tri_act[sval[p]] = a;
+        tri_act[x.slot] = a;
         if (!head) return;
-        act_edge[a] = skey[p];
+        act_edge[a] = x.edge;
         act_start[a] = (uint32_t)p;
     }
 };

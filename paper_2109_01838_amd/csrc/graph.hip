@@ -77,12 +77,13 @@ struct PackEdgesEmit {
     int dbits;
     uint64_t *key;
     uint32_t *val;
-    __device__ __forceinline__ void operator()(size_t e, uint32_t keep, uint32_t p) const
+    struct Item { int32_t a, b; float c; };
+    __device__ __forceinline__ Item load(size_t e) const { return {i[e], j[e], c[e]}; }
+    __device__ __forceinline__ void operator()(size_t, uint32_t keep, uint32_t p, const Item &x) const
     {
         if (!keep) return;
-        const int32_t a = i[e], b = j[e];
-        key[p] = edge_key((uint32_t)min(a, b), (uint32_t)max(a, b), dbits);
-        val[p] = __float_as_uint(c[e]);
+        key[p] = edge_key((uint32_t)min(x.a, x.b), (uint32_t)max(x.a, x.b), dbits);
+        val[p] = __float_as_uint(x.c);
     }
 };
 
@@ -104,7 +105,7 @@ struct HeadFlag {
     static constexpr int bytes = 8;   // bytes read per item
     static constexpr const char *tag = "HeadFlag";
     const uint64_t *key;
-    __device__ __forceinline__ uint32_t operator()(size_t e) const { return (e == 0 || key[e] != key[e - 1]) ? 1u : 0u; }
+    __device__ __forceinline__ uint32_t operator()(size_t e) const { return ((e == 0) | (key[e] != key[e ? e - 1 : 0])) ? 1u : 0u; }
 };
 
 // ---- a list that consists of a few sorted runs, none of which repeats a pair: one pass ---------------------------

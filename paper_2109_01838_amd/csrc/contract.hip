@@ -366,11 +366,19 @@ __global__ __launch_bounds__(kBlock) void k_relabel_keys(size_t m, const int32_t
 {
     const size_t base = (size_t)blockIdx.x * kScanTile + threadIdx.x;
     uint32_t diff = 0, kept = 0;
+    int32_t fa[kScanItems], fb[kScanItems];      // all gathers before the first store (behind the end: the last edge again)
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        const size_t e = base + (size_t)q * kBlock, at = e < m ? e : m - 1;
+        fa[q] = i[at]; fb[q] = j[at];
+    }
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) { fa[q] = fmap[fa[q]]; fb[q] = fmap[fb[q]]; }
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         const size_t e = base + (size_t)q * kBlock;
         if (e < m) {
-            const int32_t a = fmap[i[e]], b = fmap[j[e]];
+            const int32_t a = fa[q], b = fb[q];
             const uint32_t d = (uint32_t)abs(a - b);
             diff = d > diff ? d : diff;
             kept += a != b ? 1u : 0u;

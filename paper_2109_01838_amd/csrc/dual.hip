@@ -322,8 +322,8 @@ __global__ __launch_bounds__(kBlock) void k_triangle_keys(CycleSet s, size_t nt,
     int32_t a, b, c;
     fan_triangle(s, (uint32_t)q, a, b, c);
     sort3(a, b, c);
-    int32_t e0 = find_edge_in_row(rowptr, j, a, b);
-    int32_t e1 = find_edge_in_row(rowptr, j, a, c);
+    int32_t e0, e1;
+    find_two_in_row(rowptr, j, a, b, c, e0, e1);
     if (e0 < 0 || e1 < 0) { *flag = 1; e0 = 0; e1 = 0; }
     key[q] = ((KT)(uint32_t)e0 << dbits) | (KT)(uint32_t)(e1 - e0);
 }
@@ -356,8 +356,8 @@ __global__ __launch_bounds__(kBlock) void k_new_triangle_keys(CycleSet s, size_t
     const uint32_t total = set.pack(fresh, counter);
     for (uint32_t k = threadIdx.x; k < total; k += kBlock) {
         const uint32_t x = set.slot[k];
-        int32_t e0 = find_edge_in_row(rowptr, j, set.node[0][x], set.node[1][x]);
-        int32_t e1 = find_edge_in_row(rowptr, j, set.node[0][x], set.node[2][x]);
+        int32_t e0, e1;
+        find_two_in_row(rowptr, j, set.node[0][x], set.node[1][x], set.node[2][x], e0, e1);
         if (e0 < 0 || e1 < 0) { *flag = 1; e0 = 0; e1 = 0; }
         key[set.base + k] = ((KT)(uint32_t)e0 << dbits) | (KT)(uint32_t)(e1 - e0);
     }
@@ -391,12 +391,19 @@ struct TrianglesEmit {
     const float *ct_old;
     float *ct;
     bool zero_new;            // new triangles get their zero costs stored (not needed when the first iteration knows)
-    __device__ __forceinline__ void operator()(size_t q, uint32_t head, uint32_t runs_before) const
+    struct Item { int32_t e0, e1, begin, end, node; uint32_t from; };     // edges (u,v), (u,w); row of v; w; where the key came from
+    __device__ __forceinline__ Item load(size_t q) const
+    {
+        const KT k = key[q];
+        const int32_t e0 = (int32_t)(k >> dbits), e1 = e0 + (int32_t)(k & (((KT)1 << dbits) - 1)), v = j[e0];
+        return {e0, e1, rowptr[v], rowptr[v + 1], j[e1], origin ? origin[q] : 0u};
+    }
+    __device__ __forceinline__ void operator()(size_t q, uint32_t head, uint32_t runs_before, const Item &x) const
     {
         const size_t t = (size_t)runs_before + head - 1;   // the run q lies in (the first key is a head)
         if (q == 0 && *flag_in) *flag = 1;
         if (origin) {
-            const uint32_t o = origin[q];
+            const uint32_t o = x.from;
             if (o >= kept_begin && o < kept_end) {
                 const size_t old = o - kept_begin;
                 ct[3 * t] = ct_old[3 * old]; ct[3 * t + 1] = ct_old[3 * old + 1]; ct[3 * t + 2] = ct_old[3 * old + 2];
@@ -404,12 +411,9 @@ struct TrianglesEmit {
         }
         if (!head) return;
         if (!origin && zero_new) { ct[3 * t] = 0.0f; ct[3 * t + 1] = 0.0f; ct[3 * t + 2] = 0.0f; }   // a new triangle starts at zero
-        const KT k = key[q];
-        const int32_t e0 = (int32_t)(k >> dbits);
-        const int32_t e1 = e0 + (int32_t)(k & (((KT)1 << dbits) - 1));
-        int32_t e2 = find_edge_in_row(rowptr, j, j[e0], j[e1]);
+        int32_t e2 = find_edge_between(j, x.begin, x.end, x.node);
         if (e2 < 0) { *flag = 1; e2 = 0; }
-        skey[3 * t + 0] = (uint32_t)e0; skey[3 * t + 1] = (uint32_t)e1; skey[3 * t + 2] = (uint32_t)e2;
+        skey[3 * t + 0] = (uint32_t)x.e0; skey[3 * t + 1] = (uint32_t)x.e1; skey[3 * t + 2] = (uint32_t)e2;
     }
 };
 

@@ -22,12 +22,19 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const 
     const size_t base = (size_t)blockIdx.x * kScanTile + threadIdx.x;
     uint32_t diff = 0, kept = 0, down = 0;      // down: a bit per place of this thread
     bool plain = true;
+    int32_t ea[kScanItems], eb[kScanItems], ep[kScanItems], eq[kScanItems];      // edge and the one before, all read at once
+    float ew[kScanItems];
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        const size_t e = base + (size_t)q * kBlock, at = e < m ? e : m - 1, before = at > 0 ? at - 1 : 0;
+        ea[q] = i[at]; eb[q] = j[at]; ew[q] = c[at]; ep[q] = i[before]; eq[q] = j[before];
+    }
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         const size_t e = base + (size_t)q * kBlock;
         if (e >= m) continue;
-        int32_t a = i[e], b = j[e];
-        float w = c[e];
+        const int32_t a = ea[q], b = eb[q];
+        const float w = ew[q];
         kept += a != b ? 1u : 0u;
         bool bad = a < 0 || a >= n || b < 0 || b >= n || !(fabsf(w) <= 3.402823466e+38f);
         if (bad) {
@@ -37,7 +44,7 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const 
             diff = d > diff ? d : diff;
             bool canon = a < b;
             if (e > 0) {
-                const int32_t pa = i[e - 1], pb = j[e - 1];
+                const int32_t pa = ep[q], pb = eq[q];
                 canon = canon && (pa < a || (pa == a && pb < b));
                 const int32_t lo = min(a, b), hi = max(a, b), plo = min(pa, pb), phi = max(pa, pb);
                 down |= (lo < plo || (lo == plo && hi < phi)) ? 1u << q : 0u;

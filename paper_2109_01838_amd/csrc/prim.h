@@ -1787,15 +1787,23 @@ __global__ __launch_bounds__(kBlock) void k_reduce_runs(size_t m, const uint64_t
     const int local0 = w * kScanWaveItems + lane;
     uint64_t k[kScanItems];
     uint32_t x[kScanItems], v[kScanItems];
+    uint64_t before[kScanItems];      // the key in front of the wave's stretch
+    uint32_t value[kScanItems];
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        const size_t first = tile0 + (size_t)(w * kScanWaveItems + q * 64), e = first + (size_t)lane, at = e < m ? e : m - 1;
+        k[q] = key[at];
+        value[q] = val[at];
+        before[q] = key[first == 0 ? 0 : (first < m ? first : m) - 1];
+    }
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         const int local = local0 + q * 64;
         const size_t e = tile0 + (size_t)local;
-        k[q] = e < m ? key[e] : 0ull;
         uint64_t left = __shfl_up(k[q], 1, 64);
-        if (lane == 0 && e > 0 && e < m) left = key[e - 1];
+        if (lane == 0) left = before[q];
         x[q] = (e < m && (e == 0 || k[q] != left)) ? 1u : 0u;
-        s_val[local] = e < m ? __uint_as_float(val[e]) : 0.0f;
+        s_val[local] = e < m ? __uint_as_float(value[q]) : 0.0f;
         s_head[local] = (uint8_t)(e < m ? x[q] : 1u);   // what lies behind the array ends every run
     }
     uint32_t carry = 0;
@@ -1863,9 +1871,8 @@ inline rama_status reduce_runs(Ctx &ctx, const ScanPlan<uint32_t> &plan, const u
 }
 
 // position of the canonical edge (u,v), u<v, in rows given by rowptr over i (upper CSR) or -1
-__device__ __forceinline__ int32_t find_edge_in_row(const int32_t *rowptr, const int32_t *j, int32_t u, int32_t v)
+__device__ __forceinline__ int32_t find_edge_between(const int32_t *j, int32_t lo, int32_t hi, int32_t v)
 {
-    int32_t lo = rowptr[u], hi = rowptr[u + 1];
     if (hi - lo <= 8) {
         // a short row: eight entries with two 16-byte loads (one wait instead of a chain of probes);
         // what lies behind the row's end is read but not looked at (device arrays end with slack)
@@ -1883,6 +1890,36 @@ __device__ __forceinline__ int32_t find_edge_in_row(const int32_t *rowptr, const
         if (j[mid] < v) lo = mid + 1; else hi = mid;
     }
     return (lo < end && j[lo] == v) ? lo : -1;
+}
+__device__ __forceinline__ int32_t find_edge_in_row(const int32_t *rowptr, const int32_t *j, int32_t u, int32_t v)
+{
+    return find_edge_between(j, rowptr[u], rowptr[u + 1], v);
+}
+// two edges of one row, v < w: one fetch of a short row, and the probes of a long one side by side
+__device__ __forceinline__ void find_two_in_row(const int32_t *rowptr, const int32_t *j, int32_t u, int32_t v, int32_t w, int32_t &ev, int32_t &ew)
+{
+    const int32_t begin = rowptr[u], end = rowptr[u + 1];
+    ev = -1; ew = -1;
+    if (end - begin <= 8) {
+        int32_t row[8];
+        __builtin_memcpy(row, j + begin, sizeof(row));
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            if (begin + k < end && row[k] == v) ev = begin + k;
+            if (begin + k < end && row[k] == w) ew = begin + k;
+        }
+        return;
+    }
+    int32_t lo = begin, hi = end, lo2 = begin, hi2 = end;
+    while (lo < hi || lo2 < hi2) {      // a search that is over probes its last place again and stays
+        const int32_t mid = min(lo + ((hi - lo) >> 1), end - 1), mid2 = min(lo2 + ((hi2 - lo2) >> 1), end - 1);
+        const int32_t x = j[mid], y = j[mid2];
+        if (lo < hi) { if (x < v) lo = mid + 1; else hi = mid; }
+        if (lo2 < hi2) { if (y < w) lo2 = mid2 + 1; else hi2 = mid2; }
+    }
+    const int32_t x = j[min(lo, end - 1)], y = j[min(lo2, end - 1)];
+    if (lo < end && x == v) ev = lo;
+    if (lo2 < end && y == w) ew = lo2;
 }
 
 }  // namespace rama

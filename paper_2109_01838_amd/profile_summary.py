@@ -60,9 +60,12 @@ def event_name(rocprof_name):
     n = short(rocprof_name)
     n = n.replace("unsigned long", "u64").replace("unsigned int", "u32").replace(", ", ",")
     if n.startswith("k_rs_scatter<"):
-        # <key, value, has values, offsets by local scan>: the timers name key and value types only
+        # <key, value, has values, offsets by local scan, ..>: the timers name key and value types only
         args = n[len("k_rs_scatter<"):].rstrip(">").split(",")
         return f"k_rs_scatter<{args[0]},{args[1]}>" if args[2] == "true" else f"k_rs_scatter<{args[0]}>"
+    if n.startswith(("k_rs_hist<", "k_edge_update<")):
+        # <key type | store c_e, items of a thread, ..>: the timers name the first argument only
+        return n.split(",")[0].rstrip(">") + ">"
     if n.startswith("k_rs_local<"):
         # <key, value, has values, key type inside LDS>
         args = n[len("k_rs_local<"):].rstrip(">").split(",")
@@ -72,7 +75,10 @@ def event_name(rocprof_name):
         # the timers name the last functor by its tag: the class name without "Emit"; functors templated on a
         # key type or a length append it where the library does (HeadFlagT<u64> -> HeadFlag64)
         head, args = n.split("<", 1)
-        last = args.strip().rstrip(">").strip().split(",")[-1].strip()
+        parts = args.strip()[:-1].strip().split(",")
+        if parts[-1].strip().isdigit():
+            parts.pop()                       # the number of threads
+        last = parts[-1].strip()
         functor, _, targ = last.partition("<")
         targ = targ.strip().rstrip(">").strip()
         if functor.endswith("Emit"):
@@ -87,7 +93,7 @@ def event_name(rocprof_name):
     if n.startswith(("k_count_cycles<", "k_fill_cycles<")):
         # <longest walk, last level closes from the far endpoint>: the timers name the walk length only
         return n.split(",")[0].rstrip(">") + ">"
-    if "<" in n and not n.startswith(("k_rs_hist<", "k_edge_update<")):
+    if "<" in n:
         return n.split("<", 1)[0]     # plain template arguments (lengths, flags) are not part of the timers' names
     return n
 

@@ -770,25 +770,26 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const K *keys, SRC src, uint
 
 // Offsets of a pass from its [digit][tile] histogram: workgroup d scans row d (keys with digit d in
 // earlier tiles) and stores the row's total behind the table; the scatter kernel adds the keys of
-// smaller digits itself, from the 256 totals.  One launch instead of the three of a general scan.
-static __global__ __launch_bounds__(kBlock) void k_rs_rowscan(const uint32_t *hist, uint32_t *offs, uint32_t nb, uint32_t *totals)
+// smaller digits itself, from the 256 totals.  One launch instead of the three of a general scan.  In place: a thread
+// reads its words before the barriers of the scan and writes the same ones behind them (with tiles of 1024 and 2048 keys
+// a second table took more than the tiles of 6144 ever did).
+static __global__ __launch_bounds__(kBlock) void k_rs_rowscan(uint32_t *hist, uint32_t nb, uint32_t *totals)
 {
-    const uint32_t *in = hist + (size_t)blockIdx.x * nb;
-    uint32_t *out = offs + (size_t)blockIdx.x * nb;
+    uint32_t *row = hist + (size_t)blockIdx.x * nb;
     uint32_t carry = 0;
     for (uint32_t c0 = 0; c0 < nb; c0 += kScanTile) {
         const uint32_t base = c0 + threadIdx.x * kScanItems;
         uint32_t v[kScanItems], s = 0;
 #pragma unroll
         for (int q = 0; q < kScanItems; ++q) {
-            v[q] = (base + q < nb) ? in[base + q] : 0u;
+            v[q] = (base + q < nb) ? row[base + q] : 0u;
             s += v[q];
         }
         uint32_t tot;
         uint32_t run = block_inclusive_scan(s, &tot) - s + carry;
 #pragma unroll
         for (int q = 0; q < kScanItems; ++q) {
-            if (base + q < nb) out[base + q] = run;
+            if (base + q < nb) row[base + q] = run;
             run += v[q];
         }
         carry += tot;
@@ -903,7 +904,7 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vi
             for (int q = 0; q < kDigitsPerThread; ++q) { goff[q] = dig + before[q]; dig += rowsum[q]; }
         } else {
             // offs: per digit the keys in earlier tiles, and behind the table the digits' totals
-            const uint32_t *totals = offs + (size_t)kRadix * nb;
+            const uint32_t *totals = offs + ((size_t)nb << bits);
             uint32_t rows = 0, rowsum[kDigitsPerThread];
 #pragma unroll
             for (int q = 0; q < kDigitsPerThread; ++q) {
@@ -1279,7 +1280,7 @@ inline const char *rs_local_name()
 
 // one pass: histogram, offsets, scatter
 template <typename K, typename V, bool HAS_V, int ITEMS, typename SRC>
-rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist, uint32_t *offs)
+rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist)
 {
     const uint32_t nb = grid_for(n, kBlock * ITEMS);
     {
@@ -1293,11 +1294,11 @@ rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb
     } else {
         {
             ProfScope ps_(ctx, "k_rs_rowscan", (double)(((size_t)nb << bits) * 8));
-            k_rs_rowscan<<<1u << bits, kBlock, 0, ctx.stream>>>(hist, offs, nb, offs + (size_t)kRadix * nb);
+            k_rs_rowscan<<<1u << bits, kBlock, 0, ctx.stream>>>(hist, nb, hist + ((size_t)nb << bits));
         }
         LAUNCH_TRY(ctx, "rs_rowscan");
         ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-        k_rs_scatter<K, V, HAS_V, false, ITEMS, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, src, kb, vb, offs, n, shift, bits, nb);
+        k_rs_scatter<K, V, HAS_V, false, ITEMS, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb);
     }
     LAUNCH_TRY(ctx, "rs_scatter");
     return RAMA_OK;
@@ -1305,16 +1306,16 @@ rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb
 // ITEMS by the number of keys n; a pass over a source goes over its n_src >= n places in tiles of the same size
 template <typename K, typename V, bool HAS_V, typename SRC>
 rama_status radix_pass_sized(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, size_t places, int shift, int bits,
-                             uint32_t *hist, uint32_t *offs)
+                             uint32_t *hist)
 {
-    if (n <= kSortShort) return radix_pass<K, V, HAS_V, 4, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, offs);
-    if (n <= kSortMedium) return radix_pass<K, V, HAS_V, 8, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, offs);
-    return radix_pass<K, V, HAS_V, SortTile<K>::items, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, offs);
+    if (n <= kSortShort) return radix_pass<K, V, HAS_V, 4, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
+    if (n <= kSortMedium) return radix_pass<K, V, HAS_V, 8, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
+    return radix_pass<K, V, HAS_V, SortTile<K>::items, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
 }
 // stable LSD passes over the key bits [shift, shift + total_bits); a/b swap with every pass
 template <typename K, typename V, bool HAS_V, typename SRC>
 rama_status radix_passes(Ctx &ctx, K *&ka, V *&va, K *&kb, V *&vb, size_t n, int shift, int total_bits, uint32_t *hist,
-                         uint32_t *offs, bool *result_in_b, bool *iota, K *&kc, V *&vc, const SRC *&src, size_t n_src)
+                         bool *result_in_b, bool *iota, K *&kc, V *&vc, const SRC *&src, size_t n_src)
 {
     const int passes = (total_bits + kRadixBits - 1) / kRadixBits;
     int remaining = total_bits;
@@ -1323,10 +1324,10 @@ rama_status radix_passes(Ctx &ctx, K *&ka, V *&va, K *&kb, V *&vb, size_t n, int
         const V *vin = (HAS_V && *iota) ? (const V *)nullptr : va;   // the first pass of a sort whose values are the places 0..n-1
         *iota = false;
         if (src) {
-            RAMA_TRY((radix_pass_sized<K, V, HAS_V, SRC>(ctx, ka, vin, *src, kb, vb, n, n_src, shift, bits, hist, offs)));
+            RAMA_TRY((radix_pass_sized<K, V, HAS_V, SRC>(ctx, ka, vin, *src, kb, vb, n, n_src, shift, bits, hist)));
             src = nullptr;
         } else {
-            RAMA_TRY((radix_pass_sized<K, V, HAS_V, NoSource>(ctx, ka, vin, NoSource{}, kb, vb, n, n, shift, bits, hist, offs)));
+            RAMA_TRY((radix_pass_sized<K, V, HAS_V, NoSource>(ctx, ka, vin, NoSource{}, kb, vb, n, n, shift, bits, hist)));
         }
         std::swap(ka, kb);
         std::swap(va, vb);
@@ -1442,10 +1443,11 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
         }
     }
     const uint32_t nb = grid_for(src ? n_src : n, kBlock * (n <= kSortShort ? 4 : n <= kSortMedium ? 8 : SortTile<K>::items));
-    Buf<uint32_t> hist, offs;
-    RAMA_TRY(hist.alloc(ctx, (size_t)kRadix * nb));
-    RAMA_TRY(offs.alloc(ctx, (size_t)kRadix * nb + kRadix));
     const int all_passes = (total_bits + kRadixBits - 1) / kRadixBits;
+    // [digit][tile] and the digits' totals, for the widest digit of a pass (the top bits of a split sort: whole digits)
+    const int digit_bits = n >= ctx.sort_split_min ? kRadixBits : (total_bits + all_passes - 1) / all_passes;
+    Buf<uint32_t> hist;
+    RAMA_TRY(hist.alloc(ctx, ((size_t)nb + 1) << digit_bits));
     if (n >= ctx.sort_split_min) {
         // top bits: whole passes, enough of them for segments that a workgroup can hold.  A workgroup takes the
         // segments that start in half a capacity of places, so what it gets stays below the capacity as long as no
@@ -1470,7 +1472,7 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
         const bool split = narrow || plan(LocalSort<uint64_t>::cap, &top_bits);
         if (split) {
             const int low_bits = total_bits - top_bits;
-            RAMA_TRY((radix_passes<K, V, HAS_V, SRC>(ctx, ka, va, kb, vb, n, low_bits, top_bits, hist.get(), offs.get(), result_in_b, &iota, kc, vc, src, n_src)));
+            RAMA_TRY((radix_passes<K, V, HAS_V, SRC>(ctx, ka, va, kb, vb, n, low_bits, top_bits, hist.get(), result_in_b, &iota, kc, vc, src, n_src)));
             bool done = false;
             if (narrow) RAMA_TRY((split_sort_tail<K, V, HAS_V, uint32_t>(ctx, ka, va, kb, vb, n, low_bits, &done, head_sums)));
             else RAMA_TRY((split_sort_tail<K, V, HAS_V, uint64_t>(ctx, ka, va, kb, vb, n, low_bits, &done, head_sums)));
@@ -1481,7 +1483,7 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             }
         }
     }
-    RAMA_TRY((radix_passes<K, V, HAS_V, SRC>(ctx, ka, va, kb, vb, n, 0, total_bits, hist.get(), offs.get(), result_in_b, &iota, kc, vc, src, n_src)));
+    RAMA_TRY((radix_passes<K, V, HAS_V, SRC>(ctx, ka, va, kb, vb, n, 0, total_bits, hist.get(), result_in_b, &iota, kc, vc, src, n_src)));
     if (res_k) { *res_k = ka; *res_v = va; }
     return RAMA_OK;
 }

@@ -322,6 +322,9 @@ constexpr size_t kListHitsFrom = size_t(1) << 17;
 constexpr int kHeavyRow = 128;
 constexpr unsigned kHeavyGroups = 512;
 constexpr unsigned kSpillGroups = 768;     // three workgroups per CU: what their LDS allows
+constexpr int kWalkRow = 16;               // see WalkList
+constexpr uint32_t kWalkFrom = 4096;
+static_assert(kWalkRow <= kHeavyRow, "what is walked by a thread is not heavy");
 __device__ __forceinline__ bool heavy_edge(const Adj &g, int32_t v0, int max_len)
 {
     return max_len >= 4 && g.ptr[v0 + 1] - g.ptr[v0] > kHeavyRow;
@@ -480,17 +483,42 @@ __global__ __launch_bounds__(kBlock) void k_count_cycles_short(size_t nr, const 
     cnt.p[0][r] = n3; cnt.p[1][r] = n4; cnt.p[2][r] = n5;
 }
 
+// Edges the hashed search has no room for.  Those whose v0 has few attractive neighbours (up to kWalkRow) leave most of a
+// wave idle: when there are many of them (kWalkFrom) they are walked by a thread each, in front of the heavy ones.
+// Separation up to length 5, ms, wave per edge | thread per edge: leaves of a star, 10^5 edges with one neighbour 2718 | 43;
+// leaves of eight hubs, four neighbours, 36000 edges 236 | 28; of 32 hubs, sixteen neighbours, 60000 edges 114 | 73, 2000
+// edges 44 | 520; skewed degrees (10^4 nodes, few such edges) 12.5 | 46; of 64 hubs, 32 neighbours, 30000 edges 77 | 183.
+// They stand at the back of the heavy edges' array: entry q is last[-q].
+struct WalkList {
+    uint32_t *last = nullptr, *n = nullptr;
+    __device__ __forceinline__ uint32_t by_threads() const { return n && *n >= kWalkFrom ? *n : 0u; }
+    __device__ __forceinline__ uint32_t by_waves() const { return n && *n < kWalkFrom ? *n : 0u; }
+    __device__ __forceinline__ uint32_t operator[](size_t q) const { return *(last - q); }
+};
+// the counts of the listed edges that are walked by a thread each (fixed grid, every workgroup strides over the list)
+template <int MAXL, bool MEET>
+__global__ __launch_bounds__(kBlock) void k_count_cycles_listed(WalkList list, const int32_t *ri, const int32_t *rj, Adj g, int max_len,
+                                                                int flags, ListPtrs<uint32_t, MAXL - 2> cnt, uint32_t *saturated)
+{
+    const size_t n = list.by_threads();
+    for (size_t base = (size_t)blockIdx.x * kBlock; base < n; base += (size_t)gridDim.x * kBlock) {
+        const size_t q = base + threadIdx.x;
+        const bool valid = q < n;
+        count_edge<MAXL, MEET>(valid, valid ? list[q] : 0, ri, rj, g, max_len, flags, cnt, nullptr, nullptr, saturated);
+    }
+}
+
 // counts of the listed heavy edges: a wave per edge, lane l takes the first hops l, l+64, ...
 template <int MAXL>
-__global__ __launch_bounds__(kBlock) void k_count_cycles_heavy(const uint32_t *heavy, const uint32_t *n_heavy,
+__global__ __launch_bounds__(kBlock) void k_count_cycles_heavy(const uint32_t *heavy, const uint32_t *n_heavy, WalkList walk,
                                                                const int32_t *ri, const int32_t *rj, Adj g, int max_len,
                                                                int shortest_only, ListPtrs<uint32_t, MAXL - 2> cnt,
                                                                uint32_t *saturated)
 {
-    const uint32_t nh = *n_heavy;
+    const uint32_t n_own = *n_heavy, nh = n_own + walk.by_waves();
     const int lane = (int)(threadIdx.x & 63);
     for (uint32_t h = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); h < nh; h += gridDim.x * (kBlock / 64)) {
-        const uint32_t r = heavy[h];
+        const uint32_t r = h < n_own ? heavy[h] : walk[h - n_own];
         const int32_t v0 = ri[r], vl = rj[r];
         EndRow end;
         end.load(g, vl);
@@ -589,6 +617,17 @@ __global__ __launch_bounds__(kBlock) void k_fill_cycles(size_t nh, const uint32_
     fill_edge<MAXL, MEET>(hit ? hit[h] : (uint32_t)h, ri, rj, g, live, max_len, cnt, off, out);
 }
 
+// the same for the edges k_count_cycles_listed counted
+template <int MAXL, bool MEET>
+__global__ __launch_bounds__(kBlock) void k_fill_cycles_listed(WalkList list, const int32_t *ri, const int32_t *rj, Adj g, int live, int max_len,
+                                                               ListPtrs<uint32_t, MAXL - 2> cnt, ListPtrs<uint64_t, MAXL - 2> off,
+                                                               ListPtrs<int32_t, MAXL - 2> out)
+{
+    const size_t n = list.by_threads();
+    for (size_t q = (size_t)blockIdx.x * kBlock + threadIdx.x; q < n; q += (size_t)gridDim.x * kBlock)
+        fill_edge<MAXL, MEET>(list[q], ri, rj, g, live, max_len, cnt, off, out);
+}
+
 // ---- hashed search for cycles of length up to 5 --------------------------------------------------
 // The same meeting in the middle on rows that are too long for registers and for the staged rows above.  G lanes
 // share a repulsive edge.  They enter every node of the rows of N+(vL)'s entries v3 into a hash table in LDS, with
@@ -598,9 +637,11 @@ __global__ __launch_bounds__(kBlock) void k_fill_cycles(size_t nh, const uint32_
 // wait for a row.  What bounds the kernels: LDS latency (a look is a chain of a row search, a probe and the bits) at the
 // ten to sixteen waves per CU that the tables leave room for.
 // Edges whose rows or entries do not fit the table go to a list that a second launch works off with a table of 4096
-// places; what does not fit there either (more than 64 attractive neighbours at v0, more than 63 at vL) is heavy.
+// places; what does not fit there either is walked (more than 64 attractive neighbours at v0, more than 63 at vL, or rows
+// behind these that hold more entries than the table), by a wave or a thread each (see WalkList).
 constexpr uint32_t kNoKey = 0xffffffffu;
 constexpr uint32_t kHashPairs = 1u << 24;      // beyond that a 32-bit count could overflow
+constexpr int kSpillSlots = 4096;
 template <int G, int SLOTS>
 struct alignas(16) HashStage {
     static constexpr int W = G > 32 ? 2 : 1;   // words of a bit mask over N+(vL); the last bit is "in N+(vL)"
@@ -792,7 +833,8 @@ template <int G, int SLOTS>
 __global__ __launch_bounds__(HashBlock<G>::threads) void k_count_cycles_hash(size_t nr, const uint32_t *list, const uint32_t *n_list,
                                                                            const int32_t *ri, const int32_t *rj, Adj g, int max_len,
                                                                            int shortest_only, ListPtrs<uint32_t, 3> cnt,
-                                                                           uint32_t *spill, uint32_t *n_spill)
+                                                                           uint32_t *spill, uint32_t *n_spill,
+                                                                           WalkList walk)
 {
     constexpr int kEdges = HashBlock<G>::edges;
     __shared__ HashStage<G, SLOTS> stage[kEdges];
@@ -823,7 +865,9 @@ __global__ __launch_bounds__(HashBlock<G>::threads) void k_count_cycles_hash(siz
             cnt.p[0][r] = n3;
             if (max_len >= 4) cnt.p[1][r] = n4;
             if (max_len >= 5) cnt.p[2][r] = n5;
-            if (E.spilled) spill[atomicAdd(n_spill, 1u)] = (uint32_t)r;   // counted again by the kernel behind this one
+            // counted again by a kernel behind this one
+            if (E.spilled && walk.n && E.dA <= kWalkRow) *(walk.last - atomicAdd(walk.n, 1u)) = (uint32_t)r;
+            else if (E.spilled) spill[atomicAdd(n_spill, 1u)] = (uint32_t)r;
         }
     }
 }
@@ -944,16 +988,16 @@ __global__ __launch_bounds__(kBlock) void k_triangles_group(size_t nr, const uin
 // cycles of the listed heavy edges: per round of 64 first hops every lane counts what its hop
 // closes, a wave scan turns the counts into places, and the lane walks again and writes
 template <int MAXL>
-__global__ __launch_bounds__(kBlock) void k_fill_cycles_heavy(const uint32_t *heavy, const uint32_t *n_heavy,
+__global__ __launch_bounds__(kBlock) void k_fill_cycles_heavy(const uint32_t *heavy, const uint32_t *n_heavy, WalkList walk,
                                                               const int32_t *ri, const int32_t *rj, Adj g, int live,
                                                               ListPtrs<uint32_t, MAXL - 2> cnt,
                                                               ListPtrs<uint64_t, MAXL - 2> off,
                                                               ListPtrs<int32_t, MAXL - 2> out)
 {
-    const uint32_t nh = *n_heavy;
+    const uint32_t n_own = *n_heavy, nh = n_own + walk.by_waves();
     const int lane = (int)(threadIdx.x & 63);
     for (uint32_t h = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); h < nh; h += gridDim.x * (kBlock / 64)) {
-        const uint32_t r = heavy[h];
+        const uint32_t r = h < n_own ? heavy[h] : walk[h - n_own];
         int depth = 0;
         size_t place[MAXL - 2];   // cycles of this edge already written, per length
 #pragma unroll
@@ -1024,11 +1068,13 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     const bool wide = 2 * mp > (size_t)12 * (size_t)n;
     if constexpr (MAXL == 5)
         hashed = max_len >= 4 && (ctx.cycle_search == 2 || (ctx.cycle_search == 0 && longest_row > (uint32_t)kRowRegs));
-    Buf<uint32_t> heavy, spill, n_heavy;   // n_heavy[0]: length of the heavy list, [1]: a count saturated, [2]: length of the
-                                           // list of edges that take the large hash table
+    // n_heavy[0]: length of the heavy list, [1]: a count saturated, [2]: length of the list of edges that take the large
+    // hash table, [3]: length of the list of those that do not and are walked by a thread each (in heavy's array, from the back)
+    Buf<uint32_t> heavy, spill, n_heavy;
     RAMA_TRY(heavy.alloc(ctx, may_be_heavy ? mr : 1));
     RAMA_TRY(spill.alloc(ctx, hashed ? mr : 1));
-    RAMA_TRY(zeroed<uint32_t>(ctx, 3, n_heavy));
+    RAMA_TRY(zeroed<uint32_t>(ctx, 4, n_heavy));
+    const WalkList walk = hashed ? WalkList{heavy.get() + (mr - 1), n_heavy.get() + 3} : WalkList{};
     // mode 1 is the walk that fetches a row per path at its last level, kept for comparison; walks of at
     // most three nodes have no such level
     const bool meet = MAXL >= 5 && max_len >= 5 && ctx.cycle_search != 1;
@@ -1036,18 +1082,22 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     const double search_bytes = (double)(mr * (8 + 4 * (size_t)lists) + ((size_t)n + 1) * 4 + mp * 8);
     if constexpr (MAXL == 5) {
         if (hashed) {
-            auto count = [&](auto lanes, auto slots, size_t edges, const uint32_t *list, const uint32_t *n_list, uint32_t *spill_to, uint32_t *n_spill) {
+            auto count = [&](auto lanes, auto slots, size_t edges, const uint32_t *list, const uint32_t *n_list, uint32_t *spill_to, uint32_t *n_spill,
+                             WalkList walked) {
                 constexpr int G = decltype(lanes)::value, S = decltype(slots)::value;
                 ProfScope ps_(ctx, "k_count_cycles_hash", list ? 0.0 : search_bytes);
                 k_count_cycles_hash<G, S><<<grid_for(edges, HashBlock<G>::edges), HashBlock<G>::threads, 0, ctx.stream>>>(
-                    mr, list, n_list, ri, rj, adj, max_len, shortest_only ? 1 : 0, cp, spill_to, n_spill);
+                    mr, list, n_list, ri, rj, adj, max_len, shortest_only ? 1 : 0, cp, spill_to, n_spill, walked);
             };
             using std::integral_constant;
-            if (wide) count(integral_constant<int, 64>{}, integral_constant<int, 1024>{}, mr, nullptr, nullptr, spill.get(), n_heavy.get() + 2);
-            else count(integral_constant<int, 16>{}, integral_constant<int, 256>{}, mr, nullptr, nullptr, spill.get(), n_heavy.get() + 2);
+            if (wide) count(integral_constant<int, 64>{}, integral_constant<int, 1024>{}, mr, nullptr, nullptr, spill.get(), n_heavy.get() + 2, WalkList{});
+            else count(integral_constant<int, 16>{}, integral_constant<int, 256>{}, mr, nullptr, nullptr, spill.get(), n_heavy.get() + 2, WalkList{});
             LAUNCH_TRY(ctx, "count_cycles_hash");
-            count(integral_constant<int, 64>{}, integral_constant<int, 4096>{}, kSpillGroups, spill.get(), n_heavy.get() + 2, heavy.get(), n_heavy.get());
+            count(integral_constant<int, 64>{}, integral_constant<int, kSpillSlots>{}, kSpillGroups, spill.get(), n_heavy.get() + 2, heavy.get(),
+                  n_heavy.get(), walk);
             LAUNCH_TRY(ctx, "count_cycles_hash");
+            ProfScope ps_(ctx, "k_count_cycles_listed", 0.0);
+            k_count_cycles_listed<MAXL, true><<<kHeavyGroups, kBlock, 0, ctx.stream>>>(walk, ri, rj, adj, max_len, walk_flags, cp, n_heavy.get() + 1);
         }
     }
     // triangles only, rows of more than 12 attractive neighbours on average: sixteen lanes per repulsive edge
@@ -1077,7 +1127,7 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     LAUNCH_TRY(ctx, "count_cycles");
     if (may_be_heavy) {
         ProfScope ps_(ctx, "k_count_cycles_heavy", 0.0);
-        k_count_cycles_heavy<MAXL><<<kHeavyGroups, kBlock, 0, ctx.stream>>>(heavy.get(), n_heavy.get(), ri, rj, adj, max_len,
+        k_count_cycles_heavy<MAXL><<<kHeavyGroups, kBlock, 0, ctx.stream>>>(heavy.get(), n_heavy.get(), walk, ri, rj, adj, max_len,
                                                                           shortest_only ? 1 : 0, cp, n_heavy.get() + 1);
         LAUNCH_TRY(ctx, "count_cycles_heavy");
     }
@@ -1149,8 +1199,10 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
             if (wide) write(integral_constant<int, 64>{}, integral_constant<int, 1024>{}, nh, hits, nullptr);
             else write(integral_constant<int, 16>{}, integral_constant<int, 256>{}, nh, hits, nullptr);
             LAUNCH_TRY(ctx, "fill_cycles_hash");
-            write(integral_constant<int, 64>{}, integral_constant<int, 4096>{}, kSpillGroups, spill.get(), n_heavy.get() + 2);
+            write(integral_constant<int, 64>{}, integral_constant<int, kSpillSlots>{}, kSpillGroups, spill.get(), n_heavy.get() + 2);
             LAUNCH_TRY(ctx, "fill_cycles_hash");
+            ProfScope ps_(ctx, "k_fill_cycles_listed", 0.0);
+            k_fill_cycles_listed<MAXL, true><<<kHeavyGroups, kBlock, 0, ctx.stream>>>(walk, ri, rj, adj, live, max_len, cp, op, vp);
         }
     }
     if (wide3) {
@@ -1167,7 +1219,7 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     LAUNCH_TRY(ctx, "fill_cycles");
     if (may_be_heavy) {
         ProfScope ps_(ctx, "k_fill_cycles_heavy", 0.0);
-        k_fill_cycles_heavy<MAXL><<<kHeavyGroups, kBlock, 0, ctx.stream>>>(heavy.get(), n_heavy.get(), ri, rj, adj, live, cp,
+        k_fill_cycles_heavy<MAXL><<<kHeavyGroups, kBlock, 0, ctx.stream>>>(heavy.get(), n_heavy.get(), walk, ri, rj, adj, live, cp,
                                                                          op, vp);
         LAUNCH_TRY(ctx, "fill_cycles_heavy");
     }

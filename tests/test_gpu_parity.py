@@ -125,6 +125,58 @@ def test_hashed_search_at_its_limits(rama, oracle32, isolated, d_a, d_b, row, lm
         assert np.array_equal(np_(got[L]), want[L]), (L + 3, got[L].shape, want[L].shape)
 
 
+# repulsive edges without room in the tables: 4096 and more of those with up to 8 attractive neighbours at their first
+# endpoint are walked by a thread each, fewer of them and those with more neighbours there by a wave each
+@pytest.mark.parametrize("n_edges,row", [(4095, 8), (4096, 8), (4097, 1), (4500, 9), (9000, 4)])
+@pytest.mark.parametrize("lmax,shortest", [(4, False), (5, False), (5, True)])
+def test_edges_without_room_in_the_tables(rama, oracle32, n_edges, row, lmax, shortest):
+    rng = np.random.default_rng(n_edges + row)
+    middle = n_edges + np.arange(200)
+    side = n_edges + 200 + np.arange(64)            # one entry more than a mask holds
+    last = n_edges + 264
+    e = [(v, x) for v in range(n_edges) for x in rng.choice(middle[: 40 * row], row, replace=False)]
+    e += [(x, last) for x in side] + [(y, x) for x in side for y in rng.choice(middle, 3, replace=False)]
+    e += [tuple(rng.choice(middle, 2, replace=False)) for _ in range(300)]
+    key = np.unique([min(a, b) * (last + 1) + max(a, b) for a, b in e])
+    i = np.concatenate([key // (last + 1), np.arange(n_edges)]).astype(np.int32)
+    j = np.concatenate([key % (last + 1), np.full(n_edges, last)]).astype(np.int32)
+    c = np.where(np.arange(i.size) < key.size, 1.0, -1.0).astype(np.float32)
+    n = int(last) + 1
+    want = oracle32.find_conflicted_cycles(n, i, j, c, lmax, shortest_only=shortest)
+    assert want[1].shape[0] > 0
+    got = rama.find_conflicted_cycles(n, i, j, c, lmax, shortest_only=shortest)
+    for L in range(lmax - 2):
+        assert np.array_equal(np_(got[L]), want[L]), (L + 3, got[L].shape, want[L].shape)
+
+
+def test_search_on_a_star_is_no_slower_than_the_walk(rama):
+    """Repulsive edges between the leaves of a star: every row of their far endpoints is the hub's, which no table holds.
+    A wave per edge took 60 times as long as the walk with a thread per edge (2.6 s)."""
+    import time
+    import torch
+    n = 40000
+    rng = np.random.default_rng(3)
+    a, b = np.sort(rng.integers(1, n, (2, 60000)), axis=0)
+    a, b = a[a < b], b[a < b]
+    i = torch.as_tensor(np.concatenate([np.zeros(n - 1), a]).astype(np.int32)).cuda()
+    j = torch.as_tensor(np.concatenate([np.arange(1, n), b]).astype(np.int32)).cuda()
+    c = torch.as_tensor(np.concatenate([np.ones(n - 1), -np.ones(a.size)]).astype(np.float32)).cuda()
+    took = {}
+    try:
+        for mode in (0, 3):
+            rama.set_cycle_search(mode)
+            for _ in range(2):
+                torch.cuda.synchronize()
+                t = time.perf_counter()
+                got = rama.find_conflicted_cycles(n, i, j, c, 5)
+                torch.cuda.synchronize()
+                took[mode] = time.perf_counter() - t
+            assert [g.shape[0] for g in got][1:] == [0, 0] and got[0].shape[0] > 0.9 * a.size
+    finally:
+        rama.set_cycle_search(0)
+    assert took[0] < 3 * took[3], took
+
+
 # graphs whose attractive rows have exactly up to 6 entries are counted with whole rows in registers; 7 take another search
 @pytest.mark.parametrize("row", [1, 5, 6, 7])
 def test_cycles_on_short_rows(rama, oracle32, row):

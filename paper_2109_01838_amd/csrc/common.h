@@ -382,6 +382,17 @@ private:
 
 inline unsigned grid_for(size_t n, int per_block = kBlock) { return (unsigned)((n + per_block - 1) / per_block); }
 
+// The same for kernels that stride over their items: a launch may have fewer than 2^32 threads in one dimension, which is
+// few items at 64 threads to an item (2^26 repulsive edges).
+constexpr unsigned kMostGroups = 1u << 22;
+constexpr unsigned grid_striding(size_t n, int per_block)
+{
+    const size_t groups = (n + (size_t)per_block - 1) / (size_t)per_block;
+    return groups < kMostGroups ? (unsigned)groups : kMostGroups;
+}
+static_assert((uint64_t)grid_striding(size_t(1) << 31, 1) * kBlock < (uint64_t(1) << 32), "threads in one dimension");
+static_assert(grid_striding(kMostGroups - 1, 1) == kMostGroups - 1 && grid_striding(0, 64) == 0 && grid_striding(65, 64) == 2, "one group per 64 items");
+
 // number of bits needed to write values in [0, n)
 inline int bits_for(uint64_t n)
 {

@@ -1086,7 +1086,7 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
                              WalkList walked) {
                 constexpr int G = decltype(lanes)::value, S = decltype(slots)::value;
                 ProfScope ps_(ctx, "k_count_cycles_hash", list ? 0.0 : search_bytes);
-                k_count_cycles_hash<G, S><<<grid_for(edges, HashBlock<G>::edges), HashBlock<G>::threads, 0, ctx.stream>>>(
+                k_count_cycles_hash<G, S><<<grid_striding(edges, HashBlock<G>::edges), HashBlock<G>::threads, 0, ctx.stream>>>(
                     mr, list, n_list, ri, rj, adj, max_len, shortest_only ? 1 : 0, cp, spill_to, n_spill, walked);
             };
             using std::integral_constant;
@@ -1191,7 +1191,7 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
             auto write = [&](auto lanes, auto slots, size_t edges, const uint32_t *list, const uint32_t *n_list) {
                 constexpr int G = decltype(lanes)::value, S = decltype(slots)::value;
                 ProfScope ps_(ctx, "k_fill_cycles_hash", n_list ? 0.0 : fill_bytes);
-                k_fill_cycles_hash<G, S><<<grid_for(edges, HashBlock<G>::edges), HashBlock<G>::threads, 0, ctx.stream>>>(
+                k_fill_cycles_hash<G, S><<<grid_striding(edges, HashBlock<G>::edges), HashBlock<G>::threads, 0, ctx.stream>>>(
                     nh, list, n_list, ri, rj, adj, max_len, live, cp, op, vp);
             };
             using std::integral_constant;

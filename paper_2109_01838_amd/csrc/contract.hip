@@ -663,12 +663,14 @@ __global__ __launch_bounds__(kBlock) void k_mark_conflicts(size_t m, const int32
 // The rounds that fall back to the forest are late ones: few candidates are left, and the kernels above spend their time
 // on launches (four per Boruvka round, one per level of the trees, one per sweep over the components) and on the counts
 // the host looks at in between, 1.0 to 1.9 ms a forest.  One workgroup of 1024 threads walks through all of it between
-// barriers, each thread with up to 32 candidates; only nodes that have a candidate are touched (comp, hook, rep and best
-// start out as v, v, v and 0 for all nodes).  61x97x131 grid, three forests: 10.55 -> 10.16 ms a solve;
-// 6-NN graph of 10^6 points, one forest: 15.54 -> 15.37.
-constexpr uint32_t kShortForest = 32768;
-constexpr int kForestThreads = 1024;
-static_assert(kShortForest == 32u * kForestThreads, "a bit per candidate of a thread");
+// barriers, each thread with up to eight candidates; only nodes that have a candidate are touched (comp, hook, rep and best
+// start out as v, v, v and 0 for all nodes).  A thread's candidates wait for their gathers one after the other, so longer
+// lists are better off with the whole chip.  Contraction of 20000 nodes and 60000 edges with a forest, ms, level by level |
+// here: 1000 candidates 0.44 | 0.30, 4000 0.51 | 0.39, 8000 0.60 | 0.58, 12000 1.09 | 1.27, 16000 1.40 | 2.21, 32000
+// 1.34 | 3.46; a path of 8000 33 | 23, of 24000 118 | 151.  61x97x131 grid, three forests: 10.55 -> 10.16 ms a solve.
+constexpr int kForestThreads = 1024, kForestItems = 8;
+constexpr uint32_t kShortForest = kForestThreads * kForestItems;
+static_assert(kForestItems <= 32, "a bit per candidate of a thread");
 
 __global__ __launch_bounds__(kBlock) void k_forest_init(size_t n, int32_t *comp, int32_t *hook, int32_t *rep, unsigned long long *best)
 {
@@ -684,7 +686,7 @@ __global__ __launch_bounds__(kForestThreads) void k_forest_short(uint32_t na, Ca
 {
     const uint32_t tid = threadIdx.x;
     uint32_t own = 0, tree = 0;      // this thread's candidates tid, tid + 1024, ..; those in the forest
-    for (uint32_t q = 0; q < 32 && tid + q * kForestThreads < na; ++q) own |= 1u << q;
+    for (uint32_t q = 0; q < (uint32_t)kForestItems && tid + q * kForestThreads < na; ++q) own |= 1u << q;
     uint32_t alive = own;
     for (int round = 0; round < 64; ++round) {      // the number of components with an outgoing candidate at least halves
         for (uint32_t left = alive; left; left &= left - 1) {
@@ -779,7 +781,7 @@ __global__ __launch_bounds__(kForestThreads) void k_forest_components(uint32_t n
     const uint32_t tid = threadIdx.x;
     if (tid == 0) s_kept = 0u;
     uint32_t kept = 0;
-    for (uint32_t q = 0; q < 32; ++q) {
+    for (uint32_t q = 0; q < (uint32_t)kForestItems; ++q) {
         const uint32_t k = tid + q * kForestThreads;
         if (k < na && state[k] == 1) kept |= 1u << q;
     }

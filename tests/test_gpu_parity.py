@@ -560,7 +560,7 @@ def test_diagonal_of_long_runs(rama, oracle32, sizes):
     assert np.array_equal(np_(got["diag"]), want["diag"][: len(sizes)])
 
 
-# the forest by one workgroup takes up to 32768 candidates; graphs beyond 6144 nodes, so that the round is not taken whole
+# the forest by one workgroup; graphs beyond 6144 nodes, so that the round is not taken whole
 @pytest.mark.parametrize("kind,n,m,cand", [("random", 20000, 40000, 1), ("random", 20000, 40000, 1024), ("random", 20000, 40000, 32767),
                                            ("random", 20000, 40000, 32768), ("random", 20000, 40000, 32769), ("path", 7000, 0, 0)])
 def test_forest_in_one_workgroup(rama, oracle32, kind, n, m, cand):
@@ -581,6 +581,20 @@ def test_forest_in_one_workgroup(rama, oracle32, kind, n, m, cand):
     assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
     for k in ("i", "j", "c"):
         assert np.array_equal(np_(got[k]), want[k]), k
+
+
+# a list of more than 8192 candidates is not worked off by one workgroup, which takes up to 2.6 times as long
+@pytest.mark.parametrize("cand", [8191, 8192, 8193])
+def test_forest_in_one_workgroup_up_to_its_line(rama, oracle32, cand):
+    from paper_2109_01838_amd import default_params
+    test_forest_in_one_workgroup(rama, oracle32, "random", 20000, 40000, cand)
+    g = inputs.random_graph(20000, 40000, 17)
+    c = np.where(np.arange(g["c"].size) < cand, 1.0, -1.0).astype(np.float32)
+    rama.profile_enable(True)
+    rama.contract(g["n_nodes"], g["i"], g["j"], c, params=default_params(forest_ratio=1.0), repeat=1)
+    names = {k["name"] for k in rama.profile_get()}
+    rama.profile_enable(False)
+    assert ("k_forest_short" in names) == (cand <= 8192), names
 
 
 # --------------------------------------------------------------------------------------------

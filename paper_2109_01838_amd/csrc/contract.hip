@@ -1194,13 +1194,16 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
     if (n_matched == 0) return RAMA_OK;
     RAMA_TRY(fmap.alloc(ctx, n));
     // too few pairs: switch to the spanning forest without conflicts (Sec. 3.1, "fewer than 0.1|V|")
-    if (forest_ratio > 0.0f && (double)n_matched < (double)forest_ratio * (double)g.n) {
+    const bool forest = forest_ratio > 0.0f && (double)n_matched < (double)forest_ratio * (double)g.n;
+    if (!(forest && list.n <= kShortForest)) list = Candidates{};      // nobody else needs it, and what follows needs the memory
+    if (forest) {
         Buf<uint32_t> npos;
         Buf<int32_t> si, sj, rep;
         mate.reset();
         if (used_forest) *used_forest = true;
-        if (list.n <= kShortForest) {
+        if (list.n > 0) {
             RAMA_TRY(forest_short(ctx, g, tau, list, rep, n_matched));
+            list = Candidates{};
             if (n_matched == 0) return RAMA_OK;
         } else {
             RAMA_TRY(forest_set(ctx, g, tau, si, sj, n_matched));
@@ -1215,6 +1218,7 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
     } else {
         RAMA_TRY((scan_enumerate<uint32_t>(ctx, IsPairRoot{mate.get()}, NumberPairsEmit{mate.get(), fmap.get()}, n, (double)(n * 8))));
     }
+    mate.reset();
     n_new = (int32_t)((int64_t)g.n - n_matched);   // S has no cycle: every edge of it removes one node, no need to ask the device
     RAMA_TRY(contract_edges(ctx, g, fmap.get(), n_new, out));
     return RAMA_OK;

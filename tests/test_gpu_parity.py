@@ -1130,6 +1130,20 @@ def test_context_on_a_side_stream_and_two_contexts(rama):
 # --------------------------------------------------------------------------------------------
 # workspace allocator callbacks and per-round records
 # --------------------------------------------------------------------------------------------
+@pytest.mark.parametrize("ratio", [0.0, 1.0], ids=["matching", "forest"])
+def test_contraction_holds_no_memory_of_the_matching(rama, ratio):
+    """What a round without separation needs at most: the matching its candidates twice (2 * 16 bytes), mates and three rank
+    words per node; the contraction relabelled keys, the sort's two pairs and its table, mates and mapping -- and not the
+    candidates.  An eighth of a byte per edge and 64 KiB are allowed for scan plans and counters."""
+    from paper_2109_01838_amd import default_params
+    g = inputs.cfg2(h=100, w=100, n_seeds=33)
+    n, m, na = g["n_nodes"], g["i"].size, int((g["c"] > 0).sum())
+    rama.solve(n, g["i"], g["j"], g["c"], static=True,
+               params=default_params(max_cycle_len_first=0, max_cycle_len_later=0, forest_ratio=ratio, max_rounds=1))
+    most = max(12 * m + 32 * na + 28 * n, 12 * m + 8 * m + 12 * m + 4 * m + m + 8 * n)
+    assert rama.round_stats()[0]["workspace_peak"] <= most + m // 8 + (1 << 16)
+
+
 def test_allocator_callbacks_and_injected_out_of_memory(rama):
     """The workspace comes from the caller's allocator; an allocator that runs dry at its n-th call makes the
     call in progress end with RAMA_ERR_OOM, everything taken so far goes back, and the ctx stays usable."""

@@ -753,7 +753,8 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
     ScanPlan<uint32_t> inc_heads;   // scan over the sorted slot list (incidence); its spare word carries the flag to the host
     // new triangles start at zero costs; when iterations follow at once, nobody stores or fetches those zeros
     // (the first triangle update knows).  Someone who looks at c_t before the first iteration needs them: the
-    // bound trace, a call without iterations, a caller who keeps the triangles.
+    // bound trace, a call without iterations, a caller who keeps the triangles.  Their memory is asked for behind the
+    // incidence sort then, whose two pairs of slot arrays are what a round needs most memory for.
     const bool ct_lazy = T_kept == 0 && k_iters > 0 && lb_trace == nullptr;
     auto triangles = [&](auto key_tag) -> rama_status {
         using KT = decltype(key_tag);
@@ -791,7 +792,7 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
         RAMA_TRY((scan_totals<uint32_t>(ctx, HeadFlagT<KT>{tkey.get()}, heads, head_sums.get())));
         head_sums.reset();
         T = heads.total;
-        RAMA_TRY(ct.alloc(ctx, 3 * T));
+        if (!ct_lazy) RAMA_TRY(ct.alloc(ctx, 3 * T));
         if (T_kept > 0) RAMA_TRY(fill<float>(ctx, ct.get(), 0.0f, 3 * T));   // otherwise the consumer below zeroes what it creates
         RAMA_TRY(skey.alloc(ctx, 3 * T));
         RAMA_TRY(slot.alloc(ctx, 3 * T));
@@ -829,6 +830,7 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
     rowptr.reset();
     // ---- iterations ----------------------------------------------------------------------------
     Buf<float> share, msg;
+    if (ct_lazy) RAMA_TRY(ct.alloc(ctx, 3 * T));
     RAMA_TRY(share.alloc(ctx, na));
     RAMA_TRY(msg.alloc(ctx, 3 * T));
     float *ce = aug.c.get();

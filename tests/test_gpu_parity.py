@@ -1144,6 +1144,17 @@ def test_contraction_holds_no_memory_of_the_matching(rama, ratio):
     assert rama.round_stats()[0]["workspace_peak"] <= most + m // 8 + (1 << 16)
 
 
+@pytest.mark.parametrize("background", [8770, 8840, 8900, 9225])
+def test_static_workspace_near_its_limit(rama, background):
+    """Hubs whose triangles fill the static workspace to nine tenths and more: every one of these solves has to find room."""
+    from paper_2109_01838_amd import default_params
+    g = inputs.hub_graph(n_nodes=4000, hubs=(0, 1000, 2000, 3000), hub_degree=700, n_background=background)
+    params = default_params(max_rounds=4)
+    want = rama.solve(g["n_nodes"], g["i"], g["j"], g["c"], params=params)
+    got = rama.solve(g["n_nodes"], g["i"], g["j"], g["c"], params=params, static=True)
+    assert got["lower_bound"] == want["lower_bound"] and np.array_equal(np_(got["labels"]), np_(want["labels"]))
+
+
 def test_allocator_callbacks_and_injected_out_of_memory(rama):
     """The workspace comes from the caller's allocator; an allocator that runs dry at its n-th call makes the
     call in progress end with RAMA_ERR_OOM, everything taken so far goes back, and the ctx stays usable."""

@@ -282,7 +282,11 @@ rama_status interleave_runs(Ctx &ctx, int32_t n, size_t m, const int32_t *i, con
     LAUNCH_TRY(ctx, "interleave_runs");
     int32_t bad = 0;
     RAMA_TRY(read_back(ctx, &bad, flag.get(), 4));
-    if (bad) { out.sign_sums.reset(); return RAMA_OK; }
+    if (bad) {      // the general way needs the memory
+        out.sign_sums.reset();
+        out.i.reset(); out.j.reset(); out.c.reset();
+        return RAMA_OK;
+    }
     out.m = (int64_t)m;
     *done = true;
     return RAMA_OK;

@@ -1155,6 +1155,25 @@ def test_static_workspace_near_its_limit(rama, background):
     assert got["lower_bound"] == want["lower_bound"] and np.array_equal(np_(got["labels"]), np_(want["labels"]))
 
 
+def test_runs_with_a_repeated_pair_hold_no_memory_of_the_attempt(rama):
+    """Three sorted runs whose last edge repeats a pair of the first: interleaving gives up, and the merge that follows needs
+    two key and two cost arrays (24 bytes per edge) beside what the pool keeps of the attempt, of which the costs take
+    8.  (With the attempt's 12 bytes per edge held it took 36.)"""
+    import torch
+    from paper_2109_01838_amd import Rama
+    s = 100
+    v = np.arange(s ** 3, dtype=np.int32).reshape(s, s, s)
+    i = np.concatenate([v[:-1].ravel(), v[:, :-1].ravel(), v[:, :, :-1].ravel(), v[-2:-1, -1, -1].ravel()])
+    j = np.concatenate([v[1:].ravel(), v[:, 1:].ravel(), v[:, :, 1:].ravel(), v[-1:, -1, -1].ravel()])
+    m = i.size
+    d = [torch.as_tensor(x).cuda() for x in (i, j, np.ones(m, np.float32))]
+    fresh = Rama("cuda:0", allocator="hip")
+    before = fresh.workspace_bytes()
+    assert fresh.find_conflicted_cycles(s ** 3, *d, 3)[0].shape[0] == 0
+    assert fresh.workspace_bytes() - before < 31 * m, (fresh.workspace_bytes() - before) / m
+    fresh.close()
+
+
 def test_allocator_callbacks_and_injected_out_of_memory(rama):
     """The workspace comes from the caller's allocator; an allocator that runs dry at its n-th call makes the
     call in progress end with RAMA_ERR_OOM, everything taken so far goes back, and the ctx stays usable."""

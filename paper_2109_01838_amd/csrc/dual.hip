@@ -596,7 +596,7 @@ rama_status copy_graph(Ctx &ctx, const Graph &g, Graph &out)
 
 rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *const *cycles, const int64_t *n_cycles,
                         bool validate_cycles, int k_iters, Graph &out, double *lower_bound, double *lb_trace,
-                        DualInfo *info, const DualState *prev, DualState *next, Graph *donor)
+                        DualInfo *info, DualState *prev, DualState *next, Graph *donor)
 {
     if (lists < 0 || lists > kCycleLists || k_iters < 0 || (lists > 0 && (!cycles || !n_cycles)))
         return fail(ctx, RAMA_ERR_INVALID_ARG, "message passing: bad cycle lists or iteration count");
@@ -795,7 +795,6 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
         if (!ct_lazy) RAMA_TRY(ct.alloc(ctx, 3 * T));
         if (T_kept > 0) RAMA_TRY(fill<float>(ctx, ct.get(), 0.0f, 3 * T));   // otherwise the consumer below zeroes what it creates
         RAMA_TRY(skey.alloc(ctx, 3 * T));
-        RAMA_TRY(slot.alloc(ctx, 3 * T));
         RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, 3 * T, 1, inc_heads)));
         TrianglesEmit<KT> te{tkey.get(), rowptr.get(), aug.j.get(), dbits, skey.get(), flag.get(),
                              (int32_t *)inc_heads.extra_ptr(), T_kept > 0 ? origin.get() : nullptr, cs.fan_end[kCycleLists - 1], cs.fan_end[kCycleLists],
@@ -806,6 +805,9 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
     if (kbits <= 32) RAMA_TRY(triangles(uint32_t{}));
     else RAMA_TRY(triangles(uint64_t{}));
     if (info) info->n_triangles = (int64_t)T;
+    // the kept triangles are taken over, and the keys are gone: the incidence sort needs the memory
+    if (prev) { prev->tri_nodes.reset(); prev->ct.reset(); }
+    RAMA_TRY(slot.alloc(ctx, 3 * T));
     // ---- incidence: slots of every edge in ascending triangle order ----------------------------
     // (if the flag is up, the edge ids below are placeholders -- all valid indices -- and the result is discarded)
     Buf<uint32_t> inc_head_sums;   // heads per scan tile, if the sort's last kernel could count them

@@ -1174,6 +1174,16 @@ def test_runs_with_a_repeated_pair_hold_no_memory_of_the_attempt(rama):
     fresh.close()
 
 
+@pytest.mark.parametrize("points", [60800, 60000])
+def test_static_workspace_near_its_limit_with_kept_triangles(rama, points):
+    from paper_2109_01838_amd import default_params
+    g = inputs.cfg3(n_points=points, n_seeds=points // 200)
+    params = default_params(max_rounds=2, dual_rounds=2)
+    want = rama.solve(g["n_nodes"], g["i"], g["j"], g["c"], params=params)
+    got = rama.solve(g["n_nodes"], g["i"], g["j"], g["c"], params=params, static=True)
+    assert got["lower_bound"] == want["lower_bound"] and np.array_equal(np_(got["labels"]), np_(want["labels"]))
+
+
 def test_allocator_callbacks_and_injected_out_of_memory(rama):
     """The workspace comes from the caller's allocator; an allocator that runs dry at its n-th call makes the
     call in progress end with RAMA_ERR_OOM, everything taken so far goes back, and the ctx stays usable."""

@@ -527,6 +527,7 @@ rama_status rama_find_conflicted_cycles_room(rama_ctx *ctx, int32_t n_nodes, int
     const int lists = max_cycle_len - 2;
     return finish(*ctx, cycles_into(*ctx, n_nodes, n_edges, i, j, c, max_cycle_len, shortest_only, n_cycles_out,
                                     [&](const int64_t *n, int32_t **to) -> rama_status {
+        for (int q = 0; q < lists; ++q) RAMA_TRY(list_fits(*ctx, q, n[q]));      // nobody is asked for room for what cannot be written
         for (int q = 0; q < lists; ++q)
             if (n[q] > 0) RAMA_TRY(ask_room(*ctx, room, q + 3, (size_t)n[q] * (size_t)(q + 3) * 4, (void **)&to[q]));
         return RAMA_OK;

@@ -463,6 +463,12 @@ struct CycleLists {
 // a0: any edge list -> canonical graph
 rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const int32_t *j, const float *c, Graph &out);
 
+// places in a list of cycles (list q: of length q + 3) are 32-bit numbers
+inline rama_status list_fits(Ctx &ctx, int q, int64_t n)
+{
+    return (uint64_t)(q + 3) * (uint64_t)n < (uint64_t(1) << 31) ? RAMA_OK : fail(ctx, RAMA_ERR_CAPACITY, "cycle list reaches 2^31 entries");
+}
+
 // a1: conflicted cycles of lengths 3..max_len; shortest_only keeps, per repulsive edge, only the
 // cycles of its smallest length.  `sink` (optional) is asked for the lists' memory once the counts are known: list q
 // goes to to[q] (null for an empty list) and out.v stays empty; a failure of the sink ends the search before the

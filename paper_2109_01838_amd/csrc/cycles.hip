@@ -1158,8 +1158,7 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     if (sink) RAMA_TRY(sink(out.n, to));
     double list_bytes = 0.0;
     for (int k = 0; k < lists; ++k) {
-        if ((uint64_t)(k + 3) * tot[k] >= (uint64_t(1) << 31))
-            return fail(ctx, RAMA_ERR_CAPACITY, "cycle list reaches 2^31 entries");
+        RAMA_TRY(list_fits(ctx, k, out.n[k]));
         if (!sink) RAMA_TRY(out.v[k].alloc(ctx, (size_t)(k + 3) * tot[k]));
         vp.p[k] = sink ? to[k] : out.v[k].get();
         list_bytes += 4.0 * (k + 3) * (double)tot[k];

@@ -199,6 +199,31 @@ def test_search_on_more_repulsive_edges_than_one_launch_has_waves(rama):
         assert torch.equal(got[L], want[L]), (L + 3, got[L].shape, want[L].shape)
 
 
+def test_no_room_is_asked_for_what_cannot_be_written(rama):
+    """7.2e8 triangles are a list of more than 2^31 numbers: the call says so before it asks its caller for 8 GiB."""
+    import ctypes as C
+    import torch
+    from paper_2109_01838_amd import RamaError, binding
+    top, many = 240, 25000
+    a, b = (x.to(torch.int32) for x in torch.triu_indices(top, top, 1, device="cuda:0"))
+    i = torch.cat([a, torch.arange(top, device="cuda:0", dtype=torch.int32).repeat_interleave(many)])
+    j = torch.cat([b, (top + torch.arange(many, device="cuda:0", dtype=torch.int32)).repeat(top)])
+    c = torch.ones(i.numel(), device="cuda:0")
+    c[: a.numel()] = -1.0
+    n, want = top + many, a.numel() * many
+    assert 3 * want >= 1 << 31
+    asked, cnt = [], (C.c_int64 * 1)()
+    room = binding.RamaRoom(binding.ROOM_FN(lambda _user, which, nbytes: asked.append((which, nbytes))), None)
+    st = rama.lib.rama_find_conflicted_cycles_room(rama.ctx, n, i.numel(), i.data_ptr(), j.data_ptr(), c.data_ptr(), 3, 0, C.byref(room), cnt)
+    assert (st, asked, cnt[0]) == (binding.RAMA_ERR_CAPACITY, [], want)
+    # the size query of the entry point with buffers answers as before
+    st = rama.lib.rama_find_conflicted_cycles(rama.ctx, n, i.numel(), i.data_ptr(), j.data_ptr(), c.data_ptr(), 3, 0, None, None, cnt)
+    assert (st, cnt[0]) == (binding.RAMA_ERR_CAPACITY, want)
+    with pytest.raises(RamaError) as ei:
+        rama.find_conflicted_cycles(n, i, j, c, 3)
+    assert ei.value.status == binding.RAMA_ERR_CAPACITY and "2^31" in str(ei.value)
+
+
 # graphs whose attractive rows have exactly up to 6 entries are counted with whole rows in registers; 7 take another search
 @pytest.mark.parametrize("row", [1, 5, 6, 7])
 def test_cycles_on_short_rows(rama, oracle32, row):

@@ -788,7 +788,10 @@ __global__ __launch_bounds__(kForestThreads) void k_forest_components(uint32_t n
     __syncthreads();
     const uint32_t n_wave = wave_sum((uint32_t)__popc(kept));
     if (lane_id() == 0 && n_wave) atomicAdd(&s_kept, n_wave);
-    for (int sweep = 0; sweep < 64; ++sweep) {      // the number of trees at least halves per sweep
+    // Until nothing changes: pointers only ever decrease, and two sweeps leave at most half of the roots that are not done.  (A
+    // root that has a smaller neighbour hooks.  One that has none keeps a neighbour's whole tree or meets a smaller root
+    // through it in the next sweep.)
+    for (;;) {
         bool changed = false;
         for (uint32_t left = kept; left; left &= left - 1) {
             const uint32_t k = tid + (uint32_t)(__ffs((int)left) - 1) * kForestThreads;
@@ -1102,7 +1105,7 @@ static rama_status components(Ctx &ctx, size_t n, size_t ns, const int32_t *si, 
     LAUNCH_TRY(ctx, "iota");
     if (ns == 0) return RAMA_OK;
     Buf<int32_t> changed;
-    for (int it = 0; it < 64; ++it) {   // the number of trees at least halves per sweep
+    for (int it = 0; it < 64; ++it) {   // two sweeps leave at most half of the roots that are not done (see k_forest_components)
         RAMA_TRY(zeroed<int32_t>(ctx, 1, changed));   // a fresh word per sweep
         {
             ProfScope ps_(ctx, "k_hook", (double)(ns * 24));

@@ -507,11 +507,11 @@ __device__ __forceinline__ uint32_t tail_forest(TailShared &S, int n, int m, flo
     }
     uint32_t all;
     (void)tail_scan(kept, &all, S.wave);
-    // components: hooking of the larger root onto the smaller, pointers only ever decrease
+    // components: hooking of the larger root onto the smaller until nothing changes (see k_forest_components)
     uint32_t *rep = S.work + kRep;
     for (int v = tid; v < n; v += kTailThreads) rep[v] = (uint32_t)v;
     __syncthreads();
-    for (int sweep = 0; sweep < 64; ++sweep) {
+    for (;;) {
         bool changed = false;
         for (int q = 0; q < kTailItems; ++q) {
             if (!(tree & (1u << q))) continue;

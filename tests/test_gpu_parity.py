@@ -608,6 +608,22 @@ def test_forest_in_one_workgroup(rama, oracle32, kind, n, m, cand):
         assert np.array_equal(np_(got[k]), want[k]), k
 
 
+# the centres of the trees are their largest nodes: a sweep of the components joins one smaller node to each centre
+@pytest.mark.parametrize("n,centres", [(3000, 1), (3000, 40), (7000, 1), (7000, 300)])
+def test_components_of_trees_around_their_largest_nodes(rama, oracle32, n, centres):
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(n + centres)
+    leaves = np.arange(n - centres)
+    i = np.concatenate([leaves, rng.choice(leaves, centres - 1, replace=False)])
+    j = np.concatenate([n - centres + leaves % centres, n - centres + 1 + np.arange(centres - 1)])      # neighbouring trees share a leaf
+    key = np.unique(i * n + j)
+    i, j = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    c = (rng.integers(1, 5, key.size) / 4).astype(np.float32)
+    want = oracle32.contract(n, i, j, c, repeat=1, forest_ratio=1.0)
+    got = rama.contract(n, i, j, c, params=default_params(forest_ratio=1.0), repeat=1)
+    assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
+
+
 # a list of more than 8192 candidates is not worked off by one workgroup, which takes up to 2.6 times as long
 @pytest.mark.parametrize("cand", [8191, 8192, 8193])
 def test_forest_in_one_workgroup_up_to_its_line(rama, oracle32, cand):

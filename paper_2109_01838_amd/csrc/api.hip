@@ -204,10 +204,15 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
     // Later rounds on graphs that one workgroup can hold run there, many in one launch (tail.hip; ms per solve before and
     // with it): 32^2 grid 2.25 and 0.75, 128^2 long-range grid 6.0 and 4.5, 512^2 long-range grid 10.4 and 9.6.
     const bool separates_later = P.max_cycle_len_later >= 3 && P.mp_iters_later > 0;
-    bool tail_ok = !separates_later || (P.max_cycle_len_later == 3 && P.dual_rounds == 1);
+    // A round of more triangles than the workgroup holds is handed back.  The workgroup gets its next try behind a round of
+    // at most kTailNextTry triangles: from more of them the next round does not come down to what it holds.  Solves of 8100
+    // random edges, ms with a try at every round | from 2048 | 8192 | 16384 triangles down: 200 nodes 1.55 | 1.65 | 1.47 | 1.46,
+    // 400 nodes 1.56 | 1.59 | 1.60 | 1.39, 700 nodes 2.08 | 2.08 | 2.17 | 1.97, 1000 nodes 2.20 | 2.14 | 2.09 | 2.13.
+    constexpr int64_t kTailNextTry = 8 * kTailTriangles;
+    bool tail_ok = !separates_later || (P.max_cycle_len_later == 3 && P.dual_rounds == 1), tail_handed_back = false;
     bool finished = false;
     for (int round = 1; !finished && (P.max_rounds <= 0 || round <= P.max_rounds); ++round) {
-        if (round > 1 && tail_ok && tail_fits(g)) {
+        if (round > 1 && tail_ok && !tail_handed_back && tail_fits(g)) {
             Buf<int32_t> ftail;
             TailResult res;
             ctx.active->reset_peak();
@@ -228,6 +233,7 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
                 continue;
             }
             if (P.max_rounds > 0 && round > P.max_rounds) break;
+            tail_handed_back = true;
         }
         const int lmax = round == 1 ? P.max_cycle_len_first : P.max_cycle_len_later;
         const int k = round == 1 ? P.mp_iters_first : P.mp_iters_later;
@@ -292,6 +298,7 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
         R.n_contracted = ns;
         R.used_forest = forest ? 1 : 0;
         R.workspace_peak = (int64_t)ctx.active->peak_live();
+        if (round > 1 && R.n_triangles <= kTailNextTry) tail_handed_back = false;
         clocked.push_back(ctx.rounds.size());
         ctx.rounds.push_back(R);
         if (ns == 0) break;

@@ -502,6 +502,7 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
 // contraction -- on a graph that one workgroup can hold, by a single launch.  fmap[g.n] -> [0, out.n).  out's arrays
 // (room for g.m edges; they may be g's own) get the graph behind the last round.
 constexpr int kTailEdges = 8192, kTailNodes = 6144;
+constexpr int kTailTriangles = 2048;                     // more in a round: the stage kernels take it
 constexpr int kTailMaxRounds = 24, kTailRecord = 6;      // rounds per launch, words of a round's record in the message
 constexpr int kTailDone = 0;        // the last round found nothing to contract
 constexpr int kTailMore = 1;        // max_rounds rounds ran, or kTailMaxRounds

@@ -20,7 +20,6 @@ constexpr int kTailThreads = 1024;
 constexpr int kTailWaves = kTailThreads / 64;
 constexpr int kTailItems = kTailEdges / kTailThreads;          // edges per thread
 constexpr int kTailNodeItems = kTailNodes / kTailThreads;      // nodes per thread
-constexpr int kTailTriangles = 2048;                           // more in a round: the stage kernels take it
 constexpr int kTriItems = kTailTriangles / kTailThreads;
 constexpr int kSlotItems = 3 * kTailTriangles / kTailThreads;
 constexpr int kNodeBits = 13;
@@ -179,8 +178,9 @@ __device__ __forceinline__ int tail_find(const TailShared &S, int m, uint32_t ke
     return lo < m && S.key[lo] == key ? lo : -1;
 }
 
-// Triangles with one repulsive edge (a round that separates up to length 3).  Returns their number; up to
-// kTailTriangles of them are in work[kSepKey..) -- (first edge, second edge) -- and work[kSepThird..), in any order.
+// Triangles with one repulsive edge (a round that separates up to length 3).  Returns their number if it is at most
+// kTailTriangles; they are in work[kSepKey..) -- (first edge, second edge) -- and work[kSepThird..), in any order.
+// With more of them a thread stops at the first one it has no place for, and the return is some larger number.
 __device__ __forceinline__ uint32_t tail_triangles(TailShared &S, int n, int m, uint32_t &n_attractive, uint32_t &n_repulsive)
 {
     const int tid = (int)threadIdx.x;
@@ -274,10 +274,9 @@ __device__ __forceinline__ uint32_t tail_triangles(TailShared &S, int n, int m, 
         // the edges (u,v), (u,w), (v,w) of a triangle u < v < w stand in this order in the list
         const int e0 = min(e, min(a, b)), e2 = max(e, max(a, b)), e1 = e + a + b - e0 - e2;
         const uint32_t at = atomicAdd(&S.count[2], 1u);
-        if (at < (uint32_t)kTailTriangles) {
-            S.work[kSepKey + at] = (uint32_t)e0 << 13 | (uint32_t)e1;
-            third[at] = (uint16_t)e2;
-        }
+        if (at >= (uint32_t)kTailTriangles) break;
+        S.work[kSepKey + at] = (uint32_t)e0 << 13 | (uint32_t)e1;
+        third[at] = (uint16_t)e2;
     }
     __syncthreads();
     return S.count[2];

@@ -679,6 +679,34 @@ def test_solve_rounds_in_one_workgroup(rama, oracle32, n, m, pos, later, iters, 
     assert len(rounds) == got["rounds"] and rounds[-1]["n_edges_aug"] >= got["n_edges_final"]
 
 
+@pytest.mark.parametrize("n,m,pos", [(200, 8100, 0.7), (700, 8100, 0.8)])
+def test_dense_rounds_are_handed_back(rama, oracle32, n, m, pos):
+    """Rounds of more than 2048 triangles are not for one workgroup: it gets another try only behind a round of 16384 or
+    fewer."""
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(1)
+    i, j = np.triu_indices(n, 1)
+    k = np.sort(rng.permutation(i.size)[:m])
+    i, j = i[k].astype(np.int32), j[k].astype(np.int32)
+    c = ((rng.random(m) + 0.01) * np.where(rng.random(m) < pos, 1, -1)).astype(np.float32)
+    want = oracle32.solve(n, i, j, c, max_cycle_len_first=3)
+    rama.profile_enable(True)
+    got = rama.solve(n, i, j, c, params=default_params(max_cycle_len_first=3))
+    launches = sum(x["launches"] for x in rama.profile_get() if x["name"] == "k_tail_rounds")
+    rama.profile_enable(False)
+    assert np.array_equal(np_(got["labels"]), want["labels"])
+    rounds, tries, try_next = [r["n_triangles"] for r in rama.round_stats()[1:]], 0, True
+    assert any(a > 16384 and b > 2048 for a, b in zip(rounds, rounds[1:]))
+    while rounds:
+        if try_next:
+            tries += 1
+            while rounds and rounds[0] <= 2048:
+                rounds.pop(0)
+        if rounds:
+            try_next = rounds.pop(0) <= 16384
+    assert launches == tries
+
+
 def test_contract_fig2_graph(rama, oracle32):
     # the graph of the paper's Fig. 2; with the matching rule S={st} (cost 4 is the best edge at s and t;
     # rs=3 loses at s), so only the mechanics are compared with the oracle here

@@ -337,9 +337,8 @@ class Rama:
         if wrong:
             raise wrong[0]
         self._check(st, "rama_dual_rounds")
-        io, jo, co = (made.get(q, self._empty(0, dt)) for q, dt in ((0, t.int32), (1, t.int32), (2, t.float32)))
-        k = mo.value
-        return dict(i=io[:k], j=jo[:k], c=co[:k], lower_bound=lb.value, lb_trace=list(tr), n_triangles=nt.value)
+        io, jo, co = (made[q] if q in made else self._empty(0, dt)[:0] for q, dt in ((0, t.int32), (1, t.int32), (2, t.float32)))
+        return dict(i=io, j=jo, c=co, lower_bound=lb.value, lb_trace=list(tr), n_triangles=nt.value)
 
     def contract(self, n_nodes, i, j, c, params=None, repeat=1, want_diag=True):
         t = self.torch

@@ -199,6 +199,17 @@ def test_search_on_more_repulsive_edges_than_one_launch_has_waves(rama):
         assert torch.equal(got[L], want[L]), (L + 3, got[L].shape, want[L].shape)
 
 
+def test_dual_rounds_allocates_its_result_and_nothing_else(rama, monkeypatch):
+    made = []
+    empty = rama._empty
+    monkeypatch.setattr(rama, "_empty", lambda n, dtype: made.append(int(n)) or empty(n, dtype))
+    i, j = np.arange(50, dtype=np.int32), np.arange(1, 51, dtype=np.int32)
+    got = rama.dual_rounds(51, i, j, np.ones(50, np.float32))
+    assert made == [50, 50, 50] and np.array_equal(np_(got["i"]), i) and np.array_equal(np_(got["j"]), j)
+    got = rama.dual_rounds(51, i[:0], j[:0], np.ones(0, np.float32))
+    assert all(got[k].numel() == 0 for k in "ijc")
+
+
 def test_no_room_is_asked_for_what_cannot_be_written(rama):
     """7.2e8 triangles are a list of more than 2^31 numbers: the call says so before it asks its caller for 8 GiB."""
     import ctypes as C

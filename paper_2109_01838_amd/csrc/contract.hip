@@ -5,9 +5,11 @@
 //         the canonical list) packed into one 64-bit word, so "each node points at its best
 //         incident candidate" is an integer atomicMax per endpoint -- order independent, hence
 //         deterministic.  An edge both of whose endpoints point at it is matched; rounds repeat
-//         on the shrinking list of edges whose endpoints are both still free (two kernels per
-//         round: accept, then compaction of the survivors fused with their next proposals); the
-//         list carries endpoints and rank word, so a round streams it and touches no edge array.
+//         on the shrinking list of edges whose endpoints are both still free (one kernel per round
+//         on lists of up to 2^20: compaction of the survivors fused with their next proposals,
+//         every candidate finding out itself whether its ends were matched; longer lists are
+//         accepted by a kernel in front of it; the last 8192 in one workgroup); the list carries
+//         endpoints and rank word, so a round streams it and touches no edge array.
 //   f'  : connected components of (V,S) by min-label hooking + pointer jumping; a component is
 //         represented by its smallest node; new ids are the ranks of the representatives.
 //   S'  : when the matching joins fewer than forest_ratio*|V| pairs: maximum spanning forest of the
@@ -223,7 +225,7 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
         }
 }
 
-// The rest of the matching for a list that one workgroup holds: candidates in registers, a handshake between four barriers
+// The rest of the matching for a list that one workgroup holds: candidates in registers, a handshake between three barriers
 // (about 4 us) instead of a launch, and the host hears of it once.  A longer list is left as it is.  On entry the list's
 // proposals stand in `best`.  result[0]: candidates left, result[1]: pairs made.  Contraction of a 300x301 long-range grid
 // 2.53 -> 2.41 ms, 61x97x131 solve 8.53 -> 8.38, 512^2 8.05 -> 7.95.

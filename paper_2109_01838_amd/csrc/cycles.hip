@@ -629,8 +629,7 @@ __global__ __launch_bounds__(kBlock) void k_fill_cycles_listed(WalkList list, co
 }
 
 // ---- hashed search for cycles of length up to 5 --------------------------------------------------
-// The same meeting in the middle on rows that are too long for registers and for the staged rows above.  G lanes
-// share a repulsive edge.  They enter every node of the rows of N+(vL)'s entries v3 into a hash table in LDS, with
+// The same meeting in the middle on rows that are too long for registers.  G lanes share a repulsive edge.  They enter every node of the rows of N+(vL)'s entries v3 into a hash table in LDS, with
 // one bit per v3 whose row holds the node (and one more bit for the nodes of N+(vL) itself); a pair (v1, v2),
 // v2 in N+(v1), then needs one look into the table: its bits say which v3 close (v0,v1,v2,v3,vL) and whether
 // (v0,v1,v2,vL) is a cycle.  That is d^2 entries and d^2 looks per edge, where the walk makes d^3 steps that each

@@ -645,7 +645,8 @@ __global__ __launch_bounds__(kBlock) void k_row_bounds_search(const K *keys, siz
 }
 
 // ------------------------------------------------------------------------------------------
-// stable LSD radix sort, up to kRadixBits bits per pass, 6144 / 5120 keys per workgroup.
+// stable LSD radix sort, up to kRadixBits bits per pass, 6144 / 5120 keys per workgroup (fewer on
+// arrays that would not fill the chip, see kSortShort and kSortMedium).
 // Ranking inside a wave uses ballot-based match-any, so equal digits keep their order
 // without any atomics in the scatter pass.
 // ------------------------------------------------------------------------------------------
@@ -1774,10 +1775,10 @@ __device__ __forceinline__ void block_max_into(uint32_t v, uint32_t *out)
 // the heads are found from the keys in registers (the left neighbour's key by a shuffle), and a run is
 // added up from LDS instead of by a chain of dependent fetches of keys and values; only a run that
 // crosses the end of the tile goes on in memory.
-static // `sign_sums` (optional, zero on entry): per tile of kScanTile *outputs* the number of positive costs (low half)
+// `sign_sums` (optional, zero on entry): per tile of kScanTile *outputs* the number of positive costs (low half)
 // and of negative costs (high half) -- the tile sums of the scan that splits the new graph by sign, which then
 // needs no counting pass.  A workgroup's outputs are contiguous and at most a tile long: two atomic adds.
-__global__ __launch_bounds__(kBlock) void k_reduce_runs(size_t m, const uint64_t *key, const uint32_t *val, int dbits,
+static __global__ __launch_bounds__(kBlock) void k_reduce_runs(size_t m, const uint64_t *key, const uint32_t *val, int dbits,
                                                         const uint32_t *block_offsets, int32_t *io, int32_t *jo, float *co,
                                                         unsigned long long *sign_sums)
 {

@@ -62,14 +62,14 @@ def rel_close(a, b, rel=REL):
 @pytest.fixture
 def search_mode(rama, request):
     """The ways of finding the cycles of length 4 and more: 1 = the per-thread walk that fetches a row per path
-    at its last level, 3 = the walk whose last level closes from the far endpoint's side, 2 = the cooperative
-    search for lengths 4 and 5 (rows beyond its staged sizes fall back to walk 3 edge by edge)."""
+    at its last level, 3 = the walk whose last level closes from the far endpoint's side, 2 = the hashed
+    search for lengths 4 and 5 (edges whose rows fit no table fall back to walk 3 one by one)."""
     rama.set_cycle_search(request.param)
     yield request.param
     rama.set_cycle_search(0)
 
 
-BOTH_SEARCHES = pytest.mark.parametrize("search_mode", [1, 2, 3], indirect=True, ids=["walk", "cooperative", "walk-meet"])
+BOTH_SEARCHES = pytest.mark.parametrize("search_mode", [1, 2, 3], indirect=True, ids=["walk", "hashed", "walk-meet"])
 
 
 @pytest.mark.parametrize("name", list(CASES))
@@ -596,7 +596,8 @@ def test_diagonal_of_long_runs(rama, oracle32, sizes):
     assert np.array_equal(np_(got["diag"]), want["diag"][: len(sizes)])
 
 
-# the forest by one workgroup; graphs beyond 6144 nodes, so that the round is not taken whole
+# the forest by one workgroup (and, from 32767 candidates on, by the whole chip); graphs beyond 6144 nodes, so that the
+# round is not taken whole
 @pytest.mark.parametrize("kind,n,m,cand", [("random", 20000, 40000, 1), ("random", 20000, 40000, 1024), ("random", 20000, 40000, 32767),
                                            ("random", 20000, 40000, 32768), ("random", 20000, 40000, 32769), ("path", 7000, 0, 0)])
 def test_forest_in_one_workgroup(rama, oracle32, kind, n, m, cand):

@@ -177,25 +177,33 @@ def test_search_on_a_star_is_no_slower_than_the_walk(rama):
     assert took[0] < 3 * took[3], took
 
 
-def test_search_on_more_repulsive_edges_than_one_launch_has_waves(rama):
-    """7e7 repulsive edges on a graph of 14 attractive neighbours per node: a wave each would be more than the 2^32 threads
-    a launch may have in one dimension, so the waves stride over the edges.  The lists are those of the walk."""
+def all_pairs_around_rings(n):
+    """Every pair of n nodes; the nodes a few steps apart attract each other, 14 of them per node, all others repel."""
     import torch
-    n = 11900
     i, j = (x.to(torch.int32) for x in torch.triu_indices(n, n, 1, device="cuda:0"))
     c = -torch.ones(i.numel(), device="cuda:0")
     d = j - i
     for step in (1, 30, 200, 900, 2500, 4000, 5500):
         c[(d == step) | (d == n - step)] = 1.0
-    assert int((c < 0).sum()) > 1 << 26
-    got = rama.find_conflicted_cycles(n, i, j, c, 4)
+    return i, j, c
+
+
+# (nodes, longest cycle, repulsive edges at least): a wave (lengths 4 and 5) or sixteen lanes (triangles) for each of them would
+# be more than the 2^32 threads a launch may have in one dimension
+@pytest.mark.parametrize("n,lmax,least", [(11900, 4, 1 << 26), (23400, 3, 1 << 28)])
+def test_search_on_more_repulsive_edges_than_one_launch_has_lanes(rama, n, lmax, least):
+    """The lanes stride over the edges; the lists are those of the walk."""
+    import torch
+    i, j, c = all_pairs_around_rings(n)
+    assert int((c < 0).sum()) > least
+    got = rama.find_conflicted_cycles(n, i, j, c, lmax)
     try:
         rama.set_cycle_search(3)
-        want = rama.find_conflicted_cycles(n, i, j, c, 4)
+        want = rama.find_conflicted_cycles(n, i, j, c, lmax)
     finally:
         rama.set_cycle_search(0)
-    assert want[1].shape[0] > 1000
-    for L in range(2):
+    assert want[-1].shape[0] > 1000
+    for L in range(lmax - 2):
         assert torch.equal(got[L], want[L]), (L + 3, got[L].shape, want[L].shape)
 
 

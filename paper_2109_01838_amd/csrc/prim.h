@@ -660,7 +660,10 @@ struct SortTile {
 // 24 rows of keys one after the other: 15 to 20 us a pass whatever the length), so they get smaller ones: eight keys per
 // thread, and four where even those are fewer than the CUs.  Solves with 8 (and 4) against 24/20 keys per thread:
 // 512^2 long-range grid 9.6 -> 8.8 ms, 6-NN graph of 10^6 points 15.4 -> 14.4, 61x97x131 grid 10.2 -> 8.9, 128^2
-// long-range grid 4.45 -> 3.96 (3.84 with the four).
+// long-range grid 4.45 -> 3.96 (3.84 with the four).  Contraction of shuffled random edges (a sort of 64-bit keys is most
+// of it), us a call with 4 | 8 | 24 keys per thread: 1.3*10^5 edges 165 | 174 | 218, 2.4*10^5 175 | 185 | 230, 10^6 230 |
+// 238 | 296, 1.6*10^6 289 | 291 | 336, 2.1*10^6 336 | 322 | 373, 3.1*10^6 523 | 500 | 528, 3.9*10^6 644 | 607 | 714,
+// 5.2*10^6 799 | 775 | 892: for such keys alone both lines could stand higher (four up to 1.6*10^6, eight beyond 5*10^6).
 constexpr size_t kSortShort = size_t(3) << 16, kSortMedium = size_t(3) << 20;
 #ifndef RAMA_RADIX_BITS
 #define RAMA_RADIX_BITS 8

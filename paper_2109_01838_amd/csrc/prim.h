@@ -650,29 +650,28 @@ __global__ __launch_bounds__(kBlock) void k_row_bounds_search(const K *keys, siz
 // Ranking inside a wave uses ballot-based match-any, so equal digits keep their order
 // without any atomics in the scatter pass.
 // ------------------------------------------------------------------------------------------
-// keys per thread: larger tiles give longer contiguous runs per digit on the way out; 24 (64-bit
-// keys) and 20 (32-bit keys) measured best, beyond that the LDS footprint costs more than it gains
+// Larger tiles give longer contiguous runs per digit on the way out; 6144 64-bit or 5120 32-bit keys measured best, beyond
+// that the LDS footprint costs more than it gains.  A wave ranks its rows of 64 keys one after the other (see k_rs_scatter),
+// so a tile is spread over eight waves: with four, two workgroups of 78 KB left two waves to a SIMD waiting for LDS.  One
+// pass over 9.2e7 (64-bit key, value) pairs 0.68 -> 0.56 ms, over 1.9e8 32-bit pairs 0.77 -> 0.53 (4096-key rows of sixteen
+// waves, 5120 and 6144 keys: 0.61 and 0.52).
 template <typename K>
 struct SortTile {
-    static constexpr int items = sizeof(K) == 8 ? 24 : 20;
+    static constexpr int threads = 512, items = sizeof(K) == 8 ? 12 : 10, tile = threads * items;
 };
-// Shorter arrays do not fill the chip with such tiles (10^6 keys: 163 workgroups for 256 CUs, each of which takes its
-// 24 rows of keys one after the other: 15 to 20 us a pass whatever the length), so they get smaller ones: eight keys per
-// thread, and four where even those are fewer than the CUs.  Solves with 8 (and 4) against 24/20 keys per thread:
-// 512^2 long-range grid 9.6 -> 8.8 ms, 6-NN graph of 10^6 points 15.4 -> 14.4, 61x97x131 grid 10.2 -> 8.9, 128^2
-// long-range grid 4.45 -> 3.96 (3.84 with the four).  Contraction of shuffled random edges (a sort of 64-bit keys is most
-// of it), us a call with 4 | 8 | 24 keys per thread: 1.3*10^5 edges 165 | 174 | 218, 2.4*10^5 175 | 185 | 230, 10^6 230 |
-// 238 | 296, 1.6*10^6 289 | 291 | 336, 2.1*10^6 336 | 322 | 373, 3.1*10^6 523 | 500 | 528, 3.9*10^6 644 | 607 | 714,
-// 5.2*10^6 799 | 775 | 892: for such keys alone both lines could stand higher (four up to 1.6*10^6, eight beyond 5*10^6).
+// Shorter arrays do not fill the chip with such tiles (10^6 keys: 163 workgroups for 256 CUs), so they get 2048 keys, and
+// 1024 where even those tiles are fewer than the CUs.  Whole solves, ms, as the lines stand | kSortShort at 3 * 2^18 |
+// kSortMedium at 6 * 2^20 | twice the keys a tile: 512^2 long-range grid 6.98 | 7.16 | 7.04 | 7.47, 6-NN graph of 10^6 points
+// 11.4 | 11.7 | 11.7 | 11.9, 61x97x131 grid 7.2 | 7.4 | 7.2 | 7.9, 128^2 long-range grid 2.83 | 2.94 | 2.83 | 2.91; 256 threads
+// instead of 512 for these tiles: 7.22, 11.8, 7.6, 3.00.
 constexpr size_t kSortShort = size_t(3) << 16, kSortMedium = size_t(3) << 20;
+constexpr int kShortTile = 1024, kShortThreads = 512, kMediumTile = 2048, kMediumThreads = 512;
 #ifndef RAMA_RADIX_BITS
 #define RAMA_RADIX_BITS 8
 #endif
 
 constexpr int kRadixBits = RAMA_RADIX_BITS;        // widest digit of a pass
 constexpr int kRadix = 1 << kRadixBits;
-constexpr int kDigitsPerThread = kRadix / kBlock;   // digits owned by one thread in the prefix step
-static_assert(kRadix >= kBlock && kRadix % kBlock == 0, "radix must be a multiple of the block size");
 
 // 16 bytes per lane and load: a plain copy with 4-byte accesses tops out near 3.8 TB/s on this
 // chip, one with 16-byte accesses reaches 6 TB/s.  Only the histogram uses them: the scatter
@@ -820,32 +819,41 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, int bits, uint64_t v
 // With LOCAL_SCAN (few tiles) `offs` is the raw [digit][tile] histogram and every workgroup derives
 // its own global offsets from it, which saves the scan launch of the pass.
 constexpr uint32_t kSortLocalScanTiles = 32;
-template <typename K, typename V, bool HAS_V, bool LOCAL_SCAN, int ITEMS, typename SRC>
-__global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vin, SRC src, K *kout, V *vout,
-                                                       const uint32_t *offs, size_t n, int shift, int bits,
-                                                       uint32_t nb)
+// Waves per SIMD that the LDS of a workgroup leaves room for, which is what the registers have to allow as well (pairs; keys
+// alone have LDS to spare and would spill).
+template <bool HAS_V>
+constexpr int rs_scatter_waves(int lds_bytes, int threads)
+{
+    const int waves = (160 * 1024 / lds_bytes) * (threads / 64) / 4;
+    return !HAS_V ? 1 : waves > 8 ? 8 : waves;
+}
+template <typename K, typename V, bool HAS_V, bool LOCAL_SCAN, int THREADS, int ITEMS, typename SRC>
+__global__ __launch_bounds__(THREADS, (rs_scatter_waves<HAS_V>(THREADS * ITEMS * ((int)sizeof(K) + 4) + THREADS * 8 + 1088, THREADS))) void k_rs_scatter(const K *kin, const V *vin, SRC src, K *kout, V *vout,
+                                                        const uint32_t *offs, size_t n, int shift, int bits,
+                                                        uint32_t nb)
 {
     constexpr bool kFromSource = !std::is_same<SRC, NoSource>::value;
-    constexpr int kSortItems = ITEMS;
-    constexpr int kSortTile = kBlock * ITEMS;
-    __shared__ uint32_t whist[4][kRadix];
+    constexpr int kTile = THREADS * ITEMS, NW = THREADS / 64;
+    static_assert(THREADS >= kRadix && kRadix == 256 && kTile < (1 << 16), "one digit per thread of the first four waves, 16-bit counts");
+    __shared__ uint16_t whist[NW][kRadix];
     __shared__ uint32_t gdelta[kRadix];
-    __shared__ K skey[kSortTile];
-    __shared__ uint32_t sval[HAS_V ? kSortTile : 1];
+    __shared__ uint32_t s_run[4], s_rows[4];
+    __shared__ K skey[kTile];
+    __shared__ uint32_t sval[HAS_V ? kTile : 1];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint32_t mask = (1u << bits) - 1u;
     const uint32_t tile_id = xcd_block();
     if (tile_id >= nb) return;      // the whole workgroup (padding of the grid)
-    for (int k = tid; k < 4 * kRadix; k += kBlock) (&whist[0][0])[k] = 0;
+    for (int k = tid; k < NW * kRadix / 2; k += THREADS) reinterpret_cast<uint32_t *>(&whist[0][0])[k] = 0;
     __syncthreads();
-    const size_t tile_base = (size_t)tile_id * kSortTile;
-    const size_t wave_base = tile_base + (size_t)w * (64 * kSortItems);
+    const size_t tile_base = (size_t)tile_id * kTile;
+    const size_t wave_base = tile_base + (size_t)w * (64 * ITEMS);
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    K key[kSortItems];
-    uint32_t val[kSortItems];
-    uint32_t rank[kSortItems];
+    K key[ITEMS];
+    uint32_t val[ITEMS];
+    uint32_t rank[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         size_t idx = wave_base + (size_t)r * 64 + lane;
         bool valid = idx < n;
         if constexpr (kFromSource) {
@@ -862,83 +870,53 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vi
         if constexpr (kFromSource) return src.takes_part(key[r]);
         else return wave_base + (size_t)r * 64 + lane < n;
     };
-    uint32_t cnt = (uint32_t)((n - tile_base) < (size_t)kSortTile ? (n - tile_base) : (size_t)kSortTile);
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         bool valid = takes_part(r);
         uint32_t d = (uint32_t)(key[r] >> shift) & mask;
         uint64_t m = match_digit(d, bits, __ballot(valid));
         uint32_t before = whist[w][d];
         rank[r] = before + (uint32_t)__popcll(m & lt);
         __builtin_amdgcn_wave_barrier();
-        if (valid && lane == (__ffsll((long long)m) - 1)) whist[w][d] = before + (uint32_t)__popcll(m);
+        if (valid && lane == (__ffsll((long long)m) - 1)) whist[w][d] = (uint16_t)(before + (uint32_t)__popcll(m));
         __builtin_amdgcn_wave_barrier();
     }
-    __syncthreads();
-    {   // this thread owns the digits [tid*kDigitsPerThread, +kDigitsPerThread)
-        uint32_t c[kDigitsPerThread][4], tot = 0, all;
-#pragma unroll
-        for (int q = 0; q < kDigitsPerThread; ++q)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                c[q][k] = whist[k][tid * kDigitsPerThread + q];
-                tot += c[q][k];
+    // thread d < 256 owns digit d: the tile's keys with it, wave by wave, and where they go in the output
+    uint32_t c[NW], tot = 0, in_tot = 0, in_rows = 0, rows = 0, before = 0;
+    if (tid < kRadix && tid <= (int)mask) {
+        if (LOCAL_SCAN) {      // keys with the digit in all tiles, and in earlier ones
+            for (uint32_t b = 0; b < nb; ++b) {
+                const uint32_t h = offs[(size_t)tid * nb + b];
+                if (b < tile_id) before += h;
+                rows += h;
             }
-        uint32_t run = block_inclusive_scan(tot, &all) - tot;
-        if (kFromSource) cnt = all;
-        uint32_t goff[kDigitsPerThread];
-        if (LOCAL_SCAN) {
-            // keys of smaller digits (all tiles) + keys of the same digit in earlier tiles
-            uint32_t rows = 0, before[kDigitsPerThread], rowsum[kDigitsPerThread];
-#pragma unroll
-            for (int q = 0; q < kDigitsPerThread; ++q) {
-                const uint32_t d = (uint32_t)(tid * kDigitsPerThread + q);
-                before[q] = 0; rowsum[q] = 0;
-                if (d <= mask)
-                    for (uint32_t b = 0; b < nb; ++b) {
-                        uint32_t h = offs[(size_t)d * nb + b];
-                        if (b < tile_id) before[q] += h;
-                        rowsum[q] += h;
-                    }
-                rows += rowsum[q];
-            }
-            uint32_t dummy;
-            uint32_t dig = block_inclusive_scan(rows, &dummy) - rows;
-#pragma unroll
-            for (int q = 0; q < kDigitsPerThread; ++q) { goff[q] = dig + before[q]; dig += rowsum[q]; }
-        } else {
-            // offs: per digit the keys in earlier tiles, and behind the table the digits' totals
-            const uint32_t *totals = offs + ((size_t)nb << bits);
-            uint32_t rows = 0, rowsum[kDigitsPerThread];
-#pragma unroll
-            for (int q = 0; q < kDigitsPerThread; ++q) {
-                const uint32_t d = (uint32_t)(tid * kDigitsPerThread + q);
-                rowsum[q] = d <= mask ? totals[d] : 0u;
-                rows += rowsum[q];
-            }
-            uint32_t dummy;
-            uint32_t dig = block_inclusive_scan(rows, &dummy) - rows;
-#pragma unroll
-            for (int q = 0; q < kDigitsPerThread; ++q) {
-                const uint32_t d = (uint32_t)(tid * kDigitsPerThread + q);
-                goff[q] = dig + (d <= mask ? offs[(size_t)d * nb + tile_id] : 0u);
-                dig += rowsum[q];
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kDigitsPerThread; ++q) {
-            const uint32_t d = (uint32_t)(tid * kDigitsPerThread + q);
-            gdelta[d] = goff[q] - run;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                whist[k][d] = run;
-                run += c[q][k];
-            }
+        } else {               // offs: per digit the keys in earlier tiles, and behind the table the digits' totals
+            rows = offs[((size_t)nb << bits) + tid];
+            before = offs[(size_t)tid * nb + tile_id];
         }
     }
     __syncthreads();
+    if (tid < kRadix) {
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
+        for (int k = 0; k < NW; ++k) { c[k] = whist[k][tid]; tot += c[k]; }
+        in_tot = wave_inclusive_scan(tot);
+        in_rows = wave_inclusive_scan(rows);
+        if (lane == 63) { s_run[w] = in_tot; s_rows[w] = in_rows; }
+    }
+    __syncthreads();
+    if (tid < kRadix) {
+        uint32_t run = in_tot - tot, digit = in_rows - rows;
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (k < w) { run += s_run[k]; digit += s_rows[k]; }
+        gdelta[tid] = digit + before - run;
+#pragma unroll
+        for (int k = 0; k < NW; ++k) { whist[k][tid] = (uint16_t)run; run += c[k]; }
+    }
+    __syncthreads();
+    const uint32_t cnt = s_run[0] + s_run[1] + s_run[2] + s_run[3];
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
         if (takes_part(r)) {
             uint32_t d = (uint32_t)(key[r] >> shift) & mask;
             uint32_t lpos = whist[w][d] + rank[r];
@@ -948,8 +926,8 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const K *kin, const V *vi
     }
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kSortItems; ++r) {
-        uint32_t idx = (uint32_t)r * kBlock + tid;
+    for (int r = 0; r < ITEMS; ++r) {
+        uint32_t idx = (uint32_t)r * THREADS + tid;
         if (idx < cnt) {
             K k = skey[idx];
             uint32_t pos = gdelta[(uint32_t)(k >> shift) & mask] + idx;
@@ -1020,20 +998,19 @@ __global__ __launch_bounds__(kBlock) void k_seg_bounds(const K *keys, size_t n, 
 // passes the keys return to registers in the new order.
 // LK is the type of the keys while they are being sorted: 32 bits whenever the low bits (plus the
 // few top bits in which a workgroup's segments differ) fit, which halves the LDS a key takes.
-// Measured on 9.8e7 (64-bit key, value) pairs with 26 low bits: what counts is the number of waves a
-// CU holds (LDS is the limit) and a workgroup of at most eight waves; 16 keys x 8 waves (two
-// workgroups per CU) takes 1.45 ms -- 0.55 ms for reading and writing the data and 0.22 ms per 7-bit
-// pass, which is the ballot ranking -- against 2.3 ms for 32 keys x 4 waves or 64-bit local keys.
-constexpr int kLocalSortWaves = 8;
+// What counts is the number of waves a CU holds: 8 keys x 16 waves fill it with two workgroups (9.2e7 (64-bit key, value)
+// pairs with 27 low bits 0.99 ms, 1.9e8 32-bit pairs 1.37); 16 keys x 8 waves, with keys and values side by side in LDS, left
+// two waves to a SIMD free (1.24 and 1.63 ms), and with one of them after the other the registers did (1.13 and 1.56).
+constexpr int kLocalSortWaves = 16;
 constexpr int kBucketBits = 12, kBucketMax = 32;
 template <typename LK>
 struct LocalSort {
-    static constexpr int items = sizeof(LK) == 8 ? 8 : 16;
+    static constexpr int items = sizeof(LK) == 8 ? 4 : 8;
     static constexpr int threads = kLocalSortWaves * 64;
     static constexpr int cap = threads * items;
 };
 template <typename K, typename V, bool HAS_V, typename LK>
-__global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin, const V *vin, K *kout, V *vout,
+__global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_rs_local(const K *kin, const V *vin, K *kout, V *vout,
                                                                    const uint32_t *bounds, int low_bits, uint32_t n_all,
                                                                    uint32_t *head_sums)
 {
@@ -1042,10 +1019,9 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
     constexpr int kThreads = LocalSort<LK>::threads;
     constexpr int kCap = LocalSort<LK>::cap;
     static_assert(kRadix == 256 && kThreads >= kRadix, "one digit per thread of the first four waves");
-    __shared__ uint32_t whist[NW][kRadix];
+    __shared__ __align__(16) uint16_t whist[NW][kRadix];
     __shared__ uint32_t wave_tot[4], bucket_tot[NW];
-    __shared__ LK skey[kCap];
-    __shared__ uint32_t sval[HAS_V ? kCap : 1];
+    __shared__ LK sbuf[kCap];      // the words that are compared, then the keys, then the values
     // without a bounds array the (single) workgroup takes the whole array of n_all keys
     const uint32_t beg = bounds ? bounds[blockIdx.x] : 0u, end = bounds ? bounds[blockIdx.x + 1] : n_all;
     const uint32_t cnt = end - beg;
@@ -1070,16 +1046,23 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
     }
     // Buckets first: the top kBucketBits of the keys' differing bits split the few thousand keys into buckets of one to
     // a few (an edge list: the edges of a node).  Count and place by LDS atomics -- in any order --, then every key
-    // finds its place among its bucket's keys by comparing: six LDS accesses per key in all, where each 7-bit pass below
-    // takes as many plus the ballots (9.8e7 (u64,u32) pairs with 26 low bits: 1.88 -> 1.25 ms).  A bucket of more than kBucketMax keys sends the workgroup through the passes.
-    uint16_t *const s_end = reinterpret_cast<uint16_t *>(&whist[0][0]);
-    static_assert(NW * kRadix * 4 >= (1 << kBucketBits) * 2 && kThreads * 8 == (1 << kBucketBits), "bucket counters take the digit counters' place");
+    // finds its place among its bucket's keys by comparing.  What is compared is one word: the bits below the bucket's
+    // and, behind them, the place the key came from, so that equal keys keep their order and no second array is read.
+    // Keys and values then go through the same LDS one after the other.
+    // A bucket of more than kBucketMax keys, or bits that do not fit the word, send the workgroup through the passes.
+    uint16_t *const s_end = &whist[0][0];
+    constexpr int kMyWords = (1 << kBucketBits) / 2 / kThreads;      // words of two counters
+    static_assert(NW * kRadix >= (1 << kBucketBits) && kThreads * kMyWords * 2 == (1 << kBucketBits), "bucket counters take the digit counters' place");
     const int bucket_shift = sort_bits > kBucketBits ? sort_bits - kBucketBits : 0;
-    bool passes_needed = true;
-    {
-        uint32_t *words = &whist[0][0];
+    constexpr int kPlaceBits = 13;
+    static_assert(kCap <= (1 << kPlaceBits), "a place fits its bits");
+    const LK low_mask = (LK)(((LK)1 << bucket_shift) - 1);
+    auto word_of = [&](LK k, uint32_t place) { return (LK)(((k & low_mask) << kPlaceBits) | (LK)place); };
+    bool passes_needed = bucket_shift + kPlaceBits > 8 * (int)sizeof(LK);
+    if (!passes_needed) {      // uniform
+        uint32_t *words = reinterpret_cast<uint32_t *>(&whist[0][0]);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) words[tid * 4 + k] = 0;
+        for (int k = 0; k < kMyWords; ++k) words[tid * kMyWords + k] = 0;
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
@@ -1092,10 +1075,10 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
             }
         }
         __syncthreads();
-        uint32_t c[8], mine = 0, longest = 0;
+        uint32_t c[2 * kMyWords], mine = 0, longest = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const uint32_t x = words[tid * 4 + k];
+        for (int k = 0; k < kMyWords; ++k) {
+            const uint32_t x = words[tid * kMyWords + k];
             c[2 * k] = x & 0xffffu; c[2 * k + 1] = x >> 16;
             mine += c[2 * k] + c[2 * k + 1];
             longest = max(longest, max(c[2 * k], c[2 * k + 1]));
@@ -1109,9 +1092,9 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
             for (int k = 0; k < NW - 1; ++k)
                 if (k < w) run += bucket_tot[k];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {      // ends of the buckets
+            for (int k = 0; k < kMyWords; ++k) {      // ends of the buckets
                 const uint32_t e0 = run + c[2 * k], e1 = e0 + c[2 * k + 1];
-                words[tid * 4 + k] = e0 | e1 << 16;
+                words[tid * kMyWords + k] = e0 | e1 << 16;
                 run = e1;
             }
             __syncthreads();
@@ -1121,10 +1104,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
                     const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
                     if (idx < cnt) {
                         const uint32_t b = (uint32_t)(key[r] >> bucket_shift);
-                        const uint32_t p = (b ? s_end[b - 1] : 0u) + rank[r];
-                        skey[p] = key[r];
-                        if (HAS_V) sval[p] = idx;      // where the key came from: equal keys keep their order
-                        else rank[r] = p;
+                        sbuf[(b ? s_end[b - 1] : 0u) + rank[r]] = word_of(key[r], idx);
                     }
                 }
             }
@@ -1135,12 +1115,10 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
                     const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
                     if (idx < cnt) {
                         const uint32_t b = (uint32_t)(key[r] >> bucket_shift);
-                        const uint32_t b0 = b ? s_end[b - 1] : 0u, b1 = s_end[b], self = HAS_V ? idx : rank[r];
+                        const uint32_t b0 = b ? s_end[b - 1] : 0u, b1 = s_end[b];
+                        const LK self = word_of(key[r], idx);
                         uint32_t at = b0;
-                        for (uint32_t p = b0; p < b1; ++p) {
-                            const LK k = skey[p];
-                            at += (k < key[r] || (k == key[r] && (HAS_V ? sval[p] : p) < self)) ? 1u : 0u;
-                        }
+                        for (uint32_t p = b0; p < b1; ++p) at += sbuf[p] < self ? 1u : 0u;
                         rank[r] = at;
                     }
                 }
@@ -1150,10 +1128,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
             for (int r = 0; r < kItems; ++r) {
                 if (r < rows) {
                     const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
-                    if (idx < cnt) {
-                        skey[rank[r]] = key[r];
-                        if (HAS_V) sval[rank[r]] = val[r];
-                    }
+                    if (idx < cnt) sbuf[rank[r]] = key[r];
                 }
             }
         }
@@ -1163,7 +1138,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
     for (int p = 0; passes_needed && p < passes; ++p) {
         const int bits = (remaining + (passes - p) - 1) / (passes - p);
         const uint32_t mask = (1u << bits) - 1u;
-        for (int k = tid; k < NW * kRadix; k += kThreads) (&whist[0][0])[k] = 0;
+        for (int k = tid; k < NW * kRadix / 2; k += kThreads) reinterpret_cast<uint32_t *>(&whist[0][0])[k] = 0;
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < kItems; ++r) {
@@ -1175,7 +1150,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
                 const uint32_t before = whist[w][d];
                 rank[r] = before + (uint32_t)__popcll(m & lt);
                 __builtin_amdgcn_wave_barrier();
-                if (valid && lane == (__ffsll((long long)m) - 1)) whist[w][d] = before + (uint32_t)__popcll(m);
+                if (valid && lane == (__ffsll((long long)m) - 1)) whist[w][d] = (uint16_t)(before + (uint32_t)__popcll(m));
                 __builtin_amdgcn_wave_barrier();
             }
         }
@@ -1195,7 +1170,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
                 for (int k = 0; k < 3; ++k)
                     if (k < w) run += wave_tot[k];
 #pragma unroll
-                for (int k = 0; k < NW; ++k) { whist[k][tid] = run; run += c[k]; }
+                for (int k = 0; k < NW; ++k) { whist[k][tid] = (uint16_t)run; run += c[k]; }
             }
         }
         __syncthreads();
@@ -1205,33 +1180,45 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
                 const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
                 if (idx < cnt) {
                     const uint32_t d = (uint32_t)(key[r] >> shift) & mask;
-                    const uint32_t lpos = whist[w][d] + rank[r];
-                    skey[lpos] = key[r];
-                    if (HAS_V) sval[lpos] = val[r];
+                    rank[r] += whist[w][d];
+                    sbuf[rank[r]] = key[r];
                 }
             }
         }
         __syncthreads();
-        if (p + 1 < passes) {
+        if (p + 1 < passes) {      // keys, then values, come back in the new order; after the last pass they go out below
+            auto take_turn = [&](auto &x, bool bring) {
+                if (bring) {
+                    __syncthreads();
 #pragma unroll
-            for (int r = 0; r < kItems; ++r) {
-                if (r < rows) {
-                    const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
-                    if (idx < cnt) {
-                        key[r] = skey[idx];
-                        if (HAS_V) val[r] = sval[idx];
-                    }
+                    for (int r = 0; r < kItems; ++r)
+                        if (r < rows && wave_base + (uint32_t)r * 64u + lane < cnt) sbuf[rank[r]] = (LK)x[r];
+                    __syncthreads();
                 }
-            }
+#pragma unroll
+                for (int r = 0; r < kItems; ++r) {
+                    const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
+                    if (r < rows && idx < cnt) x[r] = (std::remove_reference_t<decltype(x[r])>)sbuf[idx];
+                }
+            };
+            take_turn(key, false);
+            if (HAS_V) take_turn(val, true);
+            __syncthreads();
         }
         shift += bits;
         remaining -= bits;
     }
+    auto values_out = [&]() {      // behind the keys, through the same LDS
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kItems; ++r)
+            if (r < rows && wave_base + (uint32_t)r * 64u + lane < cnt) sbuf[rank[r]] = (LK)val[r];
+        __syncthreads();
+        for (uint32_t idx = tid; idx < cnt; idx += kThreads) vout[beg + idx] = (V)sbuf[idx];
+    };
     if (!head_sums) {   // uniform
-        for (uint32_t idx = tid; idx < cnt; idx += kThreads) {
-            kout[beg + idx] = (K)((K)skey[idx] + base);
-            if (HAS_V) vout[beg + idx] = (V)sval[idx];
-        }
+        for (uint32_t idx = tid; idx < cnt; idx += kThreads) kout[beg + idx] = (K)((K)sbuf[idx] + base);
+        if (HAS_V) values_out();
         return;
     }
     // The sorted keys are at hand: count the heads of runs of equal keys per tile of kScanTile places, for a scan
@@ -1247,10 +1234,9 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
         const bool valid = idx < cnt;
         bool head = false;
         if (valid) {
-            const LK k = skey[idx];
+            const LK k = sbuf[idx];
             kout[beg + idx] = (K)((K)k + base);
-            if (HAS_V) vout[beg + idx] = (V)sval[idx];
-            head = idx == 0 || k != skey[idx - 1];
+            head = idx == 0 || k != sbuf[idx - 1];
         }
         // the wave's 64 places lie in one tile or in two
         const uint32_t first = beg + idx0 + (uint32_t)w * 64u;
@@ -1268,6 +1254,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64) void k_rs_local(const K *kin,
         }
     }
     __syncthreads();
+    if (HAS_V) values_out();
     if (tid < kHeadTiles && s_heads[tid]) atomicAdd(&head_sums[tile0 + tid], s_heads[tid]);
 }
 
@@ -1283,18 +1270,18 @@ inline const char *rs_local_name()
 }
 
 // one pass: histogram, offsets, scatter
-template <typename K, typename V, bool HAS_V, int ITEMS, typename SRC>
+template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS, typename SRC>
 rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist)
 {
-    const uint32_t nb = grid_for(n, kBlock * ITEMS);
+    const uint32_t nb = grid_for(n, THREADS * ITEMS);
     {
         ProfScope ps_(ctx, (sizeof(K) == 8 ? "k_rs_hist<u64>" : "k_rs_hist<u32>"), (double)(n * sizeof(K)));
-        k_rs_hist<K, ITEMS, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, src, hist, n, shift, bits, nb);
+        k_rs_hist<K, THREADS * ITEMS / kBlock, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, src, hist, n, shift, bits, nb);
     }
     LAUNCH_TRY(ctx, "rs_hist");
     if (nb <= kSortLocalScanTiles) {
         ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-        k_rs_scatter<K, V, HAS_V, true, ITEMS, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb);
+        k_rs_scatter<K, V, HAS_V, true, THREADS, ITEMS, SRC><<<xcd_grid(nb), THREADS, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb);
     } else {
         {
             ProfScope ps_(ctx, "k_rs_rowscan", (double)(((size_t)nb << bits) * 8));
@@ -1302,19 +1289,19 @@ rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb
         }
         LAUNCH_TRY(ctx, "rs_rowscan");
         ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-        k_rs_scatter<K, V, HAS_V, false, ITEMS, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb);
+        k_rs_scatter<K, V, HAS_V, false, THREADS, ITEMS, SRC><<<xcd_grid(nb), THREADS, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb);
     }
     LAUNCH_TRY(ctx, "rs_scatter");
     return RAMA_OK;
 }
-// ITEMS by the number of keys n; a pass over a source goes over its n_src >= n places in tiles of the same size
+// the tile by the number of keys n; a pass over a source goes over its n_src >= n places in tiles of the same size
 template <typename K, typename V, bool HAS_V, typename SRC>
 rama_status radix_pass_sized(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, size_t places, int shift, int bits,
                              uint32_t *hist)
 {
-    if (n <= kSortShort) return radix_pass<K, V, HAS_V, 4, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
-    if (n <= kSortMedium) return radix_pass<K, V, HAS_V, 8, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
-    return radix_pass<K, V, HAS_V, SortTile<K>::items, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
+    if (n <= kSortShort) return radix_pass<K, V, HAS_V, kShortThreads, kShortTile / kShortThreads, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
+    if (n <= kSortMedium) return radix_pass<K, V, HAS_V, kMediumThreads, kMediumTile / kMediumThreads, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
+    return radix_pass<K, V, HAS_V, SortTile<K>::threads, SortTile<K>::items, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
 }
 // stable LSD passes over the key bits [shift, shift + total_bits); a/b swap with every pass
 template <typename K, typename V, bool HAS_V, typename SRC>
@@ -1446,7 +1433,7 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             return RAMA_OK;
         }
     }
-    const uint32_t nb = grid_for(src ? n_src : n, kBlock * (n <= kSortShort ? 4 : n <= kSortMedium ? 8 : SortTile<K>::items));
+    const uint32_t nb = grid_for(src ? n_src : n, n <= kSortShort ? kShortTile : n <= kSortMedium ? kMediumTile : SortTile<K>::tile);
     const int all_passes = (total_bits + kRadixBits - 1) / kRadixBits;
     // [digit][tile] and the digits' totals, for the widest digit of a pass (the top bits of a split sort: whole digits)
     const int digit_bits = n >= ctx.sort_split_min ? kRadixBits : (total_bits + all_passes - 1) / all_passes;

@@ -751,7 +751,21 @@ def test_canonicalisation_of_large_shuffled_input(rama, oracle32):
     assert np.array_equal(np_(got["c"]), wc)       # duplicates are added in input order on both sides
 
 
-# lengths at which the radix passes change their tiles (4 or 8 keys per thread, 24 / 20 beyond), and one key more or less
+# Arrays that one workgroup sorts in LDS, ordered by one comparison of a key's low bits and its place while those fit a word
+# (32 bits of key do not, 31 do), and by passes where a bucket of equal top bits is long (few nodes)
+@pytest.mark.parametrize("n,m", [(1 << 16, 8192), (50000, 8191), (32768, 8192), (20000, 8192), (300, 4097), (70, 8192), (3, 8192), (1 << 20, 4096)])
+def test_sort_inside_one_workgroup(rama, oracle32, n, m):
+    rng = np.random.default_rng(n + m)
+    i = rng.integers(0, n, m).astype(np.int32)
+    j = ((i + 1 + rng.integers(0, n - 1, m)) % n).astype(np.int32)
+    i[0], j[0] = 0, n - 1                                               # the widest second field
+    c = (-np.abs(rng.normal(size=m)) * 10.0 ** rng.integers(-3, 4, m) - 1e-3).astype(np.float32)
+    wi, wj, wc = oracle32.canonicalise(n, i, j, c)
+    got = rama.contract(n, i, j, c, repeat=1, want_diag=False)
+    assert np.array_equal(np_(got["i"]), wi) and np.array_equal(np_(got["j"]), wj) and np.array_equal(np_(got["c"]), wc)
+
+
+# lengths at which the radix passes change their tiles (1024 or 2048 keys, 6144 / 5120 beyond), and one key more or less
 # than whole tiles of each
 @pytest.mark.parametrize("m", [8193, 33 * 1024, 196608, 196609, 200 * 2048 + 1, 3145728, 3145729, 513 * 6144 + 1])
 def test_sort_at_the_limits_of_its_tiles(rama, oracle32, m):

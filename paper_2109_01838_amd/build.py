@@ -8,7 +8,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librama_hip.so")
-SOURCES = ["graph.hip", "cycles.hip", "dual.hip", "contract.hip", "tail.hip", "api.hip"]
+SOURCES = ["graph.hip", "cycles.hip", "triangles.hip", "dual.hip", "contract.hip", "tail.hip", "api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

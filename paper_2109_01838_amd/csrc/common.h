@@ -469,6 +469,12 @@ inline rama_status list_fits(Ctx &ctx, int q, int64_t n)
     return (uint64_t)(q + 3) * (uint64_t)n < (uint64_t(1) << 31) ? RAMA_OK : fail(ctx, RAMA_ERR_CAPACITY, "cycle list reaches 2^31 entries");
 }
 
+// the attractive neighbourhoods, both ends of every edge, are numbered with 31 bits
+inline rama_status adjacency_fits(Ctx &ctx, uint64_t attractive)
+{
+    return 2 * attractive < (uint64_t(1) << 31) ? RAMA_OK : fail(ctx, RAMA_ERR_CAPACITY, "positive adjacency reaches 2^31 entries");
+}
+
 // a1: conflicted cycles of lengths 3..max_len; shortest_only keeps, per repulsive edge, only the
 // cycles of its smallest length.  `sink` (optional) is asked for the lists' memory once the counts are known: list q
 // goes to to[q] (null for an empty list) and out.v stays empty; a failure of the sink ends the search before the
@@ -493,6 +499,21 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
                         bool validate_cycles, int k_iters, Graph &out, double *lower_bound, double *lb_trace,
                         DualInfo *info, DualState *prev = nullptr, DualState *next = nullptr,
                         Graph *donor = nullptr);
+
+// a1..a3 of a round that separates triangles only, without a list of cycles in between: g's costs become the reduced
+// ones after k_iters > 0 iterations.  `last`: triangles of the round before (negative: none), which tells whether one
+// workgroup is likely to hold this round's.  `separated` is called where the separation ends in the stream (for the clock).
+struct TriangleCounts {
+    int64_t triangles = 0, attractive = 0, repulsive = 0;
+};
+rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, double *lower_bound, TriangleCounts &out,
+                           const std::function<void()> &separated);
+// its two halves (triangles.hip).  few: separation and all iterations, *done stays false when there are too many
+// triangles (or g does not bring its sign counts), and nothing has been changed then; list: the three edges of every
+// triangle, in ascending order of the triangles.
+rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters, TriangleCounts &out, bool *done,
+                          const std::function<void()> &separated);
+rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<uint32_t> &slots, TriangleCounts &out);
 
 // a4..a6: one primal update.  fmap[n] -> [0,n_new); n_matched = |S|.  If |S|==0 nothing else is produced.
 rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, float forest_ratio, Buf<int32_t> &fmap,

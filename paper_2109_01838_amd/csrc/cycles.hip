@@ -12,22 +12,11 @@
 // (v0, vL, then the path v1, v2, v3), because repulsive edges are visited in canonical order
 // and every row is ascending.
 #include "prim.h"
+#include "steps.h"
 
 namespace rama {
 
 namespace {
-
-// both sign counters in one scan: attractive edges count in the low word, repulsive ones in the high word
-struct SignFlags {
-    static constexpr int bytes = 4;   // bytes read per item
-    static constexpr const char *tag = "SignFlags";
-    const float *c;
-    __device__ __forceinline__ uint64_t operator()(size_t e) const
-    {
-        const float w = c[e];
-        return w > 0.0f ? 1ull : (w < 0.0f ? (1ull << 32) : 0ull);
-    }
-};
 
 // consumer of the scan over SignFlags: an attractive edge goes to place low(prefix) of the attractive
 // list (the lower half of the adjacency is sorted from its pairs read as (j,i)), a repulsive one
@@ -1242,7 +1231,7 @@ rama_status find_cycles(Ctx &ctx, const Graph &g, int max_len, bool shortest_onl
     const uint32_t mp = (uint32_t)signs.total, mr = (uint32_t)(signs.total >> 32);
     out.n_attractive = mp; out.n_repulsive = mr;
     if (mp == 0 || mr == 0) return RAMA_OK;
-    if ((uint64_t)2 * mp >= (uint64_t(1) << 31)) return fail(ctx, RAMA_ERR_CAPACITY, "positive adjacency reaches 2^31 entries");
+    RAMA_TRY(adjacency_fits(ctx, mp));
     Buf<int32_t> pi, pj, ri, rj;
     Buf<uint32_t> lkey, lval;
     RAMA_TRY(pi.alloc(ctx, mp));

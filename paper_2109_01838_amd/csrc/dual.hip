@@ -592,6 +592,112 @@ rama_status copy_graph(Ctx &ctx, const Graph &g, Graph &out)
     return RAMA_OK;
 }
 
+// From the triangles' edges (skey: three per triangle, in ascending order of the triangles) to the reduced costs in aug.c.
+// inc_heads: a plan over the 3T slots, whose spare word, if it has one, is raised when a cycle uses an edge that is not in
+// the graph.  ct: the triangles' costs; with ct_lazy they are zero and have no memory yet.
+rama_status pass_messages(Ctx &ctx, Graph &aug, size_t T, Buf<uint32_t> &skey, ScanPlan<uint32_t> &inc_heads, Buf<float> &ct, bool ct_lazy,
+                          int k_iters, double *lower_bound, double *lb_trace, double *lb_dev, DualState *next)
+{
+    const size_t ma = (size_t)aug.m;
+    Buf<uint32_t> slot, tri_act;   // tri_act: per triangle slot its edge's number among the active edges
+    RAMA_TRY(slot.alloc(ctx, 3 * T));
+    // ---- incidence: slots of every edge in ascending triangle order ----------------------------
+    // (if the flag is up, the edge ids below are placeholders -- all valid indices -- and the result is discarded)
+    Buf<uint32_t> inc_head_sums;   // heads per scan tile, if the sort's last kernel could count them
+    RAMA_TRY((radix_sort_pairs<uint32_t, uint32_t>(ctx, skey, slot, 3 * T, bits_for((uint64_t)ma), true, &inc_head_sums, (uint64_t)ma)));   // values: the slots 0..3T-1
+    Buf<uint32_t> act_edge, act_start;
+    size_t na = 0;
+    {
+        ScanPlan<uint32_t> &heads = inc_heads;
+        RAMA_TRY((scan_totals<uint32_t>(ctx, HeadFlag32{skey.get()}, heads, inc_head_sums.get())));
+        inc_head_sums.reset();
+        if (heads.extra_value[0]) return fail(ctx, RAMA_ERR_BAD_GRAPH, "a cycle uses an edge that is not in the graph");
+        na = heads.total;
+        RAMA_TRY(act_edge.alloc(ctx, na));
+        RAMA_TRY(act_start.alloc(ctx, na + 1));
+        RAMA_TRY(tri_act.alloc(ctx, 3 * T));
+        RAMA_TRY((scan_emit<uint32_t>(ctx, HeadFlag32{skey.get()},
+                                      ActiveEdgesEmit{skey.get(), slot.get(), (uint32_t)(3 * T), (uint32_t)na, act_edge.get(),
+                                                      act_start.get(), tri_act.get()},
+                                      heads, (double)(na * 8 + 3 * T * 8))));
+    }
+    skey.reset();
+    // ---- iterations ----------------------------------------------------------------------------
+    Buf<float> share, msg;
+    if (ct_lazy) RAMA_TRY(ct.alloc(ctx, 3 * T));
+    RAMA_TRY(share.alloc(ctx, na));
+    RAMA_TRY(msg.alloc(ctx, 3 * T));
+    float *ce = aug.c.get();
+    {
+        ProfScope ps_(ctx, "k_edge_init", (double)(na * 16));
+        k_edge_init<<<grid_for(na), kBlock, 0, ctx.stream>>>(na, act_edge.get(), act_start.get(), ce, share.get());
+    }
+    LAUNCH_TRY(ctx, "edge_init");
+    if (lb_trace) {
+        RAMA_TRY(lower_bound_now(ctx, ce, ma, ct.get(), T, lb_dev));
+        RAMA_TRY(read_back(ctx, &lb_trace[0], lb_dev, 8));
+    }
+    for (int it = 1; it <= k_iters; ++it) {
+        const bool first = it == 1 && ct_lazy;
+        if (ctx.prof.wants("k_triangle_update")) {   // timed by the dispatch's own start and stop stamps
+            hipEvent_t ea, eb;
+            ctx.prof.begin_stamped("k_triangle_update", (double)(T * (first ? 48 : 60)), &ea, &eb);
+            if (first)
+                hipExtLaunchKernelGGL(k_triangle_update<true>, dim3(xcd_grid(grid_for(T))), dim3(kBlock), 0, ctx.stream, ea, eb, 0, (size_t)T,
+                                      (const uint32_t *)tri_act.get(), (const float *)share.get(), (float *)ct.get(), (float *)msg.get());
+            else
+                hipExtLaunchKernelGGL(k_triangle_update<false>, dim3(xcd_grid(grid_for(T))), dim3(kBlock), 0, ctx.stream, ea, eb, 0, (size_t)T,
+                                      (const uint32_t *)tri_act.get(), (const float *)share.get(), (float *)ct.get(), (float *)msg.get());
+        } else if (first) {
+            k_triangle_update<true><<<xcd_grid(grid_for(T)), kBlock, 0, ctx.stream>>>(T, tri_act.get(), share.get(), ct.get(), msg.get());
+        } else {
+            k_triangle_update<false><<<xcd_grid(grid_for(T)), kBlock, 0, ctx.stream>>>(T, tri_act.get(), share.get(), ct.get(), msg.get());
+        }
+        LAUNCH_TRY(ctx, "triangle_update");
+        {
+            const bool store_ce = it == k_iters || lb_trace != nullptr;
+            ProfScope ps_(ctx, store_ce ? "k_edge_update<true>" : "k_edge_update<false>", (double)(na * (store_ce ? 16 : 8) + 3 * T * 8));
+            auto update = [&](auto store, auto per) {
+                constexpr int kPer = decltype(per)::value;
+                k_edge_update<decltype(store)::value, kPer><<<xcd_grid(grid_for(na, kBlock * kPer)), kBlock, 0, ctx.stream>>>(
+                    na, act_edge.get(), act_start.get(), slot.get(), msg.get(), ce, share.get());
+            };
+            using std::integral_constant;
+            if (na <= kFewEdges) {
+                if (store_ce) update(std::true_type{}, integral_constant<int, 1>{});
+                else update(std::false_type{}, integral_constant<int, 1>{});
+            } else {
+                if (store_ce) update(std::true_type{}, integral_constant<int, kEdgesPerThread>{});
+                else update(std::false_type{}, integral_constant<int, kEdgesPerThread>{});
+            }
+        }
+        LAUNCH_TRY(ctx, "edge_update");
+        if (lb_trace) {
+            RAMA_TRY(lower_bound_now(ctx, ce, ma, ct.get(), T, lb_dev));
+            RAMA_TRY(read_back(ctx, &lb_trace[it], lb_dev, 8));
+        }
+    }
+    if (lower_bound) {
+        if (lb_trace) *lower_bound = lb_trace[k_iters];
+        else {
+            RAMA_TRY(lower_bound_now(ctx, ce, ma, ct.get(), T, lb_dev));
+            RAMA_TRY(read_back(ctx, lower_bound, lb_dev, 8));
+        }
+    }
+    if (next) {
+        next->T = T;
+        RAMA_TRY(next->tri_nodes.alloc(ctx, 3 * T));
+        {
+            ProfScope ps_(ctx, "k_triangle_nodes", (double)(T * 36));
+            k_triangle_nodes<<<grid_for(T), kBlock, 0, ctx.stream>>>(T, tri_act.get(), act_edge.get(), aug.i.get(), aug.j.get(),
+                                                                  next->tri_nodes.get());
+        }
+        LAUNCH_TRY(ctx, "triangle_nodes");
+        next->ct = std::move(ct);
+    }
+    return RAMA_OK;
+}
+
 }  // namespace
 
 rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *const *cycles, const int64_t *n_cycles,
@@ -746,8 +852,7 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
     RAMA_TRY(read_back(ctx, &hmax, maxrow, 4));
     const int dbits = bits_for((uint64_t)hmax + 1);
     const int kbits = bits_for((uint64_t)ma) + dbits;
-    Buf<uint32_t> tri_act;   // per triangle slot: its edge's number among the active edges
-    Buf<uint32_t> skey, slot;
+    Buf<uint32_t> skey;
     size_t T = 0;
     Buf<float> ct;
     ScanPlan<uint32_t> inc_heads;   // scan over the sorted slot list (incidence); its spare word carries the flag to the host
@@ -807,105 +912,46 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
     if (info) info->n_triangles = (int64_t)T;
     // the kept triangles are taken over, and the keys are gone: the incidence sort needs the memory
     if (prev) { prev->tri_nodes.reset(); prev->ct.reset(); }
-    RAMA_TRY(slot.alloc(ctx, 3 * T));
-    // ---- incidence: slots of every edge in ascending triangle order ----------------------------
-    // (if the flag is up, the edge ids below are placeholders -- all valid indices -- and the result is discarded)
-    Buf<uint32_t> inc_head_sums;   // heads per scan tile, if the sort's last kernel could count them
-    RAMA_TRY((radix_sort_pairs<uint32_t, uint32_t>(ctx, skey, slot, 3 * T, bits_for((uint64_t)ma), true, &inc_head_sums, (uint64_t)ma)));   // values: the slots 0..3T-1
-    Buf<uint32_t> act_edge, act_start;
-    size_t na = 0;
-    {
-        ScanPlan<uint32_t> &heads = inc_heads;
-        RAMA_TRY((scan_totals<uint32_t>(ctx, HeadFlag32{skey.get()}, heads, inc_head_sums.get())));
-        inc_head_sums.reset();
-        if (heads.extra_value[0]) return fail(ctx, RAMA_ERR_BAD_GRAPH, "a cycle uses an edge that is not in the graph");
-        na = heads.total;
-        RAMA_TRY(act_edge.alloc(ctx, na));
-        RAMA_TRY(act_start.alloc(ctx, na + 1));
-        RAMA_TRY(tri_act.alloc(ctx, 3 * T));
-        RAMA_TRY((scan_emit<uint32_t>(ctx, HeadFlag32{skey.get()},
-                                      ActiveEdgesEmit{skey.get(), slot.get(), (uint32_t)(3 * T), (uint32_t)na, act_edge.get(),
-                                                      act_start.get(), tri_act.get()},
-                                      heads, (double)(na * 8 + 3 * T * 8))));
-    }
-    skey.reset();
     rowptr.reset();
-    // ---- iterations ----------------------------------------------------------------------------
-    Buf<float> share, msg;
-    if (ct_lazy) RAMA_TRY(ct.alloc(ctx, 3 * T));
-    RAMA_TRY(share.alloc(ctx, na));
-    RAMA_TRY(msg.alloc(ctx, 3 * T));
-    float *ce = aug.c.get();
-    {
-        ProfScope ps_(ctx, "k_edge_init", (double)(na * 16));
-        k_edge_init<<<grid_for(na), kBlock, 0, ctx.stream>>>(na, act_edge.get(), act_start.get(), ce, share.get());
-    }
-    LAUNCH_TRY(ctx, "edge_init");
-    if (lb_trace) {
-        RAMA_TRY(lower_bound_now(ctx, ce, ma, ct.get(), T, lb_dev.get()));
-        RAMA_TRY(read_back(ctx, &lb_trace[0], lb_dev.get(), 8));
-    }
-    for (int it = 1; it <= k_iters; ++it) {
-        const bool first = it == 1 && ct_lazy;
-        if (ctx.prof.wants("k_triangle_update")) {   // timed by the dispatch's own start and stop stamps
-            hipEvent_t ea, eb;
-            ctx.prof.begin_stamped("k_triangle_update", (double)(T * (first ? 48 : 60)), &ea, &eb);
-            if (first)
-                hipExtLaunchKernelGGL(k_triangle_update<true>, dim3(xcd_grid(grid_for(T))), dim3(kBlock), 0, ctx.stream, ea, eb, 0, (size_t)T,
-                                      (const uint32_t *)tri_act.get(), (const float *)share.get(), (float *)ct.get(), (float *)msg.get());
-            else
-                hipExtLaunchKernelGGL(k_triangle_update<false>, dim3(xcd_grid(grid_for(T))), dim3(kBlock), 0, ctx.stream, ea, eb, 0, (size_t)T,
-                                      (const uint32_t *)tri_act.get(), (const float *)share.get(), (float *)ct.get(), (float *)msg.get());
-        } else if (first) {
-            k_triangle_update<true><<<xcd_grid(grid_for(T)), kBlock, 0, ctx.stream>>>(T, tri_act.get(), share.get(), ct.get(), msg.get());
-        } else {
-            k_triangle_update<false><<<xcd_grid(grid_for(T)), kBlock, 0, ctx.stream>>>(T, tri_act.get(), share.get(), ct.get(), msg.get());
-        }
-        LAUNCH_TRY(ctx, "triangle_update");
-        {
-            const bool store_ce = it == k_iters || lb_trace != nullptr;
-            ProfScope ps_(ctx, store_ce ? "k_edge_update<true>" : "k_edge_update<false>", (double)(na * (store_ce ? 16 : 8) + 3 * T * 8));
-            auto update = [&](auto store, auto per) {
-                constexpr int kPer = decltype(per)::value;
-                k_edge_update<decltype(store)::value, kPer><<<xcd_grid(grid_for(na, kBlock * kPer)), kBlock, 0, ctx.stream>>>(
-                    na, act_edge.get(), act_start.get(), slot.get(), msg.get(), ce, share.get());
-            };
-            using std::integral_constant;
-            if (na <= kFewEdges) {
-                if (store_ce) update(std::true_type{}, integral_constant<int, 1>{});
-                else update(std::false_type{}, integral_constant<int, 1>{});
-            } else {
-                if (store_ce) update(std::true_type{}, integral_constant<int, kEdgesPerThread>{});
-                else update(std::false_type{}, integral_constant<int, kEdgesPerThread>{});
-            }
-        }
-        LAUNCH_TRY(ctx, "edge_update");
-        if (lb_trace) {
-            RAMA_TRY(lower_bound_now(ctx, ce, ma, ct.get(), T, lb_dev.get()));
-            RAMA_TRY(read_back(ctx, &lb_trace[it], lb_dev.get(), 8));
-        }
-    }
-    if (lower_bound) {
-        if (lb_trace) *lower_bound = lb_trace[k_iters];
-        else {
-            RAMA_TRY(lower_bound_now(ctx, ce, ma, ct.get(), T, lb_dev.get()));
-            RAMA_TRY(read_back(ctx, lower_bound, lb_dev.get(), 8));
-        }
-    }
-    if (next) {
-        next->T = T;
-        RAMA_TRY(next->tri_nodes.alloc(ctx, 3 * T));
-        {
-            ProfScope ps_(ctx, "k_triangle_nodes", (double)(T * 36));
-            k_triangle_nodes<<<grid_for(T), kBlock, 0, ctx.stream>>>(T, tri_act.get(), act_edge.get(), aug.i.get(), aug.j.get(),
-                                                                  next->tri_nodes.get());
-        }
-        LAUNCH_TRY(ctx, "triangle_nodes");
-        next->ct = std::move(ct);
-    }
+    RAMA_TRY(pass_messages(ctx, aug, T, skey, inc_heads, ct, ct_lazy, k_iters, lower_bound, lb_trace, lb_dev.get(), next));
     out.n = aug.n; out.m = aug.m;
     out.i = std::move(aug.i); out.j = std::move(aug.j); out.c = std::move(aug.c);
     out.sign_sums.reset();   // the costs are new
+    return RAMA_OK;
+}
+
+// A round whose predecessor had this many triangles at most is tried by one workgroup first: their number shrinks from round
+// to round, mostly to a third or a fifth.  A try that succeeds takes 33 to 75 us for separation and messages where the list
+// takes 115 to 160, a try that fails costs 20 to 30.
+constexpr int64_t kTryFewFrom = 8192;
+
+rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, double *lower_bound, TriangleCounts &out,
+                           const std::function<void()> &separated)
+{
+    RAMA_TRY(zero_page_recycle(ctx));
+    out = TriangleCounts{};
+    if (g.m == 0) return RAMA_OK;
+    Buf<int32_t> rowptr;
+    RAMA_TRY(rowptr.alloc(ctx, (size_t)g.n + 1));
+    RAMA_TRY((row_bounds<int32_t, int32_t>(ctx, g.i.get(), (size_t)g.m, g.n, rowptr.get())));
+    if (last >= 0 && last <= kTryFewFrom && !lower_bound) {
+        bool done = false;
+        RAMA_TRY(triangles_few(ctx, g, rowptr.get(), k_iters, out, &done, separated));
+        if (done) return RAMA_OK;
+    }
+    Buf<uint32_t> skey;
+    RAMA_TRY(triangles_list(ctx, g, rowptr.get(), skey, out));
+    separated();
+    rowptr.reset();
+    const size_t T = (size_t)out.triangles;
+    if (T == 0) return RAMA_OK;
+    ScanPlan<uint32_t> inc_heads;
+    RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, 3 * T, 0, inc_heads)));
+    Buf<float> ct;
+    Buf<double> lb_dev;
+    RAMA_TRY(lb_dev.alloc(ctx, 1));
+    RAMA_TRY(pass_messages(ctx, g, T, skey, inc_heads, ct, true, k_iters, lower_bound, nullptr, lb_dev.get(), nullptr));
+    g.sign_sums.reset();      // the costs are new
     return RAMA_OK;
 }
 

@@ -1,10 +1,22 @@
-// Arithmetic of single steps that more than one kernel takes: the six min-marginal updates of a triangle and the rank
-// of an edge in the matching.  One definition, so that every path rounds and breaks ties alike.
+// Arithmetic of single steps that more than one kernel takes: the signs of the costs, the six min-marginal updates of a
+// triangle and the rank of an edge in the matching.  One definition, so that every path rounds and breaks ties alike.
 #pragma once
 
 #include "prim.h"
 
 namespace rama {
+
+// both sign counters in one scan: attractive edges count in the low word, repulsive ones in the high word
+struct SignFlags {
+    static constexpr int bytes = 4;   // bytes read per item
+    static constexpr const char *tag = "SignFlags";
+    const float *c;
+    __device__ __forceinline__ uint64_t operator()(size_t e) const
+    {
+        const float w = c[e];
+        return w > 0.0f ? 1ull : (w < 0.0f ? (1ull << 32) : 0ull);
+    }
+};
 
 // order of the candidate edges: larger cost first, then earlier position
 __device__ __forceinline__ uint32_t ordered_bits(float x)

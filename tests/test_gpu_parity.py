@@ -946,6 +946,63 @@ def test_solver_variants(rama, oracle32, variant):
     assert abs(got["primal"] - want["primal"]) <= 5e-3 * max(1.0, abs(want["primal"]))
 
 
+@pytest.mark.parametrize("kind,n_tri", [("apart", 1), ("apart", 2047), ("apart", 2048), ("apart", 2049), ("fan", 2048), ("fan", 2049),
+                                        ("fan", 6000), ("fans", 1800), ("random", 0), ("grid", 0)])
+def test_triangle_rounds_match_the_cycle_lists(rama, kind, n_tri):
+    """Rounds that separate triangles only take them from the edge list itself, and one workgroup passes the messages of up
+    to 2048 of them; with another cycle search than the default they go through lists of cycles.  Same integers, same sums
+    in the same order: nothing may differ."""
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(n_tri + 17)
+    tau = 0.0
+    if kind == "grid":
+        g = inputs.cfg2(seed=3, h=220, w=221, n_seeds=30)      # 2^18 edges and more
+        n, i, j, c = g["n_nodes"], g["i"], g["j"], g["c"]
+    elif kind == "random":
+        g = signed(inputs.random_graph(9000, 60000, 5), 6, 0.8)
+        n, i, j, c = g["n_nodes"], g["i"], g["j"], g["c"]
+    else:      # the first round joins the heavy pairs at the end and nothing else; the triangles meet the second round
+        if kind == "apart":
+            t = np.arange(n_tri) * 3
+            tri = [(t, t + 1), (t, t + 2), (t + 1, t + 2)]
+            used = 3 * n_tri
+        else:      # triangles around shared repulsive edges (one, or a hundred)
+            hubs = 1 if kind == "fan" else 100
+            h = np.arange(n_tri) % hubs
+            x = 2 * hubs + np.arange(n_tri)
+            tri = [(2 * np.arange(hubs), 2 * np.arange(hubs) + 1), (2 * h, x), (2 * h + 1, x)]
+            used = 2 * hubs + n_tri
+        signs = rng.integers(0, 3, size=n_tri) if kind == "apart" else None
+        i = np.concatenate([a for a, _ in tri])
+        j = np.concatenate([b for _, b in tri])
+        c = rng.uniform(0.5, 1.5, size=i.size)
+        if kind == "apart":
+            for k in range(3):
+                c[k * n_tri:(k + 1) * n_tri][signs == k] *= -1
+        else:
+            c[:tri[0][0].size] *= -1
+        base, tau = max(used, 6200), 2.0      # too many nodes for the rounds in one workgroup
+        pairs = base + 2 * np.arange(3000)
+        i = np.concatenate([i, pairs]).astype(np.int32)
+        j = np.concatenate([j, pairs + 1]).astype(np.int32)
+        c = np.concatenate([c, np.full(3000, 100.0)]).astype(np.float32)
+        n = int(pairs[-1]) + 2
+    for kw in (dict(max_cycle_len_first=0), dict(max_cycle_len_first=3, mp_iters_first=3)):
+        P = default_params(contract_threshold=tau, forest_ratio=0.0, **kw)
+        out = []
+        for mode in (0, 1):
+            rama.set_cycle_search(mode)
+            got = rama.solve(n, i, j, c, P)
+            out.append((np_(got["labels"]), got["primal"], got["lower_bound"],
+                        [{k: v for k, v in r.items() if k not in ("ms", "workspace_peak")} for r in rama.round_stats()]))
+        rama.set_cycle_search(0)
+        assert np.array_equal(out[0][0], out[1][0]) and out[0][1:] == out[1][1:]
+        if n_tri and kw["max_cycle_len_first"] == 0:
+            assert out[0][3][1]["n_triangles"] == n_tri
+        if n_tri and kw["max_cycle_len_first"] == 3:
+            assert out[0][3][0]["n_triangles"] == n_tri
+
+
 def test_determinism(rama):
     g = CASES["knn_20000"]
     n = g["n_nodes"]

@@ -440,7 +440,7 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<
     LAUNCH_TRY(ctx, "scan_reduce");
     k_total_signs<<<1, kBlock, 0, ctx.stream>>>(g.sign_sums.get() ? g.sign_sums.get() : signs.get(), (size_t)nb_signs, offs.get() + nb + 1);
     LAUNCH_TRY(ctx, "total_signs");
-    RAMA_TRY(run_triangles<kTriCount>(ctx, "k_triangles", tg, n, kept.get(), 0, nullptr, sums.get(), nullptr, nullptr,
+    RAMA_TRY(run_triangles<kTriCount>(ctx, "k_count_cycles<3>", tg, n, kept.get(), 0, nullptr, sums.get(), nullptr, nullptr,
                                       (double)m * 12 + (double)n * 4 + (double)nb * 12));
     uint64_t back[2];
     if (nb <= kScanMidMax) {
@@ -464,7 +464,7 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<
     out.triangles = (int64_t)back[0];
     if (out.triangles == 0) return RAMA_OK;
     RAMA_TRY(slots.alloc(ctx, 3 * (size_t)back[0]));
-    return run_triangles<kTriFill>(ctx, "k_triangles", tg, n, kept.get(), 0, nullptr, nullptr, offs.get(), slots.get(),
+    return run_triangles<kTriFill>(ctx, "k_fill_cycles<3>", tg, n, kept.get(), 0, nullptr, nullptr, offs.get(), slots.get(),
                                    (double)nb * 20 + (double)back[0] * 24);
 }
 

@@ -278,6 +278,7 @@ struct rama_ctx {
     int cycle_search = 0;                      // see rama_set_cycle_search
     size_t sort_split_min = size_t(1) << 21;   // arrays at least this long may take the split sort ...
     int sort_split_gain = 2;                   // ... when it replaces at least this many passes
+    bool sorts_unseen = true;                  // no in-LDS sort of this call has been given more than it holds (see unseen_top_bits)
 };
 
 namespace rama {

@@ -361,10 +361,11 @@ struct InnerFlag {
 // (a loop is seen by hi-lo = 0), what follows streams over the stored keys.
 // raw[e] = (lo, hi-lo) in two 32-bit halves; *maxdiff collects the largest hi-lo.  A workgroup takes one tile of
 // the scan that follows (kScanTile edges) and leaves the number of edges that are no loops in tile_sums: the scan
-// over NotLoopKey then needs no pass of its own to count them.
+// over NotLoopKey then needs no pass of its own to count them.  It also clears its tile's word of sign_sums, where the sign
+// counts of the contracted costs will go.
 __global__ __launch_bounds__(kBlock) void k_relabel_keys(size_t m, const int32_t *i, const int32_t *j,
                                                          const int32_t *fmap, uint64_t *raw, uint32_t *maxdiff,
-                                                         uint32_t *tile_sums)
+                                                         uint32_t *tile_sums, uint64_t *sign_sums)
 {
     const size_t base = (size_t)blockIdx.x * kScanTile + threadIdx.x;
     uint32_t diff = 0, kept = 0;
@@ -388,7 +389,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_keys(size_t m, const int32_t
         }
     }
     kept = block_sum(kept);
-    if (threadIdx.x == 0) tile_sums[blockIdx.x] = kept;
+    if (threadIdx.x == 0) { tile_sums[blockIdx.x] = kept; sign_sums[blockIdx.x] = 0ull; }
     block_max_into(diff, maxdiff);
 }
 struct NotLoopKey {
@@ -1137,10 +1138,11 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
     Buf<uint64_t> raw;
     RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, m, 1, keep)));
     RAMA_TRY(raw.alloc(ctx, m));
+    RAMA_TRY(out.sign_sums.alloc(ctx, keep.nb > 0 ? keep.nb : 1));
     {
         ProfScope ps_(ctx, "k_relabel_keys", (double)(m * 24));
         k_relabel_keys<<<keep.nb, kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), fmap, raw.get(), keep.extra_ptr(),
-                                                           keep.sums.get());
+                                                        keep.sums.get(), out.sign_sums.get());
     }
     LAUNCH_TRY(ctx, "relabel_keys");
     RAMA_TRY((scan_totals<uint32_t>(ctx, NotLoopKey{raw.get()}, keep, keep.sums.get())));   // tile sums: left by k_relabel_keys
@@ -1157,6 +1159,10 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
     RAMA_TRY(key.alloc(ctx, kept));
     RAMA_TRY(val.alloc(ctx, kept));
     Buf<uint32_t> head_sums;   // heads per scan tile, if the sort's last kernel could count them
+    ScanPlan<uint32_t> runs;
+    RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, kept, 1, runs)));
+    SortAgain<uint64_t, uint32_t> again;
+    again.flag = runs.extra_ptr();
     if (sort_takes_source(kept, m)) {
         // the sort's first pass reads the stored keys itself and leaves the loops out; they are no longer needed after it,
         // so their place serves as the second key array
@@ -1164,19 +1170,16 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
         RAMA_TRY(val2.alloc(ctx, kept));
         keep.offs.reset();
         RAMA_TRY((radix_sort_source<uint64_t, uint32_t>(ctx, RelabelledEdges{raw.get(), g.c.get(), dbits}, m, key, val, raw, val2, kept, nbits + dbits,
-                                                        &head_sums, (uint64_t)n_new << dbits)));
+                                                        &head_sums, (uint64_t)n_new << dbits, &again)));
         raw.reset();
     } else {
         RAMA_TRY((scan_emit<uint32_t>(ctx, NotLoopKey{raw.get()}, CompactKeysEmit{raw.get(), g.c.get(), dbits, key.get(), val.get()},
                                       keep, (double)(m * 4 + (size_t)kept * 12))));
         keep.offs.reset();
         raw.reset();
-        RAMA_TRY((radix_sort_pairs<uint64_t, uint32_t>(ctx, key, val, kept, nbits + dbits, false, &head_sums, (uint64_t)n_new << dbits)));
+        RAMA_TRY((radix_sort_pairs<uint64_t, uint32_t>(ctx, key, val, kept, nbits + dbits, false, &head_sums, (uint64_t)n_new << dbits, &again)));
     }
-    ScanPlan<uint32_t> runs;
-    RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, kept, 0, runs)));
-    RAMA_TRY((scan_totals<uint32_t>(ctx, HeadFlag{key.get()}, runs, head_sums.get())));
-    head_sums.reset();
+    RAMA_TRY((count_heads<uint64_t, uint32_t>(ctx, key, &val, kept, nbits + dbits, [](const uint64_t *k) { return HeadFlag{k}; }, runs, 0, head_sums, again)));
     const uint32_t uniq = runs.total;
     RAMA_TRY(out.i.alloc(ctx, uniq));
     RAMA_TRY(out.j.alloc(ctx, uniq));

@@ -593,8 +593,8 @@ rama_status copy_graph(Ctx &ctx, const Graph &g, Graph &out)
 }
 
 // From the triangles' edges (skey: three per triangle, in ascending order of the triangles) to the reduced costs in aug.c.
-// inc_heads: a plan over the 3T slots, whose spare word, if it has one, is raised when a cycle uses an edge that is not in
-// the graph.  ct: the triangles' costs; with ct_lazy they are zero and have no memory yet.
+// inc_heads: a plan over the 3T slots with two spare words, the first of which is raised when a cycle uses an edge that is
+// not in the graph.  ct: the triangles' costs; with ct_lazy they are zero and have no memory yet.
 rama_status pass_messages(Ctx &ctx, Graph &aug, size_t T, Buf<uint32_t> &skey, ScanPlan<uint32_t> &inc_heads, Buf<float> &ct, bool ct_lazy,
                           int k_iters, double *lower_bound, double *lb_trace, double *lb_dev, DualState *next)
 {
@@ -604,13 +604,15 @@ rama_status pass_messages(Ctx &ctx, Graph &aug, size_t T, Buf<uint32_t> &skey, S
     // ---- incidence: slots of every edge in ascending triangle order ----------------------------
     // (if the flag is up, the edge ids below are placeholders -- all valid indices -- and the result is discarded)
     Buf<uint32_t> inc_head_sums;   // heads per scan tile, if the sort's last kernel could count them
-    RAMA_TRY((radix_sort_pairs<uint32_t, uint32_t>(ctx, skey, slot, 3 * T, bits_for((uint64_t)ma), true, &inc_head_sums, (uint64_t)ma)));   // values: the slots 0..3T-1
+    SortAgain<uint32_t, uint32_t> again;
+    again.flag = inc_heads.extra_ptr() + 1;
+    RAMA_TRY((radix_sort_pairs<uint32_t, uint32_t>(ctx, skey, slot, 3 * T, bits_for((uint64_t)ma), true, &inc_head_sums, (uint64_t)ma, &again)));   // values: the slots 0..3T-1
     Buf<uint32_t> act_edge, act_start;
     size_t na = 0;
     {
         ScanPlan<uint32_t> &heads = inc_heads;
-        RAMA_TRY((scan_totals<uint32_t>(ctx, HeadFlag32{skey.get()}, heads, inc_head_sums.get())));
-        inc_head_sums.reset();
+        RAMA_TRY((count_heads<uint32_t, uint32_t>(ctx, skey, &slot, 3 * T, bits_for((uint64_t)ma), [](const uint32_t *k) { return HeadFlag32{k}; }, heads, 1,
+                                                  inc_head_sums, again)));
         if (heads.extra_value[0]) return fail(ctx, RAMA_ERR_BAD_GRAPH, "a cycle uses an edge that is not in the graph");
         na = heads.total;
         RAMA_TRY(act_edge.alloc(ctx, na));
@@ -886,21 +888,23 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
         }
         LAUNCH_TRY(ctx, "triangle_keys");
         Buf<uint32_t> head_sums;   // heads per scan tile, if the sort's last kernel could count them
+        ScanPlan<uint32_t> heads;
+        RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, nkeys, 1, heads)));
+        SortAgain<KT, uint32_t> again;
+        again.flag = heads.extra_ptr();
         if (T_kept > 0) {   // the sort also has to tell where the kept triangles end up
             RAMA_TRY(origin.alloc(ctx, nfan));
-            RAMA_TRY((radix_sort_pairs<KT, uint32_t>(ctx, tkey, origin, nfan, kbits, true, &head_sums, kbits < 64 ? (uint64_t)ma << dbits : 0)));   // values: the fan indices 0..nfan-1
+            RAMA_TRY((radix_sort_pairs<KT, uint32_t>(ctx, tkey, origin, nfan, kbits, true, &head_sums, kbits < 64 ? (uint64_t)ma << dbits : 0, &again)));   // values: the fan indices 0..nfan-1
         } else {
-            RAMA_TRY((radix_sort_keys<KT>(ctx, tkey, nkeys, kbits, &head_sums, kbits < 64 ? (uint64_t)ma << dbits : 0)));
+            RAMA_TRY((radix_sort_keys<KT>(ctx, tkey, nkeys, kbits, &head_sums, kbits < 64 ? (uint64_t)ma << dbits : 0, &again)));
         }
-        ScanPlan<uint32_t> heads;
-        RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, nkeys, 0, heads)));
-        RAMA_TRY((scan_totals<uint32_t>(ctx, HeadFlagT<KT>{tkey.get()}, heads, head_sums.get())));
-        head_sums.reset();
+        RAMA_TRY((count_heads<KT, uint32_t>(ctx, tkey, T_kept > 0 ? &origin : nullptr, nkeys, kbits, [](const KT *k) { return HeadFlagT<KT>{k}; }, heads, 0,
+                                            head_sums, again)));
         T = heads.total;
         if (!ct_lazy) RAMA_TRY(ct.alloc(ctx, 3 * T));
         if (T_kept > 0) RAMA_TRY(fill<float>(ctx, ct.get(), 0.0f, 3 * T));   // otherwise the consumer below zeroes what it creates
         RAMA_TRY(skey.alloc(ctx, 3 * T));
-        RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, 3 * T, 1, inc_heads)));
+        RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, 3 * T, 2, inc_heads)));
         TrianglesEmit<KT> te{tkey.get(), rowptr.get(), aug.j.get(), dbits, skey.get(), flag.get(),
                              (int32_t *)inc_heads.extra_ptr(), T_kept > 0 ? origin.get() : nullptr, cs.fan_end[kCycleLists - 1], cs.fan_end[kCycleLists],
                              T_kept > 0 ? prev->ct.get() : nullptr, ct.get(), !ct_lazy};
@@ -946,7 +950,7 @@ rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, double
     const size_t T = (size_t)out.triangles;
     if (T == 0) return RAMA_OK;
     ScanPlan<uint32_t> inc_heads;
-    RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, 3 * T, 0, inc_heads)));
+    RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, 3 * T, 2, inc_heads)));
     Buf<float> ct;
     Buf<double> lb_dev;
     RAMA_TRY(lb_dev.alloc(ctx, 1));

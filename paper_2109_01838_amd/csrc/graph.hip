@@ -416,6 +416,7 @@ rama_status merge_runs(Ctx &ctx, Buf<uint64_t> &key, Buf<uint32_t> &val, size_t 
 
 rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const int32_t *j, const float *c, Graph &out)
 {
+    ctx.sorts_unseen = true;      // every call begins here
     if (n < 0 || m < 0 || (m > 0 && (!i || !j || !c))) return fail(ctx, RAMA_ERR_INVALID_ARG, "canonicalise: bad arguments");
     if (m >= (int64_t(1) << 31) - 1) return fail(ctx, RAMA_ERR_CAPACITY, "edge count reaches 2^31");
     out.n = n;
@@ -472,6 +473,10 @@ rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const
     RAMA_TRY(key.alloc(ctx, kept));
     RAMA_TRY(val.alloc(ctx, kept));
     Buf<uint32_t> head_sums;   // heads per scan tile, if the sort's last kernel could count them
+    ScanPlan<uint32_t> runs;
+    RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, kept, 1, runs)));
+    SortAgain<uint64_t, uint32_t> again;
+    again.flag = runs.extra_ptr();
     const bool few_runs = hf[3] < kMergeRuns;
     if (!few_runs && sort_takes_source(kept, (size_t)m)) {      // the sort's first pass reads the edges itself
         Buf<uint64_t> key2;
@@ -480,7 +485,7 @@ rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const
         RAMA_TRY(val2.alloc(ctx, kept));
         keep.offs.reset();
         RAMA_TRY((radix_sort_source<uint64_t, uint32_t>(ctx, InputEdges{i, j, c, dbits}, (size_t)m, key, val, key2, val2, kept, nbits + dbits,
-                                                        &head_sums, (uint64_t)n << dbits)));
+                                                        &head_sums, (uint64_t)n << dbits, &again)));
     } else {
         RAMA_TRY((scan_emit<uint32_t>(ctx, NotLoop{i, j}, PackEdgesEmit{i, j, c, dbits, key.get(), val.get()}, keep,
                                       (double)((size_t)m * 4 + (size_t)kept * 12))));
@@ -508,12 +513,9 @@ rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const
             }
         }
         if (!merged)
-            RAMA_TRY((radix_sort_pairs<uint64_t, uint32_t>(ctx, key, val, kept, nbits + dbits, false, &head_sums, (uint64_t)n << dbits)));
+            RAMA_TRY((radix_sort_pairs<uint64_t, uint32_t>(ctx, key, val, kept, nbits + dbits, false, &head_sums, (uint64_t)n << dbits, &again)));
     }
-    ScanPlan<uint32_t> runs;
-    RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, kept, 0, runs)));
-    RAMA_TRY((scan_totals<uint32_t>(ctx, HeadFlag{key.get()}, runs, head_sums.get())));
-    head_sums.reset();
+    RAMA_TRY((count_heads<uint64_t, uint32_t>(ctx, key, &val, kept, nbits + dbits, [](const uint64_t *k) { return HeadFlag{k}; }, runs, 0, head_sums, again)));
     const uint32_t uniq = runs.total;
     RAMA_TRY(out.i.alloc(ctx, uniq));
     RAMA_TRY(out.j.alloc(ctx, uniq));

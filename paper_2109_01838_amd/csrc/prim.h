@@ -143,23 +143,26 @@ __device__ __forceinline__ void mail_send(uint64_t *mail, uint64_t seq)
     }
 }
 
-// `words` 4-byte words from device memory into the mailbox
-static __global__ __launch_bounds__(kBlock) void k_publish(const uint32_t *src, unsigned words, uint64_t *mail, uint64_t seq)
+// `words` 4-byte words from device memory into the mailbox, and `more` from another place behind them
+static __global__ __launch_bounds__(kBlock) void k_publish(const uint32_t *src, unsigned words, const uint32_t *src2, unsigned more, uint64_t *mail,
+                                                           uint64_t seq)
 {
     uint32_t *dst = (uint32_t *)(mail + 1);
     for (unsigned k = threadIdx.x; k < words; k += kBlock) dst[k] = src[k];
+    for (unsigned k = threadIdx.x; k < more; k += kBlock) dst[words + k] = src2[k];
     mail_send(mail, seq);
 }
 
-// copy `bytes` (a multiple of 4, at most what a message holds) from device memory to the host and wait
-inline rama_status read_back(Ctx &ctx, void *host, const void *dev, size_t bytes)
+// copy `bytes` (a multiple of 4, at most what a message holds with the `more` bytes from dev2 that go behind them) from
+// device memory to the host and wait
+inline rama_status read_back(Ctx &ctx, void *host, const void *dev, size_t bytes, const void *dev2 = nullptr, size_t more = 0)
 {
-    if (bytes % 4 != 0 || bytes > (Ctx::kMailWords - 1) * 8) return read_back_sync(ctx, host, dev, bytes);
+    if (more == 0 && (bytes % 4 != 0 || bytes > (Ctx::kMailWords - 1) * 8)) return read_back_sync(ctx, host, dev, bytes);
     const uint64_t seq = ++ctx.mail_seq;
-    k_publish<<<1, kBlock, 0, ctx.stream>>>((const uint32_t *)dev, (unsigned)(bytes / 4), mailbox(ctx), seq);
+    k_publish<<<1, kBlock, 0, ctx.stream>>>((const uint32_t *)dev, (unsigned)(bytes / 4), (const uint32_t *)dev2, (unsigned)(more / 4), mailbox(ctx), seq);
     LAUNCH_TRY(ctx, "publish");
     RAMA_TRY(wait_mail(ctx, seq));
-    memcpy(host, (const void *)(mailbox(ctx) + 1), bytes);
+    memcpy(host, (const void *)(mailbox(ctx) + 1), bytes + more);
     return RAMA_OK;
 }
 
@@ -239,7 +242,7 @@ __device__ __forceinline__ TO item_or_last(const F &f, size_t k, size_t n)
 // total reaches the host without a copy.
 template <typename TO, typename F>
 __global__ __launch_bounds__(kBlock) void k_scan_reduce(F f, TO *block_sums, size_t n, TO *offs, uint32_t *ticket,
-                                                        uint64_t *mail, uint64_t seq, int extra)
+                                                        uint64_t *mail, uint64_t seq, const TO *words, int extra)
 {
     const size_t base = (size_t)blockIdx.x * kScanTile + threadIdx.x;
     TO s = 0, x[kScanItems];
@@ -266,7 +269,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_reduce(F f, TO *block_sums, siz
     if (mail) {
         if (threadIdx.x == 0) {
             mail[1] = (uint64_t)total;
-            for (int e = 0; e < extra; ++e) mail[2 + e] = (uint64_t)offs[gridDim.x + 1 + e];
+            for (int e = 0; e < extra; ++e) mail[2 + e] = (uint64_t)words[e];
         }
         mail_send(mail, seq);
     }
@@ -275,13 +278,13 @@ __global__ __launch_bounds__(kBlock) void k_scan_reduce(F f, TO *block_sums, siz
 // the scan of the tile sums as a launch of its own (long arrays: the election above would make every
 // workgroup of the reduce launch wait for its sum to be visible, which costs more than a launch)
 template <typename TO>
-__global__ __launch_bounds__(kBlock) void k_scan_mid(const TO *in, TO *out, unsigned nb, uint64_t *mail, uint64_t seq, int extra)
+__global__ __launch_bounds__(kBlock) void k_scan_mid(const TO *in, TO *out, unsigned nb, uint64_t *mail, uint64_t seq, const TO *words, int extra)
 {
     const TO total = scan_tile_sums<TO, false>(in, out, nb);
     if (mail) {
         if (threadIdx.x == 0) {
             mail[1] = (uint64_t)total;
-            for (int e = 0; e < extra; ++e) mail[2 + e] = (uint64_t)out[nb + 1 + e];
+            for (int e = 0; e < extra; ++e) mail[2 + e] = (uint64_t)words[e];
         }
         mail_send(mail, seq);
     }
@@ -334,12 +337,12 @@ rama_status scan_offsets(Ctx &ctx, F f, TO *sums, TO *offs, size_t n, unsigned n
     {
         ProfScope ps_(ctx, kernel_name<F>("k_scan_reduce"), (double)(n * F::bytes));
         k_scan_reduce<TO, F><<<nb, kBlock, 0, ctx.stream>>>(f, sums, n, offs, fused ? ctx.ticket : nullptr,
-                                                           (uint64_t *)nullptr, 0, 0);
+                                                           (uint64_t *)nullptr, 0, (const TO *)nullptr, 0);
     }
     LAUNCH_TRY(ctx, "scan_reduce");
     if (!fused && nb <= kScanMidMax) {
         ProfScope ps_(ctx, "k_scan_mid", (double)((size_t)nb * 2 * sizeof(TO)));
-        k_scan_mid<TO><<<1, kBlock, 0, ctx.stream>>>(sums, offs, nb, (uint64_t *)nullptr, 0, 0);
+        k_scan_mid<TO><<<1, kBlock, 0, ctx.stream>>>(sums, offs, nb, (uint64_t *)nullptr, 0, (const TO *)nullptr, 0);
         LAUNCH_TRY(ctx, "scan_mid");
     } else if (!fused) {
         RAMA_TRY((exclusive_scan<TO, PtrInput<TO>>(ctx, PtrInput<TO>{sums}, offs, nb)));
@@ -384,19 +387,20 @@ rama_status exclusive_scan(Ctx &ctx, F f, TO *out, size_t n)
 // the tile sums and reads the total back (the caller sizes its outputs with it); scan_emit then
 // recomputes f and hands every item k its value and exclusive prefix: emit(k, f(k), prefix).  The
 // array of prefixes is never stored and the consumer does not re-read what the scan already had in
-// registers.  `extra` words behind the total belong to the caller (e.g. a maximum a producer kernel
-// left there) and come back with the same read.
+// registers.  `extra` words of the plan belong to the caller (e.g. a maximum a producer kernel left there); they start
+// at zero and come back with the same read.
 // ------------------------------------------------------------------------------------------
 template <typename TO>
 struct ScanPlan {
-    Buf<TO> offs;   // [nb] tile offsets, [nb] total, then the caller's extra words
+    Buf<TO> offs;   // [nb] tile offsets, [nb] total
     Buf<TO> sums;
+    Buf<TO> words;  // the caller's extra words
     unsigned nb = 0;
     size_t n = 0;
     int extra = 0;
     TO total = 0;
     TO extra_value[2] = {0, 0};
-    TO *extra_ptr() { return offs.get() + nb + 1; }
+    TO *extra_ptr() { return words.get(); }
 };
 
 template <typename TO>
@@ -405,10 +409,10 @@ rama_status scan_plan_alloc(Ctx &ctx, size_t n, int extra, ScanPlan<TO> &plan)
     plan.n = n;
     plan.nb = grid_for(n, kScanTile);
     plan.extra = extra;
-    RAMA_TRY(plan.offs.alloc(ctx, (size_t)plan.nb + 1 + 2));
+    RAMA_TRY(plan.offs.alloc(ctx, (size_t)plan.nb + 1));
     RAMA_TRY(plan.sums.alloc(ctx, plan.nb > 0 ? plan.nb : 1));
     // the total is always written by the scan of the tile sums; only the caller's words start at zero
-    if (extra > 0) return fill<TO>(ctx, plan.extra_ptr(), (TO)0, (size_t)extra);
+    if (extra > 0) return zeroed<TO>(ctx, (size_t)extra, plan.words);
     return RAMA_OK;
 }
 
@@ -430,12 +434,12 @@ rama_status scan_totals(Ctx &ctx, F f, ScanPlan<TO> &plan, const TO *presums = n
         if (!presummed) {
             ProfScope ps_(ctx, kernel_name<F>("k_scan_reduce"), (double)(plan.n * F::bytes));
             k_scan_reduce<TO, F><<<nb, kBlock, 0, ctx.stream>>>(f, plan.sums.get(), plan.n, plan.offs.get(),
-                                                               fused ? ctx.ticket : nullptr, mailbox(ctx), seq, plan.extra);
+                                                               fused ? ctx.ticket : nullptr, mailbox(ctx), seq, plan.words.get(), plan.extra);
         }
         LAUNCH_TRY(ctx, "scan_reduce");
         if (!fused) {
             ProfScope ps_(ctx, "k_scan_mid", (double)((size_t)nb * 2 * sizeof(TO)));
-            k_scan_mid<TO><<<1, kBlock, 0, ctx.stream>>>(sums, plan.offs.get(), nb, mailbox(ctx), seq, plan.extra);
+            k_scan_mid<TO><<<1, kBlock, 0, ctx.stream>>>(sums, plan.offs.get(), nb, mailbox(ctx), seq, plan.words.get(), plan.extra);
             LAUNCH_TRY(ctx, "scan_mid");
         }
         RAMA_TRY(wait_mail(ctx, seq));
@@ -445,13 +449,11 @@ rama_status scan_totals(Ctx &ctx, F f, ScanPlan<TO> &plan, const TO *presums = n
         if (!presummed) {
             ProfScope ps_(ctx, kernel_name<F>("k_scan_reduce"), (double)(plan.n * F::bytes));
             k_scan_reduce<TO, F><<<nb, kBlock, 0, ctx.stream>>>(f, plan.sums.get(), plan.n, (TO *)nullptr, (uint32_t *)nullptr,
-                                                               (uint64_t *)nullptr, 0, 0);
+                                                               (uint64_t *)nullptr, 0, (const TO *)nullptr, 0);
         }
         LAUNCH_TRY(ctx, "scan_reduce");
-        // the nested scan writes nb+1 words (offsets and total), nothing beyond: the caller's extra words,
-        // which sit one further on, stay as they are
         RAMA_TRY((exclusive_scan<TO, PtrInput<TO>>(ctx, PtrInput<TO>{sums}, plan.offs.get(), nb)));
-        RAMA_TRY(read_back(ctx, back, plan.offs.get() + nb, (size_t)(1 + plan.extra) * sizeof(TO)));
+        RAMA_TRY(read_back(ctx, back, plan.offs.get() + nb, sizeof(TO), plan.words.get(), (size_t)plan.extra * sizeof(TO)));
     } else if (plan.extra > 0) {
         RAMA_TRY(read_back(ctx, back + 1, plan.extra_ptr(), (size_t)plan.extra * sizeof(TO)));
     }
@@ -830,7 +832,7 @@ constexpr int rs_scatter_waves(int lds_bytes, int threads)
 template <typename K, typename V, bool HAS_V, bool LOCAL_SCAN, int THREADS, int ITEMS, typename SRC>
 __global__ __launch_bounds__(THREADS, (rs_scatter_waves<HAS_V>(THREADS * ITEMS * ((int)sizeof(K) + 4) + THREADS * 8 + 1088, THREADS))) void k_rs_scatter(const K *kin, const V *vin, SRC src, K *kout, V *vout,
                                                         const uint32_t *offs, size_t n, int shift, int bits,
-                                                        uint32_t nb)
+                                                        uint32_t nb, uint32_t *starts)
 {
     constexpr bool kFromSource = !std::is_same<SRC, NoSource>::value;
     constexpr int kTile = THREADS * ITEMS, NW = THREADS / 64;
@@ -910,6 +912,10 @@ __global__ __launch_bounds__(THREADS, (rs_scatter_waves<HAS_V>(THREADS * ITEMS *
         for (int k = 0; k < 3; ++k)
             if (k < w) { run += s_run[k]; digit += s_rows[k]; }
         gdelta[tid] = digit + before - run;
+        if (starts && tile_id == 0 && tid <= (int)mask) {      // where the digits' keys begin, and the end of the last one's
+            starts[tid] = digit;
+            if (tid == (int)mask) starts[mask + 1u] = digit + rows;
+        }
 #pragma unroll
         for (int k = 0; k < NW; ++k) { whist[k][tid] = (uint16_t)run; run += c[k]; }
     }
@@ -1012,7 +1018,7 @@ struct LocalSort {
 template <typename K, typename V, bool HAS_V, typename LK>
 __global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_rs_local(const K *kin, const V *vin, K *kout, V *vout,
                                                                    const uint32_t *bounds, int low_bits, uint32_t n_all,
-                                                                   uint32_t *head_sums)
+                                                                   uint32_t *head_sums, uint32_t *oversize)
 {
     constexpr int NW = kLocalSortWaves;
     constexpr int kItems = LocalSort<LK>::items;
@@ -1025,7 +1031,10 @@ __global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_rs_local(const K *k
     // without a bounds array the (single) workgroup takes the whole array of n_all keys
     const uint32_t beg = bounds ? bounds[blockIdx.x] : 0u, end = bounds ? bounds[blockIdx.x + 1] : n_all;
     const uint32_t cnt = end - beg;
-    if (cnt == 0 || cnt > (uint32_t)kCap) return;      // the caller has ruled the second case out
+    if (cnt == 0 || cnt > (uint32_t)kCap) {      // the second case: ruled out by the caller, or told to it
+        if (cnt && oversize && threadIdx.x == 0) *oversize = 1u;
+        return;
+    }
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const K base = (kin[beg] >> low_bits) << low_bits;
     const uint64_t top_span = (uint64_t)((kin[end - 1] >> low_bits) - (kin[beg] >> low_bits));
@@ -1271,7 +1280,7 @@ inline const char *rs_local_name()
 
 // one pass: histogram, offsets, scatter
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS, typename SRC>
-rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist)
+rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist, uint32_t *starts)
 {
     const uint32_t nb = grid_for(n, THREADS * ITEMS);
     {
@@ -1281,7 +1290,7 @@ rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb
     LAUNCH_TRY(ctx, "rs_hist");
     if (nb <= kSortLocalScanTiles) {
         ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-        k_rs_scatter<K, V, HAS_V, true, THREADS, ITEMS, SRC><<<xcd_grid(nb), THREADS, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb);
+        k_rs_scatter<K, V, HAS_V, true, THREADS, ITEMS, SRC><<<xcd_grid(nb), THREADS, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb, starts);
     } else {
         {
             ProfScope ps_(ctx, "k_rs_rowscan", (double)(((size_t)nb << bits) * 8));
@@ -1289,7 +1298,7 @@ rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb
         }
         LAUNCH_TRY(ctx, "rs_rowscan");
         ProfScope ps_(ctx, rs_scatter_name<K, HAS_V>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
-        k_rs_scatter<K, V, HAS_V, false, THREADS, ITEMS, SRC><<<xcd_grid(nb), THREADS, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb);
+        k_rs_scatter<K, V, HAS_V, false, THREADS, ITEMS, SRC><<<xcd_grid(nb), THREADS, 0, ctx.stream>>>(ka, va, src, kb, vb, hist, n, shift, bits, nb, starts);
     }
     LAUNCH_TRY(ctx, "rs_scatter");
     return RAMA_OK;
@@ -1297,16 +1306,17 @@ rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb
 // the tile by the number of keys n; a pass over a source goes over its n_src >= n places in tiles of the same size
 template <typename K, typename V, bool HAS_V, typename SRC>
 rama_status radix_pass_sized(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, size_t places, int shift, int bits,
-                             uint32_t *hist)
+                             uint32_t *hist, uint32_t *starts)
 {
-    if (n <= kSortShort) return radix_pass<K, V, HAS_V, kShortThreads, kShortTile / kShortThreads, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
-    if (n <= kSortMedium) return radix_pass<K, V, HAS_V, kMediumThreads, kMediumTile / kMediumThreads, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
-    return radix_pass<K, V, HAS_V, SortTile<K>::threads, SortTile<K>::items, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist);
+    if (n <= kSortShort) return radix_pass<K, V, HAS_V, kShortThreads, kShortTile / kShortThreads, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, starts);
+    if (n <= kSortMedium) return radix_pass<K, V, HAS_V, kMediumThreads, kMediumTile / kMediumThreads, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, starts);
+    return radix_pass<K, V, HAS_V, SortTile<K>::threads, SortTile<K>::items, SRC>(ctx, ka, va, src, kb, vb, places, shift, bits, hist, starts);
 }
-// stable LSD passes over the key bits [shift, shift + total_bits); a/b swap with every pass
+// stable LSD passes over the key bits [shift, shift + total_bits); a/b swap with every pass.  starts (optional): where the
+// keys of every digit of the last pass begin, and n.
 template <typename K, typename V, bool HAS_V, typename SRC>
 rama_status radix_passes(Ctx &ctx, K *&ka, V *&va, K *&kb, V *&vb, size_t n, int shift, int total_bits, uint32_t *hist,
-                         bool *result_in_b, bool *iota, K *&kc, V *&vc, const SRC *&src, size_t n_src)
+                         bool *result_in_b, bool *iota, K *&kc, V *&vc, const SRC *&src, size_t n_src, uint32_t *starts = nullptr)
 {
     const int passes = (total_bits + kRadixBits - 1) / kRadixBits;
     int remaining = total_bits;
@@ -1315,10 +1325,10 @@ rama_status radix_passes(Ctx &ctx, K *&ka, V *&va, K *&kb, V *&vb, size_t n, int
         const V *vin = (HAS_V && *iota) ? (const V *)nullptr : va;   // the first pass of a sort whose values are the places 0..n-1
         *iota = false;
         if (src) {
-            RAMA_TRY((radix_pass_sized<K, V, HAS_V, SRC>(ctx, ka, vin, *src, kb, vb, n, n_src, shift, bits, hist)));
+            RAMA_TRY((radix_pass_sized<K, V, HAS_V, SRC>(ctx, ka, vin, *src, kb, vb, n, n_src, shift, bits, hist, starts)));
             src = nullptr;
         } else {
-            RAMA_TRY((radix_pass_sized<K, V, HAS_V, NoSource>(ctx, ka, vin, NoSource{}, kb, vb, n, n, shift, bits, hist)));
+            RAMA_TRY((radix_pass_sized<K, V, HAS_V, NoSource>(ctx, ka, vin, NoSource{}, kb, vb, n, n, shift, bits, hist, starts)));
         }
         std::swap(ka, kb);
         std::swap(va, vb);
@@ -1367,12 +1377,38 @@ rama_status split_sort_tail(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
     {
         ProfScope ps_(ctx, rs_local_name<K, HAS_V, LK>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
         k_rs_local<K, V, HAS_V, LK><<<nbk, LS::threads, 0, ctx.stream>>>(ka, va, kb, vb, bounds.get(), low_bits, (uint32_t)n,
-                                                                      head_sums ? head_sums->get() : nullptr);
+                                                                      head_sums ? head_sums->get() : nullptr, (uint32_t *)nullptr);
     }
     LAUNCH_TRY(ctx, "rs_local");
     *done = true;
     return RAMA_OK;
 }
+
+// A sort of a few hundred thousand keys is launches and nothing else, so it takes one pass over the top bits and one in-LDS
+// sort, a workgroup to a digit, and nobody waits to hear whether every digit's keys fit: the in-LDS sort raises a flag if
+// not, which comes to the host with the count that it waits for behind the sort anyway (sort_and_count_heads), and the keys
+// are sorted by passes then (and so is what comes after them in the same call).  Bits of that pass: digits of kUnseenSegment keys on average, a fifth of what a workgroup holds,
+// or of half as many as it holds at most where eight bits are too few for that.  0: no such sort.
+// 1.3e5 64-bit pairs: four launches instead of nine; contraction of a 300x301 long-range grid 2.17 -> 1.95 ms, 128^2 long-range
+// solve 2.36 -> 2.17, 512^2 5.87 -> 5.69, 6-NN graph of 10^6 points 9.95 -> 9.66, 61x97x131 volume 5.80 -> 5.55.  (The split sort,
+// which waits to hear, measured the same as passes from 2^16 keys up to its line at 2^21.)
+constexpr size_t kUnseenSegment = 1536;
+inline int unseen_top_bits(size_t n, int total_bits, uint64_t key_limit, bool *narrow)
+{
+    for (int t = 1; t <= kRadixBits && t < total_bits; ++t) {
+        const int low = total_bits - t;
+        *narrow = low <= 32;
+        const size_t cap = (size_t)(*narrow ? LocalSort<uint32_t>::cap : LocalSort<uint64_t>::cap);
+        const uint64_t digits = key_limit ? ((key_limit - 1) >> low) + 1 : uint64_t(1) << t;
+        const size_t seg = (size_t)(((uint64_t)n + digits - 1) / digits);
+        if (seg <= cap / 2 && (seg <= kUnseenSegment || t == kRadixBits)) return t;
+    }
+    return 0;
+}
+struct SortUnseen {
+    uint32_t *flag = nullptr;      // a zeroed word
+    bool used = false;
+};
 
 // Sorts keys (and 32-bit values) by the low `total_bits` bits of the key.  a/b are two buffers
 // of n elements each; input in a; on return *result_in_b says where the sorted data is.
@@ -1391,13 +1427,15 @@ static __global__ __launch_bounds__(kBlock) void k_iota(size_t n, uint32_t *p)
 template <typename K, typename V, bool HAS_V, typename SRC = NoSource>
 rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int total_bits, bool *result_in_b, bool iota = false,
                             Buf<uint32_t> *head_sums = nullptr, uint64_t key_limit = 0, K *kc = nullptr, V *vc = nullptr,
-                            K **res_k = nullptr, V **res_v = nullptr, const SRC *src = nullptr, size_t n_src = 0)
+                            K **res_k = nullptr, V **res_v = nullptr, const SRC *src = nullptr, size_t n_src = 0, SortUnseen *unseen = nullptr)
 {
     // src (optional): the keys and values come from a source of n_src places, n of which take part; there is no input a
     // then, and n is more than one workgroup sorts alone
     // kc, vc (optional): a third pair of buffers; the input a is then only read, and the sorted data ends up in b or
     // in c: *res_k, *res_v say where
     // key_limit (optional): all keys are below it (and it needs total_bits bits); 0 = nothing known
+    // unseen (optional): the sort may be one that fails later (see unseen_top_bits); if so, unseen->used says it, and the
+    // keys that the in-LDS sort read, in the other buffers, must stay until the flag is known
     if (key_limit && (total_bits >= 64 || key_limit > (uint64_t(1) << total_bits))) key_limit = 0;
     // head_sums (optional): comes back allocated and filled -- per tile of kScanTile places the number of keys that
     // differ from their left neighbour -- when the sort ends in the in-LDS kernel, and empty otherwise
@@ -1421,11 +1459,11 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             if (narrow) {
                 ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint32_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
                 k_rs_local<K, V, HAS_V, uint32_t><<<1, LocalSort<uint32_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, (const uint32_t *)nullptr,
-                                                                                                  total_bits, (uint32_t)n, hs);
+                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr);
             } else {
                 ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint64_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
                 k_rs_local<K, V, HAS_V, uint64_t><<<1, LocalSort<uint64_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, (const uint32_t *)nullptr,
-                                                                                                  total_bits, (uint32_t)n, hs);
+                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr);
             }
             LAUNCH_TRY(ctx, "rs_local");
             *result_in_b = true;
@@ -1433,12 +1471,36 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             return RAMA_OK;
         }
     }
+    bool unseen_narrow = false;
+    const int unseen_bits = unseen && ctx.sorts_unseen && n < ctx.sort_split_min && ctx.sort_split_min < (size_t)INT64_MAX ? unseen_top_bits(n, total_bits, key_limit, &unseen_narrow) : 0;
     const uint32_t nb = grid_for(src ? n_src : n, n <= kSortShort ? kShortTile : n <= kSortMedium ? kMediumTile : SortTile<K>::tile);
     const int all_passes = (total_bits + kRadixBits - 1) / kRadixBits;
     // [digit][tile] and the digits' totals, for the widest digit of a pass (the top bits of a split sort: whole digits)
-    const int digit_bits = n >= ctx.sort_split_min ? kRadixBits : (total_bits + all_passes - 1) / all_passes;
+    const int digit_bits = unseen_bits ? unseen_bits : n >= ctx.sort_split_min ? kRadixBits : (total_bits + all_passes - 1) / all_passes;
     Buf<uint32_t> hist;
     RAMA_TRY(hist.alloc(ctx, ((size_t)nb + 1) << digit_bits));
+    if (unseen_bits) {
+        Buf<uint32_t> starts;
+        RAMA_TRY(starts.alloc(ctx, ((size_t)1 << unseen_bits) + 1));
+        const int low_bits = total_bits - unseen_bits;
+        RAMA_TRY((radix_passes<K, V, HAS_V, SRC>(ctx, ka, va, kb, vb, n, low_bits, unseen_bits, hist.get(), result_in_b, &iota, kc, vc, src, n_src, starts.get())));
+        RAMA_TRY(head_sums_alloc(ctx, n, head_sums));
+        uint32_t *hs = head_sums ? head_sums->get() : nullptr;
+        if (unseen_narrow) {
+            ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint32_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
+            k_rs_local<K, V, HAS_V, uint32_t><<<1u << unseen_bits, LocalSort<uint32_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, starts.get(), low_bits,
+                                                                                                             (uint32_t)n, hs, unseen->flag);
+        } else {
+            ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint64_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
+            k_rs_local<K, V, HAS_V, uint64_t><<<1u << unseen_bits, LocalSort<uint64_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, starts.get(), low_bits,
+                                                                                                             (uint32_t)n, hs, unseen->flag);
+        }
+        LAUNCH_TRY(ctx, "rs_local");
+        unseen->used = true;
+        *result_in_b = !*result_in_b;
+        if (res_k) { *res_k = kb; *res_v = vb; }
+        return RAMA_OK;
+    }
     if (n >= ctx.sort_split_min) {
         // top bits: whole passes, enough of them for segments that a workgroup can hold.  A workgroup takes the
         // segments that start in half a capacity of places, so what it gets stays below the capacity as long as no
@@ -1481,9 +1543,17 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
 
 // Convenience wrappers working on Buf pairs: after the call `k`/`v` hold the sorted data.
 // `iota`: v comes in unset and stands for the values 0..n-1
+// The other pair of buffers of a sort that may turn out to have failed, and the flag that tells.
+template <typename K, typename V>
+struct SortAgain : SortUnseen {
+    Buf<K> k;
+    Buf<V> v;
+    SortUnseen *unseen() { return flag ? this : nullptr; }
+};
+
 template <typename K, typename V>
 rama_status radix_sort_pairs(Ctx &ctx, Buf<K> &k, Buf<V> &v, size_t n, int total_bits, bool iota = false,
-                             Buf<uint32_t> *head_sums = nullptr, uint64_t key_limit = 0)
+                             Buf<uint32_t> *head_sums = nullptr, uint64_t key_limit = 0, SortAgain<K, V> *again = nullptr)
 {
     static_assert(sizeof(V) == 4, "32-bit payload");
     if (head_sums) head_sums->reset();
@@ -1499,8 +1569,11 @@ rama_status radix_sort_pairs(Ctx &ctx, Buf<K> &k, Buf<V> &v, size_t n, int total
     RAMA_TRY(k2.alloc(ctx, n));
     RAMA_TRY(v2.alloc(ctx, n));
     bool in_b = false;
-    RAMA_TRY((radix_sort_impl<K, V, true>(ctx, k.get(), v.get(), k2.get(), v2.get(), n, total_bits, &in_b, iota, head_sums, key_limit)));
+    RAMA_TRY((radix_sort_impl<K, V, true>(ctx, k.get(), v.get(), k2.get(), v2.get(), n, total_bits, &in_b, iota, head_sums, key_limit,
+                                                 (K *)nullptr, (V *)nullptr, (K **)nullptr, (V **)nullptr, (const NoSource *)nullptr, 0,
+                                                 again ? again->unseen() : nullptr)));
     if (in_b) { k.swap(k2); v.swap(v2); }
+    if (again && again->used) { again->k = std::move(k2); again->v = std::move(v2); }
     return RAMA_OK;
 }
 
@@ -1515,15 +1588,16 @@ inline bool sort_takes_source(size_t n, size_t n_src)
 }
 template <typename K, typename V, typename SRC>
 rama_status radix_sort_source(Ctx &ctx, const SRC &source, size_t n_src, Buf<K> &k, Buf<V> &v, Buf<K> &k2, Buf<V> &v2, size_t n, int total_bits,
-                              Buf<uint32_t> *head_sums, uint64_t key_limit)
+                              Buf<uint32_t> *head_sums, uint64_t key_limit, SortAgain<K, V> *again = nullptr)
 {
     static_assert(sizeof(V) == 4, "32-bit payload");
     bool in_b = false;
     K *rk = nullptr;
     V *rv = nullptr;
     RAMA_TRY((radix_sort_impl<K, V, true, SRC>(ctx, (K *)nullptr, (V *)nullptr, k.get(), v.get(), n, total_bits, &in_b, false, head_sums, key_limit,
-                                               k2.get(), v2.get(), &rk, &rv, &source, n_src)));
+                                               k2.get(), v2.get(), &rk, &rv, &source, n_src, again ? again->unseen() : nullptr)));
     if (rk == k2.get()) { k.swap(k2); v.swap(v2); }
+    if (again && again->used) { again->k = std::move(k2); again->v = std::move(v2); }
     return RAMA_OK;
 }
 
@@ -1557,7 +1631,8 @@ rama_status radix_sort_pairs_from(Ctx &ctx, const K *kin, const V *vin, Buf<K> &
 }
 
 template <typename K>
-rama_status radix_sort_keys(Ctx &ctx, Buf<K> &k, size_t n, int total_bits, Buf<uint32_t> *head_sums = nullptr, uint64_t key_limit = 0)
+rama_status radix_sort_keys(Ctx &ctx, Buf<K> &k, size_t n, int total_bits, Buf<uint32_t> *head_sums = nullptr, uint64_t key_limit = 0,
+                            SortAgain<K, uint32_t> *again = nullptr)
 {
     if (head_sums) head_sums->reset();
     if (n <= 1) return RAMA_OK;
@@ -1565,9 +1640,43 @@ rama_status radix_sort_keys(Ctx &ctx, Buf<K> &k, size_t n, int total_bits, Buf<u
     RAMA_TRY(k2.alloc(ctx, n));
     bool in_b = false;
     RAMA_TRY((radix_sort_impl<K, uint32_t, false>(ctx, k.get(), (uint32_t *)nullptr, k2.get(), (uint32_t *)nullptr, n,
-                                                  total_bits, &in_b, false, head_sums, key_limit)));
+                                                  total_bits, &in_b, false, head_sums, key_limit, (K *)nullptr, (uint32_t *)nullptr,
+                                                  (K **)nullptr, (uint32_t **)nullptr, (const NoSource *)nullptr, 0, again ? again->unseen() : nullptr)));
     if (in_b) k.swap(k2);
+    if (again && again->used) again->k = std::move(k2);
     return RAMA_OK;
+}
+
+// What follows a sort whose flag is the word `word` of `plan`: the heads of the sorted keys are counted (scan_totals) and the
+// count comes to the host with the flag.  If it is raised, the keys are sorted once more, from the buffers that the
+// in-LDS sort read (in the order of their top bits, which does no harm), and counted again.  flags(k): the scan's input.
+template <typename K, typename V, typename FLAGS>
+rama_status count_heads(Ctx &ctx, Buf<K> &k, Buf<V> *v, size_t n, int total_bits, const FLAGS &flags, ScanPlan<uint32_t> &plan, int word,
+                        Buf<uint32_t> &head_sums, SortAgain<K, V> &again)
+{
+    RAMA_TRY((scan_totals<uint32_t>(ctx, flags(k.get()), plan, head_sums.get())));
+    head_sums.reset();
+    if (!again.used || !plan.extra_value[word]) {
+        again.k.reset(); again.v.reset();
+        return RAMA_OK;
+    }
+    ctx.sorts_unseen = false;
+    const uint32_t nb = grid_for(n, n <= kSortShort ? kShortTile : n <= kSortMedium ? kMediumTile : SortTile<K>::tile);
+    Buf<uint32_t> hist;
+    RAMA_TRY(hist.alloc(ctx, ((size_t)nb + 1) << kRadixBits));
+    K *ka = again.k.get(), *kb = k.get(), *kc = nullptr;
+    V *va = again.v.get(), *vb = v ? v->get() : nullptr, *vc = nullptr;
+    bool in_b = false, iota = false;
+    const NoSource *src = nullptr;
+    if (v) RAMA_TRY((radix_passes<K, V, true, NoSource>(ctx, ka, va, kb, vb, n, 0, total_bits, hist.get(), &in_b, &iota, kc, vc, src, 0)));
+    else RAMA_TRY((radix_passes<K, V, false, NoSource>(ctx, ka, va, kb, vb, n, 0, total_bits, hist.get(), &in_b, &iota, kc, vc, src, 0)));
+    if (!in_b) {
+        k.swap(again.k);
+        if (v) v->swap(again.v);
+    }
+    again.k.reset(); again.v.reset();
+    RAMA_TRY(plan.sums.alloc(ctx, plan.nb));
+    return scan_totals<uint32_t>(ctx, flags(k.get()), plan);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1843,7 +1952,8 @@ static __global__ __launch_bounds__(kBlock) void k_reduce_runs(size_t m, const u
 }
 
 // `plan`: the scan over HeadFlag{key} (scan_totals has run); uniq = its total.  `sign_sums` (optional): an array of
-// ceil(uniq / kScanTile) words that gets the sign counts of the output costs per tile.
+// ceil(uniq / kScanTile) words that gets the sign counts of the output costs per tile; if it has memory already, the words are
+// there and zero.
 inline rama_status reduce_runs(Ctx &ctx, const ScanPlan<uint32_t> &plan, const uint64_t *key, const uint32_t *val, int dbits,
                                int32_t *io, int32_t *jo, float *co, Buf<uint64_t> *sign_sums = nullptr)
 {
@@ -1851,8 +1961,10 @@ inline rama_status reduce_runs(Ctx &ctx, const ScanPlan<uint32_t> &plan, const u
     unsigned long long *ss = nullptr;
     if (sign_sums) {
         const size_t tiles = ((size_t)plan.total + kScanTile - 1) / kScanTile;
-        RAMA_TRY(sign_sums->alloc(ctx, tiles > 0 ? tiles : 1));
-        RAMA_TRY(fill<uint64_t>(ctx, sign_sums->get(), 0ull, tiles > 0 ? tiles : 1));
+        if (!sign_sums->get()) {
+            RAMA_TRY(sign_sums->alloc(ctx, tiles > 0 ? tiles : 1));
+            RAMA_TRY(fill<uint64_t>(ctx, sign_sums->get(), 0ull, tiles > 0 ? tiles : 1));
+        }
         ss = (unsigned long long *)sign_sums->get();
     }
     {

@@ -435,7 +435,7 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<
         RAMA_TRY(signs.alloc(ctx, nb_signs));
         ProfScope ps_(ctx, kernel_name<SignFlags>("k_scan_reduce"), (double)(m * 4));
         k_scan_reduce<uint64_t, SignFlags><<<nb_signs, kBlock, 0, ctx.stream>>>(SignFlags{g.c.get()}, signs.get(), m, (uint64_t *)nullptr, (uint32_t *)nullptr,
-                                                                               (uint64_t *)nullptr, 0, 0);
+                                                                               (uint64_t *)nullptr, 0, (const uint64_t *)nullptr, 0);
     }
     LAUNCH_TRY(ctx, "scan_reduce");
     k_total_signs<<<1, kBlock, 0, ctx.stream>>>(g.sign_sums.get() ? g.sign_sums.get() : signs.get(), (size_t)nb_signs, offs.get() + nb + 1);
@@ -447,7 +447,7 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<
         const uint64_t seq = ++ctx.mail_seq;
         {
             ProfScope ps_(ctx, "k_scan_mid", (double)((size_t)nb * 16));
-            k_scan_mid<uint64_t><<<1, kBlock, 0, ctx.stream>>>(sums.get(), offs.get(), nb, mailbox(ctx), seq, 1);
+            k_scan_mid<uint64_t><<<1, kBlock, 0, ctx.stream>>>(sums.get(), offs.get(), nb, mailbox(ctx), seq, offs.get() + nb + 1, 1);
         }
         LAUNCH_TRY(ctx, "scan_mid");
         RAMA_TRY(wait_mail(ctx, seq));

@@ -778,6 +778,24 @@ def test_sort_at_the_limits_of_its_tiles(rama, oracle32, m):
     assert np.array_equal(np_(got["i"]), wi) and np.array_equal(np_(got["j"]), wj) and np.array_equal(np_(got["c"]), wc)
 
 
+# One pass over the top bits and one in-LDS sort, a workgroup to a digit: `crowd` keys with the same digit, as many as a
+# workgroup holds (8192; 4096 of 64 bits) and one more, in front, in the middle and at the end of the others
+@pytest.mark.parametrize("n,m,crowd,at", [(40000, 30000, 8192, 0.5), (40000, 30000, 8193, 0.5), (40000, 30000, 8193, 0.0), (40000, 30000, 9000, 1.0),
+                                          (1 << 21, 12000, 4096, 0.5), (1 << 21, 12000, 4097, 0.5), (40000, 393216, 0, 0.0), (40000, 900000, 20000, 0.3)])
+def test_sort_that_may_find_out_later(rama, oracle32, n, m, crowd, at):
+    rng = np.random.default_rng(n + m + crowd)
+    i, j = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
+    lone = max(0, min(n - 2, int(at * n) - 1))
+    i[i == lone] = (lone + 1) % n                                       # nobody else's row
+    here = rng.permutation(m)[:crowd]
+    i[here], j[here] = lone, rng.integers(lone + 1, n, crowd)
+    i[0], j[0] = 0, n - 1
+    c = (-np.abs(rng.normal(size=m)) * 10.0 ** rng.integers(-3, 4, m) - 1e-3).astype(np.float32)
+    wi, wj, wc = oracle32.canonicalise(n, i, j, c)
+    got = rama.contract(n, i, j, c, repeat=1, want_diag=False)
+    assert np.array_equal(np_(got["i"]), wi) and np.array_equal(np_(got["j"]), wj) and np.array_equal(np_(got["c"]), wc)
+
+
 @pytest.mark.parametrize("n,m", [(3, 20001), (2, 2049), (5, 4096), (40, 70000)])
 def test_canonicalisation_sums_long_runs_in_input_order(rama, oracle32, n, m):
     # few nodes, many parallel edges: every run of equal pairs is thousands of entries long and crosses

@@ -227,20 +227,27 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
 
 // The rest of the matching for a list that one workgroup holds: candidates in registers, a handshake between three barriers
 // (about 4 us) instead of a launch, and the host hears of it once.  A longer list is left as it is.  On entry the list's
-// proposals stand in `best`.  result[0]: candidates left, result[1]: pairs made.  Contraction of a 300x301 long-range grid
-// 2.53 -> 2.41 ms, 61x97x131 solve 8.53 -> 8.38, 512^2 8.05 -> 7.95.
+// proposals stand in `best`.  Contraction of a 300x301 long-range grid 2.53 -> 2.41 ms, 61x97x131 solve 8.53 -> 8.38, 512^2
+// 8.05 -> 7.95.
+// With the matching complete, the new nodes of a graph of up to kNumberMax nodes are numbered here as well (fmap; see
+// NumberPairsEmit), and the message to the host goes out from here: mail[1] length of the first list | candidates left << 32,
+// mail[2]: pairs made here, then the counters of the rounds enqueued with this launch, two words each.
 constexpr int kFinishThreads = 1024, kFinishItems = 8;
 constexpr uint32_t kFinishMax = kFinishThreads * kFinishItems;
-__global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint32_t *n_list, Cands a, int32_t *mate, unsigned long long *best,
-                                                                     int rounds_left, uint32_t *result)
+constexpr int kNumberMax = 1 << 15, kNumberItems = 8;
+__global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint32_t *n_first, const uint32_t *n_list, Cands a, int32_t *mate,
+                                                                     unsigned long long *best, int rounds_left, int n_nodes, int32_t *fmap,
+                                                                     const uint32_t *counters, int n_counters, uint64_t *mail, uint64_t seq)
 {
-    __shared__ uint32_t s_left, s_pairs;
+    __shared__ uint32_t s_left, s_pairs, s_wave[kFinishThreads / 64];
     const uint32_t n = *n_list, tid = threadIdx.x;
+    if (tid == 0) { s_left = 0u; s_pairs = 0u; }
+    for (int k = (int)tid; k < n_counters; k += kFinishThreads) reinterpret_cast<uint32_t *>(mail + 3)[k] = counters[k];
     if (n > kFinishMax) {      // uniform
-        if (tid == 0) { result[0] = n; result[1] = 0u; }
+        if (tid == 0) { mail[1] = (uint64_t)*n_first | (uint64_t)n << 32; mail[2] = 0ull; }
+        mail_send(mail, seq);
         return;
     }
-    if (tid == 0) { s_left = 0u; s_pairs = 0u; }
     int32_t u[kFinishItems], v[kFinishItems];
     unsigned long long r[kFinishItems];
     uint32_t alive = 0, pairs = 0;
@@ -274,7 +281,37 @@ __global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint3
     const uint32_t n_left = wave_sum((uint32_t)__popc(alive)), n_pairs = wave_sum(pairs);
     if (lane_id() == 0) { atomicAdd(&s_left, n_left); atomicAdd(&s_pairs, n_pairs); }
     __syncthreads();
-    if (tid == 0) { result[0] = s_left; result[1] = s_pairs; }
+    if (tid == 0) { mail[1] = (uint64_t)*n_first | (uint64_t)s_left << 32; mail[2] = (uint64_t)s_pairs; }
+    uint32_t done = 0;      // nodes numbered so far
+    for (int base = 0; fmap && base < n_nodes; base += kFinishThreads * kNumberItems) {      // uniform
+        const int v0 = base + (int)tid * kNumberItems;
+        int32_t w[kNumberItems];
+        uint32_t roots = 0;
+#pragma unroll
+        for (int q = 0; q < kNumberItems; ++q) w[q] = v0 + q < n_nodes ? mate[v0 + q] : 0;
+#pragma unroll
+        for (int q = 0; q < kNumberItems; ++q) roots += v0 + q < n_nodes && (w[q] < 0 || w[q] > v0 + q) ? 1u : 0u;
+        const uint32_t inc = wave_inclusive_scan(roots);
+        if (lane_id() == 63) s_wave[tid >> 6] = inc;
+        __syncthreads();
+        uint32_t number = done + inc - roots, all = 0;
+#pragma unroll
+        for (int k = 0; k < kFinishThreads / 64; ++k) {
+            const uint32_t x = s_wave[k];
+            number += k < (int)(tid >> 6) ? x : 0u;
+            all += x;
+        }
+#pragma unroll
+        for (int q = 0; q < kNumberItems; ++q)
+            if (v0 + q < n_nodes && (w[q] < 0 || w[q] > v0 + q)) {
+                fmap[v0 + q] = (int32_t)number;
+                if (w[q] >= 0) fmap[w[q]] = (int32_t)number;
+                ++number;
+            }
+        done += all;
+        __syncthreads();
+    }
+    mail_send(mail, seq);
 }
 
 // The components of a matching are its pairs, represented by the smaller node: new numbers straight from the mates.
@@ -822,16 +859,24 @@ __global__ __launch_bounds__(kForestThreads) void k_forest_components(uint32_t n
 // rounds have used since).
 struct Candidates {
     uint32_t n = 0;
+    bool summed = false;      // the plan holds tile sums, not their scan
     ScanPlan<uint32_t> plan;
     Buf<int32_t> u, v;
     Buf<unsigned long long> r;
 };
 
-// handshake matching; mate[v] = partner or -1; returns |S| in n_matched
-static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap, Buf<int32_t> &mate, int64_t &n_matched, Candidates &list)
+// handshake matching; mate[v] = partner or -1; returns |S| in n_matched.  fmap (optional): memory for the numbers of the new
+// nodes; *numbered says whether they are there.
+// On graphs of up to kBlindEdges edges nobody waits to hear how many candidates there are: arrays and grids are made for as
+// many as there are edges, and the first look at the counts is the one behind the handshake rounds.
+constexpr size_t kBlindEdges = size_t(1) << 20;
+static_assert(kBlindEdges <= kMatchBatchMax && kBlindEdges <= kAdvMedium, "short lists");
+static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap, Buf<int32_t> &mate, int64_t &n_matched, Candidates &list,
+                            int32_t *fmap, bool *numbered)
 {
     const size_t m = (size_t)g.m, n = (size_t)g.n;
     n_matched = 0;
+    *numbered = false;
     RAMA_TRY(mate.alloc(ctx, n > 0 ? n : 1));
     MultiFill setup;   // mate = -1, rank words and counters = 0: one launch
     setup.add(mate.get(), 0xffffffffu, n);
@@ -839,12 +884,18 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
     Buf<int32_t> cu[2], cv[2];
     Buf<unsigned long long> cr[2];
     Cands cur{}, nxt{};
-    uint32_t na = 0;
     ScanPlan<uint32_t> &cand = list.plan;   // its total -- the length of the first list -- stays on the device for the first round
+    const CandFlag flag{g.c.get(), tau};
+    const int cap = rounds_cap > 0 ? rounds_cap : 0;
+    bool blind = m <= kBlindEdges && cap > 0 && !ctx.active->is_arena();
+    list.summed = blind;
     RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, m, 0, cand)));
-    RAMA_TRY((scan_totals<uint32_t>(ctx, CandFlag{g.c.get(), tau}, cand)));
-    na = list.n = cand.total;
-    if (na == 0) return setup.run(ctx);
+    uint32_t na = (uint32_t)m;
+    if (!blind) {
+        RAMA_TRY((scan_totals<uint32_t>(ctx, flag, cand)));
+        na = list.n = cand.total;
+        if (na == 0) return setup.run(ctx);
+    }
     for (int k = 0; k < 2; ++k) {
         RAMA_TRY(cu[k].alloc(ctx, na));
         RAMA_TRY(cv[k].alloc(ctx, na));
@@ -856,31 +907,35 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
     RAMA_TRY(best.alloc(ctx, n));
     RAMA_TRY(best_next.alloc(ctx, n));
     RAMA_TRY(best_after.alloc(ctx, n));
-    const int cap = rounds_cap > 0 ? rounds_cap : 0;
-    Buf<uint32_t> counters;                      // what k_handshake_finish left, then per handshake round: survivors, pairs made
-    RAMA_TRY(counters.alloc(ctx, (size_t)(2 * cap + 4)));
+    Buf<uint32_t> counters;                      // per handshake round: survivors, pairs made
+    RAMA_TRY(counters.alloc(ctx, (size_t)(2 * cap + 2)));
     setup.add(best.get(), 0u, n);
     setup.add(best_next.get(), 0u, n);
-    setup.add(counters.get(), 0u, (size_t)(2 * cap + 4));
-    RAMA_TRY(setup.run(ctx));
+    setup.add(counters.get(), 0u, (size_t)(2 * cap + 2));
     // The list is packed and makes the first round's proposals on the way: it is not read once more just for that.
-    RAMA_TRY((scan_emit<uint32_t>(ctx, CandFlag{g.c.get(), tau},
-                                  PackCandsEmit{g.i.get(), g.j.get(), g.c.get(), cur, cap > 0 ? best.get() : nullptr}, cand,
-                                  (double)((size_t)na * (cap > 0 ? 44 : 28)))));
-    LAUNCH_TRY(ctx, "propose");
+    const PackCandsEmit pack{g.i.get(), g.j.get(), g.c.get(), cur, cap > 0 ? best.get() : nullptr};
+    const double pack_bytes = (double)((size_t)na * (cap > 0 ? 44 : 28));
+    if (blind) {
+        RAMA_TRY(setup.run_with_sums(ctx, flag, cand.offs.get(), m));
+        RAMA_TRY((scan_emit_sums<uint32_t>(ctx, flag, pack, cand, pack_bytes)));
+    } else {
+        RAMA_TRY(setup.run(ctx));
+        RAMA_TRY((scan_emit<uint32_t>(ctx, flag, pack, cand, pack_bytes)));
+    }
     // Long lists: one round per look at the counts, so that every launch has its exact size.  Short lists (the launches
     // are empty anyway): as many rounds as should bring the list to what one workgroup finishes (a round keeps about two
-    // candidates in five) are enqueued on the size of its first list, then the kernel that finishes it, and the counts come
-    // back together; rounds behind one that emptied the list find a zero count and do nothing.
-    std::vector<uint32_t> back((size_t)(2 * cap + 4), 0u);
+    // candidates in five, and about half of the edges are candidates) are enqueued on the size of its first list, then the
+    // kernel that finishes it, and the counts come back together; rounds behind one that emptied the list find a zero count
+    // and do nothing.
+    std::vector<uint32_t> back((size_t)(2 * cap + 2), 0u);
     for (int r = 0; r < cap && na > 0;) {
         const bool finish = na <= kMatchBatchMax;
         int batch = finish ? 0 : 1;
         if (finish)
-            for (uint32_t left = na; left > kFinishMax && batch < cap - r; left /= 2) ++batch;
-        auto n_list = [&](int round) { return round == 0 ? cand.offs.get() + cand.nb : counters.get() + 2 + 2 * (round - 1); };
+            for (uint32_t left = blind ? na / 2 + 1 : na; (left > kFinishMax || (blind && batch == 0 && na > kFinishMax)) && batch < cap - r; left /= 2) ++batch;
+        auto n_list = [&](int round) { return round == 0 ? cand.offs.get() + cand.nb : counters.get() + 2 * (round - 1); };
         for (int b = 0; b < batch; ++b, ++r) {
-            uint32_t *count = counters.get() + 2 + 2 * r;
+            uint32_t *count = counters.get() + 2 * r;
             const bool accepts = na <= kAdvMedium;
             if (!accepts) {
                 ProfScope ps_(ctx, "k_accept", (double)((size_t)na * 40));
@@ -901,19 +956,32 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
             best.swap(best_next);          // (this, next, after) <- (next, after, this)
             best_next.swap(best_after);
         }
-        if (finish) {
+        if (!finish) {
+            RAMA_TRY(read_back(ctx, back.data(), counters.get(), (size_t)(2 * r) * 4));
+            n_matched += back[(size_t)(2 * (r - 1) + 1)];
+            na = back[(size_t)(2 * (r - 1))];
+            continue;
+        }
+        const uint64_t seq = ++ctx.mail_seq;
+        {
             ProfScope ps_(ctx, "k_handshake_finish", (double)(kFinishMax * 40));
-            k_handshake_finish<<<1, kFinishThreads, 0, ctx.stream>>>(n_list(r), cur, mate.get(), best.get(), cap - r, counters.get());
+            k_handshake_finish<<<1, kFinishThreads, 0, ctx.stream>>>(n_list(0), n_list(r), cur, mate.get(), best.get(), cap - r, g.n, fmap,
+                                                                    counters.get() + 2 * (r - batch), 2 * batch,
+                                                                    mailbox(ctx), seq);
         }
         LAUNCH_TRY(ctx, "handshake_finish");
-        RAMA_TRY(read_back(ctx, back.data(), counters.get(), (size_t)(2 + 2 * r) * 4));
-        for (int b = r - batch; b < r; ++b) n_matched += back[(size_t)(2 + 2 * b + 1)];
-        if (finish) {
-            n_matched += back[1];
-            na = back[0];
-            if (na <= kFinishMax) break;      // the rest was worked off, or the cap was reached
-        } else {
-            na = back[(size_t)(2 + 2 * (r - 1))];
+        RAMA_TRY(wait_mail(ctx, seq));
+        const volatile uint64_t *mail = mailbox(ctx);
+        const uint64_t lengths = mail[1];
+        const uint32_t left = (uint32_t)(lengths >> 32);
+        list.n = (uint32_t)lengths;
+        n_matched += (int64_t)mail[2];
+        for (int b = 0; b < batch; ++b) n_matched += (int64_t)(mail[3 + b] >> 32);
+        blind = false;
+        na = left;
+        if (left <= kFinishMax) {      // the rest was worked off, or the cap was reached
+            *numbered = fmap != nullptr;
+            break;
         }
     }
     list.u = std::move(cu[0]); list.v = std::move(cv[0]); list.r = std::move(cr[0]);
@@ -925,8 +993,10 @@ static rama_status forest_short(Ctx &ctx, const Graph &g, float tau, Candidates 
 {
     const size_t m = (size_t)g.m, n = (size_t)g.n;
     const Cands a{list.u.get(), list.v.get(), list.r.get()};
-    RAMA_TRY((scan_emit<uint32_t>(ctx, CandFlag{g.c.get(), tau}, PackCandsEmit{g.i.get(), g.j.get(), g.c.get(), a, nullptr}, list.plan,
-                                  (double)((size_t)list.n * 28))));
+    const PackCandsEmit pack{g.i.get(), g.j.get(), g.c.get(), a, nullptr};
+    const CandFlag flag{g.c.get(), tau};
+    if (list.summed) RAMA_TRY((scan_emit_sums<uint32_t>(ctx, flag, pack, list.plan, (double)((size_t)list.n * 28))));
+    else RAMA_TRY((scan_emit<uint32_t>(ctx, flag, pack, list.plan, (double)((size_t)list.n * 28))));
     Buf<int32_t> comp, hook, depth, up;
     Buf<uint32_t> up_cand;
     Buf<unsigned long long> best;
@@ -1145,6 +1215,32 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
                                                         keep.sums.get(), out.sign_sums.get());
     }
     LAUNCH_TRY(ctx, "relabel_keys");
+    bool narrow = false;
+    if (sort_takes_source(m, m) && unseen_bits_now(ctx, m, 2 * nbits, (uint64_t)n_new << nbits, &narrow)) {
+        // Nobody waits to hear how many edges are left: the sort is made for all of them, its first pass leaves the loops out
+        // and the number comes with the count behind it.  The key's second field is as wide as it can get, which costs such
+        // a sort nothing.  Measured together with the matching's counts, see kBlindEdges.
+        Buf<uint64_t> key;
+        Buf<uint32_t> val, val2, head_sums;
+        RAMA_TRY(key.alloc(ctx, m));
+        RAMA_TRY(val.alloc(ctx, m));
+        RAMA_TRY(val2.alloc(ctx, m));
+        ScanPlan<uint32_t> runs;
+        RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, m, 2, runs)));
+        SortAgain<uint64_t, uint32_t> again;
+        again.flag = runs.extra_ptr();
+        again.n_sorted = runs.extra_ptr() + 1;
+        RAMA_TRY((radix_sort_source<uint64_t, uint32_t>(ctx, RelabelledEdges{raw.get(), g.c.get(), nbits}, m, key, val, raw, val2, m, 2 * nbits,
+                                                        &head_sums, (uint64_t)n_new << nbits, &again)));
+        RAMA_TRY((count_heads<uint64_t, uint32_t>(ctx, key, &val, m, 2 * nbits, [](const uint64_t *k) { return HeadFlag{k}; }, runs, 0, head_sums, again, true)));
+        const size_t uniq = runs.total;
+        RAMA_TRY(out.i.alloc(ctx, uniq > 0 ? uniq : 1));
+        RAMA_TRY(out.j.alloc(ctx, uniq > 0 ? uniq : 1));
+        RAMA_TRY(out.c.alloc(ctx, uniq > 0 ? uniq : 1));
+        RAMA_TRY(reduce_runs(ctx, runs, key.get(), val.get(), nbits, out.i.get(), out.j.get(), out.c.get(), &out.sign_sums));
+        out.m = (int64_t)uniq;
+        return RAMA_OK;
+    }
     RAMA_TRY((scan_totals<uint32_t>(ctx, NotLoopKey{raw.get()}, keep, keep.sums.get())));   // tile sums: left by k_relabel_keys
     const uint32_t kept = keep.total;
     const int dbits = bits_for((uint64_t)keep.extra_value[0] + 1);
@@ -1197,10 +1293,15 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
     RAMA_TRY(zero_page_recycle(ctx));
     Buf<int32_t> mate;
     Candidates list;
-    RAMA_TRY(matching(ctx, g, tau, rounds_cap, mate, n_matched, list));
+    bool numbered = false;
+    if (n <= (size_t)kNumberMax) RAMA_TRY(fmap.alloc(ctx, n > 0 ? n : 1));
+    RAMA_TRY(matching(ctx, g, tau, rounds_cap, mate, n_matched, list, fmap.get(), &numbered));
     n_new = g.n;
-    if (n_matched == 0) return RAMA_OK;
-    RAMA_TRY(fmap.alloc(ctx, n));
+    if (n_matched == 0) {
+        fmap.reset();
+        return RAMA_OK;
+    }
+    if (!fmap.get()) RAMA_TRY(fmap.alloc(ctx, n));
     // too few pairs: switch to the spanning forest without conflicts (Sec. 3.1, "fewer than 0.1|V|")
     const bool forest = forest_ratio > 0.0f && (double)n_matched < (double)forest_ratio * (double)g.n;
     if (!(forest && list.n <= kShortForest)) list = Candidates{};      // nobody else needs it, and what follows needs the memory
@@ -1223,7 +1324,7 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
         ProfScope ps_(ctx, "k_number", (double)(n * 12));
         k_number<<<grid_for(n), kBlock, 0, ctx.stream>>>(n, rep.get(), npos.get(), fmap.get());
         LAUNCH_TRY(ctx, "number");
-    } else {
+    } else if (!numbered) {
         RAMA_TRY((scan_enumerate<uint32_t>(ctx, IsPairRoot{mate.get()}, NumberPairsEmit{mate.get(), fmap.get()}, n, (double)(n * 8))));
     }
     mate.reset();

@@ -491,8 +491,10 @@ template <typename E>
 struct EmitLongChain<E, std::void_t<decltype(E::long_chain)>> { static constexpr bool value = E::long_chain; };
 constexpr int kChainThreads = 1024;
 
-template <typename TO, typename F, typename E, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_scan_emit(F f, E emit, const TO *block_offsets, size_t n)
+// SUMS: the tile sums have not been scanned; a workgroup adds up those in front of its tile, and the last one stores the total
+// behind them (a few hundred tiles: less than a launch in between).
+template <typename TO, typename F, typename E, int THREADS, bool SUMS>
+__global__ __launch_bounds__(THREADS) void k_scan_emit(F f, E emit, std::conditional_t<SUMS, TO, const TO> *block_offsets, size_t n)
 {
     constexpr int kItems = kScanTile / THREADS, kWaves = THREADS / 64;
     __shared__ TO wave_tot[kWaves];
@@ -515,8 +517,16 @@ __global__ __launch_bounds__(THREADS) void k_scan_emit(F f, E emit, const TO *bl
         carry += wave_last(inc);
     }
     if (lane_id() == 0) wave_tot[w] = carry;
-    __syncthreads();
-    TO pre = block_offsets[blockIdx.x];
+    TO pre = 0;
+    if constexpr (SUMS) {
+        static_assert(THREADS == kBlock, "block_sum");
+        for (unsigned k = threadIdx.x; k < blockIdx.x; k += THREADS) pre += block_offsets[k];
+        pre = block_sum(pre);      // its barriers are wave_tot's as well
+        if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) block_offsets[gridDim.x] = pre + block_offsets[blockIdx.x];
+    } else {
+        __syncthreads();
+        pre = block_offsets[blockIdx.x];
+    }
 #pragma unroll
     for (int k = 0; k < kWaves - 1; ++k)
         if (k < w) pre += wave_tot[k];
@@ -538,7 +548,20 @@ rama_status scan_emit(Ctx &ctx, F f, E emit, const ScanPlan<TO> &plan, double by
     {
         ProfScope ps_(ctx, kernel_name<E>("k_scan_emit"), (double)(plan.n * F::bytes) + bytes);
         constexpr int kThreads = EmitLongChain<E>::value ? kChainThreads : kBlock;
-        k_scan_emit<TO, F, E, kThreads><<<plan.nb, kThreads, 0, ctx.stream>>>(f, emit, plan.offs.get(), plan.n);
+        k_scan_emit<TO, F, E, kThreads, false><<<plan.nb, kThreads, 0, ctx.stream>>>(f, emit, plan.offs.get(), plan.n);
+    }
+    LAUNCH_TRY(ctx, "scan_emit");
+    return RAMA_OK;
+}
+// the same behind the tile sums alone (in plan.offs, which gets the total as well): a consumer whose total nobody on the host
+// waits for
+template <typename TO, typename F, typename E>
+rama_status scan_emit_sums(Ctx &ctx, F f, E emit, const ScanPlan<TO> &plan, double bytes)
+{
+    if (plan.n == 0) return RAMA_OK;
+    {
+        ProfScope ps_(ctx, kernel_name<E>("k_scan_emit"), (double)(plan.n * F::bytes) + bytes);
+        k_scan_emit<TO, F, E, kBlock, true><<<plan.nb, kBlock, 0, ctx.stream>>>(f, emit, plan.offs.get(), plan.n);
     }
     LAUNCH_TRY(ctx, "scan_emit");
     return RAMA_OK;
@@ -1018,7 +1041,7 @@ struct LocalSort {
 template <typename K, typename V, bool HAS_V, typename LK>
 __global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_rs_local(const K *kin, const V *vin, K *kout, V *vout,
                                                                    const uint32_t *bounds, int low_bits, uint32_t n_all,
-                                                                   uint32_t *head_sums, uint32_t *oversize)
+                                                                   uint32_t *head_sums, uint32_t *oversize, uint32_t *n_sorted)
 {
     constexpr int NW = kLocalSortWaves;
     constexpr int kItems = LocalSort<LK>::items;
@@ -1031,6 +1054,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_rs_local(const K *k
     // without a bounds array the (single) workgroup takes the whole array of n_all keys
     const uint32_t beg = bounds ? bounds[blockIdx.x] : 0u, end = bounds ? bounds[blockIdx.x + 1] : n_all;
     const uint32_t cnt = end - beg;
+    if (n_sorted && blockIdx.x == 0 && threadIdx.x == 0) *n_sorted = bounds[gridDim.x];
     if (cnt == 0 || cnt > (uint32_t)kCap) {      // the second case: ruled out by the caller, or told to it
         if (cnt && oversize && threadIdx.x == 0) *oversize = 1u;
         return;
@@ -1377,7 +1401,7 @@ rama_status split_sort_tail(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
     {
         ProfScope ps_(ctx, rs_local_name<K, HAS_V, LK>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
         k_rs_local<K, V, HAS_V, LK><<<nbk, LS::threads, 0, ctx.stream>>>(ka, va, kb, vb, bounds.get(), low_bits, (uint32_t)n,
-                                                                      head_sums ? head_sums->get() : nullptr, (uint32_t *)nullptr);
+                                                                      head_sums ? head_sums->get() : nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr);
     }
     LAUNCH_TRY(ctx, "rs_local");
     *done = true;
@@ -1405,8 +1429,14 @@ inline int unseen_top_bits(size_t n, int total_bits, uint64_t key_limit, bool *n
     }
     return 0;
 }
+inline int unseen_bits_now(const Ctx &ctx, size_t n, int total_bits, uint64_t key_limit, bool *narrow)
+{
+    if (!ctx.sorts_unseen || n >= ctx.sort_split_min || ctx.sort_split_min >= (size_t)INT64_MAX) return 0;
+    return unseen_top_bits(n, total_bits, key_limit, narrow);
+}
 struct SortUnseen {
     uint32_t *flag = nullptr;      // a zeroed word
+    uint32_t *n_sorted = nullptr;  // optional: gets the number of keys, where the caller knows no more than a bound
     bool used = false;
 };
 
@@ -1459,11 +1489,11 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             if (narrow) {
                 ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint32_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
                 k_rs_local<K, V, HAS_V, uint32_t><<<1, LocalSort<uint32_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, (const uint32_t *)nullptr,
-                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr);
+                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr, (uint32_t *)nullptr);
             } else {
                 ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint64_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
                 k_rs_local<K, V, HAS_V, uint64_t><<<1, LocalSort<uint64_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, (const uint32_t *)nullptr,
-                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr);
+                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr, (uint32_t *)nullptr);
             }
             LAUNCH_TRY(ctx, "rs_local");
             *result_in_b = true;
@@ -1472,7 +1502,7 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
         }
     }
     bool unseen_narrow = false;
-    const int unseen_bits = unseen && ctx.sorts_unseen && n < ctx.sort_split_min && ctx.sort_split_min < (size_t)INT64_MAX ? unseen_top_bits(n, total_bits, key_limit, &unseen_narrow) : 0;
+    const int unseen_bits = unseen ? unseen_bits_now(ctx, n, total_bits, key_limit, &unseen_narrow) : 0;
     const uint32_t nb = grid_for(src ? n_src : n, n <= kSortShort ? kShortTile : n <= kSortMedium ? kMediumTile : SortTile<K>::tile);
     const int all_passes = (total_bits + kRadixBits - 1) / kRadixBits;
     // [digit][tile] and the digits' totals, for the widest digit of a pass (the top bits of a split sort: whole digits)
@@ -1489,11 +1519,11 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
         if (unseen_narrow) {
             ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint32_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
             k_rs_local<K, V, HAS_V, uint32_t><<<1u << unseen_bits, LocalSort<uint32_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, starts.get(), low_bits,
-                                                                                                             (uint32_t)n, hs, unseen->flag);
+                                                                                                             (uint32_t)n, hs, unseen->flag, unseen->n_sorted);
         } else {
             ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint64_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
             k_rs_local<K, V, HAS_V, uint64_t><<<1u << unseen_bits, LocalSort<uint64_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, starts.get(), low_bits,
-                                                                                                             (uint32_t)n, hs, unseen->flag);
+                                                                                                             (uint32_t)n, hs, unseen->flag, unseen->n_sorted);
         }
         LAUNCH_TRY(ctx, "rs_local");
         unseen->used = true;
@@ -1650,12 +1680,17 @@ rama_status radix_sort_keys(Ctx &ctx, Buf<K> &k, size_t n, int total_bits, Buf<u
 // What follows a sort whose flag is the word `word` of `plan`: the heads of the sorted keys are counted (scan_totals) and the
 // count comes to the host with the flag.  If it is raised, the keys are sorted once more, from the buffers that the
 // in-LDS sort read (in the order of their top bits, which does no harm), and counted again.  flags(k): the scan's input.
+// bounded: n is a bound, the number of keys comes with the flag, in the word behind it, and takes the place of n in the plan.
 template <typename K, typename V, typename FLAGS>
 rama_status count_heads(Ctx &ctx, Buf<K> &k, Buf<V> *v, size_t n, int total_bits, const FLAGS &flags, ScanPlan<uint32_t> &plan, int word,
-                        Buf<uint32_t> &head_sums, SortAgain<K, V> &again)
+                        Buf<uint32_t> &head_sums, SortAgain<K, V> &again, bool bounded = false)
 {
     RAMA_TRY((scan_totals<uint32_t>(ctx, flags(k.get()), plan, head_sums.get())));
     head_sums.reset();
+    if (bounded) {
+        n = plan.n = plan.extra_value[word + 1];
+        plan.nb = grid_for(n, kScanTile);
+    }
     if (!again.used || !plan.extra_value[word]) {
         again.k.reset(); again.v.reset();
         return RAMA_OK;
@@ -1768,9 +1803,8 @@ struct FillJobs {
     size_t end[4];   // running totals of the arrays' lengths in 16-byte pieces
     size_t words[4];
 };
-static __global__ __launch_bounds__(kBlock) void k_fill_multi(FillJobs jobs)
+__device__ __forceinline__ void fill_piece(const FillJobs &jobs, size_t k)
 {
-    const size_t k = (size_t)blockIdx.x * kBlock + threadIdx.x;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         const size_t first = a ? jobs.end[a - 1] : 0;
@@ -1782,6 +1816,25 @@ static __global__ __launch_bounds__(kBlock) void k_fill_multi(FillJobs jobs)
             else for (size_t q = w; q < jobs.words[a]; ++q) jobs.p[a][q] = v;
         }
     }
+}
+static __global__ __launch_bounds__(kBlock) void k_fill_multi(FillJobs jobs)
+{
+    fill_piece(jobs, (size_t)blockIdx.x * kBlock + threadIdx.x);
+}
+// tile sums of f over n items, and the arrays of a MultiFill on the way
+template <typename F>
+__global__ __launch_bounds__(kBlock) void k_fill_and_sum(FillJobs jobs, F f, uint32_t *sums, unsigned nb, size_t n)
+{
+    for (size_t k = (size_t)blockIdx.x * kBlock + threadIdx.x; k < jobs.end[3]; k += (size_t)gridDim.x * kBlock) fill_piece(jobs, k);
+    if (blockIdx.x >= nb) return;      // the whole workgroup
+    const size_t base = (size_t)blockIdx.x * kScanTile + threadIdx.x;
+    uint32_t x[kScanItems], s = 0;
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) x[q] = item_or_last<uint32_t>(f, base + (size_t)q * kBlock, n);
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) s += x[q];
+    s = block_sum(s);
+    if (threadIdx.x == 0) sums[blockIdx.x] = s;
 }
 class MultiFill {
 public:
@@ -1808,6 +1861,20 @@ public:
             k_fill_multi<<<grid_for(total_), kBlock, 0, ctx.stream>>>(jobs_);
         }
         LAUNCH_TRY(ctx, "fill_multi");
+        return RAMA_OK;
+    }
+    // the fills by the launch that adds up f tile by tile
+    template <typename F>
+    rama_status run_with_sums(Ctx &ctx, const F &f, uint32_t *sums, size_t n)
+    {
+        if (overflow_) return fail(ctx, RAMA_ERR_INVALID_ARG, "more than four arrays in one fill");
+        for (int a = n_; a < 4; ++a) { jobs_.p[a] = nullptr; jobs_.v[a] = 0; jobs_.end[a] = total_; jobs_.words[a] = 0; }
+        {
+            ProfScope ps_(ctx, "k_fill_and_sum", bytes_ + (double)(n * F::bytes));
+            const unsigned nb = grid_for(n, kScanTile), fill_groups = grid_for(total_, 4 * kBlock);
+            k_fill_and_sum<F><<<nb > fill_groups ? nb : fill_groups, kBlock, 0, ctx.stream>>>(jobs_, f, sums, nb, n);
+        }
+        LAUNCH_TRY(ctx, "fill_and_sum");
         return RAMA_OK;
     }
 

@@ -76,8 +76,8 @@ def event_name(rocprof_name):
         # key type or a length append it where the library does (HeadFlagT<u64> -> HeadFlag64)
         head, args = n.split("<", 1)
         parts = args.strip()[:-1].strip().split(",")
-        if parts[-1].strip().isdigit():
-            parts.pop()                       # the number of threads
+        while parts[-1].strip().isdigit() or parts[-1].strip() in ("true", "false"):
+            parts.pop()                       # the number of threads, the kind of offsets
         last = parts[-1].strip()
         functor, _, targ = last.partition("<")
         targ = targ.strip().rstrip(">").strip()

@@ -681,6 +681,27 @@ def test_contraction_in_one_workgroup(rama, oracle32, n, m, repeat, ratio, pos):
     assert np.array_equal(np_(got["diag"]), want["diag"][: got["n_nodes"]])
 
 
+# Both sides of the lines up to which the matching's last workgroup numbers the nodes (2^15 nodes; 8192 at a time) and nobody
+# waits for the number of candidates or of kept edges (2^20 edges); every edge a candidate, none, and too many candidates
+# left for the last workgroup behind the rounds that should bring them there (a star keeps all of them)
+@pytest.mark.parametrize("n,m,pos", [(32768, 60000, 0.8), (32769, 60000, 0.8), (8193, 40000, 0.5), (20000, 1 << 20, 0.6), (20000, (1 << 20) + 1, 0.6),
+                                     (9000, 30000, 1.0), (9000, 30000, 0.0), (70000, 60000, -1.0), (2, 9000, 1.0)])
+def test_contraction_that_waits_for_no_counts(rama, oracle32, n, m, pos):
+    rng = np.random.default_rng(n + m)
+    if pos < 0:      # a star, its costs ascending: a handshake round matches one pair, the others propose again
+        i, j = np.zeros(n - 1, np.int32), np.arange(1, n, dtype=np.int32)
+        i, j = np.concatenate([i, rng.integers(1, n, m)]).astype(np.int32), np.concatenate([j, rng.integers(1, n, m)]).astype(np.int32)
+        c = np.concatenate([np.linspace(1, 2, n - 1), np.linspace(0.1, 0.9, m)]).astype(np.float32)
+    else:
+        i, j = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
+        c = (np.round(rng.random(m) * 8 + 1) / 8 * np.where(rng.random(m) < pos, 1, -1)).astype(np.float32)
+    want = oracle32.contract(n, i, j, c, repeat=1)
+    got = rama.contract(n, i, j, c, repeat=1)
+    assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+
+
 @pytest.mark.parametrize("n,m,pos", [(64, 300, 0.7), (90, 2000, 0.9), (128, 8128, 0.75), (128, 8128, 0.97), (1000, 8000, 0.8), (4000, 8200, 0.9),
                                      (400, 6000, 0.9), (8000, 20000, 0.85)])
 @pytest.mark.parametrize("later,iters,max_rounds", [(3, 5, 0), (3, 1, 3), (0, 0, 0), (3, 12, 2)])

@@ -514,6 +514,10 @@ rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, double
 // triangle, in ascending order of the triangles.
 rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters, TriangleCounts &out, bool *done,
                           const std::function<void()> &separated);
+// messages_few: k_iters > 0 iterations over T triangles that messages_fit (edges: three per triangle, ascending triangles,
+// whose costs are zero in the beginning and go to ct, if given); *raised: what a kernel in front left in *flag.
+bool messages_fit(size_t T);
+rama_status messages_few(Ctx &ctx, const uint32_t *edges, size_t T, int k_iters, float *ce, float *ct, const uint32_t *flag, bool *raised);
 rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<uint32_t> &slots, TriangleCounts &out);
 
 // a4..a6: one primal update.  fmap[n] -> [0,n_new); n_matched = |S|.  If |S|==0 nothing else is produced.

@@ -231,14 +231,16 @@ struct FewShared {
     uint32_t wave[kFewThreads / 64];
 };
 
-// mail[1]: number of triangles, mail[2]: attractive edges | repulsive edges << 32.  Nothing is done for more than kFewTriangles.
-__global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *list, const uint32_t *counter, const uint64_t *sign_sums,
-                                                              size_t n_sums, int iters, float *ce, uint64_t *mail, uint64_t seq)
+// counter (optional): the number of triangles, which n_triangles is otherwise.  ct (optional) gets their costs in the end.
+// mail[1]: number of triangles, mail[2]: attractive edges | repulsive edges << 32 (sums of sign_sums), mail[3]: *flag (optional).
+// Nothing is done for more than kFewTriangles.
+__global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *list, const uint32_t *counter, uint32_t n_triangles, const uint64_t *sign_sums,
+                                                              size_t n_sums, int iters, float *ce, float *ct, const uint32_t *flag, uint64_t *mail, uint64_t seq)
 {
     __shared__ FewShared S;
     __shared__ unsigned long long s_signs;
     const int tid = (int)threadIdx.x, lane = lane_id(), w = tid >> 6;
-    const uint32_t T = *counter;
+    const uint32_t T = counter ? *counter : n_triangles;
     if (tid == 0) s_signs = 0;
     __syncthreads();
     {
@@ -367,9 +369,16 @@ __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *li
                 }
             __syncthreads();
         }
+        if (ct) {      // uniform
+#pragma unroll
+            for (int q = 0; q < kFewPer; ++q) {
+                const uint32_t t = (uint32_t)(tid + q * kFewThreads);
+                if (t < T) { ct[3 * t] = a[q]; ct[3 * t + 1] = b[q]; ct[3 * t + 2] = c[q]; }
+            }
+        }
     }
     __syncthreads();
-    if (tid == 0) { mail[1] = (uint64_t)T; mail[2] = (uint64_t)s_signs; }
+    if (tid == 0) { mail[1] = (uint64_t)T; mail[2] = (uint64_t)s_signs; mail[3] = flag ? (uint64_t)*flag : 0ull; }
     mail_send(mail, seq);
 }
 
@@ -406,8 +415,8 @@ rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters
     const uint64_t seq = ++ctx.mail_seq;
     {
         ProfScope ps_(ctx, "k_messages_few", (double)(grid_for((size_t)g.m, kScanTile) * 8 + kFewSlots * 4));
-        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(list.get(), counter.get(), g.sign_sums.get(), (size_t)grid_for((size_t)g.m, kScanTile), k_iters,
-                                                         g.c.get(), mailbox(ctx), seq);
+        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(list.get(), counter.get(), 0, g.sign_sums.get(), (size_t)grid_for((size_t)g.m, kScanTile), k_iters,
+                                                         g.c.get(), nullptr, nullptr, mailbox(ctx), seq);
     }
     LAUNCH_TRY(ctx, "messages_few");
     RAMA_TRY(wait_mail(ctx, seq));
@@ -418,6 +427,20 @@ rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters
     out.attractive = (int64_t)(uint32_t)signs; out.repulsive = (int64_t)(signs >> 32);
     if (found) g.sign_sums.reset();      // the costs are new
     *done = true;
+    return RAMA_OK;
+}
+
+bool messages_fit(size_t T) { return T > 0 && T <= (size_t)kFewTriangles; }
+rama_status messages_few(Ctx &ctx, const uint32_t *edges, size_t T, int k_iters, float *ce, float *ct, const uint32_t *flag, bool *raised)
+{
+    const uint64_t seq = ++ctx.mail_seq;
+    {
+        ProfScope ps_(ctx, "k_messages_few", (double)(T * 24));
+        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(edges, nullptr, (uint32_t)T, nullptr, 0, k_iters, ce, ct, flag, mailbox(ctx), seq);
+    }
+    LAUNCH_TRY(ctx, "messages_few");
+    RAMA_TRY(wait_mail(ctx, seq));
+    *raised = ((const volatile uint64_t *)mailbox(ctx))[3] != 0;
     return RAMA_OK;
 }
 

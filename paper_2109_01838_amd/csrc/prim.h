@@ -935,10 +935,13 @@ __global__ __launch_bounds__(THREADS, (rs_scatter_waves<HAS_V>(THREADS * ITEMS *
         for (int k = 0; k < 3; ++k)
             if (k < w) { run += s_run[k]; digit += s_rows[k]; }
         gdelta[tid] = digit + before - run;
-        if (starts && tile_id == 0 && tid <= (int)mask) {      // where the digits' keys begin, and the end of the last one's
-            starts[tid] = digit;
-            if (tid == (int)mask) starts[mask + 1u] = digit + rows;
-        }
+        // where the digits' keys begin, and the end of the last one's; only arrays with small tiles are asked (the code alone
+        // costs the large ones registers: 2.4e7 32-bit pairs 83 -> 105 us)
+        if constexpr (kTile <= kMediumTile)
+            if (starts && tile_id == 0 && tid <= (int)mask) {
+                starts[tid] = digit;
+                if (tid == (int)mask) starts[mask + 1u] = digit + rows;
+            }
 #pragma unroll
         for (int k = 0; k < NW; ++k) { whist[k][tid] = (uint16_t)run; run += c[k]; }
     }
@@ -1434,6 +1437,7 @@ inline int unseen_bits_now(const Ctx &ctx, size_t n, int total_bits, uint64_t ke
     if (!ctx.sorts_unseen || n >= ctx.sort_split_min || ctx.sort_split_min >= (size_t)INT64_MAX) return 0;
     return unseen_top_bits(n, total_bits, key_limit, narrow);
 }
+static_assert((LocalSort<uint32_t>::cap / 2) << kRadixBits <= kSortMedium, "tiles that tell where the digits begin");
 struct SortUnseen {
     uint32_t *flag = nullptr;      // a zeroed word
     uint32_t *n_sorted = nullptr;  // optional: gets the number of keys, where the caller knows no more than a bound

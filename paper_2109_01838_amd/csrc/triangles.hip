@@ -13,8 +13,8 @@
 //   many    counted tile by tile, scanned, listed in order; the incidence sort and the iterations of dual.hip follow.
 //
 // Measured against the lists of cycles (cycles.hip, then chords, keys and their sort in dual.hip), us for the separation and
-// the message passing of a round: 9.4e7 edges with 1.5e7 triangles 4850, 1.6e6 edges with 3.1e5 triangles 300 instead
-// of 433, 3.2e5 with 2.5e4 of a volume's late round 124 instead of 273, 8.1e4 with 246 triangles 40 instead of 185.  Solves:
+// the message passing of a round: 9.4e7 edges with 1.5e7 triangles 4800 instead of 6900, 1.6e6 with 3.1e5 300 instead of 433,
+// 3.2e5 with 2.5e4 of a volume's late round 124 instead of 273, 8.1e4 with 246 triangles 40 instead of 185.  Solves:
 // 128^2 long-range grid 2.79 -> 2.28 ms, 512^2 7.0 -> 5.9, 6-NN graph of 10^6 points 11.5 -> 9.95, 61x97x131 volume 7.2 -> 5.8,
 // 320^3 volume 84.4 -> 78.1.
 #include "prim.h"

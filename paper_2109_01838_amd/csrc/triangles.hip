@@ -37,7 +37,9 @@ struct TriangleGraph {
     const int32_t *rowptr, *i, *j;
     const float *c;
     size_t m;
+    const uint64_t *signs;      // attractive edges | repulsive edges << 32
 };
+__device__ __forceinline__ bool both_signs(uint64_t signs) { return (uint32_t)signs != 0u && (signs >> 32) != 0u; }
 
 constexpr int kTriBatch = 2;                   // tries a thread has under way at a time
 // triangles of a tile that the counting pass keeps: contracted grids and neighbour graphs have about one to five edges
@@ -67,6 +69,12 @@ __global__ __launch_bounds__(kBlock) void k_triangles(TriangleGraph g, uint32_t 
     if (tile >= nb) return;      // the whole workgroup (padding of the grid)
     const int tid = (int)threadIdx.x, lane = lane_id(), w = tid >> 6;
     uint64_t at = 0;
+    if constexpr (MODE != kTriFill) {
+        if (!both_signs(*g.signs)) {      // no triangle in the whole graph
+            if (MODE == kTriCount && tid == 0) sums[tile] = 0;
+            return;
+        }
+    }
     if constexpr (MODE == kTriFill) {
         at = offs[tile];
         const uint32_t n = (uint32_t)(offs[tile + 1] - at);
@@ -232,23 +240,14 @@ struct FewShared {
 };
 
 // counter (optional): the number of triangles, which n_triangles is otherwise.  ct (optional) gets their costs in the end.
-// mail[1]: number of triangles, mail[2]: attractive edges | repulsive edges << 32 (sums of sign_sums), mail[3]: *flag (optional).
+// mail[1]: number of triangles, mail[2]: *signs (optional), mail[3]: *flag (optional).
 // Nothing is done for more than kFewTriangles.
-__global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *list, const uint32_t *counter, uint32_t n_triangles, const uint64_t *sign_sums,
-                                                              size_t n_sums, int iters, float *ce, float *ct, const uint32_t *flag, uint64_t *mail, uint64_t seq)
+__global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *list, const uint32_t *counter, uint32_t n_triangles, const uint64_t *signs,
+                                                              int iters, float *ce, float *ct, const uint32_t *flag, uint64_t *mail, uint64_t seq)
 {
     __shared__ FewShared S;
-    __shared__ unsigned long long s_signs;
     const int tid = (int)threadIdx.x, lane = lane_id(), w = tid >> 6;
     const uint32_t T = counter ? *counter : n_triangles;
-    if (tid == 0) s_signs = 0;
-    __syncthreads();
-    {
-        uint64_t s = 0;
-        for (size_t k = (size_t)tid; k < n_sums; k += kFewThreads) s += sign_sums[k];
-        s = wave_sum(s);
-        if (lane == 0 && s) atomicAdd(&s_signs, (unsigned long long)s);
-    }
     if (T > 0 && T <= (uint32_t)kFewTriangles) {      // uniform
         uint32_t e[kFewPer][3];
         uint32_t h[kFewPer][3];      // place in the table | arrival << 16
@@ -378,7 +377,7 @@ __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *li
         }
     }
     __syncthreads();
-    if (tid == 0) { mail[1] = (uint64_t)T; mail[2] = (uint64_t)s_signs; mail[3] = flag ? (uint64_t)*flag : 0ull; }
+    if (tid == 0) { mail[1] = (uint64_t)T; mail[2] = signs ? *signs : 0ull; mail[3] = flag ? (uint64_t)*flag : 0ull; }
     mail_send(mail, seq);
 }
 
@@ -400,6 +399,18 @@ rama_status run_triangles(Ctx &ctx, const char *name, const TriangleGraph &tg, s
     return RAMA_OK;
 }
 
+// sums: sign counts per tile of kScanTile edges
+rama_status total_signs(Ctx &ctx, const uint64_t *sums, size_t m, uint64_t *out)
+{
+    const size_t nb = grid_for(m, kScanTile);
+    {
+        ProfScope ps_(ctx, "k_total_signs", (double)(nb * 8));
+        k_total_signs<<<1, kBlock, 0, ctx.stream>>>(sums, nb, out);
+    }
+    LAUNCH_TRY(ctx, "total_signs");
+    return RAMA_OK;
+}
+
 }  // namespace
 
 rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters, TriangleCounts &out, bool *done, const std::function<void()> &separated)
@@ -407,24 +418,26 @@ rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters
     *done = false;
     if (!g.sign_sums.get()) return RAMA_OK;
     Buf<uint32_t> list, counter;
+    Buf<uint64_t> signs;
     RAMA_TRY(list.alloc(ctx, (size_t)kFewSlots));
     RAMA_TRY(zeroed<uint32_t>(ctx, 1, counter));
-    RAMA_TRY(run_triangles<kTriList>(ctx, "k_triangles", TriangleGraph{rowptr, g.i.get(), g.j.get(), g.c.get(), (size_t)g.m}, (size_t)g.n,
+    RAMA_TRY(signs.alloc(ctx, 1));
+    RAMA_TRY(total_signs(ctx, g.sign_sums.get(), (size_t)g.m, signs.get()));
+    RAMA_TRY(run_triangles<kTriList>(ctx, "k_triangles", TriangleGraph{rowptr, g.i.get(), g.j.get(), g.c.get(), (size_t)g.m, signs.get()}, (size_t)g.n,
                                      list.get(), (uint32_t)kFewTriangles, counter.get(), nullptr, nullptr, nullptr, (double)g.m * 12 + (double)g.n * 4));
     separated();
     const uint64_t seq = ++ctx.mail_seq;
     {
-        ProfScope ps_(ctx, "k_messages_few", (double)(grid_for((size_t)g.m, kScanTile) * 8 + kFewSlots * 4));
-        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(list.get(), counter.get(), 0, g.sign_sums.get(), (size_t)grid_for((size_t)g.m, kScanTile), k_iters,
-                                                         g.c.get(), nullptr, nullptr, mailbox(ctx), seq);
+        ProfScope ps_(ctx, "k_messages_few", (double)(kFewSlots * 4));
+        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(list.get(), counter.get(), 0, signs.get(), k_iters, g.c.get(), nullptr, nullptr, mailbox(ctx), seq);
     }
     LAUNCH_TRY(ctx, "messages_few");
     RAMA_TRY(wait_mail(ctx, seq));
     const volatile uint64_t *mail = mailbox(ctx);
-    const uint64_t found = mail[1], signs = mail[2];
+    const uint64_t found = mail[1], by_sign = mail[2];
     if (found > (uint64_t)kFewTriangles) return RAMA_OK;
     out.triangles = (int64_t)found;
-    out.attractive = (int64_t)(uint32_t)signs; out.repulsive = (int64_t)(signs >> 32);
+    out.attractive = (int64_t)(uint32_t)by_sign; out.repulsive = (int64_t)(by_sign >> 32);
     if (found) g.sign_sums.reset();      // the costs are new
     *done = true;
     return RAMA_OK;
@@ -436,7 +449,7 @@ rama_status messages_few(Ctx &ctx, const uint32_t *edges, size_t T, int k_iters,
     const uint64_t seq = ++ctx.mail_seq;
     {
         ProfScope ps_(ctx, "k_messages_few", (double)(T * 24));
-        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(edges, nullptr, (uint32_t)T, nullptr, 0, k_iters, ce, ct, flag, mailbox(ctx), seq);
+        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(edges, nullptr, (uint32_t)T, nullptr, k_iters, ce, ct, flag, mailbox(ctx), seq);
     }
     LAUNCH_TRY(ctx, "messages_few");
     RAMA_TRY(wait_mail(ctx, seq));
@@ -448,10 +461,10 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<
 {
     const size_t m = (size_t)g.m, n = (size_t)g.n;
     const unsigned nb = triangle_tiles(m, n), nb_signs = grid_for(m, kScanTile);
-    const TriangleGraph tg{rowptr, g.i.get(), g.j.get(), g.c.get(), m};
     Buf<uint64_t> sums, offs, signs;      // offs: nb places, the number of triangles, the sign counts
     RAMA_TRY(sums.alloc(ctx, nb));
     RAMA_TRY(offs.alloc(ctx, (size_t)nb + 2));
+    const TriangleGraph tg{rowptr, g.i.get(), g.j.get(), g.c.get(), m, offs.get() + nb + 1};
     Buf<uint32_t> kept;
     RAMA_TRY(kept.alloc(ctx, 3 * (size_t)nb * (size_t)tri_room(wide_tiles(m, n) ? kBlock : 64)));
     if (!g.sign_sums.get()) {
@@ -461,8 +474,7 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<
                                                                                (uint64_t *)nullptr, 0, (const uint64_t *)nullptr, 0);
     }
     LAUNCH_TRY(ctx, "scan_reduce");
-    k_total_signs<<<1, kBlock, 0, ctx.stream>>>(g.sign_sums.get() ? g.sign_sums.get() : signs.get(), (size_t)nb_signs, offs.get() + nb + 1);
-    LAUNCH_TRY(ctx, "total_signs");
+    RAMA_TRY(total_signs(ctx, g.sign_sums.get() ? g.sign_sums.get() : signs.get(), m, offs.get() + nb + 1));
     RAMA_TRY(run_triangles<kTriCount>(ctx, "k_count_cycles<3>", tg, n, kept.get(), 0, nullptr, sums.get(), nullptr, nullptr,
                                       (double)m * 12 + (double)n * 4 + (double)nb * 12));
     uint64_t back[2];

@@ -1042,6 +1042,38 @@ def test_triangle_rounds_match_the_cycle_lists(rama, kind, n_tri):
             assert out[0][3][0]["n_triangles"] == n_tri
 
 
+def separation_ms(rama, n, i, j, c, params):
+    """Best of four: per round (edges, ms of separation and message passing) by the default search and through the lists of
+    cycles; the two agree in every result."""
+    import torch
+    i, j, c = (torch.as_tensor(x).cuda() for x in (i, j, c))
+    out = []
+    for mode in (0, 1):
+        rama.set_cycle_search(mode)
+        for k in range(4):
+            got = rama.solve(n, i, j, c, params)
+            stats = rama.round_stats()
+            ms = [r["ms"]["cycles"] + r["ms"]["dual"] for r in stats]
+            best = ms if k == 0 else [min(a, b) for a, b in zip(best, ms)]
+        seen = [{k: v for k, v in r.items() if k not in ("ms", "workspace_peak")} for r in stats]
+        out.append((np_(got["labels"]), got["primal"], got["lower_bound"], seen, best))
+    rama.set_cycle_search(0)
+    assert np.array_equal(out[0][0], out[1][0]) and out[0][1:4] == out[1][1:4]
+    return [(r["n_edges"], a, b) for r, a, b in zip(out[0][3], out[0][4], out[1][4])]
+
+
+@pytest.mark.parametrize("pos", [0.0, 1.0])
+def test_rounds_of_one_sign_are_not_searched(rama, pos):
+    """Without an attractive or without a repulsive edge there is no triangle: nobody looks for one, neither behind a round
+    of many triangles nor behind one of few (a search of these rows takes 0.6 to 3 ms)."""
+    from paper_2109_01838_amd import default_params
+    g = signed(inputs.random_graph(3000, 600000, 11), 12, pos)
+    rounds = separation_ms(rama, g["n_nodes"], g["i"], g["j"], g["c"], default_params(max_cycle_len_first=3))
+    for edges, ms, ms_lists in rounds:
+        if edges > 20000:
+            assert ms <= 3.0 * ms_lists + 0.1, rounds
+
+
 def test_determinism(rama):
     g = CASES["knn_20000"]
     n = g["n_nodes"]

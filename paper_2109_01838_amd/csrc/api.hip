@@ -249,7 +249,8 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
         if (lmax >= 3 && k > 0) {
             if (P.dual_rounds == 1 && lmax == 3 && ctx.cycle_search == 0) {
                 TriangleCounts tc;
-                RAMA_TRY(triangle_round(ctx, g, k, round == 1 ? -1 : ctx.rounds.back().n_triangles, round == 1 ? &lbr : nullptr, tc,
+                const bool searched = round > 1 && ctx.rounds.back().n_attractive >= 0;      // the round before
+                RAMA_TRY(triangle_round(ctx, g, k, searched ? ctx.rounds.back().n_triangles : -1, round == 1 ? &lbr : nullptr, tc,
                                         [&] { clock.mark(round, 1); dual_marked = true; }));
                 R.n_attractive = tc.attractive; R.n_repulsive = tc.repulsive;
                 R.n_cycles[0] = tc.triangles;

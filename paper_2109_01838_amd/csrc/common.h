@@ -502,7 +502,7 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
                         Graph *donor = nullptr);
 
 // a1..a3 of a round that separates triangles only, without a list of cycles in between: g's costs become the reduced
-// ones after k_iters > 0 iterations.  `last`: triangles of the round before (negative: none), which tells whether one
+// ones after k_iters > 0 iterations.  `last`: triangles of the round before (negative: it looked for none), which tells whether one
 // workgroup is likely to hold this round's.  `separated` is called where the separation ends in the stream (for the clock).
 struct TriangleCounts {
     int64_t triangles = 0, attractive = 0, repulsive = 0;

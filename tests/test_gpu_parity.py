@@ -1074,6 +1074,21 @@ def test_rounds_of_one_sign_are_not_searched(rama, pos):
             assert ms <= 3.0 * ms_lists + 0.1, rounds
 
 
+@pytest.mark.parametrize("first,shape", [(0, (112, 120, 128)), (3, (1, 1500, 1600))])
+def test_rounds_of_many_triangles_behind_none(rama, first, shape):
+    """The round in front has no triangles, because it looks for none (first = 0) or because a grid has none: the next one's
+    are far too many for one workgroup."""
+    from paper_2109_01838_amd import default_params
+    ids = np.arange(np.prod(shape), dtype=np.int32).reshape(shape)
+    i = np.concatenate([np.delete(ids, -1, a).ravel() for a in range(3)])
+    j = np.concatenate([np.delete(ids, 0, a).ravel() for a in range(3)])
+    c = np.random.default_rng(3).normal(0.15, 0.5, i.size).astype(np.float32)
+    rounds = separation_ms(rama, ids.size, i, j, c, default_params(max_cycle_len_first=first, max_rounds=3))
+    assert rama.round_stats()[0]["n_triangles"] == 0 and rama.round_stats()[1]["n_triangles"] > 300000
+    for edges, ms, ms_lists in rounds[1:]:
+        assert ms <= 1.5 * ms_lists + 0.1, rounds
+
+
 def test_determinism(rama):
     g = CASES["knn_20000"]
     n = g["n_nodes"]

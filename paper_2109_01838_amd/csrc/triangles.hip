@@ -50,12 +50,18 @@ struct TriangleTile {
     int32_t scan[EDGES], lo[EDGES], hi[EDGES]; // start of the stretch that is walked; the stretch that is searched
     uint8_t kind[EDGES];                       // bit 0: the edge is repulsive, bit 1: row v is walked
     uint32_t wave[2][kTriBatch * (kBlock / 64)];
+    uint32_t over;
 };
+
+// The counter of a list that takes no more than `cap`, and a word that says it is full, once per XCD, each in a cache line of
+// its own: 6.2e4 waves that look at the counter itself, one after the other in one line, took 65 us.
+constexpr int kListLine = 32, kListWords = kListLine * 9;
+__device__ __forceinline__ uint32_t *list_over(uint32_t *counter, uint32_t xcd) { return counter + kListLine * (1u + xcd); }
 
 // Bounded by the latency of a try's chain (its edge by bisection in LDS, the entry, three to five probes, the sign), so
 // what counts is the number of tries under way: two to a thread, every step made for both before the next; 64 edges to a
 // workgroup on short lists and on dense rows, 256 beyond (see wide_tiles).
-// The listing pass is over as soon as there are more than cap triangles: the waves that meet the counter beyond it leave.
+// The listing pass is over as soon as there are more than cap triangles: the wave that brings the counter beyond cap tells it.
 // (Run to its end, with an atomic for every wave that finds any, it took 2 ms for the 2.1e6 triangles of 9.6e6 edges, 11 for
 // 8.8e6 of 3.9e7.)
 // The counting pass keeps what it finds, tile by tile in `list`, as long as the tile's room lasts, and the fill pass copies
@@ -88,8 +94,10 @@ __global__ __launch_bounds__(kBlock) void k_triangles(TriangleGraph g, uint32_t 
         }
     }
     const size_t e_first = (size_t)tile * EDGES;
-    uint32_t tries = 0, counted = 0;
-    if constexpr (MODE == kTriList) counted = __hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t tries = 0;
+    if constexpr (MODE == kTriList) {
+        if (tid == 0) S.over = __hip_atomic_load(list_over(counter, blockIdx.x & 7u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (tid < EDGES) {
         const size_t e = e_first + (size_t)tid;
         if (e < g.m) {
@@ -116,8 +124,8 @@ __global__ __launch_bounds__(kBlock) void k_triangles(TriangleGraph g, uint32_t 
     }
     if (tid < EDGES) S.before[tid] = pre + inc - tries;
     __syncthreads();
-    if constexpr (MODE == kTriList) {      // no barrier behind this point: a wave may leave by itself
-        if (counted > cap) return;
+    if constexpr (MODE == kTriList) {
+        if (S.over) return;      // the whole workgroup; behind this point there is no barrier, and a wave may leave by itself
     }
     uint32_t found = 0;
     for (uint32_t p0 = 0, turn = 1; p0 < total; p0 += kTriBatch * kBlock, ++turn) {      // the same number of turns for all threads
@@ -173,10 +181,13 @@ __global__ __launch_bounds__(kBlock) void k_triangles(TriangleGraph g, uint32_t 
 #pragma unroll
             for (int q = 0; q < kTriBatch; ++q)
                 if (hits[q]) {      // uniform in the wave
+                    const uint32_t n = (uint32_t)__popcll(hits[q]);
                     uint32_t base = 0;
-                    if (lane == 0) base = atomicAdd(counter, (uint32_t)__popcll(hits[q]));
+                    if (lane == 0) base = atomicAdd(counter, n);
                     base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
-                    full |= base >= cap;
+                    if (base <= cap && base + n > cap && lane < 8)      // one wave
+                        __hip_atomic_store(list_over(counter, (uint32_t)lane), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    full |= base > cap;
                     base += (uint32_t)__popcll(hits[q] & ((1ull << lane) - 1ull));
                     if (e1[q] >= 0 && base < cap) put(list, base, q);
                 }
@@ -431,7 +442,7 @@ rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters
     Buf<uint32_t> list, counter;
     Buf<uint64_t> signs;
     RAMA_TRY(list.alloc(ctx, (size_t)kFewSlots));
-    RAMA_TRY(zeroed<uint32_t>(ctx, 1, counter));
+    RAMA_TRY(zeroed<uint32_t>(ctx, (size_t)kListWords, counter));
     RAMA_TRY(signs.alloc(ctx, 1));
     RAMA_TRY(total_signs(ctx, g.sign_sums.get(), (size_t)g.m, signs.get()));
     RAMA_TRY(run_triangles<kTriList>(ctx, "k_triangles", TriangleGraph{rowptr, g.i.get(), g.j.get(), g.c.get(), (size_t)g.m, signs.get()}, (size_t)g.n,

@@ -247,16 +247,19 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
         int64_t ntri = 0;
         bool dual_marked = false;
         if (lmax >= 3 && k > 0) {
-            if (P.dual_rounds == 1 && lmax == 3 && ctx.cycle_search == 0) {
-                TriangleCounts tc;
-                const bool searched = round > 1 && ctx.rounds.back().n_attractive >= 0;      // the round before
-                RAMA_TRY(triangle_round(ctx, g, k, searched ? ctx.rounds.back().n_triangles : -1, round == 1 ? &lbr : nullptr, tc,
+            // triangles from the edge list itself, also in a dense graph if `any`
+            TriangleCounts tc;
+            const bool searched = round > 1 && ctx.rounds.back().n_attractive >= 0;      // the round before
+            auto from_edges = [&](bool any) -> rama_status {
+                RAMA_TRY(triangle_round(ctx, g, k, searched ? ctx.rounds.back().n_triangles : -1, any, round == 1 ? &lbr : nullptr, tc,
                                         [&] { clock.mark(round, 1); dual_marked = true; }));
                 R.n_attractive = tc.attractive; R.n_repulsive = tc.repulsive;
                 R.n_cycles[0] = tc.triangles;
                 ntri = tc.triangles;
                 ran = ntri > 0;
-            } else if (P.dual_rounds == 1) {
+                return RAMA_OK;
+            };
+            auto from_lists = [&](Graph *donor) -> rama_status {
                 CycleLists cyc;
                 RAMA_TRY(find_cycles(ctx, g, lmax, P.shortest_cycles_only != 0, cyc));
                 clock.mark(round, 1);
@@ -269,12 +272,24 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
                     Graph aug;
                     DualInfo info;
                     RAMA_TRY(dual_update(ctx, g, kCycleLists, lists, cyc.n, false, k, aug, round == 1 ? &lbr : nullptr,
-                                         nullptr, &info, nullptr, nullptr, &g));
+                                         nullptr, &info, nullptr, nullptr, donor));
                     ntri = info.n_triangles;
                     ran = true;
                     g = std::move(aug);
                 }
-            } else {
+                return RAMA_OK;
+            };
+            const bool edges_first = P.dual_rounds == 1 && lmax == 3 && ctx.cycle_search == 0;
+            if (edges_first) RAMA_TRY(from_edges(false));
+            if (edges_first && tc.dense) {
+                // The lists need more room than the search on the edges: where that is limited the graph stays, and is searched
+                // in spite of its density if they do not find it.
+                const rama_status st = from_lists(ctx.active->is_arena() ? nullptr : &g);
+                if (st == RAMA_ERR_OOM && ctx.active->is_arena()) RAMA_TRY(from_edges(true));
+                else RAMA_TRY(st);
+            } else if (!edges_first && P.dual_rounds == 1) {
+                RAMA_TRY(from_lists(&g));
+            } else if (!edges_first) {
                 // separations and message-passing blocks interleave: the stage clock books all as cycles
                 RAMA_TRY(dual_block(ctx, g, lmax, P.shortest_cycles_only != 0, k, P.dual_rounds, round == 1 ? &lbr : nullptr,
                                     &ran, nullptr, R.n_cycles, &ntri));

@@ -504,21 +504,28 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
 // a1..a3 of a round that separates triangles only, without a list of cycles in between: g's costs become the reduced
 // ones after k_iters > 0 iterations.  `last`: triangles of the round before (negative: it looked for none), which tells whether one
 // workgroup is likely to hold this round's.  `separated` is called where the separation ends in the stream (for the clock).
+// A dense graph is left as it is, for the lists of cycles, unless `any` says to search it all the same.
 struct TriangleCounts {
     int64_t triangles = 0, attractive = 0, repulsive = 0;
+    bool dense = false;
 };
-rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, double *lower_bound, TriangleCounts &out,
+rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, bool any, double *lower_bound, TriangleCounts &out,
                            const std::function<void()> &separated);
-// its two halves (triangles.hip).  few: separation and all iterations, *done stays false when there are too many
-// triangles (or g does not bring its sign counts), and nothing has been changed then; list: the three edges of every
+// its parts (triangles.hip).  survey: what the other two look at before they search; few: separation and all iterations, *done
+// stays false when there are too many triangles, and nothing has been changed then; list: the three edges of every
 // triangle, in ascending order of the triangles.
-rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters, TriangleCounts &out, bool *done,
+struct TriangleSurvey {
+    Buf<uint64_t> words;
+    uint64_t most_tries = 0;      // a graph of which the sample has more is left
+};
+rama_status triangle_survey(Ctx &ctx, const Graph &g, const int32_t *rowptr, bool any, TriangleSurvey &survey);
+rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, const TriangleSurvey &survey, int k_iters, TriangleCounts &out, bool *done,
                           const std::function<void()> &separated);
 // messages_few: k_iters > 0 iterations over T triangles that messages_fit (edges: three per triangle, ascending triangles,
 // whose costs are zero in the beginning and go to ct, if given); *raised: what a kernel in front left in *flag.
 bool messages_fit(size_t T);
 rama_status messages_few(Ctx &ctx, const uint32_t *edges, size_t T, int k_iters, float *ce, float *ct, const uint32_t *flag, bool *raised);
-rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<uint32_t> &slots, TriangleCounts &out);
+rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, const TriangleSurvey &survey, Buf<uint32_t> &slots, TriangleCounts &out);
 
 // a4..a6: one primal update.  fmap[n] -> [0,n_new); n_matched = |S|.  If |S|==0 nothing else is produced.
 rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, float forest_ratio, Buf<int32_t> &fmap,

@@ -943,7 +943,7 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
 // takes 115 to 160, a try that fails costs 20 to 30.
 constexpr int64_t kTryFewFrom = 8192;
 
-rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, double *lower_bound, TriangleCounts &out,
+rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, bool any, double *lower_bound, TriangleCounts &out,
                            const std::function<void()> &separated)
 {
     RAMA_TRY(zero_page_recycle(ctx));
@@ -952,13 +952,16 @@ rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, double
     Buf<int32_t> rowptr;
     RAMA_TRY(rowptr.alloc(ctx, (size_t)g.n + 1));
     RAMA_TRY((row_bounds<int32_t, int32_t>(ctx, g.i.get(), (size_t)g.m, g.n, rowptr.get())));
+    TriangleSurvey survey;
+    RAMA_TRY(triangle_survey(ctx, g, rowptr.get(), any, survey));
     if (last >= 0 && last <= kTryFewFrom && !lower_bound) {
         bool done = false;
-        RAMA_TRY(triangles_few(ctx, g, rowptr.get(), k_iters, out, &done, separated));
-        if (done) return RAMA_OK;
+        RAMA_TRY(triangles_few(ctx, g, rowptr.get(), survey, k_iters, out, &done, separated));
+        if (done || out.dense) return RAMA_OK;
     }
     Buf<uint32_t> skey;
-    RAMA_TRY(triangles_list(ctx, g, rowptr.get(), skey, out));
+    RAMA_TRY(triangles_list(ctx, g, rowptr.get(), survey, skey, out));
+    if (out.dense) return RAMA_OK;
     separated();
     rowptr.reset();
     const size_t T = (size_t)out.triangles;

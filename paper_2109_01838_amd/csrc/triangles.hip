@@ -5,7 +5,8 @@
 // ascending triples (u,v,w).  So the triangles come out of the list itself: for every edge (u,v), the common entries of
 // the rest of row u and of row v, with the signs looked at on the way -- no attractive adjacency (which takes a sort of
 // the lower neighbours), no list of cycles, no keys and no sort to put the triangles in order.  The work is the sum over
-// the edges of the shorter of the two stretches, whatever the degrees.
+// all edges of the shorter of the two stretches, of which a dense graph has many that can be no triangle's: a survey tells,
+// and such a round goes through the lists of cycles (see kDenseTries).
 //
 // Two ways from there:
 //   few     at most kFewTriangles: listed in any order by one launch, and one workgroup does the incidence and all
@@ -37,9 +38,60 @@ struct TriangleGraph {
     const int32_t *rowptr, *i, *j;
     const float *c;
     size_t m;
-    const uint64_t *signs;      // attractive edges | repulsive edges << 32
+    const uint64_t *survey;     // see k_survey
+    uint64_t most_tries;        // of its sample
 };
-__device__ __forceinline__ bool both_signs(uint64_t signs) { return (uint32_t)signs != 0u && (signs >> 32) != 0u; }
+
+// What is tried for edge e: the entries of the shorter of two stretches, [a0,a1) the rest of its row and [b0,b1) the row of
+// its second node.
+struct EdgeTries {
+    int32_t a0, a1, b0, b1;
+    float c;
+    bool walk_v;
+    uint32_t n;
+};
+__device__ __forceinline__ EdgeTries edge_tries(const TriangleGraph &g, size_t e)
+{
+    EdgeTries t;
+    const int32_t v = g.j[e];
+    t.c = g.c[e];
+    t.a0 = (int32_t)e + 1; t.a1 = g.rowptr[g.i[e] + 1]; t.b0 = g.rowptr[v]; t.b1 = g.rowptr[v + 1];
+    t.walk_v = t.b1 - t.b0 < t.a1 - t.a0;
+    t.n = t.c > 0.0f || t.c < 0.0f ? (uint32_t)(t.walk_v ? t.b1 - t.b0 : t.a1 - t.a0) : 0u;
+    return t;
+}
+
+// In front of the search, survey[0]: attractive edges | repulsive edges << 32, survey[1]: tries of a sample of the edges, 64 in
+// a row at up to kSurveySpots places spread evenly.  The search leaves at once when there is no edge of one sign, and when
+// its tries are many (see kDenseTries).  Two to three us in front of a round.
+constexpr int kSurveyThreads = 1024, kSurveyGroups = 64, kSurveySpots = kSurveyGroups * (kSurveyThreads / 64);
+constexpr size_t survey_sample(size_t m) { return m < (size_t)kSurveySpots * 64 ? m : (size_t)kSurveySpots * 64; }
+// sums: n_sums packed sign counts; survey[1] is zero on entry
+__global__ __launch_bounds__(kSurveyThreads) void k_survey(TriangleGraph g, const uint64_t *sums, unsigned n_sums, uint64_t *survey)
+{
+    __shared__ unsigned long long s_all;
+    const int tid = (int)threadIdx.x;
+    if (tid == 0) s_all = 0;
+    __syncthreads();
+    uint64_t x = 0;
+    if (blockIdx.x == kSurveyGroups) {
+        for (unsigned k = (unsigned)tid; k < n_sums; k += kSurveyThreads) x += sums[k];
+    } else {
+        const size_t spot = (size_t)blockIdx.x * (kSurveyThreads / 64) + (size_t)(tid >> 6);
+        const size_t first = g.m <= (size_t)kSurveySpots * 64 ? spot * 64 : spot * g.m / kSurveySpots;
+        const size_t e = first + (size_t)lane_id();
+        if (e < g.m) x = edge_tries(g, e).n;
+    }
+    x = wave_sum(x);
+    if (lane_id() == 0 && x) atomicAdd(&s_all, (unsigned long long)x);
+    __syncthreads();
+    if (tid == 0) {
+        if (blockIdx.x == kSurveyGroups) survey[0] = s_all;
+        else if (s_all) atomicAdd((unsigned long long *)&survey[1], s_all);
+    }
+}
+__host__ __device__ inline bool both_signs(uint64_t signs) { return (uint32_t)signs != 0u && (signs >> 32) != 0u; }
+__device__ __forceinline__ bool not_searched(const TriangleGraph &g) { return !both_signs(g.survey[0]) || g.survey[1] > g.most_tries; }
 
 constexpr int kTriBatch = 2;                   // tries a thread has under way at a time
 // triangles of a tile that the counting pass keeps: contracted grids and neighbour graphs have about one to five edges
@@ -79,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void k_triangles(TriangleGraph g, uint32_t 
     const int tid = (int)threadIdx.x, lane = lane_id(), w = tid >> 6;
     uint64_t at = 0;
     if constexpr (MODE != kTriFill) {
-        if (!both_signs(*g.signs)) {      // no triangle in the whole graph
+        if (not_searched(g)) {
             if (MODE == kTriCount && tid == 0) sums[tile] = 0;
             return;
         }
@@ -101,15 +153,12 @@ __global__ __launch_bounds__(kBlock) void k_triangles(TriangleGraph g, uint32_t 
     if (tid < EDGES) {
         const size_t e = e_first + (size_t)tid;
         if (e < g.m) {
-            const int32_t v = g.j[e];
-            const float c = g.c[e];
-            const int32_t a0 = (int32_t)e + 1, a1 = g.rowptr[g.i[e] + 1], b0 = g.rowptr[v], b1 = g.rowptr[v + 1];
-            const bool walk_v = b1 - b0 < a1 - a0;
-            tries = c > 0.0f || c < 0.0f ? (uint32_t)(walk_v ? b1 - b0 : a1 - a0) : 0u;
-            S.scan[tid] = walk_v ? b0 : a0;
-            S.lo[tid] = walk_v ? a0 : b0;
-            S.hi[tid] = walk_v ? a1 : b1;
-            S.kind[tid] = (uint8_t)((c < 0.0f ? 1 : 0) | (walk_v ? 2 : 0));
+            const EdgeTries t = edge_tries(g, e);
+            tries = t.n;
+            S.scan[tid] = t.walk_v ? t.b0 : t.a0;
+            S.lo[tid] = t.walk_v ? t.a0 : t.b0;
+            S.hi[tid] = t.walk_v ? t.a1 : t.b1;
+            S.kind[tid] = (uint8_t)((t.c < 0.0f ? 1 : 0) | (t.walk_v ? 2 : 0));
         }
     }
     const uint32_t inc = wave_inclusive_scan(tries);
@@ -221,16 +270,6 @@ __global__ __launch_bounds__(kBlock) void k_triangles(TriangleGraph g, uint32_t 
     }
 }
 
-// sum of nb packed sign counts, by one workgroup
-__global__ __launch_bounds__(kBlock) void k_total_signs(const uint64_t *sums, size_t nb, uint64_t *out)
-{
-    uint64_t s = 0;
-    for (size_t k = threadIdx.x; k < nb; k += kBlock) s += sums[k];
-    uint64_t all;
-    (void)block_inclusive_scan(s, &all);
-    if (threadIdx.x == 0) *out = all;
-}
-
 // ---------------------------------------------------------------------------------------------
 // message passing over few triangles: everything by one workgroup
 // ---------------------------------------------------------------------------------------------
@@ -262,9 +301,9 @@ struct FewShared {
 };
 
 // counter (optional): the number of triangles, which n_triangles is otherwise.  ct (optional) gets their costs in the end.
-// mail[1]: number of triangles, mail[2]: *signs (optional), mail[3]: *flag (optional).
+// mail[1]: number of triangles, mail[2], mail[4]: the survey (optional), mail[3]: *flag (optional).
 // Nothing is done for more than kFewTriangles.
-__global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *list, const uint32_t *counter, uint32_t n_triangles, const uint64_t *signs,
+__global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *list, const uint32_t *counter, uint32_t n_triangles, const uint64_t *survey,
                                                               int iters, float *ce, float *ct, const uint32_t *flag, uint64_t *mail, uint64_t seq)
 {
     __shared__ FewShared S;
@@ -399,7 +438,7 @@ __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *li
         }
     }
     __syncthreads();
-    if (tid == 0) { mail[1] = (uint64_t)T; mail[2] = signs ? *signs : 0ull; mail[3] = flag ? (uint64_t)*flag : 0ull; }
+    if (tid == 0) { mail[1] = (uint64_t)T; mail[2] = survey ? survey[0] : 0ull; mail[3] = flag ? (uint64_t)*flag : 0ull; mail[4] = survey ? survey[1] : 0ull; }
     mail_send(mail, seq);
 }
 
@@ -421,45 +460,81 @@ rama_status run_triangles(Ctx &ctx, const char *name, const TriangleGraph &tg, s
     return RAMA_OK;
 }
 
-// sums: sign counts per tile of kScanTile edges
-rama_status total_signs(Ctx &ctx, const uint64_t *sums, size_t m, uint64_t *out)
+// With more tries per edge than kDenseTries, and kManyTries in all, the lists of cycles are the better way: their search starts
+// from the repulsive edges and intersects attractive neighbours only, which on dense graphs is a small part of the tries.
+// Separation and messages of a round in us, edge list | cycle lists (survey and this search's empty launch included), by
+// tries per edge.  Random graphs: 5.4 (10^6 edges) 165 | 338, 7.5 (7.6e5) 121 | 334, 10.5 (9.5e5) 299 | 324, 13.1 (9.0e5)
+// 304 | 340, 16.0 (8.4e5) 342 | 379, 16.1 (8.4e6) 1913 | 1311, 20 (9.3e5) 395 | 393, 30 (8.3e6) 2970 | 1862, 45 (9.6e5) 698 |
+// 536, 133 (10^6) 3553 | 1644.  Where rows lie close together the line could stand higher: long-range grid 13.4 (10^6) 222 |
+// 350, windows 11.4 (2.1e6) 1703 | 1858, 19 (3.6e6) 4500 | 5001, 48 (1.9e6) 596 | 559.  Few tries in all: 13 (6.8e4 edges) 44 |
+// 136, 23 (2.3e5) 64 | 112, 59 (1.7e4) 107 | 138.
+constexpr uint64_t kDenseTries = 16, kManyTries = uint64_t(1) << 21;
+// the same for the sample of m edges
+constexpr uint64_t most_tries(size_t m)
 {
-    const size_t nb = grid_for(m, kScanTile);
-    {
-        ProfScope ps_(ctx, "k_total_signs", (double)(nb * 8));
-        k_total_signs<<<1, kBlock, 0, ctx.stream>>>(sums, nb, out);
-    }
-    LAUNCH_TRY(ctx, "total_signs");
-    return RAMA_OK;
+    const uint64_t dense = kDenseTries * (uint64_t)survey_sample(m), many = m ? kManyTries * (uint64_t)survey_sample(m) / m : 0;
+    return dense > many ? dense : many;
+}
+static_assert(most_tries(0) == 0 && most_tries(1) == kManyTries && most_tries(survey_sample(~size_t(0))) == kManyTries, "short lists");
+static_assert(most_tries(size_t(1) << 18) == kDenseTries << 16 && most_tries((size_t(1) << 31) - 1) == kDenseTries << 16, "long lists");
+
+void take_survey(TriangleCounts &out, uint64_t signs, uint64_t tries, const TriangleSurvey &survey)
+{
+    out.attractive = (int64_t)(uint32_t)signs; out.repulsive = (int64_t)(signs >> 32);
+    out.dense = both_signs(signs) && tries > survey.most_tries;
+}
+TriangleGraph triangle_graph(const Graph &g, const int32_t *rowptr, const TriangleSurvey &survey)
+{
+    return {rowptr, g.i.get(), g.j.get(), g.c.get(), (size_t)g.m, survey.words.get(), survey.most_tries};
 }
 
 }  // namespace
 
-rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, int k_iters, TriangleCounts &out, bool *done, const std::function<void()> &separated)
+rama_status triangle_survey(Ctx &ctx, const Graph &g, const int32_t *rowptr, bool any, TriangleSurvey &survey)
+{
+    const size_t m = (size_t)g.m;
+    const unsigned n_sums = grid_for(m, kScanTile);
+    survey.most_tries = any ? ~uint64_t(0) : most_tries(m);
+    RAMA_TRY(zeroed<uint64_t>(ctx, 2, survey.words));
+    Buf<uint64_t> signs;
+    if (!g.sign_sums.get()) {
+        RAMA_TRY(signs.alloc(ctx, n_sums));
+        ProfScope ps_(ctx, kernel_name<SignFlags>("k_scan_reduce"), (double)(m * 4));
+        k_scan_reduce<uint64_t, SignFlags><<<n_sums, kBlock, 0, ctx.stream>>>(SignFlags{g.c.get()}, signs.get(), m, (uint64_t *)nullptr, (uint32_t *)nullptr,
+                                                                             (uint64_t *)nullptr, 0, (const uint64_t *)nullptr, 0);
+    }
+    LAUNCH_TRY(ctx, "scan_reduce");
+    {
+        ProfScope ps_(ctx, "k_survey", (double)((size_t)n_sums * 8 + survey_sample(m) * 12));
+        k_survey<<<kSurveyGroups + 1, kSurveyThreads, 0, ctx.stream>>>(triangle_graph(g, rowptr, survey), g.sign_sums.get() ? g.sign_sums.get() : signs.get(),
+                                                                    n_sums, survey.words.get());
+    }
+    LAUNCH_TRY(ctx, "survey");
+    return RAMA_OK;
+}
+
+rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, const TriangleSurvey &survey, int k_iters, TriangleCounts &out, bool *done,
+                          const std::function<void()> &separated)
 {
     *done = false;
-    if (!g.sign_sums.get()) return RAMA_OK;
     Buf<uint32_t> list, counter;
-    Buf<uint64_t> signs;
     RAMA_TRY(list.alloc(ctx, (size_t)kFewSlots));
     RAMA_TRY(zeroed<uint32_t>(ctx, (size_t)kListWords, counter));
-    RAMA_TRY(signs.alloc(ctx, 1));
-    RAMA_TRY(total_signs(ctx, g.sign_sums.get(), (size_t)g.m, signs.get()));
-    RAMA_TRY(run_triangles<kTriList>(ctx, "k_triangles", TriangleGraph{rowptr, g.i.get(), g.j.get(), g.c.get(), (size_t)g.m, signs.get()}, (size_t)g.n,
-                                     list.get(), (uint32_t)kFewTriangles, counter.get(), nullptr, nullptr, nullptr, (double)g.m * 12 + (double)g.n * 4));
+    RAMA_TRY(run_triangles<kTriList>(ctx, "k_triangles", triangle_graph(g, rowptr, survey), (size_t)g.n, list.get(), (uint32_t)kFewTriangles, counter.get(),
+                                     nullptr, nullptr, nullptr, (double)g.m * 12 + (double)g.n * 4));
     separated();
     const uint64_t seq = ++ctx.mail_seq;
     {
         ProfScope ps_(ctx, "k_messages_few", (double)(kFewSlots * 4));
-        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(list.get(), counter.get(), 0, signs.get(), k_iters, g.c.get(), nullptr, nullptr, mailbox(ctx), seq);
+        k_messages_few<<<1, kFewThreads, 0, ctx.stream>>>(list.get(), counter.get(), 0, survey.words.get(), k_iters, g.c.get(), nullptr, nullptr, mailbox(ctx), seq);
     }
     LAUNCH_TRY(ctx, "messages_few");
     RAMA_TRY(wait_mail(ctx, seq));
     const volatile uint64_t *mail = mailbox(ctx);
-    const uint64_t found = mail[1], by_sign = mail[2];
-    if (found > (uint64_t)kFewTriangles) return RAMA_OK;
+    const uint64_t found = mail[1];
+    take_survey(out, mail[2], mail[4], survey);
+    if (out.dense || found > (uint64_t)kFewTriangles) return RAMA_OK;
     out.triangles = (int64_t)found;
-    out.attractive = (int64_t)(uint32_t)by_sign; out.repulsive = (int64_t)(by_sign >> 32);
     if (found) g.sign_sums.reset();      // the costs are new
     *done = true;
     return RAMA_OK;
@@ -479,43 +554,36 @@ rama_status messages_few(Ctx &ctx, const uint32_t *edges, size_t T, int k_iters,
     return RAMA_OK;
 }
 
-rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, Buf<uint32_t> &slots, TriangleCounts &out)
+rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, const TriangleSurvey &survey, Buf<uint32_t> &slots, TriangleCounts &out)
 {
     const size_t m = (size_t)g.m, n = (size_t)g.n;
-    const unsigned nb = triangle_tiles(m, n), nb_signs = grid_for(m, kScanTile);
-    Buf<uint64_t> sums, offs, signs;      // offs: nb places, the number of triangles, the sign counts
+    const unsigned nb = triangle_tiles(m, n);
+    const TriangleGraph tg = triangle_graph(g, rowptr, survey);
+    Buf<uint64_t> sums, offs;      // offs: nb places, the number of triangles
     RAMA_TRY(sums.alloc(ctx, nb));
-    RAMA_TRY(offs.alloc(ctx, (size_t)nb + 2));
-    const TriangleGraph tg{rowptr, g.i.get(), g.j.get(), g.c.get(), m, offs.get() + nb + 1};
+    RAMA_TRY(offs.alloc(ctx, (size_t)nb + 1));
     Buf<uint32_t> kept;
     RAMA_TRY(kept.alloc(ctx, 3 * (size_t)nb * (size_t)tri_room(wide_tiles(m, n) ? kBlock : 64)));
-    if (!g.sign_sums.get()) {
-        RAMA_TRY(signs.alloc(ctx, nb_signs));
-        ProfScope ps_(ctx, kernel_name<SignFlags>("k_scan_reduce"), (double)(m * 4));
-        k_scan_reduce<uint64_t, SignFlags><<<nb_signs, kBlock, 0, ctx.stream>>>(SignFlags{g.c.get()}, signs.get(), m, (uint64_t *)nullptr, (uint32_t *)nullptr,
-                                                                               (uint64_t *)nullptr, 0, (const uint64_t *)nullptr, 0);
-    }
-    LAUNCH_TRY(ctx, "scan_reduce");
-    RAMA_TRY(total_signs(ctx, g.sign_sums.get() ? g.sign_sums.get() : signs.get(), m, offs.get() + nb + 1));
     RAMA_TRY(run_triangles<kTriCount>(ctx, "k_count_cycles<3>", tg, n, kept.get(), 0, nullptr, sums.get(), nullptr, nullptr,
                                       (double)m * 12 + (double)n * 4 + (double)nb * 12));
-    uint64_t back[2];
+    uint64_t back[3];
     if (nb <= kScanMidMax) {
         const uint64_t seq = ++ctx.mail_seq;
         {
             ProfScope ps_(ctx, "k_scan_mid", (double)((size_t)nb * 16));
-            k_scan_mid<uint64_t><<<1, kBlock, 0, ctx.stream>>>(sums.get(), offs.get(), nb, mailbox(ctx), seq, offs.get() + nb + 1, 1);
+            k_scan_mid<uint64_t><<<1, kBlock, 0, ctx.stream>>>(sums.get(), offs.get(), nb, mailbox(ctx), seq, survey.words.get(), 2);
         }
         LAUNCH_TRY(ctx, "scan_mid");
         RAMA_TRY(wait_mail(ctx, seq));
         const volatile uint64_t *mail = mailbox(ctx);
-        back[0] = mail[1]; back[1] = mail[2];
+        for (int k = 0; k < 3; ++k) back[k] = mail[1 + k];
     } else {
         RAMA_TRY((exclusive_scan<uint64_t, PtrInput<uint64_t>>(ctx, PtrInput<uint64_t>{sums.get()}, offs.get(), nb)));
-        RAMA_TRY(read_back(ctx, back, offs.get() + nb, sizeof back));
+        RAMA_TRY(read_back(ctx, back, offs.get() + nb, 8, survey.words.get(), 16));
     }
-    out.attractive = (int64_t)(uint32_t)back[1]; out.repulsive = (int64_t)(back[1] >> 32);
     out.triangles = 0;
+    take_survey(out, back[1], back[2], survey);
+    if (out.dense) return RAMA_OK;
     RAMA_TRY(adjacency_fits(ctx, (uint64_t)out.attractive));
     RAMA_TRY(list_fits(ctx, 0, (int64_t)(back[0] < (uint64_t(1) << 31) ? back[0] : (uint64_t(1) << 31))));
     out.triangles = (int64_t)back[0];

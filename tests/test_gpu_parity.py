@@ -1089,6 +1089,25 @@ def test_rounds_of_many_triangles_behind_none(rama, first, shape):
         assert ms <= 1.5 * ms_lists + 0.1, rounds
 
 
+@pytest.mark.parametrize("kind,n,m", [("clique", 2000, 0.0), ("clique", 2000, 0.02), ("random", 3000, 600000), ("random", 20000, 500000),
+                                      # a sample of all edges and of one edge less; few and many tries in all
+                                      ("random", 1000, 65536), ("random", 1000, 65537), ("random", 3000, 65535), ("random", 1000, 130001)])
+def test_dense_rounds_go_through_the_cycle_lists(rama, kind, n, m):
+    """Where every edge has many neighbours the walk over the edge list would try far more than can be a triangle (33 ms
+    instead of 2 for 2000 nodes, all joined, in clusters of ten with two edges in a hundred turned round)."""
+    from paper_2109_01838_amd import default_params
+    if kind == "clique":
+        rng = np.random.default_rng(5)
+        i, j = np.triu_indices(n, 1)
+        c = np.where(i // 10 == j // 10, 1, -1) * np.where(rng.random(i.size) < m, -1, 1) * (np.abs(rng.normal(1, 0.3, i.size)) + 0.05)
+        i, j, c = i.astype(np.int32), j.astype(np.int32), c.astype(np.float32)
+    else:
+        g = signed(inputs.random_graph(n, m, 13), 14, 0.5)
+        i, j, c = g["i"], g["j"], g["c"]
+    for edges, ms, ms_lists in separation_ms(rama, n, i, j, c, default_params(max_cycle_len_first=3)):
+        assert edges <= 20000 or ms <= 1.5 * ms_lists + 0.1
+
+
 def test_determinism(rama):
     g = CASES["knn_20000"]
     n = g["n_nodes"]
@@ -1418,6 +1437,23 @@ def test_runs_with_a_repeated_pair_hold_no_memory_of_the_attempt(rama):
     assert fresh.find_conflicted_cycles(s ** 3, *d, 3)[0].shape[0] == 0
     assert fresh.workspace_bytes() - before < 31 * m, (fresh.workspace_bytes() - before) / m
     fresh.close()
+
+
+@pytest.mark.parametrize("pos,through_lists", [(0.05, True), (0.075, False)])
+def test_static_workspace_of_a_dense_graph(rama, pos, through_lists):
+    """Where the static workspace has no room for the lists of cycles a dense graph's triangles come from its edges."""
+    from paper_2109_01838_amd import default_params
+    i, j = (x.astype(np.int32) for x in np.triu_indices(724, 1))
+    rng = np.random.default_rng(75)
+    c = ((rng.random(i.size) + 0.05) * np.where(rng.random(i.size) < pos, 1, -1)).astype(np.float32)
+    params = default_params(max_cycle_len_first=3)
+    want = rama.solve(724, i, j, c, params)
+    got = rama.solve(724, i, j, c, params, static=True)
+    assert rama.round_stats()[0]["n_triangles"] == want["n_triangles_first"] > 400000
+    # 70 to 75 bytes per triangle, against 58
+    assert (want["n_triangles_first"] * 75 < 64 << 20) == through_lists and (want["n_triangles_first"] * 70 > 64 << 20) == (not through_lists)
+    assert np.array_equal(np_(got["labels"]), np_(want["labels"]))
+    assert (got["primal"], got["lower_bound"], got["rounds"]) == (want["primal"], want["lower_bound"], want["rounds"])
 
 
 @pytest.mark.parametrize("points", [60800, 60000])

@@ -470,10 +470,15 @@ inline rama_status list_fits(Ctx &ctx, int q, int64_t n)
     return (uint64_t)(q + 3) * (uint64_t)n < (uint64_t(1) << 31) ? RAMA_OK : fail(ctx, RAMA_ERR_CAPACITY, "cycle list reaches 2^31 entries");
 }
 
-// the attractive neighbourhoods, both ends of every edge, are numbered with 31 bits
-inline rama_status adjacency_fits(Ctx &ctx, uint64_t attractive)
+// The attractive neighbourhoods, both ends of every edge, are numbered with 31 bits.  A graph without an attractive or without
+// a repulsive edge has no conflicted cycles and gets none, however large it is; for the others the limit is the same whichever
+// way a round takes, so that it does not hang on what the rounds in front of it found.
+constexpr bool adjacency_refused(uint64_t attractive, uint64_t repulsive) { return repulsive != 0 && 2 * attractive >= (uint64_t(1) << 31); }
+static_assert(!adjacency_refused((uint64_t(1) << 31) - 1, 0) && !adjacency_refused(0, (uint64_t(1) << 31) - 1), "graphs of one sign");
+static_assert(!adjacency_refused((uint64_t(1) << 30) - 1, 1) && adjacency_refused(uint64_t(1) << 30, 1), "graphs of both signs");
+inline rama_status adjacency_fits(Ctx &ctx, uint64_t attractive, uint64_t repulsive)
 {
-    return 2 * attractive < (uint64_t(1) << 31) ? RAMA_OK : fail(ctx, RAMA_ERR_CAPACITY, "positive adjacency reaches 2^31 entries");
+    return adjacency_refused(attractive, repulsive) ? fail(ctx, RAMA_ERR_CAPACITY, "positive adjacency reaches 2^31 entries") : RAMA_OK;
 }
 
 // a1: conflicted cycles of lengths 3..max_len; shortest_only keeps, per repulsive edge, only the

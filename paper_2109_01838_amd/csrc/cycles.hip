@@ -1311,7 +1311,7 @@ rama_status find_cycles(Ctx &ctx, const Graph &g, int max_len, bool shortest_onl
     const uint32_t mp = (uint32_t)signs.total, mr = (uint32_t)(signs.total >> 32);
     out.n_attractive = mp; out.n_repulsive = mr;
     if (mp == 0 || mr == 0) return RAMA_OK;
-    RAMA_TRY(adjacency_fits(ctx, mp));
+    RAMA_TRY(adjacency_fits(ctx, mp, mr));
     Buf<int32_t> pi, pj, ri, rj;
     Buf<uint32_t> lkey, lval;
     RAMA_TRY(pi.alloc(ctx, mp));

@@ -478,10 +478,11 @@ constexpr uint64_t most_tries(size_t m)
 static_assert(most_tries(0) == 0 && most_tries(1) == kManyTries && most_tries(survey_sample(~size_t(0))) == kManyTries, "short lists");
 static_assert(most_tries(size_t(1) << 18) == kDenseTries << 16 && most_tries((size_t(1) << 31) - 1) == kDenseTries << 16, "long lists");
 
-void take_survey(TriangleCounts &out, uint64_t signs, uint64_t tries, const TriangleSurvey &survey)
+rama_status take_survey(Ctx &ctx, TriangleCounts &out, uint64_t signs, uint64_t tries, const TriangleSurvey &survey)
 {
     out.attractive = (int64_t)(uint32_t)signs; out.repulsive = (int64_t)(signs >> 32);
     out.dense = both_signs(signs) && tries > survey.most_tries;
+    return adjacency_fits(ctx, (uint64_t)out.attractive, (uint64_t)out.repulsive);
 }
 TriangleGraph triangle_graph(const Graph &g, const int32_t *rowptr, const TriangleSurvey &survey)
 {
@@ -532,7 +533,7 @@ rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, const Trian
     RAMA_TRY(wait_mail(ctx, seq));
     const volatile uint64_t *mail = mailbox(ctx);
     const uint64_t found = mail[1];
-    take_survey(out, mail[2], mail[4], survey);
+    RAMA_TRY(take_survey(ctx, out, mail[2], mail[4], survey));
     if (out.dense || found > (uint64_t)kFewTriangles) return RAMA_OK;
     out.triangles = (int64_t)found;
     if (found) g.sign_sums.reset();      // the costs are new
@@ -582,9 +583,8 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, cons
         RAMA_TRY(read_back(ctx, back, offs.get() + nb, 8, survey.words.get(), 16));
     }
     out.triangles = 0;
-    take_survey(out, back[1], back[2], survey);
+    RAMA_TRY(take_survey(ctx, out, back[1], back[2], survey));
     if (out.dense) return RAMA_OK;
-    RAMA_TRY(adjacency_fits(ctx, (uint64_t)out.attractive));
     RAMA_TRY(list_fits(ctx, 0, (int64_t)(back[0] < (uint64_t(1) << 31) ? back[0] : (uint64_t(1) << 31))));
     out.triangles = (int64_t)back[0];
     if (out.triangles == 0) return RAMA_OK;

@@ -691,11 +691,8 @@ struct SortTile {
 // instead of 512 for these tiles: 7.22, 11.8, 7.6, 3.00.
 constexpr size_t kSortShort = size_t(3) << 16, kSortMedium = size_t(3) << 20;
 constexpr int kShortTile = 1024, kShortThreads = 512, kMediumTile = 2048, kMediumThreads = 512;
-#ifndef RAMA_RADIX_BITS
-#define RAMA_RADIX_BITS 8
-#endif
 
-constexpr int kRadixBits = RAMA_RADIX_BITS;        // widest digit of a pass
+constexpr int kRadixBits = 8;        // widest digit of a pass
 constexpr int kRadix = 1 << kRadixBits;
 
 // 16 bytes per lane and load: a plain copy with 4-byte accesses tops out near 3.8 TB/s on this
@@ -708,10 +705,10 @@ constexpr int kRadix = 1 << kRadixBits;
 // histogram) were also measured: the scatter kernels ran 25-50 % slower while they waited on the
 // agent-scope status words, the all-digit histogram is bound by its LDS atomics, and the whole
 // solve took 11 % longer than with histogram + scan + scatter per pass.
-// Where one pass over 9.8e7 (64-bit key, value) pairs spends its time (one 8-bit pass, measured with
-// keys built for the purpose): the scatter kernel takes 0.78 ms on uniformly random digits, 0.57 ms
-// when every key has the same digit (the output is then one sequential stream), and 0.47 ms for a
-// 4-bit digit with sequential output -- so roughly 0.37 ms is moving the 24 bytes per key (6.3 TB/s),
+// Where one pass over 9.8e7 (64-bit key, value) pairs spent its time with tiles of four waves (one 8-bit pass, measured with
+// keys built for the purpose; with eight waves it takes 0.56 ms, see SortTile): the scatter kernel took 0.78 ms on uniformly
+// random digits, 0.57 ms when every key has the same digit (the output is then one sequential stream), and 0.47 ms for a
+// 4-bit digit with sequential output -- so roughly 0.37 ms was moving the 24 bytes per key (6.3 TB/s),
 // 0.2 ms the ballot ranking (about 26 us per digit bit) and 0.2 ms the cost of writing 256 separate
 // pieces of ~24 keys per tile.  Computing all rows' ballots before touching the counters, or
 // skipping the ballots for rows with a single digit, changed nothing measurable.
@@ -837,7 +834,7 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, int bits, uint64_t v
 }
 
 // One pass of the sort for one tile: (1) every wave ranks its items x 64 keys by digit with ballots,
-// (2) per-digit prefix over the four waves and over the digits gives each key its place in the
+// (2) per-digit prefix over the tile's waves and over the digits gives each key its place in the
 // tile's digit-sorted order, (3) keys (and values) are staged in LDS in that order, (4) the tile
 // is written out linearly -- neighbouring lanes hold neighbouring keys of the same digit, so the
 // global stores fall into contiguous runs instead of 64 scattered lines per instruction.
@@ -1413,9 +1410,12 @@ rama_status split_sort_tail(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
 
 // A sort of a few hundred thousand keys is launches and nothing else, so it takes one pass over the top bits and one in-LDS
 // sort, a workgroup to a digit, and nobody waits to hear whether every digit's keys fit: the in-LDS sort raises a flag if
-// not, which comes to the host with the count that it waits for behind the sort anyway (sort_and_count_heads), and the keys
-// are sorted by passes then (and so is what comes after them in the same call).  Bits of that pass: digits of kUnseenSegment keys on average, a fifth of what a workgroup holds,
-// or of half as many as it holds at most where eight bits are too few for that.  0: no such sort.
+// not, which comes to the host with the count that it waits for behind the sort anyway (count_heads), and the keys are sorted
+// by passes then.  So is what comes after them in the same call: a node that crowds one digit does so in the contracted graphs
+// as well (contraction to the end of 3.4e5 edges with one row of 40000, ms, switched off | tried at every sort 42.0 | 44.6, of
+// 6e4 edges with one of 20000 3.88 | 4.14, of 8e5 edges with falling degrees 63.5 | 65.6).  Bits of that pass: digits of
+// kUnseenSegment keys on average, a fifth of the 32-bit words that a workgroup holds and three eighths of the 64-bit ones, or
+// of half as many as it holds at most where eight bits are too few for that.  0: no such sort.
 // 1.3e5 64-bit pairs: four launches instead of nine; contraction of a 300x301 long-range grid 2.17 -> 1.95 ms, 128^2 long-range
 // solve 2.36 -> 2.17, 512^2 5.87 -> 5.69, 6-NN graph of 10^6 points 9.95 -> 9.66, 61x97x131 volume 5.80 -> 5.55.  (The split sort,
 // which waits to hear, measured the same as passes from 2^16 keys up to its line at 2^21.)
@@ -1575,8 +1575,6 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
     return RAMA_OK;
 }
 
-// Convenience wrappers working on Buf pairs: after the call `k`/`v` hold the sorted data.
-// `iota`: v comes in unset and stands for the values 0..n-1
 // The other pair of buffers of a sort that may turn out to have failed, and the flag that tells.
 template <typename K, typename V>
 struct SortAgain : SortUnseen {
@@ -1585,6 +1583,8 @@ struct SortAgain : SortUnseen {
     SortUnseen *unseen() { return flag ? this : nullptr; }
 };
 
+// Convenience wrappers working on Buf pairs: after the call `k`/`v` hold the sorted data.
+// `iota`: v comes in unset and stands for the values 0..n-1
 template <typename K, typename V>
 rama_status radix_sort_pairs(Ctx &ctx, Buf<K> &k, Buf<V> &v, size_t n, int total_bits, bool iota = false,
                              Buf<uint32_t> *head_sums = nullptr, uint64_t key_limit = 0, SortAgain<K, V> *again = nullptr)

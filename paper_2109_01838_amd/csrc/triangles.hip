@@ -521,7 +521,7 @@ rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, const Trian
     Buf<uint32_t> list, counter;
     RAMA_TRY(list.alloc(ctx, (size_t)kFewSlots));
     RAMA_TRY(zeroed<uint32_t>(ctx, (size_t)kListWords, counter));
-    RAMA_TRY(run_triangles<kTriList>(ctx, "k_triangles", triangle_graph(g, rowptr, survey), (size_t)g.n, list.get(), (uint32_t)kFewTriangles, counter.get(),
+    RAMA_TRY(run_triangles<kTriList>(ctx, "k_triangles<list>", triangle_graph(g, rowptr, survey), (size_t)g.n, list.get(), (uint32_t)kFewTriangles, counter.get(),
                                      nullptr, nullptr, nullptr, (double)g.m * 12 + (double)g.n * 4));
     separated();
     const uint64_t seq = ++ctx.mail_seq;
@@ -565,7 +565,7 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, cons
     RAMA_TRY(offs.alloc(ctx, (size_t)nb + 1));
     Buf<uint32_t> kept;
     RAMA_TRY(kept.alloc(ctx, 3 * (size_t)nb * (size_t)tri_room(wide_tiles(m, n) ? kBlock : 64)));
-    RAMA_TRY(run_triangles<kTriCount>(ctx, "k_count_cycles<3>", tg, n, kept.get(), 0, nullptr, sums.get(), nullptr, nullptr,
+    RAMA_TRY(run_triangles<kTriCount>(ctx, "k_triangles<count>", tg, n, kept.get(), 0, nullptr, sums.get(), nullptr, nullptr,
                                       (double)m * 12 + (double)n * 4 + (double)nb * 12));
     uint64_t back[3];
     if (nb <= kScanMidMax) {
@@ -589,7 +589,7 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, cons
     out.triangles = (int64_t)back[0];
     if (out.triangles == 0) return RAMA_OK;
     RAMA_TRY(slots.alloc(ctx, 3 * (size_t)back[0]));
-    return run_triangles<kTriFill>(ctx, "k_fill_cycles<3>", tg, n, kept.get(), 0, nullptr, nullptr, offs.get(), slots.get(),
+    return run_triangles<kTriFill>(ctx, "k_triangles<fill>", tg, n, kept.get(), 0, nullptr, nullptr, offs.get(), slots.get(),
                                    (double)nb * 20 + (double)back[0] * 24);
 }
 

@@ -94,8 +94,8 @@ def event_name(rocprof_name):
         # <longest walk, last level closes from the far endpoint>: the timers name the walk length only
         return n.split(",")[0].rstrip(">") + ">"
     if n.startswith("k_triangles<"):
-        # <list | count | fill, edges of a tile>: counting and listing the 3-cycles have the timers of the walks
-        return {"1": "k_count_cycles<3>", "2": "k_fill_cycles<3>"}.get(n[len("k_triangles<")], "k_triangles")
+        # <which pass, edges of a tile>: the timers name the pass
+        return "k_triangles<" + ("list", "count", "fill")[int(n[len("k_triangles<")])] + ">"
     if "<" in n:
         return n.split("<", 1)[0]     # plain template arguments (lengths, flags) are not part of the timers' names
     return n

@@ -1156,9 +1156,14 @@ def test_profile_hooks_and_workspace(rama):
     g = CASES["grid3d_24"]
     rama.profile_enable(True)
     rama.solve(g["n_nodes"], g["i"], g["j"], g["c"])
+    first = {k["name"] for k in rama.profile_get()}
+    rama.set_cycle_search(1)       # rounds that separate triangles only through the lists of cycles as well
+    rama.solve(g["n_nodes"], g["i"], g["j"], g["c"])
+    rama.set_cycle_search(0)
     prof = rama.profile_get()
     rama.profile_enable(False)
     names = {k["name"] for k in prof}
+    assert "k_triangles<count>" in first and not any(n.endswith("_cycles<3>") for n in first)
     assert {"k_triangle_update", "k_edge_update<false>", "k_edge_update<true>", "k_count_cycles<5>", "k_count_cycles<3>", "k_scan_emit<PackCands>", "k_reduce_runs"} <= names
     assert any(n.startswith("k_rs_scatter<") for n in names) and any(n.startswith("k_scan_apply<") for n in names)
     for k in prof:

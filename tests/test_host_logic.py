@@ -58,7 +58,9 @@ def test_profiler_names_map_onto_timer_names():
     assert f("void rama::(anonymous namespace)::k_count_cycles<5>(unsigned long, int const*)") == "k_count_cycles<5>"
     assert f("void rama::(anonymous namespace)::k_count_cycles<5, true>(unsigned long, int const*)") == "k_count_cycles<5>"
     assert f("void rama::(anonymous namespace)::k_fill_cycles<7, false>(unsigned long)") == "k_fill_cycles<7>"
-    assert f("void rama::(anonymous namespace)::k_triangles<1, 64>(rama::(anonymous namespace)::TriangleGraph)") == "k_count_cycles<3>"
+    assert f("void rama::(anonymous namespace)::k_triangles<1, 64>(rama::(anonymous namespace)::TriangleGraph)") == "k_triangles<count>"
+    assert f("void rama::(anonymous namespace)::k_triangles<0, 256>(rama::(anonymous namespace)::TriangleGraph)") == "k_triangles<list>"
+    assert f("void rama::(anonymous namespace)::k_triangles<2, 256>(rama::(anonymous namespace)::TriangleGraph)") == "k_triangles<fill>"
     assert f("void rama::(anonymous namespace)::k_count_cycles_listed<5, true>(unsigned int const*)") == "k_count_cycles_listed"
     assert f("void rama::(anonymous namespace)::k_count_cycles_hash<16, 256>(unsigned long)") == "k_count_cycles_hash"
     assert f("void rama::(anonymous namespace)::k_edge_update<false>(unsigned long)") == "k_edge_update<false>"

@@ -682,8 +682,8 @@ def test_contraction_in_one_workgroup(rama, oracle32, n, m, repeat, ratio, pos):
 
 
 # Both sides of the lines up to which the matching's last workgroup numbers the nodes (2^15 nodes; 8192 at a time) and nobody
-# waits for the number of candidates or of kept edges (2^20 edges); every edge a candidate, none, and too many candidates
-# left for the last workgroup behind the rounds that should bring them there (a star keeps all of them)
+# waits for the number of candidates or of kept edges (2^20 edges, all different: parallel ones are added up before); every
+# edge a candidate, none, and too many candidates left for the last workgroup behind the rounds that should bring them there (a star keeps all of them)
 @pytest.mark.parametrize("n,m,pos", [(32768, 60000, 0.8), (32769, 60000, 0.8), (8193, 40000, 0.5), (20000, 1 << 20, 0.6), (20000, (1 << 20) + 1, 0.6),
                                      (9000, 30000, 1.0), (9000, 30000, 0.0), (70000, 60000, -1.0), (2, 9000, 1.0)])
 def test_contraction_that_waits_for_no_counts(rama, oracle32, n, m, pos):
@@ -694,12 +694,44 @@ def test_contraction_that_waits_for_no_counts(rama, oracle32, n, m, pos):
         c = np.concatenate([np.linspace(1, 2, n - 1), np.linspace(0.1, 0.9, m)]).astype(np.float32)
     else:
         i, j = rng.integers(0, n, m).astype(np.int32), rng.integers(0, n, m).astype(np.int32)
+        if m >= 1 << 20:
+            g = inputs.random_graph(n, m, n + m)
+            i, j = g["i"], g["j"]
+            assert i.size == m and np.unique(i * np.int64(n) + j).size == m
         c = (np.round(rng.random(m) * 8 + 1) / 8 * np.where(rng.random(m) < pos, 1, -1)).astype(np.float32)
     want = oracle32.contract(n, i, j, c, repeat=1)
     got = rama.contract(n, i, j, c, repeat=1)
     assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
     for k in ("i", "j", "c"):
         assert np.array_equal(np_(got[k]), want[k]), k
+
+
+@pytest.mark.parametrize("leaves", [8192, 8193, 20000])
+def test_contraction_that_crowds_a_row(rama, oracle32, leaves):
+    """The input's edges are in order and need no sort; a forest joins 2000 nodes into one, whose row is then as long as what a
+    workgroup sorts in LDS, or longer: nobody knew how many edges would be kept, and they are sorted once more."""
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(leaves)
+    hub, n = 2000, 2000 + leaves + 9000
+    leaf = hub + np.arange(leaves)
+    rest = np.unique(np.sort(rng.integers(hub + 1024, n, (60000, 2)), axis=1), axis=0)      # their rows have digits of their own
+    rest = rest[rest[:, 0] < rest[:, 1]]
+    i = np.concatenate([np.arange(hub - 1), leaf % hub, rest[:, 0]])
+    j = np.concatenate([np.arange(1, hub), leaf, rest[:, 1]])
+    c = np.concatenate([100.0 + rng.random(hub - 1), -rng.random(leaves + rest.shape[0]) - 0.01])
+    order = np.lexsort((j, i))
+    i, j, c = i[order].astype(np.int32), j[order].astype(np.int32), c[order].astype(np.float32)
+    rama.profile_enable(True)
+    got = rama.contract(n, i, j, c, params=default_params(forest_ratio=1.0), repeat=1)
+    passes = sum(x["launches"] for x in rama.profile_get() if x["name"].startswith("k_rs_hist"))
+    rama.profile_enable(False)
+    want = oracle32.contract(n, i, j, c, repeat=1, forest_ratio=1.0)
+    assert got["n_nodes"] == want["n_nodes"] == n - hub + 1 and np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+    row, others = int((np_(got["i"]) == 0).sum()), int((np_(got["i"]) != 0).sum())
+    assert row == leaves and others > 50000
+    assert passes == 1 if leaves <= 8192 else passes > 2
 
 
 @pytest.mark.parametrize("n,m,pos", [(64, 300, 0.7), (90, 2000, 0.9), (128, 8128, 0.75), (128, 8128, 0.97), (1000, 8000, 0.8), (4000, 8200, 0.9),
@@ -774,12 +806,16 @@ def test_canonicalisation_of_large_shuffled_input(rama, oracle32):
 
 # Arrays that one workgroup sorts in LDS, ordered by one comparison of a key's low bits and its place while those fit a word
 # (32 bits of key do not, 31 do), and by passes where a bucket of equal top bits is long (few nodes)
-@pytest.mark.parametrize("n,m", [(1 << 16, 8192), (50000, 8191), (32768, 8192), (20000, 8192), (300, 4097), (70, 8192), (3, 8192), (1 << 20, 4096)])
-def test_sort_inside_one_workgroup(rama, oracle32, n, m):
+@pytest.mark.parametrize("n,m,bits", [(1 << 16, 8192, 32), (50000, 8191, 32), (50000, 8192, 31), (32768, 8192, 30), (20000, 8192, 30), (300, 4097, 18),
+                                      (70, 8192, 14), (3, 8192, 4), (1 << 20, 4096, 40)])
+def test_sort_inside_one_workgroup(rama, oracle32, n, m, bits):
     rng = np.random.default_rng(n + m)
     i = rng.integers(0, n, m).astype(np.int32)
     j = ((i + 1 + rng.integers(0, n - 1, m)) % n).astype(np.int32)
-    i[0], j[0] = 0, n - 1                                               # the widest second field
+    far = min(n - 1, (1 << bits - (n - 1).bit_length()) - 1)            # the widest second field
+    j = np.clip(j, i - far, i + far).astype(np.int32)
+    i[0], j[0] = 0, far
+    assert (n - 1).bit_length() + int(np.abs(i.astype(np.int64) - j).max()).bit_length() == bits
     c = (-np.abs(rng.normal(size=m)) * 10.0 ** rng.integers(-3, 4, m) - 1e-3).astype(np.float32)
     wi, wj, wc = oracle32.canonicalise(n, i, j, c)
     got = rama.contract(n, i, j, c, repeat=1, want_diag=False)
@@ -986,7 +1022,7 @@ def test_solver_variants(rama, oracle32, variant):
 
 
 @pytest.mark.parametrize("kind,n_tri", [("apart", 1), ("apart", 2047), ("apart", 2048), ("apart", 2049), ("fan", 2048), ("fan", 2049),
-                                        ("fan", 6000), ("fans", 1800), ("random", 0), ("grid", 0)])
+                                        ("fan", 6000), ("fans", 1800), ("random", 0), ("wide", 0), ("grid", 0)])
 def test_triangle_rounds_match_the_cycle_lists(rama, kind, n_tri):
     """Rounds that separate triangles only take them from the edge list itself, and one workgroup passes the messages of up
     to 2048 of them; with another cycle search than the default they go through lists of cycles.  Same integers, same sums
@@ -999,6 +1035,9 @@ def test_triangle_rounds_match_the_cycle_lists(rama, kind, n_tri):
         n, i, j, c = g["n_nodes"], g["i"], g["j"], g["c"]
     elif kind == "random":
         g = signed(inputs.random_graph(9000, 60000, 5), 6, 0.8)
+        n, i, j, c = g["n_nodes"], g["i"], g["j"], g["c"]
+    elif kind == "wide":       # few triangles among many edges of few nodes' each: a second round of wide tiles
+        g = signed(inputs.random_graph(200000, 600000, 5), 6, 0.8)
         n, i, j, c = g["n_nodes"], g["i"], g["j"], g["c"]
     else:      # the first round joins the heavy pairs at the end and nothing else; the triangles meet the second round
         if kind == "apart":
@@ -1040,6 +1079,9 @@ def test_triangle_rounds_match_the_cycle_lists(rama, kind, n_tri):
             assert out[0][3][1]["n_triangles"] == n_tri
         if n_tri and kw["max_cycle_len_first"] == 3:
             assert out[0][3][0]["n_triangles"] == n_tri
+        if kind == "wide" and kw["max_cycle_len_first"] == 3:
+            r = out[0][3][1]
+            assert 1 << 18 <= r["n_edges"] <= 6 * r["n_nodes"] and 0 < r["n_triangles"] <= 2048
 
 
 def separation_ms(rama, n, i, j, c, params):

@@ -298,6 +298,7 @@ rama_status solve_impl(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const i
         if (!dual_marked) clock.mark(round, 1);
         R.n_triangles = ntri;
         R.n_edges_aug = g.m;
+        if (R.n_attractive == 0) g.none_attractive = true;      // looked for, and then nothing was separated
         if (round == 1) {
             for (int q = 0; q < kCycleLists; ++q) S.n_cycles_first[q] = R.n_cycles[q];
             if (ran) { lb = lbr; have_lb = true; S.n_triangles_first = ntri; }

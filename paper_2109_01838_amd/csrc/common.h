@@ -448,6 +448,7 @@ struct Graph {
     // optional, left by the kernel that wrote c: per tile of 2048 edges the number of positive (low half) and
     // negative (high half) costs; valid only while c is what that kernel wrote
     Buf<uint64_t> sign_sums;
+    bool none_attractive = false;   // no cost is positive (false: not known)
 };
 
 constexpr int kMaxCycleLen = RAMA_MAX_CYCLE_LEN;

@@ -1290,13 +1290,16 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
 {
     const size_t n = (size_t)g.n;
     if (used_forest) *used_forest = false;
+    n_new = g.n; n_matched = 0;
+    // The rounds of a matching are enqueued without a look at the candidates; where it is known that there are none that costs
+    // 35 us at the end of every solve, and 46 in a contraction of 10^6 repulsive edges, for nothing.
+    if (g.none_attractive && tau >= 0.0f) return RAMA_OK;
     RAMA_TRY(zero_page_recycle(ctx));
     Buf<int32_t> mate;
     Candidates list;
     bool numbered = false;
     if (n <= (size_t)kNumberMax) RAMA_TRY(fmap.alloc(ctx, n > 0 ? n : 1));
     RAMA_TRY(matching(ctx, g, tau, rounds_cap, mate, n_matched, list, fmap.get(), &numbered));
-    n_new = g.n;
     if (n_matched == 0) {
         fmap.reset();
         return RAMA_OK;

@@ -11,11 +11,11 @@ namespace {
 // flags[0]: endpoint out of range or non-finite cost; flags[1]: list is not canonical;
 // flags[2]: largest |i-j| of a valid edge; flags[3]: number of places where the oriented pair (min, max) is smaller
 // than the one before it (few of them: the list is a handful of sorted runs, e.g. one per grid direction); flags[4]: there is
-// a self-loop or a pair equal to the one before it; flags[5..]: the first kMaxRuns - 1 of the places counted in flags[3],
-// in any order.  A workgroup takes one tile of the scan over NotLoop (kScanTile edges) and leaves the number of edges
+// a self-loop or a pair equal to the one before it; flags[5]: there is a positive cost; flags[6..]: the first kMaxRuns - 1 of the
+// places counted in flags[3], in any order.  A workgroup takes one tile of the scan over NotLoop (kScanTile edges) and leaves the number of edges
 // that are no self-loops in tile_sums, so that scan needs no counting pass.
 constexpr int kMaxRuns = 16;
-constexpr int kFlagWords = 5 + kMaxRuns - 1;
+constexpr int kFirstRun = 6, kFlagWords = kFirstRun + kMaxRuns - 1;
 __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const int32_t *i, const int32_t *j,
                                                      const float *c, int32_t *flags, uint32_t *tile_sums)
 {
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const 
         if (e >= m) continue;
         const int32_t a = ea[q], b = eb[q];
         const float w = ew[q];
-        kept += a != b ? 1u : 0u;
+        kept += (a != b ? 1u : 0u) + (w > 0.0f ? 1u << 16 : 0u);      // the positive ones in the upper half
         bool bad = a < 0 || a >= n || b < 0 || b >= n || !(fabsf(w) <= 3.402823466e+38f);
         if (bad) {
             flags[0] = 1;
@@ -55,13 +55,17 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const 
         }
     }
     if (!plain) flags[4] = 1;
+    static_assert(kScanTile < (1 << 16), "two counts in a word");
     kept = block_sum(kept);
     const uint32_t downs = block_sum((uint32_t)__popc(down));
-    if (threadIdx.x == 0) tile_sums[blockIdx.x] = kept;
+    if (threadIdx.x == 0) {
+        tile_sums[blockIdx.x] = kept & 0xffffu;
+        if (kept >> 16 && !*(volatile int32_t *)&flags[5]) flags[5] = 1;
+    }
     if (downs > 0 && downs < (uint32_t)kMaxRuns) {      // uniform
         for (; down; down &= down - 1) {
             const uint32_t at = atomicAdd((uint32_t *)&flags[3], 1u);
-            if (at < (uint32_t)(kMaxRuns - 1)) flags[5 + at] = (int32_t)(base + (size_t)(__ffs((int)down) - 1) * kBlock);
+            if (at < (uint32_t)(kMaxRuns - 1)) flags[kFirstRun + at] = (int32_t)(base + (size_t)(__ffs((int)down) - 1) * kBlock);
         }
     } else if (downs && threadIdx.x == 0) {
         atomicAdd((uint32_t *)&flags[3], downs);        // too many for a list of runs
@@ -440,6 +444,7 @@ rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const
     int32_t hf[kFlagWords];
     RAMA_TRY(read_back(ctx, hf, flags.get(), sizeof hf));
     if (hf[0]) return fail(ctx, RAMA_ERR_BAD_GRAPH, "edge endpoint outside [0,n_nodes) or non-finite cost");
+    out.none_attractive = hf[5] == 0;      // sums of parallel edges are none either
     if (!hf[1]) {  // already canonical: plain copy
         RAMA_TRY(out.i.alloc(ctx, m));
         RAMA_TRY(out.j.alloc(ctx, m));
@@ -451,7 +456,7 @@ rama_status canonicalise(Ctx &ctx, int32_t n, int64_t m, const int32_t *i, const
         return RAMA_OK;
     }
     if (hf[3] < kMaxRuns && !hf[4] && m > (int64_t)LocalSort<uint64_t>::cap) {
-        std::vector<uint32_t> start(hf + 5, hf + 5 + hf[3]);
+        std::vector<uint32_t> start(hf + kFirstRun, hf + kFirstRun + hf[3]);
         start.push_back(0u);
         start.push_back((uint32_t)m);
         std::sort(start.begin(), start.end());

@@ -681,6 +681,35 @@ def test_contraction_in_one_workgroup(rama, oracle32, n, m, repeat, ratio, pos):
     assert np.array_equal(np_(got["diag"]), want["diag"][: got["n_nodes"]])
 
 
+def test_graphs_without_attractive_edges_are_not_matched(rama, oracle32):
+    """No candidates, and it is known: from the input's costs (parallel ones included), or from the separation of the last
+    round.  Self-loops are no candidates either, and a threshold below zero may make some."""
+    from paper_2109_01838_amd import default_params
+    g = signed(inputs.random_graph(5000, 30000, 3, allow_messy=True), 4, 0.0)
+    n, i, j, c = g["n_nodes"], g["i"], g["j"], g["c"]
+    mixed = signed(inputs.random_graph(20000, 60000, 5), 6, 0.5)
+    for kw, tau in ((dict(repeat=1), 0.0), (dict(repeat=0), 0.0), (dict(repeat=1), 0.5), (dict(repeat=1), -0.3)):
+        want = oracle32.contract(n, i, j, c, tau=tau, **kw)
+        rama.profile_enable(True)
+        got = rama.contract(n, i, j, c, params=default_params(contract_threshold=tau), **kw)
+        names = {k["name"] for k in rama.profile_get()}
+        rama.profile_enable(False)
+        assert ("k_handshake_finish" in names) == (tau < 0.0)
+        assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
+        for k in ("i", "j", "c"):
+            assert np.array_equal(np_(got[k]), want[k]), k
+    # a whole solve: its last round on more edges than one workgroup takes
+    rama.profile_enable(True)
+    got = rama.solve(mixed["n_nodes"], mixed["i"], mixed["j"], mixed["c"])
+    launches = sum(k["launches"] for k in rama.profile_get() if k["name"] == "k_handshake_finish")
+    rama.profile_enable(False)
+    want = oracle32.solve(mixed["n_nodes"], mixed["i"], mixed["j"], mixed["c"])
+    assert np.array_equal(np_(got["labels"]), want["labels"]) and got["rounds"] == want["rounds"]
+    last = rama.round_stats()[-1]
+    assert last["n_attractive"] == 0 and last["n_contracted"] == 0 and last["n_edges"] > 8192
+    assert launches == sum(r["n_contracted"] > 0 for r in rama.round_stats())
+
+
 # Both sides of the lines up to which the matching's last workgroup numbers the nodes (2^15 nodes; 8192 at a time) and nobody
 # waits for the number of candidates or of kept edges (2^20 edges, all different: parallel ones are added up before); every
 # edge a candidate, none, and too many candidates left for the last workgroup behind the rounds that should bring them there (a star keeps all of them)

@@ -287,28 +287,40 @@ constexpr int kFewSlots = 3 * kFewTriangles;
 constexpr int kFewRuns = kFewSlots / kFewThreads;              // runs of slots per thread, at most
 constexpr int kFewTable = 8192, kFewEntries = kFewTable / kFewThreads;
 constexpr uint32_t kNoEdge = 0xffffffffu;
+// Slots of an edge in more triangles than this are not compared with each other but put in order by a bit per triangle and the
+// counts of the bits in front, which takes triangles that come in ascending order.  Message passing with one iteration, us,
+// all compared | as it is: one edge in 2048 triangles 505 | 194 (by the kernels for any number 260), in 512 194 | 154, in 256
+// 150 either way.
+constexpr uint32_t kLongRun = 256;
+constexpr int kLongRuns = kFewSlots / ((int)kLongRun + 1), kLongWords = kFewTriangles / 32;
+static_assert(kLongWords == 64, "a wave adds up the words of a run");
 static_assert(kFewSlots < kFewTable && kFewSlots < (1 << 16) && 4 * kFewTriangles <= (1 << 16), "the table keeps room; 16-bit places and slots");
 struct FewShared {
     union {
         struct { uint32_t edge[kFewTable], count[kFewTable]; } table;                   // then: number of the edge, start of its slots
         struct { float share[kFewSlots], msg[4 * kFewTriangles]; } pass;
+        struct { float share[kFewSlots]; uint32_t bits[kLongRuns][kLongWords], before[kLongRuns][kLongWords]; } runs;      // before the first messages
     };
     uint64_t key[kFewTriangles];       // (u,v) << 32 | (u,w), as places in the edge list
     uint32_t act_edge[kFewSlots];
     uint16_t start[kFewSlots + 1];
     uint16_t arrived[kFewSlots], slot[kFewSlots];       // 4 * triangle + which: as they came, in order
-    uint32_t wave[kFewThreads / 64];
+    uint32_t wave[kFewThreads / 64], n_long;
 };
 
-// counter (optional): the number of triangles, which n_triangles is otherwise.  ct (optional) gets their costs in the end.
+// counter (optional): the number of triangles, which come in any order; otherwise there are n_triangles, ascending.  ct (optional)
+// gets their costs in the end.
 // mail[1]: number of triangles, mail[2], mail[4]: the survey (optional), mail[3]: *flag (optional).
-// Nothing is done for more than kFewTriangles.
+// Nothing is done for more than kFewTriangles, nor for triangles in any order with a run longer than kLongRun (mail[1] is then
+// kFewTriangles + 1).
 __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *list, const uint32_t *counter, uint32_t n_triangles, const uint64_t *survey,
                                                               int iters, float *ce, float *ct, const uint32_t *flag, uint64_t *mail, uint64_t seq)
 {
     __shared__ FewShared S;
     const int tid = (int)threadIdx.x, lane = lane_id(), w = tid >> 6;
     const uint32_t T = counter ? *counter : n_triangles;
+    bool left = false;      // uniform
+    if (tid == 0) S.n_long = 0;
     if (T > 0 && T <= (uint32_t)kFewTriangles) {      // uniform
         uint32_t e[kFewPer][3];
         uint32_t h[kFewPer][3];      // place in the table | arrival << 16
@@ -378,22 +390,7 @@ __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *li
                 }
             }
         }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kFewPer; ++q) {
-            const uint32_t t = (uint32_t)(tid + q * kFewThreads);
-            if (t < T) {
-                const uint64_t self = S.key[t];
-#pragma unroll
-                for (int k = 0; k < 3; ++k) {
-                    const uint32_t s0 = S.start[e[q][k]], s1 = S.start[e[q][k] + 1];
-                    uint32_t at = s0;
-                    for (uint32_t p = s0; p < s1; ++p) at += S.key[S.arrived[p] >> 2] < self ? 1u : 0u;
-                    S.slot[at] = (uint16_t)(4u * t + (uint32_t)k);
-                }
-            }
-        }
-        uint32_t edge[kFewRuns], first[kFewRuns], len[kFewRuns];
+        uint32_t edge[kFewRuns], first[kFewRuns], len[kFewRuns], longest = 0;
 #pragma unroll
         for (int r = 0; r < kFewRuns; ++r) {
             const uint32_t a = (uint32_t)(tid + r * kFewThreads);
@@ -402,12 +399,60 @@ __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *li
                 edge[r] = S.act_edge[a];
                 first[r] = S.start[a];
                 len[r] = S.start[a + 1] - first[r];
-                S.pass.share[a] = ce[edge[r]] / (float)len[r];      // the table is no longer looked at
+                longest = max(longest, len[r]);
             }
         }
+        const bool any_long = __syncthreads_or(longest > kLongRun) != 0;      // behind it the table is no longer looked at
+        left = any_long && counter;
+        if (any_long && !left) {
+#pragma unroll
+            for (int r = 0; r < kFewRuns; ++r)
+                if (len[r] > kLongRun) S.arrived[first[r]] = (uint16_t)atomicAdd(&S.n_long, 1u);      // the run's number
+            for (int k = tid; k < kLongRuns * kLongWords; k += kFewThreads) (&S.runs.bits[0][0])[k] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < kFewPer; ++q) {
+                const uint32_t t = (uint32_t)(tid + q * kFewThreads);
+                if (t < T) {
+#pragma unroll
+                    for (int k = 0; k < 3; ++k) {
+                        const uint32_t s0 = S.start[e[q][k]];
+                        if (S.start[e[q][k] + 1] - s0 > kLongRun) atomicOr(&S.runs.bits[S.arrived[s0]][t >> 5], 1u << (t & 31u));
+                    }
+                }
+            }
+            __syncthreads();
+            for (uint32_t r = (uint32_t)w; r < S.n_long; r += kFewThreads / 64) {
+                const uint32_t n = (uint32_t)__popc(S.runs.bits[r][lane]);
+                S.runs.before[r][lane] = wave_inclusive_scan(n) - n;
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int q = 0; q < kFewPer; ++q) {
+            const uint32_t t = (uint32_t)(tid + q * kFewThreads);
+            if (t < T && !left) {
+                const uint64_t self = S.key[t];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const uint32_t s0 = S.start[e[q][k]], s1 = S.start[e[q][k] + 1];
+                    uint32_t at = s0;
+                    if (s1 - s0 > kLongRun) {
+                        const uint32_t r = S.arrived[s0];
+                        at += S.runs.before[r][t >> 5] + (uint32_t)__popc(S.runs.bits[r][t >> 5] & ((1u << (t & 31u)) - 1u));
+                    } else {
+                        for (uint32_t p = s0; p < s1; ++p) at += S.key[S.arrived[p] >> 2] < self ? 1u : 0u;
+                    }
+                    S.slot[at] = (uint16_t)(4u * t + (uint32_t)k);
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < kFewRuns; ++r)
+            if (len[r]) S.pass.share[tid + r * kFewThreads] = ce[edge[r]] / (float)len[r];
         __syncthreads();
         float a[kFewPer] = {}, b[kFewPer] = {}, c[kFewPer] = {};
-        for (int it = 1; it <= iters; ++it) {
+        for (int it = 1; it <= iters && !left; ++it) {
 #pragma unroll
             for (int q = 0; q < kFewPer; ++q) {
                 const uint32_t t = (uint32_t)(tid + q * kFewThreads);
@@ -438,7 +483,7 @@ __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *li
         }
     }
     __syncthreads();
-    if (tid == 0) { mail[1] = (uint64_t)T; mail[2] = survey ? survey[0] : 0ull; mail[3] = flag ? (uint64_t)*flag : 0ull; mail[4] = survey ? survey[1] : 0ull; }
+    if (tid == 0) { mail[1] = left ? (uint64_t)kFewTriangles + 1 : (uint64_t)T; mail[2] = survey ? survey[0] : 0ull; mail[3] = flag ? (uint64_t)*flag : 0ull; mail[4] = survey ? survey[1] : 0ull; }
     mail_send(mail, seq);
 }
 

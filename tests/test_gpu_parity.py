@@ -509,6 +509,49 @@ def test_message_passing_repeated_chords_and_triangles(rama, oracle32, n5, twice
     assert np.array_equal(np_(got["c"]), want["c"])
 
 
+def fan_graph(hubs, n_tri, seed):
+    """n_tri triangles dealt out to `hubs` repulsive edges."""
+    rng = np.random.default_rng(seed)
+    h, x = np.arange(n_tri) % hubs, 2 * hubs + np.arange(n_tri)
+    i = np.concatenate([2 * np.arange(hubs), 2 * h, 2 * h + 1])
+    j = np.concatenate([2 * np.arange(hubs) + 1, x, x])
+    c = rng.uniform(0.5, 1.5, i.size)
+    c[:hubs] *= -1
+    order = np.lexsort((j, i))
+    return 2 * hubs + n_tri, i[order].astype(np.int32), j[order].astype(np.int32), c[order].astype(np.float32)
+
+
+# edges in as many triangles as are compared with each other, and in one more; as many long ones as there can be
+@pytest.mark.parametrize("hubs,n_tri", [(1, 256), (1, 257), (1, 2047), (1, 2048), (1, 2049), (7, 7 * 257), (7, 2048), (8, 2048), (3, 1000)])
+@pytest.mark.parametrize("k", [1, 4])
+def test_message_passing_of_edges_in_many_triangles(rama, oracle32, hubs, n_tri, k):
+    n, i, j, c = fan_graph(hubs, n_tri, n_tri)
+    cyc = oracle32.find_conflicted_cycles(n, i, j, c, 3)
+    cyc = [x[np.random.default_rng(1).permutation(x.shape[0])] for x in cyc]
+    want = oracle32.message_passing(n, i, j, c, cyc, k)
+    got = rama.message_passing(n, i, j, c, cyc, k)
+    assert np.array_equal(np_(got["i"]), want["i"]) and np.array_equal(np_(got["j"]), want["j"])
+    assert np.array_equal(np_(got["c"]), want["c"])
+
+
+def test_one_workgroup_is_no_slower_on_an_edge_in_all_triangles(rama):
+    """2048 triangles are passed by one workgroup, 2049 by the kernels for any number."""
+    import time
+    import torch
+    best = {}
+    for n_tri in (2048, 2049):
+        n, *g = fan_graph(1, n_tri, 3)
+        g = [torch.as_tensor(x).cuda() for x in g]
+        cyc = rama.find_conflicted_cycles(n, *g, max_cycle_len=3)
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            rama.message_passing(n, *g, cyc, 1)
+            torch.cuda.synchronize()
+            best[n_tri] = min(best.get(n_tri, 1.0), time.perf_counter() - t0)
+    assert best[2048] <= 1.3 * best[2049], best
+
+
 def test_message_passing_rejects_foreign_cycles(rama):
     from paper_2109_01838_amd import RamaError, binding
     g = CASES["cfg1"]

@@ -174,7 +174,9 @@ rama_status rama_set_sort_split(rama_ctx *ctx, int64_t n_min, int32_t min_passes
  * (modes 1 and 3), or by sixteen lanes per edge that bisect the longer row for sixteen entries of the shorter
  * one at a time (mode 2).
  * mode 0 (default) chooses from the sizes of the graph: for lengths 4-5 between 2 and 3, for triangles the
- * sixteen-lane search when the attractive rows hold more than 12 entries on average.
+ * sixteen-lane search when the attractive rows hold more than 12 entries on average.  Rounds of a solve that
+ * separate triangles only (max_cycle_len 3, dual_rounds 1) take them from the edge list itself in mode 0, unless
+ * the graph is dense, and from the searches' lists in the others.
  */
 rama_status rama_set_cycle_search(rama_ctx *ctx, int32_t mode);
 

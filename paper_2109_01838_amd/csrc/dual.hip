@@ -940,7 +940,7 @@ rama_status dual_update(Ctx &ctx, const Graph &g, int lists, const int32_t *cons
 
 // A round whose predecessor had this many triangles at most is tried by one workgroup first: their number shrinks from round
 // to round, mostly to a third or a fifth.  A try that succeeds takes 33 to 75 us for separation and messages where the list
-// takes 115 to 160, a try that fails costs 20 to 30.
+// takes 115 to 160, a try that fails costs 20 to 30 at 10^5 edges, and up to the time of the counting pass at 10^7.
 constexpr int64_t kTryFewFrom = 8192;
 
 rama_status triangle_round(Ctx &ctx, Graph &g, int k_iters, int64_t last, bool any, double *lower_bound, TriangleCounts &out,

@@ -509,7 +509,7 @@ def test_message_passing_repeated_chords_and_triangles(rama, oracle32, n5, twice
     assert np.array_equal(np_(got["c"]), want["c"])
 
 
-def fan_graph(hubs, n_tri, seed):
+def triangle_fan(hubs, n_tri, seed):
     """n_tri triangles dealt out to `hubs` repulsive edges."""
     rng = np.random.default_rng(seed)
     h, x = np.arange(n_tri) % hubs, 2 * hubs + np.arange(n_tri)
@@ -525,7 +525,7 @@ def fan_graph(hubs, n_tri, seed):
 @pytest.mark.parametrize("hubs,n_tri", [(1, 256), (1, 257), (1, 2047), (1, 2048), (1, 2049), (7, 7 * 257), (7, 2048), (8, 2048), (3, 1000)])
 @pytest.mark.parametrize("k", [1, 4])
 def test_message_passing_of_edges_in_many_triangles(rama, oracle32, hubs, n_tri, k):
-    n, i, j, c = fan_graph(hubs, n_tri, n_tri)
+    n, i, j, c = triangle_fan(hubs, n_tri, n_tri)
     cyc = oracle32.find_conflicted_cycles(n, i, j, c, 3)
     cyc = [x[np.random.default_rng(1).permutation(x.shape[0])] for x in cyc]
     want = oracle32.message_passing(n, i, j, c, cyc, k)
@@ -540,7 +540,7 @@ def test_one_workgroup_is_no_slower_on_an_edge_in_all_triangles(rama):
     import torch
     best = {}
     for n_tri in (2048, 2049):
-        n, *g = fan_graph(1, n_tri, 3)
+        n, *g = triangle_fan(1, n_tri, 3)
         g = [torch.as_tensor(x).cuda() for x in g]
         cyc = rama.find_conflicted_cycles(n, *g, max_cycle_len=3)
         for _ in range(20):

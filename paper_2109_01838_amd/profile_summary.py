@@ -146,7 +146,7 @@ def report(raw, out):
     stats_txt = capture(stats, os.path.join(raw, "prof_bench", "bench_kernel_stats.csv"), n_solves, 26)
     with open(os.path.join(out, "cfg5_solve_kernel_trace.txt"), "w") as f:
         f.write(f"""# rocprofv3 kernel-trace summary: bench.py default run ({d['config']['workload']}, {d['config']['n_edges']} edges; 1 warm-up + 1 all-kernel-timed + 3 timed solves = {n_solves} solves)
-# command (on the GPU box; $REPO = repository root, $OUT = any scratch directory):
+# command (on the machine with the GPU; $REPO = repository root, $OUT = any scratch directory):
 #   cd /tmp && export TMPDIR=/tmp && rocprofv3 --kernel-trace --stats -d $OUT/prof_bench -o bench --output-format csv -- python3 $REPO/bench.py --other-workloads '' --cpu-config none > $OUT/bench_rocprof.log
 # condensed with: python -m paper_2109_01838_amd.profile_summary report $OUT profiles
 # bench.py's own HIP-event figures for the dominant kernel in the same run:
@@ -164,7 +164,7 @@ def report(raw, out):
     traffic_json(fetch, write, fs, ws, os.path.join(out, "cfg5_solve_hbm_traffic.json"))
     with open(os.path.join(out, "cfg5_solve_hbm_traffic.txt"), "w") as f:
         f.write(f"""# rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (KiB per dispatch), two separate runs, {d['config']['workload']}, one solve each
-# commands (on the GPU box; $REPO = repository root, $OUT = any scratch directory):
+# commands (on the machine with the GPU; $REPO = repository root, $OUT = any scratch directory):
 #   rocprofv3 --pmc FETCH_SIZE -d $OUT/pmc_fetch -o fetch --output-format csv -- python3 $REPO/bench.py --steps 1 --warmup 0 --no-profile --other-workloads '' --cpu-config none --copy-calibration
 #   rocprofv3 --pmc WRITE_SIZE -d $OUT/pmc_write -o write --output-format csv -- python3 $REPO/bench.py --steps 1 --warmup 0 --no-profile --other-workloads '' --cpu-config none --copy-calibration
 # condensed with: python -m paper_2109_01838_amd.profile_summary report $OUT profiles
@@ -189,7 +189,7 @@ def report_workload(raw, out, workload):
     stats_txt = capture(stats, os.path.join(raw, f"prof_{workload}", f"{workload}_kernel_stats.csv"), n_solves, 32)
     with open(os.path.join(out, f"{workload}_solve_kernel_trace.txt"), "w") as f:
         f.write(f"""# rocprofv3 kernel-trace summary: bench.py on {d['config']['workload']} ({d['config']['n_edges']} edges; 1 warm-up + 1 all-kernel-timed + 3 timed solves = {n_solves} solves)
-# command (on the GPU box; $REPO = repository root, $OUT = any scratch directory):
+# command (on the machine with the GPU; $REPO = repository root, $OUT = any scratch directory):
 #   cd /tmp && export TMPDIR=/tmp && rocprofv3 --kernel-trace --stats -d $OUT/prof_{workload} -o {workload} --output-format csv -- python3 $REPO/bench.py --workload {workload} --other-workloads '' --cpu-config none > $OUT/bench_{workload}_rocprof.log
 # condensed with: python -m paper_2109_01838_amd.profile_summary report-workload $OUT profiles {workload}
 # bench.py in the same run: ms_per_step {d['ms_per_step']:.2f} (under the profiler), rounds {d['rounds']}, cycles found in round 1 {d['n_cycles_first'][:3]}

@@ -753,6 +753,26 @@ def test_graphs_without_attractive_edges_are_not_matched(rama, oracle32):
     assert launches == sum(r["n_contracted"] > 0 for r in rama.round_stats())
 
 
+# rows of the candidate list that fill a wave, span two, or are broken up by edges that are no candidates; the costs leave the
+# best candidate of a row at its front, at its end and in the middle
+@pytest.mark.parametrize("degree", [1, 2, 3, 4, 33, 63, 64, 65, 127, 128, 300])
+@pytest.mark.parametrize("pos", [1.0, 0.6])
+@pytest.mark.parametrize("slope", [-1, 0, 1])
+def test_rows_of_the_first_proposals(rama, oracle32, degree, pos, slope):
+    rows = 9000 // degree + 3
+    rng = np.random.default_rng(degree)
+    i = np.repeat(np.arange(rows), degree)
+    j = rows + rng.integers(0, 4 * rows, i.size)
+    c = 1.0 + slope * np.tile(np.arange(degree), rows) / (2.0 * degree) + (0.0 if slope else 1.0) * rng.random(i.size)
+    c = (c * np.where(rng.random(i.size) < pos, 1, -1)).astype(np.float32)
+    n = 5 * rows
+    want = oracle32.contract(n, i.astype(np.int32), j.astype(np.int32), c, repeat=1)
+    got = rama.contract(n, i.astype(np.int32), j.astype(np.int32), c, repeat=1)
+    assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+
+
 # Both sides of the lines up to which the matching's last workgroup numbers the nodes (2^15 nodes; 8192 at a time) and nobody
 # waits for the number of candidates or of kept edges (2^20 edges, all different: parallel ones are added up before); every
 # edge a candidate, none, and too many candidates left for the last workgroup behind the rounds that should bring them there (a star keeps all of them)

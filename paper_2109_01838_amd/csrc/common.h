@@ -261,7 +261,7 @@ struct rama_ctx {
     void *pinned = nullptr;  // small pinned host block for scalar read-backs
     static constexpr size_t kPinnedBytes = 4096;
     // Scalars the host waits for (counts that size the next launch) travel through a mailbox in pinned host
-    // memory: the producing kernel stores the values, fences, and stores the running message number last; the
+    // memory: the producing kernel stores the values, waits for them, and stores the running message number last; the
     // host polls that number for a bounded time instead of going through a stream synchronisation (~9 us
     // instead of ~17 us per round trip measured), and falls back to the synchronisation when the kernels in
     // front of the message take longer.

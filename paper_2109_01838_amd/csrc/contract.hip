@@ -228,27 +228,38 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
         }
 }
 
-// The rest of the matching for a list that one workgroup holds: candidates in registers, a handshake between three barriers
-// (about 4 us) instead of a launch, and the host hears of it once.  A longer list is left as it is.  On entry the list's
-// proposals stand in `best`.  Contraction of a 300x301 long-range grid 2.53 -> 2.41 ms, 61x97x131 solve 8.53 -> 8.38, 512^2
-// 8.05 -> 7.95.
+// The rest of the matching for a list that one workgroup holds, and the host hears of it once; a longer list is left as it
+// is.  Candidates stay in registers, the nodes' rank words in LDS: by the node's number where the graph has at most
+// kFinishDirect nodes, else by its place in a hash table, which lists of half the length fill to four fifths at most.
+// A handshake is three barriers that wait for LDS only, about 0.8 us (4 with the words in memory, whose four round trips a
+// barrier waits for each).
 // With the matching complete, the new nodes of a graph of up to kNumberMax nodes are numbered here as well (fmap; see
-// NumberPairsEmit), and the message to the host goes out from here: mail[1] length of the first list | candidates left << 32,
-// mail[2]: pairs made here, then the counters of the rounds enqueued with this launch, two words each.
-constexpr int kFinishThreads = 1024, kFinishItems = 8;
-constexpr uint32_t kFinishMax = kFinishThreads * kFinishItems;
-constexpr int kNumberMax = 1 << 15, kNumberItems = 8;
+// NumberPairsEmit): all mates are read at once, and one scan numbers them (four turns of reading, scanning and storing took
+// 22 us for 26000 nodes).  The message to the host goes out in front of that: mail[1] length of the first list | candidates left
+// << 32, mail[2]: pairs made here, then the counters of the rounds enqueued with this launch, two words each.
+constexpr int kFinishThreads = 1024, kFinishItems = 8, kFinishWaves = kFinishThreads / 64;
+constexpr int kFinishDirect = 1 << 14, kFinishSlots = 10240;
+constexpr uint32_t kFinishMax = kFinishThreads * kFinishItems, kFinishMaxHashed = kFinishMax / 2;
+static_assert(2 * kFinishMaxHashed <= kFinishSlots / 5 * 4 && kFinishSlots * 12 <= kFinishDirect * 8, "the table keeps room and takes the words' place");
+__host__ __device__ constexpr uint32_t finish_max(int n_nodes) { return n_nodes <= kFinishDirect ? kFinishMax : kFinishMaxHashed; }
+constexpr int kNumberMax = 1 << 15, kNumberRows = kNumberMax / kFinishThreads;
 __global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint32_t *n_first, const uint32_t *n_list, Cands a, int32_t *mate,
-                                                                     unsigned long long *best, int rounds_left, int n_nodes, int32_t *fmap,
+                                                                     int rounds_left, int n_nodes, int32_t *fmap,
                                                                      const uint32_t *counters, int n_counters, uint64_t *mail, uint64_t seq)
 {
-    __shared__ uint32_t s_left, s_pairs, s_wave[kFinishThreads / 64];
+    constexpr unsigned long long kMatched = ~0ull;      // in a node's word: no candidate's rank
+    __shared__ unsigned long long s_best[kFinishDirect];
+    __shared__ uint32_t s_left, s_pairs, s_any[2], s_wave[kFinishWaves];
     const uint32_t n = *n_list, tid = threadIdx.x;
-    if (tid == 0) { s_left = 0u; s_pairs = 0u; }
-    for (int k = (int)tid; k < n_counters; k += kFinishThreads) reinterpret_cast<uint32_t *>(mail + 3)[k] = counters[k];
-    if (n > kFinishMax) {      // uniform
-        if (tid == 0) { mail[1] = (uint64_t)*n_first | (uint64_t)n << 32; mail[2] = 0ull; }
-        mail_send(mail, seq);
+    const int lane = lane_id(), w = (int)(tid >> 6);
+    if (tid == 0) { s_left = 0u; s_pairs = 0u; s_any[0] = 0u; s_any[1] = 0u; }
+    auto tell = [&](uint32_t left, uint32_t made) {      // the first wave
+        for (int k = lane; k < n_counters; k += 64) mail_put(reinterpret_cast<uint32_t *>(mail + 3) + k, counters[k]);
+        if (lane == 0) { mail_put(mail + 1, (uint64_t)*n_first | (uint64_t)left << 32); mail_put(mail + 2, (uint64_t)made); }
+        mail_send_wave(mail, seq);
+    };
+    if (n > finish_max(n_nodes)) {      // uniform
+        if (w == 0) tell(n, 0u);
         return;
     }
     int32_t u[kFinishItems], v[kFinishItems];
@@ -260,61 +271,96 @@ __global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint3
         u[q] = 0; v[q] = 0; r[q] = 0ull;
         if (k < n) { u[q] = a.u[k]; v[q] = a.v[k]; r[q] = a.r[k]; alive |= 1u << q; }
     }
+    const bool direct = n_nodes <= kFinishDirect;
+    int32_t *s_node = reinterpret_cast<int32_t *>(s_best + kFinishSlots);
+    for (int k = (int)tid; k < (direct ? n_nodes : kFinishSlots); k += kFinishThreads) {
+        s_best[k] = 0ull;
+        if (!direct) s_node[k] = -1;
+    }
+    lds_barrier();
+    auto place_of = [&](int32_t node) {
+        if (direct) return node;
+        uint32_t h = (uint32_t)(((uint64_t)((uint32_t)node * 0x9E3779B1u) * (uint32_t)kFinishSlots) >> 32);
+        for (;;) {      // the table is never full: the walk ends
+            const int32_t old = atomicCAS(&s_node[h], -1, node);
+            if (old == -1 || old == node) return (int32_t)h;
+            h = h + 1 == (uint32_t)kFinishSlots ? 0u : h + 1;
+        }
+    };
+    int32_t su[kFinishItems], sv[kFinishItems];
+#pragma unroll
+    for (int q = 0; q < kFinishItems; ++q) {
+        su[q] = 0; sv[q] = 0;
+        if (alive & (1u << q)) {
+            su[q] = place_of(u[q]); sv[q] = place_of(v[q]);
+            atomicMax(&s_best[su[q]], r[q]); atomicMax(&s_best[sv[q]], r[q]);
+        }
+    }
+    if (__ballot(alive != 0u) && lane == 0) s_any[0] = 1u;
     for (int round = 0; round < rounds_left; ++round) {
-        if (!__syncthreads_or(alive != 0u)) break;
+        lds_barrier();
+        if (!s_any[round & 1]) break;      // uniform
+        if (tid == 0) s_any[(round + 1) & 1] = 0u;
 #pragma unroll
         for (int q = 0; q < kFinishItems; ++q)
-            if ((alive & (1u << q)) && load_past_cache(&best[u[q]]) == r[q] && load_past_cache(&best[v[q]]) == r[q]) {
+            if ((alive & (1u << q)) && s_best[su[q]] == r[q] && s_best[sv[q]] == r[q]) {
                 mate[u[q]] = v[q]; mate[v[q]] = u[q];
+                s_best[su[q]] = kMatched; s_best[sv[q]] = kMatched;      // whoever reads it in this step has lost either way
                 ++pairs;
             }
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
         for (int q = 0; q < kFinishItems; ++q)
             if (alive & (1u << q)) {
-                if (mate[u[q]] >= 0 || mate[v[q]] >= 0) alive &= ~(1u << q);
-                else { best[u[q]] = 0ull; best[v[q]] = 0ull; }
+                if (s_best[su[q]] == kMatched || s_best[sv[q]] == kMatched) alive &= ~(1u << q);
+                else { s_best[su[q]] = 0ull; s_best[sv[q]] = 0ull; }
             }
-        __syncthreads();
+        if (__ballot(alive != 0u) && lane == 0) s_any[(round + 1) & 1] = 1u;
+        lds_barrier();
 #pragma unroll
         for (int q = 0; q < kFinishItems; ++q)
-            if (alive & (1u << q)) { atomicMax(&best[u[q]], r[q]); atomicMax(&best[v[q]], r[q]); }
+            if (alive & (1u << q)) { atomicMax(&s_best[su[q]], r[q]); atomicMax(&s_best[sv[q]], r[q]); }
     }
-    __syncthreads();
     const uint32_t n_left = wave_sum((uint32_t)__popc(alive)), n_pairs = wave_sum(pairs);
-    if (lane_id() == 0) { atomicAdd(&s_left, n_left); atomicAdd(&s_pairs, n_pairs); }
-    __syncthreads();
-    if (tid == 0) { mail[1] = (uint64_t)*n_first | (uint64_t)s_left << 32; mail[2] = (uint64_t)s_pairs; }
-    uint32_t done = 0;      // nodes numbered so far
-    for (int base = 0; fmap && base < n_nodes; base += kFinishThreads * kNumberItems) {      // uniform
-        const int v0 = base + (int)tid * kNumberItems;
-        int32_t w[kNumberItems];
-        uint32_t roots = 0;
+    if (lane == 0) { atomicAdd(&s_left, n_left); atomicAdd(&s_pairs, n_pairs); }
+    __syncthreads();      // the mates as well
+    if (w == 0) tell(s_left, s_pairs);      // the host goes on; what it enqueues waits for the numbers
+    if (fmap) {      // uniform; a wave takes `rows` rows of 64 nodes
+        const int rows = (n_nodes + kFinishThreads - 1) / kFinishThreads, base = w * rows * 64 + lane;
+        const uint64_t below = (1ull << lane) - 1ull;
+        int32_t m[kNumberRows];
+        uint32_t roots = 0, mine = 0;      // bit q: the node of row q
 #pragma unroll
-        for (int q = 0; q < kNumberItems; ++q) w[q] = v0 + q < n_nodes ? mate[v0 + q] : 0;
-#pragma unroll
-        for (int q = 0; q < kNumberItems; ++q) roots += v0 + q < n_nodes && (w[q] < 0 || w[q] > v0 + q) ? 1u : 0u;
-        const uint32_t inc = wave_inclusive_scan(roots);
-        if (lane_id() == 63) s_wave[tid >> 6] = inc;
-        __syncthreads();
-        uint32_t number = done + inc - roots, all = 0;
-#pragma unroll
-        for (int k = 0; k < kFinishThreads / 64; ++k) {
-            const uint32_t x = s_wave[k];
-            number += k < (int)(tid >> 6) ? x : 0u;
-            all += x;
-        }
-#pragma unroll
-        for (int q = 0; q < kNumberItems; ++q)
-            if (v0 + q < n_nodes && (w[q] < 0 || w[q] > v0 + q)) {
-                fmap[v0 + q] = (int32_t)number;
-                if (w[q] >= 0) fmap[w[q]] = (int32_t)number;
-                ++number;
+        for (int q = 0; q < kNumberRows; ++q)
+            if (q < rows) {      // uniform, as below: a workgroup that works alone is bound by the instructions it issues
+                const int node = base + q * 64;
+                m[q] = node < n_nodes ? mate[node] : 0;
             }
-        done += all;
+#pragma unroll
+        for (int q = 0; q < kNumberRows; ++q)
+            if (q < rows) {
+                const int node = base + q * 64;
+                const bool root = node < n_nodes && (m[q] < 0 || m[q] > node);
+                roots |= root ? 1u << q : 0u;
+                mine += (uint32_t)__popcll(__ballot(root));
+            }
+        if (lane == 0) s_wave[w] = mine;
         __syncthreads();
+        uint32_t number = 0;
+#pragma unroll
+        for (int k = 0; k < kFinishWaves - 1; ++k) number += k < w ? s_wave[k] : 0u;
+#pragma unroll
+        for (int q = 0; q < kNumberRows; ++q)
+            if (q < rows) {
+                const uint64_t row = __ballot((roots >> q) & 1u);
+                if ((roots >> q) & 1u) {
+                    const int32_t x = (int32_t)(number + (uint32_t)__popcll(row & below));
+                    fmap[base + q * 64] = x;
+                    if (m[q] >= 0) fmap[m[q]] = x;
+                }
+                number += (uint32_t)__popcll(row);
+            }
     }
-    mail_send(mail, seq);
 }
 
 // The components of a matching are its pairs, represented by the smaller node: new numbers straight from the mates.
@@ -852,7 +898,7 @@ __global__ __launch_bounds__(kForestThreads) void k_forest_components(uint32_t n
         for (int32_t x = load_past_cache(&rep[p]); x != p; x = load_past_cache(&rep[p])) p = x;
         rep[u] = p; rep[v] = p;
     }
-    if (tid == 0) mail[1] = (uint64_t)s_kept;
+    if (tid == 0) mail_put(mail + 1, (uint64_t)s_kept);
     mail_send(mail, seq);
 }
 
@@ -931,11 +977,12 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
     // kernel that finishes it, and the counts come back together; rounds behind one that emptied the list find a zero count
     // and do nothing.
     std::vector<uint32_t> back((size_t)(2 * cap + 2), 0u);
+    const uint32_t last_max = finish_max(g.n);
     for (int r = 0; r < cap && na > 0;) {
         const bool finish = na <= kMatchBatchMax;
         int batch = finish ? 0 : 1;
         if (finish)
-            for (uint32_t left = blind ? na / 2 + 1 : na; (left > kFinishMax || (blind && batch == 0 && na > kFinishMax)) && batch < cap - r; left /= 2) ++batch;
+            for (uint32_t left = blind ? na / 2 + 1 : na; (left > last_max || (blind && batch == 0 && na > last_max)) && batch < cap - r; left /= 2) ++batch;
         auto n_list = [&](int round) { return round == 0 ? cand.offs.get() + cand.nb : counters.get() + 2 * (round - 1); };
         for (int b = 0; b < batch; ++b, ++r) {
             uint32_t *count = counters.get() + 2 * r;
@@ -968,7 +1015,7 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
         const uint64_t seq = ++ctx.mail_seq;
         {
             ProfScope ps_(ctx, "k_handshake_finish", (double)(kFinishMax * 40));
-            k_handshake_finish<<<1, kFinishThreads, 0, ctx.stream>>>(n_list(0), n_list(r), cur, mate.get(), best.get(), cap - r, g.n, fmap,
+            k_handshake_finish<<<1, kFinishThreads, 0, ctx.stream>>>(n_list(0), n_list(r), cur, mate.get(), cap - r, g.n, fmap,
                                                                     counters.get() + 2 * (r - batch), 2 * batch,
                                                                     mailbox(ctx), seq);
         }
@@ -982,7 +1029,7 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
         for (int b = 0; b < batch; ++b) n_matched += (int64_t)(mail[3 + b] >> 32);
         blind = false;
         na = left;
-        if (left <= kFinishMax) {      // the rest was worked off, or the cap was reached
+        if (left <= last_max) {      // the rest was worked off, or the cap was reached
             *numbered = fmap != nullptr;
             break;
         }

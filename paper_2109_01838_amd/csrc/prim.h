@@ -43,6 +43,15 @@ inline rama_status zero_page_recycle(Ctx &ctx)
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 
+// A barrier that orders what the workgroup does in LDS and does not wait for its loads and stores elsewhere (__syncthreads
+// does: up to a microsecond where any are under way).
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // Consecutive workgroups of a launch go to the eight XCDs in turn, each with an L2 of its own.  A kernel whose
 // neighbouring workgroups gather from the same stretch of an array then fetches that stretch into all eight L2s.
 // Launched with xcd_grid(nb) workgroups and numbering its work by xcd_block(), a kernel gives every XCD one
@@ -132,15 +141,23 @@ __device__ __forceinline__ T block_sum(T v)
 // ------------------------------------------------------------------------------------------
 // scalars for the host: the mailbox
 // ------------------------------------------------------------------------------------------
-// closes message `seq`: everything this workgroup stored into mail[1..] before is visible to the host first
+// The words of a message go to the host past the caches, and its number follows when they have arrived there: every wave
+// waits for its own words.  A fence for the whole system would write the L2 back as well, of which the host sees nothing: with
+// one in front of the number and one behind it a message of sixteen waves took 4 us.
+template <typename T>
+__device__ __forceinline__ void mail_put(T *word, T v) { __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+// closes message `seq`, all of whose words the calling wave has put into mail[1..]
+__device__ __forceinline__ void mail_send_wave(uint64_t *mail, uint64_t seq)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (lane_id() == 0) mail_put(mail, seq);
+}
+// closes message `seq`: everything this workgroup put into mail[1..] before is visible to the host first
 __device__ __forceinline__ void mail_send(uint64_t *mail, uint64_t seq)
 {
-    __threadfence_system();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-        *(volatile uint64_t *)mail = seq;
-        __threadfence_system();
-    }
+    if (threadIdx.x == 0) mail_put(mail, seq);
 }
 
 // `words` 4-byte words from device memory into the mailbox, and `more` from another place behind them
@@ -148,8 +165,8 @@ static __global__ __launch_bounds__(kBlock) void k_publish(const uint32_t *src, 
                                                            uint64_t seq)
 {
     uint32_t *dst = (uint32_t *)(mail + 1);
-    for (unsigned k = threadIdx.x; k < words; k += kBlock) dst[k] = src[k];
-    for (unsigned k = threadIdx.x; k < more; k += kBlock) dst[words + k] = src2[k];
+    for (unsigned k = threadIdx.x; k < words; k += kBlock) mail_put(dst + k, src[k]);
+    for (unsigned k = threadIdx.x; k < more; k += kBlock) mail_put(dst + words + k, src2[k]);
     mail_send(mail, seq);
 }
 
@@ -268,8 +285,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_reduce(F f, TO *block_sums, siz
     if (threadIdx.x == 0) *ticket = 0u;
     if (mail) {
         if (threadIdx.x == 0) {
-            mail[1] = (uint64_t)total;
-            for (int e = 0; e < extra; ++e) mail[2 + e] = (uint64_t)words[e];
+            mail_put(mail + 1, (uint64_t)total);
+            for (int e = 0; e < extra; ++e) mail_put(mail + 2 + e, (uint64_t)words[e]);
         }
         mail_send(mail, seq);
     }
@@ -283,8 +300,8 @@ __global__ __launch_bounds__(kBlock) void k_scan_mid(const TO *in, TO *out, unsi
     const TO total = scan_tile_sums<TO, false>(in, out, nb);
     if (mail) {
         if (threadIdx.x == 0) {
-            mail[1] = (uint64_t)total;
-            for (int e = 0; e < extra; ++e) mail[2 + e] = (uint64_t)words[e];
+            mail_put(mail + 1, (uint64_t)total);
+            for (int e = 0; e < extra; ++e) mail_put(mail + 2 + e, (uint64_t)words[e]);
         }
         mail_send(mail, seq);
     }

@@ -630,12 +630,12 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_rounds(TailArgs A)
         }
         if (tid == 0) {
             const uint64_t t3 = wall_clock64();
-            rec[0] = (uint64_t)(uint32_t)n_old | (uint64_t)(uint32_t)m_old << 32;
-            rec[1] = (uint64_t)n_attractive | (uint64_t)n_repulsive << 32;
-            rec[2] = (uint64_t)T | (uint64_t)(forest ? 1u : 0u) << 32;
-            rec[3] = (uint64_t)ns;
-            rec[4] = (uint64_t)(uint32_t)(t1 - t0) | (uint64_t)(uint32_t)(t2 - t1) << 32;
-            rec[5] = (uint64_t)(t3 - t2);
+            mail_put(rec + 0, (uint64_t)(uint32_t)n_old | (uint64_t)(uint32_t)m_old << 32);
+            mail_put(rec + 1, (uint64_t)n_attractive | (uint64_t)n_repulsive << 32);
+            mail_put(rec + 2, (uint64_t)T | (uint64_t)(forest ? 1u : 0u) << 32);
+            mail_put(rec + 3, (uint64_t)ns);
+            mail_put(rec + 4, (uint64_t)(uint32_t)(t1 - t0) | (uint64_t)(uint32_t)(t2 - t1) << 32);
+            mail_put(rec + 5, (uint64_t)(t3 - t2));
         }
         rec += kTailRecord;
         ++rounds;
@@ -647,8 +647,8 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_rounds(TailArgs A)
         A.co[e] = S.cost[e];
     }
     if (tid == 0) {
-        A.mail[1] = (uint64_t)status | (uint64_t)rounds << 32;
-        A.mail[2] = (uint64_t)(uint32_t)n | (uint64_t)(uint32_t)m << 32;
+        mail_put(A.mail + 1, (uint64_t)status | (uint64_t)rounds << 32);
+        mail_put(A.mail + 2, (uint64_t)(uint32_t)n | (uint64_t)(uint32_t)m << 32);
     }
     mail_send(A.mail, A.seq);
 }

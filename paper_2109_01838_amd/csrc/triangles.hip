@@ -483,7 +483,12 @@ __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *li
         }
     }
     __syncthreads();
-    if (tid == 0) { mail[1] = left ? (uint64_t)kFewTriangles + 1 : (uint64_t)T; mail[2] = survey ? survey[0] : 0ull; mail[3] = flag ? (uint64_t)*flag : 0ull; mail[4] = survey ? survey[1] : 0ull; }
+    if (tid == 0) {
+        mail_put(mail + 1, left ? (uint64_t)kFewTriangles + 1 : (uint64_t)T);
+        mail_put(mail + 2, survey ? survey[0] : (uint64_t)0);
+        mail_put(mail + 3, flag ? (uint64_t)*flag : (uint64_t)0);
+        mail_put(mail + 4, survey ? survey[1] : (uint64_t)0);
+    }
     mail_send(mail, seq);
 }
 

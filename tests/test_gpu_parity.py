@@ -773,6 +773,34 @@ def test_rows_of_the_first_proposals(rama, oracle32, degree, pos, slope):
         assert np.array_equal(np_(got[k]), want[k]), k
 
 
+# The last workgroup of a matching: rank words by node (up to 16384) and by hash (twice as many places to find for lists of up
+# to 4096), full lists of edges without a common node, paths of ascending costs (a pair a handshake, more of them than the cap
+# allows), nodes that fill their last row of 64 or begin one, both sides of the 32768 it numbers
+@pytest.mark.parametrize("n,m,kind", [(2, 1, "path"), (65, 40, "path"), (1023, 1022, "path"), (1024, 1023, "path"), (1025, 1024, "path"),
+                                      (16384, 8192, "pairs"), (16384, 8192, "path"), (16385, 4096, "pairs"), (16385, 4096, "path"),
+                                      (16385, 4097, "path"), (32768, 4096, "pairs"), (32768, 4095, "random"), (32769, 4096, "random"),
+                                      (16384, 9000, "random"), (16385, 9000, "random"), (300, 8192, "random"), (200000, 4096, "spread")])
+@pytest.mark.parametrize("cap", [32, 3])
+def test_last_workgroup_of_a_matching(rama, oracle32, n, m, kind, cap):
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(n + m)
+    if kind == "path":
+        i, j, c = np.arange(m), np.arange(1, m + 1), np.linspace(1, 2, m)
+    elif kind == "pairs":
+        i, j, c = 2 * np.arange(m), 2 * np.arange(m) + 1, 1 + rng.random(m)
+    else:
+        i, j = rng.integers(0, n, m), rng.integers(0, n, m)
+        c = np.round(8 * rng.random(m) + 1) / 8 if kind == "random" else 1 + rng.random(m)
+        if kind == "spread":      # a node of few in many: the table's places are far apart
+            i = i // 97 * 97
+    i, j, c = i.astype(np.int32), j.astype(np.int32), c.astype(np.float32)
+    want = oracle32.contract(n, i, j, c, repeat=1, rounds_cap=cap, forest_ratio=0.0)
+    got = rama.contract(n, i, j, c, params=default_params(matching_rounds_cap=cap, forest_ratio=0.0), repeat=1)
+    assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+
+
 # Both sides of the lines up to which the matching's last workgroup numbers the nodes (2^15 nodes; 8192 at a time) and nobody
 # waits for the number of candidates or of kept edges (2^20 edges, all different: parallel ones are added up before); every
 # edge a candidate, none, and too many candidates left for the last workgroup behind the rounds that should bring them there (a star keeps all of them)

@@ -81,6 +81,19 @@ public:
                 return;
             }
     }
+    // an array turned out to be shorter than what was asked for: in the arena, where memory is short, the rest is given back
+    void shorten(void *p, size_t bytes)
+    {
+        bytes = (bytes + 32 + 255) & ~size_t(255);
+        for (int k = (int)used_.size() - 1; arena_ && k >= 0; --k)
+            if (used_[k].ptr == p && used_[k].bytes > bytes) {
+                const Blk rest{(char *)p + bytes, used_[k].bytes - bytes};
+                used_[k].bytes = bytes;
+                live_ -= rest.bytes;
+                arena_release(rest);
+                return;
+            }
+    }
     void trim()
     {
         if (arena_) return;
@@ -368,6 +381,11 @@ public:
     {
         if (ptr_ && ctx_) ctx_->release(ptr_);
         ptr_ = nullptr; count_ = 0; ctx_ = nullptr;
+    }
+    void shorten(size_t count)
+    {
+        if (ptr_ && ctx_) ctx_->shorten(ptr_, count * sizeof(T));
+        count_ = count;
     }
     T *get() const { return ptr_; }
     operator T *() const { return ptr_; }

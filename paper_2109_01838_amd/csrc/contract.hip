@@ -449,10 +449,15 @@ struct InnerFlag {
 // the scan that follows (kScanTile edges) and leaves the number of edges that are no loops in tile_sums: the scan
 // over NotLoopKey then needs no pass of its own to count them.  It also clears its tile's word of sign_sums, where the sign
 // counts of the contracted costs will go.
+// With PARTS > 0 the sort's first digit (the top bits of lo, of which `shift` are left out) is counted on the way, for each of
+// the PARTS tiles of the sort that the workgroup's edges make up: hist[digit][tile].
+template <int PARTS>
 __global__ __launch_bounds__(kBlock) void k_relabel_keys(size_t m, const int32_t *i, const int32_t *j,
                                                          const int32_t *fmap, uint64_t *raw, uint32_t *maxdiff,
-                                                         uint32_t *tile_sums, uint64_t *sign_sums)
+                                                         uint32_t *tile_sums, uint64_t *sign_sums, uint32_t *hist, uint32_t nb, int shift, int bits)
 {
+    constexpr int kParts = PARTS > 0 ? PARTS : 1, kPartItems = kScanItems / kParts;
+    __shared__ uint32_t s_digits[kParts][kRadix];
     const size_t base = (size_t)blockIdx.x * kScanTile + threadIdx.x;
     uint32_t diff = 0, kept = 0;
     int32_t fa[kScanItems], fb[kScanItems];      // all gathers before the first store (behind the end: the last edge again)
@@ -461,21 +466,45 @@ __global__ __launch_bounds__(kBlock) void k_relabel_keys(size_t m, const int32_t
         const size_t e = base + (size_t)q * kBlock, at = e < m ? e : m - 1;
         fa[q] = i[at]; fb[q] = j[at];
     }
+    if constexpr (PARTS > 0) {
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) s_digits[p][threadIdx.x] = 0u;
+        __syncthreads();
+    }
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) { fa[q] = fmap[fa[q]]; fb[q] = fmap[fb[q]]; }
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
         const size_t e = base + (size_t)q * kBlock;
+        const int32_t a = fa[q], b = fb[q];
+        const uint32_t d = (uint32_t)abs(a - b), lo = (uint32_t)min(a, b);
         if (e < m) {
-            const int32_t a = fa[q], b = fb[q];
-            const uint32_t d = (uint32_t)abs(a - b);
             diff = d > diff ? d : diff;
             kept += a != b ? 1u : 0u;
-            raw[e] = ((uint64_t)(uint32_t)min(a, b) << 32) | d;
+            raw[e] = ((uint64_t)lo << 32) | d;
+        }
+        if constexpr (PARTS > 0) {      // rows are nearly in order: most of a wave has the digit of its first lane
+            uint64_t left = __ballot(e < m && a != b);
+            if (left) {                 // uniform
+                const uint32_t x = lo >> shift;
+                const int first = __ffsll((long long)left) - 1;
+                const uint32_t x0 = (uint32_t)__builtin_amdgcn_readlane((int)x, first);
+                const uint64_t same = __ballot(x == x0) & left;
+                if (lane_id() == first) atomicAdd(&s_digits[q / kPartItems][x0], (uint32_t)__popcll(same));
+                left &= ~same;
+                if (left & (1ull << lane_id())) atomicAdd(&s_digits[q / kPartItems][x], 1u);
+            }
         }
     }
     kept = block_sum(kept);
-    if (threadIdx.x == 0) { tile_sums[blockIdx.x] = kept; sign_sums[blockIdx.x] = 0ull; }
+    if (threadIdx.x == 0) { if (tile_sums) tile_sums[blockIdx.x] = kept; sign_sums[blockIdx.x] = 0ull; }
+    if constexpr (PARTS > 0) {      // all have counted: the barriers of the sum
+#pragma unroll
+        for (int p = 0; p < PARTS; ++p) {
+            const uint32_t tile = blockIdx.x * PARTS + p;
+            if (threadIdx.x < (1u << bits) && tile < nb) hist[(size_t)threadIdx.x * nb + tile] = s_digits[p][threadIdx.x];
+        }
+    }
     block_max_into(diff, maxdiff);
 }
 struct NotLoopKey {
@@ -540,6 +569,134 @@ struct HeadFlag {
     const uint64_t *key;
     __device__ __forceinline__ uint32_t operator()(size_t e) const { return ((e == 0) | (key[e] != key[e ? e - 1 : 0])) ? 1u : 0u; }
 };
+
+// Contraction of a middle-sized list behind one pass over the top bits of lo: a workgroup to a digit sorts the digit's edges in
+// LDS, adds up the runs of equal pairs there, in order of appearance, and leaves its edges at the digit's place, not more than
+// there were; counts[digit] tells how many.  The second field of the keys is as wide as a node's number; in LDS it gets
+// the bits that the largest hi - lo needs, without which a row is one bucket of the in-LDS sort.
+// Bounded by the instructions that one workgroup of sixteen waves issues (2600 edges: 3 us until they are there, 5 to sort, 2 to
+// add up; a round's edges of a 300x301 long-range grid 14 us, where the in-LDS sort, the count of heads and the
+// sums as launches of their own took 20 + 4 + 11).
+__global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_sum_digit(const uint64_t *key, const uint32_t *val, const uint32_t *starts, int nbits, int low_bits,
+                                                                      const uint32_t *maxdiff, uint32_t *counts, uint32_t *oversize,
+                                                                      int32_t *ti, int32_t *tj, float *tc)
+{
+    using LS = LocalSort<uint32_t>;
+    constexpr int kItems = LS::items;
+    __shared__ LocalSortShared<uint32_t> S;
+    __shared__ float s_val[LS::cap];
+    __shared__ uint32_t s_runs[kLocalSortWaves];
+    const uint32_t beg = starts[blockIdx.x], cnt = starts[blockIdx.x + 1] - beg;
+    const int tid = (int)threadIdx.x, lane = lane_id(), w = tid >> 6;
+    if (cnt == 0 || cnt > (uint32_t)LS::cap) {
+        if (tid == 0) { counts[blockIdx.x] = 0u; if (cnt) *oversize = 1u; }
+        return;
+    }
+    const int rows = (int)((cnt + LS::threads - 1) / LS::threads);
+    const uint32_t first = (uint32_t)w * (uint32_t)rows * 64u + (uint32_t)lane;
+    const uint32_t lo0 = (uint32_t)blockIdx.x << (low_bits - nbits), widest = *maxdiff;
+    const int dbits = 32 - __clz((int)widest);      // at least one: there is an edge
+    const uint32_t dmask = widest | ((1u << (dbits - 1)) - 1u);
+    uint32_t k[kItems], v[kItems], rank[kItems];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        k[r] = 0; v[r] = 0;
+        const uint32_t p = first + (uint32_t)r * 64u;
+        if (r < rows && p < cnt) {
+            const uint64_t x = key[beg + p];
+            k[r] = (((uint32_t)(x >> nbits) - lo0) << dbits) | ((uint32_t)x & dmask);
+            v[r] = val[beg + p];
+        }
+    }
+    local_sort<true>(S, k, v, rank, rows, cnt, low_bits - nbits + dbits);
+#pragma unroll
+    for (int r = 0; r < kItems; ++r)
+        if (r < rows && first + (uint32_t)r * 64u < cnt) s_val[rank[r]] = __uint_as_float(v[r]);
+    uint32_t heads = 0, mine = 0;
+#pragma unroll
+    for (int r = 0; r < kItems; ++r)
+        if (r < rows) {
+            const uint32_t p = first + (uint32_t)r * 64u;
+            const bool head = p < cnt && (p == 0 || S.buf[p] != S.buf[p - 1]);
+            heads |= head ? 1u << r : 0u;
+            mine += (uint32_t)__popcll(__ballot(head));
+        }
+    if (lane == 0) s_runs[w] = mine;
+    lds_barrier();
+    uint32_t at = beg, all = 0;
+#pragma unroll
+    for (int q = 0; q < kLocalSortWaves; ++q) {
+        const uint32_t x = s_runs[q];
+        at += q < w ? x : 0u;
+        all += x;
+    }
+    if (tid == 0) counts[blockIdx.x] = all;
+#pragma unroll
+    for (int r = 0; r < kItems; ++r)
+        if (r < rows) {
+            const uint64_t row = __ballot((heads >> r) & 1u);
+            if ((heads >> r) & 1u) {
+                uint32_t p = first + (uint32_t)r * 64u;
+                const uint32_t x = S.buf[p], to = at + (uint32_t)__popcll(row & ((1ull << lane) - 1ull));
+                float acc = s_val[p];
+                for (++p; p < cnt && S.buf[p] == x; ++p) acc = acc + s_val[p];
+                const uint32_t lo = lo0 + (x >> dbits);
+                ti[to] = (int32_t)lo; tj[to] = (int32_t)(lo + (x & dmask)); tc[to] = acc;
+            }
+            at += (uint32_t)__popcll(row);
+        }
+}
+
+// The digits' edges one behind the other, a workgroup to a digit; sign counts per kScanTile edges (see k_reduce_runs); the
+// last workgroup tells the host: mail[1] number of edges, mail[2]: *oversize, mail[3]: number of edges before they were added up.
+constexpr int kJoinThreads = 512;
+__global__ __launch_bounds__(kJoinThreads) void k_join_digits(const uint32_t *starts, const uint32_t *counts, const int32_t *ti, const int32_t *tj, const float *tc,
+                                                              int32_t *io, int32_t *jo, float *co, unsigned long long *sign_sums,
+                                                              const uint32_t *oversize, uint64_t *mail, uint64_t seq)
+{
+    constexpr int kTiles = LocalSort<uint32_t>::cap / kScanTile + 1;
+    __shared__ uint32_t s_sum[kJoinThreads / 64], s_sign[kTiles];
+    const int tid = (int)threadIdx.x;
+    uint32_t x = 0;
+    for (int d = tid; d < (int)blockIdx.x; d += kJoinThreads) x += counts[d];
+    x = wave_sum(x);
+    if (lane_id() == 0) s_sum[tid >> 6] = x;
+    if (tid < kTiles) s_sign[tid] = 0u;
+    __syncthreads();
+    uint32_t at = 0;
+#pragma unroll
+    for (int w = 0; w < kJoinThreads / 64; ++w) at += s_sum[w];
+    const uint32_t beg = starts[blockIdx.x], n = counts[blockIdx.x], tile0 = at / (uint32_t)kScanTile;
+    if (blockIdx.x == gridDim.x - 1 && tid < 64) {
+        if (tid == 0) {
+            mail_put(mail + 1, (uint64_t)(at + n));
+            mail_put(mail + 2, (uint64_t)*oversize);
+            mail_put(mail + 3, (uint64_t)starts[gridDim.x]);
+        }
+        mail_send_wave(mail, seq);
+    }
+    for (uint32_t k0 = 0; k0 < n; k0 += kJoinThreads) {      // uniform
+        const uint32_t k = k0 + (uint32_t)tid;
+        float c = 0.0f;
+        if (k < n) {
+            c = tc[beg + k];
+            io[at + k] = ti[beg + k]; jo[at + k] = tj[beg + k]; co[at + k] = c;
+        }
+        // the wave's 64 places lie in one tile or in two
+        const uint64_t pos = __ballot(c > 0.0f), neg = __ballot(c < 0.0f);
+        const uint32_t p = at + k0 + (uint32_t)(tid & ~63), t = p / (uint32_t)kScanTile, lower = (t + 1) * (uint32_t)kScanTile - p;
+        const uint64_t low = lower < 64u ? (1ull << lower) - 1ull : ~0ull;
+        if (lane_id() == 0) {
+            const uint32_t a = (uint32_t)__popcll(pos & low) | (uint32_t)__popcll(neg & low) << 16;
+            const uint32_t b = (uint32_t)__popcll(pos & ~low) | (uint32_t)__popcll(neg & ~low) << 16;
+            if (a) atomicAdd(&s_sign[t - tile0], a);
+            if (b) atomicAdd(&s_sign[t - tile0 + 1], b);
+        }
+    }
+    __syncthreads();
+    if (tid < kTiles && s_sign[tid])
+        atomicAdd(&sign_sums[tile0 + tid], (unsigned long long)(s_sign[tid] & 0xffffu) | (unsigned long long)(s_sign[tid] >> 16) << 32);
+}
 
 // diag[k] = sum of the values of run k of the sorted keys, in order of appearance (an ordered sum is a chain of adds, so
 // what can be saved is the wait for its operands).  A wave takes 64 places; the runs that start there are added up from
@@ -1247,6 +1404,77 @@ static rama_status components(Ctx &ctx, size_t n, size_t ns, const int32_t *si, 
     return fail(ctx, RAMA_ERR_HIP, "connected components did not converge");
 }
 
+// contract_edges for a middle-sized list: five launches and a wait, where counting the digits, counting the heads and the sums
+// as launches of their own were seven.  Contraction of a 300x301 long-range grid to the end 1.72 -> 1.54 ms, 128^2 static solve
+// 2.07 -> 1.99, 512^2 5.46 -> 5.37, 6-NN graph of 10^6 points 9.35 -> 9.24, 61x97x131 volume 5.45 -> 5.29.  *done stays false if some digit holds more edges than a workgroup sorts.
+static rama_status contract_by_digits(Ctx &ctx, const Graph &g, const int32_t *fmap, int nbits, int top_bits, Graph &out, bool *done)
+{
+    const size_t m = (size_t)g.m;
+    const int low_bits = 2 * nbits - top_bits;
+    const bool short_tiles = m <= kSortShort;
+    const uint32_t nb = grid_for(m, short_tiles ? kShortTile : kMediumTile), tiles = grid_for(m, kScanTile), digits = 1u << top_bits;
+    static_assert(kScanTile == kMediumTile && kScanTile == 2 * kShortTile, "tiles of the sort per tile of k_relabel_keys");
+    Buf<uint64_t> raw, key;
+    Buf<uint32_t> val, val2, hist, starts, counts, words;      // words: largest hi - lo, a digit is too long
+    RAMA_TRY(raw.alloc(ctx, m));
+    RAMA_TRY(key.alloc(ctx, m));
+    RAMA_TRY(val.alloc(ctx, m));
+    RAMA_TRY(val2.alloc(ctx, m));
+    RAMA_TRY(hist.alloc(ctx, ((size_t)nb + 1) << top_bits));
+    RAMA_TRY(starts.alloc(ctx, (size_t)digits + 1));
+    RAMA_TRY(counts.alloc(ctx, (size_t)digits));
+    RAMA_TRY(zeroed<uint32_t>(ctx, 2, words));
+    RAMA_TRY(out.sign_sums.alloc(ctx, tiles));
+    {
+        ProfScope ps_(ctx, "k_rs_hist<relabelled>", (double)(m * 24));      // the count of the sort's one pass as well
+        auto relabel = [&](auto kernel) {
+            kernel<<<tiles, kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), fmap, raw.get(), words.get(), (uint32_t *)nullptr, out.sign_sums.get(),
+                                                     hist.get(), nb, nbits - top_bits, top_bits);
+        };
+        if (short_tiles) relabel(k_relabel_keys<2>);
+        else relabel(k_relabel_keys<1>);
+    }
+    LAUNCH_TRY(ctx, "relabel_keys");
+    const RelabelledEdges source{raw.get(), g.c.get(), nbits};
+    if (short_tiles)
+        RAMA_TRY((radix_pass<uint64_t, uint32_t, true, kShortThreads, kShortTile / kShortThreads>(ctx, (const uint64_t *)nullptr, (const uint32_t *)nullptr, source, key.get(), val.get(),
+                                                                                                 m, low_bits, top_bits, hist.get(), starts.get(), true)));
+    else
+        RAMA_TRY((radix_pass<uint64_t, uint32_t, true, kMediumThreads, kMediumTile / kMediumThreads>(ctx, (const uint64_t *)nullptr, (const uint32_t *)nullptr, source, key.get(), val.get(),
+                                                                                                    m, low_bits, top_bits, hist.get(), starts.get(), true)));
+    // the relabelled edges are no longer needed: the digits' edges take their place
+    int32_t *ti = reinterpret_cast<int32_t *>(raw.get()), *tj = ti + m;
+    float *tc = reinterpret_cast<float *>(val2.get());
+    {
+        ProfScope ps_(ctx, "k_reduce_runs", (double)(m * 24));      // the timers keep one name for the kernels that add up runs
+        k_sum_digit<<<digits, LocalSort<uint32_t>::threads, 0, ctx.stream>>>(key.get(), val.get(), starts.get(), nbits, low_bits, words.get(), counts.get(),
+                                                                          words.get() + 1, ti, tj, tc);
+    }
+    LAUNCH_TRY(ctx, "sum_digit");
+    key.reset(); val.reset();      // the result may take their place
+    RAMA_TRY(out.i.alloc(ctx, m));
+    RAMA_TRY(out.j.alloc(ctx, m));
+    RAMA_TRY(out.c.alloc(ctx, m));
+    const uint64_t seq = ++ctx.mail_seq;
+    {
+        ProfScope ps_(ctx, "k_join_digits", (double)(m * 24));
+        k_join_digits<<<digits, kJoinThreads, 0, ctx.stream>>>(starts.get(), counts.get(), ti, tj, tc, out.i.get(), out.j.get(), out.c.get(),
+                                                            (unsigned long long *)out.sign_sums.get(), words.get() + 1, mailbox(ctx), seq);
+    }
+    LAUNCH_TRY(ctx, "join_digits");
+    RAMA_TRY(wait_mail(ctx, seq));
+    const volatile uint64_t *mail = mailbox(ctx);
+    if (mail[2]) {
+        ctx.sorts_unseen = false;
+        out.i.reset(); out.j.reset(); out.c.reset(); out.sign_sums.reset();
+        return RAMA_OK;
+    }
+    out.m = (int64_t)mail[1];
+    out.i.shorten((size_t)out.m); out.j.shorten((size_t)out.m); out.c.shorten((size_t)out.m);
+    *done = true;
+    return RAMA_OK;
+}
+
 // contracted graph of canonical g under fmap (n_new new nodes)
 static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap, int32_t n_new, Graph &out)
 {
@@ -1254,6 +1482,15 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
     out.n = n_new;
     out.m = 0;
     const int nbits = bits_for((uint64_t)n_new);
+    // A middle-sized list: one pass over the top bits of lo, whose digits are counted by the kernel that makes the keys, and a
+    // workgroup to a digit does the rest.  Nobody waits to hear how many edges are left.
+    bool narrow = false;
+    const int top_bits = sort_takes_source(m, m) ? unseen_bits_now(ctx, m, 2 * nbits, (uint64_t)n_new << nbits, &narrow) : 0;
+    if (top_bits > 0 && narrow && top_bits <= nbits) {
+        bool done = false;
+        RAMA_TRY(contract_by_digits(ctx, g, fmap, nbits, top_bits, out, &done));
+        if (done) return RAMA_OK;
+    }
     ScanPlan<uint32_t> keep;   // the extra word behind the total: largest hi-lo
     Buf<uint64_t> raw;
     RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, m, 1, keep)));
@@ -1261,36 +1498,10 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
     RAMA_TRY(out.sign_sums.alloc(ctx, keep.nb > 0 ? keep.nb : 1));
     {
         ProfScope ps_(ctx, "k_relabel_keys", (double)(m * 24));
-        k_relabel_keys<<<keep.nb, kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), fmap, raw.get(), keep.extra_ptr(),
-                                                        keep.sums.get(), out.sign_sums.get());
+        k_relabel_keys<0><<<keep.nb, kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), fmap, raw.get(), keep.extra_ptr(),
+                                                           keep.sums.get(), out.sign_sums.get(), (uint32_t *)nullptr, 0u, 0, 0);
     }
     LAUNCH_TRY(ctx, "relabel_keys");
-    bool narrow = false;
-    if (sort_takes_source(m, m) && unseen_bits_now(ctx, m, 2 * nbits, (uint64_t)n_new << nbits, &narrow)) {
-        // Nobody waits to hear how many edges are left: the sort is made for all of them, its first pass leaves the loops out
-        // and the number comes with the count behind it.  The key's second field is as wide as it can get, which costs such
-        // a sort nothing.  Measured together with the matching's counts, see kBlindEdges.
-        Buf<uint64_t> key;
-        Buf<uint32_t> val, val2, head_sums;
-        RAMA_TRY(key.alloc(ctx, m));
-        RAMA_TRY(val.alloc(ctx, m));
-        RAMA_TRY(val2.alloc(ctx, m));
-        ScanPlan<uint32_t> runs;
-        RAMA_TRY((scan_plan_alloc<uint32_t>(ctx, m, 2, runs)));
-        SortAgain<uint64_t, uint32_t> again;
-        again.flag = runs.extra_ptr();
-        again.n_sorted = runs.extra_ptr() + 1;
-        RAMA_TRY((radix_sort_source<uint64_t, uint32_t>(ctx, RelabelledEdges{raw.get(), g.c.get(), nbits}, m, key, val, raw, val2, m, 2 * nbits,
-                                                        &head_sums, (uint64_t)n_new << nbits, &again)));
-        RAMA_TRY((count_heads<uint64_t, uint32_t>(ctx, key, &val, m, 2 * nbits, [](const uint64_t *k) { return HeadFlag{k}; }, runs, 0, head_sums, again, true)));
-        const size_t uniq = runs.total;
-        RAMA_TRY(out.i.alloc(ctx, uniq > 0 ? uniq : 1));
-        RAMA_TRY(out.j.alloc(ctx, uniq > 0 ? uniq : 1));
-        RAMA_TRY(out.c.alloc(ctx, uniq > 0 ? uniq : 1));
-        RAMA_TRY(reduce_runs(ctx, runs, key.get(), val.get(), nbits, out.i.get(), out.j.get(), out.c.get(), &out.sign_sums));
-        out.m = (int64_t)uniq;
-        return RAMA_OK;
-    }
     RAMA_TRY((scan_totals<uint32_t>(ctx, NotLoopKey{raw.get()}, keep, keep.sums.get())));   // tile sums: left by k_relabel_keys
     const uint32_t kept = keep.total;
     const int dbits = bits_for((uint64_t)keep.extra_value[0] + 1);

@@ -1055,45 +1055,29 @@ struct LocalSort {
     static constexpr int threads = kLocalSortWaves * 64;
     static constexpr int cap = threads * items;
 };
-template <typename K, typename V, bool HAS_V, typename LK>
-__global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_rs_local(const K *kin, const V *vin, K *kout, V *vout,
-                                                                   const uint32_t *bounds, int low_bits, uint32_t n_all,
-                                                                   uint32_t *head_sums, uint32_t *oversize, uint32_t *n_sorted)
+template <typename LK>
+struct LocalSortShared {
+    __align__(16) uint16_t whist[kLocalSortWaves][kRadix];
+    uint32_t wave_tot[4], bucket_tot[kLocalSortWaves];
+    LK buf[LocalSort<LK>::cap];      // the words that are compared, then the keys, then the values
+};
+// Sorts cnt keys of sort_bits bits (stable): item r of lane l in wave w is number (w * rows + r) * 64 + l.  In the end the keys
+// stand in S.buf in their order, rank[r] is the place of key r there (of the key that came last to this thread, if there
+// were passes: val goes along), and everybody has passed a barrier.
+template <bool HAS_V, typename LK>
+__device__ __forceinline__ void local_sort(LocalSortShared<LK> &S, LK (&key)[LocalSort<LK>::items], uint32_t (&val)[LocalSort<LK>::items],
+                                           uint32_t (&rank)[LocalSort<LK>::items], int rows, uint32_t cnt, int sort_bits)
 {
-    constexpr int NW = kLocalSortWaves;
-    constexpr int kItems = LocalSort<LK>::items;
-    constexpr int kThreads = LocalSort<LK>::threads;
-    constexpr int kCap = LocalSort<LK>::cap;
+    constexpr int NW = kLocalSortWaves, kItems = LocalSort<LK>::items, kThreads = LocalSort<LK>::threads, kCap = LocalSort<LK>::cap;
     static_assert(kRadix == 256 && kThreads >= kRadix, "one digit per thread of the first four waves");
-    __shared__ __align__(16) uint16_t whist[NW][kRadix];
-    __shared__ uint32_t wave_tot[4], bucket_tot[NW];
-    __shared__ LK sbuf[kCap];      // the words that are compared, then the keys, then the values
-    // without a bounds array the (single) workgroup takes the whole array of n_all keys
-    const uint32_t beg = bounds ? bounds[blockIdx.x] : 0u, end = bounds ? bounds[blockIdx.x + 1] : n_all;
-    const uint32_t cnt = end - beg;
-    if (n_sorted && blockIdx.x == 0 && threadIdx.x == 0) *n_sorted = bounds[gridDim.x];
-    if (cnt == 0 || cnt > (uint32_t)kCap) {      // the second case: ruled out by the caller, or told to it
-        if (cnt && oversize && threadIdx.x == 0) *oversize = 1u;
-        return;
-    }
+    auto &whist = S.whist;
+    auto &wave_tot = S.wave_tot;
+    auto &bucket_tot = S.bucket_tot;
+    LK *const sbuf = S.buf;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const K base = (kin[beg] >> low_bits) << low_bits;
-    const uint64_t top_span = (uint64_t)((kin[end - 1] >> low_bits) - (kin[beg] >> low_bits));
-    const int sort_bits = low_bits + (top_span ? 64 - __clzll((long long)top_span) : 0);
     const int passes = (sort_bits + kRadixBits - 1) / kRadixBits;
-    const int rows = (int)((cnt + kThreads - 1) / kThreads);       // rows of 64 keys per wave
     const uint32_t wave_base = (uint32_t)w * (uint32_t)rows * 64u;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    LK key[kItems];
-    uint32_t val[kItems];
-    uint32_t rank[kItems];
-#pragma unroll
-    for (int r = 0; r < kItems; ++r) {
-        const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
-        const bool valid = r < rows && idx < cnt;
-        key[r] = valid ? (LK)(kin[beg + idx] - base) : (LK)0;
-        if (HAS_V) val[r] = valid ? (uint32_t)vin[beg + idx] : 0u;
-    }
     // Buckets first: the top kBucketBits of the keys' differing bits split the few thousand keys into buckets of one to
     // a few (an edge list: the edges of a node).  Count and place by LDS atomics -- in any order --, then every key
     // finds its place among its bucket's keys by comparing.  What is compared is one word: the bits below the bucket's
@@ -1258,6 +1242,42 @@ __global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_rs_local(const K *k
         shift += bits;
         remaining -= bits;
     }
+}
+
+template <typename K, typename V, bool HAS_V, typename LK>
+__global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_rs_local(const K *kin, const V *vin, K *kout, V *vout,
+                                                                   const uint32_t *bounds, int low_bits, uint32_t n_all,
+                                                                   uint32_t *head_sums, uint32_t *oversize)
+{
+    constexpr int kItems = LocalSort<LK>::items;
+    constexpr int kThreads = LocalSort<LK>::threads;
+    constexpr int kCap = LocalSort<LK>::cap;
+    __shared__ LocalSortShared<LK> S;
+    LK *const sbuf = S.buf;
+    // without a bounds array the (single) workgroup takes the whole array of n_all keys
+    const uint32_t beg = bounds ? bounds[blockIdx.x] : 0u, end = bounds ? bounds[blockIdx.x + 1] : n_all;
+    const uint32_t cnt = end - beg;
+    if (cnt == 0 || cnt > (uint32_t)kCap) {      // the second case: ruled out by the caller, or told to it
+        if (cnt && oversize && threadIdx.x == 0) *oversize = 1u;
+        return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const K base = (kin[beg] >> low_bits) << low_bits;
+    const uint64_t top_span = (uint64_t)((kin[end - 1] >> low_bits) - (kin[beg] >> low_bits));
+    const int sort_bits = low_bits + (top_span ? 64 - __clzll((long long)top_span) : 0);
+    const int rows = (int)((cnt + kThreads - 1) / kThreads);       // rows of 64 keys per wave
+    const uint32_t wave_base = (uint32_t)w * (uint32_t)rows * 64u;
+    LK key[kItems];
+    uint32_t val[kItems];
+    uint32_t rank[kItems];
+#pragma unroll
+    for (int r = 0; r < kItems; ++r) {
+        const uint32_t idx = wave_base + (uint32_t)r * 64u + lane;
+        const bool valid = r < rows && idx < cnt;
+        key[r] = valid ? (LK)(kin[beg + idx] - base) : (LK)0;
+        if (HAS_V) val[r] = valid ? (uint32_t)vin[beg + idx] : 0u;
+    }
+    local_sort<HAS_V>(S, key, val, rank, rows, cnt, sort_bits);
     auto values_out = [&]() {      // behind the keys, through the same LDS
         __syncthreads();
 #pragma unroll
@@ -1319,12 +1339,13 @@ inline const char *rs_local_name()
     return sizeof(K) == 8 ? "k_rs_local<u64>" : "k_rs_local<u32>";
 }
 
-// one pass: histogram, offsets, scatter
+// one pass: histogram (unless it is there: `counted`), offsets, scatter
 template <typename K, typename V, bool HAS_V, int THREADS, int ITEMS, typename SRC>
-rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist, uint32_t *starts)
+rama_status radix_pass(Ctx &ctx, const K *ka, const V *va, const SRC &src, K *kb, V *vb, size_t n, int shift, int bits, uint32_t *hist, uint32_t *starts,
+                       bool counted = false)
 {
     const uint32_t nb = grid_for(n, THREADS * ITEMS);
-    {
+    if (!counted) {
         ProfScope ps_(ctx, (sizeof(K) == 8 ? "k_rs_hist<u64>" : "k_rs_hist<u32>"), (double)(n * sizeof(K)));
         k_rs_hist<K, THREADS * ITEMS / kBlock, SRC><<<xcd_grid(nb), kBlock, 0, ctx.stream>>>(ka, src, hist, n, shift, bits, nb);
     }
@@ -1418,7 +1439,7 @@ rama_status split_sort_tail(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
     {
         ProfScope ps_(ctx, rs_local_name<K, HAS_V, LK>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
         k_rs_local<K, V, HAS_V, LK><<<nbk, LS::threads, 0, ctx.stream>>>(ka, va, kb, vb, bounds.get(), low_bits, (uint32_t)n,
-                                                                      head_sums ? head_sums->get() : nullptr, (uint32_t *)nullptr, (uint32_t *)nullptr);
+                                                                      head_sums ? head_sums->get() : nullptr, (uint32_t *)nullptr);
     }
     LAUNCH_TRY(ctx, "rs_local");
     *done = true;
@@ -1457,7 +1478,6 @@ inline int unseen_bits_now(const Ctx &ctx, size_t n, int total_bits, uint64_t ke
 static_assert((LocalSort<uint32_t>::cap / 2) << kRadixBits <= kSortMedium, "tiles that tell where the digits begin");
 struct SortUnseen {
     uint32_t *flag = nullptr;      // a zeroed word
-    uint32_t *n_sorted = nullptr;  // optional: gets the number of keys, where the caller knows no more than a bound
     bool used = false;
 };
 
@@ -1510,11 +1530,11 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
             if (narrow) {
                 ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint32_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
                 k_rs_local<K, V, HAS_V, uint32_t><<<1, LocalSort<uint32_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, (const uint32_t *)nullptr,
-                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr, (uint32_t *)nullptr);
+                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr);
             } else {
                 ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint64_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
                 k_rs_local<K, V, HAS_V, uint64_t><<<1, LocalSort<uint64_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, (const uint32_t *)nullptr,
-                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr, (uint32_t *)nullptr);
+                                                                                                  total_bits, (uint32_t)n, hs, (uint32_t *)nullptr);
             }
             LAUNCH_TRY(ctx, "rs_local");
             *result_in_b = true;
@@ -1540,11 +1560,11 @@ rama_status radix_sort_impl(Ctx &ctx, K *ka, V *va, K *kb, V *vb, size_t n, int 
         if (unseen_narrow) {
             ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint32_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
             k_rs_local<K, V, HAS_V, uint32_t><<<1u << unseen_bits, LocalSort<uint32_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, starts.get(), low_bits,
-                                                                                                             (uint32_t)n, hs, unseen->flag, unseen->n_sorted);
+                                                                                                             (uint32_t)n, hs, unseen->flag);
         } else {
             ProfScope ps_(ctx, rs_local_name<K, HAS_V, uint64_t>(), (double)(n * (2 * sizeof(K) + (HAS_V ? 8 : 0))));
             k_rs_local<K, V, HAS_V, uint64_t><<<1u << unseen_bits, LocalSort<uint64_t>::threads, 0, ctx.stream>>>(ka, va, kb, vb, starts.get(), low_bits,
-                                                                                                             (uint32_t)n, hs, unseen->flag, unseen->n_sorted);
+                                                                                                             (uint32_t)n, hs, unseen->flag);
         }
         LAUNCH_TRY(ctx, "rs_local");
         unseen->used = true;
@@ -1701,17 +1721,12 @@ rama_status radix_sort_keys(Ctx &ctx, Buf<K> &k, size_t n, int total_bits, Buf<u
 // What follows a sort whose flag is the word `word` of `plan`: the heads of the sorted keys are counted (scan_totals) and the
 // count comes to the host with the flag.  If it is raised, the keys are sorted once more, from the buffers that the
 // in-LDS sort read (in the order of their top bits, which does no harm), and counted again.  flags(k): the scan's input.
-// bounded: n is a bound, the number of keys comes with the flag, in the word behind it, and takes the place of n in the plan.
 template <typename K, typename V, typename FLAGS>
 rama_status count_heads(Ctx &ctx, Buf<K> &k, Buf<V> *v, size_t n, int total_bits, const FLAGS &flags, ScanPlan<uint32_t> &plan, int word,
-                        Buf<uint32_t> &head_sums, SortAgain<K, V> &again, bool bounded = false)
+                        Buf<uint32_t> &head_sums, SortAgain<K, V> &again)
 {
     RAMA_TRY((scan_totals<uint32_t>(ctx, flags(k.get()), plan, head_sums.get())));
     head_sums.reset();
-    if (bounded) {
-        n = plan.n = plan.extra_value[word + 1];
-        plan.nb = grid_for(n, kScanTile);
-    }
     if (!again.used || !plan.extra_value[word]) {
         again.k.reset(); again.v.reset();
         return RAMA_OK;

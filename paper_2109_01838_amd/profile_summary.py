@@ -63,6 +63,11 @@ def event_name(rocprof_name):
         # <key, value, has values, offsets by local scan, ..>: the timers name key and value types only
         args = n[len("k_rs_scatter<"):].rstrip(">").split(",")
         return f"k_rs_scatter<{args[0]},{args[1]}>" if args[2] == "true" else f"k_rs_scatter<{args[0]}>"
+    if n.startswith("k_relabel_keys<"):
+        # <tiles of the sort that a workgroup counts>
+        return "k_relabel_keys" if n.endswith("<0>") else "k_rs_hist<relabelled>"
+    if n == "k_sum_digit":
+        return "k_reduce_runs"
     if n.startswith(("k_rs_hist<", "k_edge_update<")):
         # <key type | store c_e, items of a thread, ..>: the timers name the first argument only
         return n.split(",")[0].rstrip(">") + ">"

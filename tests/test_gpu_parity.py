@@ -801,6 +801,41 @@ def test_last_workgroup_of_a_matching(rama, oracle32, n, m, kind, cap):
         assert np.array_equal(np_(got[k]), want[k]), k
 
 
+# Contraction with a workgroup to a digit: lists on both sides of the tiles (1024 edges up to 196608, 2048 beyond) and of the
+# lines where it begins (8192 edges) and ends (2^21); parallel edges that fill buckets of the in-LDS sort, rows far apart and
+# close together (the bits of hi - lo), digits without an edge, nothing left at all
+@pytest.mark.parametrize("n,m,near", [(3000, 8193, 0), (3000, 9217, 5), (200, 19000, 0), (150, 8300, 0), (70000, 196608, 4), (70000, 196609, 4),
+                                      (5000, 197633, 0), (1000000, 300000, 2), (1048577, 300000, 0), (600, 170000, 0), (40000, 2097151, 0)])
+@pytest.mark.parametrize("ratio", [0.0, 1.0], ids=["matching", "forest"])
+def test_contraction_by_digits(rama, oracle32, n, m, near, ratio):
+    from paper_2109_01838_amd import default_params
+    if ratio and m > 400000:
+        pytest.skip("the oracle's forest takes its time")
+    rng = np.random.default_rng(n + m)
+    i = rng.integers(0, n, 2 * m)
+    j = (i + rng.integers(1, near + 1, i.size)) % n if near else rng.integers(0, n, i.size)
+    key = np.unique(np.minimum(i, j) * np.int64(n) + np.maximum(i, j))
+    key = key[key // n != key % n]
+    key = np.sort(rng.permutation(key)[:m])
+    i, j = (key // n).astype(np.int32), (key % n).astype(np.int32)
+    c = (np.round(rng.random(i.size) * 16 - 6) / 8).astype(np.float32)
+    want = oracle32.contract(n, i, j, c, repeat=1, forest_ratio=ratio)
+    got = rama.contract(n, i, j, c, params=default_params(forest_ratio=ratio), repeat=1)
+    assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+
+
+def test_contraction_leaves_nothing(rama, oracle32):
+    """A clique whose edges all attract, as a forest: one node is left, and no edge."""
+    from paper_2109_01838_amd import default_params
+    n = 200
+    i, j = np.triu_indices(n, 1)
+    c = np.linspace(1, 2, i.size).astype(np.float32)
+    got = rama.contract(n, i.astype(np.int32), j.astype(np.int32), c, params=default_params(forest_ratio=1.0), repeat=1)
+    assert got["n_nodes"] == 1 and got["i"].numel() == 0 and not np_(got["mapping"]).any()
+
+
 # Both sides of the lines up to which the matching's last workgroup numbers the nodes (2^15 nodes; 8192 at a time) and nobody
 # waits for the number of candidates or of kept edges (2^20 edges, all different: parallel ones are added up before); every
 # edge a candidate, none, and too many candidates left for the last workgroup behind the rounds that should bring them there (a star keeps all of them)

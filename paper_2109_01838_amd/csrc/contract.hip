@@ -102,23 +102,55 @@ struct PackCandsEmit {
 template <typename T>
 __device__ __forceinline__ T load_past_cache(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
-// matched edges fix their endpoints
-// The length of a round's candidate list is read from device memory (*n_list: the count the previous
-// round's compaction left there), so that several handshake rounds can be enqueued without the host
-// looking at the counts in between; the grid is sized from an upper bound and surplus workgroups leave.
-__global__ __launch_bounds__(kBlock) void k_accept(const uint32_t *n_list, Cands a, const unsigned long long *best, int32_t *mate)
+// Where a handshake round finds its candidates.  The first list is dense.  The survivors of a round go to kLists lists,
+// workgroup b's to list b % kLists; each has as many places as the first round's workgroups of its number have candidates, and
+// a counter in a cache line of its own: survivors | pairs made << 32.  With one counter for all, its two atomics took 15 ns each
+// of every workgroup, one after the other, and that was what a round waited for: 4e5 candidates 23 us and 10 with the lists,
+// 6.5e6 108 and 65; all rounds of a 320^3 solve 5.9 ms and 4.1.
+// Lengths are read from device memory, so that several handshake rounds can be enqueued without the host looking at the counts
+// in between; the grid is sized from an upper bound and surplus workgroups leave.
+constexpr uint32_t kLists = 32, kListWords = 8;      // 64-bit words of a counter's line
+struct ListPlaces {
+    uint32_t each, more;      // places of a list, the first `more` of them one workgroup's more: `group`
+    uint32_t group;
+    __host__ __device__ __forceinline__ uint32_t begin(uint32_t l) const { return l * each + (l < more ? l : more) * group; }
+};
+struct CandList {
+    Cands a;
+    const uint32_t *n_dense;              // length of the dense list
+    const unsigned long long *counts;     // of the lists; nullptr: the list is dense
+    ListPlaces places;
+};
+// the workgroup's candidates: places [first, end) of the arrays, at most GROUP of them
+template <uint32_t GROUP>
+__device__ __forceinline__ bool group_of(const CandList &l, size_t &first, size_t &end)
 {
-    const size_t na = *n_list;
-    size_t k = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (k >= na) return;
-    const int32_t u = a.u[k], v = a.v[k];
-    const unsigned long long r = a.r[k];
+    if (!l.counts) {
+        first = (size_t)blockIdx.x * GROUP; end = *l.n_dense;
+    } else {
+        const uint32_t s = blockIdx.x % kLists;
+        end = l.places.begin(s);
+        first = end + (size_t)(blockIdx.x / kLists) * GROUP;
+        end += (uint32_t)l.counts[(size_t)s * kListWords];
+    }
+    return first < end;
+}
+
+// matched edges fix their endpoints
+__global__ __launch_bounds__(kBlock) void k_accept(CandList list, const unsigned long long *best, int32_t *mate)
+{
+    size_t first, end;
+    if (!group_of<kBlock>(list, first, end)) return;
+    const size_t k = first + threadIdx.x;
+    if (k >= end) return;
+    const int32_t u = list.a.u[k], v = list.a.v[k];
+    const unsigned long long r = list.a.r[k];
     if (best[u] == r && best[v] == r) { mate[u] = v; mate[v] = u; }
 }
 
 // Survivors (both endpoints still free) move to the next list and at once propose for the next
 // round.  Every workgroup compacts 2048 candidates locally and reserves its output range with a
-// single atomicAdd; the order of the ranges varies from run to run, which is harmless: proposals
+// single atomicAdd, which notes the pairs as well; the order of the ranges varies from run to run, which is harmless: proposals
 // (atomicMax) and the accept test do not depend on the order of the list.
 // Three rank arrays rotate: this round's proposals were read by k_accept, the survivors propose into
 // the second, and they clear their endpoints' words in the third, which takes the proposals of the
@@ -135,16 +167,17 @@ constexpr uint32_t kMatchBatchMax = 1u << 20;   // candidate lists up to this le
 // front, and the pairs are noted here).  Contraction of a 300x301 long-range grid 2.68 ->
 // 2.53 ms, 512^2 solve 8.38 -> 8.07, 6-NN graph of 10^6 points 14.28 -> 13.98; on longer lists the gathers cost more than the launch.
 template <int ITEMS, bool ACCEPTS>
-__global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cands a, int32_t *mate, Cands next,
+__global__ __launch_bounds__(kBlock) void k_advance(CandList list, int32_t *mate, Cands next,
                                                     const unsigned long long *best, const int32_t *gi, const int32_t *gj,
                                                     unsigned long long *best_next, unsigned long long *best_after,
-                                                    uint32_t *counter)
+                                                    unsigned long long *counters)
 {
     __shared__ uint32_t s_base, s_wave[4], s_pairs[4];
-    const size_t na = *n_list;
-    if ((size_t)blockIdx.x * (kBlock * ITEMS) >= na) return;   // the whole workgroup: nothing left of the list here
+    size_t group, na;
+    if (!group_of<kBlock * ITEMS>(list, group, na)) return;   // the whole workgroup: nothing left of the list here
+    const Cands &a = list.a;
     const int w = threadIdx.x >> 6, lane = lane_id();
-    const size_t base = (size_t)blockIdx.x * (kBlock * ITEMS) + (size_t)w * (64 * ITEMS) + lane;
+    const size_t base = group + (size_t)w * (64 * ITEMS) + lane;
     int32_t u[ITEMS], v[ITEMS];
     unsigned long long r[ITEMS];
     uint32_t where[ITEMS];
@@ -186,7 +219,7 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
             if (in && mu[q] < 0 && mv[q] < 0) live |= 1u << q;
         }
 #pragma unroll
-        for (int q = 0; q < ITEMS; ++q) r[q] = a.r[(live & (1u << q)) ? base + (size_t)q * 64 : (size_t)0];   // most do not survive
+        for (int q = 0; q < ITEMS; ++q) r[q] = a.r[(live & (1u << q)) ? base + (size_t)q * 64 : group];   // most do not survive
     }
 #pragma unroll
     for (int q = 0; q < ITEMS; ++q) {
@@ -206,14 +239,9 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
     __syncthreads();
     if (threadIdx.x == 0) {
         const uint32_t total = s_wave[0] + s_wave[1] + s_wave[2] + s_wave[3];
-        const uint32_t made = s_pairs[0] + s_pairs[1] + s_pairs[2] + s_pairs[3];
-        if (gridDim.x == 1) {   // the only workgroup: its range starts at 0, and nobody has to wait for the counters
-            s_base = 0u;
-            counter[0] = total; counter[1] = made;
-        } else {
-            s_base = total ? atomicAdd(counter, total) : 0u;
-            if (made) atomicAdd(counter + 1, made);     // counter[1]: pairs made in this handshake round
-        }
+        const uint32_t made = s_pairs[0] + s_pairs[1] + s_pairs[2] + s_pairs[3], l = blockIdx.x % kLists;
+        const unsigned long long both = (unsigned long long)total | (unsigned long long)made << 32;
+        s_base = list.places.begin(l) + (both ? (uint32_t)atomicAdd(&counters[(size_t)l * kListWords], both) : 0u);
     }
     __syncthreads();
     uint32_t off = s_base;
@@ -236,40 +264,68 @@ __global__ __launch_bounds__(kBlock) void k_advance(const uint32_t *n_list, Cand
 // With the matching complete, the new nodes of a graph of up to kNumberMax nodes are numbered here as well (fmap; see
 // NumberPairsEmit): all mates are read at once, and one scan numbers them (four turns of reading, scanning and storing took
 // 22 us for 26000 nodes).  The message to the host goes out in front of that: mail[1] length of the first list | candidates left
-// << 32, mail[2]: pairs made here, then the counters of the rounds enqueued with this launch, two words each.
+// << 32, mail[2]: pairs made here and in the rounds enqueued with this launch, whose counters come along.
 constexpr int kFinishThreads = 1024, kFinishItems = 8, kFinishWaves = kFinishThreads / 64;
 constexpr int kFinishDirect = 1 << 14, kFinishSlots = 10240;
 constexpr uint32_t kFinishMax = kFinishThreads * kFinishItems, kFinishMaxHashed = kFinishMax / 2;
 static_assert(2 * kFinishMaxHashed <= kFinishSlots / 5 * 4 && kFinishSlots * 12 <= kFinishDirect * 8, "the table keeps room and takes the words' place");
 __host__ __device__ constexpr uint32_t finish_max(int n_nodes) { return n_nodes <= kFinishDirect ? kFinishMax : kFinishMaxHashed; }
 constexpr int kNumberMax = 1 << 15, kNumberRows = kNumberMax / kFinishThreads;
-__global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint32_t *n_first, const uint32_t *n_list, Cands a, int32_t *mate,
+__global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint32_t *n_first, CandList list, int32_t *mate,
                                                                      int rounds_left, int n_nodes, int32_t *fmap,
-                                                                     const uint32_t *counters, int n_counters, uint64_t *mail, uint64_t seq)
+                                                                     const unsigned long long *counters, int n_counters, uint64_t *mail, uint64_t seq)
 {
     constexpr unsigned long long kMatched = ~0ull;      // in a node's word: no candidate's rank
     __shared__ unsigned long long s_best[kFinishDirect];
-    __shared__ uint32_t s_left, s_pairs, s_any[2], s_wave[kFinishWaves];
-    const uint32_t n = *n_list, tid = threadIdx.x;
+    __shared__ uint32_t s_left, s_pairs, s_any[2], s_wave[kFinishWaves], s_before[kLists];
+    const uint32_t tid = threadIdx.x;
     const int lane = lane_id(), w = (int)(tid >> 6);
+    const Cands &a = list.a;
+    // candidates, and those in the lists in front of a list
+    uint32_t n, before = 0;
+    if (!list.counts) {
+        n = *list.n_dense;
+    } else {
+        const uint32_t x = lane < (int)kLists ? (uint32_t)list.counts[(size_t)lane * kListWords] : 0u;
+        const uint32_t inc = wave_inclusive_scan(x);
+        before = inc - x;
+        n = wave_last(inc);
+    }
+    if (tid < kLists) s_before[tid] = before;
     if (tid == 0) { s_left = 0u; s_pairs = 0u; s_any[0] = 0u; s_any[1] = 0u; }
+    lds_barrier();
+    uint32_t pairs = 0;      // made in the rounds enqueued with this launch
+    for (int k = (int)tid; k < n_counters * (int)kLists; k += kFinishThreads) pairs += (uint32_t)(counters[(size_t)k * kListWords] >> 32);
     auto tell = [&](uint32_t left, uint32_t made) {      // the first wave
-        for (int k = lane; k < n_counters; k += 64) mail_put(reinterpret_cast<uint32_t *>(mail + 3) + k, counters[k]);
         if (lane == 0) { mail_put(mail + 1, (uint64_t)*n_first | (uint64_t)left << 32); mail_put(mail + 2, (uint64_t)made); }
         mail_send_wave(mail, seq);
     };
     if (n > finish_max(n_nodes)) {      // uniform
-        if (w == 0) tell(n, 0u);
+        pairs = wave_sum(pairs);
+        if (lane == 0 && pairs) atomicAdd(&s_pairs, pairs);
+        __syncthreads();
+        if (w == 0) tell(n, s_pairs);
         return;
     }
     int32_t u[kFinishItems], v[kFinishItems];
     unsigned long long r[kFinishItems];
-    uint32_t alive = 0, pairs = 0;
+    uint32_t alive = 0;
 #pragma unroll
     for (int q = 0; q < kFinishItems; ++q) {
         const uint32_t k = tid + (uint32_t)q * kFinishThreads;
         u[q] = 0; v[q] = 0; r[q] = 0ull;
-        if (k < n) { u[q] = a.u[k]; v[q] = a.v[k]; r[q] = a.r[k]; alive |= 1u << q; }
+        if (k < n) {
+            uint32_t at = k;
+            if (list.counts) {      // the last list with at most k candidates in front of it
+                uint32_t l = 0;
+#pragma unroll
+                for (uint32_t step = kLists / 2; step > 0; step >>= 1)
+                    if (s_before[l + step] <= k) l += step;
+                at = list.places.begin(l) + (k - s_before[l]);
+            }
+            u[q] = a.u[at]; v[q] = a.v[at]; r[q] = a.r[at];
+            alive |= 1u << q;
+        }
     }
     const bool direct = n_nodes <= kFinishDirect;
     int32_t *s_node = reinterpret_cast<int32_t *>(s_best + kFinishSlots);
@@ -361,6 +417,18 @@ __global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint3
                 number += (uint32_t)__popcll(row);
             }
     }
+}
+
+// mail[1]: candidates in a round's lists | in the longest of them << 32, mail[2]: pairs made in the round
+__global__ __launch_bounds__(64) void k_look_at_lists(const unsigned long long *counts, uint64_t *mail, uint64_t seq)
+{
+    const unsigned long long x = lane_id() < (int)kLists ? counts[(size_t)lane_id() * kListWords] : 0ull;
+    const uint32_t n = wave_sum((uint32_t)x), pairs = wave_sum((uint32_t)(x >> 32));
+    uint32_t longest = (uint32_t)x;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) longest = max(longest, (uint32_t)__shfl_xor((int)longest, off, 64));
+    if (lane_id() == 0) { mail_put(mail + 1, (uint64_t)n | (uint64_t)longest << 32); mail_put(mail + 2, (uint64_t)pairs); }
+    mail_send_wave(mail, seq);
 }
 
 // The components of a matching are its pairs, represented by the smaller node: new numbers straight from the mates.
@@ -1102,10 +1170,13 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
         na = list.n = cand.total;
         if (na == 0) return setup.run(ctx);
     }
+    const uint32_t group = na <= kAdvMedium ? kBlock * 2 : kBlock * kAdvItems, groups = grid_for(na, (int)group);
+    const ListPlaces places{groups / kLists * group, groups % kLists, group};
+    if ((uint64_t)groups * group > 0xFFFFFFFFull) return fail(ctx, RAMA_ERR_CAPACITY, "matching: more than 2^32 places");
     for (int k = 0; k < 2; ++k) {
-        RAMA_TRY(cu[k].alloc(ctx, na));
-        RAMA_TRY(cv[k].alloc(ctx, na));
-        RAMA_TRY(cr[k].alloc(ctx, na));
+        RAMA_TRY(cu[k].alloc(ctx, (size_t)groups * group));
+        RAMA_TRY(cv[k].alloc(ctx, (size_t)groups * group));
+        RAMA_TRY(cr[k].alloc(ctx, (size_t)groups * group));
     }
     cur = Cands{cu[0].get(), cv[0].get(), cr[0].get()};
     nxt = Cands{cu[1].get(), cv[1].get(), cr[1].get()};
@@ -1113,11 +1184,15 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
     RAMA_TRY(best.alloc(ctx, n));
     RAMA_TRY(best_next.alloc(ctx, n));
     RAMA_TRY(best_after.alloc(ctx, n));
-    Buf<uint32_t> counters;                      // per handshake round: survivors, pairs made
-    RAMA_TRY(counters.alloc(ctx, (size_t)(2 * cap + 2)));
+    // the counters of kRoundsAhead rounds; where there are more, the next ones get others (and the last one's are read once more)
+    constexpr int kRoundsAhead = 8;
+    constexpr size_t kRoundWords = (size_t)kLists * kListWords;
+    const size_t counter_words = (size_t)(cap < kRoundsAhead ? cap : kRoundsAhead) * kRoundWords;
+    Buf<unsigned long long> counters, counters_before;
+    RAMA_TRY(counters.alloc(ctx, counter_words));
     setup.add(best.get(), 0u, n);
     setup.add(best_next.get(), 0u, n);
-    setup.add(counters.get(), 0u, (size_t)(2 * cap + 2));
+    setup.add(counters.get(), 0u, counter_words);
     // The list is packed and makes the first round's proposals on the way: it is not read once more just for that.
     const PackCandsEmit pack{g.i.get(), g.j.get(), g.c.get(), cur, cap > 0 ? best.get() : nullptr};
     const double pack_bytes = (double)((size_t)na * (cap > 0 ? 44 : 28));
@@ -1133,57 +1208,74 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
     // candidates in five, and about half of the edges are candidates) are enqueued on the size of its first list, then the
     // kernel that finishes it, and the counts come back together; rounds behind one that emptied the list find a zero count
     // and do nothing.
-    std::vector<uint32_t> back((size_t)(2 * cap + 2), 0u);
     const uint32_t last_max = finish_max(g.n);
+    uint32_t longest = places.begin(1);      // of the lists: a bound
+    int first_round = 0, rounds_before = 0;      // of the counters; how many there were before them
     for (int r = 0; r < cap && na > 0;) {
         const bool finish = na <= kMatchBatchMax;
         int batch = finish ? 0 : 1;
         if (finish)
             for (uint32_t left = blind ? na / 2 + 1 : na; (left > last_max || (blind && batch == 0 && na > last_max)) && batch < cap - r; left /= 2) ++batch;
-        auto n_list = [&](int round) { return round == 0 ? cand.offs.get() + cand.nb : counters.get() + 2 * (round - 1); };
+        if (batch > kRoundsAhead) batch = kRoundsAhead;
+        if (r + batch - first_round > kRoundsAhead) {
+            counters_before = std::move(counters);
+            RAMA_TRY(counters.alloc(ctx, counter_words));
+            RAMA_TRY(fill<unsigned long long>(ctx, counters.get(), 0ull, counter_words));
+            rounds_before = r - first_round;
+            first_round = r;
+        }
+        auto counts = [&](int round) {
+            return round >= first_round ? counters.get() + (size_t)(round - first_round) * kRoundWords
+                                        : counters_before.get() + (size_t)(rounds_before - 1) * kRoundWords;
+        };
+        auto list_of = [&](int round) {
+            return round == 0 ? CandList{cur, cand.offs.get() + cand.nb, nullptr, places} : CandList{cur, nullptr, counts(round - 1), places};
+        };
+        auto groups_of = [&](int round, uint32_t size) { return round == 0 ? grid_for(na, (int)size) : kLists * grid_for(longest, (int)size); };
         for (int b = 0; b < batch; ++b, ++r) {
-            uint32_t *count = counters.get() + 2 * r;
             const bool accepts = na <= kAdvMedium;
             if (!accepts) {
                 ProfScope ps_(ctx, "k_accept", (double)((size_t)na * 40));
-                k_accept<<<grid_for(na), kBlock, 0, ctx.stream>>>(n_list(r), cur, best.get(), mate.get());
+                k_accept<<<groups_of(r, kBlock), kBlock, 0, ctx.stream>>>(list_of(r), best.get(), mate.get());
             }
             LAUNCH_TRY(ctx, "accept");
             {
                 ProfScope ps_(ctx, "k_advance", (double)((size_t)na * (accepts ? 80 : 56)));
                 if (accepts)
-                    k_advance<2, true><<<grid_for(na, kBlock * 2), kBlock, 0, ctx.stream>>>(
-                        n_list(r), cur, mate.get(), nxt, best.get(), g.i.get(), g.j.get(), best_next.get(), best_after.get(), count);
+                    k_advance<2, true><<<groups_of(r, kBlock * 2), kBlock, 0, ctx.stream>>>(
+                        list_of(r), mate.get(), nxt, best.get(), g.i.get(), g.j.get(), best_next.get(), best_after.get(), counts(r));
                 else
-                    k_advance<kAdvItems, false><<<grid_for(na, kBlock * kAdvItems), kBlock, 0, ctx.stream>>>(
-                        n_list(r), cur, mate.get(), nxt, best.get(), g.i.get(), g.j.get(), best_next.get(), best_after.get(), count);
+                    k_advance<kAdvItems, false><<<groups_of(r, kBlock * kAdvItems), kBlock, 0, ctx.stream>>>(
+                        list_of(r), mate.get(), nxt, best.get(), g.i.get(), g.j.get(), best_next.get(), best_after.get(), counts(r));
             }
             LAUNCH_TRY(ctx, "advance");
             Cands t = cur; cur = nxt; nxt = t;
             best.swap(best_next);          // (this, next, after) <- (next, after, this)
             best_next.swap(best_after);
         }
+        const uint64_t seq = ++ctx.mail_seq;
+        const volatile uint64_t *mail = mailbox(ctx);
         if (!finish) {
-            RAMA_TRY(read_back(ctx, back.data(), counters.get(), (size_t)(2 * r) * 4));
-            n_matched += back[(size_t)(2 * (r - 1) + 1)];
-            na = back[(size_t)(2 * (r - 1))];
+            k_look_at_lists<<<1, 64, 0, ctx.stream>>>(counts(r - 1), mailbox(ctx), seq);
+            LAUNCH_TRY(ctx, "look_at_lists");
+            RAMA_TRY(wait_mail(ctx, seq));
+            const uint64_t lengths = mail[1];
+            na = (uint32_t)lengths;
+            longest = (uint32_t)(lengths >> 32);
+            n_matched += (int64_t)mail[2];
             continue;
         }
-        const uint64_t seq = ++ctx.mail_seq;
         {
             ProfScope ps_(ctx, "k_handshake_finish", (double)(kFinishMax * 40));
-            k_handshake_finish<<<1, kFinishThreads, 0, ctx.stream>>>(n_list(0), n_list(r), cur, mate.get(), cap - r, g.n, fmap,
-                                                                    counters.get() + 2 * (r - batch), 2 * batch,
-                                                                    mailbox(ctx), seq);
+            k_handshake_finish<<<1, kFinishThreads, 0, ctx.stream>>>(cand.offs.get() + cand.nb, list_of(r), mate.get(), cap - r, g.n, fmap,
+                                                                    batch ? counts(r - batch) : nullptr, batch, mailbox(ctx), seq);
         }
         LAUNCH_TRY(ctx, "handshake_finish");
         RAMA_TRY(wait_mail(ctx, seq));
-        const volatile uint64_t *mail = mailbox(ctx);
         const uint64_t lengths = mail[1];
         const uint32_t left = (uint32_t)(lengths >> 32);
         list.n = (uint32_t)lengths;
         n_matched += (int64_t)mail[2];
-        for (int b = 0; b < batch; ++b) n_matched += (int64_t)(mail[3 + b] >> 32);
         blind = false;
         na = left;
         if (left <= last_max) {      // the rest was worked off, or the cap was reached

@@ -779,7 +779,9 @@ def test_rows_of_the_first_proposals(rama, oracle32, degree, pos, slope):
 @pytest.mark.parametrize("n,m,kind", [(2, 1, "path"), (65, 40, "path"), (1023, 1022, "path"), (1024, 1023, "path"), (1025, 1024, "path"),
                                       (16384, 8192, "pairs"), (16384, 8192, "path"), (16385, 4096, "pairs"), (16385, 4096, "path"),
                                       (16385, 4097, "path"), (32768, 4096, "pairs"), (32768, 4095, "random"), (32769, 4096, "random"),
-                                      (16384, 9000, "random"), (16385, 9000, "random"), (300, 8192, "random"), (200000, 4096, "spread")])
+                                      (16384, 9000, "random"), (16385, 9000, "random"), (300, 8192, "random"), (200000, 4096, "spread"),
+                                      # more rounds than there are counters for at a time, of lists that stay long
+                                      (20001, 20000, "path"), (1100001, 1100000, "path")])
 @pytest.mark.parametrize("cap", [32, 3])
 def test_last_workgroup_of_a_matching(rama, oracle32, n, m, kind, cap):
     from paper_2109_01838_amd import default_params

@@ -22,12 +22,20 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const 
     const size_t base = (size_t)blockIdx.x * kScanTile + threadIdx.x;
     uint32_t diff = 0, kept = 0, down = 0;      // down: a bit per place of this thread
     bool plain = true;
-    int32_t ea[kScanItems], eb[kScanItems], ep[kScanItems], eq[kScanItems];      // edge and the one before, all read at once
+    bool ordered = true, valid = true;
+    // all edges are read at once, and those in front of a wave's stretches; the others' neighbours come from the lane in front
+    int32_t ea[kScanItems], eb[kScanItems], ep[kScanItems], eq[kScanItems];
     float ew[kScanItems];
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
-        const size_t e = base + (size_t)q * kBlock, at = e < m ? e : m - 1, before = at > 0 ? at - 1 : 0;
+        const size_t e = base + (size_t)q * kBlock, at = e < m ? e : m - 1;
+        const size_t first = e - (size_t)lane_id(), before = first == 0 ? 0 : (first < m ? first : m) - 1;      // uniform in the wave
         ea[q] = i[at]; eb[q] = j[at]; ew[q] = c[at]; ep[q] = i[before]; eq[q] = j[before];
+    }
+#pragma unroll
+    for (int q = 0; q < kScanItems; ++q) {
+        const int32_t a = __shfl_up(ea[q], 1, 64), b = __shfl_up(eb[q], 1, 64);
+        if (lane_id() != 0) { ep[q] = a; eq[q] = b; }
     }
 #pragma unroll
     for (int q = 0; q < kScanItems; ++q) {
@@ -38,7 +46,7 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const 
         kept += (a != b ? 1u : 0u) + (w > 0.0f ? 1u << 16 : 0u);      // the positive ones in the upper half
         bool bad = a < 0 || a >= n || b < 0 || b >= n || !(fabsf(w) <= 3.402823466e+38f);
         if (bad) {
-            flags[0] = 1;
+            valid = false;
         } else {
             const uint32_t d = (uint32_t)abs(a - b);
             diff = d > diff ? d : diff;
@@ -51,10 +59,15 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const 
                 plain = plain && !(lo == plo && hi == phi);
             }
             plain = plain && a != b;
-            if (!canon) flags[1] = 1;
+            ordered = ordered && canon;
         }
     }
-    if (!plain) flags[4] = 1;
+    // a flag is stored once a wave and not where it is seen to be set: stores to one word are carried out one after the other
+    // (2.3e6 edges in arbitrary order 91 -> 18 us)
+    auto raise = [&](bool any, int32_t *flag) {
+        if (__ballot(any) && lane_id() == 0 && !*(volatile int32_t *)flag) *flag = 1;
+    };
+    raise(!valid, &flags[0]); raise(!ordered, &flags[1]); raise(!plain, &flags[4]);
     static_assert(kScanTile < (1 << 16), "two counts in a word");
     kept = block_sum(kept);
     const uint32_t downs = block_sum((uint32_t)__popc(down));
@@ -67,7 +80,7 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, size_t m, const 
             const uint32_t at = atomicAdd((uint32_t *)&flags[3], 1u);
             if (at < (uint32_t)(kMaxRuns - 1)) flags[kFirstRun + at] = (int32_t)(base + (size_t)(__ffs((int)down) - 1) * kBlock);
         }
-    } else if (downs && threadIdx.x == 0) {
+    } else if (downs && threadIdx.x == 0 && *(volatile uint32_t *)&flags[3] < (uint32_t)kMaxRuns) {
         atomicAdd((uint32_t *)&flags[3], downs);        // too many for a list of runs
     }
     block_max_into(diff, (uint32_t *)&flags[2]);

@@ -1048,7 +1048,7 @@ __global__ __launch_bounds__(kBlock) void k_seg_bounds(const K *keys, size_t n, 
 // pairs with 27 low bits 0.99 ms, 1.9e8 32-bit pairs 1.37); 16 keys x 8 waves, with keys and values side by side in LDS, left
 // two waves to a SIMD free (1.24 and 1.63 ms), and with one of them after the other the registers did (1.13 and 1.56).
 constexpr int kLocalSortWaves = 16;
-constexpr int kBucketBits = 12, kBucketMax = 32;
+constexpr int kBucketBits = 12, kBucketMax = 32, kAtATime = 4;
 template <typename LK>
 struct LocalSort {
     static constexpr int items = sizeof(LK) == 8 ? 4 : 8;
@@ -1059,7 +1059,7 @@ template <typename LK>
 struct LocalSortShared {
     __align__(16) uint16_t whist[kLocalSortWaves][kRadix];
     uint32_t wave_tot[4], bucket_tot[kLocalSortWaves];
-    LK buf[LocalSort<LK>::cap];      // the words that are compared, then the keys, then the values
+    LK buf[LocalSort<LK>::cap + kAtATime];      // the words that are compared (read a few at a time, beyond the last), then the keys, then the values
 };
 // Sorts cnt keys of sort_bits bits (stable): item r of lane l in wave w is number (w * rows + r) * 64 + l.  In the end the keys
 // stand in S.buf in their order, rank[r] is the place of key r there (of the key that came last to this thread, if there
@@ -1152,7 +1152,13 @@ __device__ __forceinline__ void local_sort(LocalSortShared<LK> &S, LK (&key)[Loc
                         const uint32_t b0 = b ? s_end[b - 1] : 0u, b1 = s_end[b];
                         const LK self = word_of(key[r], idx);
                         uint32_t at = b0;
-                        for (uint32_t p = b0; p < b1; ++p) at += sbuf[p] < self ? 1u : 0u;
+                        for (uint32_t p = b0; p < b1; p += kAtATime) {
+                            LK x[kAtATime];
+#pragma unroll
+                            for (int k = 0; k < kAtATime; ++k) x[k] = sbuf[p + k];
+#pragma unroll
+                            for (int k = 0; k < kAtATime; ++k) at += p + k < b1 && x[k] < self ? 1u : 0u;
+                        }
                         rank[r] = at;
                     }
                 }

@@ -6,9 +6,12 @@
 // spanning forest, contraction -- between barriers, and the host hears of it when it is over.  The arithmetic, its order
 // and every tie are those of the stage kernels, so the results are the same bit for bit.
 //
-// Bounded by barriers and LDS latency (one CU works).  Measured per round before the tries of the separation were dealt out
-// evenly: 84 us at 7254 edges (540 through the stage kernels), 48 at 4958 with a forest (1240), 30 at 438 with message
-// passing (390 to 600), 14 at 36 edges; with that, all rounds of a 128^2 long-range grid took 281 instead of 347 us.
+// Bounded by barriers, LDS latency and the instructions that sixteen waves on one CU issue, so what counts is that a step
+// of a short list takes few of them: loops over a thread's items end where the list does, triangles' slots and contracted
+// edges find their places by counting and comparing instead of by passes, and barriers wait for LDS only.  Measured per round,
+// with passes and loops of full length | as it is: 36 edges 17 | 10 us, 438 edges with a triangle 31 | 20, 2678 edges 43 | 33,
+// 6210 edges 120 | 93 (through the stage kernels 250 to 1100 whatever the size); all rounds of a 32^2 grid 220 | 130, of a 128^2
+// long-range grid 285 | 202, of the contraction of a 300x301 one 323 | 258.
 #include "prim.h"
 #include "steps.h"
 
@@ -29,10 +32,11 @@ static_assert(kTailEdges % kTailThreads == 0 && kTailNodes % (2 * kTailThreads) 
 
 // the work area (in 4-byte words), used by one step after another:
 //   sort        keys [0, 8192), values [8192, 16384), digit counts of the 16 waves [16384, 20480)
-//   separation  row ends [0, 3136) (16 bits each), cursors [3136, 6272), adjacency [6272, 14464) (16-bit edge numbers),
+//   separation  row ends [0, 3136) (16 bits each), cursors, then first edges of the rows [3136, 6272), adjacency [6272, 14464) (16-bit edge numbers),
 //               triangles found: keys [14464, 16512), third edges [16512, 17536) (16 bits each), entries each
 //               repulsive edge is tried with [17536, 21632) (16 bits each), their sums per thread [21632, 22656)
-//   messages    sorted slots as the sort left them, messages [14336, 20480)
+//   messages    slots of every edge [0, 8192), as they came [8192, 11264) and in order [11264, 14336) (16 bits each), or sorted
+//               slots as the sort left them; messages [14336, 20480)
 //   matching    rank words [0, 12288), mates [12288, 15360) (16 bits each)
 //   forest      rank words [0, 12288), later depth, parent, edge to it (16 bits each) [0, 9216); components
 //               [12288, 15360), hooks [15360, 18432), forest bits [18432, 18688), removed bits [18688, 18944)
@@ -40,12 +44,13 @@ static_assert(kTailEdges % kTailThreads == 0 && kTailNodes % (2 * kTailThreads) 
 constexpr int kWorkWords = 22656;
 constexpr int kSortVal = kTailEdges, kSortHist = 2 * kTailEdges;
 constexpr int kSepCur = 3136, kSepAdj = 6272, kSepKey = 14464, kSepThird = 16512, kSepTries = 17536, kSepBefore = 21632;
-constexpr int kMsg = 14336;
+constexpr int kMsg = 14336, kArrived = 8192, kSlot = 11264;
 constexpr int kMate = 12288, kComp = 12288, kHook = 15360, kInForest = 18432, kRemoved = 18688;
 constexpr int kDepth = 0, kUp = 3072, kUpEdge = 6144;
 constexpr int kRep = 0, kNew = 6144;
 static_assert(kSepCur * 2 >= kTailNodes + 1 && kSepAdj + kTailEdges <= kSepKey && kSepThird + kTailTriangles / 2 <= kSepTries &&
               kSepTries + kTailEdges / 2 <= kSepBefore && kSepBefore + kTailThreads <= kWorkWords, "separation");
+static_assert(kArrived >= kTailEdges && kArrived + 3 * kTailTriangles / 2 <= kSlot && kSlot + 3 * kTailTriangles / 2 <= kMsg && kMsg <= kSepKey, "slots");
 static_assert(kSortVal + 3 * kTailTriangles <= kMsg && kMsg + 3 * kTailTriangles <= kWorkWords, "messages");
 static_assert(2 * kTailNodes <= kMate && kMate + kTailNodes / 2 <= kHook && kHook + kTailNodes / 2 <= kInForest, "matching, forest");
 static_assert(kInForest + kTailEdges / 32 <= kRemoved && kRemoved + kTailEdges / 32 <= kWorkWords, "forest bits");
@@ -57,7 +62,7 @@ struct TailShared {
     uint32_t work[kWorkWords];
     uint32_t wave[kTailWaves];
     uint32_t digit[4];
-    uint32_t count[4];
+    uint32_t count[6];
 };
 
 struct TailArgs {
@@ -167,33 +172,26 @@ __device__ __forceinline__ int tail_bits(uint32_t n)      // bits for values in 
     return n <= 2u ? 1 : 32 - __clz((int)(n - 1u));
 }
 
-// place of an edge in the sorted list, or -1
-__device__ __forceinline__ int tail_find(const TailShared &S, int m, uint32_t key)
-{
-    int lo = 0, hi = m;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (S.key[mid] < key) lo = mid + 1; else hi = mid;
-    }
-    return lo < m && S.key[lo] == key ? lo : -1;
-}
+// items of a list of `count` that a thread takes: loops over a thread's items end there (uniform), so that a short list does
+// not pay for the longest one
+__device__ __forceinline__ int tail_per_thread(int count) { return (count + kTailThreads - 1) / kTailThreads; }
 
 // Triangles with one repulsive edge (a round that separates up to length 3).  Returns their number if it is at most
 // kTailTriangles; they are in work[kSepKey..) -- (first edge, second edge) -- and work[kSepThird..), in any order.
 // With more of them a thread stops at the first one it has no place for, and the return is some larger number.
 __device__ __forceinline__ uint32_t tail_triangles(TailShared &S, int n, int m, uint32_t &n_attractive, uint32_t &n_repulsive)
 {
-    const int tid = (int)threadIdx.x;
+    const int tid = (int)threadIdx.x, per = tail_per_thread(m), per_node = tail_per_thread(n);
     uint16_t *row_end = (uint16_t *)S.work, *adj = (uint16_t *)(S.work + kSepAdj);
-    for (int k = tid; k < kSepAdj; k += kTailThreads) S.work[k] = 0;      // degrees and cursors
+    for (int k = tid; 2 * k < n; k += kTailThreads) S.work[k] = 0;      // degrees
     if (tid < 3) S.count[tid] = 0;
-    __syncthreads();
+    lds_barrier();
     uint32_t pos = 0, neg = 0;
 #pragma unroll
     for (int q = 0; q < kTailItems; ++q) {
+        if (q >= per) break;
         const int e = tid + q * kTailThreads;
-        if (e >= m) continue;
-        const float c = S.cost[e];
+        const float c = e < m ? S.cost[e] : 0.0f;
         neg += c < 0.0f ? 1u : 0u;
         if (c > 0.0f) {
             ++pos;
@@ -203,25 +201,32 @@ __device__ __forceinline__ uint32_t tail_triangles(TailShared &S, int n, int m, 
         }
     }
     pos = wave_sum(pos); neg = wave_sum(neg);
-    if (tail_lane() == 0) { atomicAdd(&S.count[0], pos); atomicAdd(&S.count[1], neg); }
-    __syncthreads();
+    if (tail_lane() == 0 && (pos | neg)) { atomicAdd(&S.count[0], pos); atomicAdd(&S.count[1], neg); }
+    lds_barrier();
     n_attractive = S.count[0]; n_repulsive = S.count[1];
     if (n_attractive == 0 || n_repulsive == 0) return 0;
     uint32_t deg[kTailNodeItems], mine = 0, all;
 #pragma unroll
-    for (int q = 0; q < kTailNodeItems; ++q) { deg[q] = row_end[tid * kTailNodeItems + q]; mine += deg[q]; }
+    for (int q = 0; q < kTailNodeItems; ++q) {
+        const int v = tid * per_node + q;
+        deg[q] = q < per_node && v < n ? row_end[v] : 0u;
+        mine += deg[q];
+    }
     uint32_t run = tail_scan(mine, &all, S.wave);
     uint16_t *cursor = (uint16_t *)(S.work + kSepCur);
 #pragma unroll
     for (int q = 0; q < kTailNodeItems; ++q) {
-        const int v = tid * kTailNodeItems + q;
-        cursor[v] = (uint16_t)run;
-        run += deg[q];
-        row_end[v] = (uint16_t)run;
+        const int v = tid * per_node + q;
+        if (q < per_node && v < n) {
+            cursor[v] = (uint16_t)run;
+            run += deg[q];
+            row_end[v] = (uint16_t)run;
+        }
     }
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int q = 0; q < kTailItems; ++q) {
+        if (q >= per) break;
         const int e = tid + q * kTailThreads;
         if (e < m && S.cost[e] > 0.0f) {
             const uint32_t u = S.key[e] >> kNodeBits, v = S.key[e] & kNodeMask;
@@ -231,11 +236,22 @@ __device__ __forceinline__ uint32_t tail_triangles(TailShared &S, int n, int m, 
             adj[(av >> (16 * (v & 1))) & 0xffffu] = (uint16_t)e;
         }
     }
-    __syncthreads();
+    lds_barrier();
     // Every repulsive edge is tried with each entry of the shorter of its rows; the tries are dealt out evenly over the
-    // threads (an edge per thread and turn left most of a wave waiting for its longest row).
-    uint16_t *tries = (uint16_t *)(S.work + kSepTries), *third = (uint16_t *)(S.work + kSepThird);
-    uint32_t *before = S.work + kSepBefore;      // tries of the edges of the threads in front; thread t: edges 8t .. 8t+7
+    // threads (an edge per thread and turn left most of a wave waiting for its longest row), a stretch of them to each, which
+    // finds its first edge once.  The third edge is looked for in its row of the list; the rows begin at row_first, which
+    // takes the cursors' place.
+    uint16_t *row_first = cursor, *tries = (uint16_t *)(S.work + kSepTries), *third = (uint16_t *)(S.work + kSepThird);
+    uint32_t *before = S.work + kSepBefore;      // tries of the edges of the threads in front; thread t: edges t * per ..
+    for (int v = tid; v <= n; v += kTailThreads) {
+        const uint32_t key = (uint32_t)v << kNodeBits;
+        int lo = 0, hi = m;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (S.key[mid] < key) lo = mid + 1; else hi = mid;
+        }
+        row_first[v] = (uint16_t)lo;
+    }
     auto rows_of = [&](int e, uint32_t &s, uint32_t &o, int &s0) {      // s: the end with the shorter row, which starts at s0
         s = S.key[e] >> kNodeBits; o = S.key[e] & kNodeMask;
         s0 = s ? row_end[s - 1] : 0;
@@ -245,45 +261,136 @@ __device__ __forceinline__ uint32_t tail_triangles(TailShared &S, int n, int m, 
         return len;
     };
     uint32_t sum = 0, all_tries;
+    uint32_t s, o;
+    int s0;
 #pragma unroll
     for (int q = 0; q < kTailItems; ++q) {
-        const int e = tid * kTailItems + q;
-        uint32_t s, o;
-        int s0;
-        const uint32_t len = e < m && S.cost[e] < 0.0f ? (uint32_t)rows_of(e, s, o, s0) : 0u;
-        tries[e] = (uint16_t)len;
-        sum += len;
+        if (q >= per) break;
+        const int e = tid * per + q;
+        if (e < m) {
+            const uint32_t len = S.cost[e] < 0.0f ? (uint32_t)rows_of(e, s, o, s0) : 0u;
+            tries[e] = (uint16_t)len;
+            sum += len;
+        }
     }
     before[tid] = tail_scan(sum, &all_tries, S.wave);
-    __syncthreads();
-    for (uint32_t p = (uint32_t)tid; p < all_tries; p += kTailThreads) {
-        int t = 0;      // the last thread with at most p tries before its own
+    lds_barrier();
+    const uint32_t stretch = (all_tries + kTailThreads - 1) / kTailThreads, first = (uint32_t)tid * stretch;
+    const uint32_t last = first + stretch < all_tries ? first + stretch : all_tries;
+    if (first < last) {
+        int t = 0;      // the last thread with at most `first` tries before its own
 #pragma unroll
         for (int step = kTailThreads / 2; step > 0; step >>= 1)
-            if (before[t + step] <= p) t += step;
-        int e = t * kTailItems;
-        uint32_t k = p - before[t];
-        for (uint32_t len = tries[e]; k >= len; len = tries[++e]) k -= len;
-        uint32_t s, o;
-        int s0;
+            if (before[t + step] <= first) t += step;
+        int e = t * per;
+        uint32_t k = first - before[t], len = tries[e];
+        while (k >= len) { k -= len; len = tries[++e]; }
         (void)rows_of(e, s, o, s0);
-        const int a = adj[s0 + (int)k];
-        const uint32_t lo = S.key[a] >> kNodeBits, hi = S.key[a] & kNodeMask, x = lo == s ? hi : lo;
-        const int b = tail_find(S, m, min(x, o) << kNodeBits | max(x, o));
-        if (b < 0 || !(S.cost[b] > 0.0f)) continue;
-        // the edges (u,v), (u,w), (v,w) of a triangle u < v < w stand in this order in the list
-        const int e0 = min(e, min(a, b)), e2 = max(e, max(a, b)), e1 = e + a + b - e0 - e2;
-        const uint32_t at = atomicAdd(&S.count[2], 1u);
-        if (at >= (uint32_t)kTailTriangles) break;
-        S.work[kSepKey + at] = (uint32_t)e0 << 13 | (uint32_t)e1;
-        third[at] = (uint16_t)e2;
+        for (uint32_t p = first;;) {
+            const int a = adj[s0 + (int)k];
+            const uint32_t u = S.key[a] >> kNodeBits, v = S.key[a] & kNodeMask, x = u == s ? v : u, x0 = min(x, o);
+            const uint32_t wanted = x0 << kNodeBits | max(x, o);
+            int lo = row_first[x0], hi = row_first[x0 + 1];
+            const int end = hi;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (S.key[mid] < wanted) lo = mid + 1; else hi = mid;
+            }
+            if (lo < end && S.key[lo] == wanted && S.cost[lo] > 0.0f) {
+                // the edges (u,v), (u,w), (v,w) of a triangle u < v < w stand in this order in the list
+                const int b = lo, e0 = min(e, min(a, b)), e2 = max(e, max(a, b)), e1 = e + a + b - e0 - e2;
+                const uint32_t at = atomicAdd(&S.count[2], 1u);
+                if (at >= (uint32_t)kTailTriangles) break;
+                S.work[kSepKey + at] = (uint32_t)e0 << 13 | (uint32_t)e1;
+                third[at] = (uint16_t)e2;
+            }
+            if (++p >= last) break;
+            if (++k >= len) {      // there are tries left, so an edge behind this one has some
+                k = 0;
+                do len = tries[++e]; while (len == 0);
+                (void)rows_of(e, s, o, s0);
+            }
+        }
     }
-    __syncthreads();
+    lds_barrier();
     return S.count[2];
 }
 
-// `iters` iterations of message passing over the T <= kTailTriangles triangles tail_triangles left behind
-__device__ __forceinline__ void tail_messages(TailShared &S, int m, uint32_t T, int iters)
+// Places of a stable sort of the keys of the items in `in` (bit r: item r) by their `bits` bits, as local_sort does it: the top
+// bits make buckets, and a key finds its place among its bucket's by comparing a word that ends with the place it came from,
+// which is base + 64 r.  Keys and values are then in work[0..) and work[kSortVal..); false, and nothing done, if a bucket
+// is too long.
+constexpr int kTailBucketBits = 12, kTailBucketMax = 160;
+__device__ __forceinline__ bool tail_bucket_sort(TailShared &S, const uint32_t (&key)[kTailItems], const uint32_t (&val)[kTailItems], uint32_t in,
+                                                 int rows, uint32_t base, int bits)
+{
+    static_assert((1 << kTailBucketBits) == 4 * kTailThreads && kSortHist + 2 * kTailThreads <= kWorkWords, "two words of two counters to a thread");
+    const int tid = (int)threadIdx.x, shift = bits > kTailBucketBits ? bits - kTailBucketBits : 0;
+    uint32_t *count = S.work + kSortHist;
+    const uint16_t *end = reinterpret_cast<const uint16_t *>(count);
+    count[2 * tid] = 0; count[2 * tid + 1] = 0;
+    if (tid == 0) S.count[3] = 0;
+    lds_barrier();
+    uint32_t at[kTailItems];
+#pragma unroll
+    for (int r = 0; r < kTailItems; ++r) {
+        if (r >= rows) break;
+        if (in & (1u << r)) {
+            const uint32_t b = key[r] >> shift;
+            at[r] = (atomicAdd(&count[b >> 1], 1u << (16 * (b & 1))) >> (16 * (b & 1))) & 0xffffu;      // at most 8192 in all: no carry
+        }
+    }
+    lds_barrier();
+    const uint32_t x = count[2 * tid], y = count[2 * tid + 1];
+    const uint32_t c0 = x & 0xffffu, c1 = x >> 16, c2 = y & 0xffffu, c3 = y >> 16;
+    if (max(max(c0, c1), max(c2, c3)) > (uint32_t)kTailBucketMax) S.count[3] = 1;
+    uint32_t all;
+    const uint32_t run = tail_scan(c0 + c1 + c2 + c3, &all, S.wave);
+    if (S.count[3]) {      // uniform; nobody changes it before the next barrier
+        lds_barrier();
+        return false;
+    }
+    count[2 * tid] = (run + c0) | (run + c0 + c1) << 16;
+    count[2 * tid + 1] = (run + c0 + c1 + c2) | (run + c0 + c1 + c2 + c3) << 16;
+    lds_barrier();
+    const uint32_t low = (1u << shift) - 1u;
+#pragma unroll
+    for (int r = 0; r < kTailItems; ++r) {
+        if (r >= rows) break;
+        if (in & (1u << r)) {
+            const uint32_t b = key[r] >> shift;
+            S.work[(b ? end[b - 1] : 0u) + at[r]] = (key[r] & low) << 13 | (base + (uint32_t)r * 64u);
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < kTailItems; ++r) {
+        if (r >= rows) break;
+        if (in & (1u << r)) {
+            const uint32_t b = key[r] >> shift, b0 = b ? end[b - 1] : 0u, b1 = end[b];
+            const uint32_t self = (key[r] & low) << 13 | (base + (uint32_t)r * 64u);
+            at[r] = b0;
+            for (uint32_t p = b0; p < b1; p += 4) {      // four words under way at a time
+                uint32_t x[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) x[k] = S.work[p + k];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) at[r] += p + k < b1 && x[k] < self ? 1u : 0u;
+            }
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < kTailItems; ++r) {
+        if (r >= rows) break;
+        if (in & (1u << r)) { S.work[at[r]] = key[r]; S.work[kSortVal + at[r]] = val[r]; }
+    }
+    lds_barrier();
+    return true;
+}
+
+// message passing where an edge has many slots: triangles, then slots, put into order by sorts
+__device__ __forceinline__ void tail_messages_sorted(TailShared &S, int m, uint32_t T, int iters)
 {
     const int tid = (int)threadIdx.x, lane = tail_lane(), w = tail_wave();
     const int ebits = tail_bits((uint32_t)m);
@@ -362,46 +469,184 @@ __device__ __forceinline__ void tail_messages(TailShared &S, int m, uint32_t T, 
     }
 }
 
-// handshake matching; mates (0xffff: none) in work[kMate..); returns the number of pairs
+// The slots of an edge -- its places in triangles -- in the order of the triangles, by counting and comparing (see k_messages_few):
+// work[e]: the first of edge e's slots | their number << 16, slot[]: 3 * triangle + which.  The triangles stay where they
+// are.  false, and nothing else done, if an edge has more than kTailRun slots.
+constexpr uint32_t kTailRun = 48;
+__device__ __forceinline__ bool tail_slots(TailShared &S, int m, uint32_t T, uint32_t (&e)[kTriItems][3])
+{
+    const int tid = (int)threadIdx.x, per = tail_per_thread(m);
+    uint16_t *arrived = (uint16_t *)(S.work + kArrived), *slot = (uint16_t *)(S.work + kSlot);
+    for (int k = tid; k < m; k += kTailThreads) S.work[k] = 0;
+    if (tid == 0) S.count[3] = 0;
+    uint32_t key[kTriItems], at[kTriItems][3];
+#pragma unroll
+    for (int q = 0; q < kTriItems; ++q) {
+        const uint32_t t = (uint32_t)(tid + q * kTailThreads);
+        key[q] = t < T ? S.work[kSepKey + t] : 0u;
+        e[q][0] = key[q] >> 13; e[q][1] = key[q] & 8191u;
+        e[q][2] = t < T ? reinterpret_cast<const uint16_t *>(S.work + kSepThird)[t] : 0u;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < kTriItems; ++q)
+        if ((uint32_t)(tid + q * kTailThreads) < T)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) at[q][k] = atomicAdd(&S.work[e[q][k]], 1u);
+    lds_barrier();
+    uint32_t c[kTailItems], mine = 0, all, longest = 0;
+#pragma unroll
+    for (int q = 0; q < kTailItems; ++q) {
+        const int x = tid * per + q;
+        c[q] = q < per && x < m ? S.work[x] : 0u;
+        mine += c[q];
+        longest = max(longest, c[q]);
+    }
+    if (longest > kTailRun) S.count[3] = 1;
+    uint32_t run = tail_scan(mine, &all, S.wave);
+    if (S.count[3]) {      // uniform
+        lds_barrier();
+        return false;
+    }
+#pragma unroll
+    for (int q = 0; q < kTailItems; ++q) {
+        const int x = tid * per + q;
+        if (q < per && x < m) S.work[x] = run | c[q] << 16;
+        run += c[q];
+    }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < kTriItems; ++q) {
+        const uint32_t t = (uint32_t)(tid + q * kTailThreads);
+        if (t < T)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) arrived[(S.work[e[q][k]] & 0xffffu) + at[q][k]] = (uint16_t)t;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < kTriItems; ++q) {
+        const uint32_t t = (uint32_t)(tid + q * kTailThreads);
+        if (t < T)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const uint32_t x = S.work[e[q][k]], p0 = x & 0xffffu, p1 = p0 + (x >> 16);
+                uint32_t to = p0;
+                for (uint32_t p = p0; p < p1; ++p) to += S.work[kSepKey + arrived[p]] < key[q] ? 1u : 0u;
+                slot[to] = (uint16_t)(3u * t + (uint32_t)k);
+            }
+    }
+    lds_barrier();
+    return true;
+}
+
+// `iters` iterations of message passing over the T <= kTailTriangles triangles tail_triangles left behind
+__device__ __forceinline__ void tail_messages(TailShared &S, int m, uint32_t T, int iters)
+{
+    const int tid = (int)threadIdx.x, per = tail_per_thread(m);
+    uint32_t e[kTriItems][3];
+    if (!tail_slots(S, m, T, e)) return tail_messages_sorted(S, m, T, iters);
+    const uint16_t *slot = (const uint16_t *)(S.work + kSlot);
+    uint32_t run[kTailItems];      // of the edges tid, tid + kTailThreads ..: first slot | slots << 16
+#pragma unroll
+    for (int q = 0; q < kTailItems; ++q) {
+        const int x = tid + q * kTailThreads;
+        run[q] = q < per && x < m ? S.work[x] : 0u;
+        if (run[q] >> 16) S.cost[x] = S.cost[x] / (float)(run[q] >> 16);      // from here to the last iteration: the share
+    }
+    lds_barrier();
+    float *msg = reinterpret_cast<float *>(S.work + kMsg);
+    float a[kTriItems] = {}, b[kTriItems] = {}, c[kTriItems] = {};
+    for (int it = 1; it <= iters; ++it) {
+#pragma unroll
+        for (int q = 0; q < kTriItems; ++q) {
+            const uint32_t t = (uint32_t)(tid + q * kTailThreads);
+            if (t < T) {
+                a[q] = a[q] + S.cost[e[q][0]]; b[q] = b[q] + S.cost[e[q][1]]; c[q] = c[q] + S.cost[e[q][2]];
+                float oa, ob, oc;
+                triangle_to_edges(a[q], b[q], c[q], oa, ob, oc);
+                msg[3 * t] = oa; msg[3 * t + 1] = ob; msg[3 * t + 2] = oc;
+            }
+        }
+        lds_barrier();
+#pragma unroll
+        for (int q = 0; q < kTailItems; ++q) {
+            if (q >= per) break;
+            const uint32_t len = run[q] >> 16, p0 = run[q] & 0xffffu;
+            if (len) {
+                float acc = 0.0f;
+                for (uint32_t p = p0; p < p0 + len; ++p) acc = acc + msg[slot[p]];
+                S.cost[tid + q * kTailThreads] = it == iters ? acc : acc / (float)len;
+            }
+        }
+        lds_barrier();
+    }
+}
+
+// handshake matching (see k_handshake_finish); mates (0xffff: none) in work[kMate..); returns the number of pairs
 __device__ __forceinline__ uint32_t tail_matching(TailShared &S, int n, int m, float tau, int cap)
 {
-    const int tid = (int)threadIdx.x;
+    constexpr unsigned long long kMatched = ~0ull;      // in a node's word: no candidate's rank
+    const int tid = (int)threadIdx.x, per = tail_per_thread(m);
     unsigned long long *best = reinterpret_cast<unsigned long long *>(S.work);
     uint16_t *mate = (uint16_t *)(S.work + kMate);
-    for (int k = tid; k < kTailNodes / 2; k += kTailThreads) S.work[kMate + k] = 0xffffffffu;
+    uint32_t *any = S.count + 4;      // [2]: candidates left in this round, in the next one
+    for (int k = tid; 2 * k < n; k += kTailThreads) S.work[kMate + k] = 0xffffffffu;
+    for (int v = tid; v < n; v += kTailThreads) best[v] = 0ull;
+    if (tid < 2) any[tid] = 0u;
     uint32_t alive = 0, made = 0, uv[kTailItems];
     unsigned long long rank[kTailItems];
 #pragma unroll
     for (int q = 0; q < kTailItems; ++q) {
         const int e = tid + q * kTailThreads;
         uv[q] = 0; rank[q] = 0;
-        if (e < m && S.cost[e] > tau) {
+        if (q < per && e < m && S.cost[e] > tau) {
             alive |= 1u << q;
             uv[q] = S.key[e];
             rank[q] = edge_rank(S.cost[e], (uint32_t)e);
         }
     }
-    for (int r = 0; r < cap; ++r) {
-        if (!__syncthreads_or(alive != 0u)) break;
-        for (int v = tid; v < n; v += kTailThreads) best[v] = 0ull;
-        __syncthreads();
+    lds_barrier();
+    auto propose = [&] {
 #pragma unroll
-        for (int q = 0; q < kTailItems; ++q)
+        for (int q = 0; q < kTailItems; ++q) {
+            if (q >= per) break;
             if (alive & (1u << q)) {
                 atomicMax(&best[uv[q] >> kNodeBits], rank[q]);
                 atomicMax(&best[uv[q] & kNodeMask], rank[q]);
             }
-        __syncthreads();
+        }
+    };
+    if (__ballot(alive != 0u) && tail_lane() == 0) any[0] = 1u;
+    propose();
+    for (int r = 0; r < cap; ++r) {
+        lds_barrier();
+        if (!any[r & 1]) break;      // uniform
+        if (tid == 0) any[(r + 1) & 1] = 0u;
 #pragma unroll
-        for (int q = 0; q < kTailItems; ++q)
+        for (int q = 0; q < kTailItems; ++q) {
+            if (q >= per) break;
             if (alive & (1u << q)) {
                 const uint32_t u = uv[q] >> kNodeBits, v = uv[q] & kNodeMask;
-                if (best[u] == rank[q] && best[v] == rank[q]) { mate[u] = (uint16_t)v; mate[v] = (uint16_t)u; ++made; }
+                if (best[u] == rank[q] && best[v] == rank[q]) {
+                    mate[u] = (uint16_t)v; mate[v] = (uint16_t)u;
+                    best[u] = kMatched; best[v] = kMatched;      // whoever reads it in this step has lost either way
+                    ++made;
+                }
             }
-        __syncthreads();
+        }
+        lds_barrier();
 #pragma unroll
-        for (int q = 0; q < kTailItems; ++q)
-            if ((alive & (1u << q)) && (mate[uv[q] >> kNodeBits] != 0xffffu || mate[uv[q] & kNodeMask] != 0xffffu)) alive &= ~(1u << q);
+        for (int q = 0; q < kTailItems; ++q) {
+            if (q >= per) break;
+            if (alive & (1u << q)) {
+                const uint32_t u = uv[q] >> kNodeBits, v = uv[q] & kNodeMask;
+                if (best[u] == kMatched || best[v] == kMatched) alive &= ~(1u << q);
+                else { best[u] = 0ull; best[v] = 0ull; }
+            }
+        }
+        if (__ballot(alive != 0u) && tail_lane() == 0) any[(r + 1) & 1] = 1u;
+        lds_barrier();
+        propose();
     }
     uint32_t all;
     (void)tail_scan(made, &all, S.wave);
@@ -568,27 +813,30 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_rounds(TailArgs A)
         if (ns) {
             // new numbers: ranks of the representatives
             uint32_t root = 0, n_new;
+            const int per_node = tail_per_thread(n);
 #pragma unroll
             for (int q = 0; q < kTailNodeItems; ++q) {
-                const int v = tid * kTailNodeItems + q;
+                if (q >= per_node) break;
+                const int v = tid * per_node + q;
                 root += v < n && rep[v] == (uint32_t)v ? 1u : 0u;
             }
             uint32_t run = tail_scan(root, &n_new, S.wave);
 #pragma unroll
             for (int q = 0; q < kTailNodeItems; ++q) {
-                const int v = tid * kTailNodeItems + q;
+                if (q >= per_node) break;
+                const int v = tid * per_node + q;
                 if (v < n && rep[v] == (uint32_t)v) fnew[v] = (uint16_t)run++;
             }
-            __syncthreads();
+            lds_barrier();
             for (int v = tid; v < n; v += kTailThreads)
                 if (rep[v] != (uint32_t)v) fnew[v] = fnew[rep[v]];
-            __syncthreads();
+            lds_barrier();
             for (int v = tid; v < A.n; v += kTailThreads) A.fmap[v] = fnew[A.fmap[v]];   // always the same thread's entries
-            // relabelled edges, loops behind everything else; sorted, runs summed in order
+            // relabelled edges without the loops, sorted, runs summed in order
             const int nb = tail_bits(n_new);
             const uint32_t fmask = (1u << nb) - 1u, loop_key = 0xffffffffu >> (32 - 2 * nb);
             const uint32_t rows = ((uint32_t)m + kTailThreads - 1) / kTailThreads, base = (uint32_t)w * rows * 64u + (uint32_t)lane;
-            uint32_t key[kTailItems] = {}, val[kTailItems] = {}, stays = 0, kept;
+            uint32_t key[kTailItems] = {}, val[kTailItems] = {}, stays = 0, kept;      // bit r: edge r stays
 #pragma unroll
             for (int r = 0; r < kTailItems; ++r) {
                 const uint32_t e = base + (uint32_t)r * 64u;
@@ -596,11 +844,11 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_rounds(TailArgs A)
                     const uint32_t a = fnew[S.key[e] >> kNodeBits], b = fnew[S.key[e] & kNodeMask];
                     key[r] = a == b ? loop_key : min(a, b) << nb | max(a, b);
                     val[r] = __float_as_uint(S.cost[e]);
-                    stays += a != b ? 1u : 0u;
+                    stays |= a != b ? 1u << r : 0u;
                 }
             }
-            (void)tail_scan(stays, &kept, S.wave);
-            tail_sort(S, key, val, (uint32_t)m, 2 * nb);
+            (void)tail_scan((uint32_t)__popc(stays), &kept, S.wave);
+            if (!tail_bucket_sort(S, key, val, stays, (int)rows, base, 2 * nb)) tail_sort(S, key, val, (uint32_t)m, 2 * nb);      // loops come last
             const uint32_t *skey = S.work, *sval = S.work + kSortVal;
             uint32_t heads = 0, place[kTailItems], carry = 0;
 #pragma unroll

@@ -909,6 +909,26 @@ def test_solve_rounds_in_one_workgroup(rama, oracle32, n, m, pos, later, iters, 
     assert len(rounds) == got["rounds"] and rounds[-1]["n_edges_aug"] >= got["n_edges_final"]
 
 
+# rounds in one workgroup that fill its buckets and runs: a repulsive edge in `pages` triangles (up to 48 slots of an edge are put
+# into order by comparing, more by sorts), a node in `leaves` edges (a bucket of up to 160 keys is)
+@pytest.mark.parametrize("pages,leaves", [(47, 10), (48, 159), (49, 161), (50, 400), (200, 1000), (600, 5000), (3, 6000)])
+def test_long_rows_and_runs_in_one_workgroup(rama, oracle32, pages, leaves):
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(pages + leaves)
+    page = 2 + np.arange(pages)
+    hub = 2 + pages
+    leaf = hub + 1 + np.arange(min(leaves, 6140 - hub))
+    spare = leaf[-1] + 1
+    i = np.concatenate([[0], np.zeros(pages), np.ones(pages), np.full(leaf.size, hub), [spare]]).astype(np.int32)
+    j = np.concatenate([[1], page, page, leaf, [spare + 1]]).astype(np.int32)
+    c = np.concatenate([[-50.0], 1 + rng.random(2 * pages), rng.random(leaf.size) - 0.5, [5.0]]).astype(np.float32)
+    for later in (3, 0):
+        kw = dict(max_cycle_len_first=0, mp_iters_first=0, max_cycle_len_later=later, mp_iters_later=4, max_rounds=6)
+        want = oracle32.solve(int(spare + 2), i, j, c, **kw)
+        got = rama.solve(int(spare + 2), i, j, c, params=default_params(**kw))
+        assert np.array_equal(np_(got["labels"]), want["labels"]) and got["rounds"] == want["rounds"]
+
+
 @pytest.mark.parametrize("n,m,pos", [(200, 8100, 0.7), (700, 8100, 0.8)])
 def test_dense_rounds_are_handed_back(rama, oracle32, n, m, pos):
     """Rounds of more than 2048 triangles are not for one workgroup: it gets another try only behind a round of 16384 or

@@ -699,6 +699,7 @@ struct alignas(16) HashStage {
     // would sit in the adjacency array if the row's items were numbered from that on
     int32_t rowA[G], offA[G], fromA[G];
     int32_t rowB[G], offB[G], fromB[G];        // the same of N+(vL)
+    std::conditional_t<(G > 32), uint64_t, uint32_t> others[G];      // of N+(v0)'s entries: the bits of N+(vL) but the one of the entry itself
 };
 // LDS that one wave shares: orders what its lanes wrote before against what they read behind
 __device__ __forceinline__ void wave_lds_fence()
@@ -770,15 +771,93 @@ __device__ __forceinline__ uint64_t hash_look(const HashStage<G, SLOTS> &S, uint
     if constexpr (HashStage<G, SLOTS>::W == 2) m |= (uint64_t)S.mask[1][h] << 32;
     return m;
 }
-// the last k with off[k] <= w (off ascends, entries behind the last row hold the largest int)
+// A lane's next kHashBatch items, G apart, take every step together: one after the other, each would wait for its own chain
+// (the row by bisection, the entry, the first place of the table).
+// Measured with item after item, a search for every item's row and a second look for every pair that closes a 5-cycle | as it is,
+// count + fill in us: 6-NN graph of 3*10^5 points 118 + 139 | 90 + 108, of 10^6 402 + 455 | 304 + 353, 512^2 long-range grid 298 + 176
+// | 270 + 145, 180x181 one behind a dual round (64 lanes) 226 + 218 | 199 + 183.
+constexpr int kHashBatch = 4;
+// row[q]: the row of item w[q], one of the items base .. base + G * kHashBatch - 1; off[k] (`mine`: lane k's) items come before row
+// k, the largest int behind the last row.  No row is empty: its node's neighbour is in it.
 template <int G>
-__device__ __forceinline__ int row_of(const int32_t *off, int32_t w)
+__device__ __forceinline__ void rows_of_items(const int32_t *off, int32_t mine, uint32_t base, const int32_t (&w)[kHashBatch], int (&row)[kHashBatch])
 {
-    int k = 0;
+    if constexpr (G * kHashBatch == 64) {      // a bit for the first item of every row: rows are counted, not searched
+        const uint32_t at = (uint32_t)mine - base;
+        uint32_t lo = at < 32u ? 1u << at : 0u, hi = at >= 32u && at < 64u ? 1u << (at - 32u) : 0u;
+        lo |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x128, 0xf, 0xf, false);      // row_ror:8 4 2 1: all sixteen lanes' bits
+        hi |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x128, 0xf, 0xf, false);
+        lo |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x124, 0xf, 0xf, false);
+        hi |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x124, 0xf, 0xf, false);
+        lo |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x122, 0xf, 0xf, false);
+        hi |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x122, 0xf, 0xf, false);
+        lo |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)lo, 0x121, 0xf, 0xf, false);
+        hi |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)hi, 0x121, 0xf, 0xf, false);
+        const int in_front = __popcll(lanes_ballot<G>((uint32_t)mine < base)) - 1;
 #pragma unroll
-    for (int step = G / 2; step > 0; step >>= 1)
-        if (off[k + step] <= w) k += step;
-    return k;
+        for (int q = 0; q < kHashBatch; ++q) {
+            const uint32_t p = (uint32_t)w[q] - base;      // bits 0 .. p
+            row[q] = in_front + __popc(lo & (p >= 31u ? ~0u : (2u << p) - 1u)) + __popc(p >= 32u ? hi & (p >= 63u ? ~0u : (2u << (p - 32u)) - 1u) : 0u);
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < kHashBatch; ++q) row[q] = 0;
+#pragma unroll
+        for (int step = G / 2; step > 0; step >>= 1) {
+            int32_t x[kHashBatch];
+#pragma unroll
+            for (int q = 0; q < kHashBatch; ++q) x[q] = off[row[q] + step];
+#pragma unroll
+            for (int q = 0; q < kHashBatch; ++q) row[q] += x[q] <= w[q] ? step : 0;
+        }
+    }
+}
+// v[q] (< 0: none) get their places in the table, and `bit[q]` in the mask there
+template <int G, int SLOTS>
+__device__ __forceinline__ void hash_enter_items(HashStage<G, SLOTS> &S, const int32_t (&v)[kHashBatch], const int (&bit)[kHashBatch])
+{
+    constexpr int W = HashStage<G, SLOTS>::W;
+    uint32_t h[kHashBatch], old[kHashBatch];
+#pragma unroll
+    for (int q = 0; q < kHashBatch; ++q) {
+        h[q] = hash_slot<SLOTS>((uint32_t)v[q]);
+        old[q] = v[q] >= 0 ? atomicCAS(&S.key[h[q]], kNoKey, (uint32_t)v[q]) : kNoKey;
+    }
+#pragma unroll
+    for (int q = 0; q < kHashBatch; ++q)
+        if (v[q] >= 0) {
+            while (old[q] != kNoKey && old[q] != (uint32_t)v[q]) {
+                h[q] = (h[q] + 1) & (SLOTS - 1);
+                old[q] = atomicCAS(&S.key[h[q]], kNoKey, (uint32_t)v[q]);
+            }
+            atomicOr(&S.mask[W == 2 ? bit[q] >> 5 : 0][h[q]], 1u << (bit[q] & 31));
+        }
+}
+// hash_look for v[q]
+template <int G, int SLOTS>
+__device__ __forceinline__ void hash_look_items(const HashStage<G, SLOTS> &S, const int32_t (&v)[kHashBatch], uint64_t (&m)[kHashBatch])
+{
+    uint32_t h[kHashBatch], k[kHashBatch];
+#pragma unroll
+    for (int q = 0; q < kHashBatch; ++q) {
+        h[q] = hash_slot<SLOTS>((uint32_t)v[q]);
+        k[q] = S.key[h[q]];
+        m[q] = S.mask[0][h[q]];
+        if constexpr (HashStage<G, SLOTS>::W == 2) m[q] |= (uint64_t)S.mask[1][h[q]] << 32;
+    }
+#pragma unroll
+    for (int q = 0; q < kHashBatch; ++q)
+        if (k[q] != (uint32_t)v[q]) {
+            m[q] = 0;
+            while (k[q] != kNoKey) {
+                h[q] = (h[q] + 1) & (SLOTS - 1);
+                k[q] = S.key[h[q]];
+                if (k[q] != (uint32_t)v[q]) continue;
+                m[q] = S.mask[0][h[q]];
+                if constexpr (HashStage<G, SLOTS>::W == 2) m[q] |= (uint64_t)S.mask[1][h[q]] << 32;
+                break;
+            }
+        }
 }
 
 struct HashEdge {
@@ -786,6 +865,8 @@ struct HashEdge {
     int dA, dB;
     uint32_t pairs;     // number of (v1, v2) pairs
     int32_t my_v1;      // lane k < dA: rowA[k]
+    int32_t my_off;     // offA[lane]
+    bool three;         // my_v1 is in N+(vL)
     bool live;          // the edge is searched here (valid, both rows non-empty, everything fits)
     bool spilled;       // it does not fit
 };
@@ -797,7 +878,7 @@ __device__ __forceinline__ HashEdge hash_stage(HashStage<G, SLOTS> &S, bool vali
     constexpr int kFlag = G > 32 ? 31 : G - 1;   // bit of the last mask word: in N+(vL)
     const int gl = (int)(threadIdx.x & (G - 1));
     HashEdge E;
-    E.v0 = v0; E.vl = vl; E.my_v1 = -1; E.pairs = 0;
+    E.v0 = v0; E.vl = vl; E.my_v1 = -1; E.my_off = 0x7fffffff; E.three = false; E.pairs = 0;
     int32_t pa0 = 0, pa1 = 0, pb0 = 0, pb1 = 0;
     if (valid) { pa0 = g.ptr[v0]; pa1 = g.ptr[v0 + 1]; pb0 = g.ptr[vl]; pb1 = g.ptr[vl + 1]; }
     E.dA = pa1 - pa0; E.dB = pb1 - pb0;
@@ -826,8 +907,10 @@ __device__ __forceinline__ HashEdge hash_stage(HashStage<G, SLOTS> &S, bool vali
     E.live = search && !E.spilled;
     if (!E.live) return E;
     wave_lds_fence();      // the stage may still be in use for the edge before this one
-    S.rowA[gl] = E.my_v1; S.fromA[gl] = startA - (int32_t)beforeA; S.offA[gl] = gl < E.dA ? (int32_t)beforeA : 0x7fffffff;
-    S.rowB[gl] = v3; S.fromB[gl] = startB - (int32_t)beforeB; S.offB[gl] = gl < E.dB ? (int32_t)beforeB : 0x7fffffff;
+    const int32_t my_offB = gl < E.dB ? (int32_t)beforeB : 0x7fffffff;
+    E.my_off = gl < E.dA ? (int32_t)beforeA : 0x7fffffff;
+    S.rowA[gl] = E.my_v1; S.fromA[gl] = startA - (int32_t)beforeA; S.offA[gl] = E.my_off;
+    S.rowB[gl] = v3; S.fromB[gl] = startB - (int32_t)beforeB; S.offB[gl] = my_offB;
     for (int k = gl * 4; k < SLOTS; k += G * 4) {
         *reinterpret_cast<uint4 *>(&S.key[k]) = make_uint4(kNoKey, kNoKey, kNoKey, kNoKey);
 #pragma unroll
@@ -835,38 +918,59 @@ __device__ __forceinline__ HashEdge hash_stage(HashStage<G, SLOTS> &S, bool vali
     }
     wave_lds_fence();
     if (v3 >= 0) atomicOr(&S.mask[W - 1][hash_enter(S, (uint32_t)v3)], 1u << kFlag);
-    for (uint32_t w = (uint32_t)gl; w < entries; w += G) {
-        const int b = row_of<G>(S.offB, (int32_t)w);
-        const int32_t v2 = g.nb[S.fromB[b] + (int32_t)w];
-        if (v2 == v0 || v2 == vl) continue;
-        atomicOr(&S.mask[W == 2 ? b >> 5 : 0][hash_enter(S, (uint32_t)v2)], 1u << (b & 31));
+    for (uint32_t base = 0; base < entries; base += G * kHashBatch) {
+        int32_t w[kHashBatch], v2[kHashBatch];
+        int row[kHashBatch];
+#pragma unroll
+        for (int q = 0; q < kHashBatch; ++q) w[q] = (int32_t)min(base + (uint32_t)(q * G + gl), entries - 1);
+        rows_of_items<G>(S.offB, my_offB, base, w, row);
+#pragma unroll
+        for (int q = 0; q < kHashBatch; ++q) v2[q] = g.nb[S.fromB[row[q]] + w[q]];
+#pragma unroll
+        for (int q = 0; q < kHashBatch; ++q)
+            if (base + (uint32_t)(q * G + gl) >= entries || v2[q] == v0 || v2[q] == vl) v2[q] = -1;
+        hash_enter_items(S, v2, row);
+    }
+    wave_lds_fence();
+    if (E.my_v1 >= 0) {      // v3 == v1 closes no cycle; it can only come up where v1 is in N+(vL)
+        uint64_t others = ~0ull;
+        E.three = ((hash_look(S, (uint32_t)E.my_v1) >> (G - 1)) & 1ull) != 0;
+        if (E.three) {
+            int lo = 0, hi = E.dB;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (S.rowB[mid] < E.my_v1) lo = mid + 1; else hi = mid;
+            }
+            others = ~(1ull << lo);
+        }
+        S.others[gl] = (std::remove_reference_t<decltype(S.others[0])>)others;
     }
     wave_lds_fence();
     return E;
 }
 
-// what the table says about pair number w: v1, v2, whether (v0,v1,v2,vl) is a cycle, which v3 close a 5-cycle
+// what the table says about the pairs base + q * G + lane: v1, v2, whether (v0,v1,v2,vl) is a cycle, which v3 close a 5-cycle
+// (nothing of the pairs behind the last one)
 template <int G, int SLOTS>
-__device__ __forceinline__ void hash_pair(const HashStage<G, SLOTS> &S, const HashEdge &E, const Adj &g, uint32_t w, int32_t &v1,
-                                          int32_t &v2, bool &four, uint64_t &fives)
+__device__ __forceinline__ void hash_pairs(const HashStage<G, SLOTS> &S, const HashEdge &E, const Adj &g, uint32_t base, int32_t (&v1)[kHashBatch],
+                                           int32_t (&v2)[kHashBatch], bool (&four)[kHashBatch], uint64_t (&fives)[kHashBatch])
 {
     constexpr uint64_t kFlagBit = 1ull << (G - 1);
-    const int a = row_of<G>(S.offA, (int32_t)w);
-    v1 = S.rowA[a];
-    v2 = g.nb[S.fromA[a] + (int32_t)w];
-    const uint64_t m = hash_look(S, (uint32_t)v2);     // v0 and vl are not in the table
-    four = (m & kFlagBit) != 0;
-    fives = m & ~kFlagBit;
-    if (fives) {            // v3 == v1 is no cycle; it can only be among the bits when v1 is in N+(vL)
-        const uint64_t m1 = hash_look(S, (uint32_t)v1);
-        if (m1 & kFlagBit) {
-            int lo = 0, hi = E.dB;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (S.rowB[mid] < v1) lo = mid + 1; else hi = mid;
-            }
-            fives &= ~(1ull << lo);
-        }
+    const uint32_t first = base + (uint32_t)(threadIdx.x & (G - 1));
+    int32_t w[kHashBatch];
+    int row[kHashBatch];
+    uint64_t m[kHashBatch], others[kHashBatch];
+#pragma unroll
+    for (int q = 0; q < kHashBatch; ++q) w[q] = (int32_t)min(first + (uint32_t)(q * G), E.pairs - 1);
+    rows_of_items<G>(S.offA, E.my_off, base, w, row);
+#pragma unroll
+    for (int q = 0; q < kHashBatch; ++q) { v1[q] = S.rowA[row[q]]; v2[q] = g.nb[S.fromA[row[q]] + w[q]]; others[q] = S.others[row[q]]; }
+    hash_look_items(S, v2, m);                         // v0 and vl are not in the table
+#pragma unroll
+    for (int q = 0; q < kHashBatch; ++q) {
+        if (first + (uint32_t)(q * G) >= E.pairs) m[q] = 0;
+        four[q] = (m[q] & kFlagBit) != 0;
+        fives[q] = m[q] & ~kFlagBit & others[q];
     }
 }
 
@@ -894,14 +998,14 @@ __global__ __launch_bounds__(HashBlock<G>::threads) void k_count_cycles_hash(siz
         const HashEdge E = hash_stage(S, true, ri[r], rj[r], g, max_len);
         uint32_t n3 = 0, n4 = 0, n5 = 0;
         if (E.live) {
-            if (E.my_v1 >= 0) n3 = (uint32_t)(hash_look(S, (uint32_t)E.my_v1) >> (G - 1)) & 1u;
-            for (uint32_t w = (uint32_t)gl; w < E.pairs; w += G) {
-                int32_t v1, v2;
-                bool four;
-                uint64_t fives;
-                hash_pair(S, E, g, w, v1, v2, four, fives);
-                n4 += four ? 1u : 0u;
-                n5 += (uint32_t)__popcll(fives);
+            n3 = E.three ? 1u : 0u;
+            for (uint32_t base = 0; base < E.pairs; base += G * kHashBatch) {
+                int32_t v1[kHashBatch], v2[kHashBatch];
+                bool four[kHashBatch];
+                uint64_t fives[kHashBatch];
+                hash_pairs(S, E, g, base, v1, v2, four, fives);
+#pragma unroll
+                for (int q = 0; q < kHashBatch; ++q) { n4 += four[q] ? 1u : 0u; n5 += (uint32_t)__popcll(fives[q]); }
             }
         }
         n3 = lanes_sum<G>(n3); n4 = lanes_sum<G>(n4); n5 = lanes_sum<G>(n5);
@@ -943,7 +1047,7 @@ __global__ __launch_bounds__(HashBlock<G>::threads) void k_fill_cycles_hash(size
         const HashEdge E = hash_stage(S, want3 || want4 || want5, ri[r], rj[r], g, want5 ? max_len : 4);
         if (!E.live) continue;     // nothing to write, or written by the kernels behind this one; the whole group goes on
         if (want3) {
-            const bool c3 = E.my_v1 >= 0 && ((hash_look(S, (uint32_t)E.my_v1) >> (G - 1)) & 1ull);
+            const bool c3 = E.three;
             const uint64_t vote = lanes_ballot<G>(c3);
             if (c3) {
                 int32_t *o = out.p[0] + 3 * (off.p[0][r] + (uint64_t)__popcll(vote & below));
@@ -952,31 +1056,34 @@ __global__ __launch_bounds__(HashBlock<G>::threads) void k_fill_cycles_hash(size
         }
         if (!want4 && !want5) continue;
         uint64_t at4 = want4 ? off.p[1][r] : 0, at5 = want5 ? off.p[2][r] : 0;
-        for (uint32_t base = 0; base < E.pairs; base += G) {   // the same number of turns for every lane of the group
-            const uint32_t w = base + (uint32_t)gl;
-            int32_t v1 = 0, v2 = 0;
-            bool four = false;
-            uint64_t fives = 0;
-            if (w < E.pairs) hash_pair(S, E, g, w, v1, v2, four, fives);
-            if (want4) {
-                const uint64_t vote = lanes_ballot<G>(four);
-                if (four) {
-                    int32_t *o = out.p[1] + 4 * (at4 + (uint64_t)__popcll(vote & below));
-                    o[0] = E.v0; o[1] = v1; o[2] = v2; o[3] = E.vl;
+        for (uint32_t base = 0; base < E.pairs; base += G * kHashBatch) {   // the same number of turns for every lane of the group
+            int32_t v1[kHashBatch], v2[kHashBatch];
+            bool four[kHashBatch];
+            uint64_t fives[kHashBatch];
+            hash_pairs(S, E, g, base, v1, v2, four, fives);
+#pragma unroll
+            for (int q = 0; q < kHashBatch; ++q) {
+                if (base + (uint32_t)(q * G) >= E.pairs) break;      // the same for every lane of the group
+                if (want4) {
+                    const uint64_t vote = lanes_ballot<G>(four[q]);
+                    if (four[q]) {
+                        int32_t *o = out.p[1] + 4 * (at4 + (uint64_t)__popcll(vote & below));
+                        o[0] = E.v0; o[1] = v1[q]; o[2] = v2[q]; o[3] = E.vl;
+                    }
+                    at4 += (uint64_t)__popcll(vote);
                 }
-                at4 += (uint64_t)__popcll(vote);
-            }
-            if (want5) {
-                uint32_t total;
-                const uint32_t before = lanes_exclusive_scan<G>((uint32_t)__popcll(fives), &total);
-                int32_t *o = out.p[2] + 5 * (at5 + before);
-                while (fives) {
-                    const int b = __ffsll((long long)fives) - 1;
-                    fives &= fives - 1;
-                    o[0] = E.v0; o[1] = v1; o[2] = v2; o[3] = S.rowB[b]; o[4] = E.vl;
-                    o += 5;
+                if (want5) {
+                    uint32_t total;
+                    const uint32_t before = lanes_exclusive_scan<G>((uint32_t)__popcll(fives[q]), &total);
+                    int32_t *o = out.p[2] + 5 * (at5 + before);
+                    while (fives[q]) {
+                        const int b = __ffsll((long long)fives[q]) - 1;
+                        fives[q] &= fives[q] - 1;
+                        o[0] = E.v0; o[1] = v1[q]; o[2] = v2[q]; o[3] = S.rowB[b]; o[4] = E.vl;
+                        o += 5;
+                    }
+                    at5 += total;
                 }
-                at5 += total;
             }
         }
     }

@@ -127,6 +127,19 @@ def test_hashed_search_at_its_limits(rama, oracle32, isolated, d_a, d_b, row, lm
 
 # repulsive edges without room in the tables: 4096 and more of those with up to 8 attractive neighbours at their first
 # endpoint are walked by a thread each, fewer of them and those with more neighbours there by a wave each
+# items of a repulsive edge around the 64 that sixteen lanes take at a time, and the 256 of 64 lanes
+@pytest.mark.parametrize("isolated", [0, 4000], ids=["wide", "narrow"])
+@pytest.mark.parametrize("d_a,d_b,row", [(3, 3, 1), (7, 9, 6), (8, 8, 6), (8, 8, 7), (13, 9, 5), (16, 7, 8), (5, 13, 9), (20, 20, 11), (17, 16, 14), (30, 25, 9)])
+@pytest.mark.parametrize("lmax", [4, 5])
+def test_hashed_search_takes_items_in_batches(rama, oracle32, isolated, d_a, d_b, row, lmax):
+    for seed in range(3):
+        n, i, j, c = fan_graph(d_a, d_b, row, isolated, seed)
+        want = oracle32.find_conflicted_cycles(n, i, j, c, lmax)
+        got = rama.find_conflicted_cycles(n, i, j, c, lmax)
+        for w, g in zip(want, got):
+            assert np.array_equal(np_(g), w)
+
+
 @pytest.mark.parametrize("n_edges,row", [(4095, 8), (4096, 8), (4097, 1), (4500, 9), (9000, 4)])
 @pytest.mark.parametrize("lmax,shortest", [(4, False), (5, False), (5, True)])
 def test_edges_without_room_in_the_tables(rama, oracle32, n_edges, row, lmax, shortest):

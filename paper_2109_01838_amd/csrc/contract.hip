@@ -1215,7 +1215,7 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
         const bool finish = na <= kMatchBatchMax;
         int batch = finish ? 0 : 1;
         if (finish)
-            for (uint32_t left = blind ? na / 2 + 1 : na; (left > last_max || (blind && batch == 0 && na > last_max)) && batch < cap - r; left /= 2) ++batch;
+            for (uint32_t left = blind ? na / 2 + 1 : na; (left > last_max || (blind && batch == 0 && na > last_max)) && batch < cap - r; left = left / 5 * 2) ++batch;
         if (batch > kRoundsAhead) batch = kRoundsAhead;
         if (r + batch - first_round > kRoundsAhead) {
             counters_before = std::move(counters);

@@ -617,6 +617,7 @@ rama_status rama_contract(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const
         LAUNCH_TRY(*ctx, "iota");
         const Graph *cur = &g0;
         int32_t n_cur = n_nodes;
+        bool diag_made = false;
         for (;;) {
             if (tail_fits(*cur)) {
                 Buf<int32_t> ftail;
@@ -644,7 +645,7 @@ rama_status rama_contract(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const
             int32_t n_new = n_cur;
             int64_t ns = 0;
             RAMA_TRY(contract_once(*ctx, *cur, params->contract_threshold, params->matching_rounds_cap, params->forest_ratio, fprime,
-                                   n_new, gn, ns));
+                                   n_new, gn, ns, nullptr, repeat ? diag_out : nullptr, &diag_made));
             if (ns == 0) break;
             {
                 ProfScope ps_(*ctx, "k_compose", (double)((size_t)n_nodes * 12));
@@ -661,7 +662,7 @@ rama_status rama_contract(rama_ctx *ctx, int32_t n_nodes, int64_t n_edges, const
         RAMA_TRY(copy_out(*ctx, i_out, cur->i.get(), (size_t)cur->m * 4));
         RAMA_TRY(copy_out(*ctx, j_out, cur->j.get(), (size_t)cur->m * 4));
         RAMA_TRY(copy_out(*ctx, c_out, cur->c.get(), (size_t)cur->m * 4));
-        if (diag_out) RAMA_TRY(contraction_diagonal(*ctx, g0, mapping, n_cur, diag_out));
+        if (diag_out && !diag_made) RAMA_TRY(contraction_diagonal(*ctx, g0, mapping, n_cur, diag_out));
         return finish(*ctx, RAMA_OK);
     };
     return finish(*ctx, body());

@@ -552,8 +552,9 @@ rama_status messages_few(Ctx &ctx, const uint32_t *edges, size_t T, int k_iters,
 rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, const TriangleSurvey &survey, Buf<uint32_t> &slots, TriangleCounts &out);
 
 // a4..a6: one primal update.  fmap[n] -> [0,n_new); n_matched = |S|.  If |S|==0 nothing else is produced.
+// diag (optional): behind a matching it gets the diagonal, [n_new], and *diag_made is set.
 rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, float forest_ratio, Buf<int32_t> &fmap,
-                          int32_t &n_new, Graph &out, int64_t &n_matched, bool *used_forest = nullptr);
+                          int32_t &n_new, Graph &out, int64_t &n_matched, bool *used_forest = nullptr, float *diag = nullptr, bool *diag_made = nullptr);
 
 // Whole rounds -- separation of triangles (optional) with k_iters iterations of message passing, matching or forest,
 // contraction -- on a graph that one workgroup can hold, by a single launch.  fmap[g.n] -> [0, out.n).  out's arrays

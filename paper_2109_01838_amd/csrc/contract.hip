@@ -517,12 +517,16 @@ struct InnerFlag {
 // the scan that follows (kScanTile edges) and leaves the number of edges that are no loops in tile_sums: the scan
 // over NotLoopKey then needs no pass of its own to count them.  It also clears its tile's word of sign_sums, where the sign
 // counts of the contracted costs will go.
+// diag (optional, behind a matching): a new node is a pair, and a canonical list has one edge between its nodes, whose cost is
+// the diagonal's entry.  Collecting the inner edges, sorting them by their node and adding up runs of one were thirteen
+// launches and a wait, 190 us for the 9.7e6 edges of a 127x160x161 grid; a pass of its own 44, here 12.
 // With PARTS > 0 the sort's first digit (the top bits of lo, of which `shift` are left out) is counted on the way, for each of
 // the PARTS tiles of the sort that the workgroup's edges make up: hist[digit][tile].
 template <int PARTS>
 __global__ __launch_bounds__(kBlock) void k_relabel_keys(size_t m, const int32_t *i, const int32_t *j,
                                                          const int32_t *fmap, uint64_t *raw, uint32_t *maxdiff,
-                                                         uint32_t *tile_sums, uint64_t *sign_sums, uint32_t *hist, uint32_t nb, int shift, int bits)
+                                                         uint32_t *tile_sums, uint64_t *sign_sums, uint32_t *hist, uint32_t nb, int shift, int bits,
+                                                         const float *c, float *diag)
 {
     constexpr int kParts = PARTS > 0 ? PARTS : 1, kPartItems = kScanItems / kParts;
     __shared__ uint32_t s_digits[kParts][kRadix];
@@ -550,6 +554,7 @@ __global__ __launch_bounds__(kBlock) void k_relabel_keys(size_t m, const int32_t
             diff = d > diff ? d : diff;
             kept += a != b ? 1u : 0u;
             raw[e] = ((uint64_t)lo << 32) | d;
+            if (diag && a == b) diag[a] = c[e];
         }
         if constexpr (PARTS > 0) {      // rows are nearly in order: most of a wave has the digit of its first lane
             uint64_t left = __ballot(e < m && a != b);
@@ -1499,7 +1504,7 @@ static rama_status components(Ctx &ctx, size_t n, size_t ns, const int32_t *si, 
 // contract_edges for a middle-sized list: five launches and a wait, where counting the digits, counting the heads and the sums
 // as launches of their own were seven.  Contraction of a 300x301 long-range grid to the end 1.72 -> 1.54 ms, 128^2 static solve
 // 2.07 -> 1.99, 512^2 5.46 -> 5.37, 6-NN graph of 10^6 points 9.35 -> 9.24, 61x97x131 volume 5.45 -> 5.29.  *done stays false if some digit holds more edges than a workgroup sorts.
-static rama_status contract_by_digits(Ctx &ctx, const Graph &g, const int32_t *fmap, int nbits, int top_bits, Graph &out, bool *done)
+static rama_status contract_by_digits(Ctx &ctx, const Graph &g, const int32_t *fmap, int nbits, int top_bits, Graph &out, float *diag, bool *done)
 {
     const size_t m = (size_t)g.m;
     const int low_bits = 2 * nbits - top_bits;
@@ -1521,7 +1526,7 @@ static rama_status contract_by_digits(Ctx &ctx, const Graph &g, const int32_t *f
         ProfScope ps_(ctx, "k_rs_hist<relabelled>", (double)(m * 24));      // the count of the sort's one pass as well
         auto relabel = [&](auto kernel) {
             kernel<<<tiles, kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), fmap, raw.get(), words.get(), (uint32_t *)nullptr, out.sign_sums.get(),
-                                                     hist.get(), nb, nbits - top_bits, top_bits);
+                                                     hist.get(), nb, nbits - top_bits, top_bits, g.c.get(), diag);
         };
         if (short_tiles) relabel(k_relabel_keys<2>);
         else relabel(k_relabel_keys<1>);
@@ -1568,7 +1573,7 @@ static rama_status contract_by_digits(Ctx &ctx, const Graph &g, const int32_t *f
 }
 
 // contracted graph of canonical g under fmap (n_new new nodes)
-static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap, int32_t n_new, Graph &out)
+static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap, int32_t n_new, Graph &out, float *diag)
 {
     const size_t m = (size_t)g.m;
     out.n = n_new;
@@ -1580,7 +1585,7 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
     const int top_bits = sort_takes_source(m, m) ? unseen_bits_now(ctx, m, 2 * nbits, (uint64_t)n_new << nbits, &narrow) : 0;
     if (top_bits > 0 && narrow && top_bits <= nbits) {
         bool done = false;
-        RAMA_TRY(contract_by_digits(ctx, g, fmap, nbits, top_bits, out, &done));
+        RAMA_TRY(contract_by_digits(ctx, g, fmap, nbits, top_bits, out, diag, &done));
         if (done) return RAMA_OK;
     }
     ScanPlan<uint32_t> keep;   // the extra word behind the total: largest hi-lo
@@ -1591,7 +1596,7 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
     {
         ProfScope ps_(ctx, "k_relabel_keys", (double)(m * 24));
         k_relabel_keys<0><<<keep.nb, kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), fmap, raw.get(), keep.extra_ptr(),
-                                                           keep.sums.get(), out.sign_sums.get(), (uint32_t *)nullptr, 0u, 0, 0);
+                                                           keep.sums.get(), out.sign_sums.get(), (uint32_t *)nullptr, 0u, 0, 0, g.c.get(), diag);
     }
     LAUNCH_TRY(ctx, "relabel_keys");
     RAMA_TRY((scan_totals<uint32_t>(ctx, NotLoopKey{raw.get()}, keep, keep.sums.get())));   // tile sums: left by k_relabel_keys
@@ -1639,7 +1644,7 @@ static rama_status contract_edges(Ctx &ctx, const Graph &g, const int32_t *fmap,
 }
 
 rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, float forest_ratio, Buf<int32_t> &fmap,
-                          int32_t &n_new, Graph &out, int64_t &n_matched, bool *used_forest)
+                          int32_t &n_new, Graph &out, int64_t &n_matched, bool *used_forest, float *diag, bool *diag_made)
 {
     const size_t n = (size_t)g.n;
     if (used_forest) *used_forest = false;
@@ -1685,8 +1690,12 @@ rama_status contract_once(Ctx &ctx, const Graph &g, float tau, int rounds_cap, f
     }
     mate.reset();
     n_new = (int32_t)((int64_t)g.n - n_matched);   // S has no cycle: every edge of it removes one node, no need to ask the device
-    RAMA_TRY(contract_edges(ctx, g, fmap.get(), n_new, out));
-    return RAMA_OK;
+    if (forest) diag = nullptr;
+    if (diag) {
+        RAMA_TRY(fill<float>(ctx, diag, 0.0f, (size_t)n_new));
+        *diag_made = true;
+    }
+    return contract_edges(ctx, g, fmap.get(), n_new, out, diag);
 }
 
 rama_status contraction_diagonal(Ctx &ctx, const Graph &g, const int32_t *fmap, int32_t n_new, float *diag)

@@ -820,7 +820,7 @@ def test_last_workgroup_of_a_matching(rama, oracle32, n, m, kind, cap):
 # lines where it begins (8192 edges) and ends (2^21); parallel edges that fill buckets of the in-LDS sort, rows far apart and
 # close together (the bits of hi - lo), digits without an edge, nothing left at all
 @pytest.mark.parametrize("n,m,near", [(3000, 8193, 0), (3000, 9217, 5), (200, 19000, 0), (150, 8300, 0), (70000, 196608, 4), (70000, 196609, 4),
-                                      (5000, 197633, 0), (1000000, 300000, 2), (1048577, 300000, 0), (600, 170000, 0), (40000, 2097151, 0)])
+                                      (5000, 197633, 0), (1000000, 300000, 2), (1048577, 300000, 0), (600, 170000, 0), (40000, 2097151, 0), (40000, 2097153, 0)])
 @pytest.mark.parametrize("ratio", [0.0, 1.0], ids=["matching", "forest"])
 def test_contraction_by_digits(rama, oracle32, n, m, near, ratio):
     from paper_2109_01838_amd import default_params
@@ -839,6 +839,7 @@ def test_contraction_by_digits(rama, oracle32, n, m, near, ratio):
     assert got["n_nodes"] == want["n_nodes"] and np.array_equal(np_(got["mapping"]), want["mapping"])
     for k in ("i", "j", "c"):
         assert np.array_equal(np_(got[k]), want[k]), k
+    assert np.array_equal(np_(got["diag"]), want["diag"][: got["n_nodes"]])
 
 
 def test_contraction_leaves_nothing(rama, oracle32):

@@ -127,6 +127,27 @@ def test_hashed_search_at_its_limits(rama, oracle32, isolated, d_a, d_b, row, lm
 
 # repulsive edges without room in the tables: 4096 and more of those with up to 8 attractive neighbours at their first
 # endpoint are walked by a thread each, fewer of them and those with more neighbours there by a wave each
+# common neighbours of a repulsive edge around the sixteen there is room for between counting and writing
+@pytest.mark.parametrize("pages", [0, 1, 15, 16, 17, 31, 32, 33, 200])
+def test_common_neighbours_with_and_without_room(rama, oracle32, pages):
+    sizes = [pages, 3, 16, 17, pages + 1]
+    i, j, c, n = [], [], [], 0
+    rng = np.random.default_rng(pages)
+    for k in sizes:
+        a, b, page = n, n + 1, n + 2 + np.arange(k)
+        i += [[a], np.full(k, a), np.full(k, b)]
+        j += [[b], page, page]
+        c += [[-1.0], 0.5 + rng.random(k), 0.5 + rng.random(k)]
+        n += k + 2
+    i, j = np.concatenate(i).astype(np.int32), np.concatenate(j).astype(np.int32)
+    c = np.concatenate(c).astype(np.float32)
+    want = oracle32.find_conflicted_cycles(n, i, j, c, 3)
+    rama.set_cycle_search(2)
+    got = rama.find_conflicted_cycles(n, i, j, c, 3)
+    rama.set_cycle_search(0)
+    assert np.array_equal(np_(got[0]), want[0]) and want[0].shape[0] == sum(sizes)
+
+
 # items of a repulsive edge around the 64 that sixteen lanes take at a time, and the 256 of 64 lanes
 @pytest.mark.parametrize("isolated", [0, 4000], ids=["wide", "narrow"])
 @pytest.mark.parametrize("d_a,d_b,row", [(3, 3, 1), (7, 9, 6), (8, 8, 6), (8, 8, 7), (13, 9, 5), (16, 7, 8), (5, 13, 9), (20, 20, 11), (17, 16, 14), (30, 25, 9)])

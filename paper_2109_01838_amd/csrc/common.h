@@ -44,22 +44,21 @@ public:
     }
     hipError_t alloc(size_t bytes, void **out)
     {
-        // every block ends with at least 32 readable bytes of slack: kernels fetch short index rows
-        // with 16-byte loads and may read (never use) up to 28 bytes behind the last element
-        bytes = (bytes + 32 + 255) & ~size_t(255);
+        bytes = rounded(bytes);
         if (arena_) return arena_alloc(bytes, out);
-        int best = -1;
-        for (int k = 0; k < (int)free_.size(); ++k)
-            if (free_[k].bytes >= bytes && (best < 0 || free_[k].bytes < free_[best].bytes)) best = k;
-        if (best >= 0 && free_[best].bytes <= 2 * bytes + (size_t(1) << 20)) {
-            *out = free_[best].ptr;
-            used_.push_back(free_[best]);
-            went_live(free_[best].bytes);
-            free_.erase(free_.begin() + best);
-            return hipSuccess;
-        }
         void *p = nullptr;
-        hipError_t e = fresh(&p, bytes);
+        hipError_t e = hipSuccess;
+        do {
+            const int best = smallest_cached(bytes);
+            if (best >= 0 && free_[best].bytes <= 2 * bytes + (size_t(1) << 20)) {
+                *out = free_[best].ptr;
+                used_.push_back(free_[best]);
+                went_live(free_[best].bytes);
+                free_.erase(free_.begin() + best);
+                return hipSuccess;
+            }
+            e = fresh(&p, bytes);
+        } while (e != hipSuccess && take_spares_back());
         if (e != hipSuccess) {  // give cached blocks back to their source and retry once
             trim();
             e = fresh(&p, bytes);
@@ -84,13 +83,40 @@ public:
     // an array turned out to be shorter than what was asked for: in the arena, where memory is short, the rest is given back
     void shorten(void *p, size_t bytes)
     {
-        bytes = (bytes + 32 + 255) & ~size_t(255);
+        bytes = rounded(bytes);
         for (int k = (int)used_.size() - 1; arena_ && k >= 0; --k)
             if (used_[k].ptr == p && used_[k].bytes > bytes) {
                 const Blk rest{(char *)p + bytes, used_[k].bytes - bytes};
                 used_[k].bytes = bytes;
                 live_ -= rest.bytes;
                 arena_release(rest);
+                return;
+            }
+    }
+    // Memory that its holder can do without.  A spare block is one of the cached ones, nothing is asked of their source for
+    // it, and it is taken back -- *slot is null then -- before a request fails: what fits without spares fits with them.
+    size_t cached_blocks(size_t bytes) const
+    {
+        size_t n = 0;
+        for (const Blk &b : free_) n += b.bytes >= rounded(bytes) ? 1 : 0;
+        return n;
+    }
+    bool take_spare(size_t bytes, void **slot)
+    {
+        const int k = smallest_cached(rounded(bytes));
+        if (k < 0) return false;
+        *slot = free_[k].ptr;
+        spares_.push_back({free_[k], slot});
+        went_live(free_[k].bytes);
+        free_.erase(free_.begin() + k);
+        return true;
+    }
+    void release_spare(void **slot)
+    {
+        for (size_t k = 0; k < spares_.size(); ++k)
+            if (spares_[k].slot == slot) {
+                spare_back(spares_[k]);
+                spares_.erase(spares_.begin() + (long)k);
                 return;
             }
     }
@@ -115,6 +141,31 @@ public:
 
 private:
     struct Blk { void *ptr; size_t bytes; };
+    struct Spare { Blk blk; void **slot; };
+    // every block ends with at least 32 readable bytes of slack: kernels fetch short index rows
+    // with 16-byte loads and may read (never use) up to 28 bytes behind the last element
+    static size_t rounded(size_t bytes) { return (bytes + 32 + 255) & ~size_t(255); }
+    // the smallest cached block of at least `bytes` bytes, or -1
+    int smallest_cached(size_t bytes) const
+    {
+        int best = -1;
+        for (int k = 0; k < (int)free_.size(); ++k)
+            if (free_[k].bytes >= bytes && (best < 0 || free_[k].bytes < free_[best].bytes)) best = k;
+        return best;
+    }
+    void spare_back(const Spare &s)
+    {
+        *s.slot = nullptr;
+        live_ -= s.blk.bytes;
+        free_.push_back(s.blk);
+    }
+    bool take_spares_back()
+    {
+        const bool any = !spares_.empty();
+        for (const Spare &s : spares_) spare_back(s);
+        spares_.clear();
+        return any;
+    }
     void went_live(size_t bytes)
     {
         live_ += bytes;
@@ -164,6 +215,7 @@ private:
         }
     }
     std::vector<Blk> free_, used_, holes_;
+    std::vector<Spare> spares_;
     size_t total_ = 0, live_ = 0, peak_live_ = 0;
     void *(*alloc_fn_)(void *, size_t) = nullptr;
     void (*free_fn_)(void *, void *) = nullptr;
@@ -397,6 +449,34 @@ private:
     Pool *ctx_ = nullptr;   // the pool the block came from
     T *ptr_ = nullptr;
     size_t count_ = 0;
+};
+
+// RAII spare blocks of the ctx pool (see Pool::take_spare), all of one size: the arena has none
+template <int MOST>
+class Spares {
+public:
+    Spares() = default;
+    Spares(const Spares &) = delete;
+    Spares &operator=(const Spares &) = delete;
+    ~Spares()
+    {
+        for (int k = 0; k < n_; ++k) pool_->release_spare(&ptr_[k]);
+    }
+    static int available(Ctx &ctx, size_t bytes)
+    {
+        const size_t n = ctx.active->cached_blocks(bytes);
+        return n < (size_t)MOST ? (int)n : MOST;
+    }
+    void take(Ctx &ctx, int n, size_t bytes)
+    {
+        pool_ = ctx.active;
+        while (n_ < n && n_ < MOST && pool_->take_spare(bytes, &ptr_[n_])) ++n_;
+    }
+    void *get(int k) const { return ptr_[k]; }      // null: taken back, or never there
+private:
+    Pool *pool_ = nullptr;
+    void *ptr_[MOST] = {};
+    int n_ = 0;
 };
 
 inline unsigned grid_for(size_t n, int per_block = kBlock) { return (unsigned)((n + per_block - 1) / per_block); }

@@ -1097,28 +1097,65 @@ __global__ __launch_bounds__(HashBlock<G>::threads) void k_fill_cycles_hash(size
 // neighbours.  The shorter row is ascending, so the triangles (v0, v1, vL) come out in list order.
 constexpr int kTriLanes = 16;                    // lanes per repulsive edge (one DPP row)
 constexpr int kTriEdges = kBlock / kTriLanes;    // edges per workgroup
-// The counting pass notes the common neighbours of an edge where there is room for them (`room`, kTriLanes places per edge;
-// optional), and the fill pass copies them instead of searching again: triangles of a 400x301 window graph, 2.4e6 of 2.9e5
-// repulsive edges, count + fill 39 + 44 -> 41 + 20 us.  Lists of more than kTriRoomEdges edges would take more than 256 MB, and the
-// static workspace has none to spare.
-constexpr size_t kTriRoomEdges = size_t(1) << 22;
+// The counting pass notes the common neighbours of an edge where there is room for them, up to kTriLanes of an edge, and the
+// fill pass copies them instead of searching again: triangles of a 400x301 window graph, 2.4e6 of 2.9e5
+// repulsive edges, count + fill 41 + 46 us without and 45 + 26 with it.  The room is what the pool has left of building the adjacency: spare blocks, in each of
+// which every edge has `width` places.
+constexpr int kRoomParts = 6;
+struct TriRoom {
+    int32_t *part[kRoomParts];
+    int width, places;      // of an edge: in a part, in all
+    __device__ __forceinline__ int32_t *place(int k) const      // k < places: place k of edge 0, `width` in front of that of edge 1
+    {
+        int32_t *p = part[0] + k;
+#pragma unroll
+        for (int q = 1; q < kRoomParts; ++q)
+            if (k >= q * width) p = part[q] + (k - q * width);
+        return p;
+    }
+};
+// the room for mr edges that the cached blocks make up, as many places as can be, in the fewest parts
+inline TriRoom tri_room(Ctx &ctx, size_t mr, Spares<kRoomParts> &blocks)
+{
+    TriRoom room = {};
+    int parts = 0;
+    if (ctx.active->is_arena()) return room;
+    for (int w = kTriLanes; w >= 1; --w) {
+        const int want = (kTriLanes + w - 1) / w, have = Spares<kRoomParts>::available(ctx, mr * (size_t)w * 4), p = have < want ? have : want;
+        const int places = p * w < kTriLanes ? p * w : kTriLanes;
+        if (places > room.places) { room.places = places; room.width = w; parts = p; }
+    }
+    blocks.take(ctx, parts, mr * (size_t)room.width * 4);
+    return room;
+}
+// what is left of it: nothing, if a part was taken back
+inline TriRoom tri_room_now(TriRoom room, const Spares<kRoomParts> &blocks)
+{
+    for (int q = 0; q * room.width < room.places; ++q) {
+        room.part[q] = (int32_t *)blocks.get(q);
+        if (!room.part[q]) room.places = 0;
+    }
+    return room;
+}
 template <bool FILL>
 __global__ __launch_bounds__(kBlock) void k_triangles_group(size_t nr, const uint32_t *hit, const int32_t *ri,
                                                             const int32_t *rj, Adj g, uint32_t *cnt0, const uint64_t *off0,
-                                                            int32_t *out0, int32_t *room)
+                                                            int32_t *out0, TriRoom room)
 {
-    const int gl = (int)(threadIdx.x & (kTriLanes - 1));
+    __shared__ int32_t s_note[kTriEdges][kTriLanes];      // found so far, so that a lane writes to one place of the room only
+    const int gl = (int)(threadIdx.x & (kTriLanes - 1)), group = (int)threadIdx.x / kTriLanes;
+    int32_t *const mine = gl < room.places ? room.place(gl) : nullptr;
     // strides (see grid_striding); a group of lanes has the same h throughout
-    for (size_t h = (size_t)blockIdx.x * kTriEdges + threadIdx.x / kTriLanes; h < nr; h += (size_t)gridDim.x * kTriEdges) {
+    for (size_t h = (size_t)blockIdx.x * kTriEdges + group; h < nr; h += (size_t)gridDim.x * kTriEdges) {
         const uint32_t r = hit ? hit[h] : (uint32_t)h;
         uint32_t n = 0;
         if (FILL) n = cnt0[r];
         if (FILL && n == 0) continue;
         const int32_t v0 = ri[r], vl = rj[r];
-        if (FILL && room && n <= (uint32_t)kTriLanes) {
+        if (FILL && n <= (uint32_t)room.places) {
             if ((uint32_t)gl < n) {
                 int32_t *o = out0 + 3 * (off0[r] + (uint64_t)gl);
-                o[0] = v0; o[1] = room[(size_t)r * kTriLanes + gl]; o[2] = vl;
+                o[0] = v0; o[1] = mine[(size_t)r * (size_t)room.width]; o[2] = vl;
             }
             continue;
         }
@@ -1149,11 +1186,16 @@ __global__ __launch_bounds__(kBlock) void k_triangles_group(size_t nr, const uin
                     at += (uint64_t)__popc(vote);
                 } else {
                     const uint32_t k = found + (uint32_t)__popc(vote & ((1u << gl) - 1u));
-                    if (room && common && k < (uint32_t)kTriLanes) room[(size_t)r * kTriLanes + k] = x;
+                    if (common && k < (uint32_t)kTriLanes) s_note[group][k] = x;
                     found += (uint32_t)__popc(vote);
                 }
             }
-        if (!FILL && gl == 0) cnt0[r] = found;
+        if (!FILL) {
+            wave_lds_fence();
+            if (mine && (uint32_t)gl < found) mine[(size_t)r * (size_t)room.width] = s_note[group][gl];
+            wave_lds_fence();
+            if (gl == 0) cnt0[r] = found;
+        }
     }
 }
 
@@ -1276,12 +1318,15 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     bool wide3 = false;
     if constexpr (MAXL == 3)
         wide3 = ctx.cycle_search == 2 || (ctx.cycle_search == 0 && 2 * mp > (size_t)12 * (size_t)n);
-    Buf<int32_t> room;
-    if (wide3 && mr <= kTriRoomEdges && !ctx.active->is_arena()) (void)room.alloc(ctx, mr * kTriLanes);      // none: it is done without
+    ScanPlan<uint64_t> places;      // of triangles
+    if constexpr (MAXL == 3) RAMA_TRY((scan_plan_alloc<uint64_t>(ctx, mr, 0, places)));
+    Spares<kRoomParts> blocks;
+    TriRoom room = {};
+    if (wide3) room = tri_room_now(tri_room(ctx, mr, blocks), blocks);
     if (wide3) {
         ProfScope ps_(ctx, "k_count_triangles_group", search_bytes);
         k_triangles_group<false><<<grid_striding(mr, kTriEdges), kBlock, 0, ctx.stream>>>(mr, (const uint32_t *)nullptr, ri, rj, adj, cp.p[0],
-                                                                                   (const uint64_t *)nullptr, (int32_t *)nullptr, room.get());
+                                                                                   (const uint64_t *)nullptr, (int32_t *)nullptr, room);
     } else if (!hashed) {
         ProfScope ps_(ctx, MAXL == 3 ? "k_count_cycles<3>" : MAXL == 5 ? "k_count_cycles<5>" : "k_count_cycles<7>", search_bytes);
         bool short_rows = false;
@@ -1309,11 +1354,10 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     if constexpr (MAXL == 3) {
         // one list, whose counts (common neighbours) cannot saturate: the total comes back from the scan of the tile sums,
         // and the places are only computed when there is a cycle
-        ScanPlan<uint64_t> places;
-        RAMA_TRY((scan_plan_alloc<uint64_t>(ctx, mr, 0, places)));
         RAMA_TRY((scan_totals<uint64_t>(ctx, PtrInput<uint32_t>{cnt[0].get()}, places)));
         tot[0] = places.total;
         if (tot[0]) RAMA_TRY((scan_store<uint64_t>(ctx, PtrInput<uint32_t>{cnt[0].get()}, places, off[0].get())));
+        places.offs.reset(); places.sums.reset();
     } else {
         Buf<uint64_t> summary;
         RAMA_TRY(summary.alloc(ctx, NL + 1));
@@ -1401,7 +1445,7 @@ rama_status count_and_fill(Ctx &ctx, size_t mr, const int32_t *ri, const int32_t
     if (wide3) {
         ProfScope ps_(ctx, "k_fill_triangles_group", fill_bytes);
         k_triangles_group<true><<<grid_striding(nh, kTriEdges), kBlock, 0, ctx.stream>>>(nh, list_hits ? hit.get() : nullptr, ri, rj, adj, cp.p[0],
-                                                                                  op.p[0], vp.p[0], room.get());
+                                                                                  op.p[0], vp.p[0], tri_room_now(room, blocks));
     } else if (!hashed) {
         ProfScope ps_(ctx, MAXL == 3 ? "k_fill_cycles<3>" : MAXL == 5 ? "k_fill_cycles<5>" : "k_fill_cycles<7>", fill_bytes);
         if (meet && long_cycles)

@@ -1775,6 +1775,79 @@ def test_allocator_callbacks_and_injected_out_of_memory(rama):
     r.close()
 
 
+def test_triangles_of_long_rows_need_no_more_memory(oracle32):
+    """Sixteen lanes an edge note the common neighbours that they count in memory that the call has done with.  Whatever the
+    caller's allocator can give to the workspace and to the results together: where the search by one thread an edge gets
+    through, so does this one, with the same triangles, and no failure is left behind."""
+    import torch
+    from paper_2109_01838_amd import Rama, RamaError
+
+    class Limited(Rama):
+        def __init__(self, limit):
+            self.out, self.peak, self.limit, sizes = 0, 0, limit, {}
+
+            def alloc(nbytes):
+                self.take(nbytes)
+                p = torch.cuda.caching_allocator_alloc(int(nbytes), 0)
+                sizes[p] = nbytes
+                return p
+
+            def free(p):
+                self.out -= sizes.pop(p)
+                torch.cuda.caching_allocator_delete(p)
+            super().__init__("cuda:0", allocator=(alloc, free))
+
+        def take(self, nbytes):
+            if self.out + nbytes > self.limit:
+                raise MemoryError
+            self.out += nbytes
+            self.peak = max(self.peak, self.out)
+
+        def _empty(self, n, dtype):
+            self.take(max(int(n), 1) * 4)
+            return super()._empty(n, dtype)
+
+    def search(g, mode, limit):
+        r = Limited(limit)
+        try:
+            r.set_cycle_search(mode)
+            try:
+                tri = np_(r.find_conflicted_cycles(g["n_nodes"], g["i"], g["j"], g["c"], 3)[0])
+            except (RamaError, MemoryError):
+                return None, r.peak
+            assert r.lib.rama_last_error(r.ctx) == b""
+            return tri, r.peak
+        finally:
+            r.close()
+
+    for h, w in ((40, 41), (130, 131), (310, 231)):       # 4e3, 4e4 and 1.7e5 repulsive edges (edges with triangles are listed from 2^17 on)
+        n, i, j = inputs.grid_edges((h, w), [(0, 1), (0, 2)])
+        parts = [(i, j)]
+        v = np.arange(h * w, dtype=np.int32).reshape(h, w)
+        for a in (1, 2):
+            for b in range(-2, 3):
+                parts.append((v[:h - a, max(0, -b):w - max(0, b)].ravel(), v[a:, max(0, b):w + min(0, b)].ravel()))
+        i, j = (np.concatenate([p[k] for p in parts]) for k in (0, 1))
+        rng = np.random.default_rng(h)
+        g = dict(n_nodes=n, i=i, j=j, c=(rng.random(i.size) + 0.1).astype(np.float32) * np.where(rng.random(i.size) < 0.2, -1, 1).astype(np.float32))
+        for k in "ijc":
+            g[k] = torch.as_tensor(g[k]).cuda()
+        want, peak = search(g, 1, 1 << 40)
+        got, most = search(g, 2, 1 << 40)
+        assert np.array_equal(got, want) and want.shape[0] > 10 * h * w
+        assert most <= peak + (1 << 16), (most, peak)
+        passed = 0
+        for limit in np.linspace(0.8 * peak, peak, 21).astype(np.int64).tolist():
+            want_at, _ = search(g, 1, limit)
+            got_at, _ = search(g, 2, limit)
+            assert got_at is not None or want_at is None, (limit, peak)
+            assert got_at is None or np.array_equal(got_at, want)
+            passed += want_at is not None
+        assert 0 < passed
+    o = oracle32.find_conflicted_cycles(*(g[k] if k == "n_nodes" else np_(g[k]) for k in ("n_nodes", "i", "j", "c")), 3)
+    assert np.array_equal(want, o[0])
+
+
 def test_round_records(rama, oracle32):
     g = CASES["knn_20000"]
     n = g["n_nodes"]

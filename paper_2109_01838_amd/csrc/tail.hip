@@ -56,7 +56,7 @@ static_assert(2 * kTailNodes <= kMate && kMate + kTailNodes / 2 <= kHook && kHoo
 static_assert(kInForest + kTailEdges / 32 <= kRemoved && kRemoved + kTailEdges / 32 <= kWorkWords, "forest bits");
 static_assert(kSortHist + kTailWaves * kRadix <= kWorkWords, "sort");
 
-struct TailShared {
+struct alignas(8) TailShared {
     uint32_t key[kTailEdges];      // lo << 13 | hi, ascending
     float cost[kTailEdges];
     uint32_t work[kWorkWords];
@@ -64,6 +64,7 @@ struct TailShared {
     uint32_t digit[4];
     uint32_t count[6];
 };
+static_assert(alignof(TailShared) % 8 == 0 && offsetof(TailShared, work) % 8 == 0, "the work area holds 64-bit rank words, whose LDS atomics fault elsewhere");
 
 struct TailArgs {
     int32_t n, m;

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <functional>
 #include <string>
+#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -500,14 +501,26 @@ inline int bits_for(uint64_t n)
     return b;
 }
 
-// the mailbox as kernels see it (pinned host memory is mapped at the same address on the device)
-inline uint64_t *mailbox(Ctx &ctx) { return (uint64_t *)((char *)ctx.pinned + 2048); }
+// A word of the mailbox.  Kernels write it by mail_put and mail_put_half and in no other way: what an ordinary store leaves
+// in a cache need not be with the host when the message's number is.
+class MailWord {
+public:
+    MailWord &operator=(const MailWord &) = delete;
+private:
+    uint64_t word_;
+    friend __device__ void mail_put(MailWord *, uint64_t);
+    friend __device__ void mail_put_half(MailWord *, unsigned, uint32_t);
+};
+static_assert(sizeof(MailWord) == 8 && !std::is_assignable<MailWord &, uint64_t>::value && !std::is_assignable<MailWord &, MailWord>::value, "no plain stores");
+// the mailbox as kernels see it (pinned host memory is mapped at the same address on the device), and as the host reads it
+inline MailWord *mailbox(Ctx &ctx) { return (MailWord *)((char *)ctx.pinned + 2048); }
+inline const volatile uint64_t *mail_words(Ctx &ctx) { return (const volatile uint64_t *)mailbox(ctx); }
 
 // waits until message `seq` is in the mailbox: bounded polling, then the stream synchronisation.  (The
 // per-kernel timers are collected at the synchronisation that ends every call of the library.)
 inline rama_status wait_mail(Ctx &ctx, uint64_t seq)
 {
-    volatile uint64_t *m = mailbox(ctx);
+    const volatile uint64_t *m = mail_words(ctx);
     {
         // polls as long as it takes the kernels in front of the message; the clock is only there to end the
         // wait if the message never comes (a failed launch, a fault): the synchronisation below then reports it

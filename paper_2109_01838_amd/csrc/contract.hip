@@ -273,7 +273,7 @@ __host__ __device__ constexpr uint32_t finish_max(int n_nodes) { return n_nodes 
 constexpr int kNumberMax = 1 << 15, kNumberRows = kNumberMax / kFinishThreads;
 __global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint32_t *n_first, CandList list, int32_t *mate,
                                                                      int rounds_left, int n_nodes, int32_t *fmap,
-                                                                     const unsigned long long *counters, int n_counters, uint64_t *mail, uint64_t seq)
+                                                                     const unsigned long long *counters, int n_counters, MailWord *mail, uint64_t seq)
 {
     constexpr unsigned long long kMatched = ~0ull;      // in a node's word: no candidate's rank
     __shared__ unsigned long long s_best[kFinishDirect];
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_handshake_finish(const uint3
 }
 
 // mail[1]: candidates in a round's lists | in the longest of them << 32, mail[2]: pairs made in the round
-__global__ __launch_bounds__(64) void k_look_at_lists(const unsigned long long *counts, uint64_t *mail, uint64_t seq)
+__global__ __launch_bounds__(64) void k_look_at_lists(const unsigned long long *counts, MailWord *mail, uint64_t seq)
 {
     const unsigned long long x = lane_id() < (int)kLists ? counts[(size_t)lane_id() * kListWords] : 0ull;
     const uint32_t n = wave_sum((uint32_t)x), pairs = wave_sum((uint32_t)(x >> 32));
@@ -725,7 +725,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_sum_digit(const uin
 constexpr int kJoinThreads = 512;
 __global__ __launch_bounds__(kJoinThreads) void k_join_digits(const uint32_t *starts, const uint32_t *counts, const int32_t *ti, const int32_t *tj, const float *tc,
                                                               int32_t *io, int32_t *jo, float *co, unsigned long long *sign_sums,
-                                                              const uint32_t *oversize, uint64_t *mail, uint64_t seq)
+                                                              const uint32_t *oversize, MailWord *mail, uint64_t seq)
 {
     constexpr int kTiles = LocalSort<uint32_t>::cap / kScanTile + 1;
     __shared__ uint32_t s_sum[kJoinThreads / 64], s_sign[kTiles];
@@ -1094,7 +1094,7 @@ __global__ __launch_bounds__(kBlock) void k_mark_conflicts_short(size_t m, const
 }
 
 // components of the forest edges that were not removed; their number goes to the host
-__global__ __launch_bounds__(kForestThreads) void k_forest_components(uint32_t na, Cands a, const uint8_t *state, int32_t *rep, uint64_t *mail, uint64_t seq)
+__global__ __launch_bounds__(kForestThreads) void k_forest_components(uint32_t na, Cands a, const uint8_t *state, int32_t *rep, MailWord *mail, uint64_t seq)
 {
     __shared__ uint32_t s_kept;
     const uint32_t tid = threadIdx.x;
@@ -1259,7 +1259,7 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
             best_next.swap(best_after);
         }
         const uint64_t seq = ++ctx.mail_seq;
-        const volatile uint64_t *mail = mailbox(ctx);
+        const volatile uint64_t *mail = mail_words(ctx);
         if (!finish) {
             k_look_at_lists<<<1, 64, 0, ctx.stream>>>(counts(r - 1), mailbox(ctx), seq);
             LAUNCH_TRY(ctx, "look_at_lists");
@@ -1337,7 +1337,7 @@ static rama_status forest_short(Ctx &ctx, const Graph &g, float tau, Candidates 
     }
     LAUNCH_TRY(ctx, "forest_components");
     RAMA_TRY(wait_mail(ctx, seq));
-    n_set = (int64_t)((const volatile uint64_t *)mailbox(ctx))[1];
+    n_set = (int64_t)mail_words(ctx)[1];
     return RAMA_OK;
 }
 
@@ -1560,7 +1560,7 @@ static rama_status contract_by_digits(Ctx &ctx, const Graph &g, const int32_t *f
     }
     LAUNCH_TRY(ctx, "join_digits");
     RAMA_TRY(wait_mail(ctx, seq));
-    const volatile uint64_t *mail = mailbox(ctx);
+    const volatile uint64_t *mail = mail_words(ctx);
     if (mail[2]) {
         ctx.sorts_unseen = false;
         out.i.reset(); out.j.reset(); out.c.reset(); out.sign_sums.reset();

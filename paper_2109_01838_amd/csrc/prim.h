@@ -144,16 +144,20 @@ __device__ __forceinline__ T block_sum(T v)
 // The words of a message go to the host past the caches, and its number follows when they have arrived there: every wave
 // waits for its own words.  A fence for the whole system would write the L2 back as well, of which the host sees nothing: with
 // one in front of the number and one behind it a message of sixteen waves took 4 us.
-template <typename T>
-__device__ __forceinline__ void mail_put(T *word, T v) { __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+__device__ __forceinline__ void mail_put(MailWord *to, uint64_t v) { __hip_atomic_store(&to->word_, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+// 4-byte word k behind `to`
+__device__ __forceinline__ void mail_put_half(MailWord *to, unsigned k, uint32_t v)
+{
+    __hip_atomic_store((uint32_t *)&to->word_ + k, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // closes message `seq`, all of whose words the calling wave has put into mail[1..]
-__device__ __forceinline__ void mail_send_wave(uint64_t *mail, uint64_t seq)
+__device__ __forceinline__ void mail_send_wave(MailWord *mail, uint64_t seq)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     if (lane_id() == 0) mail_put(mail, seq);
 }
 // closes message `seq`: everything this workgroup put into mail[1..] before is visible to the host first
-__device__ __forceinline__ void mail_send(uint64_t *mail, uint64_t seq)
+__device__ __forceinline__ void mail_send(MailWord *mail, uint64_t seq)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -161,12 +165,11 @@ __device__ __forceinline__ void mail_send(uint64_t *mail, uint64_t seq)
 }
 
 // `words` 4-byte words from device memory into the mailbox, and `more` from another place behind them
-static __global__ __launch_bounds__(kBlock) void k_publish(const uint32_t *src, unsigned words, const uint32_t *src2, unsigned more, uint64_t *mail,
+static __global__ __launch_bounds__(kBlock) void k_publish(const uint32_t *src, unsigned words, const uint32_t *src2, unsigned more, MailWord *mail,
                                                            uint64_t seq)
 {
-    uint32_t *dst = (uint32_t *)(mail + 1);
-    for (unsigned k = threadIdx.x; k < words; k += kBlock) mail_put(dst + k, src[k]);
-    for (unsigned k = threadIdx.x; k < more; k += kBlock) mail_put(dst + words + k, src2[k]);
+    for (unsigned k = threadIdx.x; k < words; k += kBlock) mail_put_half(mail + 1, k, src[k]);
+    for (unsigned k = threadIdx.x; k < more; k += kBlock) mail_put_half(mail + 1, words + k, src2[k]);
     mail_send(mail, seq);
 }
 
@@ -179,7 +182,7 @@ inline rama_status read_back(Ctx &ctx, void *host, const void *dev, size_t bytes
     k_publish<<<1, kBlock, 0, ctx.stream>>>((const uint32_t *)dev, (unsigned)(bytes / 4), (const uint32_t *)dev2, (unsigned)(more / 4), mailbox(ctx), seq);
     LAUNCH_TRY(ctx, "publish");
     RAMA_TRY(wait_mail(ctx, seq));
-    memcpy(host, (const void *)(mailbox(ctx) + 1), bytes + more);
+    memcpy(host, (const void *)(mail_words(ctx) + 1), bytes + more);
     return RAMA_OK;
 }
 
@@ -259,7 +262,7 @@ __device__ __forceinline__ TO item_or_last(const F &f, size_t k, size_t n)
 // total reaches the host without a copy.
 template <typename TO, typename F>
 __global__ __launch_bounds__(kBlock) void k_scan_reduce(F f, TO *block_sums, size_t n, TO *offs, uint32_t *ticket,
-                                                        uint64_t *mail, uint64_t seq, const TO *words, int extra)
+                                                        MailWord *mail, uint64_t seq, const TO *words, int extra)
 {
     const size_t base = (size_t)blockIdx.x * kScanTile + threadIdx.x;
     TO s = 0, x[kScanItems];
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(kBlock) void k_scan_reduce(F f, TO *block_sums, siz
 // the scan of the tile sums as a launch of its own (long arrays: the election above would make every
 // workgroup of the reduce launch wait for its sum to be visible, which costs more than a launch)
 template <typename TO>
-__global__ __launch_bounds__(kBlock) void k_scan_mid(const TO *in, TO *out, unsigned nb, uint64_t *mail, uint64_t seq, const TO *words, int extra)
+__global__ __launch_bounds__(kBlock) void k_scan_mid(const TO *in, TO *out, unsigned nb, MailWord *mail, uint64_t seq, const TO *words, int extra)
 {
     const TO total = scan_tile_sums<TO, false>(in, out, nb);
     if (mail) {
@@ -354,12 +357,12 @@ rama_status scan_offsets(Ctx &ctx, F f, TO *sums, TO *offs, size_t n, unsigned n
     {
         ProfScope ps_(ctx, kernel_name<F>("k_scan_reduce"), (double)(n * F::bytes));
         k_scan_reduce<TO, F><<<nb, kBlock, 0, ctx.stream>>>(f, sums, n, offs, fused ? ctx.ticket : nullptr,
-                                                           (uint64_t *)nullptr, 0, (const TO *)nullptr, 0);
+                                                           (MailWord *)nullptr, 0, (const TO *)nullptr, 0);
     }
     LAUNCH_TRY(ctx, "scan_reduce");
     if (!fused && nb <= kScanMidMax) {
         ProfScope ps_(ctx, "k_scan_mid", (double)((size_t)nb * 2 * sizeof(TO)));
-        k_scan_mid<TO><<<1, kBlock, 0, ctx.stream>>>(sums, offs, nb, (uint64_t *)nullptr, 0, (const TO *)nullptr, 0);
+        k_scan_mid<TO><<<1, kBlock, 0, ctx.stream>>>(sums, offs, nb, (MailWord *)nullptr, 0, (const TO *)nullptr, 0);
         LAUNCH_TRY(ctx, "scan_mid");
     } else if (!fused) {
         RAMA_TRY((exclusive_scan<TO, PtrInput<TO>>(ctx, PtrInput<TO>{sums}, offs, nb)));
@@ -460,13 +463,13 @@ rama_status scan_totals(Ctx &ctx, F f, ScanPlan<TO> &plan, const TO *presums = n
             LAUNCH_TRY(ctx, "scan_mid");
         }
         RAMA_TRY(wait_mail(ctx, seq));
-        const volatile uint64_t *m = mailbox(ctx);
+        const volatile uint64_t *m = mail_words(ctx);
         for (int k = 0; k < 1 + plan.extra; ++k) back[k] = (TO)m[1 + k];
     } else if (plan.n > 0) {
         if (!presummed) {
             ProfScope ps_(ctx, kernel_name<F>("k_scan_reduce"), (double)(plan.n * F::bytes));
             k_scan_reduce<TO, F><<<nb, kBlock, 0, ctx.stream>>>(f, plan.sums.get(), plan.n, (TO *)nullptr, (uint32_t *)nullptr,
-                                                               (uint64_t *)nullptr, 0, (const TO *)nullptr, 0);
+                                                               (MailWord *)nullptr, 0, (const TO *)nullptr, 0);
         }
         LAUNCH_TRY(ctx, "scan_reduce");
         RAMA_TRY((exclusive_scan<TO, PtrInput<TO>>(ctx, PtrInput<TO>{sums}, plan.offs.get(), nb)));

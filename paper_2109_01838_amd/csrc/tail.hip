@@ -75,7 +75,7 @@ struct TailArgs {
     int32_t *fmap;                 // [n]: node of the first graph -> node of the last
     int separate, iters, cap, max_rounds;
     float tau, forest_ratio;
-    uint64_t *mail;
+    MailWord *mail;
     uint64_t seq;
 };
 
@@ -788,7 +788,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_rounds(TailArgs A)
     }
     for (int v = tid; v < A.n; v += kTailThreads) A.fmap[v] = v;
     __syncthreads();
-    uint64_t *rec = A.mail + 3;
+    MailWord *rec = A.mail + 3;
     uint32_t status = kTailMore, rounds = 0;
     while (rounds < (uint32_t)A.max_rounds) {
         const uint64_t t0 = wall_clock64();
@@ -920,7 +920,7 @@ rama_status tail_rounds(Ctx &ctx, const Graph &g, Graph &out, bool separate, int
     }
     LAUNCH_TRY(ctx, "tail_rounds");
     RAMA_TRY(wait_mail(ctx, seq));
-    const volatile uint64_t *mail = mailbox(ctx);
+    const volatile uint64_t *mail = mail_words(ctx);
     auto lo = [](uint64_t x) { return (int64_t)(uint32_t)x; };
     auto hi = [](uint64_t x) { return (int64_t)(x >> 32); };
     res.status = (int)lo(mail[1]);

@@ -314,7 +314,7 @@ struct FewShared {
 // Nothing is done for more than kFewTriangles, nor for triangles in any order with a run longer than kLongRun (mail[1] is then
 // kFewTriangles + 1).
 __global__ __launch_bounds__(kFewThreads) void k_messages_few(const uint32_t *list, const uint32_t *counter, uint32_t n_triangles, const uint64_t *survey,
-                                                              int iters, float *ce, float *ct, const uint32_t *flag, uint64_t *mail, uint64_t seq)
+                                                              int iters, float *ce, float *ct, const uint32_t *flag, MailWord *mail, uint64_t seq)
 {
     __shared__ FewShared S;
     const int tid = (int)threadIdx.x, lane = lane_id(), w = tid >> 6;
@@ -552,7 +552,7 @@ rama_status triangle_survey(Ctx &ctx, const Graph &g, const int32_t *rowptr, boo
         RAMA_TRY(signs.alloc(ctx, n_sums));
         ProfScope ps_(ctx, kernel_name<SignFlags>("k_scan_reduce"), (double)(m * 4));
         k_scan_reduce<uint64_t, SignFlags><<<n_sums, kBlock, 0, ctx.stream>>>(SignFlags{g.c.get()}, signs.get(), m, (uint64_t *)nullptr, (uint32_t *)nullptr,
-                                                                             (uint64_t *)nullptr, 0, (const uint64_t *)nullptr, 0);
+                                                                             (MailWord *)nullptr, 0, (const uint64_t *)nullptr, 0);
     }
     LAUNCH_TRY(ctx, "scan_reduce");
     {
@@ -581,7 +581,7 @@ rama_status triangles_few(Ctx &ctx, Graph &g, const int32_t *rowptr, const Trian
     }
     LAUNCH_TRY(ctx, "messages_few");
     RAMA_TRY(wait_mail(ctx, seq));
-    const volatile uint64_t *mail = mailbox(ctx);
+    const volatile uint64_t *mail = mail_words(ctx);
     const uint64_t found = mail[1];
     RAMA_TRY(take_survey(ctx, out, mail[2], mail[4], survey));
     if (out.dense || found > (uint64_t)kFewTriangles) return RAMA_OK;
@@ -601,7 +601,7 @@ rama_status messages_few(Ctx &ctx, const uint32_t *edges, size_t T, int k_iters,
     }
     LAUNCH_TRY(ctx, "messages_few");
     RAMA_TRY(wait_mail(ctx, seq));
-    *raised = ((const volatile uint64_t *)mailbox(ctx))[3] != 0;
+    *raised = mail_words(ctx)[3] != 0;
     return RAMA_OK;
 }
 
@@ -626,7 +626,7 @@ rama_status triangles_list(Ctx &ctx, const Graph &g, const int32_t *rowptr, cons
         }
         LAUNCH_TRY(ctx, "scan_mid");
         RAMA_TRY(wait_mail(ctx, seq));
-        const volatile uint64_t *mail = mailbox(ctx);
+        const volatile uint64_t *mail = mail_words(ctx);
         for (int k = 0; k < 3; ++k) back[k] = mail[1 + k];
     } else {
         RAMA_TRY((exclusive_scan<uint64_t, PtrInput<uint64_t>>(ctx, PtrInput<uint64_t>{sums.get()}, offs.get(), nb)));

@@ -81,7 +81,8 @@ public:
                 return;
             }
     }
-    // an array turned out to be shorter than what was asked for: in the arena, where memory is short, the rest is given back
+    // an array turned out to be shorter than what was asked for: in the arena, where memory is short, the rest is given back.
+    // Blocks of another source go back whole only, so there the array keeps its block until it is released.
     void shorten(void *p, size_t bytes)
     {
         bytes = rounded(bytes);

@@ -8,7 +8,8 @@
 //         on the shrinking list of edges whose endpoints are both still free (one kernel per round
 //         on lists of up to 2^20: compaction of the survivors fused with their next proposals,
 //         every candidate finding out itself whether its ends were matched; longer lists are
-//         accepted by a kernel in front of it; the last 8192 in one workgroup); the list carries
+//         accepted by a kernel in front of it; the last 8192 on up to 16384 nodes, or 4096 on more, by
+//         one workgroup); the list carries
 //         endpoints and rank word, so a round streams it and touches no edge array.
 //   f'  : connected components of (V,S) by min-label hooking + pointer jumping; a component is
 //         represented by its smallest node; new ids are the ranks of the representatives.
@@ -721,7 +722,7 @@ __global__ __launch_bounds__(kLocalSortWaves * 64, 8) void k_sum_digit(const uin
 }
 
 // The digits' edges one behind the other, a workgroup to a digit; sign counts per kScanTile edges (see k_reduce_runs); the
-// last workgroup tells the host: mail[1] number of edges, mail[2]: *oversize, mail[3]: number of edges before they were added up.
+// last workgroup tells the host: mail[1] number of edges, mail[2]: *oversize.
 constexpr int kJoinThreads = 512;
 __global__ __launch_bounds__(kJoinThreads) void k_join_digits(const uint32_t *starts, const uint32_t *counts, const int32_t *ti, const int32_t *tj, const float *tc,
                                                               int32_t *io, int32_t *jo, float *co, unsigned long long *sign_sums,
@@ -744,7 +745,6 @@ __global__ __launch_bounds__(kJoinThreads) void k_join_digits(const uint32_t *st
         if (tid == 0) {
             mail_put(mail + 1, (uint64_t)(at + n));
             mail_put(mail + 2, (uint64_t)*oversize);
-            mail_put(mail + 3, (uint64_t)starts[gridDim.x]);
         }
         mail_send_wave(mail, seq);
     }
@@ -1261,7 +1261,10 @@ static rama_status matching(Ctx &ctx, const Graph &g, float tau, int rounds_cap,
         const uint64_t seq = ++ctx.mail_seq;
         const volatile uint64_t *mail = mail_words(ctx);
         if (!finish) {
-            k_look_at_lists<<<1, 64, 0, ctx.stream>>>(counts(r - 1), mailbox(ctx), seq);
+            {
+                ProfScope ps_(ctx, "k_look_at_lists", (double)(kLists * 8));
+                k_look_at_lists<<<1, 64, 0, ctx.stream>>>(counts(r - 1), mailbox(ctx), seq);
+            }
             LAUNCH_TRY(ctx, "look_at_lists");
             RAMA_TRY(wait_mail(ctx, seq));
             const uint64_t lengths = mail[1];
@@ -1523,7 +1526,7 @@ static rama_status contract_by_digits(Ctx &ctx, const Graph &g, const int32_t *f
     RAMA_TRY(zeroed<uint32_t>(ctx, 2, words));
     RAMA_TRY(out.sign_sums.alloc(ctx, tiles));
     {
-        ProfScope ps_(ctx, "k_rs_hist<relabelled>", (double)(m * 24));      // the count of the sort's one pass as well
+        ProfScope ps_(ctx, "k_rs_hist<relabelled>", (double)(m * 24));      // makes the keys and counts for the sort's one pass
         auto relabel = [&](auto kernel) {
             kernel<<<tiles, kBlock, 0, ctx.stream>>>(m, g.i.get(), g.j.get(), fmap, raw.get(), words.get(), (uint32_t *)nullptr, out.sign_sums.get(),
                                                      hist.get(), nb, nbits - top_bits, top_bits, g.c.get(), diag);
@@ -1539,11 +1542,12 @@ static rama_status contract_by_digits(Ctx &ctx, const Graph &g, const int32_t *f
     else
         RAMA_TRY((radix_pass<uint64_t, uint32_t, true, kMediumThreads, kMediumTile / kMediumThreads>(ctx, (const uint64_t *)nullptr, (const uint32_t *)nullptr, source, key.get(), val.get(),
                                                                                                     m, low_bits, top_bits, hist.get(), starts.get(), true)));
-    // the relabelled edges are no longer needed: the digits' edges take their place
+    // the relabelled edges are no longer needed: the digits' edges take their place.  The timers book k_sum_digit, its sort
+    // included, with the other kernel that adds up runs.
     int32_t *ti = reinterpret_cast<int32_t *>(raw.get()), *tj = ti + m;
     float *tc = reinterpret_cast<float *>(val2.get());
     {
-        ProfScope ps_(ctx, "k_reduce_runs", (double)(m * 24));      // the timers keep one name for the kernels that add up runs
+        ProfScope ps_(ctx, "k_reduce_runs", (double)(m * 24));
         k_sum_digit<<<digits, LocalSort<uint32_t>::threads, 0, ctx.stream>>>(key.get(), val.get(), starts.get(), nbits, low_bits, words.get(), counts.get(),
                                                                           words.get() + 1, ti, tj, tc);
     }

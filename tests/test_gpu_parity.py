@@ -125,8 +125,6 @@ def test_hashed_search_at_its_limits(rama, oracle32, isolated, d_a, d_b, row, lm
         assert np.array_equal(np_(got[L]), want[L]), (L + 3, got[L].shape, want[L].shape)
 
 
-# repulsive edges without room in the tables: 4096 and more of those with up to 8 attractive neighbours at their first
-# endpoint are walked by a thread each, fewer of them and those with more neighbours there by a wave each
 # common neighbours of a repulsive edge around the sixteen there is room for between counting and writing
 @pytest.mark.parametrize("pages", [0, 1, 15, 16, 17, 31, 32, 33, 200])
 def test_common_neighbours_with_and_without_room(rama, oracle32, pages):
@@ -143,8 +141,10 @@ def test_common_neighbours_with_and_without_room(rama, oracle32, pages):
     c = np.concatenate(c).astype(np.float32)
     want = oracle32.find_conflicted_cycles(n, i, j, c, 3)
     rama.set_cycle_search(2)
-    got = rama.find_conflicted_cycles(n, i, j, c, 3)
-    rama.set_cycle_search(0)
+    try:
+        got = rama.find_conflicted_cycles(n, i, j, c, 3)
+    finally:
+        rama.set_cycle_search(0)
     assert np.array_equal(np_(got[0]), want[0]) and want[0].shape[0] == sum(sizes)
 
 
@@ -161,6 +161,8 @@ def test_hashed_search_takes_items_in_batches(rama, oracle32, isolated, d_a, d_b
             assert np.array_equal(np_(g), w)
 
 
+# repulsive edges without room in the tables: 4096 and more of those with up to 8 attractive neighbours at their first
+# endpoint are walked by a thread each, fewer of them and those with more neighbours there by a wave each
 @pytest.mark.parametrize("n_edges,row", [(4095, 8), (4096, 8), (4097, 1), (4500, 9), (9000, 4)])
 @pytest.mark.parametrize("lmax,shortest", [(4, False), (5, False), (5, True)])
 def test_edges_without_room_in_the_tables(rama, oracle32, n_edges, row, lmax, shortest):
@@ -837,9 +839,9 @@ def test_last_workgroup_of_a_matching(rama, oracle32, n, m, kind, cap):
         assert np.array_equal(np_(got[k]), want[k]), k
 
 
-# Contraction with a workgroup to a digit: lists on both sides of the tiles (1024 edges up to 196608, 2048 beyond) and of the
-# lines where it begins (8192 edges) and ends (2^21); parallel edges that fill buckets of the in-LDS sort, rows far apart and
-# close together (the bits of hi - lo), digits without an edge, nothing left at all
+# Contraction with a workgroup to a digit: lists on both sides of the tiles (1024 edges up to 196608, 2048 beyond); parallel
+# edges that fill buckets of the in-LDS sort, rows far apart and close together (the bits of hi - lo), digits without an edge,
+# and lists that are too long for it, on both sides of 2^21 edges (its own lines: test_lines_of_contraction_by_digits)
 @pytest.mark.parametrize("n,m,near", [(3000, 8193, 0), (3000, 9217, 5), (200, 19000, 0), (150, 8300, 0), (70000, 196608, 4), (70000, 196609, 4),
                                       (5000, 197633, 0), (1000000, 300000, 2), (1048577, 300000, 0), (600, 170000, 0), (40000, 2097151, 0), (40000, 2097153, 0)])
 @pytest.mark.parametrize("ratio", [0.0, 1.0], ids=["matching", "forest"])
@@ -863,6 +865,74 @@ def test_contraction_by_digits(rama, oracle32, n, m, near, ratio):
     assert np.array_equal(np_(got["diag"]), want["diag"][: got["n_nodes"]])
 
 
+def pairs_and_more(n_new, m, pairs, seed):
+    """m edges of n_new + pairs nodes, between nodes that are close, of which only those of `pairs` pairs of neighbours attract:
+    what a matching and a forest contract.  Half of the others come in twos that are parallel behind it."""
+    rng = np.random.default_rng(seed)
+    n = n_new + pairs
+    first = np.arange(pairs, dtype=np.int64) * (n - 1) // pairs
+    p, x = rng.choice(first, m), rng.integers(0, n, 2 * m)
+    twos, near = p + rng.integers(2, 800, m), x + rng.integers(1, 800, x.size)
+    key = np.stack([p * n + twos, (p + 1) * n + twos], axis=1)[twos < n][: m // 4].ravel()
+    inner = first * n + first + 1
+    key = np.concatenate([key, (x * n + near)[near < n]])
+    key = key[np.sort(np.unique(key, return_index=True)[1])]       # the twos first
+    key = key[~np.isin(key, inner)][:m - pairs]
+    assert key.size == m - pairs
+    c = np.concatenate([1 + rng.random(pairs), -(rng.integers(1, 9, key.size) / 8)])
+    key = np.concatenate([inner, key])
+    order = np.argsort(key)
+    key, c = key[order], c[order]
+    return n, (key // n).astype(np.int32), (key % n).astype(np.int32), c.astype(np.float32)
+
+
+# Both sides of the lines of contraction by digits, which comes for lists of more than 8192 edges if the bits of a new node's
+# number and those of a row that are left behind at most eight bits of a digit fit 32, and a digit has at most 4096 edges on average:
+# 2^20 edges where the nodes use 256 digits up, 528384 where they are just enough for one bit more and use 129
+@pytest.mark.parametrize("n_new,m,digits", [(6900, 8192, False), (6900, 8193, True), (65536, 1 << 20, True), (65536, (1 << 20) + 1, False),
+                                            (32769, 528384, True), (32769, 528385, False), (1 << 20, 300000, True), ((1 << 20) + 1, 300000, False)])
+@pytest.mark.parametrize("ratio", [0.0, 1.0], ids=["matching", "forest"])
+def test_lines_of_contraction_by_digits(rama, oracle32, n_new, m, digits, ratio):
+    from paper_2109_01838_amd import default_params
+    n, i, j, c = pairs_and_more(n_new, m, 2000, m)
+    want = oracle32.contract(n, i, j, c, repeat=1, forest_ratio=ratio)
+    rama.profile_enable(True)
+    got = rama.contract(n, i, j, c, params=default_params(forest_ratio=ratio), repeat=1)
+    names = {k["name"] for k in rama.profile_get()}
+    rama.profile_enable(False)
+    assert ("k_join_digits" in names) == digits and ("k_relabel_keys" in names) == (not digits)
+    assert got["n_nodes"] == want["n_nodes"] == n_new and np.array_equal(np_(got["mapping"]), want["mapping"])
+    assert want["i"].size < m - 2000
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+    assert np.array_equal(np_(got["diag"]), want["diag"][:n_new])
+
+
+@pytest.mark.parametrize("leaves,fits", [(8000, True), (8192, True), (8193, False), (12000, False)])
+def test_matching_that_crowds_a_digit(rama, oracle32, leaves, fits):
+    """One row with all that a workgroup sorts in LDS, or more, behind a matching: the contraction by digits gives up, the edges
+    are relabelled once more, and the diagonal is written twice."""
+    from paper_2109_01838_amd import default_params
+    n, i, j, c = pairs_and_more(60000, 70000, 2000, leaves)
+    keep = (i >= 1100) | (c > 0)                           # the digit of the first 1024 new nodes is the hub's alone
+    hub, leaf = 0, 4000 + np.arange(leaves)                # it is contracted with 1
+    i, j = np.concatenate([i[keep], np.full(leaves, hub)]), np.concatenate([j[keep], leaf])
+    c = np.concatenate([c[keep], -1 - np.arange(leaves) / leaves])
+    order = np.lexsort((j, i))
+    i, j, c = i[order].astype(np.int32), j[order].astype(np.int32), c[order].astype(np.float32)
+    want = oracle32.contract(n, i, j, c, repeat=1, forest_ratio=0.0)
+    assert 0 <= leaves - np.bincount(want["i"])[:1024].sum() < leaves // 10
+    rama.profile_enable(True)
+    got = rama.contract(n, i, j, c, params=default_params(forest_ratio=0.0), repeat=1)
+    names = {k["name"] for k in rama.profile_get()}
+    rama.profile_enable(False)
+    assert "k_join_digits" in names and ("k_relabel_keys" in names) == (not fits)
+    assert got["n_nodes"] == want["n_nodes"] == 60000 and np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
+    assert np.array_equal(np_(got["diag"]), want["diag"][:60000]) and np.count_nonzero(want["diag"]) == 2000
+
+
 def test_contraction_leaves_nothing(rama, oracle32):
     """A clique whose edges all attract, as a forest: one node is left, and no edge."""
     from paper_2109_01838_amd import default_params
@@ -873,7 +943,7 @@ def test_contraction_leaves_nothing(rama, oracle32):
     assert got["n_nodes"] == 1 and got["i"].numel() == 0 and not np_(got["mapping"]).any()
 
 
-# Both sides of the lines up to which the matching's last workgroup numbers the nodes (2^15 nodes; 8192 at a time) and nobody
+# Both sides of the lines up to which the matching's last workgroup numbers the nodes (2^15 nodes) and nobody
 # waits for the number of candidates or of kept edges (2^20 edges, all different: parallel ones are added up before); every
 # edge a candidate, none, and too many candidates left for the last workgroup behind the rounds that should bring them there (a star keeps all of them)
 @pytest.mark.parametrize("n,m,pos", [(32768, 60000, 0.8), (32769, 60000, 0.8), (8193, 40000, 0.5), (20000, 1 << 20, 0.6), (20000, (1 << 20) + 1, 0.6),
@@ -944,8 +1014,7 @@ def test_solve_rounds_in_one_workgroup(rama, oracle32, n, m, pos, later, iters, 
     assert len(rounds) == got["rounds"] and rounds[-1]["n_edges_aug"] >= got["n_edges_final"]
 
 
-# rounds in one workgroup that fill its buckets and runs: a repulsive edge in `pages` triangles (up to 48 slots of an edge are put
-# into order by comparing, more by sorts), a node in `leaves` edges (a bucket of up to 160 keys is)
+# one-workgroup rounds without triangles that contract a book of `pages` pages and a star of up to `leaves` leaves
 @pytest.mark.parametrize("pages,leaves", [(47, 10), (48, 159), (49, 161), (50, 400), (200, 1000), (600, 5000), (3, 6000)])
 def test_long_rows_and_runs_in_one_workgroup(rama, oracle32, pages, leaves):
     from paper_2109_01838_amd import default_params
@@ -962,6 +1031,66 @@ def test_long_rows_and_runs_in_one_workgroup(rama, oracle32, pages, leaves):
         want = oracle32.solve(int(spare + 2), i, j, c, **kw)
         got = rama.solve(int(spare + 2), i, j, c, params=default_params(**kw))
         assert np.array_equal(np_(got["labels"]), want["labels"]) and got["rounds"] == want["rounds"]
+
+
+# One-workgroup rounds whose messages go by comparing (an edge of up to 48 slots) and by sorts (more): a repulsive edge in `pages`
+# triangles, whose other edges are in one to three.  The first round contracts every node with one of its own, so that the second
+# one, the first in one workgroup, has the book as it is.  What is contracted then, and when, depends on the messages.
+@pytest.mark.parametrize("pages", [3, 47, 48, 49, 50, 200, 680])
+def test_messages_of_long_runs_in_one_workgroup(rama, oracle32, pages):
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(pages)
+    page, nodes = 2 + np.arange(pages), np.arange(2 + pages)
+    i = np.concatenate([[0], np.zeros(pages), np.ones(pages), page[:-1], nodes]).astype(np.int32)
+    j = np.concatenate([[1], page, page, page[1:], nodes.size + nodes]).astype(np.int32)
+    c = np.concatenate([[-0.4 * pages], 1 + rng.random(2 * pages), -0.2 - rng.random(pages - 1), 100 + rng.random(nodes.size)]).astype(np.float32)
+    n = 2 * nodes.size
+    second = oracle32.contract(n, i, j, c, repeat=1, rounds_cap=1, forest_ratio=0.0)
+    tri = oracle32.find_conflicted_cycles(second["n_nodes"], second["i"], second["j"], second["c"], 3)[0]
+    sides = np.sort(np.concatenate([tri[:, :2], tri[:, 1:], tri[:, ::2]]), axis=1)
+    slots = np.unique(sides[:, 0] * nodes.size + sides[:, 1], return_counts=True)[1]
+    assert slots.max() == pages and tri.shape[0] == 3 * pages - 2 <= 2048
+    kw = dict(max_cycle_len_first=0, mp_iters_first=0, max_cycle_len_later=3, matching_rounds_cap=1, forest_ratio=0.0)
+    want, without = (oracle32.solve(n, i, j, c, mp_iters_later=k, **kw) for k in (4, 0))
+    assert pages == 3 or not np.array_equal(want["labels"], without["labels"])
+    rama.profile_enable(True)
+    got = rama.solve(n, i, j, c, params=default_params(mp_iters_later=4, **kw))
+    names = {k["name"] for k in rama.profile_get()}
+    rama.profile_enable(False)
+    rounds = rama.round_stats()
+    assert "k_tail_rounds" in names and rounds[1]["n_edges"] == second["i"].size and rounds[1]["n_triangles"] == tri.shape[0]
+    assert np.array_equal(np_(got["labels"]), want["labels"]) and got["rounds"] == want["rounds"]
+    assert got["n_edges_final"] == want["n_edges_final"] and rel_close(got["primal"], want["primal"], 1e-9)
+
+
+# Contraction in one workgroup on both sides of the 160 keys that a bucket of its sort may hold: with 2049 to 4096 nodes left a
+# bucket is a row, and the longest row is the hub's, `twice` of whose edges are parallel to another one
+@pytest.mark.parametrize("row,twice", [(159, 0), (160, 0), (160, 60), (161, 0), (161, 61), (2500, 300)])
+@pytest.mark.parametrize("n_new", [2049, 4096])
+def test_rows_that_fill_a_bucket_in_one_workgroup(rama, oracle32, row, twice, n_new):
+    from paper_2109_01838_amd import default_params
+    rng = np.random.default_rng(row + n_new)
+    row = min(row, n_new - 400)
+    pairs = 400 + twice                    # nodes 2k + 1 and 2k + 2, k < pairs
+    n = n_new + pairs
+    assert n <= 6144
+    leaf = np.concatenate([1 + 2 * np.arange(twice), 2 + 2 * np.arange(twice), 2 * pairs + 1 + rng.permutation(n - 2 * pairs - 1)[:row - 2 * twice]])
+    inner, far = 1 + 2 * np.arange(pairs), rng.integers(1, n, (2000, 2))
+    i, j = np.concatenate([inner, np.zeros(leaf.size, np.int64), far[:, 0]]), np.concatenate([inner + 1, leaf, far[:, 1]])
+    i, j = np.minimum(i, j), np.maximum(i, j)
+    c = np.concatenate([1 + rng.random(pairs), -0.1 - rng.random(i.size - pairs)]).astype(np.float32)
+    first = np.unique(i.astype(np.int64) * n + j, return_index=True)[1]
+    first = first[i[first] != j[first]]
+    i, j, c = i[first].astype(np.int32), j[first].astype(np.int32), c[first]
+    want = oracle32.contract(n, i, j, c, repeat=1, forest_ratio=0.0)
+    assert want["n_nodes"] == n_new and i.size <= 8192
+    a, b = want["mapping"][i], want["mapping"][j]
+    rows = np.bincount(np.minimum(a, b)[a != b])
+    assert rows[0] == rows.max() == row and want["i"].size <= np.count_nonzero(a != b) - twice
+    got = rama.contract(n, i, j, c, params=default_params(forest_ratio=0.0), repeat=1)
+    assert np.array_equal(np_(got["mapping"]), want["mapping"])
+    for k in ("i", "j", "c"):
+        assert np.array_equal(np_(got[k]), want[k]), k
 
 
 @pytest.mark.parametrize("n,m,pos", [(200, 8100, 0.7), (700, 8100, 0.8)])
